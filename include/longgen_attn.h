@@ -117,8 +117,8 @@ int lg_sparse_attn_fwd(const void* q, const void* k, const void* v, void* out, f
  *   dq_i = scale * sum_j dS_ij k_j;   dk_j = scale * sum_i dS_ij q_i;   dv_j = sum_i P_ij dout_i
  * (sums over live pairs only; dk/dv also summed over the query heads of a kv head).
  * workspace holds per-row values (float32 [B,Hq,N]: Delta on the float32 path; -Delta and
- * -lse / scale on the bf16 path), any float32 partial sums and, on the bf16 path, the counters
- * of the kernels' work queues (cleared by every call).  A workspace belongs to one call at a
+ * -lse / scale on the bf16 path), any float32 partial sums and the kernels' counters (cleared by
+ * every call).  A workspace belongs to one call at a
  * time: two calls that may overlap (different streams) need a workspace each.  It must be ordinary device memory (hipMalloc /
  * PyTorch): with a strided pattern or Hq > Hkv the bf16 path adds partial dk/dv sums of sink
  * and strided-column keys into it with hardware float atomics; their order is not fixed, so
@@ -138,8 +138,8 @@ int lg_sparse_attn_bwd(const void* q, const void* k, const void* v, const void* 
  * Measurement aid (benchmarks only): lg_sparse_attn_bwd with each of its three kernels
  * bracketed by HIP events on hip_stream.  Synchronises the stream and writes the kernel
  * durations in milliseconds to the HOST array kernel_ms[3] = {set-up, dq, dk/dv}:
- *   set-up  float32 path: the Delta pre-pass kernel; bf16 path: the kernel that clears the work-queue
- *           counters (a few microseconds: on that path Delta is formed inside the dq kernel)
+ *   set-up  bf16 path: the kernel that clears the work-queue counters (a few microseconds); float32
+ *           path: nothing (on both paths Delta is formed inside the dq kernel)
  *   dq      the dq kernel
  *   dk/dv   the dk/dv kernel and, for strided patterns and GQA, what precedes it: the column-table
  *           kernel, the clearing of the partial sums and the column instance

@@ -1,281 +1,579 @@
-// lg_bwd_f32.hip — float32 backward (paper Section 3.2: masked key blocks are skipped
-// in the backward step as well), plus the Delta pre-pass shared with the bf16 path.
+// lg_bwd_f32.hip — float32 backward (paper Section 3.2: masked key blocks are skipped in the backward step as
+// well).
 //
 //   Delta_i = <dout_i, out_i>
 //   P_ij = exp(scale <q_i,k_j> - lse_i),  dP_ij = <dout_i, v_j>,  dS_ij = P_ij (dP_ij - Delta_i)
-//   dq_i = scale sum_j dS_ij k_j        (query-tile major, same tile walk as the forward)
-//   dk_j = scale sum_i dS_ij q_i,  dv_j = sum_i P_ij dout_i   (key-tile major over the
-//          contiguous range of live query tiles, summed over the query heads of the group)
-// Precision path for float32 data: plain FMA, no matrix cores.  4 lanes share a row
-// (query row in the dq kernel, key row in the dk/dv kernel), each owning D/4 dims.
-#include <hip/hip_bf16.h>
-
+//   dq_i = scale sum_j dS_ij k_j        (query-tile major, same tile walk as the forward; forms Delta too)
+//   dk_j = scale sum_i dS_ij q_i,  dv_j = sum_i P_ij dout_i   (key-tile major, summed over the query heads of
+//          the group)
+// Precision path for float32 data: every product on the float32 matrix instruction (lg_f32.h).  Both kernels use
+// 8 waves per 64 x 64 tile: 4 groups of 16 rows (keys) x 2 halves of the tile's other axis, summed through LDS at
+// the end, so that two waves share a SIMD.
+//
+// The dk/dv work of a key tile is cut into parts: its window part (nsp equal runs of (head, query tile) steps,
+// more than one only where key tiles x kv heads would leave CUs idle) and, for keys that every later query sees
+// (sink, strided columns), its column part.  As one workgroup per key tile the sink tile of a 1024-token sequence
+// with two query heads per kv head ran 32 steps where every other ran 6 and took 0.9 ms of a 1.1 ms pass.  Each
+// part of a tile with several leaves float32 partial sums in the workspace; the workgroup that finishes last adds
+// them in a fixed order, so the results stay bit-reproducible.
 #include "../../include/longgen_attn.h"
+#include "lg_f32.h"
 #include "lg_kernels.h"
 
 namespace {
 
-constexpr int SUB = 8;
+constexpr float LOG2E = 1.44269504088896340736f;
+constexpr int NT = 512;
+using I0 = std::integral_constant<int, 0>;
+using I1 = std::integral_constant<int, 1>;
+using I2 = std::integral_constant<int, 2>;
+static_assert(LG_F32_TQ == 64 && LG_F32_TK == 64 && LG_F32_BTQ == 64 && LG_F32_BTK == 64, "64 x 64 tiles");
 
-__device__ __forceinline__ float quad_sum(float a) {
-  a += __shfl_xor(a, 1);
-  a += __shfl_xor(a, 2);
-  return a;
-}
-
-// ---------------------------------------------------------------- Delta pre-pass
-__device__ __forceinline__ float dot16(const float* a, const float* b) {
-  const float4 x = *reinterpret_cast<const float4*>(a), y = *reinterpret_cast<const float4*>(b);
-  return x.x * y.x + x.y * y.y + x.z * y.z + x.w * y.w;
-}
-__device__ __forceinline__ float dot16(const __hip_bfloat16* a, const __hip_bfloat16* b) {
-  const uint4 x = *reinterpret_cast<const uint4*>(a), y = *reinterpret_cast<const uint4*>(b);
-  const unsigned xw[4] = {x.x, x.y, x.z, x.w}, yw[4] = {y.x, y.y, y.z, y.w};
-  float s = 0.f;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    s = fmaf(__uint_as_float(xw[t] << 16), __uint_as_float(yw[t] << 16), s);
-    s = fmaf(__uint_as_float(xw[t] & 0xffff0000u), __uint_as_float(yw[t] & 0xffff0000u), s);
-  }
-  return s;
-}
-
-// One row per LPR = D*sizeof(T)/16 lanes; rows = B*Hq*N.  delta = dsign * <dout, out>;
-// lse2 (optional) = lse * lscale.  delta and lse2 are dense [B*Hq, N]; in dout, out and lse one head
-// follows the other after ld rows.
-template <typename T, int D>
-__global__ __launch_bounds__(256) void delta_kernel(const T* __restrict__ dout, const T* __restrict__ out,
-                                                    float* __restrict__ delta, const float* __restrict__ lse,
-                                                    float* __restrict__ lse2, float dsign, float lscale,
-                                                    long long rows, int N, int ld) {
-  constexpr int E = 16 / sizeof(T);
-  constexpr int LPR = D / E;
-  const long long row = (long long)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
-  const int c = threadIdx.x % LPR;
-  long long rr = row < rows ? row : rows - 1;
-  if (ld != N) rr = (rr / N) * ld + rr % N;
-  float s = dot16(dout + rr * D + c * E, out + rr * D + c * E);
-#pragma unroll
-  for (int x = 1; x < LPR; x <<= 1) s += __shfl_xor(s, x);
-  if (c == 0 && row < rows) {
-    delta[row] = dsign * s;
-    if (lse2) lse2[row] = lse[rr] * lscale;
-  }
-}
-
-// ---------------------------------------------------------------- dq
+// ------------------------------------------------------------------------- dq
+// Also forms Delta for the dk/dv kernel and clears its arrival counters.
 template <int D>
-__global__ __launch_bounds__(256) void dq_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
-                                                     const float* __restrict__ v, const float* __restrict__ dout,
-                                                     const float* __restrict__ lse,
-                                                     const float* __restrict__ delta, float* __restrict__ dq,
-                                                     int Hq, int Hkv, float scale, LgMask m) {
-  constexpr int TQ = LG_F32_TQ, TK = LG_F32_TK, DS = D / 4;
-  __shared__ float sK[TK * D];
-  __shared__ float sV[TK * D];
-  const int N = m.N;
-  const int tid = threadIdx.x, r = tid >> 2, c = tid & 3;
-  const int qt = blockIdx.x, hq = blockIdx.y, b = blockIdx.z;
-  const int hk = hq / (Hq / Hkv);
-  const int q0 = qt * TQ, q1 = min(q0 + TQ - 1, N - 1);
-  const int i = q0 + r, iq = min(i, N - 1);
-  const size_t qbase = ((size_t)(b * Hq + hq) * m.ld) * D;
-  const size_t kbase = ((size_t)(b * Hkv + hk) * m.ld) * D;
-  const size_t rbase = (size_t)(b * Hq + hq) * N;     // Delta (workspace, dense)
-  const size_t lbase = (size_t)(b * Hq + hq) * m.ld;  // lse (caller's)
+__global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void dq_f32_kernel(
+    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
+    const float* __restrict__ out, const float* __restrict__ dout, const float* __restrict__ lse,
+    float* __restrict__ delta, float* __restrict__ dq, int Hq, int Hkv, float scale, LgMask m, int nqt, int total,
+    int per_xcd, unsigned* __restrict__ arrived, int ncounters) {
+  using T = LgF32Tile<D>;
+  using Dma = LgTileDma<T, NT>;
+  constexpr int TQ = LG_F32_TQ, TK = LG_F32_TK, DC = D / 16;
+  constexpr int STAGE = 2 * T::BYTES, LPT = 2 * Dma::CH;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * STAGE];
 
-  float qr[DS], gr[DS], acc[DS];
-#pragma unroll
-  for (int d = 0; d < DS; ++d) {
-    qr[d] = q[qbase + (size_t)iq * D + c * DS + d];
-    gr[d] = dout[qbase + (size_t)iq * D + c * DS + d];
-    acc[d] = 0.f;
-  }
-  const float li = lse[lbase + iq], di = delta[rbase + iq];
-
-  const LgQSched qs = lg_qsched_init(m, q0, q1);
-  for (int t = lg_qsched_next(m, qs, -1); t >= 0; t = lg_qsched_next(m, qs, t)) {
-    const int k0 = t * TK;
-    const bool full = lg_qsched_full(m, qs, t);
-    __syncthreads();
-    for (int e = tid * 4; e < TK * D; e += 256 * 4) {
-      const int row = e / D, col = e % D;
-      const int j = min(k0 + row, N - 1);
-      *reinterpret_cast<float4*>(&sK[e]) = *reinterpret_cast<const float4*>(&k[kbase + (size_t)j * D + col]);
-      *reinterpret_cast<float4*>(&sV[e]) = *reinterpret_cast<const float4*>(&v[kbase + (size_t)j * D + col]);
-    }
-    __syncthreads();
-#pragma unroll 1
-    for (int c0 = 0; c0 < TK; c0 += SUB) {
-#pragma unroll
-      for (int jj = 0; jj < SUB; ++jj) {
-        const float* kr = &sK[(c0 + jj) * D + c * DS];
-        const float* vr = &sV[(c0 + jj) * D + c * DS];
-        float s = 0.f, dp = 0.f;
-#pragma unroll
-        for (int d = 0; d < DS; ++d) {
-          s = fmaf(qr[d], kr[d], s);
-          dp = fmaf(gr[d], vr[d], dp);
-        }
-        s = quad_sum(s) * scale;
-        dp = quad_sum(dp);
-        const bool ok = full || lg_live(m, i, k0 + c0 + jj);
-        const float p = ok ? expf(s - li) : 0.f;
-        const float ds = p * (dp - di);
-#pragma unroll
-        for (int d = 0; d < DS; ++d) acc[d] = fmaf(ds, kr[d], acc[d]);
-      }
-    }
-  }
-  if (i < N) {
-#pragma unroll
-    for (int d = 0; d < DS; ++d) dq[qbase + (size_t)i * D + c * DS + d] = acc[d] * scale;
-  }
-}
-
-// ---------------------------------------------------------------- dk, dv
-template <int D>
-__global__ __launch_bounds__(256) void dkdv_f32_kernel(const float* __restrict__ q, const float* __restrict__ k,
-                                                       const float* __restrict__ v,
-                                                       const float* __restrict__ dout,
-                                                       const float* __restrict__ lse,
-                                                       const float* __restrict__ delta, float* __restrict__ dk,
-                                                       float* __restrict__ dv, int Hq, int Hkv, float scale,
-                                                       LgMask m) {
-  constexpr int TQ = LG_F32_BTQ, TK = LG_F32_BTK, DS = D / 4;
-  __shared__ float sQ[TQ * D];
-  __shared__ float sG[TQ * D];
-  __shared__ float sL[TQ], sD[TQ];
-  const int N = m.N;
-  const int tid = threadIdx.x, r = tid >> 2, c = tid & 3;
-  const int kt = blockIdx.x, hk = blockIdx.y, b = blockIdx.z;
+  const int tid = threadIdx.x;
+  for (long long x = (long long)blockIdx.x * NT + tid; x < ncounters; x += (long long)gridDim.x * NT) arrived[x] = 0u;
+  const int L = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (L >= total) return;
   const int G = Hq / Hkv;
-  const int k0 = kt * TK, k1 = min(k0 + TK - 1, N - 1);
-  const int j = k0 + r, jk = min(j, N - 1);
-  const size_t kbase = ((size_t)(b * Hkv + hk) * m.ld) * D;
+  const int gq = L % G, rest = L / G;
+  const int qt = nqt - 1 - rest % nqt, bhk = rest / nqt;
+  const int b = bhk / Hkv, hk = bhk % Hkv, hq = hk * G + gq;
+  const int N = m.N;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, h = lane >> 4;
+  const int rg = wave & 3, kh = wave >> 2;
+  const int q0 = qt * TQ, q1 = min(q0 + TQ - 1, N - 1);
+  const int qw0 = min(q0 + 16 * rg, N - 1), qw1 = min(q0 + 16 * rg + 15, N - 1);
+  const int i = q0 + 16 * rg + n, iq = min(i, N - 1);
+  const size_t qbase = (size_t)(b * Hq + hq) * m.ld * D;
+  const size_t kbase = (size_t)(b * Hkv + hk) * m.ld * D;
+  const float c2 = scale * LOG2E;
 
-  float kr[DS], vr[DS], ak[DS], av[DS];
+  float4 qf[DC], gf[DC];
+  // Delta as the diagonal of out dO^T, in the order in which dP is summed: where out_i is v_j (a row with one live
+  // key) dP - Delta is then exactly zero, as it should be
+  f32x4_t dl = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int d = 0; d < DS; ++d) {
-    kr[d] = k[kbase + (size_t)jk * D + c * DS + d];
-    vr[d] = v[kbase + (size_t)jk * D + c * DS + d];
-    ak[d] = av[d] = 0.f;
+  for (int c = 0; c < DC; ++c) {
+    const size_t at = qbase + (size_t)iq * D + 16 * c + 4 * h;
+    qf[c] = *reinterpret_cast<const float4*>(q + at);
+    gf[c] = *reinterpret_cast<const float4*>(dout + at);
+    const float4 ov = *reinterpret_cast<const float4*>(out + at);
+    dl = lg_mfma16(ov.x, gf[c].x, dl);
+    dl = lg_mfma16(ov.y, gf[c].y, dl);
+    dl = lg_mfma16(ov.z, gf[c].z, dl);
+    dl = lg_mfma16(ov.w, gf[c].w, dl);
   }
-  int lo, hi;
-  lg_qtile_range(m, k0, k1, TQ, &lo, &hi);
+  // row n of column n is register n % 4 of lane (n, h = n / 4)
+  float di = __shfl((n & 2) ? ((n & 1) ? dl[3] : dl[2]) : ((n & 1) ? dl[1] : dl[0]), 16 * (n >> 2) + n);
+  float lse2 = lse[(size_t)(b * Hq + hq) * m.ld + iq] * LOG2E;
+  if (kh == 0 && h == 0 && i < N) delta[(size_t)(b * Hq + hq) * N + i] = di;
+  asm volatile("" : "+v"(lse2), "+v"(di));  // everything loaded so far is waited for here, not in the tile loop
+#pragma unroll
+  for (int c = 0; c < DC; ++c) asm volatile("" ::"v"(qf[c].x));
 
-  for (int gq = 0; gq < G; ++gq) {
-    const int hq = hk * G + gq;
-    const size_t qbase = ((size_t)(b * Hq + hq) * m.ld) * D;
-    const size_t rbase = (size_t)(b * Hq + hq) * N;     // Delta (workspace, dense)
-    const size_t lbase = (size_t)(b * Hq + hq) * m.ld;  // lse (caller's)
-    for (int u = lo; u <= hi; ++u) {
-      const int q0 = u * TQ, q1 = min(q0 + TQ - 1, N - 1);
-      const bool full = lg_tile_kind(m, q0, q1, k0, k0 + TK - 1) == LG_TILE_FULL && q0 + TQ <= N;
-      __syncthreads();
-      for (int e = tid * 4; e < TQ * D; e += 256 * 4) {
-        const int row = e / D, col = e % D;
-        const int i = min(q0 + row, N - 1);
-        *reinterpret_cast<float4*>(&sQ[e]) = *reinterpret_cast<const float4*>(&q[qbase + (size_t)i * D + col]);
-        *reinterpret_cast<float4*>(&sG[e]) = *reinterpret_cast<const float4*>(&dout[qbase + (size_t)i * D + col]);
-      }
-      if (tid < TQ) {
-        const int i = min(q0 + tid, N - 1);
-        sL[tid] = lse[lbase + i];
-        sD[tid] = delta[rbase + i];
-      }
-      __syncthreads();
-#pragma unroll 1
-      for (int c0 = 0; c0 < TQ; c0 += SUB) {
+  f32x4_t acc[DC];
 #pragma unroll
-        for (int ii = 0; ii < SUB; ++ii) {
-          const float* qr = &sQ[(c0 + ii) * D + c * DS];
-          const float* gr = &sG[(c0 + ii) * D + c * DS];
-          float s = 0.f, dp = 0.f;
+  for (int db = 0; db < DC; ++db) acc[db] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  Dma dma;
+  dma.init(tid);
+  LgF32Reader<D> rd;
+  rd.init(n, h);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)LG_LDS_PTR(unsigned char, smem);
+  auto issue = [&](int t, int stage) {
+    dma.issue(k + kbase + (size_t)t * TK * D, N - t * TK, lds0 + stage * STAGE);
+    dma.issue(v + kbase + (size_t)t * TK * D, N - t * TK, lds0 + stage * STAGE + T::BYTES);
+  };
+  const LgQSched qs = lg_qsched_init(m, q0, q1);
+  int t = lg_qsched_next(m, qs, -1);
+  issue(t, 0);
+  int tn = lg_qsched_next(m, qs, t);
+  if (tn >= 0) issue(tn, 1);
+  for (int stage = 0; t >= 0; stage ^= 1) {
+    if (tn >= 0) LG_WAIT_VMCNT(LPT);
+    else LG_WAIT_VMCNT(0);
+    __syncthreads();
+    const int sk = stage * STAGE, sv = sk + T::BYTES;
+    const int rb0 = 2 * kh, kk = t * TK + 32 * kh;
+    int kind0 = LG_TILE_FULL, kind1 = LG_TILE_FULL;  // of the wave's two 16-key blocks
+    if (!lg_qsched_full(m, qs, t)) {
+      kind0 = lg_tile_kind(m, qw0, qw1, kk, kk + 15);
+      kind1 = lg_tile_kind(m, qw0, qw1, kk + 16, kk + 31);
+    }
+    const bool masked = kind0 == LG_TILE_PARTIAL || kind1 == LG_TILE_PARTIAL;
+    // as in the forward: units of matrix instructions, their LDS operands requested one unit ahead
+    auto run = [&](auto B0_, auto NB_) {
+      constexpr int B0 = decltype(B0_)::value, NB = decltype(NB_)::value;
+      f32x4_t s[NB], dp[NB];
+      float4 ka[2][NB], va[2][NB];
+      float kc[2][DC];
+      auto read_rows = [&](int c) {
 #pragma unroll
-          for (int d = 0; d < DS; ++d) {
-            s = fmaf(qr[d], kr[d], s);
-            dp = fmaf(gr[d], vr[d], dp);
-          }
-          s = quad_sum(s) * scale;
-          dp = quad_sum(dp);
-          const int i = q0 + c0 + ii;
-          const bool ok = full || (i < N && lg_live(m, i, j));
-          const float p = ok ? expf(s - sL[c0 + ii]) : 0.f;
-          const float ds = p * (dp - sD[c0 + ii]);
+        for (int x = 0; x < NB; ++x) {
+          ka[c & 1][x] = rd.row4(smem, sk, rb0 + B0 + x, c);
+          va[c & 1][x] = rd.row4(smem, sv, rb0 + B0 + x, c);
+        }
+      };
+      auto read_cols = [&](int u) {  // unit u = 4 x + r
 #pragma unroll
-          for (int d = 0; d < DS; ++d) {
-            ak[d] = fmaf(ds, qr[d], ak[d]);
-            av[d] = fmaf(p, gr[d], av[d]);
-          }
+        for (int db = 0; db < DC; ++db) kc[u & 1][db] = rd.col(smem, sk, rb0 + B0 + (u >> 2), u & 3, db);
+      };
+#pragma unroll
+      for (int x = 0; x < NB; ++x) s[x] = dp[x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      read_rows(0);
+#pragma unroll
+      for (int c = 0; c < DC; ++c) {
+        if (c + 1 < DC) read_rows(c + 1);
+        else read_cols(0);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
+          s[x] = lg_mfma16(ka[c & 1][x].x, qf[c].x, s[x]);
+          dp[x] = lg_mfma16(va[c & 1][x].x, gf[c].x, dp[x]);
+        }
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
+          s[x] = lg_mfma16(ka[c & 1][x].y, qf[c].y, s[x]);
+          dp[x] = lg_mfma16(va[c & 1][x].y, gf[c].y, dp[x]);
+        }
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
+          s[x] = lg_mfma16(ka[c & 1][x].z, qf[c].z, s[x]);
+          dp[x] = lg_mfma16(va[c & 1][x].z, gf[c].z, dp[x]);
+        }
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
+          s[x] = lg_mfma16(ka[c & 1][x].w, qf[c].w, s[x]);
+          dp[x] = lg_mfma16(va[c & 1][x].w, gf[c].w, dp[x]);
         }
       }
-    }
-  }
-  if (j < N) {
 #pragma unroll
-    for (int d = 0; d < DS; ++d) {
-      dk[kbase + (size_t)j * D + c * DS + d] = ak[d] * scale;
-      dv[kbase + (size_t)j * D + c * DS + d] = av[d];
-    }
+      for (int x = 0; x < NB; ++x)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          float p = __builtin_amdgcn_exp2f(fmaf(s[x][r], c2, -lse2));
+          if (masked && !lg_live(m, i, kk + 16 * (B0 + x) + 4 * h + r)) p = 0.f;
+          s[x][r] = p * (dp[x][r] - di);
+        }
+#pragma unroll
+      for (int u = 0; u < 4 * NB; ++u) {
+        if (u + 1 < 4 * NB) read_cols(u + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int db = 0; db < DC; ++db) acc[db] = lg_mfma16(kc[u & 1][db], s[u >> 2][u & 3], acc[db]);
+      }
+    };
+    if (kind0 != LG_TILE_DEAD && kind1 != LG_TILE_DEAD) run(I0{}, I2{});
+    else if (kind0 != LG_TILE_DEAD) run(I0{}, I1{});
+    else if (kind1 != LG_TILE_DEAD) run(I1{}, I1{});
+    __syncthreads();  // everyone is done with this stage
+    const int t2 = tn >= 0 ? lg_qsched_next(m, qs, tn) : -1;
+    if (t2 >= 0) issue(t2, stage);
+    t = tn;
+    tn = t2;
   }
+
+  float4* so = reinterpret_cast<float4*>(smem);  // add the two key halves
+  if (kh == 1)
+#pragma unroll
+    for (int db = 0; db < DC; ++db)
+      so[(rg * DC + db) * 64 + lane] = make_float4(acc[db][0], acc[db][1], acc[db][2], acc[db][3]);
+  __syncthreads();
+  if (kh == 0 && i < N)
+#pragma unroll
+    for (int db = 0; db < DC; ++db) {
+      const float4 x = so[(rg * DC + db) * 64 + lane];
+      *reinterpret_cast<float4*>(dq + qbase + (size_t)i * D + 16 * db + 4 * h) =
+          make_float4((acc[db][0] + x.x) * scale, (acc[db][1] + x.y) * scale, (acc[db][2] + x.z) * scale,
+                      (acc[db][3] + x.w) * scale);
+    }
 }
 
-template <typename T>
-hipError_t launch_delta_t(const void* dout, const void* out, float* delta, const float* lse, float* lse2,
-                          float dsign, float lscale, long long rows, int N, int ld, int D, hipStream_t s) {
-  const int lpr = D * (int)sizeof(T) / 16;
-  const int rpb = 256 / lpr;
-  const unsigned grid = (unsigned)((rows + rpb - 1) / rpb);
-  if (D == 64)
-    delta_kernel<T, 64><<<grid, 256, 0, s>>>((const T*)dout, (const T*)out, delta, lse, lse2, dsign, lscale, rows, N, ld);
-  else
-    delta_kernel<T, 128><<<grid, 256, 0, s>>>((const T*)dout, (const T*)out, delta, lse, lse2, dsign, lscale, rows, N, ld);
-  return hipGetLastError();
+// ---------------------------------------------------------------------- dk, dv
+// How the dk/dv work is cut (a function of the shape and the pattern alone, so that a sequence's results do not
+// depend on what else runs).
+struct F32Parts {
+  int nkt, nqt;
+  int nsp;    // window parts per key tile
+  int ncand;  // leading key tiles that may hold column keys
+  int ncc;    // column parts per such tile
+  size_t counters_off, part_off, end;  // workspace: Delta | arrival counters | partial dk, dv
+};
+
+__host__ __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
+F32Parts f32_parts(const LgShape& sh, const LgMask& m) {
+  F32Parts p;
+  p.nkt = p.nqt = ceil_div(sh.N, 64);
+  const int G = sh.Hq / sh.Hkv;
+  const long long base = (long long)p.nkt * sh.Hkv * sh.B;
+  int w = (m.wb * m.b + 63) / 64 + 1;  // query tiles the window of a key tile reaches
+  if (w > p.nqt) w = p.nqt;
+  const long long steps = (long long)w * G;
+  // two workgroups per CU, as long as a part keeps three steps
+  long long nsp = (512 + base - 1) / base;
+  if (nsp > steps / 3) nsp = steps / 3;
+  p.nsp = nsp < 1 ? 1 : (int)nsp;
+  // (the window of key tile 0 ends first: if it reaches the last row, no tile has a column part)
+  const int whi0 = lg_qtile_window_hi(m, sh.N < 64 ? sh.N - 1 : 63, 64);
+  p.ncand = 0;
+  if (whi0 < p.nqt - 1) p.ncand = m.stride > 0 ? p.nkt : ceil_div(m.sink, 64);
+  if (p.ncand > p.nkt) p.ncand = p.nkt;
+  // A column part is about as long as a window part, four steps at least (below that its own start and the final
+  // sum weigh more).  Strided patterns have many column tiles: a few parts each fill the GPU and keep the partial
+  // sums small.
+  const long long csteps = (long long)(p.nqt - 1 - whi0) * G;
+  long long len = (steps + p.nsp - 1) / p.nsp;
+  if (len < 4) len = 4;
+  if (m.stride == 0 && m.sink <= 16) len *= 3;  // (a step with one key group takes a third of the time)
+  long long ncc = (csteps + len - 1) / len;
+  const int most = m.stride > 0 ? 8 : 64;
+  p.ncc = p.ncand == 0 ? 0 : (int)(ncc < 1 ? 1 : ncc > most ? most : ncc);
+  const size_t rows = (((size_t)sh.B * sh.Hq * sh.N * sizeof(float)) + 255) & ~(size_t)255;
+  const bool split = p.nsp > 1 || p.ncand > 0;
+  const size_t heads = (size_t)sh.B * sh.Hkv;
+  p.counters_off = rows;
+  p.part_off = p.counters_off + (split ? (heads * p.nkt * sizeof(unsigned) + 255) & ~(size_t)255 : 0);
+  p.end = p.part_off + (split ? heads * ((size_t)p.nkt * p.nsp + (size_t)p.ncand * p.ncc) * 2 * 64 * sh.D * sizeof(float) : 0);
+  return p;
+}
+
+template <int D>
+__global__ __launch_bounds__(NT, 2) void dkdv_f32_kernel(
+    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
+    const float* __restrict__ dout, const float* __restrict__ lse, const float* __restrict__ delta,
+    float* __restrict__ dk, float* __restrict__ dv, int Hq, int Hkv, float scale, LgMask m, F32Parts pt, int heads,
+    unsigned* __restrict__ arrived, float* __restrict__ part) {
+  using T = LgF32Tile<D>;
+  using Dma = LgTileDma<T, NT>;
+  constexpr int TQ = LG_F32_BTQ, TK = LG_F32_BTK, DC = D / 16;
+  constexpr int OFF_G = T::BYTES, OFF_L = 2 * T::BYTES, STAGE = 2 * T::BYTES + 1024, LPT = 2 * Dma::CH;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * STAGE];
+  __shared__ unsigned s_before;
+
+  // work item: the column parts first (they are there for few tiles and as long as any), then the window parts
+  const int G = Hq / Hkv, N = m.N;
+  const int ncol = heads * pt.ncand * pt.ncc;
+  const bool column = (int)blockIdx.x < ncol;
+  int x = column ? blockIdx.x : blockIdx.x - ncol;
+  const int np = column ? pt.ncc : pt.nsp;
+  // heads innermost, first key tiles (the longest, where the window is) first
+  const int bh = x % heads;
+  x /= heads;
+  const int pi = x % np, kt = x / np;
+  const int b = bh / Hkv, hk = bh % Hkv;
+  const int k0 = kt * TK, k1 = min(k0 + TK - 1, N - 1);
+  const int wlo = k0 / TQ, whi = lg_qtile_window_hi(m, k1, TQ);
+  const bool has_col = pt.ncand > 0 && whi < pt.nqt - 1 && lg_has_column_key(m, k0, k1);
+  if (column && !has_col) return;
+  // steps of the whole part group: (query head, query tile), head slowest
+  const int lo = column ? whi + 1 : wlo, per_head = column ? pt.nqt - 1 - whi : whi - wlo + 1;
+  const int steps = per_head * G, len = ceil_div(steps, np);
+  const int s0 = pi * len, s1 = min(steps, s0 + len);
+  if (s0 >= s1) return;
+  const int wsteps = (whi - wlo + 1) * G, csteps = has_col ? (pt.nqt - 1 - whi) * G : 0;
+  const int nmain = ceil_div(wsteps, ceil_div(wsteps, pt.nsp));
+  const int ncols = has_col ? ceil_div(csteps, ceil_div(csteps, pt.ncc)) : 0;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, h = lane >> 4;
+  // A wave's 16 keys and its row blocks of a 64-row step: key group wave % 4 and two of the four blocks, or, in a
+  // column part with column keys in one group only (a sink of up to 16 tokens), that group for waves 0..3 with one
+  // block each: as one wave pair the group ran on one SIMD of the four.
+  int kg = wave & 3, ngrp = 0;
+  for (int x = 0; x < 4; ++x)
+    if (column && k0 + 16 * x < N && lg_has_column_key(m, k0 + 16 * x, min(k0 + 16 * x + 15, N - 1))) {
+      ++ngrp;
+      kg = x;
+    }
+  const bool narrow = ngrp == 1;
+  if (!narrow) kg = wave & 3;
+  const int rb0 = narrow ? wave & 3 : 2 * (wave >> 2);
+  const bool owner = narrow ? wave == 0 : wave < 4;  // holds the sum over the row blocks at the end
+  const int j = k0 + 16 * kg + n, jk = min(j, N - 1);
+  const int kw0 = min(k0 + 16 * kg, N - 1), kw1 = k0 + 16 * kg + 15;  // this wave's keys
+  const size_t kbase = (size_t)(b * Hkv + hk) * m.ld * D;
+  const float c2 = scale * LOG2E;
+
+  float4 kf[DC], vf[DC];
+#pragma unroll
+  for (int c = 0; c < DC; ++c) {
+    kf[c] = *reinterpret_cast<const float4*>(k + kbase + (size_t)jk * D + 16 * c + 4 * h);
+    vf[c] = *reinterpret_cast<const float4*>(v + kbase + (size_t)jk * D + 16 * c + 4 * h);
+  }
+#pragma unroll
+  for (int c = 0; c < DC; ++c) asm volatile("" ::"v"(kf[c].x), "v"(vf[c].x));
+  f32x4_t ak[DC], av[DC];
+#pragma unroll
+  for (int db = 0; db < DC; ++db) ak[db] = av[db] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  Dma dma;
+  dma.init(tid);
+  LgF32Reader<D> rd;
+  rd.init(n, h);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)LG_LDS_PTR(unsigned char, smem);
+  auto issue = [&](int hq, int u, int stage) {
+    const int q0 = u * TQ;
+    const uint32_t st = lds0 + stage * STAGE;
+    const size_t urow = (size_t)(b * Hq + hq) * m.ld;
+    if (wave < 2) {  // wave 0: lse rows, wave 1: Delta rows (dense in the workspace)
+      const int r = min(q0 + lane, N - 1);
+      lg_dma_f32x64(wave == 0 ? lse + urow + r : delta + (size_t)(b * Hq + hq) * N + r, st + OFF_L + wave * 256);
+    }
+    dma.issue(q + (urow + q0) * D, N - q0, st);
+    dma.issue(dout + (urow + q0) * D, N - q0, st + OFF_G);
+  };
+  int hq_c = hk * G + s0 / per_head, u_c = lo + s0 % per_head;  // step being computed
+  int hq_i = hq_c, u_i = u_c;                                   // step being issued
+  auto advance = [&](int& hq, int& u) {
+    if (++u == lo + per_head) {
+      u = lo;
+      ++hq;
+    }
+  };
+  issue(hq_i, u_i, 0);
+  advance(hq_i, u_i);
+  if (s0 + 1 < s1) issue(hq_i, u_i, 1);
+  for (int st = s0; st < s1; ++st) {
+    const int stage = (st - s0) & 1;
+    if (st + 1 < s1) LG_WAIT_VMCNT(LPT);
+    else LG_WAIT_VMCNT(0);
+    __syncthreads();
+    const int sq = stage * STAGE, sg = sq + OFF_G;
+    const float* sL = reinterpret_cast<const float*>(smem + sq + OFF_L);
+    const int r0 = u_c * TQ + 16 * rb0;
+    // this wave's two 16-row blocks (narrow: one) against its 16 keys
+    const int kind0 = r0 < N && !(narrow && wave > 3) ? lg_tile_kind(m, r0, min(r0 + 15, N - 1), kw0, kw1) : (int)LG_TILE_DEAD;
+    const int kind1 = r0 + 16 < N && !narrow ? lg_tile_kind(m, r0 + 16, min(r0 + 31, N - 1), kw0, kw1) : (int)LG_TILE_DEAD;
+    const bool masked = kind0 == LG_TILE_PARTIAL || kind1 == LG_TILE_PARTIAL || r0 + 31 >= N;
+    auto run = [&](auto B0_, auto NB_) {
+      constexpr int B0 = decltype(B0_)::value, NB = decltype(NB_)::value;
+      f32x4_t s[NB], dp[NB];
+      float4 qa[2][NB], ga[2][NB];
+      float qc[2][DC], gc[2][DC];
+      auto read_rows = [&](int c) {
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
+          qa[c & 1][x] = rd.row4(smem, sq, rb0 + B0 + x, c);
+          ga[c & 1][x] = rd.row4(smem, sg, rb0 + B0 + x, c);
+        }
+      };
+      auto read_cols = [&](int u) {  // unit u = 4 x + r
+#pragma unroll
+        for (int db = 0; db < DC; ++db) {
+          gc[u & 1][db] = rd.col(smem, sg, rb0 + B0 + (u >> 2), u & 3, db);
+          qc[u & 1][db] = rd.col(smem, sq, rb0 + B0 + (u >> 2), u & 3, db);
+        }
+      };
+      float4 l4[NB], d4[NB];
+#pragma unroll
+      for (int x = 0; x < NB; ++x) {
+        s[x] = dp[x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        l4[x] = *reinterpret_cast<const float4*>(sL + 16 * (rb0 + B0 + x) + 4 * h);
+        d4[x] = *reinterpret_cast<const float4*>(sL + 64 + 16 * (rb0 + B0 + x) + 4 * h);
+      }
+      read_rows(0);
+#pragma unroll
+      for (int c = 0; c < DC; ++c) {
+        if (c + 1 < DC) read_rows(c + 1);
+        else read_cols(0);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
+          s[x] = lg_mfma16(qa[c & 1][x].x, kf[c].x, s[x]);
+          dp[x] = lg_mfma16(ga[c & 1][x].x, vf[c].x, dp[x]);
+        }
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
+          s[x] = lg_mfma16(qa[c & 1][x].y, kf[c].y, s[x]);
+          dp[x] = lg_mfma16(ga[c & 1][x].y, vf[c].y, dp[x]);
+        }
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
+          s[x] = lg_mfma16(qa[c & 1][x].z, kf[c].z, s[x]);
+          dp[x] = lg_mfma16(ga[c & 1][x].z, vf[c].z, dp[x]);
+        }
+#pragma unroll
+        for (int x = 0; x < NB; ++x) {
+          s[x] = lg_mfma16(qa[c & 1][x].w, kf[c].w, s[x]);
+          dp[x] = lg_mfma16(ga[c & 1][x].w, vf[c].w, dp[x]);
+        }
+      }
+#pragma unroll
+      for (int x = 0; x < NB; ++x) {
+        const float ls[4] = {l4[x].x, l4[x].y, l4[x].z, l4[x].w}, de[4] = {d4[x].x, d4[x].y, d4[x].z, d4[x].w};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = r0 + 16 * (B0 + x) + 4 * h + r;
+          float p = __builtin_amdgcn_exp2f(fmaf(s[x][r], c2, -ls[r] * LOG2E));
+          if (masked && !(row < N && lg_live(m, row, j))) p = 0.f;
+          s[x][r] = p;
+          dp[x][r] = p * (dp[x][r] - de[r]);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 4 * NB; ++u) {
+        if (u + 1 < 4 * NB) read_cols(u + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int db = 0; db < DC; ++db) {
+          av[db] = lg_mfma16(gc[u & 1][db], s[u >> 2][u & 3], av[db]);
+          ak[db] = lg_mfma16(qc[u & 1][db], dp[u >> 2][u & 3], ak[db]);
+        }
+      }
+    };
+    if (kind0 != LG_TILE_DEAD && kind1 != LG_TILE_DEAD) run(I0{}, I2{});
+    else if (kind0 != LG_TILE_DEAD) run(I0{}, I1{});
+    else if (kind1 != LG_TILE_DEAD) run(I1{}, I1{});
+    __syncthreads();  // everyone is done with this stage
+    advance(hq_c, u_c);
+    if (st + 2 < s1) {
+      advance(hq_i, u_i);
+      issue(hq_i, u_i, stage);
+    }
+  }
+
+  // add the row blocks
+  float4* so = reinterpret_cast<float4*>(smem);
+  const int give = narrow ? wave - 1 : wave - 4;  // LDS slot of a wave that is not an owner
+  if (!owner && !(narrow && wave > 3))
+#pragma unroll
+    for (int db = 0; db < DC; ++db) {
+      so[(give * 2 * DC + db) * 64 + lane] = make_float4(ak[db][0], ak[db][1], ak[db][2], ak[db][3]);
+      so[(give * 2 * DC + DC + db) * 64 + lane] = make_float4(av[db][0], av[db][1], av[db][2], av[db][3]);
+    }
+  __syncthreads();
+  if (owner)
+    for (int y = narrow ? 0 : wave; y < (narrow ? 3 : wave + 1); ++y)
+#pragma unroll
+      for (int db = 0; db < DC; ++db) {
+        const float4 a = so[(y * 2 * DC + db) * 64 + lane], c = so[(y * 2 * DC + DC + db) * 64 + lane];
+        ak[db] += f32x4_t{a.x, a.y, a.z, a.w};
+        av[db] += f32x4_t{c.x, c.y, c.z, c.w};
+      }
+  auto put = [&](int key, int db, f32x4_t a, f32x4_t c) {
+    const size_t at = kbase + (size_t)key * D + 16 * db + 4 * h;
+    *reinterpret_cast<float4*>(dk + at) = make_float4(a[0] * scale, a[1] * scale, a[2] * scale, a[3] * scale);
+    *reinterpret_cast<float4*>(dv + at) = make_float4(c[0], c[1], c[2], c[3]);
+  };
+  if (nmain + ncols == 1) {
+    if (owner && j < N)
+#pragma unroll
+      for (int db = 0; db < DC; ++db) put(j, db, ak[db], av[db]);
+    return;
+  }
+  // partial sums: slot of (tile, part), then [dk | dv][key group][dim block][lane] float4
+  const size_t pslot = 2 * (size_t)64 * D;
+  const size_t main0 = ((size_t)bh * pt.nkt + kt) * pt.nsp;
+  const size_t col0 = (size_t)heads * pt.nkt * pt.nsp + ((size_t)bh * pt.ncand + kt) * pt.ncc;
+  // does a column part serve keys of group g?  (no other group's slot of a column part is written or read)
+  auto col_group = [&](int g) {
+    const int a = k0 + 16 * g;
+    return has_col && a < N && lg_has_column_key(m, a, min(a + 15, N - 1));
+  };
+  float* mine = part + (column ? col0 + pi : main0 + pi) * pslot;
+  if (owner && (!column || col_group(kg)))
+#pragma unroll
+    for (int db = 0; db < DC; ++db) {
+      lg_store_shared4(mine + ((kg * DC + db) * 64 + lane) * 4, ak[db]);
+      lg_store_shared4(mine + (((4 + kg) * DC + db) * 64 + lane) * 4, av[db]);
+    }
+  lg_shared_stores_done();
+  __syncthreads();
+  if (tid == 0)
+    s_before = __hip_atomic_fetch_add(arrived + (size_t)bh * pt.nkt + kt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if (s_before != (unsigned)(nmain + ncols - 1)) return;  // another part will be the last
+  // the last one adds all parts in their order: wave = (key group, half of the dims), four parts' loads in flight
+  constexpr int HB = DC / 2, AHEAD = 4;
+  const int g = wave & 3, db0 = (wave >> 2) * HB;
+  const int nsum = nmain + (col_group(g) ? ncols : 0);
+  f32x4_t sk_[HB], sv_[HB];
+#pragma unroll
+  for (int y = 0; y < HB; ++y) sk_[y] = sv_[y] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int p0 = 0; p0 < nsum; p0 += AHEAD) {
+    f32x4_t a[AHEAD][HB], c[AHEAD][HB];
+#pragma unroll
+    for (int x = 0; x < AHEAD; ++x) {
+      const int p = min(p0 + x, nsum - 1);
+      const float* src = part + (p < nmain ? main0 + p : col0 + p - nmain) * pslot;
+#pragma unroll
+      for (int y = 0; y < HB; ++y) {
+        a[x][y] = lg_load_shared4(src + ((g * DC + db0 + y) * 64 + lane) * 4);
+        c[x][y] = lg_load_shared4(src + (((4 + g) * DC + db0 + y) * 64 + lane) * 4);
+      }
+    }
+#pragma unroll
+    for (int x = 0; x < AHEAD; ++x)
+      if (p0 + x < nsum)
+#pragma unroll
+        for (int y = 0; y < HB; ++y) {
+          sk_[y] += a[x][y];
+          sv_[y] += c[x][y];
+        }
+  }
+  if (k0 + 16 * g + n < N)
+#pragma unroll
+    for (int y = 0; y < HB; ++y) put(k0 + 16 * g + n, db0 + y, sk_[y], sv_[y]);
+}
+
+template <int D>
+hipError_t launch_bwd(const float* q, const float* k, const float* v, const float* out, const float* lse,
+                      const float* dout, float* dq, float* dk, float* dv, void* ws, const LgShape& sh,
+                      const LgMask& m, hipStream_t s, hipEvent_t* ev) {
+  const F32Parts pt = f32_parts(sh, m);
+  const int heads = sh.B * sh.Hkv;
+  float* delta = (float*)ws;
+  unsigned* arrived = (unsigned*)((char*)ws + pt.counters_off);
+  float* part = (float*)((char*)ws + pt.part_off);
+  const long long ncnt = pt.part_off > pt.counters_off ? (long long)heads * pt.nkt : 0;
+  const long long tl = (long long)pt.nqt * sh.Hq * sh.B;
+  const long long items = (long long)heads * ((long long)pt.nkt * pt.nsp + (long long)pt.ncand * pt.ncc);
+  if (tl > 0x7fffffffLL - 8 || items > 0x7fffffffLL || ncnt > 0x7fffffffLL) return hipErrorInvalidValue;
+  if (ev) {  // (nothing to set up on this path)
+    (void)hipEventRecord(ev[0], s);
+    (void)hipEventRecord(ev[1], s);
+  }
+  const int total = (int)tl, per_xcd = (total + 7) / 8;
+  dq_f32_kernel<D><<<dim3(per_xcd * 8), NT, 0, s>>>(q, k, v, out, dout, lse, delta, dq, sh.Hq, sh.Hkv, sh.scale, m,
+                                                    pt.nqt, total, per_xcd, arrived, (int)ncnt);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if (ev) (void)hipEventRecord(ev[2], s);
+  dkdv_f32_kernel<D><<<dim3((unsigned)items), NT, 0, s>>>(q, k, v, dout, lse, delta, dk, dv, sh.Hq, sh.Hkv, sh.scale,
+                                                          m, pt, heads, arrived, part);
+  e = hipGetLastError();
+  if (ev) (void)hipEventRecord(ev[3], s);
+  return e;
 }
 
 }  // namespace
 
-// Delta pre-pass for either dtype (used by both backward paths).
-hipError_t lg_launch_delta(const void* dout, const void* out, float* delta, const float* lse, float* lse2,
-                           float dsign, float lscale, long long rows, int N, int ld, int D, int dtype,
-                           hipStream_t s) {
-  return dtype == LG_F32
-             ? launch_delta_t<float>(dout, out, delta, lse, lse2, dsign, lscale, rows, N, ld, D, s)
-             : launch_delta_t<__hip_bfloat16>(dout, out, delta, lse, lse2, dsign, lscale, rows, N, ld, D, s);
-}
-
 size_t lg_bwd_workspace_bytes(const LgShape& sh, const LgMask& m, int dtype) {
-  // Delta [B, Hq, N] float32, rounded up to 256 bytes; the bf16 path adds a scaled copy of lse in the
-  // same shape and its column-tile area
+  if (dtype == LG_F32) return f32_parts(sh, m).end;
+  // the bf16 path: -Delta and -lse / scale, [B, Hq, N] float32 each, rounded up to 256 bytes, then its column area
   const size_t n = (((size_t)sh.B * sh.Hq * sh.N * sizeof(float)) + 255) & ~(size_t)255;
-  return dtype == LG_BF16 ? lg_bwd_bf16_workspace_bytes(sh, m, 2 * n) : n;
+  return lg_bwd_bf16_workspace_bytes(sh, m, 2 * n);
 }
 
 hipError_t lg_launch_bwd_f32(const float* q, const float* k, const float* v, const float* out,
                              const float* lse, const float* dout, float* dq, float* dk, float* dv,
                              void* ws, const LgShape& sh, const LgMask& m, hipStream_t s,
                              hipEvent_t* ev) {
-  float* delta = (float*)ws;
-  if (ev) (void)hipEventRecord(ev[0], s);
-  hipError_t e = lg_launch_delta(dout, out, delta, nullptr, nullptr, 1.f, 0.f, (long long)sh.B * sh.Hq * sh.N, sh.N, m.ld, sh.D,
-                                 LG_F32, s);
-  if (e != hipSuccess) return e;
-  if (ev) (void)hipEventRecord(ev[1], s);
-  const dim3 gq((sh.N + LG_F32_TQ - 1) / LG_F32_TQ, sh.Hq, sh.B);
-  const dim3 gk((sh.N + LG_F32_BTK - 1) / LG_F32_BTK, sh.Hkv, sh.B);
-  if (sh.D == 64)
-    dq_f32_kernel<64><<<gq, 256, 0, s>>>(q, k, v, dout, lse, delta, dq, sh.Hq, sh.Hkv, sh.scale, m);
-  else
-    dq_f32_kernel<128><<<gq, 256, 0, s>>>(q, k, v, dout, lse, delta, dq, sh.Hq, sh.Hkv, sh.scale, m);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (ev) (void)hipEventRecord(ev[2], s);
-  if (sh.D == 64)
-    dkdv_f32_kernel<64><<<gk, 256, 0, s>>>(q, k, v, dout, lse, delta, dk, dv, sh.Hq, sh.Hkv, sh.scale, m);
-  else
-    dkdv_f32_kernel<128><<<gk, 256, 0, s>>>(q, k, v, dout, lse, delta, dk, dv, sh.Hq, sh.Hkv, sh.scale, m);
-  e = hipGetLastError();
-  if (ev) (void)hipEventRecord(ev[3], s);
-  return e;
+  return sh.D == 64 ? launch_bwd<64>(q, k, v, out, lse, dout, dq, dk, dv, ws, sh, m, s, ev)
+                    : launch_bwd<128>(q, k, v, out, lse, dout, dq, dk, dv, ws, sh, m, s, ev);
 }

@@ -45,15 +45,9 @@ long long lg_fwd_bf16_pack_tiles(LgPack* pack);
 hipError_t lg_launch_fwd_bf16_pack(const void* q, const void* k, const void* v, void* out, float* lse,
                                    const LgShape& sh, const LgMask& tmpl, const LgPack& pack, hipStream_t s);
 
-// delta_i = dsign * <dout_i, out_i> for rows = B*Hq*N rows of D elements of either dtype;
-// lse2 (may be NULL) = lse * lscale.  delta and lse2 are dense; in dout, out and lse a head's N rows are
-// followed by the next head's after ld rows.
-hipError_t lg_launch_delta(const void* dout, const void* out, float* delta, const float* lse, float* lse2,
-                           float dsign, float lscale, long long rows, int N, int ld, int D, int dtype,
-                           hipStream_t s);
 size_t lg_bwd_workspace_bytes(const LgShape& sh, const LgMask& m, int dtype);
 size_t lg_bwd_bf16_workspace_bytes(const LgShape& sh, const LgMask& m, size_t head_bytes);
-// ev: NULL, or 4 events recorded before the Delta pre-pass, between the kernels and after the
+// ev: NULL, or 4 events recorded before the set-up, before the dq kernel, before the dk/dv kernels and after the
 // last one (measurement aid).
 hipError_t lg_launch_bwd_f32(const float* q, const float* k, const float* v, const float* out,
                              const float* lse, const float* dout, float* dq, float* dk, float* dv,

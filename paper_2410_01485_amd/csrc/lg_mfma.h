@@ -14,6 +14,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <utility>
+
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
@@ -44,6 +46,40 @@ __device__ __forceinline__ uint32_t lg_pack_bf16(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, h);
 }
 
+// Values that one workgroup leaves for another of the same launch (partial results summed by whichever finishes
+// last): device-scope accesses, which go through to memory the workgroups of all XCDs see, instead of device-wide
+// fences, which write back and invalidate a whole L2 (in the float32 dk/dv kernel such a fence per wave cost 87 of
+// 138 us).  Stores, lg_shared_stores_done(), a barrier, then a device-scope atomic announces them.
+__device__ __forceinline__ void lg_store_shared2(float* p, float x, float y) {
+  const unsigned long long w =
+      __builtin_bit_cast(unsigned, x) | ((unsigned long long)__builtin_bit_cast(unsigned, y) << 32);
+  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void lg_store_shared4(float* p, f32x4_t x) {
+  lg_store_shared2(p, x[0], x[1]);
+  lg_store_shared2(p + 2, x[2], x[3]);
+}
+__device__ __forceinline__ f32x2_t lg_load_shared2(const float* p) {
+  const unsigned long long w = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+  return f32x2_t{__builtin_bit_cast(float, (unsigned)w), __builtin_bit_cast(float, (unsigned)(w >> 32))};
+}
+__device__ __forceinline__ f32x4_t lg_load_shared4(const float* p) {
+  const f32x2_t a = lg_load_shared2(p), b = lg_load_shared2(p + 2);
+  return f32x4_t{a[0], a[1], b[0], b[1]};
+}
+__device__ __forceinline__ void lg_shared_stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 __device__ __forceinline__ bf16x8_t lg_as_bf16x8(uint4 x) { return __builtin_bit_cast(bf16x8_t, x); }
+
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order
+template <int... I, typename F>
+__device__ __forceinline__ void lg_static_for_impl(std::integer_sequence<int, I...>, F&& f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void lg_static_for(F&& f) {
+  lg_static_for_impl(std::make_integer_sequence<int, N>{}, f);
+}
 
 #endif  // LG_MFMA_H_

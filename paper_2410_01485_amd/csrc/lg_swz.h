@@ -43,10 +43,11 @@ struct LgSwzTile {
 // bits [3:0] and [15:14] of the immediate
 #define LG_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
 
-// Direct global->LDS copy of one tile by NT threads.
-template <int D, int NT>
-struct LgDma {
-  using T = LgSwzTile<D>;
+// Direct global->LDS copy of one tile by NT threads.  Tile: a layout with ROWS, CPR (16-byte chunks per row),
+// ROW_BYTES and the swizzle pi(row).
+template <typename Tile, int NT>
+struct LgTileDma {
+  using T = Tile;
   static constexpr int CH = T::ROWS * T::CPR / NT;  // 16-byte chunks per thread
   static_assert(CH >= 1, "tile smaller than the workgroup");
   uint32_t voff[CH];   // global byte offset of this lane's chunk inside the tile
@@ -64,7 +65,7 @@ struct LgDma {
   // src: first row of the tile in global memory (wave-uniform); rows_left: rows of the matrix
   // from there on (rows past the end are replaced by the last valid row); lds: LDS byte
   // address of the tile (wave-uniform).
-  __device__ __forceinline__ void issue(const uint16_t* src, int rows_left, uint32_t lds) const {
+  __device__ __forceinline__ void issue(const void* src, int rows_left, uint32_t lds) const {
     // two copies of the loop behind one wave-uniform branch: whole tiles (nearly all) spend no
     // vector instructions on addresses
     if (rows_left >= T::ROWS) {
@@ -79,13 +80,15 @@ struct LgDma {
       }
     }
   }
-  __device__ __forceinline__ void load(const uint16_t* src, uint32_t off, uint32_t lds, int x) const {
+  __device__ __forceinline__ void load(const void* src, uint32_t off, uint32_t lds, int x) const {
     const uint32_t m0 = lds + wave_off + x * NT * 16;  // all scalar
     // (an LDS-bound load reads M0 one issue slot after a scalar write at the earliest)
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(__builtin_amdgcn_readfirstlane(m0)), "v"(off), "s"(src)
                  : "memory");
   }
 };
+template <int D, int NT>
+using LgDma = LgTileDma<LgSwzTile<D>, NT>;
 
 // Direct global->LDS copy of 64 consecutive floats by one wave: lane l fetches src[l]
 // (src is this lane's own address) and the wave's 256 bytes land contiguously at `lds`.

@@ -4,8 +4,6 @@
 #ifndef LG_WIDE_H_
 #define LG_WIDE_H_
 
-#include <utility>
-
 #include "lg_mfma.h"
 
 namespace {
@@ -100,16 +98,6 @@ constexpr bool lg_readable_after(int reader, int last_writer) { return reader >=
 // A matrix instruction number `consumer` may read an operand that the vector piece placed after
 // instruction number `last_piece` completed: at least one whole matrix instruction lies in between.
 constexpr bool lg_operand_ready(int consumer, int last_piece) { return consumer >= last_piece + 2; }
-
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order
-template <int... I, typename F>
-__device__ __forceinline__ void lg_static_for_impl(std::integer_sequence<int, I...>, F&& f) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void lg_static_for(F&& f) {
-  lg_static_for_impl(std::make_integer_sequence<int, N>{}, f);
-}
 
 template <int I>
 struct LgFrag;

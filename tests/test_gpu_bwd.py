@@ -162,6 +162,20 @@ def test_long_windows_wide_kernels(B, Hq, Hkv, N, D, sink, window, block, stride
     check_bwd(B, Hq, Hkv, N, D, sink, window, block, stride, dtype=torch.bfloat16, seed=77)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,N,D,sink,window,block,stride", [
+    # float32 dk/dv parts: a sink in one 16-key group (one wave per row block), in two and in five groups; window parts
+    # split over workgroups; column parts of strided blocks; a window whose last rows end one tile before the sequence
+    (1, 4, 2, 1500, 64, 16, 128, 1, 0),
+    (2, 2, 1, 1100, 128, 40, 64, 1, 0),
+    (1, 2, 2, 1000, 64, 70, 100, 1, 0),
+    (1, 1, 1, 1030, 128, 0, 1030, 1, 0),
+    (1, 2, 1, 900, 64, 48, 96, 48, 3),
+    (1, 2, 2, 192, 64, 8, 65, 1, 0),
+])
+def test_float32_parts(B, Hq, Hkv, N, D, sink, window, block, stride):
+    check_bwd(B, Hq, Hkv, N, D, sink, window, block, stride, dtype=torch.float32, seed=83)
+
+
 def test_bwd_deterministic_long_window():
     q, k, v, g = lg_synth.prefill_inputs(1, 2, 2, 2000, 128, 10, torch.bfloat16, with_dout=True)
     a = run_fwd_bwd(q, k, v, g, 64, 1024)
