@@ -328,7 +328,7 @@ size_t lg_sparse_attn_decode_cache_workspace_bytes(int B, int Hq, int Hkv, int N
                                                    int sink, int window, int block, int stride, int dtype) {
   if (check_decode(B, Hq, Hkv, N, D, sink, window, block, stride, dtype) != LG_OK) return 0;
   const LgDecSegs g = lg_decode_segments(lg_make_cache_mask(N, sink, window, block, stride));
-  return lg_decode_workspace_bytes(B, Hq, Hkv, D, g.pre[g.n]);
+  return lg_decode_workspace_bytes(B, Hq, Hkv, D, g.pre[g.n], dtype, false);
 }
 
 int lg_sparse_attn_decode_cache(const void* q, const void* k_cache, const void* v_cache, void* out,
@@ -346,7 +346,7 @@ int lg_sparse_attn_decode_cache(const void* q, const void* k_cache, const void* 
       !aligned16(lse) || !aligned16(workspace))
     return LG_ERR_INVALID_ARG;
   const LgDecSegs g = lg_decode_segments(lg_make_cache_mask(N, sink, window, block, stride));
-  const size_t need = lg_decode_workspace_bytes(B, Hq, Hkv, D, g.pre[g.n]);
+  const size_t need = lg_decode_workspace_bytes(B, Hq, Hkv, D, g.pre[g.n], dtype, false);
   if (need > 0 && (!workspace || workspace_bytes < need)) return LG_ERR_WORKSPACE;
   const LgShape sh = make_shape(B, Hq, Hkv, N, D, scale);
   hipError_t e = lg_launch_decode(q, k_cache, v_cache, out, lse, workspace, B, Hq, Hkv, cache_slots, g, D,
@@ -405,7 +405,9 @@ static int check_paged(int n_max, int sink, int window, int block, int stride, i
 
 size_t lg_sparse_attn_decode_paged_workspace_bytes(int B, int Hq, int Hkv, int n_max, int D,
                                                    int sink, int window, int block, int stride, int dtype) {
-  return lg_sparse_attn_decode_cache_workspace_bytes(B, Hq, Hkv, n_max, D, sink, window, block, stride, dtype);
+  if (check_decode(B, Hq, Hkv, n_max, D, sink, window, block, stride, dtype) != LG_OK) return 0;
+  return lg_decode_workspace_bytes(B, Hq, Hkv, D, lg_decode_keys_max(lg_make_cache_mask(n_max, sink, window, block, stride)),
+                                   dtype, true);
 }
 
 int lg_sparse_attn_decode_paged(const void* q, const void* k_pages, const void* v_pages,
@@ -426,8 +428,8 @@ int lg_sparse_attn_decode_paged(const void* q, const void* k_pages, const void* 
       !aligned16(workspace) || ((uintptr_t)page_table & 3) || ((uintptr_t)seq_lens & 3))
     return LG_ERR_INVALID_ARG;
   const LgMask cm = lg_make_cache_mask(n_max, sink, window, block, stride);
-  const LgDecSegs g = lg_decode_segments(cm);  // the longest context: most keys
-  const size_t need = lg_decode_workspace_bytes(B, Hq, Hkv, D, g.pre[g.n]);
+  const LgDecSegs g = lg_decode_segments(cm);
+  const size_t need = lg_decode_workspace_bytes(B, Hq, Hkv, D, lg_decode_keys_max(cm), dtype, true);
   if (need > 0 && (!workspace || workspace_bytes < need)) return LG_ERR_WORKSPACE;
   const LgShape sh = make_shape(B, Hq, Hkv, n_max, D, scale);
   hipError_t e = lg_launch_decode(q, k_pages, v_pages, out, lse, workspace, B, Hq, Hkv, 0, g, D, dtype, sh.scale,

@@ -2,17 +2,15 @@
 // second paragraph: at inference the bottleneck is loading the KV cache as fast as
 // possible; the attention-sink variant keeps the window in a rolling buffer).
 //
-// One query per (b, hq); every valid cache slot is read exactly once.  The work is
-// pure HBM streaming (about one flop per byte), so it runs on vector ALUs with
-// 16-byte coalesced loads: LPR consecutive lanes read one key row, a wave reads
-// 64/LPR consecutive rows per load, and U loads of K and of V are in flight per
-// lane.  The slots of one (b, hkv) are split over `splits` workgroups so the chip
-// is filled even for small batches; a second tiny kernel merges the partial
-// (max, sum, accumulator) triples.  All query heads of a kv head are served by the
-// same pass over K/V (GQA).
+// One query per (b, hq); every valid cache slot is read exactly once.  Two kernels:
+//   decode_mfma_kernel  bf16, all query heads of a kv head (up to 16) at once on the matrix cores
+//   decode_kernel       float32, on vector ALUs: LPR consecutive lanes read one key row, a wave reads 64/LPR
+//                       consecutive rows per load, and U loads of K and of V are in flight per lane
+// The slots of one (b, hkv) are split over workgroups so the chip is filled even for small batches; each leaves
+// its normalised result and log-sum-exp in the workspace, and the one that finishes last adds them (decode_finish).
 //
 // The keys of a step are up to four runs of consecutive slots (LgDecSegs: sink tokens,
-// live part of the rolling window, retained strided blocks); the kernel walks their
+// live part of the rolling window, retained strided blocks); the kernels walk their
 // concatenation.  The common case, one run starting at slot 0, has its own instance
 // without the index translation.  A third instance serves paged caches with per-sequence
 // context lengths: the runs are computed per sequence on the device and a slot goes through
@@ -24,17 +22,16 @@
 #include "../../include/longgen_attn.h"
 #include "lg_kernels.h"
 #include "lg_mask.h"
+#include "lg_mfma.h"
+
+#include <algorithm>
+#include <atomic>
+#include <random>
 
 namespace {
 
 constexpr int WAVES = 4;
-#ifndef LG_DEC_U
-#define LG_DEC_U 8
-#endif
-#ifndef LG_DEC_TARGET
-#define LG_DEC_TARGET 512
-#endif
-constexpr int U = LG_DEC_U;  // key rows per lane group per iteration
+constexpr int U = 8;  // vector kernel: key rows per lane group per iteration
 
 template <int CTRL>
 __device__ __forceinline__ float dpp_f(float x) {
@@ -89,56 +86,244 @@ struct Frag<__hip_bfloat16, 8> {
 __device__ __forceinline__ void store_out(float* p, float x) { *p = x; }
 __device__ __forceinline__ void store_out(__hip_bfloat16* p, float x) { *p = __float2bfloat16(x); }
 
-// Partial record in the workspace, per (b, hq, split): D accumulators, max, sum
-// (max and running values are in the log2 domain: score * scale * log2(e)).
+// Running maxima are in the log2 domain: score * scale * log2(e).
 // What a paged launch adds to the arguments.
 struct LgPaged {
   const int* page_table;  // [B, pages_per_seq]
   const int* seq_lens;    // [B]
-  int pages_per_seq, page_shift, n_max, num_pages;
+  int pages_per_seq, page_shift, n_max, num_pages, B;
+  int keys_max;           // no sequence has more keys
+  int few;                // workgroups of a small step
   LgMask cm;              // cache geometry (lg_make_cache_mask), N filled in per sequence
 };
 
 enum { LG_DEC_PLAIN = 0, LG_DEC_SEGS = 1, LG_DEC_PAGED = 2 };
 
-template <typename T, int D, int GT, int MODE>
-__global__ __launch_bounds__(WAVES * 64) void decode_kernel(const T* __restrict__ q,
-                                                            const T* __restrict__ kc,
-                                                            const T* __restrict__ vc,
-                                                            T* __restrict__ out, float* __restrict__ lse,
-                                                            float* __restrict__ ws, int Hq, int Hkv,
-                                                            int C, int valid, int chunk, int splits,
-                                                            float scale_log2e, LgDecSegs segs, LgPaged pg) {
+// ---------------------------------------------------------------- work of a decode launch
+// The keys of every (b, kv head, head chunk) -- a "row" here -- are cut into `splits` parts of `chunk` keys; a
+// workgroup takes one part.  (Paged: as many parts as the sequence's own length fills; the workgroups beyond leave.)
+// A row of several parts is added up by the last of its workgroups to finish (decode_finish).
+struct LgDecWork {
+  int splits, chunk;         // (paged: the most parts of a row and the least keys of a part)
+  unsigned epoch;            // of this call, never 0
+  unsigned long long* word;  // [rows][splits][max(GT, 2)]: epoch << 32 | log2-sum-exp of a head
+  float* o;                  // [rows][splits][GT][D]: normalised partial results
+};
+constexpr int UNIT = 32, LG_DEC_SPLITS_MAX = 64;
+// Workgroups with keys that a paged step aims at: three per CU, what the matrix-core kernel's registers admit, or (bf16)
+// one per CU when all rows together have so few keys that a workgroup's start and the final sum weigh more than its
+// reads.
+constexpr int DEC_FULL = 768, DEC_FEW = 256;
+constexpr float DEC_MANY_KEYS = 300000.f;
+
+struct LgDecPart {
+  int b, q;           // sequence, and kv head * chunks + chunk
+  int s0, s1;         // its keys
+  int split, parts;   // of the row
+  size_t row;
+};
+
+// The part of this workgroup; false: none.  Grid: splits x rows of a sequence x B.  Paged (heads: rows of a sequence):
+// one dimension, the parts of all sequences one after the other; segs receives the sequence's runs.
+template <int MODE>
+__device__ __forceinline__ bool lg_dec_part(const LgDecWork& wk, const LgPaged& pg, int heads, LgDecSegs& segs,
+                                            int valid, LgDecPart& p) {
+  if (MODE != LG_DEC_PAGED) {
+    p.split = blockIdx.x;
+    p.q = blockIdx.y;
+    p.b = blockIdx.z;
+    p.row = (size_t)p.b * heads + p.q;
+    p.parts = wk.splits;
+    p.s0 = p.split * wk.chunk;
+    p.s1 = min(valid, p.s0 + wk.chunk);
+    return p.s0 < valid;
+  }
+  // The lengths of the batch set the size of a part: about as many workgroups as the GPU holds at a time (fewer for a
+  // step that is over in a few rounds anyway), no more parts per row than the workspace has room for.  As a grid of
+  // (parts of the longest) x rows, with workgroups that find nothing to do, the others came out uneven over the CUs.
+  const int lane = threadIdx.x & 63, B = pg.B;
+  auto keys = [&](int x) { return x < B ? min(max(pg.seq_lens[x], 1), pg.keys_max) : 0; };  // never too few
+  const int first = keys(lane);  // (a batch of up to 64: the only look at the lengths)
+  float sum = (float)first;
+  for (int x = 64 + lane; x < B; x += 64) sum += (float)keys(x);
+#pragma unroll
+  for (int x = 1; x < 64; x <<= 1) sum += __shfl_xor(sum, x);
+  const float all = sum * heads;
+  const float target = all > DEC_MANY_KEYS ? fmaxf(DEC_FULL - 0.25f * B * heads, DEC_FEW) : (float)pg.few;
+  const int chunk = max(wk.chunk, 128 * __builtin_amdgcn_readfirstlane((int)ceilf(all / (128.f * target))));
+  const int w = blockIdx.x;
+  int before = 0;
+  for (int c = 0; c < B; c += 64) {
+    const int k = c == 0 ? first : keys(c + lane);
+    const int mine = (k + chunk - 1) / chunk * heads;
+    int upto = mine;
+#pragma unroll
+    for (int x = 1; x < 64; x <<= 1) {
+      const int y = __shfl_up(upto, x);
+      if (lane >= x) upto += y;
+    }
+    const unsigned long long past = __builtin_amdgcn_ballot_w64(before + upto > w);
+    if (past != 0ull) {
+      const int x = __builtin_ctzll(past);
+      p.b = c + x;
+      const int at = w - before - __builtin_amdgcn_readlane(upto - mine, x);
+      p.split = at / heads;
+      p.q = at - p.split * heads;
+      break;
+    }
+    before += __builtin_amdgcn_readlane(upto, 63);
+    if (c + 64 >= B) return false;
+  }
+  p.row = (size_t)p.b * heads + p.q;
+  const int N = __builtin_amdgcn_readfirstlane(min(max(pg.seq_lens[p.b], 1), pg.n_max));
+  if (pg.cm.b == 1 && pg.cm.stride == 0) {  // token-granular: the slots in use are one run
+    valid = min(N, pg.cm.sink + pg.cm.window);
+    segs.start[0] = 0;
+    segs.pre[1] = segs.pre[2] = segs.pre[3] = 0x7fffffff;
+  } else {
+    LgMask cm = pg.cm;
+    cm.N = N;
+    segs = lg_decode_segments(cm);
+    valid = segs.pre[segs.n];
+  }
+  p.parts = (valid + chunk - 1) / chunk;
+  p.s0 = p.split * chunk;
+  p.s1 = min(valid, p.s0 + chunk);
+  return p.s0 < valid;
+}
+
+// Called by all threads (256) of a workgroup after its stores of a part's normalised results to wk.o.  lse2(g): the
+// part's log2-sum-exp of head g < ng.  Stores them, tagged with the call's epoch, once the results have arrived in
+// memory; then reads the tagged words of all parts of the row.  The workspace comes with any contents, so only words
+// under the epoch count.  A word is in memory before the others are read: the workgroup whose words arrive last sees
+// those of all parts and adds them up; should two see them all, both write the same result.  Whoever does clears the
+// words, so that a replay of the same launch from a graph starts afresh.  (A counter per row behind compare-and-swap
+// cost a memory round trip per part in series: 55 us with 33 parts.)
+// GT: heads a record has room for; scratch: LDS, GT * LG_DEC_SPLITS_MAX floats.
+template <typename T, int D, typename LSE2>
+__device__ __forceinline__ void decode_finish(const LgDecWork& wk, const LgDecPart& p, int ng, int GT,
+                                              T* __restrict__ out, float* __restrict__ lse, size_t out_row,
+                                              float* scratch, LSE2&& lse2) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, np = p.parts;
+  const int nw = GT > 2 ? GT : 2;  // words of a record (two at least: 64 bits of tag in all)
+  lg_shared_stores_done();
+  __syncthreads();
+  if (tid < nw)
+    __hip_atomic_store(wk.word + (p.row * wk.splits + p.split) * nw + tid,
+                       ((unsigned long long)wk.epoch << 32) | __float_as_uint(lse2(min(tid, ng - 1))), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+  lg_shared_stores_done();
+  __syncthreads();
+  const size_t rec = p.row * wk.splits;
+  unsigned long long* pw = wk.word + rec * nw;
+  bool here = true;
+  for (int y = tid; y < nw * np; y += WAVES * 64) {
+    const unsigned long long w = __hip_atomic_load(pw + y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    here = here && (unsigned)(w >> 32) == wk.epoch;
+    if (y % nw < GT) scratch[y / nw * GT + y % nw] = __uint_as_float((unsigned)w);
+  }
+  if (!__syncthreads_and(here)) return;
+  const float* po = wk.o + rec * GT * D;
+  constexpr int AHEAD = 8;  // loads in flight
+  f32x2_t x[AHEAD];
+  const int e_last = ng * D / 2 - 1;
+  auto load = [&](int e, int s0) {
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) x[u] = lg_load_shared2(po + (size_t)min(s0 + u, np - 1) * GT * D + 2 * e);
+  };
+  load(min(tid, e_last), 0);  // on their way while the weights are made
+  for (int y = tid; y < nw * np; y += WAVES * 64)
+    __hip_atomic_store(pw + y, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int g = wave; g < ng; g += WAVES) {  // weights of the parts of one head
+    const float l = lane < np ? scratch[lane * GT + g] : -INFINITY;
+    float M = l;
+#pragma unroll
+    for (int y = 1; y < 64; y <<= 1) M = fmaxf(M, __shfl_xor(M, y));
+    const float w = exp2f(l - M);
+    float sum = w;
+#pragma unroll
+    for (int y = 1; y < 64; y <<= 1) sum += __shfl_xor(sum, y);
+    if (lane < np) scratch[lane * GT + g] = w / sum;
+    if (lse != nullptr && lane == 0) lse[out_row + g] = (M + log2f(sum)) * 0.69314718055994530942f;
+  }
+  __syncthreads();
+  for (int e = tid; e <= e_last; e += WAVES * 64) {
+    const int g = e / (D / 2);
+    f32x2_t acc = {0.f, 0.f};
+    for (int s0 = 0; s0 < np; s0 += AHEAD) {
+      if (e != tid || s0 > 0) load(e, s0);
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u)
+        if (s0 + u < np) {
+          const float w = scratch[(s0 + u) * GT + g];
+          acc[0] = fmaf(w, x[u][0], acc[0]);
+          acc[1] = fmaf(w, x[u][1], acc[1]);
+        }
+    }
+    store_out(out + out_row * D + 2 * e, acc[0]);
+    store_out(out + out_row * D + 2 * e + 1, acc[1]);
+  }
+}
+
+// log2-sum-exp of head g from the waves' maxima and sums
+template <int N>
+__device__ __forceinline__ float lg_lse2(const float (&sM)[WAVES][N], const float (&sL)[WAVES][N], int g) {
+  float M = -INFINITY, L = 0.f;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) M = fmaxf(M, sM[w][g]);
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) L += sL[w][g] * exp2f(sM[w][g] - M);
+  return M + log2f(L);
+}
+
+// Cache row of key `slot` of the concatenated runs.
+__device__ __forceinline__ int lg_dec_slot(const LgDecSegs& segs, int slot) {
+  int shift = segs.start[0];
+  if (slot >= segs.pre[1]) shift = segs.start[1] - segs.pre[1];
+  if (slot >= segs.pre[2]) shift = segs.start[2] - segs.pre[2];
+  if (slot >= segs.pre[3]) shift = segs.start[3] - segs.pre[3];
+  return slot + shift;
+}
+// Row of slot `slot` of sequence b in a paged pool.  (A table entry outside the pool is clamped into it: a wrong
+// result, never a stray read.)
+__device__ __forceinline__ size_t lg_dec_page_row(const LgPaged& pg, int b, int Hkv, int hk, int slot) {
+  const int page = min(max(pg.page_table[(size_t)b * pg.pages_per_seq + (slot >> pg.page_shift)], 0), pg.num_pages - 1);
+  return (((size_t)page * Hkv + hk) << pg.page_shift) + (slot & ((1 << pg.page_shift) - 1));
+}
+
+// ---------------------------------------------------------------- float32, vector ALUs
+template <int D, int GT, int MODE>
+__global__ __launch_bounds__(WAVES * 64, 2) void decode_kernel(const float* __restrict__ q,
+                                                               const float* __restrict__ kc,
+                                                               const float* __restrict__ vc,
+                                                               float* __restrict__ out, float* __restrict__ lse,
+                                                               LgDecWork wk, int Hq, int Hkv, int C, int valid,
+                                                               float scale_log2e, LgDecSegs segs, LgPaged pg) {
+  typedef float T;
   constexpr int E = 16 / sizeof(T);      // elements per 16-byte lane load
   constexpr int LPR = D / E;             // lanes per key row
   constexpr int KPW = 64 / LPR;          // key rows per wave per load
   constexpr int GROUPS = WAVES * KPW;    // lane groups per workgroup
   __shared__ float sM[WAVES][GT], sL[WAVES][GT];
   __shared__ float sO[WAVES][GT][D];
+  __shared__ float scratch[GT * LG_DEC_SPLITS_MAX];
 
   const int G = Hq / Hkv;
   const int ngc = (G + GT - 1) / GT;  // chunks of GT query heads per kv head
-  const int split = blockIdx.x;
-  const int hk = blockIdx.y / ngc, gc = blockIdx.y % ngc;
-  const int b = blockIdx.z;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int grp = wave * KPW + lane / LPR;
   const int dl = (lane % LPR) * E;  // first head-dim element of this lane
-  if (MODE == LG_DEC_PAGED) {  // this sequence's own context length, key runs and share of the keys
-    LgMask cm = pg.cm;
-    cm.N = min(max(pg.seq_lens[b], 1), pg.n_max);
-    segs = lg_decode_segments(cm);
-    valid = segs.pre[segs.n];
-    chunk = (valid + splits - 1) / splits;
-  }
-  const int s0 = split * chunk;
-  const int s1 = min(valid, s0 + chunk);
+  LgDecPart p;
+  if (!lg_dec_part<MODE>(wk, pg, Hkv * ngc, segs, valid, p)) return;
+  const int b = p.b, hk = p.q / ngc, gc = p.q % ngc;
+  const int ng = min(GT, G - gc * GT);
+  const int s0 = p.s0, s1 = p.s1;
+  const size_t out_row = (size_t)b * Hq + hk * G + gc * GT;
 
   float qf[GT][E], o[GT][E], mrun[GT], lrun[GT];
 #pragma unroll
   for (int g = 0; g < GT; ++g) {
-    const int hq = min(hk * G + gc * GT + g, Hq - 1);
-    Frag<T, E>::load(q + ((size_t)b * Hq + hq) * D + dl, qf[g]);
+    Frag<T, E>::load(q + (out_row + min(g, ng - 1)) * D + dl, qf[g]);
     mrun[g] = -INFINITY;
     lrun[g] = 0.f;
 #pragma unroll
@@ -158,20 +343,9 @@ __global__ __launch_bounds__(WAVES * 64) void decode_kernel(const T* __restrict_
       const int key = base + u * GROUPS + grp;  // index into the concatenated runs
       ok[u] = key < s1;
       int slot = ok[u] ? key : s1 - 1;
-      if (MODE != LG_DEC_PLAIN) {
-        int shift = segs.start[0];
-        if (slot >= segs.pre[1]) shift = segs.start[1] - segs.pre[1];
-        if (slot >= segs.pre[2]) shift = segs.start[2] - segs.pre[2];
-        if (slot >= segs.pre[3]) shift = segs.start[3] - segs.pre[3];
-        slot += shift;
-      }
+      if (MODE != LG_DEC_PLAIN) slot = lg_dec_slot(segs, slot);
       size_t off = (size_t)slot * D;
-      if (MODE == LG_DEC_PAGED) {
-        // (a table entry outside the pool is clamped into it: a wrong result, never a stray read)
-        const int page = min(max(pg.page_table[(size_t)b * pg.pages_per_seq + (slot >> pg.page_shift)], 0),
-                             pg.num_pages - 1);
-        off = ((((size_t)page * Hkv + hk) << pg.page_shift) + (slot & ((1 << pg.page_shift) - 1))) * D;
-      }
+      if (MODE == LG_DEC_PAGED) off = lg_dec_page_row(pg, b, Hkv, hk, slot) * D;
       Frag<T, E>::load(kbase + off, kf[u]);
       Frag<T, E>::load(vbase + off, vf[u]);
     }
@@ -197,10 +371,10 @@ __global__ __launch_bounds__(WAVES * 64) void decode_kernel(const T* __restrict_
       for (int e = 0; e < E; ++e) o[g][e] *= alpha;
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const float p = exp2f(s[u] - msafe);
-        psum += p;
+        const float pr = exp2f(s[u] - msafe);
+        psum += pr;
 #pragma unroll
-        for (int e = 0; e < E; ++e) o[g][e] = fmaf(p, vf[u][e], o[g][e]);
+        for (int e = 0; e < E; ++e) o[g][e] = fmaf(pr, vf[u][e], o[g][e]);
       }
       lrun[g] = lrun[g] * alpha + psum;
     }
@@ -235,54 +409,238 @@ __global__ __launch_bounds__(WAVES * 64) void decode_kernel(const T* __restrict_
   }
   __syncthreads();
 
-  // merge the waves; GT*D outputs spread over the workgroup
-  for (int idx = threadIdx.x; idx < GT * D; idx += WAVES * 64) {
+  // merge the waves; ng*D outputs spread over the workgroup
+  for (int idx = threadIdx.x; idx < ng * D; idx += WAVES * 64) {
     const int g = idx / D, d = idx % D;
-    const int hq = hk * G + gc * GT + g;
-    if (gc * GT + g >= G) continue;
     float M = -INFINITY;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) M = fmaxf(M, sM[w][g]);
-    const float Ms = (M == -INFINITY) ? 0.f : M;  // a split without keys (paged, short sequence)
     float L = 0.f, acc = 0.f;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) {
-      const float f = exp2f(sM[w][g] - Ms);
+      const float f = exp2f(sM[w][g] - M);
       L += sL[w][g] * f;
       acc += sO[w][g][d] * f;
     }
-    const size_t row = (size_t)b * Hq + hq;
-    if (splits == 1) {
-      store_out(out + row * D + d, acc / L);
-      if (lse != nullptr && d == 0) lse[row] = (M + log2f(L)) * 0.69314718055994530942f;
+    if (p.parts == 1) {
+      store_out(out + out_row * D + idx, acc / L);
+      if (lse != nullptr && d == 0) lse[out_row + g] = (M + log2f(L)) * 0.69314718055994530942f;
     } else {
-      float* rec = ws + (row * splits + split) * (D + 2);
-      rec[d] = acc;
-      if (d == 0) {
-        rec[D] = M;
-        rec[D + 1] = L;
-      }
+      const size_t at = (p.row * wk.splits + p.split) * GT;
+      __hip_atomic_store(wk.o + at * D + idx, acc / L, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
+  if (p.parts > 1)
+    decode_finish<T, D>(wk, p, ng, GT, out, lse, out_row, scratch, [&](int g) { return lg_lse2(sM, sL, g); });
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__(D) void decode_merge_kernel(const float* __restrict__ ws,
-                                                         T* __restrict__ out, float* __restrict__ lse,
-                                                         int splits) {
-  const size_t row = blockIdx.x;
-  const int d = threadIdx.x;
-  const float* rec = ws + row * splits * (D + 2);
-  float M = -INFINITY;
-  for (int s = 0; s < splits; ++s) M = fmaxf(M, rec[s * (D + 2) + D]);
-  float L = 0.f, acc = 0.f;
-  for (int s = 0; s < splits; ++s) {
-    const float f = exp2f(rec[s * (D + 2) + D] - M);
-    L += rec[s * (D + 2) + D + 1] * f;
-    acc += rec[s * (D + 2) + d] * f;
+// ---------------------------------------------------------------- bf16, matrix cores
+// All G <= 16 query heads of a kv head at once.  On the vector ALUs every head costs a multiply-add per element of K
+// and V and a reduction over the lanes of a row: with 8 heads that kernel ran at 1.2 TB/s, a sixth of what it reads
+// at with one.  Here a wave takes a unit of 32 keys at a time on 16x16x32 instructions:
+//   S (keys x heads) = K Q^T    A operand: lane (n, h) loads 16 bytes (dims 32 c + 8 h ..) of key row n straight from
+//                               memory; the two 16-key blocks take rows so that register r of block x at lane group h
+//                               is key 8 h + 4 x + r
+//   O^T (dims x heads) += V^T P contraction slots 8 h .. 8 h + 7 = keys 8 h .. 8 h + 7: the B operand is the lane's
+//                               own P values; for A a lane loads its VE dims of those 8 keys (whole rows over the 16
+//                               lanes) and pairs them up with byte permutes
+// No LDS on the way.  P enters the second product as three bf16 terms, which hold all 24 bits of the float32 value:
+// K, V and Q are used as stored, sums are float32.  V goes past the caches (every byte is used once); K is read in
+// half lines by two loads each, so it does not (both non-temporal: 94 instead of 86 us at 545 MB).  Bound: memory; per
+// 16 KB (D = 128) a wave spends 512 matrix and about 600 vector cycles, several times less than the bytes take.
+// Measured (vector kernel -> this): 16 x 32 heads x 4160 slots 162 -> 159 us (6.9 TB/s); 8 x 8 kv heads of 8 query heads x 3648
+// slots 101 -> 26 us; 48 sequences of 20 .. 32768 tokens, 8 kv heads of 4 query heads, paged 109 -> 77 us.
+template <int D>
+struct LgVRow;
+template <>
+struct LgVRow<128> {
+  typedef lg_u32x4 type;
+};
+template <>
+struct LgVRow<64> {
+  typedef unsigned type __attribute__((ext_vector_type(2)));
+};
+
+template <int D, int MODE>
+__global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc,
+    __hip_bfloat16* __restrict__ out, float* __restrict__ lse, LgDecWork wk, int Hq, int Hkv, int C, int valid,
+    float scale_log2e, LgDecSegs segs, LgPaged pg) {
+  constexpr int DC = D / 32, VE = D / 16;  // 32-dim contraction steps; dims per lane of a V row
+  constexpr int PAGES = 1024;              // page-table entries of a sequence kept in LDS
+  typedef typename LgVRow<D>::type vrow_t;
+  __shared__ float sO[WAVES][16][D + 4];
+  __shared__ float sM[WAVES][16], sL[WAVES][16];
+  __shared__ int spage[MODE == LG_DEC_PAGED ? PAGES : 1];
+
+  const int G = Hq / Hkv;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n = lane & 15, h = lane >> 4;
+  const int ka = 8 * (n >> 2) + (n & 3);  // this lane's key of block 0 (block 1: + 4)
+  LgDecPart p;
+  if (!lg_dec_part<MODE>(wk, pg, Hkv, segs, valid, p)) return;
+  const int b = p.b, hk = p.q;
+  const size_t out_row = (size_t)b * Hq + hk * G;
+  bf16x8_t qf[DC];
+#pragma unroll
+  for (int c = 0; c < DC; ++c) {
+    uint4 x = make_uint4(0u, 0u, 0u, 0u);
+    if (n < G) x = *reinterpret_cast<const uint4*>(q + (out_row + n) * D + 32 * c + 8 * h);
+    qf[c] = lg_as_bf16x8(x);
   }
-  store_out(out + row * D + d, acc / L);
-  if (lse != nullptr && d == 0) lse[row] = (M + log2f(L)) * 0.69314718055994530942f;
+  f32x4_t acc[VE];
+#pragma unroll
+  for (int i = 0; i < VE; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  float mref = -INFINITY, lrow = 0.f;
+
+  const size_t head = MODE == LG_DEC_PAGED ? 0 : ((size_t)b * Hkv + hk) * C * D;
+  const uint16_t* kb_ = kc + head;
+  const uint16_t* vb_ = vc + head + VE * n;
+  const int r1 = p.s1;
+  // The sequence's page-table entries go to LDS first (a table of more than PAGES entries is read in place: behind
+  // each unit's loads, which keeps the next unit's waiting).
+  const bool in_lds = MODE == LG_DEC_PAGED && pg.pages_per_seq <= PAGES;
+  if (in_lds) {
+    for (int x = tid; x < pg.pages_per_seq; x += WAVES * 64)
+      spage[x] = min(max(pg.page_table[(size_t)b * pg.pages_per_seq + x], 0), pg.num_pages - 1);
+    __syncthreads();
+  }
+  // cache row of key key0 + lane % 32 of a unit; the lanes hand them round
+  auto resolve = [&](int key0, auto IN_LDS) -> unsigned {
+    if (MODE == LG_DEC_PLAIN) return 0;
+    const int slot = lg_dec_slot(segs, min(key0 + (lane & (UNIT - 1)), r1 - 1));
+    if (MODE == LG_DEC_SEGS) return slot;
+    // (rows of a pool that fits the memory: below 2^32)
+    if (!decltype(IN_LDS)::value) return lg_dec_page_row(pg, b, Hkv, hk, slot);
+    return (((unsigned)spage[slot >> pg.page_shift] * Hkv + hk) << pg.page_shift) + (slot & ((1 << pg.page_shift) - 1));
+  };
+    struct Unit {
+      lg_u32x4 k[2][DC];
+      vrow_t v[8];
+    };
+    auto load = [&](Unit& t, int key0, unsigned rows) {
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        const unsigned r = MODE == LG_DEC_PLAIN ? (unsigned)min(key0 + ka + 4 * x, r1 - 1) : __shfl(rows, ka + 4 * x);
+#pragma unroll
+        for (int c = 0; c < DC; ++c)
+          t.k[x][c] = *reinterpret_cast<const lg_u32x4*>(kb_ + (size_t)r * D + 32 * c + 8 * h);
+      }
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const unsigned r = MODE == LG_DEC_PLAIN ? (unsigned)min(key0 + 8 * h + j, r1 - 1) : __shfl(rows, 8 * h + j);
+        t.v[j] = __builtin_nontemporal_load(reinterpret_cast<const vrow_t*>(vb_ + (size_t)r * D));
+      }
+    };
+    auto compute = [&](const Unit& t, int key0) {
+      f32x4_t s[2];
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        s[x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < DC; ++c)
+          s[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, t.k[x][c]), qf[c], s[x], 0, 0, 0);
+      }
+      float mx = -INFINITY;
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          if (key0 + 8 * h + 4 * x + r >= r1) s[x][r] = -INFINITY;
+          mx = fmaxf(mx, s[x][r]);
+        }
+      // the exponent's reference moves only when a maximum has outgrown it by 2^8
+      if (__builtin_amdgcn_ballot_w64((mx - mref) * scale_log2e > 8.0f) != 0) {
+        float mnew = fmaxf(mx, mref);
+        mnew = fmaxf(mnew, __shfl_xor(mnew, 16));
+        mnew = fmaxf(mnew, lg_other_half(mnew));
+        const float alpha = mnew == -INFINITY ? 1.f : exp2f((mref - mnew) * scale_log2e);
+        mref = mnew;
+        lrow *= alpha;
+#pragma unroll
+        for (int i = 0; i < VE; ++i) acc[i] *= alpha;
+      }
+      const float moff = mref == -INFINITY ? 0.f : mref * scale_log2e;
+      uint32_t w[3][4];  // P in three bf16 terms
+#pragma unroll
+      for (int y = 0; y < 4; ++y) {
+        float p0 = exp2f(fmaf(s[y >> 1][2 * (y & 1)], scale_log2e, -moff));
+        float p1 = exp2f(fmaf(s[y >> 1][2 * (y & 1) + 1], scale_log2e, -moff));
+        lrow += p0 + p1;
+#pragma unroll
+        for (int z = 0; z < 3; ++z) {
+          w[z][y] = lg_pack_bf16(p0, p1);
+          p0 -= __uint_as_float(w[z][y] << 16);
+          p1 -= __uint_as_float(w[z][y] & 0xffff0000u);
+        }
+      }
+      bf16x8_t pf[3];
+#pragma unroll
+      for (int z = 0; z < 3; ++z) pf[z] = lg_as_bf16x8(make_uint4(w[z][0], w[z][1], w[z][2], w[z][3]));
+#pragma unroll
+      for (int i = 0; i < VE; ++i) {  // dim VE n + i of keys 8 h .. 8 h + 7
+        uint32_t a[4];
+#pragma unroll
+        for (int y = 0; y < 4; ++y)
+          a[y] = __builtin_amdgcn_perm(t.v[2 * y + 1][i / 2], t.v[2 * y][i / 2], (i & 1) ? 0x07060302u : 0x05040100u);
+        const bf16x8_t av = lg_as_bf16x8(make_uint4(a[0], a[1], a[2], a[3]));
+#pragma unroll
+        for (int z = 0; z < 3; ++z) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, pf[z], acc[i], 0, 0, 0);
+      }
+    };
+    constexpr int STEP = UNIT * WAVES;
+    auto all_units = [&](auto IN_LDS) {
+      unsigned rows = resolve(p.s0 + UNIT * wave, IN_LDS);
+      for (int key = p.s0 + UNIT * wave; key < r1; key += STEP) {
+        Unit t;
+        load(t, key, rows);
+        rows = resolve(key + STEP, IN_LDS);
+        __builtin_amdgcn_sched_barrier(0);  // all of the unit's loads are issued before anything waits for one
+        compute(t, key);
+      }
+    };
+    if (MODE != LG_DEC_PAGED || in_lds) all_units(std::true_type{});
+    else all_units(std::false_type{});
+
+  // merge the waves: acc[i] register r is dim VE (4 h + r) + i of head n
+  lrow += __shfl_xor(lrow, 16);
+  lrow += lg_other_half(lrow);
+  if (n < G) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int i = 0; i < VE; ++i) sO[wave][n][VE * (4 * h + r) + i] = acc[i][r];
+    if (h == 0) {
+      sM[wave][n] = mref == -INFINITY ? -INFINITY : mref * scale_log2e;
+      sL[wave][n] = lrow;
+    }
+  }
+  __syncthreads();
+  for (int e = tid; e < G * D / 2; e += WAVES * 64) {
+    const int g = e / (D / 2), d = 2 * (e % (D / 2));
+    float M = -INFINITY;
+#pragma unroll
+    for (int x = 0; x < WAVES; ++x) M = fmaxf(M, sM[x][g]);
+    float L = 0.f, a0 = 0.f, a1 = 0.f;
+#pragma unroll
+    for (int x = 0; x < WAVES; ++x) {
+      const float f = exp2f(sM[x][g] - M);
+      L += sL[x][g] * f;
+      a0 += sO[x][g][d] * f;
+      a1 += sO[x][g][d + 1] * f;
+    }
+    const float inv = 1.f / L;
+    if (p.parts == 1) {
+      *reinterpret_cast<uint32_t*>(out + out_row * D + 2 * e) = lg_pack_bf16(a0 * inv, a1 * inv);
+      if (lse != nullptr && d == 0) lse[out_row + g] = (M + log2f(L)) * 0.69314718055994530942f;
+    } else {
+      const size_t at = (p.row * wk.splits + p.split) * G;
+      lg_store_shared2(wk.o + at * D + 2 * e, a0 * inv, a1 * inv);
+    }
+  }
+  if (p.parts > 1)  // (sO is free: the barrier in decode_finish comes first)
+    decode_finish<__hip_bfloat16, D>(wk, p, G, G, out, lse, out_row, &sO[0][0][0],
+                                     [&](int g) { return lg_lse2(sM, sL, g); });
 }
 
 // One thread per 16 bytes of a new token row (K and V): the token goes to its sink or ring
@@ -444,66 +802,143 @@ hipError_t launch_split_headdim(const void* q, const void* kc, const void* vc, v
   return hipGetLastError();
 }
 
+// A tag that the words of a workspace do not hold by chance: a counter from a random start.
+unsigned next_epoch() {
+  static std::atomic<unsigned> next{std::random_device{}()};
+  unsigned e;
+  do e = next.fetch_add(1, std::memory_order_relaxed);
+  while (e == 0);
+  return e;
+}
+
+// Query heads per workgroup row: all of a kv head's, or chunks of up to 8 on the vector kernel.
+int heads_per_row(int G, int dtype) {
+  if (dtype == LG_BF16 || G <= 2) return G;
+  return G <= 4 ? 4 : 8;
+}
+
+struct DecPlan {
+  int rows, most, splits, chunk;
+  size_t part_bytes;  // workspace per part: most * rows * part_bytes serves every context up to the one given
+};
+DecPlan dec_plan(int B, int Hq, int Hkv, int D, int valid, int dtype, bool paged) {
+  const int G = Hq / Hkv, gt = heads_per_row(G, dtype);
+  DecPlan p;
+  p.rows = B * Hkv * ((G + gt - 1) / gt);
+  p.part_bytes = (gt > 2 ? gt : 2) * sizeof(unsigned long long) + (size_t)gt * D * sizeof(float);
+  const int rounds = (valid + 127) / 128;  // of four units, one per wave
+  // Most parts per row: five workgroups per CU; records within LG_DECODE_STATIC_SCRATCH_BYTES as long as that leaves
+  // two workgroups per CU.  (Grows with the context, never falls: a workspace for the longest serves the shorter.)
+  const int wgs = paged ? 2048 : 1280;
+  long long most = wgs / p.rows;
+  const long long fit = (long long)(LG_DECODE_STATIC_SCRATCH_BYTES / ((size_t)p.rows * p.part_bytes));
+  if (most > fit) most = fit;
+  const int two = (511 + p.rows) / p.rows;
+  if (most < two) most = two;
+  if (most > LG_DEC_SPLITS_MAX) most = LG_DEC_SPLITS_MAX;
+  if (most > rounds) most = rounds;
+  p.most = (int)most;
+  int best_per = rounds;
+  if (paged) {
+    best_per = (rounds + p.most - 1) / p.most;
+  } else if (dtype == LG_F32) {  // the vector kernel needs two workgroups per CU, of about 256 keys or more each
+    const int n = std::max(1, std::min({(511 + p.rows) / p.rows, p.most, (valid + 255) / 256}));
+    const int step = D == 64 ? 128 : 64;  // keys that its waves take in one round
+    p.chunk = n == 1 ? valid : ((valid + n - 1) / n + step - 1) / step * step;
+    p.splits = (valid + p.chunk - 1) / p.chunk;
+    return p;
+  } else {
+    // time in us: the bytes at 6.6 GB/ms, more when the last workgroups find CUs idle or crowd them, or the rounds of
+    // one workgroup at their latency; then the sum over the parts
+    const float t_bytes = (float)p.rows * valid * (D * (dtype == LG_F32 ? 8 : 4)) / 6.6e6f;
+    float best = 0.f;
+    for (int n = 1; n <= p.most; ++n) {
+      const int per = (rounds + n - 1) / n;
+      if ((rounds + per - 1) / per != n) continue;
+      const int wg = p.rows * n, k = (wg + 255) / 256;
+      const float even = k * 256.f / wg;
+      float t = t_bytes * (1.f + 0.35f * (even - 1.f) + 0.02f * (k - 1));
+      if (t < 2.2f * per) t = 2.2f * per;
+      if (n > 1) t += 3.5f + 0.1f * n + (k > 1 ? 2.f : 0.f);
+      if (n == 1 || t < best) {
+        best = t;
+        best_per = per;
+      }
+    }
+  }
+  p.splits = (rounds + best_per - 1) / best_per;
+  p.chunk = p.splits == 1 ? valid : 128 * best_per;
+  return p;
+}
+
 template <typename T, int D>
 hipError_t launch_typed(const void* q, const void* kc, const void* vc, void* out, float* lse, void* ws,
                         int B, int Hq, int Hkv, int C, const LgDecSegs& segs, float scale, hipStream_t s,
                         const LgPaged* paged) {
-  const int valid = segs.pre[segs.n];  // paged: of the longest admissible context (sizes the split)
+  constexpr int dtype = sizeof(T) == 4 ? LG_F32 : LG_BF16;
+  const int valid = paged ? paged->keys_max : segs.pre[segs.n];
   const bool plain = segs.n == 1 && segs.start[0] == 0;
   LgPaged pg = {};
   if (paged) pg = *paged;
-  const int G = Hq / Hkv;
-  const int splits = lg_decode_splits(B, Hkv, valid);
-  const int chunk = (valid + splits - 1) / splits;
+  const int G = Hq / Hkv, gt = heads_per_row(G, dtype);
+  const DecPlan plan = dec_plan(B, Hq, Hkv, D, valid, dtype, paged != nullptr);
   const float sl2 = scale * 1.44269504088896340736f;
+  LgDecWork wk = {};
+  wk.splits = plan.splits;
+  wk.chunk = plan.chunk;
+  if (plan.splits > 1) {
+    wk.epoch = next_epoch();
+    wk.word = (unsigned long long*)ws;
+    wk.o = (float*)(wk.word + (size_t)plan.rows * plan.splits * (gt > 2 ? gt : 2));
+  }
+  dim3 grid(plan.splits, plan.rows / B, B);
+  if (paged) {
+    pg.B = B;
+    pg.few = dtype == LG_F32 ? DEC_FULL : DEC_FEW;
+    // a part per 1 / DEC_FULL of all keys, and one more per row for what is left over
+    const long long most = std::min<long long>((long long)plan.rows * plan.splits, (long long)DEC_FULL + plan.rows);
+    grid = dim3((unsigned)most);
+  }
   const T* tq = (const T*)q;
   const T* tk = (const T*)kc;
   const T* tv = (const T*)vc;
   T* to = (T*)out;
-  float* fws = (float*)ws;
-#define LG_DECODE_LAUNCH(GT)                                                                          \
-  do {                                                                                                \
-    const dim3 grid(splits, Hkv*((G + GT - 1) / GT), B);                                              \
-    if (paged)                                                                                        \
-      decode_kernel<T, D, GT, LG_DEC_PAGED><<<grid, WAVES * 64, 0, s>>>(                              \
-          tq, tk, tv, to, lse, fws, Hq, Hkv, C, valid, chunk, splits, sl2, segs, pg);                 \
-    else if (plain)                                                                                   \
-      decode_kernel<T, D, GT, LG_DEC_PLAIN><<<grid, WAVES * 64, 0, s>>>(                              \
-          tq, tk, tv, to, lse, fws, Hq, Hkv, C, valid, chunk, splits, sl2, segs, pg);                 \
-    else                                                                                              \
-      decode_kernel<T, D, GT, LG_DEC_SEGS><<<grid, WAVES * 64, 0, s>>>(                               \
-          tq, tk, tv, to, lse, fws, Hq, Hkv, C, valid, chunk, splits, sl2, segs, pg);                 \
-  } while (0)
-  if (G == 1) LG_DECODE_LAUNCH(1);
-  else if (G == 2) LG_DECODE_LAUNCH(2);
-  else if (G <= 4) LG_DECODE_LAUNCH(4);
-  else LG_DECODE_LAUNCH(8);
+  if constexpr (sizeof(T) == 2) {
+    const uint16_t *uq = (const uint16_t*)q, *uk = (const uint16_t*)kc, *uv = (const uint16_t*)vc;
+#define LG_DECODE_LAUNCH(MODE) \
+  decode_mfma_kernel<D, MODE><<<grid, WAVES * 64, 0, s>>>(uq, uk, uv, to, lse, wk, Hq, Hkv, C, valid, sl2, segs, pg)
+    if (paged) LG_DECODE_LAUNCH(LG_DEC_PAGED);
+    else if (plain) LG_DECODE_LAUNCH(LG_DEC_PLAIN);
+    else LG_DECODE_LAUNCH(LG_DEC_SEGS);
 #undef LG_DECODE_LAUNCH
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || splits == 1) return e;
-  decode_merge_kernel<T, D><<<dim3(B * Hq), D, 0, s>>>(fws, to, lse, splits);
+  } else {
+#define LG_DECODE_LAUNCH_M(GT, MODE) \
+  decode_kernel<D, GT, MODE><<<grid, WAVES * 64, 0, s>>>(tq, tk, tv, to, lse, wk, Hq, Hkv, C, valid, sl2, segs, pg)
+#define LG_DECODE_LAUNCH(GT)                             \
+  do {                                                   \
+    if (paged) LG_DECODE_LAUNCH_M(GT, LG_DEC_PAGED);     \
+    else if (plain) LG_DECODE_LAUNCH_M(GT, LG_DEC_PLAIN); \
+    else LG_DECODE_LAUNCH_M(GT, LG_DEC_SEGS);            \
+  } while (0)
+    if (gt == 1) LG_DECODE_LAUNCH(1);
+    else if (gt == 2) LG_DECODE_LAUNCH(2);
+    else if (gt == 4) LG_DECODE_LAUNCH(4);
+    else LG_DECODE_LAUNCH(8);
+#undef LG_DECODE_LAUNCH
+#undef LG_DECODE_LAUNCH_M
+  }
   return hipGetLastError();
 }
 
 }  // namespace
 
-// About two workgroups per CU (measured best at the 16 x 32 x 4160-slot workload: one
-// workgroup per (b, kv head), no merge pass), at least 256 slots each
-// and never an empty split.
-int lg_decode_splits(int B, int Hkv, int valid) {
-  const long long pairs = (long long)B * Hkv;
-  long long want = (LG_DEC_TARGET + pairs - 1) / pairs;
-  const long long cap = (valid + 255) / 256;
-  if (want > cap) want = cap;
-  if (want < 1) want = 1;
-  const int chunk = (int)((valid + want - 1) / want);
-  return (valid + chunk - 1) / chunk;
-}
+// Keys of a decode step at any context of up to m.N tokens, m from lg_make_cache_mask: at most this many.  (In block
+// mode a shorter context can have a few more than the longest.)
+int lg_decode_keys_max(const LgMask& m) { return (int)std::min<long long>(m.N, lg_cache_slots(m.N, m)); }
 
-size_t lg_decode_workspace_bytes(int B, int Hq, int Hkv, int D, int valid) {
-  const int splits = lg_decode_splits(B, Hkv, valid);
-  if (splits == 1) return 0;
-  return (size_t)B * Hq * splits * (D + 2) * sizeof(float);
+size_t lg_decode_workspace_bytes(int B, int Hq, int Hkv, int D, int valid, int dtype, bool paged) {
+  const DecPlan p = dec_plan(B, Hq, Hkv, D, valid, dtype, paged);
+  return p.most > 1 ? (size_t)p.rows * p.most * p.part_bytes : 0;
 }
 
 // paged: NULL for a contiguous cache [B, Hkv, C, D]; else page table, lengths and geometry of a
@@ -523,6 +958,7 @@ hipError_t lg_launch_decode(const void* q, const void* kc, const void* vc, void*
     pg.n_max = n_max;
     pg.num_pages = num_pages;
     pg.cm = *cache_mask;
+    pg.keys_max = lg_decode_keys_max(pg.cm);
     pp = &pg;
   }
   if (dtype == LG_F32) {

@@ -59,8 +59,8 @@ hipError_t lg_launch_bwd_bf16(const void* q, const void* k, const void* v, const
                               hipEvent_t* ev);
 
 // Decode: C = sink + window cache slots per (b, hkv), `valid` of them in use.
-int lg_decode_splits(int B, int Hkv, int valid);
-size_t lg_decode_workspace_bytes(int B, int Hq, int Hkv, int D, int valid);
+int lg_decode_keys_max(const LgMask& m);
+size_t lg_decode_workspace_bytes(int B, int Hq, int Hkv, int D, int valid, int dtype, bool paged);
 hipError_t lg_launch_decode(const void* q, const void* kc, const void* vc, void* out, float* lse,
                             void* ws, int B, int Hq, int Hkv, int C, const LgDecSegs& segs, int D,
                             int dtype, float scale, hipStream_t s, const int* page_table = nullptr,

@@ -221,3 +221,24 @@ def test_paged_generation_step_all_sequences_at_once():
         for b, p in enumerate(pos):
             assert_close(f32np(out[b]), want[b][0][0, :, p], TOL_OUT[dtype], TOL_REL[dtype], "step %d seq %d out" % (s, b))
             assert_close(f32np(lse[b]), want[b][1][0, :, p], TOL_LSE[dtype], None, "step %d seq %d lse" % (s, b))
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,D,sink,window,page_size", [
+    # parts of different sequences in one launch: more sequences than lanes; one long among short ones, sizes around the
+    # 128 keys of a round, 16 heads per kv head; a page table of more entries than a workgroup keeps at hand
+    ([1 + 37 * x % 1500 for x in range(70)], 8, 2, 64, 4, 900, 32),
+    ([6000, 1, 40, 127, 128, 129, 257], 16, 1, 128, 64, 4096, 64),
+    ([17100, 16400, 50], 2, 1, 128, 16, 17000, 16),
+])
+def test_paged_parts(lens, Hq, Hkv, D, sink, window, page_size):
+    dt = torch.bfloat16
+    n_max, table, kp, vp, ctx = paged_setup(lens, Hq, Hkv, D, sink, window, 1, 0, page_size, dt, 21)
+    for b, (q, k, v) in enumerate(ctx):
+        lg.lg_kv_paged_append(k.to(DEV), v.to(DEV), kp, vp, table[b:b + 1], torch.zeros(1, dtype=torch.int32, device=DEV),
+                              n_max, sink, window)
+    out, lse = paged_decode([q[0, :, n - 1] for (q, _, _), n in zip(ctx, lens)], kp, vp, table, lens, n_max, sink,
+                            window, 1, 0)
+    for b, ((q, k, v), n) in enumerate(zip(ctx, lens)):
+        wo, wl = O.fwd(f32np(q), f32np(k), f32np(v), sink, window, rows=(n - 1, n))
+        assert_close(f32np(out[b]), wo[0, :, n - 1], TOL_OUT[dt], TOL_REL[dt], "paged seq %d of %d out" % (b, n))
+        assert_close(f32np(lse[b]), wl[0, :, n - 1], TOL_LSE[dt], None, "paged seq %d of %d lse" % (b, n))

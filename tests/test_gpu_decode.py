@@ -57,6 +57,17 @@ def test_decode_split_and_single_pass(dtype):
     check_decode(40, 32, 32, 128, 16, 240, 7000, dtype, seed=14)    # many rows: one workgroup each
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("B,Hq,Hkv,D,window,N", [
+    # parts of a row: around the 128 keys of a round, the most parts (64) with a short last one, a whole row of several
+    # rounds per workgroup
+    (1, 16, 1, 64, 4000, 127), (1, 16, 1, 64, 4000, 129), (3, 4, 2, 128, 4000, 257), (1, 5, 1, 128, 9000, 8500),
+    (20, 32, 16, 64, 600, 5000),
+])
+def test_decode_parts(dtype, B, Hq, Hkv, D, window, N):
+    check_decode(B, Hq, Hkv, D, 4, window, N, dtype, seed=15)
+
+
 def test_decode_equals_last_row_of_prefill():
     # the ring cache built from a longer context by the slot map reproduces row N-1 of the forward
     B, Hq, Hkv, D, sink, window, N = 1, 4, 2, 128, 8, 120, 1000
