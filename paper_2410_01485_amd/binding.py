@@ -1,8 +1,10 @@
-"""ctypes binding of liblonggen_attn.so: same names as the C ABI, argument marshalling only.
+"""Binding of liblonggen_attn.so: same names as the C ABI, argument marshalling only.
 
 Tensors are torch tensors on a HIP device (contiguous, dense layouts of
 include/longgen_attn.h); their data pointers and the current stream are handed to the
-library.  Nothing here computes: a missing or unbuilt library is an error, never a fallback.
+library.  The calls a program makes per step go through the extension module _lg_bind
+(csrc/lg_bind.cpp), sizes and host-only views through ctypes.  Nothing here computes: a missing or
+unbuilt library is an error, never a fallback.
 """
 import ctypes
 import os
@@ -12,6 +14,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 # LONGGEN_ATTN_LIB: path of another build of the same library (e.g. one with sanitized host code)
 _LIB_PATH = os.environ.get("LONGGEN_ATTN_LIB") or os.path.join(_HERE, "liblonggen_attn.so")
 _lib = None
+_native = None
 
 _vp, _i, _f, _sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_float, ctypes.c_size_t
 
@@ -90,6 +93,25 @@ def lib():
     return _lib
 
 
+_ENTRIES = ("lg_sparse_attn_fwd", "lg_sparse_attn_bwd", "lg_sparse_attn_fwd_varlen", "lg_sparse_attn_bwd_varlen",
+            "lg_sparse_attn_decode", "lg_sparse_attn_decode_cache", "lg_sparse_attn_decode_cache_static",
+            "lg_kv_ring_append", "lg_sparse_attn_decode_paged", "lg_kv_paged_append")
+
+
+def _load_native():
+    """The extension module, told where the loaded library's entry points are."""
+    global _native
+    import torch
+    L = lib()
+    try:
+        from . import _lg_bind
+    except ImportError as e:
+        raise RuntimeError("_lg_bind is not built: run `python -m paper_2410_01485_amd.build`") from e
+    _lg_bind.setup({n: ctypes.cast(getattr(L, n), _vp).value for n in _ENTRIES}, torch._C._cuda_getCurrentRawStream)
+    _native = _lg_bind
+    return _lg_bind
+
+
 def status_str(status):
     return lib().lg_status_str(int(status)).decode()
 
@@ -138,14 +160,7 @@ def _ws_bytes(workspace):
 
 def lg_sparse_attn_fwd(q, k, v, out, lse, sink, window, block=1, stride=0, scale=0.0):
     """out, lse <- sparse attention forward of q [B,Hq,N,D], k,v [B,Hkv,N,D]; lse may be None."""
-    B, Hq, N, D = q.shape
-    Hkv = k.shape[1]
-    _check(q, B, Hq, N, D), _check(k, B, Hkv, N, D, like=q), _check(v, B, Hkv, N, D, like=q)
-    _check(out, B, Hq, N, D, like=q)
-    if lse is not None:
-        _check_lse(lse, B, Hq, N)
-    st = lib().lg_sparse_attn_fwd(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), B, Hq, Hkv, N, D,
-                                  sink, window, block, stride, _dtype_code(q), scale, _stream(q))
+    st = (_native or _load_native()).fwd(q, k, v, out, lse, sink, window, block, stride, scale)
     if st != 0:
         raise LgError(st, "lg_sparse_attn_fwd")
 
@@ -157,17 +172,8 @@ def bwd_workspace_bytes(B, Hq, Hkv, N, D, sink, window, block, stride, dtype):
 def lg_sparse_attn_bwd(q, k, v, out, lse, dout, dq, dk, dv, workspace, sink, window, block=1, stride=0,
                        scale=0.0):
     """dq, dk, dv <- backward of lg_sparse_attn_fwd; workspace is a uint8 device tensor."""
-    B, Hq, N, D = q.shape
-    Hkv = k.shape[1]
-    for t in (q, out, dout, dq):
-        _check(t, B, Hq, N, D, like=q)
-    for t in (k, v, dk, dv):
-        _check(t, B, Hkv, N, D, like=q)
-    _check_lse(lse, B, Hq, N)
-    st = lib().lg_sparse_attn_bwd(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), _ptr(dout), _ptr(dq),
-                                  _ptr(dk), _ptr(dv), _ptr(workspace), _ws_bytes(workspace),
-                                  B, Hq, Hkv, N, D, sink, window, block, stride, _dtype_code(q), scale,
-                                  _stream(q))
+    st = (_native or _load_native()).bwd(q, k, v, out, lse, dout, dq, dk, dv, workspace, sink, window, block, stride,
+                                         scale)
     if st != 0:
         raise LgError(st, "lg_sparse_attn_bwd")
 
@@ -203,16 +209,7 @@ def _cu_array(cu_seqlens):
 def lg_sparse_attn_fwd_varlen(q, k, v, out, lse, cu_seqlens, sink, window, block=1, stride=0, scale=0.0):
     """Forward over packed sequences: q,out [Hq,T,D], k,v [Hkv,T,D], lse [Hq,T] or None; cu_seqlens is a host
     sequence of num_seqs + 1 offsets (0 first, T last)."""
-    Hq, T, D = q.shape
-    Hkv = k.shape[0]
-    cu, ns = _cu_array(cu_seqlens)
-    if cu[ns] != T:
-        raise ValueError("cu_seqlens ends at %d, the tensors hold %d tokens" % (cu[ns], T))
-    _check(q, Hq, T, D), _check(k, Hkv, T, D, like=q), _check(v, Hkv, T, D, like=q), _check(out, Hq, T, D, like=q)
-    if lse is not None:
-        _check_lse(lse, Hq, T)
-    st = lib().lg_sparse_attn_fwd_varlen(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), cu, ns, Hq, Hkv, D,
-                                         sink, window, block, stride, _dtype_code(q), scale, _stream(q))
+    st = (_native or _load_native()).fwd_varlen(q, k, v, out, lse, cu_seqlens, sink, window, block, stride, scale)
     if st != 0:
         raise LgError(st, "lg_sparse_attn_fwd_varlen")
 
@@ -226,20 +223,8 @@ def bwd_varlen_workspace_bytes(cu_seqlens, Hq, Hkv, D, sink, window, block, stri
 def lg_sparse_attn_bwd_varlen(q, k, v, out, lse, dout, dq, dk, dv, workspace, cu_seqlens, sink, window, block=1,
                               stride=0, scale=0.0):
     """dq, dk, dv <- backward of lg_sparse_attn_fwd_varlen (same packed layout)."""
-    Hq, T, D = q.shape
-    Hkv = k.shape[0]
-    cu, ns = _cu_array(cu_seqlens)
-    if cu[ns] != T:
-        raise ValueError("cu_seqlens ends at %d, the tensors hold %d tokens" % (cu[ns], T))
-    for t in (q, out, dout, dq):
-        _check(t, Hq, T, D, like=q)
-    for t in (k, v, dk, dv):
-        _check(t, Hkv, T, D, like=q)
-    _check_lse(lse, Hq, T)
-    st = lib().lg_sparse_attn_bwd_varlen(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), _ptr(dout), _ptr(dq),
-                                         _ptr(dk), _ptr(dv), _ptr(workspace), _ws_bytes(workspace), cu, ns,
-                                         Hq, Hkv, D, sink, window, block, stride, _dtype_code(q), scale,
-                                         _stream(q))
+    st = (_native or _load_native()).bwd_varlen(q, k, v, out, lse, dout, dq, dk, dv, workspace, cu_seqlens, sink,
+                                                window, block, stride, scale)
     if st != 0:
         raise LgError(st, "lg_sparse_attn_bwd_varlen")
 
@@ -261,16 +246,8 @@ def decode_workspace_bytes(B, Hq, Hkv, N, D, sink, window, dtype):
 def lg_sparse_attn_decode(q, k_cache, v_cache, out, lse, workspace, N, sink, window, block=1, stride=0,
                           scale=0.0):
     """out, lse <- one-token attention of q [B,Hq,D] over caches [B,Hkv,sink+window,D]."""
-    B, Hq, D = q.shape
-    Hkv = k_cache.shape[1]
-    _check(q, B, Hq, D), _check(k_cache, B, Hkv, sink + window, D, like=q)
-    _check(v_cache, B, Hkv, sink + window, D, like=q), _check(out, B, Hq, D, like=q)
-    if lse is not None:
-        _check_lse(lse, B, Hq)
-    st = lib().lg_sparse_attn_decode(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(out), _ptr(lse),
-                                     _ptr(workspace), _ws_bytes(workspace),
-                                     B, Hq, Hkv, N, D, sink, window, block, stride, _dtype_code(q), scale,
-                                     _stream(q))
+    st = (_native or _load_native()).decode(q, k_cache, v_cache, out, lse, workspace, N, sink, window, block, stride,
+                                            scale)
     if st != 0:
         raise LgError(st, "lg_sparse_attn_decode")
 
@@ -282,14 +259,7 @@ def lg_kv_cache_slots(n_max, sink, window, block=1, stride=0):
 
 def lg_kv_ring_append(k_new, v_new, k_cache, v_cache, pos, sink, window, block=1, stride=0):
     """Store k_new, v_new [B,Hkv,T,D] (positions pos..pos+T-1) into caches [B,Hkv,slots,D] in place."""
-    B, Hkv, T, D = k_new.shape
-    slots = k_cache.shape[2]
-    _check(v_new, B, Hkv, T, D), _check(k_new, B, Hkv, T, D)
-    _check(k_cache, B, Hkv, slots, D), _check(v_cache, B, Hkv, slots, D)
-    if k_cache.dtype != k_new.dtype or v_cache.dtype != k_new.dtype or v_new.dtype != k_new.dtype:
-        raise TypeError("caches and new rows must share one dtype")
-    st = lib().lg_kv_ring_append(_ptr(k_new), _ptr(v_new), _ptr(k_cache), _ptr(v_cache), B, Hkv, D, T, pos, slots,
-                                 sink, window, block, stride, _dtype_code(k_new), _stream(k_new))
+    st = (_native or _load_native()).ring_append(k_new, v_new, k_cache, v_cache, pos, sink, window, block, stride)
     if st != 0:
         raise LgError(st, "lg_kv_ring_append")
 
@@ -302,31 +272,16 @@ def decode_cache_workspace_bytes(B, Hq, Hkv, N, D, sink, window, block, stride, 
 def lg_sparse_attn_decode_cache(q, k_cache, v_cache, out, lse, workspace, N, sink, window, block=1, stride=0,
                                 scale=0.0):
     """out, lse <- one-token attention of q [B,Hq,D] over caches [B,Hkv,slots,D] of any pattern."""
-    B, Hq, D = q.shape
-    Hkv, slots = k_cache.shape[1], k_cache.shape[2]
-    _check(q, B, Hq, D), _check(k_cache, B, Hkv, slots, D, like=q), _check(v_cache, B, Hkv, slots, D, like=q)
-    _check(out, B, Hq, D, like=q)
-    if lse is not None:
-        _check_lse(lse, B, Hq)
-    st = lib().lg_sparse_attn_decode_cache(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(out), _ptr(lse),
-                                           _ptr(workspace), _ws_bytes(workspace),
-                                           B, Hq, Hkv, N, D, sink, window, block, stride, slots, _dtype_code(q),
-                                           scale, _stream(q))
+    st = (_native or _load_native()).decode_cache(q, k_cache, v_cache, out, lse, workspace, N, sink, window, block,
+                                                 stride, scale)
     if st != 0:
         raise LgError(st, "lg_sparse_attn_decode_cache")
 
 
 def lg_sparse_attn_decode_cache_static(q, k_cache, v_cache, out, lse, N, sink, window, block=1, stride=0, scale=0.0):
     """lg_sparse_attn_decode_cache without a workspace argument: the library's built-in scratch array is used."""
-    B, Hq, D = q.shape
-    Hkv, slots = k_cache.shape[1], k_cache.shape[2]
-    _check(q, B, Hq, D), _check(k_cache, B, Hkv, slots, D, like=q), _check(v_cache, B, Hkv, slots, D, like=q)
-    _check(out, B, Hq, D, like=q)
-    if lse is not None:
-        _check_lse(lse, B, Hq)
-    st = lib().lg_sparse_attn_decode_cache_static(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(out), _ptr(lse),
-                                                  B, Hq, Hkv, N, D, sink, window, block, stride, slots,
-                                                  _dtype_code(q), scale, _stream(q))
+    st = (_native or _load_native()).decode_cache_static(q, k_cache, v_cache, out, lse, N, sink, window,
+                                                        block, stride, scale)
     if st != 0:
         raise LgError(st, "lg_sparse_attn_decode_cache_static")
 
@@ -336,28 +291,12 @@ def decode_paged_workspace_bytes(B, Hq, Hkv, n_max, D, sink, window, block, stri
                                                                  dtype))
 
 
-def _check_i32(t, *shape):
-    import torch
-    if t.dtype != torch.int32:
-        raise TypeError("expected an int32 tensor")
-    _check(t, *shape)
-
-
 def lg_sparse_attn_decode_paged(q, k_pages, v_pages, page_table, seq_lens, out, lse, workspace, n_max, sink, window,
                                 block=1, stride=0, scale=0.0):
     """Decode over a paged cache: k_pages, v_pages [pages, Hkv, page_size, D]; page_table [B, pages_per_seq] and
     seq_lens [B] int32 on the device."""
-    B, Hq, D = q.shape
-    num_pages, Hkv, page_size = k_pages.shape[0], k_pages.shape[1], k_pages.shape[2]
-    _check(q, B, Hq, D), _check(k_pages, num_pages, Hkv, page_size, D, like=q)
-    _check(v_pages, num_pages, Hkv, page_size, D, like=q), _check(out, B, Hq, D, like=q)
-    _check_i32(page_table, B, page_table.shape[1]), _check_i32(seq_lens, B)
-    if lse is not None:
-        _check_lse(lse, B, Hq)
-    st = lib().lg_sparse_attn_decode_paged(_ptr(q), _ptr(k_pages), _ptr(v_pages), _ptr(page_table), _ptr(seq_lens),
-                                           _ptr(out), _ptr(lse), _ptr(workspace), _ws_bytes(workspace),
-                                           B, Hq, Hkv, n_max, D, sink, window, block, stride, page_size,
-                                           page_table.shape[1], num_pages, _dtype_code(q), scale, _stream(q))
+    st = (_native or _load_native()).decode_paged(q, k_pages, v_pages, page_table, seq_lens, out, lse, workspace,
+                                                 n_max, sink, window, block, stride, scale)
     if st != 0:
         raise LgError(st, "lg_sparse_attn_decode_paged")
 
@@ -365,14 +304,8 @@ def lg_sparse_attn_decode_paged(q, k_pages, v_pages, page_table, seq_lens, out, 
 def lg_kv_paged_append(k_new, v_new, k_pages, v_pages, page_table, positions, n_max, sink, window, block=1,
                        stride=0):
     """Store k_new, v_new [B,Hkv,T,D] (sequence b: positions[b] .. +T-1) into the paged caches in place."""
-    B, Hkv, T, D = k_new.shape
-    num_pages, page_size = k_pages.shape[0], k_pages.shape[2]
-    _check(v_new, B, Hkv, T, D, like=k_new), _check(k_new, B, Hkv, T, D)
-    _check(k_pages, num_pages, Hkv, page_size, D, like=k_new), _check(v_pages, num_pages, Hkv, page_size, D, like=k_new)
-    _check_i32(page_table, B, page_table.shape[1]), _check_i32(positions, B)
-    st = lib().lg_kv_paged_append(_ptr(k_new), _ptr(v_new), _ptr(k_pages), _ptr(v_pages), _ptr(page_table),
-                                  _ptr(positions), B, Hkv, D, T, n_max, sink, window, block, stride, page_size,
-                                  page_table.shape[1], num_pages, _dtype_code(k_new), _stream(k_new))
+    st = (_native or _load_native()).paged_append(k_new, v_new, k_pages, v_pages, page_table, positions, n_max, sink,
+                                                 window, block, stride)
     if st != 0:
         raise LgError(st, "lg_kv_paged_append")
 

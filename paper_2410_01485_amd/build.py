@@ -1,4 +1,5 @@
-"""Build liblonggen_attn.so from csrc/*.hip with hipcc for gfx950 (cross-compiles without a GPU).
+"""Build liblonggen_attn.so from csrc/*.hip with hipcc for gfx950 (cross-compiles without a GPU) and the extension
+module _lg_bind.so, the tensor side of the binding, from csrc/lg_bind.cpp with g++.
 
     python -m paper_2410_01485_amd.build
 """
@@ -10,6 +11,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblonggen_attn.so")
+BIND = os.path.join(HERE, "_lg_bind.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          # packed-fp32 instructions are kept out of the generated code on purpose
@@ -28,6 +30,22 @@ SAN_COMPILE = ["-O1", "-g", "-Xarch_host", "-fsanitize=address", "-Xarch_host", 
 SAN_LINK = ["-fno-gpu-sanitize", "-fsanitize=address", "-fsanitize=undefined", "-shared-libsan"]
 
 
+def start_bind():
+    """Start compiling the extension module (host code only; torch's C++ headers, no library of ours linked)."""
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    tmp = BIND + ".tmp%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           os.path.join(CSRC, "lg_bind.cpp"), "-o", tmp, "-I", sysconfig.get_paths()["include"]]
+    for d in cpp_extension.include_paths():
+        cmd += ["-isystem", d]
+    for d in cpp_extension.library_paths():
+        cmd += ["-L", d]
+    cmd += ["-ltorch_python", "-ltorch_cpu", "-lc10"]
+    return tmp, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+
+
 def build(verbose=True, jobs=8, sanitize_host=False, out=None):
     """Compile every translation unit (in parallel) and link the shared library.
 
@@ -37,6 +55,7 @@ def build(verbose=True, jobs=8, sanitize_host=False, out=None):
     objdir = os.path.join(HERE, "_build_san" if sanitize_host else "_build")
     os.makedirs(objdir, exist_ok=True)
     flags = FLAGS + (SAN_COMPILE if sanitize_host else [])
+    bind = None if sanitize_host else start_bind()
     procs = []
     objs = []
     for src in sources():
@@ -57,8 +76,15 @@ def build(verbose=True, jobs=8, sanitize_host=False, out=None):
             print("FAILED: %s\n%s" % (src, out), file=sys.stderr)
         elif verbose and out.strip():
             print(out)
+    if bind is not None:
+        out = bind[1].communicate()[0].decode()
+        if bind[1].returncode != 0:
+            failed = True
+            print("FAILED: lg_bind.cpp\n%s" % out, file=sys.stderr)
+        else:
+            os.replace(bind[0], BIND)
     if failed:
-        raise RuntimeError("hipcc failed")
+        raise RuntimeError("compilation failed")
     tmp = lib + ".tmp%d" % os.getpid()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC"] + (SAN_LINK if sanitize_host else []) + ["-o", tmp] + objs
     if verbose:
