@@ -170,7 +170,8 @@ int lg_debug_bwd_kernel_ms(const void* q, const void* k, const void* v, const vo
  * backward enqueue one set of launches per sequence, in order, each at the sequence's own length: there
  * the launches of short sequences (under ~64K query rows x heads) do not fill the GPU.
  * The backward workspace is shared by the sequences (size = the largest any of them needs; the
- * remarks on lg_sparse_attn_bwd's workspace apply).
+ * remarks on lg_sparse_attn_bwd's workspace apply).  On the bf16 path as many sequences as fit it run
+ * side by side (its size is never below 64 MiB); a larger workspace_bytes lets more of them do so.
  * Errors, beyond the common ones: LG_ERR_NULL for cu_seqlens == NULL; LG_ERR_INVALID_ARG for
  * num_seqs < 1, cu_seqlens[0] != 0, a decreasing offset, a sequence longer than 2^30, or
  * Hq*T*D beyond 2^40 elements.  *_workspace_bytes returns 0 for invalid arguments.

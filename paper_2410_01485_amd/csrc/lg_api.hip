@@ -212,22 +212,16 @@ int lg_sparse_attn_fwd_varlen(const void* q, const void* k, const void* v, void*
     }
     return LG_OK;
   }
-  const size_t es = dtype == LG_F32 ? 4 : 2;
   for (int x = 0; x < num_seqs; ++x) {
     const int n = cu_seqlens[x + 1] - cu_seqlens[x];
     if (n == 0) continue;
     const LgShape sh = make_shape(1, Hq, Hkv, n, D, scale);
     LgMask m = lg_make_mask(n, sink, window, block, stride);
     m.ld = T;  // a head's rows of all sequences lie side by side
-    const size_t off = (size_t)cu_seqlens[x] * D * es;
-    const char* qs = (const char*)q + off;
-    const char* ks = (const char*)k + off;
-    const char* vs = (const char*)v + off;
-    char* os = (char*)out + off;
-    float* ls = lse ? lse + cu_seqlens[x] : nullptr;
-    const hipError_t e = (dtype == LG_F32)
-        ? lg_launch_fwd_f32((const float*)qs, (const float*)ks, (const float*)vs, (float*)os, ls, sh, m, s)
-        : lg_launch_fwd_bf16(qs, ks, vs, os, ls, sh, m, s);
+    const size_t off = (size_t)cu_seqlens[x] * D;
+    const hipError_t e =
+        lg_launch_fwd_f32((const float*)q + off, (const float*)k + off, (const float*)v + off, (float*)out + off,
+                          lse ? lse + cu_seqlens[x] : nullptr, sh, m, s);
     if (e != hipSuccess) return LG_ERR_LAUNCH;
   }
   return LG_OK;
@@ -266,24 +260,28 @@ int lg_sparse_attn_bwd_varlen(const void* q, const void* k, const void* v, const
                                           cu_seqlens, num_seqs, Hq, Hkv, D, sink, window, block, stride, dtype))
     return LG_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  const size_t es = dtype == LG_F32 ? 4 : 2;
+  if (dtype == LG_BF16) {
+    const LgShape sh = make_shape(1, Hq, Hkv, longest > 0 ? longest : 1, D, scale);
+    LgMask tmpl = lg_make_mask(1 << 30, sink, window, block, stride);  // as in the forward
+    tmpl.ld = T;
+    return lg_launch_bwd_bf16_pack(q, k, v, out, lse, dout, dq, dk, dv, workspace, workspace_bytes, sh, tmpl, cu_seqlens,
+                                   num_seqs, s) == hipSuccess
+               ? LG_OK
+               : LG_ERR_LAUNCH;
+  }
   for (int x = 0; x < num_seqs; ++x) {
     const int n = cu_seqlens[x + 1] - cu_seqlens[x];
     if (n == 0) continue;
     const LgShape sh = make_shape(1, Hq, Hkv, n, D, scale);
     LgMask m = lg_make_mask(n, sink, window, block, stride);
     m.ld = T;
-    const size_t off = (size_t)cu_seqlens[x] * D * es;
-    const char *qs = (const char*)q + off, *ks = (const char*)k + off, *vs = (const char*)v + off;
-    const char *os = (const char*)out + off, *gs = (const char*)dout + off;
-    char *dqs = (char*)dq + off, *dks = (char*)dk + off, *dvs = (char*)dv + off;
-    const float* ls = lse + cu_seqlens[x];
+    const size_t off = (size_t)cu_seqlens[x] * D;
     // the launches of one sequence follow those of the one before on the stream, so all of them
     // use the same workspace, each with the layout of its own length
-    const hipError_t e = (dtype == LG_F32)
-        ? lg_launch_bwd_f32((const float*)qs, (const float*)ks, (const float*)vs, (const float*)os, ls,
-                            (const float*)gs, (float*)dqs, (float*)dks, (float*)dvs, workspace, sh, m, s, nullptr)
-        : lg_launch_bwd_bf16(qs, ks, vs, os, ls, gs, dqs, dks, dvs, workspace, sh, m, s, nullptr);
+    const hipError_t e = lg_launch_bwd_f32((const float*)q + off, (const float*)k + off, (const float*)v + off,
+                                           (const float*)out + off, lse + cu_seqlens[x], (const float*)dout + off,
+                                           (float*)dq + off, (float*)dk + off, (float*)dv + off, workspace, sh, m, s,
+                                           nullptr);
     if (e != hipSuccess) return LG_ERR_LAUNCH;
   }
   return LG_OK;

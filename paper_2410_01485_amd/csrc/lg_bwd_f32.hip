@@ -565,9 +565,7 @@ hipError_t launch_bwd(const float* q, const float* k, const float* v, const floa
 
 size_t lg_bwd_workspace_bytes(const LgShape& sh, const LgMask& m, int dtype) {
   if (dtype == LG_F32) return f32_parts(sh, m).end;
-  // the bf16 path: -Delta and -lse / scale, [B, Hq, N] float32 each, rounded up to 256 bytes, then its column area
-  const size_t n = (((size_t)sh.B * sh.Hq * sh.N * sizeof(float)) + 255) & ~(size_t)255;
-  return lg_bwd_bf16_workspace_bytes(sh, m, 2 * n);
+  return lg_bwd_bf16_workspace_bytes(sh, m);
 }
 
 hipError_t lg_launch_bwd_f32(const float* q, const float* k, const float* v, const float* out,

@@ -46,7 +46,7 @@ hipError_t lg_launch_fwd_bf16_pack(const void* q, const void* k, const void* v, 
                                    const LgShape& sh, const LgMask& tmpl, const LgPack& pack, hipStream_t s);
 
 size_t lg_bwd_workspace_bytes(const LgShape& sh, const LgMask& m, int dtype);
-size_t lg_bwd_bf16_workspace_bytes(const LgShape& sh, const LgMask& m, size_t head_bytes);
+size_t lg_bwd_bf16_workspace_bytes(const LgShape& sh, const LgMask& m);
 // ev: NULL, or 4 events recorded before the set-up, before the dq kernel, before the dk/dv kernels and after the
 // last one (measurement aid).
 hipError_t lg_launch_bwd_f32(const float* q, const float* k, const float* v, const float* out,
@@ -57,6 +57,12 @@ hipError_t lg_launch_bwd_bf16(const void* q, const void* k, const void* v, const
                               const float* lse, const void* dout, void* dq, void* dk, void* dv,
                               void* ws, const LgShape& sh, const LgMask& m, hipStream_t s,
                               hipEvent_t* ev);
+// sh, tmpl: as for the packed forward.  ws_bytes: at least what the longest sequence needs; more lets more sequences
+// share a set of launches.
+hipError_t lg_launch_bwd_bf16_pack(const void* q, const void* k, const void* v, const void* out, const float* lse,
+                                   const void* dout, void* dq, void* dk, void* dv, void* ws, size_t ws_bytes,
+                                   const LgShape& sh, const LgMask& tmpl, const int* cu_seqlens, int num_seqs,
+                                   hipStream_t s);
 
 // Decode: C = sink + window cache slots per (b, hkv), `valid` of them in use.
 int lg_decode_keys_max(const LgMask& m);

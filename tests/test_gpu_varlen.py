@@ -167,6 +167,16 @@ def test_long_sequences_take_the_resident_kernels():
     check_pack([5000, 700, 9000], 2, 2, 128, 64, 4096, 1, 0, torch.bfloat16, 403, oracle_rows=2000)
 
 
+@pytest.mark.parametrize("D,lens,Hq,Hkv,sink,window,block,stride", [
+    (128, [300, 1500, 6000, 1, 0, 257, 5000, 769], 4, 2, 64, 1024, 1, 0),   # both forms of dq and dk/dv, lone columns
+    (128, [2500, 64, 4000, 700], 4, 1, 64, 256, 64, 8),                     # dq forms differ by the strided columns
+    (64, [1800, 255, 0, 3000], 2, 2, 64, 128, 64, 2),
+    (128, [5 + (37 * s) % 90 for s in range(140)], 2, 2, 4, 16, 1, 0),      # more sequences than one set of launches takes
+])
+def test_packed_backward_mix(D, lens, Hq, Hkv, sink, window, block, stride):
+    check_pack(lens, Hq, Hkv, D, sink, window, block, stride, torch.bfloat16, 407, oracle_rows=1000)
+
+
 def test_neighbours_in_the_pack_do_not_matter():
     """A sequence's results do not depend on what is packed around it: the neighbours are replaced by values
     that would wreck them if read (Inf in V, huge K, Q and dO), the middle sequence comes out bit-identical.
