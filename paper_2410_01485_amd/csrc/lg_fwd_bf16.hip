@@ -1,17 +1,24 @@
 // lg_fwd_bf16.hip — bf16 prefill forward on the gfx950 matrix cores (paper Section
 // 3.2: fused online-softmax attention that never loads key tiles whose mask is zero).
 //
-// Workgroup = 8 wavefronts = 256 query rows of one (b, hq); wave w owns 32 rows.
-// Two waves share each SIMD, so one wave's softmax (vector ALU) overlaps the other's
-// matrix work.  Per live key tile (64 keys, from the closed-form scheduler in lg_mask.h):
+// Workgroup = 4 wavefronts = 128 query rows of one (b, hq); wave w owns 32 rows.  Per live key tile
+// (64 keys, from the closed-form scheduler in lg_mask.h):
 //   S^T = K Q^T     (keys x queries): A = K rows from LDS, B = Q kept in registers
 //   online softmax  on S^T: a lane holds 32 keys of ONE query, so row max / row sum
 //                   are in-lane reductions plus one exchange with lane^32
 //   O^T += V^T P^T  (dims x queries): A = V read from LDS through the transposing
 //                   LDS load, B = P^T straight from the S^T accumulator registers
-// K and V tiles travel global -> LDS directly (no registers) into a 4-stage ring;
-// tiles t+1..t+3 are in flight while tile t is computed, one barrier per tile.
 // Masking is applied only on PARTIAL tiles.
+//
+// What bounds it, and the shape that follows.  A tile costs a wave 1024 cycles of the matrix pipe (D = 128) and about
+// as many of vector work, one after the other, so a SIMD needs several waves that are NOT in the same phase: three
+// workgroups per CU for D = 128, four for D = 64, each with barriers of its own and little LDS (two K tiles and one V
+// tile, 48 KB / 24 KB; K of tile t + 2 and V of tile t + 1 are requested as soon as tile t has left their place).
+// One workgroup of 8 waves in step (two per SIMD) with a 128 KB ring needed 30 % more cycles; 6 or 12 waves per
+// workgroup are slower as well, 6 because they do not spread evenly over four SIMDs.  Smaller workgroups also waste
+// less on short sequences.  32 heads of 128, 131072 tokens, window 4096: 9.1 -> 8.45 ms (1040 TFLOP/s, the clock now
+// settles at 1.8 GHz instead of 2.2 under the power limit); 8 x 1024 tokens: 144 -> 116 us; 2 x 16 heads of 64, 1003
+// tokens: 26 -> 18 us.
 #include "lg_kernels.h"
 #include "lg_mfma.h"
 #include "lg_swz.h"
@@ -19,10 +26,14 @@
 namespace {
 
 constexpr int TK = LG_BF16_TK;  // 64 keys per step
-constexpr int TQ = LG_BF16_TQ;  // 256 query rows per workgroup
+constexpr int TQ = 128;         // query rows per workgroup
 constexpr int NT = TQ * 2;      // threads: one wave per 32 rows
-constexpr int STAGES = 4;
-static_assert(TQ == 256 && TK == 64, "8 waves x 32 rows, 64-key tiles");
+// Waves per SIMD, and LDS operands of S requested ahead of the matrix instruction that uses them, as the registers
+// of so many waves allow (168 for D = 128, 128 for D = 64)
+template <int D>
+struct LgFwdTune {
+  static constexpr int WAVES = D == 128 ? 3 : 4, AHEAD = D == 128 ? 2 : 3;
+};
 
 // TOKEN: the pattern is token-granular without strided columns (block <= 1, stride 0).  The
 // mask fields that are then known let the compiler drop the block / stride arithmetic from
@@ -31,7 +42,7 @@ static_assert(TQ == 256 && TK == 64, "8 waves x 32 rows, 64-key tiles");
 // sequences of different lengths side by side in each head (nqt = all their query tiles; B = 1).
 struct LgNoPack {};
 template <int D, bool TOKEN, typename PackT>
-__global__ __launch_bounds__(NT) void fwd_bf16_kernel(const uint16_t* __restrict__ q,
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>::WAVES, LgFwdTune<D>::WAVES))) void fwd_bf16_kernel(const uint16_t* __restrict__ q,
                                                       const uint16_t* __restrict__ k,
                                                       const uint16_t* __restrict__ v,
                                                       uint16_t* __restrict__ out,
@@ -52,9 +63,7 @@ __global__ __launch_bounds__(NT) void fwd_bf16_kernel(const uint16_t* __restrict
   using Dma = LgDma<D, NT>;
   constexpr int DC = D / 16;            // 16-wide contraction chunks of the head dim
   constexpr int DB = D / 32;            // 32-row blocks of O^T
-  constexpr int STAGE = 2 * T::BYTES;   // K tile + V tile
-  constexpr int LPT = 2 * Dma::CH;      // direct loads per thread per tile
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[STAGES * STAGE];
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[3 * T::BYTES];  // two K tiles, a V tile
 
   // XCD-aware order: workgroup ids are dealt round-robin to the 8 XCDs, so give
   // each XCD one contiguous run of the logical (head, query tile) sequence; its L2
@@ -95,19 +104,6 @@ __global__ __launch_bounds__(NT) void fwd_bf16_kernel(const uint16_t* __restrict
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   const int qw0 = min(q0 + wave_s * 32, N - 1), qw1 = min(q0 + wave_s * 32 + 31, N - 1);  // this wave's rows
 
-  // Q fragments (B operand): lane (n, g) holds dims 16*dc + 8g .. +7 of its row.
-  bf16x8_t qf[DC];
-  {
-    const uint16_t* qr = q + qbase + (size_t)min(i, N - 1) * D + g * 8;
-#pragma unroll
-    for (int dc = 0; dc < DC; ++dc) qf[dc] = lg_as_bf16x8(*reinterpret_cast<const uint4*>(qr + dc * 16));
-    // Touch the fragments here so that the compiler's own wait for these loads sits before
-    // the tile ring starts: a wait placed inside the loop would also drain the direct loads
-    // that are meant to stay in flight.
-#pragma unroll
-    for (int dc = 0; dc < DC; ++dc) asm volatile("" ::"v"(qf[dc]));
-  }
-
   f32x16_t oacc[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db)
@@ -122,12 +118,8 @@ __global__ __launch_bounds__(NT) void fwd_bf16_kernel(const uint16_t* __restrict
   const uint32_t lds0 = (uint32_t)(uintptr_t)LG_LDS_PTR(unsigned char, smem);
   const bf16x2_t ones = {(__bf16)1.0f, (__bf16)1.0f};
 
-  auto issue = [&](int t, int stage) {
-    const size_t off = (size_t)t * TK * D;
-    dma.issue(kh + off, N - t * TK, lds0 + stage * STAGE);
-    dma.issue(vh + off, N - t * TK, lds0 + stage * STAGE + T::BYTES);
-  };
-
+  auto issue_k = [&](int t, int buf) { dma.issue(kh + (size_t)t * TK * D, N - t * TK, lds0 + buf * T::BYTES); };
+  auto issue_v = [&](int t) { dma.issue(vh + (size_t)t * TK * D, N - t * TK, lds0 + 2 * T::BYTES); };
   // ring: tiles are issued up to 3 ahead of the one being computed
   const LgQSched qs = lg_qsched_init(m, q0, q1);
   // patterns without strided columns walk the window run rotated (L2 sharing between neighbours)
@@ -137,34 +129,42 @@ __global__ __launch_bounds__(NT) void fwd_bf16_kernel(const uint16_t* __restrict
     return lg_qsched_next(m, qs, prev);
   };
   int t = next_tile(-1);  // tile to compute next
-  int t_issue = t;                           // tile to issue next
-  int ahead = 0;                             // tiles issued and not yet computed
-  for (; ahead < STAGES - 1 && t_issue >= 0; ++ahead) {
-    issue(t_issue, ahead);
-    t_issue = next_tile(t_issue);
+  int t1 = -1;
+  if (t >= 0) {
+    issue_k(t, 0);
+    t1 = next_tile(t);
+    if (t1 >= 0) issue_k(t1, 1);
+  }
+  // Q fragments (B operand): lane (n, g) holds dims 16*dc + 8g .. +7 of its row.
+  bf16x8_t qf[DC];
+  {
+    const uint16_t* qr = q + qbase + (size_t)min(i, N - 1) * D + g * 8;
+#pragma unroll
+    for (int dc = 0; dc < DC; ++dc) qf[dc] = lg_as_bf16x8(*reinterpret_cast<const uint4*>(qr + dc * 16));
+    // Touch the fragments here so that the compiler's own wait for these loads sits before
+    // the tile ring starts: a wait placed inside the loop would also drain the direct loads
+    // that are meant to stay in flight.
+#pragma unroll
+    for (int dc = 0; dc < DC; ++dc) asm volatile("" ::"v"(qf[dc]));
   }
 
-  int stage = 0;  // ring position of tile t
+  int buf = 0;
   while (t >= 0) {
-    // this wave's loads of tile t have landed once at most (ahead-1) newer tiles are pending
-    if (ahead >= 3) LG_WAIT_VMCNT(2 * LPT);
-    else if (ahead == 2) LG_WAIT_VMCNT(LPT);
+    if (t1 >= 0) LG_WAIT_VMCNT(Dma::CH);
     else LG_WAIT_VMCNT(0);
-    __syncthreads();  // everyone's loads of tile t landed; everyone is done with tile t-1
-    if (t_issue >= 0) {
-      issue(t_issue, (stage + STAGES - 1) % STAGES);  // into the stage tile t-1 just left
-      t_issue = next_tile(t_issue);
-      ++ahead;
-    }
+    __syncthreads();  // K(t) landed; everyone is done with V(t-1)
+    issue_v(t);
+    const int t2 = t1 >= 0 ? next_tile(t1) : -1;
 
     const int k0 = t * TK;
-    // A tile that is not live throughout for the workgroup's 256 rows is classified again for
+    // A tile that is not live throughout for the workgroup's 128 rows is classified again for
     // this wave's 32 rows: most waves then find it wholly live or wholly dead (they sit it out).
     int kind = LG_TILE_FULL;
     if (!lg_qsched_full(m, qs, t)) kind = lg_tile_kind(m, qw0, qw1, k0, k0 + TK - 1);
     const bool full = kind == LG_TILE_FULL;
-    const int sk = stage * STAGE;   // byte offsets of the K and V tiles inside smem
-    const int sv = sk + T::BYTES;
+    const int sk = buf * T::BYTES;   // byte offsets of the K and V tiles inside smem
+    const int sv = 2 * T::BYTES;
+    bf16x8_t pf[4];  // P^T as bf16, B operand of the second product, per 16-key group
     if (kind != LG_TILE_DEAD) {
 
     // ---- S^T = K Q^T ----
@@ -173,29 +173,21 @@ __global__ __launch_bounds__(NT) void fwd_bf16_kernel(const uint16_t* __restrict
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) sacc[kb][r] = 0.f;
-    // The K rows are requested half a product ahead of the matrix instructions that use them (the compiler
-    // on its own asks for each operand just before its use, which leaves the LDS latency in the wave's
-    // critical path eight times per tile).
+    // Each K operand is requested AHEAD matrix instructions early (the compiler on its own asks for it just before
+    // its use, which leaves the LDS latency in the wave's critical path sixteen times per tile).
     {
-      constexpr int HC = DC / 2;
-      bf16x8_t ka[2][HC], kn[2][HC];
-#pragma unroll
-      for (int dc = 0; dc < HC; ++dc)
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) ka[kb][dc] = rd.read_rows(smem, sk, kb, dc);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int dc = 0; dc < HC; ++dc) {
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) kn[kb][dc] = rd.read_rows(smem, sk, kb, HC + dc);
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) sacc[kb] = lg_mfma32(ka[kb][dc], qf[dc], sacc[kb]);
+      constexpr int NQ = 2 * DC, DIST = LgFwdTune<D>::AHEAD;
+      bf16x8_t op[DIST + 1];
+      lg_static_for<DIST>([&](auto U) {
+        constexpr int u = decltype(U)::value;
+        op[u] = rd.read_rows(smem, sk, u & 1, u >> 1);
+      });
+      lg_static_for<NQ>([&](auto U) {
+        constexpr int u = decltype(U)::value, w = u + DIST;
         __builtin_amdgcn_sched_barrier(0);
-      }
-#pragma unroll
-      for (int dc = 0; dc < HC; ++dc)
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb) sacc[kb] = lg_mfma32(kn[kb][dc], qf[HC + dc], sacc[kb]);
+        if constexpr (w < NQ) op[w % (DIST + 1)] = rd.read_rows(smem, sk, w & 1, w >> 1);
+        sacc[u & 1] = lg_mfma32(op[u % (DIST + 1)], qf[u >> 1], sacc[u & 1]);
+      });
     }
 
     // ---- online softmax (log2 domain) ----
@@ -248,7 +240,6 @@ __global__ __launch_bounds__(NT) void fwd_bf16_kernel(const uint16_t* __restrict
     }
     const float moff = (mref == -INFINITY) ? 0.f : mref * scale_log2e;
     float psum = 0.f;
-    bf16x8_t pf[4];  // P^T as bf16, B operand of the second product, per 16-key group
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -265,7 +256,11 @@ __global__ __launch_bounds__(NT) void fwd_bf16_kernel(const uint16_t* __restrict
         pf[2 * kb + h] = lg_as_bf16x8(make_uint4(w[0], w[1], w[2], w[3]));
       }
     lrow += psum;
-
+    }
+    LG_WAIT_VMCNT(0);
+    __syncthreads();  // V(t) landed; everyone is done with K(t)
+    if (t2 >= 0) issue_k(t2, buf);
+    if (kind != LG_TILE_DEAD) {
     // ---- O^T += V^T P^T ----
 #pragma unroll
     for (int c = 0; c < 4; ++c)
@@ -273,9 +268,9 @@ __global__ __launch_bounds__(NT) void fwd_bf16_kernel(const uint16_t* __restrict
       for (int db = 0; db < DB; ++db) oacc[db] = lg_mfma32(rd.read_cols(smem, sv, db, c), pf[c], oacc[db]);
     }  // kind != dead
 
-    --ahead;
-    t = next_tile(t);
-    stage = (stage + 1) % STAGES;
+    t = t1;
+    t1 = t2;
+    buf ^= 1;
   }
 
   // ---- epilogue: normalise, write O (bf16) and LSE (natural log) ----
