@@ -98,7 +98,7 @@ __global__ __launch_bounds__(512) void dq_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const uint16_t* __restrict__ out, const uint16_t* __restrict__ dout, const float* __restrict__ lse,
     float* __restrict__ ndelta, float* __restrict__ nlse, uint16_t* __restrict__ dq, int Hq, int Hkv, float scale,
-    LgMask m_in, int nqt, int total, int per_xcd, LgBwdWork wk) {
+    LgMask m_in, int nqt, int total, int run, LgBwdWork wk) {
   LgMask m = m_in;
   if (TOKEN) {
     m.b = 1;
@@ -118,7 +118,7 @@ __global__ __launch_bounds__(512) void dq_bf16_kernel(
   constexpr int LPT = 2 * Dma::CH;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[STAGES * STAGE];
 
-  const int L = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  const int L = lg_item_of(blockIdx.x, run);
   if (L >= total) return;
   // logical order: (b, kv head) slowest, then query tile (longest rows first), then the query
   // heads of the GQA group: the G workgroups that walk the same K/V tiles run side by side
@@ -1235,7 +1235,7 @@ __device__ __forceinline__ void dq_wide_item(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const uint16_t* __restrict__ out, const uint16_t* __restrict__ dout, const float* __restrict__ lse,
     float* __restrict__ ndelta, float* __restrict__ nlse, uint16_t* __restrict__ dq, int Hq, int Hkv, float scale,
-    LgMask m_in, int nqt, int total, int per_xcd, const LgBwdWork& wk, const int bid) {
+    LgMask m_in, int nqt, int total, int run, const LgBwdWork& wk, const int bid) {
   LgMask m = m_in;
   if (TOKEN) {
     m.b = 1;
@@ -1255,7 +1255,7 @@ __device__ __forceinline__ void dq_wide_item(
   constexpr int STAGE = 2 * T::BYTES;  // K tile + V tile
   __shared__ __attribute__((aligned(1024))) unsigned char smem[STAGES * STAGE];
 
-  const int L = (bid % 8) * per_xcd + bid / 8;
+  const int L = lg_item_of(bid, run);
   if (L >= total) return;
   const int G = Hq / Hkv;
   const int gq = L % G, rest = L / G;
@@ -1493,13 +1493,13 @@ __global__ __launch_bounds__(256) void dq_wide_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const uint16_t* __restrict__ out, const uint16_t* __restrict__ dout, const float* __restrict__ lse,
     float* __restrict__ ndelta, float* __restrict__ nlse, uint16_t* __restrict__ dq, int Hq, int Hkv, float scale,
-    LgMask m, int nqt, int total, int per_xcd, LgBwdWork wk, int* __restrict__ queue, int nitems) {
+    LgMask m, int nqt, int total, int run, LgBwdWork wk, int* __restrict__ queue, int nitems) {
   __shared__ int s_item;
   const int xcd = blockIdx.x & 7;
   for (;;) {
     const int id = lg_queue_take(queue, nitems, xcd, &s_item);
     if (id < 0) return;
-    dq_wide_item<TOKEN>(q, k, v, out, dout, lse, ndelta, nlse, dq, Hq, Hkv, scale, m, nqt, total, per_xcd, wk, id);
+    dq_wide_item<TOKEN>(q, k, v, out, dout, lse, ndelta, nlse, dq, Hq, Hkv, scale, m, nqt, total, run, wk, id);
   }
 }
 
@@ -1609,7 +1609,7 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
     return hipErrorInvalidDevice;
-  const long long most = 0x7fffffffLL - 8;
+  const long long most = 0x7fffffffLL - 8 * 16 * 64;  // (room for the padding of the last runs)
   if ((long long)(a.qt_wide + a.qt_rest) * Hq * a.B > most || (long long)(a.kt_wide + a.kt_rest) * Hkv * a.B > most ||
       (long long)a.citems * Hq * a.B > most)
     return hipErrorInvalidValue;
@@ -1623,22 +1623,23 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
 
   LgBwdWork wk = {packed ? seqs : nullptr, items, (int)(packed ? a.size.rows : m.N), 0};
   if (a.qt_wide > 0) {
-    const int total = a.qt_wide * Hq * a.B, per_xcd = (total + 7) / 8, nitems = per_xcd * 8;
+    const int total = a.qt_wide * Hq * a.B, run = lg_run_length(m, total, Hkv * a.B, 8 * (Hq / Hkv), packed);
+    const int nitems = (int)lg_run_grid(total, run);
     const dim3 grid((unsigned)(nitems < cus ? nitems : cus));
     if (token)
       dq_wide_bf16_kernel<true><<<grid, 256, 0, s>>>(uq, uk, uv, uo, ug, lse, ndelta, nlse, dq, Hq, Hkv, scale, m,
-                                                     a.qt_wide, total, per_xcd, wk, queue, nitems);
+                                                     a.qt_wide, total, run, wk, queue, nitems);
     else
       dq_wide_bf16_kernel<false><<<grid, 256, 0, s>>>(uq, uk, uv, uo, ug, lse, ndelta, nlse, dq, Hq, Hkv, scale, m,
-                                                      a.qt_wide, total, per_xcd, wk, queue, nitems);
+                                                      a.qt_wide, total, run, wk, queue, nitems);
   }
   if (a.qt_rest > 0) {
-    const int total = a.qt_rest * Hq * a.B, per_xcd = (total + 7) / 8;
-    const dim3 grid((unsigned)(per_xcd * 8));
+    const int total = a.qt_rest * Hq * a.B, run = lg_run_length(m, total, Hkv * a.B, 8 * (Hq / Hkv), packed);
+    const dim3 grid((unsigned)lg_run_grid(total, run));
     wk.qt_first = a.qt_wide;
 #define LG_DQ_LAUNCH(DD, TT)                                                                                           \
   dq_bf16_kernel<DD, TT><<<grid, 512, 0, s>>>(uq, uk, uv, uo, ug, lse, ndelta, nlse, dq, Hq, Hkv, scale, m, a.qt_rest, \
-                                              total, per_xcd, wk)
+                                              total, run, wk)
     if (a.D == 64) {
       if (token) LG_DQ_LAUNCH(64, true);
       else LG_DQ_LAUNCH(64, false);

@@ -36,7 +36,7 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void dq_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
     const float* __restrict__ out, const float* __restrict__ dout, const float* __restrict__ lse,
     float* __restrict__ delta, float* __restrict__ dq, int Hq, int Hkv, float scale, LgMask m, int nqt, int total,
-    int per_xcd, unsigned* __restrict__ arrived, int ncounters) {
+    int run, unsigned* __restrict__ arrived, int ncounters) {
   using T = LgF32Tile<D>;
   using Dma = LgTileDma<T, NT>;
   constexpr int TQ = LG_F32_TQ, TK = LG_F32_TK, DC = D / 16;
@@ -45,7 +45,7 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void dq_f32_kernel(
 
   const int tid = threadIdx.x;
   for (long long x = (long long)blockIdx.x * NT + tid; x < ncounters; x += (long long)gridDim.x * NT) arrived[x] = 0u;
-  const int L = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  const int L = lg_item_of(blockIdx.x, run);
   if (L >= total) return;
   const int G = Hq / Hkv;
   const int gq = L % G, rest = L / G;
@@ -548,9 +548,9 @@ hipError_t launch_bwd(const float* q, const float* k, const float* v, const floa
     (void)hipEventRecord(ev[0], s);
     (void)hipEventRecord(ev[1], s);
   }
-  const int total = (int)tl, per_xcd = (total + 7) / 8;
-  dq_f32_kernel<D><<<dim3(per_xcd * 8), NT, 0, s>>>(q, k, v, out, dout, lse, delta, dq, sh.Hq, sh.Hkv, sh.scale, m,
-                                                    pt.nqt, total, per_xcd, arrived, (int)ncnt);
+  const int total = (int)tl, run = lg_run_length(m, total, sh.B * sh.Hkv, 4 * (sh.Hq / sh.Hkv), false);
+  dq_f32_kernel<D><<<dim3((unsigned)lg_run_grid(total, run)), NT, 0, s>>>(q, k, v, out, dout, lse, delta, dq, sh.Hq, sh.Hkv, sh.scale, m,
+                                                    pt.nqt, total, run, arrived, (int)ncnt);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (ev) (void)hipEventRecord(ev[2], s);

@@ -48,7 +48,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
                                                       uint16_t* __restrict__ out,
                                                       float* __restrict__ lse, int Hq, int Hkv,
                                                       float scale_log2e, LgMask m_in, int nqt,
-                                                      int total, int per_xcd, PackT pack) {
+                                                      int total, int run, PackT pack) {
   constexpr bool PACK = !__is_same(PackT, LgNoPack);
   LgMask m = m_in;
   if (TOKEN) {
@@ -65,10 +65,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
   constexpr int DB = D / 32;            // 32-row blocks of O^T
   __shared__ __attribute__((aligned(1024))) unsigned char smem[3 * T::BYTES];  // two K tiles, a V tile
 
-  // XCD-aware order: workgroup ids are dealt round-robin to the 8 XCDs, so give
-  // each XCD one contiguous run of the logical (head, query tile) sequence; its L2
-  // then sees neighbouring query tiles, whose key windows overlap.
-  const int L = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  const int L = lg_item_of(blockIdx.x, run);
   if (L >= total) return;
   // logical order: (b, kv head) slowest, then query tile (longest rows first), then the query
   // heads of the GQA group: the G workgroups that walk the same K/V tiles run side by side
@@ -300,14 +297,14 @@ hipError_t lg_launch_fwd_bf16(const void* q, const void* k, const void* v, void*
   const long long total_ll = (long long)nqt * sh.Hq * sh.B;
   if (total_ll > 0x7fffffffLL - 8) return hipErrorInvalidValue;
   const int total = (int)total_ll;
-  const int per_xcd = (total + 7) / 8;
+  const int run = lg_run_length(m, total, sh.B * sh.Hkv, 16 * (sh.Hq / sh.Hkv), false);
   const float sl2 = sh.scale * 1.44269504088896340736f;
-  const dim3 grid(per_xcd * 8);
+  const dim3 grid((unsigned)lg_run_grid(total, run));
   const bool token = m.b == 1 && m.stride == 0;
 #define LG_FWD_LAUNCH(DD, TT)                                                                            \
   fwd_bf16_kernel<DD, TT, LgNoPack><<<grid, NT, 0, s>>>((const uint16_t*)q, (const uint16_t*)k,          \
                                                         (const uint16_t*)v, (uint16_t*)out, lse, sh.Hq,  \
-                                                        sh.Hkv, sl2, m, nqt, total, per_xcd, LgNoPack{})
+                                                        sh.Hkv, sl2, m, nqt, total, run, LgNoPack{})
   if (sh.D == 64) {
     if (token) LG_FWD_LAUNCH(64, true);
     else LG_FWD_LAUNCH(64, false);
@@ -336,14 +333,14 @@ hipError_t lg_launch_fwd_bf16_pack(const void* q, const void* k, const void* v, 
   const long long total_ll = (long long)nqt * sh.Hq;
   if (nqt < 1 || total_ll > 0x7fffffffLL - 8) return hipErrorInvalidValue;
   const int total = (int)total_ll;
-  const int per_xcd = (total + 7) / 8;
+  const int run = lg_run_length(tmpl, total, sh.Hkv, 16 * (sh.Hq / sh.Hkv), true);
   const float sl2 = sh.scale * 1.44269504088896340736f;
-  const dim3 grid(per_xcd * 8);
+  const dim3 grid((unsigned)lg_run_grid(total, run));
   const bool token = tmpl.b == 1 && tmpl.stride == 0;
 #define LG_FWD_LAUNCH(DD, TT)                                                                          \
   fwd_bf16_kernel<DD, TT, LgPack><<<grid, NT, 0, s>>>((const uint16_t*)q, (const uint16_t*)k,          \
                                                       (const uint16_t*)v, (uint16_t*)out, lse, sh.Hq,  \
-                                                      sh.Hkv, sl2, tmpl, nqt, total, per_xcd, pack)
+                                                      sh.Hkv, sl2, tmpl, nqt, total, run, pack)
   if (sh.D == 64) {
     if (token) LG_FWD_LAUNCH(64, true);
     else LG_FWD_LAUNCH(64, false);

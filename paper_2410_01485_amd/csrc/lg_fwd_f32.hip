@@ -27,14 +27,14 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_f32_kernel(const floa
                                                                       float* __restrict__ out,
                                                                       float* __restrict__ lse, int Hq, int Hkv,
                                                                       float scale, LgMask m, int nqt, int total,
-                                                                      int per_xcd) {
+                                                                      int run) {
   using T = LgF32Tile<D>;
   using Dma = LgTileDma<T, NT>;
   constexpr int DC = D / 16;
   constexpr int STAGE = 2 * T::BYTES, LPT = 2 * Dma::CH;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * STAGE];
 
-  const int L = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;  // XCD-contiguous, as the bf16 kernels
+  const int L = lg_item_of(blockIdx.x, run);
   if (L >= total) return;
   const int G = Hq / Hkv;
   const int gq = L % G, rest = L / G;
@@ -201,11 +201,11 @@ hipError_t lg_launch_fwd_f32(const float* q, const float* k, const float* v, flo
   const int nqt = (sh.N + TQ - 1) / TQ;
   const long long tl = (long long)nqt * sh.Hq * sh.B;
   if (tl > 0x7fffffffLL - 8) return hipErrorInvalidValue;
-  const int total = (int)tl, per_xcd = (total + 7) / 8;
-  const dim3 grid(per_xcd * 8);
+  const int total = (int)tl, run = lg_run_length(m, total, sh.B * sh.Hkv, 4 * (sh.Hq / sh.Hkv), false);
+  const dim3 grid((unsigned)lg_run_grid(total, run));
   if (sh.D == 64)
-    fwd_f32_kernel<64><<<grid, NT, 0, s>>>(q, k, v, out, lse, sh.Hq, sh.Hkv, sh.scale, m, nqt, total, per_xcd);
+    fwd_f32_kernel<64><<<grid, NT, 0, s>>>(q, k, v, out, lse, sh.Hq, sh.Hkv, sh.scale, m, nqt, total, run);
   else
-    fwd_f32_kernel<128><<<grid, NT, 0, s>>>(q, k, v, out, lse, sh.Hq, sh.Hkv, sh.scale, m, nqt, total, per_xcd);
+    fwd_f32_kernel<128><<<grid, NT, 0, s>>>(q, k, v, out, lse, sh.Hq, sh.Hkv, sh.scale, m, nqt, total, run);
   return hipGetLastError();
 }

@@ -103,6 +103,25 @@ LG_HD bool lg_live(const LgMask& m, int i, int j) {
   return m.stride > 0 && lg_strided(m, kb);
 }
 
+// ---------------------------------------------------------------------------------
+// Which item of a kernel's list workgroup `id` takes.  Workgroup ids are dealt round-robin to the 8 XCDs; each XCD gets
+// runs of `run` consecutive items, so that its L2 sees neighbouring tiles, whose windows overlap, dealt in turn.
+LG_HD int lg_item_of(int id, int run) {
+  const int x = id >> 3;
+  return (x / run * 8 + (id & 7)) * run + x % run;
+}
+// The run length for `total` items listed head by head (heads: batch x kv heads), and the workgroups that cover them.
+// One run per XCD shares most, and is even where every XCD gets whole heads or the rows cost about the same (a window
+// well below the length, no strided columns).  Otherwise (causal or strided rows that grow along the sequence; packed
+// sequences: m.N is a length none reaches, varied = true) the XCD with the longest rows would run almost twice as long
+// as the average, and runs of `few` items are dealt.
+LG_HD int lg_run_length(const LgMask& m, int total, int heads, int few, bool varied) {
+  const int each = (total + 7) / 8;
+  const bool even = heads % 8 == 0 || (!varied && m.stride == 0 && m.window <= m.N / 4);
+  return even || few >= each ? each : few;
+}
+LG_HD long long lg_run_grid(int total, int run) { return ((long long)total + 8LL * run - 1) / (8LL * run) * (8LL * run); }
+
 enum { LG_TILE_DEAD = 0, LG_TILE_PARTIAL = 1, LG_TILE_FULL = 2 };
 
 // Classify the tile of query rows [q0, q1] x keys [k0, k1] (inclusive bounds).
