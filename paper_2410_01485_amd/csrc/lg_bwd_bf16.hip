@@ -51,19 +51,44 @@ struct LgBwdSeqs {
   int wrow0[LG_PACK_MAX];         // ... and of the workspace's per-row arrays
   int len[LG_PACK_MAX];
   int ncol[LG_PACK_MAX];          // column groups split off (0: none)
+  int nlone[LG_PACK_MAX];         // exactly one group: chunks of its column part (0 otherwise)
   int qtile0[LG_PACK_MAX + 1];    // query tiles (LG_BF16_TQ rows) of the sequences before
   int ktile0[LG_PACK_MAX + 1];    // key tiles (LG_BF16_BTK keys)
   int grp0[LG_PACK_MAX + 1];      // 64-key groups: offset into col_of_group
   int col0[LG_PACK_MAX + 1];      // split-off column groups: offset into col_list and the partial sums
-  int citem0[LG_PACK_MAX + 1];    // column work items (virtual tile x chunk)
+  int citem0[LG_PACK_MAX + 1];    // column work items (virtual tile x chunk), sequences with several groups
+  int litem0[LG_PACK_MAX + 1];    // column work items (chunk), sequences with one group
 };
 
-// What tells a kernel which sequence and tile a work item is.
+// What tells a kernel which sequence and tile a work item is, and where partial sums are.
 struct LgBwdWork {
   const LgBwdSeqs* seqs;  // nullptr: a batch of sequences of one length
-  const int* items;       // packed dk/dv: item id -> (sequence << 24 | key tile) for id / Hkv, kv head id % Hkv
+  const int* items;       // packed dk/dv: (sequence << 24 | key tile)
+  int B;
   int wld;                // rows from one head to the next in the workspace's per-row arrays
   int qt_first;           // packed dq: the launch's first query tile
+  // column parts (see the dk/dv section)
+  const int* col_of_group;
+  const int* col_list;
+  int ncol;               // split-off column groups of a head, of all packed sequences together
+  int nlone;              // batch: chunks of a lone group's column part
+  int chunk;              // query tiles per column work item where there are several groups
+  float* colpart;         // [b x kv head][ncol] sums, one group slot each
+  float* lonepart;        // Hq == Hkv: [b x kv head][lone chunks of all sequences] group slots
+  int nlone_all;          // lone chunks of all sequences
+  unsigned* arrived;      // Hq == Hkv: [b x kv head][sequence] chunks of a lone group that are done
+  // window parts cut into `heads_cut` sets of query heads times `rows_cut` runs of query tiles
+  int heads_cut, rows_cut;
+  float* parts;           // [key tile][b x kv head][part] four group slots each
+};
+
+// Partial sums are kept the way the accumulators hold them, 64 keys ("group slot") at a time: [32-key block][dk, dv]
+// [32-dim block][register][lane] floats, so that every store, load or atomic of a wave covers 256 consecutive bytes.
+template <int D>
+struct LgSlot {
+  static constexpr int DB = D / 32;
+  static constexpr int FLOATS = 64 * D * 2;
+  __device__ __forceinline__ static int at(int kb, int which, int db) { return ((kb * 2 + which) * DB + db) * 1024; }
 };
 
 // The sequence that owns position t, given the n non-decreasing starts: the last one that starts at or before t.
@@ -286,18 +311,13 @@ __global__ __launch_bounds__(512) void dq_bf16_kernel(
 // Column keys (sink tokens, keys of strided block columns) are seen by every later query.
 // The query range of a key tile therefore has a dense window part (like every tile) and, if it
 // holds column keys, a long column part: all later rows, but only its column keys live.
-// With one column group per head (the sink of a sink + window pattern) and no GQA the tile that
-// holds it simply runs its whole range and is launched first.  Otherwise (strided patterns, or G
-// query heads per kv head, which one workgroup would have to walk one after the other) the column
-// parts are split off: the COLUMN instance of the kernel packs the 64-key column groups four at
-// a time into virtual 256-key tiles, so that all 8 waves have live keys and a Q / dO tile is
-// used by 256 keys again, cuts their query range into chunks of LG_COL_CHUNK tiles that run as
-// separate workgroups, and adds float32 partial sums into the workspace with hardware atomics
-// (their order is not fixed, so the last bits of dk/dv of column keys can differ from run to
-// run).  The main instance then handles the window part of every tile and folds the partial
-// sums in before it rounds to bf16.  bwd_setup_kernel lists the column groups once per call.
-constexpr int LG_COL_CHUNK = 64;  // query tiles (64 rows each) per column workgroup
-
+// The column parts are split off.  Where there are several column groups of 64 keys (strided patterns), the COLUMN
+// instance of the kernel packs them four at a time into virtual 256-key tiles, so that all 8 waves have live keys and
+// a Q / dO tile is used by 256 keys again, cuts their query range into chunks that run as separate workgroups, and adds
+// float32 sums into the workspace with hardware atomics (their order is not fixed, so the last bits of dk/dv of column
+// keys can differ from run to run).  A lone group (the sink of a sink + window pattern) has a kernel of its own
+// (dkdv_lone_bf16_kernel), without atomics where Hq == Hkv.  The main instance then handles the window part of every
+// tile and folds the sums in before it rounds to bf16.  bwd_setup_kernel lists the column groups once per call.
 // What the kernels below find in the workspace, written in one launch: the work queues' counters and the partial sums
 // of the column parts cleared, the column tables, and for packed sequences their descriptor and the dk/dv work items.
 //   col_of_group[c] = index of 64-key group c among the column groups, or -1; col_list = inverse
@@ -305,7 +325,7 @@ constexpr int LG_COL_CHUNK = 64;  // query tiles (64 rows each) per column workg
 //          the end of their sequence, which the most query tiles see, come first
 struct LgBwdSetup {
   int n, nwide;  // packed sequences, longest first, and how many of them take the 64-keys-per-wave dk/dv kernel; n = 0: batch
-  int row0[LG_PACK_MAX], len[LG_PACK_MAX], ncol[LG_PACK_MAX], citems[LG_PACK_MAX];
+  int row0[LG_PACK_MAX], len[LG_PACK_MAX], ncol[LG_PACK_MAX], citems[LG_PACK_MAX], nlone[LG_PACK_MAX];
 };
 constexpr int SETUP_NT = 512;
 
@@ -338,7 +358,8 @@ __device__ void column_table(int* __restrict__ col_of_group, int* __restrict__ c
 __global__ __launch_bounds__(SETUP_NT) void bwd_setup_kernel(LgBwdSetup a, LgMask m, int* __restrict__ queue,
                                                              LgBwdSeqs* __restrict__ seqs, int* __restrict__ items,
                                                              int* __restrict__ col_of_group, int* __restrict__ col_list,
-                                                             int ncol, float* __restrict__ part, size_t part_floats) {
+                                                             int ncol, unsigned* __restrict__ arrived, int narrived,
+                                                             float* __restrict__ part, size_t part_floats) {
   const int tid = threadIdx.x, nt = a.n > 0 ? a.n : 1;
   if ((int)blockIdx.x > nt) {  // (device-scope stores: atomics of every XCD add to these values)
     const size_t step = (size_t)(gridDim.x - 1 - nt) * SETUP_NT;
@@ -346,16 +367,20 @@ __global__ __launch_bounds__(SETUP_NT) void bwd_setup_kernel(LgBwdSetup a, LgMas
       lg_store_shared2(part + 2 * x, 0.f, 0.f);
     return;
   }
-  if (blockIdx.x == 0 && tid < 16) queue[tid] = 0;
+  if (blockIdx.x == 0) {
+    if (tid < 16) queue[tid] = 0;
+    for (int x = tid; x < narrived; x += SETUP_NT) arrived[x] = 0;
+  }
   if (a.n == 0) {
     if (blockIdx.x == 1 && ncol > 0) column_table(col_of_group, col_list, m);
     return;
   }
   // running sums over the sequences: query tiles, key tiles, groups, split-off column groups, column work items, rows
-  __shared__ int sum[6][LG_PACK_MAX + 1];
+  // and chunks of lone groups
+  __shared__ int sum[7][LG_PACK_MAX + 1];
   static_assert(SETUP_NT >= LG_PACK_MAX + 1, "a thread per sequence");
   const int len = tid < a.n ? a.len[tid] : 0;
-  if (tid < 6) sum[tid][0] = 0;
+  if (tid < 7) sum[tid][0] = 0;
   if (tid < LG_PACK_MAX) {
     sum[0][tid + 1] = (len + LG_BF16_TQ - 1) / LG_BF16_TQ;
     sum[1][tid + 1] = (len + LG_BF16_BTK - 1) / LG_BF16_BTK;
@@ -363,14 +388,15 @@ __global__ __launch_bounds__(SETUP_NT) void bwd_setup_kernel(LgBwdSetup a, LgMas
     sum[3][tid + 1] = tid < a.n ? a.ncol[tid] : 0;
     sum[4][tid + 1] = tid < a.n ? a.citems[tid] : 0;
     sum[5][tid + 1] = len;
+    sum[6][tid + 1] = tid < a.n ? a.nlone[tid] : 0;
   }
   __syncthreads();
   for (int d = 1; d < LG_PACK_MAX; d <<= 1) {
-    int y[6];
-    for (int x = 0; x < 6; ++x) y[x] = tid < LG_PACK_MAX && tid + 1 > d ? sum[x][tid + 1 - d] : 0;
+    int y[7];
+    for (int x = 0; x < 7; ++x) y[x] = tid < LG_PACK_MAX && tid + 1 > d ? sum[x][tid + 1 - d] : 0;
     __syncthreads();
     if (tid < LG_PACK_MAX)
-      for (int x = 0; x < 6; ++x) sum[x][tid + 1] += y[x];
+      for (int x = 0; x < 7; ++x) sum[x][tid + 1] += y[x];
     __syncthreads();
   }
   if (blockIdx.x > 0) {
@@ -385,6 +411,7 @@ __global__ __launch_bounds__(SETUP_NT) void bwd_setup_kernel(LgBwdSetup a, LgMas
     seqs->wrow0[tid] = sum[5][tid];
     seqs->len[tid] = len;
     seqs->ncol[tid] = a.ncol[tid];
+    seqs->nlone[tid] = a.nlone[tid];
   }
   if (tid <= a.n) {
     seqs->qtile0[tid] = sum[0][tid];
@@ -392,6 +419,7 @@ __global__ __launch_bounds__(SETUP_NT) void bwd_setup_kernel(LgBwdSetup a, LgMas
     seqs->grp0[tid] = sum[2][tid];
     seqs->col0[tid] = sum[3][tid];
     seqs->citem0[tid] = sum[4][tid];
+    seqs->litem0[tid] = sum[6][tid];
   }
   for (int t = tid; t < sum[1][a.n]; t += SETUP_NT) {
     int lo = 0, hi = a.n;  // the sequence of key tile t
@@ -414,46 +442,127 @@ __global__ __launch_bounds__(SETUP_NT) void bwd_setup_kernel(LgBwdSetup a, LgMas
   }
 }
 
-// Adds a 32 x 32 accumulator block (lane (n, g), register r <-> row n, column 8 (r / 4) + 4 g + r % 4)
-// to dst[row * ld + column], rows below nrows only, with float32 atomics.  The block is turned
-// through 4 KB of LDS that belong to the calling wave (16-byte chunks XOR-swizzled by row), so that
-// one atomic instruction adds two whole rows of 32 consecutive floats -- two cache lines --
-// instead of two floats in each of 32 lines, which is what bounds the column instances otherwise.
-template <typename Acc>
-__device__ __forceinline__ void lg_atomic_add_block(float* tr, const Acc& acc, float* dst, int ld, int nrows,
-                                                    int n, int g) {
-#pragma unroll
-  for (int r4 = 0; r4 < 4; ++r4)
-    *reinterpret_cast<float4*>(tr + n * 32 + 4 * ((2 * r4 + g) ^ (n & 7))) =
-        make_float4(acc[4 * r4], acc[4 * r4 + 1], acc[4 * r4 + 2], acc[4 * r4 + 3]);
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (one wave: its LDS accesses complete in order)
-#pragma unroll
-  for (int it = 0; it < 16; ++it) {
-    const int row = 2 * it + g;
-    const float x = tr[row * 32 + 4 * ((n >> 2) ^ (row & 7)) + (n & 3)];
-    if (row < nrows) unsafeAtomicAdd(dst + (size_t)row * ld + n, x);  // hardware float add in L2
-  }
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-}
-
-// The sequence of a dk/dv work item: where its rows and column groups start, how many groups are split off.
+// The sequence of a dk/dv work item: where its rows, key tiles and column groups start, how many groups are split off.
 struct LgBwdItem {
-  int row0, wrow0, grp0, col0, ncol;
+  int row0, wrow0, ktile0, grp0, col0, ncol;
 };
 __device__ __forceinline__ LgBwdItem lg_bwd_item(const LgBwdSeqs* __restrict__ seqs, int sq, LgMask& m) {
   m = lg_mask_for_length(m, lg_uniform(seqs->len[sq]));
-  return {lg_uniform(seqs->row0[sq]), lg_uniform(seqs->wrow0[sq]), lg_uniform(seqs->grp0[sq]),
-          lg_uniform(seqs->col0[sq]), lg_uniform(seqs->ncol[sq])};
+  return {lg_uniform(seqs->row0[sq]), lg_uniform(seqs->wrow0[sq]), lg_uniform(seqs->ktile0[sq]),
+          lg_uniform(seqs->grp0[sq]), lg_uniform(seqs->col0[sq]), lg_uniform(seqs->ncol[sq])};
 }
 
-// ncol_all: column groups handled by the COLUMN instance (0: none are split off), of all packed sequences together
+// A main work item: key tile, (b, kv head) and part of the window part.  One part, a batch: all items in runs per XCD
+// (lg_item_of), so that neighbouring key tiles share their Q / dO rows in one XCD's L2.  Otherwise kv heads innermost
+// (with a multiple of 8 of them all key tiles of a head run on one XCD), packed sequences in the order of the item
+// list.  False: an id of the padding.
+struct LgBwdMain {
+  int kt, bh, part;
+};
+__device__ __forceinline__ bool lg_bwd_main(const LgBwdWork& wk, int bid, int nkt, int total, int run, LgMask& m,
+                                            LgBwdItem& it, LgBwdMain& w) {
+  const int nbh = total / nkt, nparts = wk.heads_cut * wk.rows_cut;
+  w.part = 0;
+  if (wk.seqs || nparts > 1) {
+    w.bh = bid % nbh;
+    const int y = bid / nbh;
+    w.part = y % nparts;
+    w.kt = y / nparts;
+    if (wk.seqs) {
+      const int x = lg_uniform(wk.items[w.kt]);
+      w.kt = x & 0xffffff;
+      it = lg_bwd_item(wk.seqs, x >> 24, m);
+    }
+    return true;
+  }
+  const int L = lg_item_of(bid, run);
+  w.bh = L / nkt;
+  w.kt = L % nkt;
+  return L < total;
+}
+// The query tiles [lo, hi] and query heads of the part: the window part of keys [k0, k1] (all query tiles that see them
+// where no column parts are split off), rows and heads cut evenly.
+__device__ __forceinline__ void lg_bwd_part_range(const LgBwdWork& wk, const LgMask& m, bool split, int k0, int k1, int part,
+                                                  int G, int* lo, int* hi, int* head0, int* nheads) {
+  lg_qtile_range(m, k0, k1, LG_BF16_BTQ, lo, hi);
+  if (split) *hi = lg_qtile_window_hi(m, k1, LG_BF16_BTQ);
+  *nheads = G / wk.heads_cut;
+  *head0 = part / wk.rows_cut * *nheads;
+  const int c = part % wk.rows_cut, len = *hi - *lo + 1, first = *lo;
+  *lo = first + len * c / wk.rows_cut;
+  *hi = first + len * (c + 1) / wk.rows_cut - 1;
+}
+// Where a part's sums go: four group slots.
+template <int D>
+__device__ __forceinline__ float* lg_bwd_part_slot(const LgBwdWork& wk, const LgBwdItem& it, const LgBwdMain& w,
+                                                   int nbh) {
+  return wk.parts + (((size_t)(it.ktile0 + w.kt) * nbh + w.bh) * (wk.heads_cut * wk.rows_cut) + w.part) *
+                        (4 * LgSlot<D>::FLOATS);
+}
+
+// 32 query rows against the wave's 32 keys, in an order that keeps few values alive at a time:
+// S -> P -> (dV += dO^T P) -> dP -> dS -> (dK += Q^T dS).  sq, sg: the rows of Q and dO in LDS; sL: their -lse / scale,
+// 64 floats further on their -Delta; voff: the V rows of the wave's keys.
+template <int D, typename Dead>
+__device__ __forceinline__ void lg_dkdv_block(const unsigned char* smem, const LgSwzReader<D>& rd, int sq, int sg, int voff,
+                                              const float* sL, const bf16x8_t (&kf)[D / 16], f32x16_t (&ak)[D / 32],
+                                              f32x16_t (&av)[D / 32], float sl2, int g, bool full, Dead dead) {
+  constexpr int DC = D / 16, DB = D / 32;
+  float p[16];
+  __builtin_amdgcn_sched_barrier(0);  // phases stay apart: bounds the operands held at once
+  {
+    // the accumulator starts from -lse / scale of its rows (register r <-> row 8 (r / 4) + 4g + r % 4)
+    f32x16_t sc;
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+      const float4 l4 = *reinterpret_cast<const float4*>(sL + 8 * r4 + 4 * g);
+      sc[4 * r4 + 0] = l4.x; sc[4 * r4 + 1] = l4.y; sc[4 * r4 + 2] = l4.z; sc[4 * r4 + 3] = l4.w;
+    }
+#pragma unroll
+    for (int dc = 0; dc < DC; ++dc) sc = lg_mfma32(rd.read_rows(smem, sq, 0, dc), kf[dc], sc);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      float pv = __builtin_amdgcn_exp2f(sc[r] * sl2);
+      if (!full && dead(r)) pv = 0.f;
+      p[r] = pv;
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const bf16x8_t pb = lg_pack8(p + 8 * h);
+#pragma unroll
+    for (int db = 0; db < DB; ++db) av[db] = lg_mfma32(rd.read_cols(smem, sg, db, h), pb, av[db]);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  {
+    f32x16_t dp;  // starts from -Delta of its rows
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+      const float4 d4 = *reinterpret_cast<const float4*>(sL + 64 + 8 * r4 + 4 * g);
+      dp[4 * r4 + 0] = d4.x; dp[4 * r4 + 1] = d4.y; dp[4 * r4 + 2] = d4.z; dp[4 * r4 + 3] = d4.w;
+    }
+#pragma unroll
+    for (int dc = 0; dc < DC; ++dc)
+      dp = lg_mfma32(rd.read_rows(smem, sg, 0, dc), rd.read_rows(smem, voff, 0, dc), dp);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) p[r] *= dp[r];  // p becomes dS
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const bf16x8_t db_ = lg_pack8(p + 8 * h);
+#pragma unroll
+    for (int db = 0; db < DB; ++db) ak[db] = lg_mfma32(rd.read_cols(smem, sq, db, h), db_, ak[db]);
+  }
+}
+
 template <int D, bool TOKEN, bool COLUMN>
 __global__ __launch_bounds__(512) void dkdv_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const uint16_t* __restrict__ dout, const float* __restrict__ nlse, const float* __restrict__ ndelta,
     uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int Hq, int Hkv, float scale, LgMask m_in,
-    int nkt, int total, int per_xcd, const int* __restrict__ col_of_group, const int* __restrict__ col_list,
-    float* __restrict__ part_dk, float* __restrict__ part_dv, int ncol_all, LgBwdWork wk) {
+    int nkt, int total, int run, LgBwdWork wk) {
   LgMask m = m_in;
   if (TOKEN) {
     m.b = 1;
@@ -481,25 +590,17 @@ __global__ __launch_bounds__(512) void dkdv_bf16_kernel(
   const int n = lane & 31, g = lane >> 5;
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   // Work item.
-  //   main, no split-off columns: key tile 0 of every (b, kv head) holds the sink keys and runs
-  //     ~N/64 steps instead of ~(window+256)/64, so those workgroups take the first block ids
-  //     (dealt round-robin over the XCDs: they start at once, spread evenly); the other
-  //     (head, key tile) items follow in XCD-contiguous runs, so that neighbouring key tiles
-  //     share their Q / dO rows in one XCD's L2.
-  //   main, columns split off: all items in XCD-contiguous runs.
-  //   COLUMN: blockIdx.x = (chunk * nvt + virtual tile) * (heads) + (b x kv head) * G + query head of
-  //     the group: with the heads innermost every XCD gets the same mix of long and short items (and
-  //     of those that exit at once: a virtual tile has no rows in the chunks before its column part
-  //     starts), and the virtual tiles of one head that walk the same chunk of query rows run on one
-  //     XCD at about the same time.
-  //   packed: the items bwd_setup_kernel lists, kv heads innermost (with a multiple of 8 of them, all key tiles of
-  //     a head run on one XCD); COLUMN: the (chunk, virtual tile) pairs of one sequence after the other.
-  const int bid = blockIdx.x;
-  int bh, kt = 0, vt = 0, chunk = 0, gq = 0;
-  LgBwdItem it = {0, 0, 0, 0, ncol_all};
+  //   main: see lg_bwd_main.
+  //   COLUMN: (chunk * nvt + virtual tile) * (heads) + (b x kv head) * G + query head of the group: with the heads
+  //     innermost every XCD gets the same mix of long and short items (and of those that exit at once: a virtual tile
+  //     has no rows in the chunks before its column part starts), and the virtual tiles of one head that walk the same
+  //     chunk of query rows run on one XCD at about the same time.  Packed: one sequence after the other.
+  int vt = 0, chunk = 0, gq = 0;
+  LgBwdItem it = {0, 0, 0, 0, 0, wk.ncol};
+  LgBwdMain w = {0, 0, 0};
   if (COLUMN) {
-    const int nh = (total / nkt) * G;
-    int x = bid;
+    const int nh = wk.B * Hq;
+    int x = blockIdx.x;
     const int hd = x % nh;
     x /= nh;
     if (wk.seqs) {
@@ -511,32 +612,13 @@ __global__ __launch_bounds__(512) void dkdv_bf16_kernel(
     vt = x % nvt;
     chunk = x / nvt;
     gq = hd % G;
-    bh = hd / G;
-  } else if (wk.seqs) {
-    const int x = lg_uniform(wk.items[bid / Hkv]);
-    bh = bid % Hkv;
-    kt = x & 0xffffff;
-    it = lg_bwd_item(wk.seqs, x >> 24, m);
-  } else if (it.ncol > 0) {
-    const int L = (bid % 8) * per_xcd + bid / 8;
-    if (L >= total) return;
-    bh = L / nkt;
-    kt = L % nkt;
-  } else {
-    const int nbh = total / nkt;
-    if (bid < nbh) {
-      bh = bid;
-      kt = 0;
-    } else {
-      const int idx = bid - nbh;
-      const int L = (idx % 8) * per_xcd + idx / 8;
-      if (nkt == 1 || L >= total - nbh) return;
-      bh = L / (nkt - 1);
-      kt = 1 + L % (nkt - 1);
-    }
+    w.bh = hd / G;
+  } else if (!lg_bwd_main(wk, blockIdx.x, nkt, total, run, m, it, w)) {
+    return;
   }
+  const int bh = w.bh, kt = w.kt;
   const int N = m.N, ncol = it.ncol;
-  const int* clist = col_list + it.col0;
+  const int* __restrict__ clist = wk.col_list + it.col0;
   const int b = bh / Hkv, hk = bh % Hkv;
   const int k0 = kt * TK, k1 = min(k0 + TK - 1, N - 1);
   const size_t kbase = ((size_t)(b * Hkv + hk) * m.ld + it.row0) * D;
@@ -569,25 +651,23 @@ __global__ __launch_bounds__(512) void dkdv_bf16_kernel(
 #pragma unroll
     for (int r = 0; r < 16; ++r) ak[db][r] = av[db][r] = 0.f;
   // query tiles of this work item
-  int lo, hi, hq0 = hk * G, nheads = G;
+  int lo, hi, hq0 = hk * G, nheads = 1;
   if (COLUMN) {
     // the query tiles of chunk number `chunk` (chunks are cut at fixed tile numbers for all virtual
     // tiles, counted from the chunk in which the first column part starts) that come after the
     // window part of the virtual tile's first group
     const int tf = min((64 * clist[0] / TK) * TK + TK - 1, N - 1);
-    const int c_abs = (lg_qtile_window_hi(m, tf, TQ) + 1) / LG_COL_CHUNK + chunk;
+    const int c_abs = (lg_qtile_window_hi(m, tf, TQ) + 1) / wk.chunk + chunk;
     const int grp0 = clist[4 * vt];
     const int t1 = min((64 * grp0 / TK) * TK + TK - 1, N - 1);
-    lo = max(lg_qtile_window_hi(m, t1, TQ) + 1, c_abs * LG_COL_CHUNK);
-    hi = min((N - 1) / TQ, c_abs * LG_COL_CHUNK + LG_COL_CHUNK - 1);
+    lo = max(lg_qtile_window_hi(m, t1, TQ) + 1, c_abs * wk.chunk);
+    hi = min((N - 1) / TQ, c_abs * wk.chunk + wk.chunk - 1);
     if (lo > hi) return;
     hq0 += gq;
-    nheads = 1;
-  } else if (ncol > 0) {  // the window part; the column part is the COLUMN instance's
-    lo = k0 / TQ;
-    hi = lg_qtile_window_hi(m, k1, TQ);
   } else {
-    lg_qtile_range(m, k0, k1, TQ, &lo, &hi);
+    int head0;
+    lg_bwd_part_range(wk, m, ncol > 0, k0, k1, w.part, G, &lo, &hi, &head0, &nheads);
+    hq0 += head0;
   }
   const int per_head = hi - lo + 1;
   const int steps = per_head * nheads;
@@ -625,11 +705,12 @@ __global__ __launch_bounds__(512) void dkdv_bf16_kernel(
   // The query tiles [lo, hi] of a head are walked rotated: at step x the tile congruent to x
   // modulo the range length.  Neighbouring key tiles, whose ranges overlap almost completely and
   // which run side by side, then read the same Q / dO tile at the same time and share it in L2.
-  const int u0 = lo + (per_head - lo % per_head) % per_head;
+  const int u0 = per_head > 0 ? lo + (per_head - lo % per_head) % per_head : lo;
   int hq_i = hq0, u_i = u0;      // step being issued
   int u_c = u0;                  // query tile of the step being computed
   int left_i = per_head;         // steps of the head being issued that are not issued yet
-  issue_step(hq_i, u_i, 0);
+  if (steps > 0) issue_step(hq_i, u_i, 0);
+  else LG_WAIT_VMCNT(0);  // (a part without rows: nothing may still be on its way to LDS when it ends)
   for (int st = 0; st < steps; ++st) {
     const int buf = st & 1;
     LG_WAIT_VMCNT(0);
@@ -667,89 +748,48 @@ __global__ __launch_bounds__(512) void dkdv_bf16_kernel(
       return !((unsigned)(c - lo_c) < w_eff && c < n_c);
     };
 
-    // Per 32-row query block, in an order that keeps few values alive at a time:
-    // S -> P -> (dV += dO^T P) -> dP -> dS -> (dK += Q^T dS)
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-      float p[16];
-      __builtin_amdgcn_sched_barrier(0);  // phases stay apart: bounds the operands held at once
-      {
-        // the accumulator starts from -lse / scale of its rows (register r <-> row 8 (r / 4) + 4g + r % 4)
-        f32x16_t sc;
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          const float4 l4 = *reinterpret_cast<const float4*>(sL + qb * 32 + 8 * r4 + 4 * g);
-          sc[4 * r4 + 0] = l4.x; sc[4 * r4 + 1] = l4.y; sc[4 * r4 + 2] = l4.z; sc[4 * r4 + 3] = l4.w;
-        }
-#pragma unroll
-        for (int dc = 0; dc < DC; ++dc) sc = lg_mfma32(rd.read_rows(smem, sq, qb, dc), kf[dc], sc);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          float pv = __builtin_amdgcn_exp2f(sc[r] * sl2);
-          if (!full && dead(qb, r)) pv = 0.f;
-          p[r] = pv;
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const bf16x8_t pb = lg_pack8(p + 8 * h);
-#pragma unroll
-        for (int db = 0; db < DB; ++db) av[db] = lg_mfma32(rd.read_cols(smem, sg, db, 2 * qb + h), pb, av[db]);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      {
-        f32x16_t dp;  // starts from -Delta of its rows
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          const float4 d4 = *reinterpret_cast<const float4*>(sL + 64 + qb * 32 + 8 * r4 + 4 * g);
-          dp[4 * r4 + 0] = d4.x; dp[4 * r4 + 1] = d4.y; dp[4 * r4 + 2] = d4.z; dp[4 * r4 + 3] = d4.w;
-        }
-#pragma unroll
-        for (int dc = 0; dc < DC; ++dc)
-          dp = lg_mfma32(rd.read_rows(smem, sg, qb, dc), rd.read_rows(smem, voff, 0, dc), dp);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) p[r] *= dp[r];  // p becomes dS
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const bf16x8_t db_ = lg_pack8(p + 8 * h);
-#pragma unroll
-        for (int db = 0; db < DB; ++db) ak[db] = lg_mfma32(rd.read_cols(smem, sq, db, 2 * qb + h), db_, ak[db]);
-      }
-    }
+    for (int qb = 0; qb < 2; ++qb)
+      lg_dkdv_block<D>(smem, rd, sq + qb * HALF, sg + qb * HALF, voff, sL + qb * 32, kf, ak, av, sl2, g, full,
+                       [&](int r) { return dead(qb, r); });
   }
 
-  // partial sums of the column parts: [b x kv head][column group][64 keys][D] float32, dk unscaled
+  using Slot = LgSlot<D>;
   if (COLUMN) {
-    // the wave's own V rows (only this wave ever read them) serve as the turning space
-    static_assert(HALF >= 4096, "a 32 x 32 float block fits the wave's V rows");
-    float* tr = reinterpret_cast<float*>(smem + voff);
-    const int nrows = active ? min(max(N - kw0, 0), 32) : 0;
-    const size_t prow = (((size_t)bh * ncol_all + it.col0 + col_gi) * 64 + (wave_s & 1) * 32) * D;
-#pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      lg_atomic_add_block(tr, ak[db], part_dk + prow + db * 32, D, nrows, n, g);
-      lg_atomic_add_block(tr, av[db], part_dv + prow + db * 32, D, nrows, n, g);
-    }
-    return;
-  }
-  const int cid = (ncol > 0 && kw0 < N) ? col_of_group[it.grp0 + (kw0 >> 6)] : -1;
-  if (cid >= 0 && j < N) {
-    const size_t prow = (((size_t)bh * ncol_all + it.col0 + cid) * 64 + (wave_s & 1) * 32 + n) * D;
+    if (!active) return;
+    float* dst = wk.colpart + ((size_t)bh * wk.ncol + it.col0 + col_gi) * Slot::FLOATS + lane;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        const f32x4_t pk = lg_load_shared4(part_dk + prow + db * 32 + 8 * r4 + 4 * g);
-        const f32x4_t pv = lg_load_shared4(part_dv + prow + db * 32 + 8 * r4 + 4 * g);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          ak[db][4 * r4 + t] += pk[t];
-          av[db][4 * r4 + t] += pv[t];
-        }
+      for (int r = 0; r < 16; ++r) {
+        unsafeAtomicAdd(dst + Slot::at(wave_s & 1, 0, db) + 64 * r, ak[db][r]);  // hardware float adds
+        unsafeAtomicAdd(dst + Slot::at(wave_s & 1, 1, db) + 64 * r, av[db][r]);
       }
+    return;
+  }
+  if (wk.heads_cut * wk.rows_cut > 1) {  // bwd_fold_kernel adds the parts
+    float* dst = lg_bwd_part_slot<D>(wk, it, w, total / nkt) + (wave_s >> 1) * Slot::FLOATS + lane;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        dst[Slot::at(wave_s & 1, 0, db) + 64 * r] = ak[db][r];
+        dst[Slot::at(wave_s & 1, 1, db) + 64 * r] = av[db][r];
+      }
+    return;
+  }
+  const int cid = (ncol > 0 && kw0 < N) ? wk.col_of_group[it.grp0 + (kw0 >> 6)] : -1;
+  if (cid >= 0) {
+    const float* src = wk.colpart + ((size_t)bh * wk.ncol + it.col0 + cid) * Slot::FLOATS + lane;
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+      __builtin_amdgcn_sched_barrier(0);  // (not all loads at once)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        ak[db][r] += lg_load_shared1(src + Slot::at(wave_s & 1, 0, db) + 64 * r);
+        av[db][r] += lg_load_shared1(src + Slot::at(wave_s & 1, 1, db) + 64 * r);
+      }
+    }
   }
   if (j < N) {
 #pragma unroll
@@ -764,6 +804,203 @@ __global__ __launch_bounds__(512) void dkdv_bf16_kernel(
         w.y = lg_pack_bf16(av[db][4 * r4 + 2], av[db][4 * r4 + 3]);
         *reinterpret_cast<uint2*>(dv + kbase + (size_t)j * D + db * 32 + 8 * r4 + 4 * g) = w;
       }
+  }
+}
+
+// --------------------------------------------------------- dk, dv: the column part of a lone group
+// A head's only column group (the sink keys) is seen by every later query: up to N / 64 query tiles for 64 keys.  Left
+// to its key tile, one workgroup of the whole launch walks them with one wave in four (or two in eight) at work: with 2
+// heads and 24000 tokens 1.0 ms beside 0.16 ms for all the rest.  Here the eight waves of a workgroup are the 2 blocks
+// of 32 keys x the 4 blocks of 32 rows of two query tiles, double-buffered, and the range is cut into chunks.  Hq == Hkv:
+// every chunk leaves its sums in the workspace, and the one that finishes last adds them in order (bit-reproducible; the
+// cut depends on the sequence alone).  Groups of query heads: float32 atomics.
+template <int D>
+__global__ __launch_bounds__(512) void dkdv_lone_bf16_kernel(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+    const uint16_t* __restrict__ dout, const float* __restrict__ nlse, const float* __restrict__ ndelta, int Hq, int Hkv,
+    float scale, LgMask m, LgBwdWork wk) {
+  using T = LgSwzTile<D>;
+  using Slot = LgSlot<D>;
+  constexpr int NT = 512;
+  using Dma = LgDma<D, NT>;
+  constexpr int TQ = LG_BF16_BTQ, TK = LG_BF16_BTK, DC = D / 16, DB = D / 32;
+  constexpr int HALF = 32 * T::ROW_BYTES;
+  constexpr int OFF_G = T::BYTES, OFF_L = 2 * T::BYTES, STAGE = 2 * T::BYTES + 1024;  // as in the kernel above
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[T::BYTES + 4 * STAGE];  // V rows, two pairs of tiles
+  __shared__ int s_last;
+
+  const int nh = wk.B * Hq, hd = blockIdx.x % nh;
+  int chunk = blockIdx.x / nh, nchunk = wk.nlone, lone0 = 0, sq = 0, nseq = 1;
+  LgBwdItem it = {0, 0, 0, 0, 0, wk.ncol};
+  if (wk.seqs) {
+    nseq = lg_uniform(wk.seqs->n);
+    sq = lg_seq_of(wk.seqs->litem0, nseq, chunk);
+    lone0 = lg_uniform(wk.seqs->litem0[sq]);
+    nchunk = lg_uniform(wk.seqs->nlone[sq]);
+    chunk -= lone0;
+    it = lg_bwd_item(wk.seqs, sq, m);
+  }
+  const int b = hd / Hq, hq = hd % Hq, hk = hq / (Hq / Hkv), bh = b * Hkv + hk;
+  const int N = m.N, grp = lg_uniform(wk.col_list[it.col0]);
+  const int first = lg_qtile_window_hi(m, min((64 * grp / TK) * TK + TK - 1, N - 1), TQ) + 1, last = (N - 1) / TQ;
+  const int pairs = (last - first + 2) / 2;
+  const int p0 = pairs * chunk / nchunk, p1 = pairs * (chunk + 1) / nchunk;  // (never empty: nchunk <= pairs)
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = lg_uniform(tid >> 6);
+  const int n = lane & 31, g = lane >> 5;
+  const int kb = wave & 1, qb = (wave >> 1) & 1, tile = wave >> 2;
+  const float sl2 = scale * LOG2E;
+  const size_t kbase = ((size_t)bh * m.ld + it.row0) * D;
+  const size_t row0 = (size_t)hd * m.ld + it.row0, wrow0 = (size_t)hd * wk.wld + it.wrow0;
+  const int kw0 = 64 * grp + 32 * kb, j = kw0 + n;
+
+  bf16x8_t kf[DC];
+#pragma unroll
+  for (int dc = 0; dc < DC; ++dc)
+    kf[dc] = lg_as_bf16x8(*reinterpret_cast<const uint4*>(k + kbase + (size_t)min(j, N - 1) * D + dc * 16 + g * 8));
+#pragma unroll
+  for (int dc = 0; dc < DC; ++dc) asm volatile("" ::"v"(kf[dc]));
+  f32x16_t ak[DB], av[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) ak[db][r] = av[db][r] = 0.f;
+
+  Dma dma;
+  dma.init(tid);
+  LgSwzReader<D> rd;
+  rd.init(n, g);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)LG_LDS_PTR(unsigned char, smem);
+  dma.issue(v + kbase + (size_t)64 * grp * D, N - 64 * grp, lds0);
+  auto issue = [&](int pr, int buf) {
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      const int q0 = min(first + 2 * pr + x, last) * TQ;  // (an odd range repeats its last tile; nobody uses it)
+      const uint32_t st = lds0 + T::BYTES + (2 * buf + x) * STAGE;
+      if ((wave >> 1) == x)  // -lse / scale rows and -Delta rows (64 floats each)
+        lg_dma_f32x64(((wave & 1) ? ndelta : nlse) + wrow0 + min(q0 + lane, N - 1), st + OFF_L + (wave & 1) * 256);
+      dma.issue(q + (row0 + q0) * D, N - q0, st);
+      dma.issue(dout + (row0 + q0) * D, N - q0, st + OFF_G);
+    }
+  };
+  issue(p0, 0);
+  for (int pr = p0; pr < p1; ++pr) {
+    const int buf = (pr - p0) & 1;
+    LG_WAIT_VMCNT(0);
+    __syncthreads();  // this pair landed for everyone; everyone is done with the one before
+    if (pr + 1 < p1) issue(pr + 1, buf ^ 1);
+    const int u = first + 2 * pr + tile, q0 = u * TQ + 32 * qb;
+    if (u > last || q0 >= N) continue;
+    const int kind = lg_tile_kind(m, q0, min(q0 + 31, N - 1), kw0, kw0 + 31);
+    if (kind == LG_TILE_DEAD) continue;
+    const bool full = kind == LG_TILE_FULL && q0 + 32 <= N;
+    const uint32_t bits = full ? ~0u : lg_row_bits(m, j, q0, g);
+    const int st = T::BYTES + (2 * buf + tile) * STAGE;
+    lg_dkdv_block<D>(smem, rd, st + qb * HALF, st + OFF_G + qb * HALF, kb * HALF,
+                     reinterpret_cast<const float*>(smem + st + OFF_L) + 32 * qb, kf, ak, av, sl2, g, full,
+                     [&](int r) { return !((bits >> r) & 1); });
+  }
+
+  // the four row blocks' sums meet in waves 0 and 1, dk and then dv through the LDS of the tiles
+  float* red = reinterpret_cast<float*>(smem + T::BYTES);
+  static_assert(6 * DB * 4096 <= 4 * STAGE, "six waves' blocks fit");
+#pragma unroll
+  for (int which = 0; which < 2; ++which) {
+    f32x16_t(&acc)[DB] = which ? av : ak;
+    __syncthreads();
+    if (wave >= 2)
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) red[((wave - 2) * DB + db) * 1024 + 64 * r + lane] = acc[db][r];
+    __syncthreads();
+    if (wave < 2)
+#pragma unroll
+      for (int x = 0; x < 3; ++x)
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[db][r] += red[((2 * x + wave) * DB + db) * 1024 + 64 * r + lane];
+  }
+
+  float* sum = wk.colpart + ((size_t)bh * wk.ncol + it.col0) * Slot::FLOATS;
+  if (!wk.lonepart) {
+    if (wave < 2)
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          unsafeAtomicAdd(sum + Slot::at(kb, 0, db) + 64 * r + lane, ak[db][r]);  // hardware float adds
+          unsafeAtomicAdd(sum + Slot::at(kb, 1, db) + 64 * r + lane, av[db][r]);
+        }
+    return;
+  }
+  float* mine = wk.lonepart + ((size_t)bh * wk.nlone_all + lone0) * Slot::FLOATS;  // the sequence's first chunk
+  if (wave < 2)
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        float* dst = mine + (size_t)chunk * Slot::FLOATS + Slot::at(kb, 0, db) + 64 * r + lane;
+        lg_store_shared1(dst, ak[db][r]);
+        lg_store_shared1(dst + Slot::at(0, 1, 0), av[db][r]);
+      }
+  lg_shared_stores_done();
+  __syncthreads();
+  if (tid == 0)
+    s_last = __hip_atomic_fetch_add(wk.arrived + (size_t)bh * nseq + sq, 1u, __ATOMIC_RELAXED,
+                                    __HIP_MEMORY_SCOPE_AGENT) == (unsigned)(nchunk - 1);
+  __syncthreads();
+  if (!s_last) return;
+  constexpr int EACH = Slot::FLOATS / NT;
+  float a[EACH];
+#pragma unroll
+  for (int x = 0; x < EACH; ++x) a[x] = 0.f;
+  for (int c = 0; c < nchunk; ++c)
+#pragma unroll
+    for (int x = 0; x < EACH; ++x) a[x] += lg_load_shared1(mine + (size_t)c * Slot::FLOATS + x * NT + tid);
+#pragma unroll
+  for (int x = 0; x < EACH; ++x) sum[x * NT + tid] = a[x];
+}
+
+// Adds the parts of a key tile's window part, in order, and its column sums, and rounds: one workgroup per 32 keys.
+template <int D>
+__global__ __launch_bounds__(256) void bwd_fold_kernel(uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int nbh,
+                                                       float scale, LgMask m, LgBwdWork wk) {
+  using Slot = LgSlot<D>;
+  constexpr int DB = D / 32;
+  const int kb32 = blockIdx.x & 7, x = blockIdx.x >> 3, bh = x % nbh, t = x / nbh;
+  const int nparts = wk.heads_cut * wk.rows_cut;
+  LgBwdItem it = {0, 0, 0, 0, 0, wk.ncol};
+  if (wk.seqs) it = lg_bwd_item(wk.seqs, lg_seq_of(wk.seqs->ktile0, lg_uniform(wk.seqs->n), t), m);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 31, g = lane >> 5;
+  const int kw0 = (t - it.ktile0) * LG_BF16_BTK + 32 * kb32, j = kw0 + n;
+  if (kw0 >= m.N) return;
+  const float* src = wk.parts + ((size_t)t * nbh + bh) * nparts * (4 * Slot::FLOATS) + (kb32 >> 1) * Slot::FLOATS + lane;
+  const int cid = it.ncol > 0 ? wk.col_of_group[it.grp0 + (kw0 >> 6)] : -1;
+  const float* csum = wk.colpart + ((size_t)bh * wk.ncol + it.col0 + max(cid, 0)) * Slot::FLOATS + lane;
+  for (int y = wave; y < 2 * DB; y += 4) {
+    const int which = y / DB, db = y % DB, at = Slot::at(kb32 & 1, which, db);
+    float a[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) a[r] = 0.f;
+    for (int p = 0; p < nparts; ++p)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) a[r] += src[(size_t)p * (4 * Slot::FLOATS) + at + 64 * r];
+    if (cid >= 0)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) a[r] += lg_load_shared1(csum + at + 64 * r);
+    if (j < m.N) {
+      const float f = which ? 1.f : scale;
+      uint16_t* dst = (which ? dv : dk) + ((size_t)bh * m.ld + it.row0 + j) * D + db * 32 + 4 * g;
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) {
+        uint2 w;
+        w.x = lg_pack_bf16(a[4 * r4 + 0] * f, a[4 * r4 + 1] * f);
+        w.y = lg_pack_bf16(a[4 * r4 + 2] * f, a[4 * r4 + 3] * f);
+        *reinterpret_cast<uint2*>(dst + 8 * r4) = w;
+      }
+    }
   }
 }
 
@@ -806,8 +1043,7 @@ __device__ __forceinline__ void dkdv_wide_item(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const uint16_t* __restrict__ dout, const float* __restrict__ nlse, const float* __restrict__ ndelta,
     uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int Hq, int Hkv, float scale, LgMask m_in,
-    int nkt, int total, int per_xcd, const int* __restrict__ col_of_group, const int* __restrict__ col_list,
-    float* __restrict__ part_dk, float* __restrict__ part_dv, int ncol_all, const LgBwdWork& wk, const int bid) {
+    int nkt, int total, int run, const LgBwdWork& wk, const int bid) {
   LgMask m = m_in;
   if (TOKEN) {
     m.b = 1;
@@ -839,12 +1075,13 @@ __device__ __forceinline__ void dkdv_wide_item(
   const int n = lane & 31, g = lane >> 5;
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   // work item: as in the kernel above
-  int bh, kt = 0, vt = 0, chunk = 0, gq = 0;
-  LgBwdItem it = {0, 0, 0, 0, ncol_all};
+  int vt = 0, chunk = 0, gq = 0;
+  LgBwdItem it = {0, 0, 0, 0, 0, wk.ncol};
+  LgBwdMain w = {0, 0, 0};
   if (COLUMN) {
     // (the results of these divisions are pinned to scalar registers: the global->LDS copies take
     // their base addresses, which derive from them, as scalar operands)
-    const int nh = (total / nkt) * G;
+    const int nh = wk.B * Hq;
     int x = bid;
     const int hd = x % nh;
     x /= nh;
@@ -854,35 +1091,16 @@ __device__ __forceinline__ void dkdv_wide_item(
       it = lg_bwd_item(wk.seqs, sq, m);
     }
     const int nvt = (it.ncol + 3) / 4;
-    vt = __builtin_amdgcn_readfirstlane(x % nvt);
-    chunk = __builtin_amdgcn_readfirstlane(x / nvt);
-    gq = __builtin_amdgcn_readfirstlane(hd % G);
-    bh = __builtin_amdgcn_readfirstlane(hd / G);
-  } else if (wk.seqs) {
-    const int x = lg_uniform(wk.items[bid / Hkv]);
-    bh = bid % Hkv;
-    kt = x & 0xffffff;
-    it = lg_bwd_item(wk.seqs, x >> 24, m);
-  } else if (it.ncol > 0) {
-    const int L = (bid % 8) * per_xcd + bid / 8;
-    if (L >= total) return;
-    bh = L / nkt;
-    kt = L % nkt;
-  } else {
-    const int nbh = total / nkt;
-    if (bid < nbh) {
-      bh = bid;
-      kt = 0;
-    } else {
-      const int idx = bid - nbh;
-      const int L = (idx % 8) * per_xcd + idx / 8;
-      if (nkt == 1 || L >= total - nbh) return;
-      bh = L / (nkt - 1);
-      kt = 1 + L % (nkt - 1);
-    }
+    vt = lg_uniform(x % nvt);
+    chunk = lg_uniform(x / nvt);
+    gq = lg_uniform(hd % G);
+    w.bh = lg_uniform(hd / G);
+  } else if (!lg_bwd_main(wk, bid, nkt, total, run, m, it, w)) {
+    return;
   }
+  const int bh = w.bh, kt = w.kt;
   const int N = m.N, ncol = it.ncol;
-  const int* clist = col_list + it.col0;
+  const int* __restrict__ clist = wk.col_list + it.col0;
   const int b = bh / Hkv, hk = bh % Hkv;
   const int k0 = kt * TK, k1 = min(k0 + TK - 1, N - 1);
   const size_t kbase = ((size_t)(b * Hkv + hk) * m.ld + it.row0) * D;
@@ -923,25 +1141,23 @@ __device__ __forceinline__ void dkdv_wide_item(
 #pragma unroll
   for (int i = 0; i < 16; ++i) lg_acc_zero(i, zero8);
 
-  int lo, hi, hq0 = hk * G, nheads = G;
+  int lo, hi, hq0 = hk * G, nheads = 1;
   if (COLUMN) {
     // the query tiles of chunk number `chunk` (chunks are cut at fixed tile numbers for all virtual
     // tiles, counted from the chunk in which the first column part starts) that come after the
     // window part of the virtual tile's first group
     const int tf = min((64 * clist[0] / TK) * TK + TK - 1, N - 1);
-    const int c_abs = (lg_qtile_window_hi(m, tf, TQ) + 1) / LG_COL_CHUNK + chunk;
+    const int c_abs = (lg_qtile_window_hi(m, tf, TQ) + 1) / wk.chunk + chunk;
     const int grp0 = clist[4 * vt];
     const int t1 = min((64 * grp0 / TK) * TK + TK - 1, N - 1);
-    lo = max(lg_qtile_window_hi(m, t1, TQ) + 1, c_abs * LG_COL_CHUNK);
-    hi = min((N - 1) / TQ, c_abs * LG_COL_CHUNK + LG_COL_CHUNK - 1);
+    lo = max(lg_qtile_window_hi(m, t1, TQ) + 1, c_abs * wk.chunk);
+    hi = min((N - 1) / TQ, c_abs * wk.chunk + wk.chunk - 1);
     if (lo > hi) return;
     hq0 += gq;
-    nheads = 1;
-  } else if (ncol > 0) {  // the window part; the column part is the COLUMN instance's
-    lo = k0 / TQ;
-    hi = lg_qtile_window_hi(m, k1, TQ);
   } else {
-    lg_qtile_range(m, k0, k1, TQ, &lo, &hi);
+    int head0;
+    lg_bwd_part_range(wk, m, ncol > 0, k0, k1, w.part, G, &lo, &hi, &head0, &nheads);
+    hq0 += head0;
   }
   const int per_head = hi - lo + 1;
   const int steps = per_head * nheads;
@@ -972,11 +1188,12 @@ __device__ __forceinline__ void dkdv_wide_item(
     dma.issue(dout + (row0 + q0) * D, N - q0, st + OFF_G);
   };
 
-  const int u0 = lo + (per_head - lo % per_head) % per_head;  // rotated walk, as above
+  const int u0 = per_head > 0 ? lo + (per_head - lo % per_head) % per_head : lo;  // rotated walk, as above
   int hq_i = hq0, u_i = u0;
   int u_c = u0;
   int left_i = per_head;
-  issue_step(hq_i, u_i, 0);
+  if (steps > 0) issue_step(hq_i, u_i, 0);
+  else LG_WAIT_VMCNT(0);  // (a part without rows: nothing may still be on its way to LDS when it ends)
   for (int st = 0; st < steps; ++st) {
     const int buf = st & 1;
     LG_WAIT_VMCNT(0);
@@ -1132,58 +1349,60 @@ __device__ __forceinline__ void dkdv_wide_item(
 
   // the last matrix results must have landed before the blocks are copied out
   asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-  if (COLUMN) {  // partial sums of the column parts, as in the 8-wave kernel
-    float* tr = reinterpret_cast<float*>(smem + voff);
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-      const int nrows = active ? min(max(N - kw0 - 32 * kb, 0), 32) : 0;
-      const size_t prow = (((size_t)bh * ncol_all + it.col0 + col_gi) * 64 + kb * 32) * D;
-#pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        float akv[16], avv[16];
-        lg_acc_get(kb * 4 + db, akv);
-        lg_acc_get(8 + kb * 4 + db, avv);
-        lg_atomic_add_block(tr, akv, part_dk + prow + db * 32, D, nrows, n, g);
-        lg_atomic_add_block(tr, avv, part_dv + prow + db * 32, D, nrows, n, g);
-      }
-    }
-    return;
-  }
-  const int cid = (ncol > 0 && kw0 < N) ? col_of_group[it.grp0 + (kw0 >> 6)] : -1;
+  using Slot = LgSlot<D>;
+  const bool cut = !COLUMN && wk.heads_cut * wk.rows_cut > 1;
+  if (COLUMN && !active) return;
+  float* slot = (cut ? lg_bwd_part_slot<D>(wk, it, w, total / nkt) + wave_s * Slot::FLOATS
+                     : wk.colpart + ((size_t)bh * wk.ncol + it.col0 + col_gi) * Slot::FLOATS) + lane;
+  const int cid = (!COLUMN && !cut && ncol > 0 && kw0 < N) ? wk.col_of_group[it.grp0 + (kw0 >> 6)] : -1;
+  const float* csum = wk.colpart + ((size_t)bh * wk.ncol + it.col0 + max(cid, 0)) * Slot::FLOATS + lane;
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb) {
     const int jj = j + 32 * kb;
+    float c[2 * DB][16];  // the column part's sums, all of a key block in flight at once
+    if (cid >= 0)
+#pragma unroll
+      for (int x = 0; x < 2 * DB; ++x)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) c[x][r] = lg_load_shared1(csum + Slot::at(kb, x & 1, x >> 1) + 64 * r);
 #pragma unroll
     for (int db = 0; db < DB; ++db) {
       float akv[16], avv[16];
       lg_acc_get(kb * 4 + db, akv);
       lg_acc_get(8 + kb * 4 + db, avv);
-      if (jj < N)
+      float* pk = slot + Slot::at(kb, 0, db);
+      float* pv = slot + Slot::at(kb, 1, db);
+      if (COLUMN) {
 #pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        float a4[4], v4[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          a4[t] = akv[4 * r4 + t];
-          v4[t] = avv[4 * r4 + t];
+        for (int r = 0; r < 16; ++r) {
+          unsafeAtomicAdd(pk + 64 * r, akv[r]);  // hardware float adds
+          unsafeAtomicAdd(pv + 64 * r, avv[r]);
         }
-        if (cid >= 0) {  // fold in the column part's partial sums
-          const size_t prow = (((size_t)bh * ncol_all + it.col0 + cid) * 64 + kb * 32 + n) * D;
-          const f32x4_t pk = lg_load_shared4(part_dk + prow + db * 32 + 8 * r4 + 4 * g);
-          const f32x4_t pv = lg_load_shared4(part_dv + prow + db * 32 + 8 * r4 + 4 * g);
+      } else if (cut) {  // bwd_fold_kernel adds the parts
 #pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            a4[t] += pk[t];
-            v4[t] += pv[t];
+        for (int r = 0; r < 16; ++r) {
+          pk[64 * r] = akv[r];
+          pv[64 * r] = avv[r];
+        }
+      } else {
+        if (cid >= 0)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            akv[r] += c[2 * db][r];
+            avv[r] += c[2 * db + 1][r];
           }
+        if (jj < N)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+          const float *a4 = akv + 4 * r4, *v4 = avv + 4 * r4;
+          uint2 w;
+          w.x = lg_pack_bf16(a4[0] * scale, a4[1] * scale);
+          w.y = lg_pack_bf16(a4[2] * scale, a4[3] * scale);
+          *reinterpret_cast<uint2*>(dk + kbase + (size_t)jj * D + db * 32 + 8 * r4 + 4 * g) = w;
+          w.x = lg_pack_bf16(v4[0], v4[1]);
+          w.y = lg_pack_bf16(v4[2], v4[3]);
+          *reinterpret_cast<uint2*>(dv + kbase + (size_t)jj * D + db * 32 + 8 * r4 + 4 * g) = w;
         }
-        uint2 w;
-        w.x = lg_pack_bf16(a4[0] * scale, a4[1] * scale);
-        w.y = lg_pack_bf16(a4[2] * scale, a4[3] * scale);
-        *reinterpret_cast<uint2*>(dk + kbase + (size_t)jj * D + db * 32 + 8 * r4 + 4 * g) = w;
-        w.x = lg_pack_bf16(v4[0], v4[1]);
-        w.y = lg_pack_bf16(v4[2], v4[3]);
-        *reinterpret_cast<uint2*>(dv + kbase + (size_t)jj * D + db * 32 + 8 * r4 + 4 * g) = w;
       }
     }
   }
@@ -1195,10 +1414,9 @@ __global__ __launch_bounds__(256) void dkdv_wide_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const uint16_t* __restrict__ dout, const float* __restrict__ nlse, const float* __restrict__ ndelta,
     uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int Hq, int Hkv, float scale, LgMask m,
-    int nkt, int total, int per_xcd, const int* __restrict__ col_of_group, const int* __restrict__ col_list,
-    float* __restrict__ part_dk, float* __restrict__ part_dv, int ncol, LgBwdWork wk) {
-  dkdv_wide_item<TOKEN, COLUMN>(q, k, v, dout, nlse, ndelta, dk, dv, Hq, Hkv, scale, m, nkt, total, per_xcd,
-                                col_of_group, col_list, part_dk, part_dv, ncol, wk, (int)blockIdx.x);
+    int nkt, int total, int run, LgBwdWork wk) {
+  dkdv_wide_item<TOKEN, COLUMN>(q, k, v, dout, nlse, ndelta, dk, dv, Hq, Hkv, scale, m, nkt, total, run, wk,
+                                (int)blockIdx.x);
 }
 
 // The main instance: a workgroup holds a whole CU (4 x 512 registers, 130 KB of LDS), so the launch of
@@ -1209,16 +1427,13 @@ __global__ __launch_bounds__(256) void dkdv_wide_bf16_kernel_q(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const uint16_t* __restrict__ dout, const float* __restrict__ nlse, const float* __restrict__ ndelta,
     uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int Hq, int Hkv, float scale, LgMask m,
-    int nkt, int total, int per_xcd, const int* __restrict__ col_of_group, const int* __restrict__ col_list,
-    float* __restrict__ part_dk, float* __restrict__ part_dv, int ncol, LgBwdWork wk, int* __restrict__ queue,
-    int nitems) {
+    int nkt, int total, int run, LgBwdWork wk, int* __restrict__ queue, int nitems) {
   __shared__ int s_item;
   const int xcd = blockIdx.x & 7;
   for (;;) {
     const int id = lg_queue_take(queue, nitems, xcd, &s_item);
     if (id < 0) return;
-    dkdv_wide_item<TOKEN, false>(q, k, v, dout, nlse, ndelta, dk, dv, Hq, Hkv, scale, m, nkt, total, per_xcd,
-                                 col_of_group, col_list, part_dk, part_dv, ncol, wk, id);
+    dkdv_wide_item<TOKEN, false>(q, k, v, dout, nlse, ndelta, dk, dv, Hq, Hkv, scale, m, nkt, total, run, wk, id);
   }
 }
 
@@ -1507,26 +1722,32 @@ __global__ __launch_bounds__(256) void dq_wide_bf16_kernel(
 
 namespace {
 
-// Column groups of a sequence: ncol are split off (0: none) into nchunk chunks of query tiles.
+// The column groups of a sequence and the query tiles of their column parts.
 struct Columns {
-  int ncol, nchunk;
+  int ncol;         // column groups
+  int first, last;  // query tiles of the first group's column part, the longest
+  // a lone group: its chunks, up to 8 and not below 8 pairs of tiles each, by the sequence alone
+  int lone() const {
+    const int pairs = (last - first + 2) / 2;
+    return ncol != 1 ? 0 : pairs < 16 ? 1 : pairs < 64 ? pairs / 8 : 8;
+  }
+  // several: work items (virtual tile x chunk) of a query head; chunks are cut at multiples of `chunk` tiles
+  int items(int chunk) const { return ncol < 2 ? 0 : (ncol + 3) / 4 * (last / chunk - first / chunk + 1); }
 };
-Columns columns_of(const LgMask& m, bool gqa) {
-  Columns c = {0, 0};
+Columns columns_of(const LgMask& m) {
+  Columns c = {0, 0, 0};
   int first = -1;
   for (int grp = 0; grp < (m.N + 63) / 64; ++grp)
     if (lg_is_column_group(m, grp, LG_BF16_BTK, LG_BF16_BTQ)) {
       if (first < 0) first = grp;
       ++c.ncol;
     }
-  // a lone group (the sink) of a head without GQA stays with its key tile, which is launched first;
-  // with G query heads per kv head that workgroup would run G times as long as everything else
-  if (c.ncol < 2 && !gqa) c.ncol = 0;
-  if (c.ncol > 0) {  // the first group has the longest column part
+  if (c.ncol > 0) {
     const int t0 = (first * 64 / LG_BF16_BTK) * LG_BF16_BTK;
     const int t1 = (t0 + LG_BF16_BTK - 1 < m.N - 1) ? t0 + LG_BF16_BTK - 1 : m.N - 1;
-    const int first_tile = lg_qtile_window_hi(m, t1, LG_BF16_BTQ) + 1, last_tile = (m.N - 1) / LG_BF16_BTQ;
-    c.nchunk = last_tile / LG_COL_CHUNK - first_tile / LG_COL_CHUNK + 1;  // chunks are cut at fixed tile numbers
+    c.first = lg_qtile_window_hi(m, t1, LG_BF16_BTQ) + 1;
+    c.last = (m.N - 1) / LG_BF16_BTQ;
+    if (c.ncol == 1 && c.last - c.first < 6) c.ncol = 0;  // a short one stays with its key tile
   }
   return c;
 }
@@ -1541,34 +1762,84 @@ bool dq_wide(const LgMask& m, int D) {
 // dk/dv: by the query tiles of a key tile's window part
 bool dkdv_wide(const LgMask& m, int D) { return D == 128 && (m.wb * m.b + LG_BF16_BTK) / LG_BF16_BTQ >= 16; }
 
+constexpr int CUS = 256;  // compute units the cuts below are made for (they also decide the workspace's size)
+
+// How the window parts are cut: heads x rows work items per key tile and kv head.
+struct Cut {
+  int heads, rows;
+};
+// Few key tiles leave the chip idle: each is one workgroup that walks its window part for every query head of the
+// group, about 3 us (head dim 64: 2.2) per query tile.  They are cut so that the longest work item, or all of them
+// over the CUs, takes least, counting 8 us to start each one and the pass that adds the parts (4 TB/s).  Only with
+// groups of query heads or strided columns: elsewhere dk and dv do not depend on what else a launch holds.
+//   nbh: b x kv heads; tiles: key tiles of a head; steps, longest: query tiles of all of a head's key tiles, and the most
+//   of one; most: parts of a key tile that the workspace has room for
+Cut choose_cut(int D, int G, int nbh, size_t tiles, double steps, int longest, size_t most) {
+  const double each = D == 128 ? 3.0 : 2.2, items = (double)tiles * nbh;
+  Cut best = {1, 1};
+  double least = 0;
+  for (int heads = 1; heads <= G; ++heads) {
+    if (G % heads) continue;
+    for (int rows = 1; rows <= 8 && rows <= longest; ++rows) {
+      const double parts = heads * rows;
+      if (parts > 1 && (items * parts > 4 * CUS || parts > most)) break;
+      const double one = (double)(G / heads) * ((longest + rows - 1) / rows) * each + 8;
+      const double all = (steps * G * nbh * each + items * parts * 8) / CUS;
+      const double fold = parts > 1 ? 5 + items * parts * (4.0 * 64 * D * 2 * 4) / 4e6 : 0;
+      const double t = (one > all ? one : all) + fold;
+      if (parts == 1 || t < 0.9 * least) {
+        least = t;
+        best = {heads, rows};
+      }
+    }
+  }
+  return best;
+}
+// query tiles of the window parts of a sequence's key tiles
+void window_steps(const LgMask& m, double* steps, int* longest) {
+  for (int k0 = 0; k0 < m.N; k0 += LG_BF16_BTK) {
+    const int k1 = k0 + LG_BF16_BTK - 1 < m.N - 1 ? k0 + LG_BF16_BTK - 1 : m.N - 1;
+    const int len = lg_qtile_window_hi(m, k1, LG_BF16_BTQ) - k0 / LG_BF16_BTQ + 1;  // (close enough without a split)
+    *steps += len;
+    *longest = len > *longest ? len : *longest;
+  }
+}
+
 // The workspace of one set of launches.
 struct BwdSize {
-  size_t rows = 0;    // tokens of a head, all sequences (times the batch)
+  size_t seqs = 0;    // sequences (the batch: 1)
+  size_t rows = 0;    // tokens of a head
   size_t ktiles = 0;  // key tiles of a head
   size_t groups = 0;  // 64-key groups of a head
   size_t ncol = 0;    // split-off column groups of a head
+  size_t lone = 0;    // chunks of lone groups
   void add(int n, const Columns& c) {
+    ++seqs;
     rows += n;
     ktiles += (n + LG_BF16_BTK - 1) / LG_BF16_BTK;
     groups += (n + 63) / 64;
     ncol += c.ncol;
+    lone += c.lone();
   }
 };
 struct BwdLayout {  // offsets; -Delta is first
-  size_t nlse, queue, seqs, items, col_of_group, col_list, pdk, pdv, end;
+  size_t nlse, queue, arrived, seqs, items, col_of_group, col_list, colpart, lonepart, parts, end;
 };
-BwdLayout bwd_layout(const BwdSize& z, size_t B, size_t Hq, size_t Hkv, size_t D) {
+BwdLayout bwd_layout(const BwdSize& z, size_t B, size_t Hq, size_t Hkv, size_t D, const Cut& cut) {
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+  const size_t slot = 64 * D * 2 * sizeof(float), nbh = B * Hkv, nparts = (size_t)cut.heads * cut.rows;
   BwdLayout l;
   l.nlse = up(B * Hq * z.rows * sizeof(float));
   l.queue = 2 * l.nlse;  // two work queues of 8 counters
-  l.seqs = l.queue + 256;
+  l.arrived = l.queue + 256;
+  l.seqs = l.arrived + up(nbh * z.seqs * sizeof(unsigned));
   l.items = l.seqs + up(sizeof(LgBwdSeqs));
   l.col_of_group = l.items + up(z.ktiles * sizeof(int));
   l.col_list = l.col_of_group + z.groups * sizeof(int);
-  l.pdk = l.col_of_group + up(2 * z.groups * sizeof(int));
-  l.pdv = l.pdk + B * Hkv * z.ncol * 64 * D * sizeof(float);
-  l.end = l.pdv + (l.pdv - l.pdk);
+  l.colpart = l.col_of_group + up(2 * z.groups * sizeof(int));
+  l.lonepart = l.colpart + nbh * z.ncol * slot;
+  l.parts = l.lonepart + (Hq == Hkv ? nbh * z.lone * slot : 0);
+  l.end = l.parts + (nparts > 1 ? nbh * z.ktiles * nparts * 4 * slot : 0);
   return l;
 }
 
@@ -1579,51 +1850,73 @@ struct BwdLaunch {
   int B, Hq, Hkv, D;
   float scale;
   BwdSize size;
+  Cut cut;
   int qt_wide, qt_rest;   // query tiles of a head in each form of the dq kernel
   int kt_wide, kt_rest;   // key tiles of a head in each form of the dk/dv kernel
-  int citems;             // column work items of a query head
+  int chunk, citems;      // column work items of a query head where there are several groups, and their query tiles
 };
 
 hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv, const uint16_t* uo, const float* lse,
                       const uint16_t* ug, uint16_t* dq, uint16_t* dk, uint16_t* dv, void* ws, const BwdLaunch& a,
                       hipStream_t s, hipEvent_t* ev) {
   const LgMask& m = a.m;
-  const int Hq = a.Hq, Hkv = a.Hkv, ncol = (int)a.size.ncol;
+  const int Hq = a.Hq, Hkv = a.Hkv, nbh = Hkv * a.B, ncol = (int)a.size.ncol, nlone = (int)a.size.lone;
   const float scale = a.scale;
-  const BwdLayout l = bwd_layout(a.size, a.B, Hq, Hkv, a.D);
+  const BwdLayout l = bwd_layout(a.size, a.B, Hq, Hkv, a.D, a.cut);
   char* w = (char*)ws;
   // -Delta and -lse / scale: in this form the dk/dv kernels start the S and dP accumulators from them: S - lse / scale
   // needs one multiply before exp2, and dP - Delta comes out of the matrix pipe directly
   float* ndelta = (float*)w;
   float* nlse = (float*)(w + l.nlse);
   int* queue = (int*)(w + l.queue);
+  unsigned* arrived = (unsigned*)(w + l.arrived);
   LgBwdSeqs* seqs = (LgBwdSeqs*)(w + l.seqs);
   int* items = (int*)(w + l.items);
   int* col_of_group = (int*)(w + l.col_of_group);
   int* col_list = (int*)(w + l.col_list);
-  float* pdk = (float*)(w + l.pdk);
-  float* pdv = (float*)(w + l.pdv);
+  float* colpart = (float*)(w + l.colpart);
   const bool packed = a.setup.n > 0;
   const bool token = m.b == 1 && m.stride == 0;
   int cus = 0, dev = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
     return hipErrorInvalidDevice;
+  const int nparts = a.cut.heads * a.cut.rows;
   const long long most = 0x7fffffffLL - 8 * 16 * 64;  // (room for the padding of the last runs)
-  if ((long long)(a.qt_wide + a.qt_rest) * Hq * a.B > most || (long long)(a.kt_wide + a.kt_rest) * Hkv * a.B > most ||
-      (long long)a.citems * Hq * a.B > most)
+  if ((long long)(a.qt_wide + a.qt_rest) * Hq * a.B > most ||
+      (long long)(a.kt_wide + a.kt_rest) * nbh * nparts * 8 > most || (long long)a.citems * Hq * a.B > most ||
+      (long long)nlone * Hq * a.B > most)
     return hipErrorInvalidValue;
 
   if (ev) (void)hipEventRecord(ev[0], s);
-  const size_t part_floats = (l.end - l.pdk) / sizeof(float);
+  // sums that atomics add to: all but those of lone groups with Hq == Hkv
+  const size_t part_floats = a.citems > 0 || Hq != Hkv ? (l.lonepart - l.colpart) / sizeof(float) : 0;
   const size_t fill_wgs = (part_floats / 2 + 4 * SETUP_NT - 1) / (4 * SETUP_NT);
   bwd_setup_kernel<<<dim3((unsigned)(1 + (packed ? a.setup.n : 1) + (fill_wgs < 1024 ? fill_wgs : 1024))), SETUP_NT, 0,
-                     s>>>(a.setup, m, queue, seqs, items, col_of_group, col_list, ncol, pdk, part_floats);
+                     s>>>(a.setup, m, queue, seqs, items, col_of_group, col_list, ncol, arrived,
+                          nlone > 0 ? nbh * (int)a.size.seqs : 0, colpart, part_floats);
   if (ev) (void)hipEventRecord(ev[1], s);
 
-  LgBwdWork wk = {packed ? seqs : nullptr, items, (int)(packed ? a.size.rows : m.N), 0};
+  LgBwdWork wk;
+  wk.seqs = packed ? seqs : nullptr;
+  wk.items = items;
+  wk.B = a.B;
+  wk.wld = (int)(packed ? a.size.rows : m.N);
+  wk.qt_first = 0;
+  wk.col_of_group = col_of_group;
+  wk.col_list = col_list;
+  wk.ncol = ncol;
+  wk.nlone = nlone;
+  wk.chunk = a.chunk;
+  wk.colpart = colpart;
+  wk.lonepart = Hq == Hkv ? (float*)(w + l.lonepart) : nullptr;
+  wk.nlone_all = nlone;
+  wk.arrived = arrived;
+  wk.heads_cut = a.cut.heads;
+  wk.rows_cut = a.cut.rows;
+  wk.parts = (float*)(w + l.parts);
   if (a.qt_wide > 0) {
-    const int total = a.qt_wide * Hq * a.B, run = lg_run_length(m, total, Hkv * a.B, 8 * (Hq / Hkv), packed);
+    const int total = a.qt_wide * Hq * a.B, run = lg_run_length(m, total, nbh, 8 * (Hq / Hkv), packed);
     const int nitems = (int)lg_run_grid(total, run);
     const dim3 grid((unsigned)(nitems < cus ? nitems : cus));
     if (token)
@@ -1634,7 +1927,7 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
                                                       a.qt_wide, total, run, wk, queue, nitems);
   }
   if (a.qt_rest > 0) {
-    const int total = a.qt_rest * Hq * a.B, run = lg_run_length(m, total, Hkv * a.B, 8 * (Hq / Hkv), packed);
+    const int total = a.qt_rest * Hq * a.B, run = lg_run_length(m, total, nbh, 8 * (Hq / Hkv), packed);
     const dim3 grid((unsigned)lg_run_grid(total, run));
     wk.qt_first = a.qt_wide;
 #define LG_DQ_LAUNCH(DD, TT)                                                                                           \
@@ -1653,48 +1946,39 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
   if (e != hipSuccess) return e;
   if (ev) (void)hipEventRecord(ev[2], s);
 
-  const int nbh = Hkv * a.B;
 #define LG_DKDV_ARGS uq, uk, uv, ug, nlse, ndelta, dk, dv, Hq, Hkv, scale, m
-#define LG_DKDV_LAUNCH(DD, TT, CC, GRID)                                                                            \
-  dkdv_bf16_kernel<DD, TT, CC><<<GRID, 512, 0, s>>>(LG_DKDV_ARGS, nkt, total, per_xcd, col_of_group, col_list, pdk, \
-                                                    pdv, ncol, wk)
+#define LG_DKDV_LAUNCH(DD, TT, CC, GRID) \
+  dkdv_bf16_kernel<DD, TT, CC><<<GRID, 512, 0, s>>>(LG_DKDV_ARGS, nkt, total, run, wk)
+  if (nlone > 0) {
+    const dim3 grid((unsigned)(nlone * Hq * a.B));
+    if (a.D == 64) dkdv_lone_bf16_kernel<64><<<grid, 512, 0, s>>>(uq, uk, uv, ug, nlse, ndelta, Hq, Hkv, scale, m, wk);
+    else dkdv_lone_bf16_kernel<128><<<grid, 512, 0, s>>>(uq, uk, uv, ug, nlse, ndelta, Hq, Hkv, scale, m, wk);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   if (a.citems > 0) {
-    const int nkt = 1, total = nbh, per_xcd = 0;
+    const int nkt = 1, total = nbh, run = 1;
     const dim3 grid((unsigned)(a.citems * Hq * a.B));
-    // column parts are long whatever the window is: the 64-keys form whenever it exists (its
-    // general-predicate instance serves token-granular patterns too)
-    if (a.D == 128)
-      dkdv_wide_bf16_kernel<false, true><<<grid, 256, 0, s>>>(LG_DKDV_ARGS, nkt, total, per_xcd, col_of_group, col_list,
-                                                              pdk, pdv, ncol, wk);
-    else if (token) LG_DKDV_LAUNCH(64, true, true, grid);
+    // column parts are long whatever the window is: the 64-keys form whenever it exists
+    if (a.D == 128) dkdv_wide_bf16_kernel<false, true><<<grid, 256, 0, s>>>(LG_DKDV_ARGS, nkt, total, run, wk);
     else LG_DKDV_LAUNCH(64, false, true, grid);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  // work items of a batch: in XCD-contiguous runs, or (no split-off columns) the sink tiles first
-  auto batch_items = [&](int nkt, int* per_xcd) {
-    const int total = nkt * nbh;
-    *per_xcd = ncol > 0 ? (total + 7) / 8 : (total - nbh + 7) / 8;
-    return ncol > 0 ? *per_xcd * 8 : nbh + *per_xcd * 8;
-  };
   if (a.kt_wide > 0) {
     // one resident workgroup per CU, work items from the second queue
-    const int nkt = a.kt_wide, total = nkt * nbh;
-    int per_xcd = 0;
-    const int nitems = packed ? total : batch_items(nkt, &per_xcd);
+    const int nkt = a.kt_wide, total = nkt * nbh, run = lg_run_length(m, total, nbh, 8, false);
+    const int nitems = packed || nparts > 1 ? total * nparts : (int)lg_run_grid(total, run);
     const dim3 grid((unsigned)(nitems < cus ? nitems : cus));
     if (token)
-      dkdv_wide_bf16_kernel_q<true><<<grid, 256, 0, s>>>(LG_DKDV_ARGS, nkt, total, per_xcd, col_of_group, col_list, pdk,
-                                                         pdv, ncol, wk, queue + 8, nitems);
+      dkdv_wide_bf16_kernel_q<true><<<grid, 256, 0, s>>>(LG_DKDV_ARGS, nkt, total, run, wk, queue + 8, nitems);
     else
-      dkdv_wide_bf16_kernel_q<false><<<grid, 256, 0, s>>>(LG_DKDV_ARGS, nkt, total, per_xcd, col_of_group, col_list,
-                                                          pdk, pdv, ncol, wk, queue + 8, nitems);
+      dkdv_wide_bf16_kernel_q<false><<<grid, 256, 0, s>>>(LG_DKDV_ARGS, nkt, total, run, wk, queue + 8, nitems);
   }
   if (a.kt_rest > 0) {
-    const int nkt = a.kt_rest, total = nkt * nbh;
-    int per_xcd = 0;
-    const dim3 grid((unsigned)(packed ? total : batch_items(nkt, &per_xcd)));
-    wk.items += a.kt_wide;
+    const int nkt = a.kt_rest, total = nkt * nbh, run = lg_run_length(m, total, nbh, 8, false);
+    const dim3 grid((unsigned)(packed || nparts > 1 ? total * nparts : (int)lg_run_grid(total, run)));
+    wk.items = items + a.kt_wide;
     if (a.D == 64) {
       if (token) LG_DKDV_LAUNCH(64, true, false, grid);
       else LG_DKDV_LAUNCH(64, false, false, grid);
@@ -1705,26 +1989,27 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
   }
 #undef LG_DKDV_LAUNCH
 #undef LG_DKDV_ARGS
+  if (nparts > 1) {
+    const dim3 grid((unsigned)((a.kt_wide + a.kt_rest) * nbh * 8));
+    if (a.D == 64) bwd_fold_kernel<64><<<grid, 256, 0, s>>>(dk, dv, nbh, scale, m, wk);
+    else bwd_fold_kernel<128><<<grid, 256, 0, s>>>(dk, dv, nbh, scale, m, wk);
+  }
   e = hipGetLastError();
   if (ev) (void)hipEventRecord(ev[3], s);
   return e;
 }
-}  // namespace
 
-// Packed sequences that share a workspace fill the GPU together, so no workspace is made smaller than this: room for
-// 43000 to 260000 tokens (64 to 8 query heads) in one set of launches.
-constexpr size_t BWD_WORKSPACE_MIN = 64u << 20;
-
-size_t lg_bwd_bf16_workspace_bytes(const LgShape& sh, const LgMask& m) {
-  BwdSize z;
-  z.add(sh.N, columns_of(m, sh.Hq != sh.Hkv));
-  const size_t end = bwd_layout(z, sh.B, sh.Hq, sh.Hkv, sh.D).end;
-  return end > BWD_WORKSPACE_MIN ? end : BWD_WORKSPACE_MIN;
+// Query tiles per column work item where there are several groups: 64, less where that leaves CUs idle.  items(chunk):
+// work items of the launch.
+template <typename F>
+int choose_chunk(F items) {
+  int chunk = 64;
+  while (chunk > 8 && items(chunk) < 2 * CUS) chunk /= 2;
+  return chunk;
 }
 
-hipError_t lg_launch_bwd_bf16(const void* q, const void* k, const void* v, const void* out, const float* lse,
-                              const void* dout, void* dq, void* dk, void* dv, void* ws, const LgShape& sh,
-                              const LgMask& m, hipStream_t s, hipEvent_t* ev) {
+// The launch of a batch: everything but the pointers (also decides the workspace's size).
+BwdLaunch batch_launch(const LgShape& sh, const LgMask& m) {
   BwdLaunch a = {};
   a.m = m;
   a.B = sh.B;
@@ -1732,13 +2017,38 @@ hipError_t lg_launch_bwd_bf16(const void* q, const void* k, const void* v, const
   a.Hkv = sh.Hkv;
   a.D = sh.D;
   a.scale = sh.scale;
-  const Columns c = columns_of(m, sh.Hq != sh.Hkv);
+  const Columns c = columns_of(m);
   a.size.add(sh.N, c);
-  a.citems = (c.ncol + 3) / 4 * c.nchunk;
+  a.chunk = choose_chunk([&](int chunk) { return (long long)c.items(chunk) * sh.Hq * sh.B; });
+  a.citems = c.items(a.chunk);
   (dq_wide(m, sh.D) ? a.qt_wide : a.qt_rest) = (sh.N + LG_BF16_TQ - 1) / LG_BF16_TQ;
-  (dkdv_wide(m, sh.D) ? a.kt_wide : a.kt_rest) = (sh.N + LG_BF16_BTK - 1) / LG_BF16_BTK;
+  (dkdv_wide(m, sh.D) ? a.kt_wide : a.kt_rest) = (int)a.size.ktiles;
+  a.cut = {1, 1};
+  if ((sh.Hq != sh.Hkv || m.stride > 0) && a.size.ktiles * sh.B * sh.Hkv <= 2 * CUS) {
+    double steps = 0;
+    int longest = 0;
+    window_steps(m, &steps, &longest);
+    a.cut = choose_cut(sh.D, sh.Hq / sh.Hkv, sh.B * sh.Hkv, a.size.ktiles, steps, longest, 4 * CUS);
+  }
+  return a;
+}
+}  // namespace
+
+// Packed sequences that share a workspace fill the GPU together, so no workspace is made smaller than this: room for
+// 85000 to 500000 tokens (64 to 8 query heads) in one set of launches.
+constexpr size_t BWD_WORKSPACE_MIN = 128u << 20;
+
+size_t lg_bwd_bf16_workspace_bytes(const LgShape& sh, const LgMask& m) {
+  const BwdLaunch a = batch_launch(sh, m);
+  const size_t end = bwd_layout(a.size, sh.B, sh.Hq, sh.Hkv, sh.D, a.cut).end;
+  return end > BWD_WORKSPACE_MIN ? end : BWD_WORKSPACE_MIN;
+}
+
+hipError_t lg_launch_bwd_bf16(const void* q, const void* k, const void* v, const void* out, const float* lse,
+                              const void* dout, void* dq, void* dk, void* dv, void* ws, const LgShape& sh,
+                              const LgMask& m, hipStream_t s, hipEvent_t* ev) {
   return launch_bwd((const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)out, lse,
-                    (const uint16_t*)dout, (uint16_t*)dq, (uint16_t*)dk, (uint16_t*)dv, ws, a, s, ev);
+                    (const uint16_t*)dout, (uint16_t*)dq, (uint16_t*)dk, (uint16_t*)dv, ws, batch_launch(sh, m), s, ev);
 }
 
 // One set of launches for up to LG_PACK_MAX sequences.  Launched one sequence after the other, a document of 200 .. 8192
@@ -1756,14 +2066,21 @@ hipError_t lg_launch_bwd_bf16_pack(const void* q, const void* k, const void* v, 
       Columns c;
     } seq[LG_PACK_MAX];
     BwdLaunch a = {};
+    a.m = tmpl;
+    a.B = 1;
+    a.Hq = sh.Hq;
+    a.Hkv = sh.Hkv;
+    a.D = sh.D;
+    a.scale = sh.scale;
+    a.cut = {1, 1};
     int& n = a.setup.n;
     for (; x < num_seqs && n < LG_PACK_MAX; ++x) {
       const int len = cu_seqlens[x + 1] - cu_seqlens[x];
       if (len == 0) continue;
-      const Seq one = {cu_seqlens[x], len, columns_of(lg_mask_for_length(tmpl, len), sh.Hq != sh.Hkv)};
+      const Seq one = {cu_seqlens[x], len, columns_of(lg_mask_for_length(tmpl, len))};
       BwdSize z = a.size;
       z.add(len, one.c);
-      if (n > 0 && (bwd_layout(z, 1, sh.Hq, sh.Hkv, sh.D).end > ws_bytes || z.ktiles > 0xffffff ||
+      if (n > 0 && (bwd_layout(z, 1, sh.Hq, sh.Hkv, sh.D, a.cut).end > ws_bytes || z.ktiles > 0xffffff ||
                     (double)z.rows * sh.Hq > 1e9))
         break;
       a.size = z;
@@ -1772,24 +2089,34 @@ hipError_t lg_launch_bwd_bf16_pack(const void* q, const void* k, const void* v, 
       seq[y] = one;
     }
     if (n == 0) break;
-    a.m = tmpl;
-    a.B = 1;
-    a.Hq = sh.Hq;
-    a.Hkv = sh.Hkv;
-    a.D = sh.D;
-    a.scale = sh.scale;
+    auto citems = [&](int chunk) {
+      long long all = 0;
+      for (int y = 0; y < n; ++y) all += seq[y].c.items(chunk);
+      return all * sh.Hq;
+    };
+    a.chunk = choose_chunk(citems);
+    if (citems(a.chunk) > 0x7fffffffLL) return hipErrorInvalidValue;
+    double steps = 0;
+    int longest = 0;
+    const bool may_cut = (sh.Hq != sh.Hkv || tmpl.stride > 0) && a.size.ktiles * sh.Hkv <= 2 * CUS;
     for (int y = 0; y < n; ++y) {
       const LgMask m = lg_mask_for_length(tmpl, seq[y].len);
-      const int citems = (seq[y].c.ncol + 3) / 4 * seq[y].c.nchunk;
       a.setup.row0[y] = seq[y].row0;
       a.setup.len[y] = seq[y].len;
       a.setup.ncol[y] = seq[y].c.ncol;
-      a.setup.citems[y] = citems;
-      a.citems += citems;
+      a.setup.citems[y] = seq[y].c.items(a.chunk);
+      a.setup.nlone[y] = seq[y].c.lone();
+      a.citems += a.setup.citems[y];
       // (both rules are monotone in the length: the wide ones come first)
       (dq_wide(m, sh.D) ? a.qt_wide : a.qt_rest) += (seq[y].len + LG_BF16_TQ - 1) / LG_BF16_TQ;
       (dkdv_wide(m, sh.D) ? a.kt_wide : a.kt_rest) += (seq[y].len + LG_BF16_BTK - 1) / LG_BF16_BTK;
       a.setup.nwide += dkdv_wide(m, sh.D);
+      if (may_cut) window_steps(m, &steps, &longest);
+    }
+    if (may_cut) {
+      const size_t tile = (size_t)sh.Hkv * a.size.ktiles * (4 * 64 * 2 * sizeof(float)) * sh.D;
+      a.cut = choose_cut(sh.D, sh.Hq / sh.Hkv, sh.Hkv, a.size.ktiles, steps, longest,
+                         (ws_bytes - bwd_layout(a.size, 1, sh.Hq, sh.Hkv, sh.D, a.cut).end) / tile);
     }
     const hipError_t e =
         launch_bwd((const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)out, lse,

@@ -64,6 +64,12 @@ __device__ __forceinline__ f32x2_t lg_load_shared2(const float* p) {
                                                  __HIP_MEMORY_SCOPE_AGENT);
   return f32x2_t{__builtin_bit_cast(float, (unsigned)w), __builtin_bit_cast(float, (unsigned)(w >> 32))};
 }
+__device__ __forceinline__ void lg_store_shared1(float* p, float x) {
+  __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float lg_load_shared1(const float* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 __device__ __forceinline__ f32x4_t lg_load_shared4(const float* p) {
   const f32x2_t a = lg_load_shared2(p), b = lg_load_shared2(p + 2);
   return f32x4_t{a[0], a[1], b[0], b[1]};

@@ -176,6 +176,22 @@ def test_float32_parts(B, Hq, Hkv, N, D, sink, window, block, stride):
     check_bwd(B, Hq, Hkv, N, D, sink, window, block, stride, dtype=torch.float32, seed=83)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,N,D,sink,window,block,stride", [
+    # few key tiles: window parts cut by query heads and rows (a cut without rows at the end of the sequence, a group of
+    # three heads, one key tile); lone column groups in one chunk, several, none (a short column part), half a group live
+    (1, 8, 2, 2064, 128, 16, 673, 1, 0),
+    (1, 8, 1, 1300, 64, 40, 130, 1, 0),
+    (1, 6, 2, 1500, 128, 64, 64, 64, 4),
+    (1, 4, 1, 260, 128, 4, 100, 1, 0),
+    (2, 2, 2, 3001, 64, 64, 128, 1, 0),
+    (1, 2, 2, 9000, 128, 5, 700, 1, 0),
+    (1, 1, 1, 900, 128, 16, 256, 1, 0),
+    (1, 2, 2, 2500, 64, 64, 64, 64, 3),
+])
+def test_window_parts_and_lone_columns(B, Hq, Hkv, N, D, sink, window, block, stride):
+    check_bwd(B, Hq, Hkv, N, D, sink, window, block, stride, seed=84)
+
+
 def test_bwd_deterministic_long_window():
     q, k, v, g = lg_synth.prefill_inputs(1, 2, 2, 2000, 128, 10, torch.bfloat16, with_dout=True)
     a = run_fwd_bwd(q, k, v, g, 64, 1024)
