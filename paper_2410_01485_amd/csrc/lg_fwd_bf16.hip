@@ -28,11 +28,11 @@ namespace {
 constexpr int TK = LG_BF16_TK;  // 64 keys per step
 constexpr int TQ = 128;         // query rows per workgroup
 constexpr int NT = TQ * 2;      // threads: one wave per 32 rows
-// Waves per SIMD, and LDS operands of S requested ahead of the matrix instruction that uses them, as the registers
-// of so many waves allow (168 for D = 128, 128 for D = 64)
+// Waves per SIMD, and LDS operands of the two products requested ahead of the matrix instruction that uses them, as the
+// registers of so many waves allow (168 for D = 128, 128 for D = 64)
 template <int D>
 struct LgFwdTune {
-  static constexpr int WAVES = D == 128 ? 3 : 4, AHEAD = D == 128 ? 2 : 3;
+    static constexpr int WAVES = D == 128 ? 3 : 4, AHEAD = D == 128 ? 2 : 3, AHEAD_PV = 4;
 };
 
 // TOKEN: the pattern is token-granular without strided columns (block <= 1, stride 0).  The
@@ -170,8 +170,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) sacc[kb][r] = 0.f;
-    // Each K operand is requested AHEAD matrix instructions early (the compiler on its own asks for it just before
-    // its use, which leaves the LDS latency in the wave's critical path sixteen times per tile).
+    // Each operand from LDS is requested some matrix instructions early (the compiler on its own asks for it just before
+    // its use, which leaves the LDS latency in the wave's critical path sixteen times per product; for V that was 3 %
+    // at 128K tokens, 10 % where a SIMD has one wave).
     {
       constexpr int NQ = 2 * DC, DIST = LgFwdTune<D>::AHEAD;
       bf16x8_t op[DIST + 1];
@@ -259,10 +260,20 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
     if (t2 >= 0) issue_k(t2, buf);
     if (kind != LG_TILE_DEAD) {
     // ---- O^T += V^T P^T ----
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-      for (int db = 0; db < DB; ++db) oacc[db] = lg_mfma32(rd.read_cols(smem, sv, db, c), pf[c], oacc[db]);
+    {
+      constexpr int NPV = 4 * DB, DIST = LgFwdTune<D>::AHEAD_PV;
+      bf16x8_t op[DIST + 1];
+      lg_static_for<DIST>([&](auto U) {
+        constexpr int u = decltype(U)::value;
+        op[u] = rd.read_cols(smem, sv, u % DB, u / DB);
+      });
+      lg_static_for<NPV>([&](auto U) {
+        constexpr int u = decltype(U)::value, w = u + DIST;
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (w < NPV) op[w % (DIST + 1)] = rd.read_cols(smem, sv, w % DB, w / DB);
+        oacc[u % DB] = lg_mfma32(op[u % (DIST + 1)], pf[u / DB], oacc[u % DB]);
+      });
+    }
     }  // kind != dead
 
     t = t1;
