@@ -7,15 +7,14 @@
 // swizzled; lg_swz.h) and are read both with the contraction over dims (row reads) and with the
 // contraction over tile rows (transposing LDS reads), so no tile is ever stored twice.
 //
-//  dq kernel (query-tile major, same tile walk and 4-stage ring as the forward; 8 waves x
-//  32 query rows).  Per live key tile:
+//  dq kernel (query-tile major, same tile walk as the forward; 4 waves x 32 query rows).  Per live key tile:
 //     S^T  = K Q^T,  dP^T = V dO^T      (keys x queries; A = K / V rows from LDS,
 //                                        B = Q / dO fragments kept in registers)
 //     P^T  = exp2(S^T c - lse_i c'),  dS^T = P^T o (dP^T - Delta_i)   (one query per lane)
 //     dQ^T += K^T dS^T                  (dims x queries; A = K through transposing reads,
 //                                        B = dS^T straight from the accumulator registers)
-//  dk/dv kernel (key-tile major; 8 waves x 32 keys = 256 keys per workgroup; the K fragment
-//  of a wave stays in registers, the V rows of the workgroup stay in LDS).  Per live query
+//  dk/dv kernel (key-tile major; a wave for every 32 keys: 256 keys per workgroup for D = 128, 128 for D = 64; the K
+//  fragment of a wave stays in registers, the V rows of the workgroup stay in LDS).  Per live query
 //  tile of 64 rows, for every query head of the kv group:
 //     S  = Q K^T,  dP = dO V^T          (queries x keys; A = Q / dO rows from LDS)
 //     P, dS as above                    (one key per lane; S and dP start from the per-row
@@ -23,6 +22,13 @@
 //     dV^T += dO^T P,  dK^T += Q^T dS   (dims x keys; A = dO / Q through transposing reads,
 //                                        B = P / dS straight from the accumulators)
 // 7 tile products instead of the minimal 5: S and dP are computed in both kernels.
+//
+// What bounds these two: a wave's matrix and vector work follow each other, so a SIMD needs waves in different phases.
+// Workgroups are therefore as small as LDS and registers make several of them fit a CU (dq: 2 for D = 128, 3 for
+// D = 64; dk/dv: 1 and 3), each with its own barriers, and operands from LDS are requested a few matrix instructions
+// ahead.  Against one workgroup of 8 waves with a deeper ring and the compiler's order: dq, 32 heads of 128, 32768
+// tokens, window 512: 805 -> 644 us; 64/8 heads, 9830 tokens, window 455: 489 -> 367 us; dk/dv, 32 heads of 64, 32768
+// tokens, window 4096: 2441 -> 2104 us, window 512: 610 -> 475 us.
 //
 // For head dim 128 and windows of 16 or more tiles both kernels have a second form with 64 rows
 // (keys) per wave, one wave per SIMD and the accumulators in AGPRs (further down): every operand
@@ -34,6 +40,9 @@
 #include "lg_wide.h"
 
 namespace {
+
+// Keys of a dk/dv workgroup.
+constexpr int btk_of(int D) { return D == 128 ? LG_BF16_BTK : 128; }
 
 constexpr float LOG2E = 1.44269504088896340736f;
 
@@ -53,7 +62,7 @@ struct LgBwdSeqs {
   int ncol[LG_PACK_MAX];          // column groups split off (0: none)
   int nlone[LG_PACK_MAX];         // exactly one group: chunks of its column part (0 otherwise)
   int qtile0[LG_PACK_MAX + 1];    // query tiles (LG_BF16_TQ rows) of the sequences before
-  int ktile0[LG_PACK_MAX + 1];    // key tiles (LG_BF16_BTK keys)
+  int ktile0[LG_PACK_MAX + 1];    // key tiles (of a dk/dv workgroup)
   int grp0[LG_PACK_MAX + 1];      // 64-key groups: offset into col_of_group
   int col0[LG_PACK_MAX + 1];      // split-off column groups: offset into col_list and the partial sums
   int citem0[LG_PACK_MAX + 1];    // column work items (virtual tile x chunk), sequences with several groups
@@ -77,9 +86,10 @@ struct LgBwdWork {
   float* lonepart;        // Hq == Hkv: [b x kv head][lone chunks of all sequences] group slots
   int nlone_all;          // lone chunks of all sequences
   unsigned* arrived;      // Hq == Hkv: [b x kv head][sequence] chunks of a lone group that are done
+  bool by_tile;           // dk/dv items: heads innermost (always for packed sequences and cut window parts)
   // window parts cut into `heads_cut` sets of query heads times `rows_cut` runs of query tiles
   int heads_cut, rows_cut;
-  float* parts;           // [key tile][b x kv head][part] four group slots each
+  float* parts;           // [key tile][b x kv head][part] a group slot for each 64 keys
 };
 
 // Partial sums are kept the way the accumulators hold them, 64 keys ("group slot") at a time: [32-key block][dk, dv]
@@ -118,8 +128,14 @@ __device__ __forceinline__ float lg_dot8(uint4 x, uint4 y, float s) {
 // the other half of the wave hold the whole row of dout anyway) and leave -Delta and -lse / scale
 // in the workspace for the dk/dv kernels, which run after them on the same stream.
 // ------------------------------------------------------------------------- dq
+// Waves per SIMD and operands requested ahead, as the registers of so many waves allow (256 for D = 128, 168 for D = 64).
+template <int D>
+struct LgDqTune {
+  static constexpr int WAVES = D == 128 ? 2 : 3, AHEAD = D == 128 ? 3 : 2;
+};
 template <int D, bool TOKEN>
-__global__ __launch_bounds__(512) void dq_bf16_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LgDqTune<D>::WAVES, LgDqTune<D>::WAVES))) void
+dq_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const uint16_t* __restrict__ out, const uint16_t* __restrict__ dout, const float* __restrict__ lse,
     float* __restrict__ ndelta, float* __restrict__ nlse, uint16_t* __restrict__ dq, int Hq, int Hkv, float scale,
@@ -134,14 +150,13 @@ __global__ __launch_bounds__(512) void dq_bf16_kernel(
     m.wb = m.window;
   }
   using T = LgSwzTile<D>;
-  constexpr int NT = 512, STAGES = 4;
+  constexpr int NT = 256;
   using Dma = LgDma<D, NT>;
-  constexpr int TQ = LG_BF16_TQ, TK = LG_BF16_TK;
-  static_assert(TQ == 256 && TK == 64, "8 waves x 32 query rows, 64-key tiles");
+  constexpr int TQ = 128, TK = LG_BF16_TK;
+  static_assert(LG_BF16_TQ == 2 * TQ && TK == 64, "4 waves x 32 query rows, 64-key tiles");
   constexpr int DC = D / 16, DB = D / 32;
   constexpr int STAGE = 2 * T::BYTES;  // K tile + V tile
-  constexpr int LPT = 2 * Dma::CH;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[STAGES * STAGE];
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * STAGE];
 
   const int L = lg_item_of(blockIdx.x, run);
   if (L >= total) return;
@@ -149,13 +164,14 @@ __global__ __launch_bounds__(512) void dq_bf16_kernel(
   // heads of the GQA group: the G workgroups that walk the same K/V tiles run side by side
   const int G = Hq / Hkv;
   const int gq = L % G, rest = L / G;
-  int qt = nqt - 1 - (rest % nqt);
-  const int bhk = rest / nqt;
+  const int half = 1 - (rest & 1), x = (rest >> 1) % nqt;  // (nqt, qtile0: in LG_BF16_TQ rows, two workgroups each)
+  int qt = nqt - 1 - x;
+  const int bhk = (rest >> 1) / nqt;
   const int b = bhk / Hkv, hk = bhk % Hkv;
   const int hq = hk * G + gq;
   int srow = 0, swrow = 0;  // packed: first row of the sequence inside its head, in the workspace
   if (wk.seqs) {
-    const int t = wk.qt_first + rest % nqt;
+    const int t = wk.qt_first + x;
     const int sq = lg_seq_of(wk.seqs->qtile0, lg_uniform(wk.seqs->n), t);
     qt = lg_uniform(wk.seqs->qtile0[sq + 1]) - 1 - t;
     srow = lg_uniform(wk.seqs->row0[sq]);
@@ -165,7 +181,8 @@ __global__ __launch_bounds__(512) void dq_bf16_kernel(
   const int N = m.N;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n = lane & 31, g = lane >> 5;
-  const int q0 = qt * TQ, q1 = min(q0 + TQ - 1, N - 1);
+  const int q0 = (2 * qt + half) * TQ, q1 = min(q0 + TQ - 1, N - 1);
+  if (q0 >= N) return;
   const size_t row0 = (size_t)(b * Hq + hq) * m.ld + srow;       // the sequence's first row in this query head
   const size_t wrow0 = (size_t)(b * Hq + hq) * wk.wld + swrow;   // the same in the workspace
   const size_t qbase = row0 * D;
@@ -224,25 +241,15 @@ __global__ __launch_bounds__(512) void dq_bf16_kernel(
     return lg_qsched_next(m, qs, prev);
   };
   int t = next_tile(-1);
-  int t_issue = t;
-  int ahead = 0;
-  for (; ahead < STAGES - 1 && t_issue >= 0; ++ahead) {
-    issue(t_issue, ahead);
-    t_issue = next_tile(t_issue);
-  }
+  issue(t, 0);
   int stage = 0;
   while (t >= 0) {
-    if (ahead >= 3) LG_WAIT_VMCNT(2 * LPT);
-    else if (ahead == 2) LG_WAIT_VMCNT(LPT);
-    else LG_WAIT_VMCNT(0);
-    __syncthreads();  // tile t landed for everyone; everyone is done with tile t-1
-    if (t_issue >= 0) {
-      issue(t_issue, (stage + STAGES - 1) % STAGES);
-      t_issue = next_tile(t_issue);
-      ++ahead;
-    }
+    LG_WAIT_VMCNT(0);
+    __syncthreads();  // tile t landed for everyone; everyone is done with the one before
+    const int t_next = next_tile(t);
+    if (t_next >= 0) issue(t_next, stage ^ 1);
     const int k0 = t * TK;
-    // A tile that is not live throughout for the workgroup's 256 rows is classified again for
+    // A tile that is not live throughout for the workgroup's 128 rows is classified again for
     // this wave's 32 rows: most waves then find it wholly live or wholly dead (they sit it out).
     int kind = LG_TILE_FULL;
     if (!lg_qsched_full(m, qs, t)) kind = lg_tile_kind(m, qw0, qw1, k0, k0 + TK - 1);
@@ -267,14 +274,20 @@ __global__ __launch_bounds__(512) void dq_bf16_kernel(
     if (kind != LG_TILE_DEAD)
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
+      constexpr int AHEAD = LgDqTune<D>::AHEAD;
       f32x16_t sc, dp;
 #pragma unroll
       for (int r = 0; r < 16; ++r) sc[r] = dp[r] = 0.f;
-#pragma unroll
-      for (int dc = 0; dc < DC; ++dc) {
-        sc = lg_mfma32(rd.read_rows(smem, sk, kb, dc), qf[dc], sc);
-        dp = lg_mfma32(rd.read_rows(smem, sv, kb, dc), gf[dc], dp);
-      }
+      LgRing<2 * DC, AHEAD> rows;
+      auto read_rows = [&](int u) { return rd.read_rows(smem, u & 1 ? sv : sk, kb, u >> 1); };
+      rows.begin(read_rows);
+      rows.run(read_rows, [&](int u, bf16x8_t a) {
+        if (u & 1) dp = lg_mfma32(a, gf[u >> 1], dp);
+        else sc = lg_mfma32(a, qf[u >> 1], sc);
+      });
+      LgRing<2 * DB, AHEAD> cols;
+      auto read_cols = [&](int u) { return rd.read_cols(smem, sk, u % DB, 2 * kb + u / DB); };
+      cols.begin(read_cols);
       float ds[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
@@ -282,16 +295,11 @@ __global__ __launch_bounds__(512) void dq_bf16_kernel(
         if (!full && dead(kb, r)) p = 0.f;
         ds[r] = p * (dp[r] - di);
       }
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const bf16x8_t bop = lg_pack8(ds + 8 * h);
-#pragma unroll
-        for (int db = 0; db < DB; ++db) acc[db] = lg_mfma32(rd.read_cols(smem, sk, db, 2 * kb + h), bop, acc[db]);
-      }
+      const bf16x8_t bop[2] = {lg_pack8(ds), lg_pack8(ds + 8)};
+      cols.run(read_cols, [&](int u, bf16x8_t a) { acc[u % DB] = lg_mfma32(a, bop[u / DB], acc[u % DB]); });
     }
-    --ahead;
-    t = next_tile(t);
-    stage = (stage + 1) % STAGES;
+    t = t_next;
+    stage ^= 1;
   }
 
   if (i < N) {
@@ -324,19 +332,20 @@ __global__ __launch_bounds__(512) void dq_bf16_kernel(
 //   items: the key tiles of the first nwide sequences, then those of the others; within each the tiles farthest from
 //          the end of their sequence, which the most query tiles see, come first
 struct LgBwdSetup {
+  int btk;       // keys of a dk/dv workgroup
   int n, nwide;  // packed sequences, longest first, and how many of them take the 64-keys-per-wave dk/dv kernel; n = 0: batch
   int row0[LG_PACK_MAX], len[LG_PACK_MAX], ncol[LG_PACK_MAX], citems[LG_PACK_MAX], nlone[LG_PACK_MAX];
 };
 constexpr int SETUP_NT = 512;
 
 // Ranks from a ballot per wave plus the counts of the waves before it.  By a whole workgroup.
-__device__ void column_table(int* __restrict__ col_of_group, int* __restrict__ col_list, const LgMask& m) {
+__device__ void column_table(int* __restrict__ col_of_group, int* __restrict__ col_list, const LgMask& m, int btk) {
   __shared__ int wcount[SETUP_NT / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ngroups = (m.N + 63) / 64;
   int base = 0;
   for (int c0 = 0; c0 < ngroups; c0 += SETUP_NT) {
     const int c = c0 + tid;
-    const bool is = c < ngroups && lg_is_column_group(m, c, LG_BF16_BTK, LG_BF16_BTQ);
+    const bool is = c < ngroups && lg_is_column_group(m, c, btk, LG_BF16_BTQ);
     const unsigned long long bal = __ballot(is);
     if (lane == 0) wcount[wave] = __popcll(bal);
     __syncthreads();
@@ -372,7 +381,7 @@ __global__ __launch_bounds__(SETUP_NT) void bwd_setup_kernel(LgBwdSetup a, LgMas
     for (int x = tid; x < narrived; x += SETUP_NT) arrived[x] = 0;
   }
   if (a.n == 0) {
-    if (blockIdx.x == 1 && ncol > 0) column_table(col_of_group, col_list, m);
+    if (blockIdx.x == 1 && ncol > 0) column_table(col_of_group, col_list, m, a.btk);
     return;
   }
   // running sums over the sequences: query tiles, key tiles, groups, split-off column groups, column work items, rows
@@ -383,7 +392,7 @@ __global__ __launch_bounds__(SETUP_NT) void bwd_setup_kernel(LgBwdSetup a, LgMas
   if (tid < 7) sum[tid][0] = 0;
   if (tid < LG_PACK_MAX) {
     sum[0][tid + 1] = (len + LG_BF16_TQ - 1) / LG_BF16_TQ;
-    sum[1][tid + 1] = (len + LG_BF16_BTK - 1) / LG_BF16_BTK;
+    sum[1][tid + 1] = (len + a.btk - 1) / a.btk;
     sum[2][tid + 1] = (len + 63) / 64;
     sum[3][tid + 1] = tid < a.n ? a.ncol[tid] : 0;
     sum[4][tid + 1] = tid < a.n ? a.citems[tid] : 0;
@@ -402,7 +411,7 @@ __global__ __launch_bounds__(SETUP_NT) void bwd_setup_kernel(LgBwdSetup a, LgMas
   if (blockIdx.x > 0) {
     const int sq = blockIdx.x - 1;
     if (a.ncol[sq] > 0)
-      column_table(col_of_group + sum[2][sq], col_list + sum[3][sq], lg_mask_for_length(m, a.len[sq]));
+      column_table(col_of_group + sum[2][sq], col_list + sum[3][sq], lg_mask_for_length(m, a.len[sq]), a.btk);
     return;
   }
   if (tid == 0) seqs->n = a.n;
@@ -452,10 +461,10 @@ __device__ __forceinline__ LgBwdItem lg_bwd_item(const LgBwdSeqs* __restrict__ s
           lg_uniform(seqs->grp0[sq]), lg_uniform(seqs->col0[sq]), lg_uniform(seqs->ncol[sq])};
 }
 
-// A main work item: key tile, (b, kv head) and part of the window part.  One part, a batch: all items in runs per XCD
-// (lg_item_of), so that neighbouring key tiles share their Q / dO rows in one XCD's L2.  Otherwise kv heads innermost
-// (with a multiple of 8 of them all key tiles of a head run on one XCD), packed sequences in the order of the item
-// list.  False: an id of the padding.
+// A main work item: key tile, (b, kv head) and part of the window part.  Many items of a batch: in runs per XCD
+// (lg_item_of), so that neighbouring key tiles share their Q / dO rows in one XCD's L2.  Otherwise (by_tile) heads
+// innermost: the tiles with the most rows start first (with a multiple of 8 heads all tiles of a head still run on one
+// XCD), packed sequences in the order of the item list.  False: an id of the padding.
 struct LgBwdMain {
   int kt, bh, part;
 };
@@ -463,7 +472,7 @@ __device__ __forceinline__ bool lg_bwd_main(const LgBwdWork& wk, int bid, int nk
                                             LgBwdItem& it, LgBwdMain& w) {
   const int nbh = total / nkt, nparts = wk.heads_cut * wk.rows_cut;
   w.part = 0;
-  if (wk.seqs || nparts > 1) {
+  if (wk.by_tile) {
     w.bh = bid % nbh;
     const int y = bid / nbh;
     w.part = y % nparts;
@@ -492,12 +501,12 @@ __device__ __forceinline__ void lg_bwd_part_range(const LgBwdWork& wk, const LgM
   *lo = first + len * c / wk.rows_cut;
   *hi = first + len * (c + 1) / wk.rows_cut - 1;
 }
-// Where a part's sums go: four group slots.
+// Where a part's sums go: a group slot for each 64 keys.
 template <int D>
 __device__ __forceinline__ float* lg_bwd_part_slot(const LgBwdWork& wk, const LgBwdItem& it, const LgBwdMain& w,
                                                    int nbh) {
   return wk.parts + (((size_t)(it.ktile0 + w.kt) * nbh + w.bh) * (wk.heads_cut * wk.rows_cut) + w.part) *
-                        (4 * LgSlot<D>::FLOATS);
+                        (btk_of(D) / 64 * LgSlot<D>::FLOATS);
 }
 
 // 32 query rows against the wave's 32 keys, in an order that keeps few values alive at a time:
@@ -507,8 +516,11 @@ template <int D, typename Dead>
 __device__ __forceinline__ void lg_dkdv_block(const unsigned char* smem, const LgSwzReader<D>& rd, int sq, int sg, int voff,
                                               const float* sL, const bf16x8_t (&kf)[D / 16], f32x16_t (&ak)[D / 32],
                                               f32x16_t (&av)[D / 32], float sl2, int g, bool full, Dead dead) {
-  constexpr int DC = D / 16, DB = D / 32;
+  constexpr int DC = D / 16, DB = D / 32, AHEAD = D == 128 ? 2 : 3;
   float p[16];
+  LgRing<2 * DB, AHEAD> cols;
+  auto g_cols = [&](int u) { return rd.read_cols(smem, sg, u % DB, u / DB); };
+  auto q_cols = [&](int u) { return rd.read_cols(smem, sq, u % DB, u / DB); };
   __builtin_amdgcn_sched_barrier(0);  // phases stay apart: bounds the operands held at once
   {
     // the accumulator starts from -lse / scale of its rows (register r <-> row 8 (r / 4) + 4g + r % 4)
@@ -518,8 +530,11 @@ __device__ __forceinline__ void lg_dkdv_block(const unsigned char* smem, const L
       const float4 l4 = *reinterpret_cast<const float4*>(sL + 8 * r4 + 4 * g);
       sc[4 * r4 + 0] = l4.x; sc[4 * r4 + 1] = l4.y; sc[4 * r4 + 2] = l4.z; sc[4 * r4 + 3] = l4.w;
     }
-#pragma unroll
-    for (int dc = 0; dc < DC; ++dc) sc = lg_mfma32(rd.read_rows(smem, sq, 0, dc), kf[dc], sc);
+    LgRing<DC, AHEAD> rows;
+    auto q_rows = [&](int u) { return rd.read_rows(smem, sq, 0, u); };
+    rows.begin(q_rows);
+    rows.run(q_rows, [&](int u, bf16x8_t a) { sc = lg_mfma32(a, kf[u], sc); });
+    cols.begin(g_cols);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       float pv = __builtin_amdgcn_exp2f(sc[r] * sl2);
@@ -527,12 +542,9 @@ __device__ __forceinline__ void lg_dkdv_block(const unsigned char* smem, const L
       p[r] = pv;
     }
   }
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const bf16x8_t pb = lg_pack8(p + 8 * h);
-#pragma unroll
-    for (int db = 0; db < DB; ++db) av[db] = lg_mfma32(rd.read_cols(smem, sg, db, h), pb, av[db]);
+  {
+    const bf16x8_t pb[2] = {lg_pack8(p), lg_pack8(p + 8)};
+    cols.run(g_cols, [&](int u, bf16x8_t a) { av[u % DB] = lg_mfma32(a, pb[u / DB], av[u % DB]); });
   }
   __builtin_amdgcn_sched_barrier(0);
   {
@@ -542,23 +554,33 @@ __device__ __forceinline__ void lg_dkdv_block(const unsigned char* smem, const L
       const float4 d4 = *reinterpret_cast<const float4*>(sL + 64 + 8 * r4 + 4 * g);
       dp[4 * r4 + 0] = d4.x; dp[4 * r4 + 1] = d4.y; dp[4 * r4 + 2] = d4.z; dp[4 * r4 + 3] = d4.w;
     }
-#pragma unroll
-    for (int dc = 0; dc < DC; ++dc)
-      dp = lg_mfma32(rd.read_rows(smem, sg, 0, dc), rd.read_rows(smem, voff, 0, dc), dp);
+    LgRing<DC, AHEAD> rows, vrows;
+    auto g_rows = [&](int u) { return rd.read_rows(smem, sg, 0, u); };
+    auto v_rows = [&](int u) { return rd.read_rows(smem, voff, 0, u); };
+    rows.begin(g_rows);
+    vrows.begin(v_rows);
+    lg_static_for<DC>([&](auto U) {
+      constexpr int u = decltype(U)::value, w = u + AHEAD, x = w % (AHEAD + 1), y = u % (AHEAD + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (w < DC) {
+        rows.op[x] = g_rows(w);
+        vrows.op[x] = v_rows(w);
+      }
+      dp = lg_mfma32(rows.op[y], vrows.op[y], dp);
+    });
+    cols.begin(q_cols);
 #pragma unroll
     for (int r = 0; r < 16; ++r) p[r] *= dp[r];  // p becomes dS
   }
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const bf16x8_t db_ = lg_pack8(p + 8 * h);
-#pragma unroll
-    for (int db = 0; db < DB; ++db) ak[db] = lg_mfma32(rd.read_cols(smem, sq, db, h), db_, ak[db]);
+  {
+    const bf16x8_t db_[2] = {lg_pack8(p), lg_pack8(p + 8)};
+    cols.run(q_cols, [&](int u, bf16x8_t a) { ak[u % DB] = lg_mfma32(a, db_[u / DB], ak[u % DB]); });
   }
 }
 
 template <int D, bool TOKEN, bool COLUMN>
-__global__ __launch_bounds__(512) void dkdv_bf16_kernel(
+__global__ __launch_bounds__(btk_of(D) * 2) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 3, D == 128 ? 2 : 3))) void
+dkdv_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const uint16_t* __restrict__ dout, const float* __restrict__ nlse, const float* __restrict__ ndelta,
     uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int Hq, int Hkv, float scale, LgMask m_in,
@@ -573,13 +595,12 @@ __global__ __launch_bounds__(512) void dkdv_bf16_kernel(
     m.wb = m.window;
   }
   using T = LgSwzTile<D>;
-  constexpr int NT = 512;
+  constexpr int TQ = LG_BF16_BTQ, TK = btk_of(D), NT = 2 * TK, NG = TK / 64;
   using Dma = LgDma<D, NT>;
-  constexpr int TQ = LG_BF16_BTQ, TK = LG_BF16_BTK;
-  static_assert(TQ == 64 && TK == 256, "64 query rows per step, 8 waves x 32 keys");
+  static_assert(TQ == 64, "64 query rows per step, a wave for every 32 keys");
   constexpr int DC = D / 16, DB = D / 32;
   constexpr int HALF = 32 * T::ROW_BYTES;
-  constexpr int VRES = 4 * T::BYTES;                 // the workgroup's 256 V rows
+  constexpr int VRES = NG * T::BYTES;                // the workgroup's V rows
   constexpr int OFF_G = T::BYTES, OFF_L = 2 * T::BYTES;
   constexpr int STAGE = 2 * T::BYTES + 1024;         // Q tile, dO tile, -lse / scale | -Delta (2 x 64 floats)
   __shared__ __attribute__((aligned(1024))) unsigned char smem[VRES + 2 * STAGE];
@@ -608,7 +629,7 @@ __global__ __launch_bounds__(512) void dkdv_bf16_kernel(
       x -= lg_uniform(wk.seqs->citem0[sq]);
       it = lg_bwd_item(wk.seqs, sq, m);
     }
-    const int nvt = (it.ncol + 3) / 4;
+    const int nvt = (it.ncol + NG - 1) / NG;
     vt = x % nvt;
     chunk = x / nvt;
     gq = hd % G;
@@ -625,10 +646,10 @@ __global__ __launch_bounds__(512) void dkdv_bf16_kernel(
   // this wave's 32 keys: part of the key tile, or half of one of the virtual tile's column groups
   int kw0 = k0 + wave_s * 32;
   int col_gi = 0;        // COLUMN: index of this wave's column group
-  bool active = true;    // COLUMN: the virtual tile may have fewer than 4 groups
+  bool active = true;    // COLUMN: the virtual tile may have fewer groups
   int r0_w = 0;          // COLUMN: first row of the wave's column part
   if (COLUMN) {
-    col_gi = 4 * vt + (wave_s >> 1);
+    col_gi = NG * vt + (wave_s >> 1);
     active = col_gi < ncol;
     const int grp = clist[min(col_gi, ncol - 1)];
     kw0 = 64 * grp + 32 * (wave_s & 1);
@@ -658,7 +679,7 @@ __global__ __launch_bounds__(512) void dkdv_bf16_kernel(
     // window part of the virtual tile's first group
     const int tf = min((64 * clist[0] / TK) * TK + TK - 1, N - 1);
     const int c_abs = (lg_qtile_window_hi(m, tf, TQ) + 1) / wk.chunk + chunk;
-    const int grp0 = clist[4 * vt];
+    const int grp0 = clist[NG * vt];
     const int t1 = min((64 * grp0 / TK) * TK + TK - 1, N - 1);
     lo = max(lg_qtile_window_hi(m, t1, TQ) + 1, c_abs * wk.chunk);
     hi = min((N - 1) / TQ, c_abs * wk.chunk + wk.chunk - 1);
@@ -679,8 +700,8 @@ __global__ __launch_bounds__(512) void dkdv_bf16_kernel(
   const uint32_t lds0 = (uint32_t)(uintptr_t)LG_LDS_PTR(unsigned char, smem);
   // the workgroup's V rows, resident for the whole kernel
 #pragma unroll
-  for (int x = 0; x < 4; ++x) {
-    const int r0 = COLUMN ? 64 * clist[min(4 * vt + x, ncol - 1)] : k0 + 64 * x;
+  for (int x = 0; x < NG; ++x) {
+    const int r0 = COLUMN ? 64 * clist[min(NG * vt + x, ncol - 1)] : k0 + 64 * x;
     const int rc = min(r0, N - 1);  // a tile wholly past the end repeats the last row
     dma.issue(v + kbase + (size_t)rc * D, r0 < N ? N - r0 : 1, lds0 + x * T::BYTES);
   }
@@ -823,7 +844,7 @@ __global__ __launch_bounds__(512) void dkdv_lone_bf16_kernel(
   using Slot = LgSlot<D>;
   constexpr int NT = 512;
   using Dma = LgDma<D, NT>;
-  constexpr int TQ = LG_BF16_BTQ, TK = LG_BF16_BTK, DC = D / 16, DB = D / 32;
+  constexpr int TQ = LG_BF16_BTQ, TK = btk_of(D), DC = D / 16, DB = D / 32;
   constexpr int HALF = 32 * T::ROW_BYTES;
   constexpr int OFF_G = T::BYTES, OFF_L = 2 * T::BYTES, STAGE = 2 * T::BYTES + 1024;  // as in the kernel above
   __shared__ __attribute__((aligned(1024))) unsigned char smem[T::BYTES + 4 * STAGE];  // V rows, two pairs of tiles
@@ -969,14 +990,15 @@ __global__ __launch_bounds__(256) void bwd_fold_kernel(uint16_t* __restrict__ dk
                                                        float scale, LgMask m, LgBwdWork wk) {
   using Slot = LgSlot<D>;
   constexpr int DB = D / 32;
-  const int kb32 = blockIdx.x & 7, x = blockIdx.x >> 3, bh = x % nbh, t = x / nbh;
+  constexpr int KB = btk_of(D) / 32;
+  const int kb32 = blockIdx.x % KB, x = blockIdx.x / KB, bh = x % nbh, t = x / nbh;
   const int nparts = wk.heads_cut * wk.rows_cut;
   LgBwdItem it = {0, 0, 0, 0, 0, wk.ncol};
   if (wk.seqs) it = lg_bwd_item(wk.seqs, lg_seq_of(wk.seqs->ktile0, lg_uniform(wk.seqs->n), t), m);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 31, g = lane >> 5;
-  const int kw0 = (t - it.ktile0) * LG_BF16_BTK + 32 * kb32, j = kw0 + n;
+  const int kw0 = (t - it.ktile0) * btk_of(D) + 32 * kb32, j = kw0 + n;
   if (kw0 >= m.N) return;
-  const float* src = wk.parts + ((size_t)t * nbh + bh) * nparts * (4 * Slot::FLOATS) + (kb32 >> 1) * Slot::FLOATS + lane;
+  const float* src = wk.parts + ((size_t)t * nbh + bh) * nparts * (KB / 2 * Slot::FLOATS) + (kb32 >> 1) * Slot::FLOATS + lane;
   const int cid = it.ncol > 0 ? wk.col_of_group[it.grp0 + (kw0 >> 6)] : -1;
   const float* csum = wk.colpart + ((size_t)bh * wk.ncol + it.col0 + max(cid, 0)) * Slot::FLOATS + lane;
   for (int y = wave; y < 2 * DB; y += 4) {
@@ -986,7 +1008,7 @@ __global__ __launch_bounds__(256) void bwd_fold_kernel(uint16_t* __restrict__ dk
     for (int r = 0; r < 16; ++r) a[r] = 0.f;
     for (int p = 0; p < nparts; ++p)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) a[r] += src[(size_t)p * (4 * Slot::FLOATS) + at + 64 * r];
+      for (int r = 0; r < 16; ++r) a[r] += src[(size_t)p * (KB / 2 * Slot::FLOATS) + at + 64 * r];
     if (cid >= 0)
 #pragma unroll
       for (int r = 0; r < 16; ++r) a[r] += lg_load_shared1(csum + at + 64 * r);
@@ -1732,19 +1754,23 @@ struct Columns {
     return ncol != 1 ? 0 : pairs < 16 ? 1 : pairs < 64 ? pairs / 8 : 8;
   }
   // several: work items (virtual tile x chunk) of a query head; chunks are cut at multiples of `chunk` tiles
-  int items(int chunk) const { return ncol < 2 ? 0 : (ncol + 3) / 4 * (last / chunk - first / chunk + 1); }
+  int items(int D, int chunk) const {
+    const int ng = btk_of(D) / 64;
+    return ncol < 2 ? 0 : (ncol + ng - 1) / ng * (last / chunk - first / chunk + 1);
+  }
 };
-Columns columns_of(const LgMask& m) {
+Columns columns_of(const LgMask& m, int D) {
+  const int btk = btk_of(D);
   Columns c = {0, 0, 0};
   int first = -1;
   for (int grp = 0; grp < (m.N + 63) / 64; ++grp)
-    if (lg_is_column_group(m, grp, LG_BF16_BTK, LG_BF16_BTQ)) {
+    if (lg_is_column_group(m, grp, btk, LG_BF16_BTQ)) {
       if (first < 0) first = grp;
       ++c.ncol;
     }
   if (c.ncol > 0) {
-    const int t0 = (first * 64 / LG_BF16_BTK) * LG_BF16_BTK;
-    const int t1 = (t0 + LG_BF16_BTK - 1 < m.N - 1) ? t0 + LG_BF16_BTK - 1 : m.N - 1;
+    const int t0 = first * 64 / btk * btk;
+    const int t1 = t0 + btk - 1 < m.N - 1 ? t0 + btk - 1 : m.N - 1;
     c.first = lg_qtile_window_hi(m, t1, LG_BF16_BTQ) + 1;
     c.last = (m.N - 1) / LG_BF16_BTQ;
     if (c.ncol == 1 && c.last - c.first < 6) c.ncol = 0;  // a short one stays with its key tile
@@ -1769,23 +1795,25 @@ struct Cut {
   int heads, rows;
 };
 // Few key tiles leave the chip idle: each is one workgroup that walks its window part for every query head of the
-// group, about 3 us (head dim 64: 2.2) per query tile.  They are cut so that the longest work item, or all of them
-// over the CUs, takes least, counting 8 us to start each one and the pass that adds the parts (4 TB/s).  Only with
-// groups of query heads or strided columns: elsewhere dk and dv do not depend on what else a launch holds.
+// group.  They are cut so that the longest work item, or all of them over the CUs, takes least.  Measured: a query tile
+// takes 3 us, starting an item 8 (head dim 64, three workgroups per CU: 1.5 and 8 for one, 1 and 3 for each of many), the
+// pass that adds the parts 4 TB/s.  Only with groups of query heads or strided columns: elsewhere dk and dv do not
+// depend on what else a launch holds.
 //   nbh: b x kv heads; tiles: key tiles of a head; steps, longest: query tiles of all of a head's key tiles, and the most
 //   of one; most: parts of a key tile that the workspace has room for
 Cut choose_cut(int D, int G, int nbh, size_t tiles, double steps, int longest, size_t most) {
-  const double each = D == 128 ? 3.0 : 2.2, items = (double)tiles * nbh;
+  const double each1 = D == 128 ? 3.0 : 1.5, each = D == 128 ? 3.0 : 1.0, start = D == 128 ? 8 : 3;
+  const double items = (double)tiles * nbh;
   Cut best = {1, 1};
   double least = 0;
   for (int heads = 1; heads <= G; ++heads) {
     if (G % heads) continue;
     for (int rows = 1; rows <= 8 && rows <= longest; ++rows) {
       const double parts = heads * rows;
-      if (parts > 1 && (items * parts > 4 * CUS || parts > most)) break;
-      const double one = (double)(G / heads) * ((longest + rows - 1) / rows) * each + 8;
-      const double all = (steps * G * nbh * each + items * parts * 8) / CUS;
-      const double fold = parts > 1 ? 5 + items * parts * (4.0 * 64 * D * 2 * 4) / 4e6 : 0;
+      if (parts > 1 && (items * parts > (D == 128 ? 4 : 8) * CUS || parts > most)) break;
+      const double one = (double)(G / heads) * ((longest + rows - 1) / rows) * each1 + 8;
+      const double all = (steps * G * nbh * each + items * parts * start) / CUS;
+      const double fold = parts > 1 ? 5 + items * parts * (btk_of(D) * D * 8.0) / 4e6 : 0;
       const double t = (one > all ? one : all) + fold;
       if (parts == 1 || t < 0.9 * least) {
         least = t;
@@ -1796,9 +1824,9 @@ Cut choose_cut(int D, int G, int nbh, size_t tiles, double steps, int longest, s
   return best;
 }
 // query tiles of the window parts of a sequence's key tiles
-void window_steps(const LgMask& m, double* steps, int* longest) {
-  for (int k0 = 0; k0 < m.N; k0 += LG_BF16_BTK) {
-    const int k1 = k0 + LG_BF16_BTK - 1 < m.N - 1 ? k0 + LG_BF16_BTK - 1 : m.N - 1;
+void window_steps(const LgMask& m, int btk, double* steps, int* longest) {
+  for (int k0 = 0; k0 < m.N; k0 += btk) {
+    const int k1 = k0 + btk - 1 < m.N - 1 ? k0 + btk - 1 : m.N - 1;
     const int len = lg_qtile_window_hi(m, k1, LG_BF16_BTQ) - k0 / LG_BF16_BTQ + 1;  // (close enough without a split)
     *steps += len;
     *longest = len > *longest ? len : *longest;
@@ -1813,10 +1841,10 @@ struct BwdSize {
   size_t groups = 0;  // 64-key groups of a head
   size_t ncol = 0;    // split-off column groups of a head
   size_t lone = 0;    // chunks of lone groups
-  void add(int n, const Columns& c) {
+  void add(int n, int D, const Columns& c) {
     ++seqs;
     rows += n;
-    ktiles += (n + LG_BF16_BTK - 1) / LG_BF16_BTK;
+    ktiles += (n + btk_of(D) - 1) / btk_of(D);
     groups += (n + 63) / 64;
     ncol += c.ncol;
     lone += c.lone();
@@ -1839,7 +1867,7 @@ BwdLayout bwd_layout(const BwdSize& z, size_t B, size_t Hq, size_t Hkv, size_t D
   l.colpart = l.col_of_group + up(2 * z.groups * sizeof(int));
   l.lonepart = l.colpart + nbh * z.ncol * slot;
   l.parts = l.lonepart + (Hq == Hkv ? nbh * z.lone * slot : 0);
-  l.end = l.parts + (nparts > 1 ? nbh * z.ktiles * nparts * 4 * slot : 0);
+  l.end = l.parts + (nparts > 1 ? nbh * z.ktiles * nparts * (btk_of(D) / 64) * slot : 0);
   return l;
 }
 
@@ -1883,7 +1911,7 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
     return hipErrorInvalidDevice;
   const int nparts = a.cut.heads * a.cut.rows;
   const long long most = 0x7fffffffLL - 8 * 16 * 64;  // (room for the padding of the last runs)
-  if ((long long)(a.qt_wide + a.qt_rest) * Hq * a.B > most ||
+  if ((long long)(a.qt_wide + 2 * a.qt_rest) * Hq * a.B > most ||
       (long long)(a.kt_wide + a.kt_rest) * nbh * nparts * 8 > most || (long long)a.citems * Hq * a.B > most ||
       (long long)nlone * Hq * a.B > most)
     return hipErrorInvalidValue;
@@ -1912,6 +1940,9 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
   wk.lonepart = Hq == Hkv ? (float*)(w + l.lonepart) : nullptr;
   wk.nlone_all = nlone;
   wk.arrived = arrived;
+  // heads innermost also where a CU gets few items and every XCD whole heads: head by head, CUs 0, 8, .. of an XCD
+  // would get the longest items of several heads, CUs 7, 15, .. the shortest
+  wk.by_tile = packed || nparts > 1 || (nbh % 8 == 0 && (long long)(a.kt_wide + a.kt_rest) * nbh <= 8 * CUS);
   wk.heads_cut = a.cut.heads;
   wk.rows_cut = a.cut.rows;
   wk.parts = (float*)(w + l.parts);
@@ -1927,11 +1958,11 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
                                                       a.qt_wide, total, run, wk, queue, nitems);
   }
   if (a.qt_rest > 0) {
-    const int total = a.qt_rest * Hq * a.B, run = lg_run_length(m, total, nbh, 8 * (Hq / Hkv), packed);
+    const int total = 2 * a.qt_rest * Hq * a.B, run = lg_run_length(m, total, nbh, 16 * (Hq / Hkv), packed);
     const dim3 grid((unsigned)lg_run_grid(total, run));
     wk.qt_first = a.qt_wide;
 #define LG_DQ_LAUNCH(DD, TT)                                                                                           \
-  dq_bf16_kernel<DD, TT><<<grid, 512, 0, s>>>(uq, uk, uv, uo, ug, lse, ndelta, nlse, dq, Hq, Hkv, scale, m, a.qt_rest, \
+  dq_bf16_kernel<DD, TT><<<grid, 256, 0, s>>>(uq, uk, uv, uo, ug, lse, ndelta, nlse, dq, Hq, Hkv, scale, m, a.qt_rest, \
                                               total, run, wk)
     if (a.D == 64) {
       if (token) LG_DQ_LAUNCH(64, true);
@@ -1948,7 +1979,7 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
 
 #define LG_DKDV_ARGS uq, uk, uv, ug, nlse, ndelta, dk, dv, Hq, Hkv, scale, m
 #define LG_DKDV_LAUNCH(DD, TT, CC, GRID) \
-  dkdv_bf16_kernel<DD, TT, CC><<<GRID, 512, 0, s>>>(LG_DKDV_ARGS, nkt, total, run, wk)
+  dkdv_bf16_kernel<DD, TT, CC><<<GRID, 2 * btk_of(DD), 0, s>>>(LG_DKDV_ARGS, nkt, total, run, wk)
   if (nlone > 0) {
     const dim3 grid((unsigned)(nlone * Hq * a.B));
     if (a.D == 64) dkdv_lone_bf16_kernel<64><<<grid, 512, 0, s>>>(uq, uk, uv, ug, nlse, ndelta, Hq, Hkv, scale, m, wk);
@@ -1968,7 +1999,7 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
   if (a.kt_wide > 0) {
     // one resident workgroup per CU, work items from the second queue
     const int nkt = a.kt_wide, total = nkt * nbh, run = lg_run_length(m, total, nbh, 8, false);
-    const int nitems = packed || nparts > 1 ? total * nparts : (int)lg_run_grid(total, run);
+    const int nitems = wk.by_tile ? total * nparts : (int)lg_run_grid(total, run);
     const dim3 grid((unsigned)(nitems < cus ? nitems : cus));
     if (token)
       dkdv_wide_bf16_kernel_q<true><<<grid, 256, 0, s>>>(LG_DKDV_ARGS, nkt, total, run, wk, queue + 8, nitems);
@@ -1977,7 +2008,7 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
   }
   if (a.kt_rest > 0) {
     const int nkt = a.kt_rest, total = nkt * nbh, run = lg_run_length(m, total, nbh, 8, false);
-    const dim3 grid((unsigned)(packed || nparts > 1 ? total * nparts : (int)lg_run_grid(total, run)));
+    const dim3 grid((unsigned)(wk.by_tile ? total * nparts : (int)lg_run_grid(total, run)));
     wk.items = items + a.kt_wide;
     if (a.D == 64) {
       if (token) LG_DKDV_LAUNCH(64, true, false, grid);
@@ -1990,7 +2021,7 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
 #undef LG_DKDV_LAUNCH
 #undef LG_DKDV_ARGS
   if (nparts > 1) {
-    const dim3 grid((unsigned)((a.kt_wide + a.kt_rest) * nbh * 8));
+    const dim3 grid((unsigned)((a.kt_wide + a.kt_rest) * nbh * (btk_of(a.D) / 32)));
     if (a.D == 64) bwd_fold_kernel<64><<<grid, 256, 0, s>>>(dk, dv, nbh, scale, m, wk);
     else bwd_fold_kernel<128><<<grid, 256, 0, s>>>(dk, dv, nbh, scale, m, wk);
   }
@@ -2017,18 +2048,19 @@ BwdLaunch batch_launch(const LgShape& sh, const LgMask& m) {
   a.Hkv = sh.Hkv;
   a.D = sh.D;
   a.scale = sh.scale;
-  const Columns c = columns_of(m);
-  a.size.add(sh.N, c);
-  a.chunk = choose_chunk([&](int chunk) { return (long long)c.items(chunk) * sh.Hq * sh.B; });
-  a.citems = c.items(a.chunk);
+  const Columns c = columns_of(m, sh.D);
+  a.setup.btk = btk_of(sh.D);
+  a.size.add(sh.N, sh.D, c);
+  a.chunk = choose_chunk([&](int chunk) { return (long long)c.items(sh.D, chunk) * sh.Hq * sh.B; });
+  a.citems = c.items(sh.D, a.chunk);
   (dq_wide(m, sh.D) ? a.qt_wide : a.qt_rest) = (sh.N + LG_BF16_TQ - 1) / LG_BF16_TQ;
   (dkdv_wide(m, sh.D) ? a.kt_wide : a.kt_rest) = (int)a.size.ktiles;
   a.cut = {1, 1};
-  if ((sh.Hq != sh.Hkv || m.stride > 0) && a.size.ktiles * sh.B * sh.Hkv <= 2 * CUS) {
+  if ((sh.Hq != sh.Hkv || m.stride > 0) && a.size.ktiles * sh.B * sh.Hkv <= (sh.D == 128 ? 2 : 4) * CUS) {
     double steps = 0;
     int longest = 0;
-    window_steps(m, &steps, &longest);
-    a.cut = choose_cut(sh.D, sh.Hq / sh.Hkv, sh.B * sh.Hkv, a.size.ktiles, steps, longest, 4 * CUS);
+    window_steps(m, a.setup.btk, &steps, &longest);
+    a.cut = choose_cut(sh.D, sh.Hq / sh.Hkv, sh.B * sh.Hkv, a.size.ktiles, steps, longest, 8 * CUS);
   }
   return a;
 }
@@ -2073,13 +2105,14 @@ hipError_t lg_launch_bwd_bf16_pack(const void* q, const void* k, const void* v, 
     a.D = sh.D;
     a.scale = sh.scale;
     a.cut = {1, 1};
+    a.setup.btk = btk_of(sh.D);
     int& n = a.setup.n;
     for (; x < num_seqs && n < LG_PACK_MAX; ++x) {
       const int len = cu_seqlens[x + 1] - cu_seqlens[x];
       if (len == 0) continue;
-      const Seq one = {cu_seqlens[x], len, columns_of(lg_mask_for_length(tmpl, len))};
+      const Seq one = {cu_seqlens[x], len, columns_of(lg_mask_for_length(tmpl, len), sh.D)};
       BwdSize z = a.size;
-      z.add(len, one.c);
+      z.add(len, sh.D, one.c);
       if (n > 0 && (bwd_layout(z, 1, sh.Hq, sh.Hkv, sh.D, a.cut).end > ws_bytes || z.ktiles > 0xffffff ||
                     (double)z.rows * sh.Hq > 1e9))
         break;
@@ -2091,30 +2124,30 @@ hipError_t lg_launch_bwd_bf16_pack(const void* q, const void* k, const void* v, 
     if (n == 0) break;
     auto citems = [&](int chunk) {
       long long all = 0;
-      for (int y = 0; y < n; ++y) all += seq[y].c.items(chunk);
+      for (int y = 0; y < n; ++y) all += seq[y].c.items(sh.D, chunk);
       return all * sh.Hq;
     };
     a.chunk = choose_chunk(citems);
     if (citems(a.chunk) > 0x7fffffffLL) return hipErrorInvalidValue;
     double steps = 0;
     int longest = 0;
-    const bool may_cut = (sh.Hq != sh.Hkv || tmpl.stride > 0) && a.size.ktiles * sh.Hkv <= 2 * CUS;
+    const bool may_cut = (sh.Hq != sh.Hkv || tmpl.stride > 0) && a.size.ktiles * sh.Hkv <= (sh.D == 128 ? 2 : 4) * CUS;
     for (int y = 0; y < n; ++y) {
       const LgMask m = lg_mask_for_length(tmpl, seq[y].len);
       a.setup.row0[y] = seq[y].row0;
       a.setup.len[y] = seq[y].len;
       a.setup.ncol[y] = seq[y].c.ncol;
-      a.setup.citems[y] = seq[y].c.items(a.chunk);
+      a.setup.citems[y] = seq[y].c.items(sh.D, a.chunk);
       a.setup.nlone[y] = seq[y].c.lone();
       a.citems += a.setup.citems[y];
       // (both rules are monotone in the length: the wide ones come first)
       (dq_wide(m, sh.D) ? a.qt_wide : a.qt_rest) += (seq[y].len + LG_BF16_TQ - 1) / LG_BF16_TQ;
-      (dkdv_wide(m, sh.D) ? a.kt_wide : a.kt_rest) += (seq[y].len + LG_BF16_BTK - 1) / LG_BF16_BTK;
+      (dkdv_wide(m, sh.D) ? a.kt_wide : a.kt_rest) += (seq[y].len + a.setup.btk - 1) / a.setup.btk;
       a.setup.nwide += dkdv_wide(m, sh.D);
-      if (may_cut) window_steps(m, &steps, &longest);
+      if (may_cut) window_steps(m, a.setup.btk, &steps, &longest);
     }
     if (may_cut) {
-      const size_t tile = (size_t)sh.Hkv * a.size.ktiles * (4 * 64 * 2 * sizeof(float)) * sh.D;
+      const size_t tile = (size_t)sh.Hkv * a.size.ktiles * (a.setup.btk * 2 * sizeof(float)) * sh.D;
       a.cut = choose_cut(sh.D, sh.Hq / sh.Hkv, sh.Hkv, a.size.ktiles, steps, longest,
                          (ws_bytes - bwd_layout(a.size, 1, sh.Hq, sh.Hkv, sh.D, a.cut).end) / tile);
     }

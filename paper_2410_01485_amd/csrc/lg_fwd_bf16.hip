@@ -174,18 +174,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
     // its use, which leaves the LDS latency in the wave's critical path sixteen times per product; for V that was 3 %
     // at 128K tokens, 10 % where a SIMD has one wave).
     {
-      constexpr int NQ = 2 * DC, DIST = LgFwdTune<D>::AHEAD;
-      bf16x8_t op[DIST + 1];
-      lg_static_for<DIST>([&](auto U) {
-        constexpr int u = decltype(U)::value;
-        op[u] = rd.read_rows(smem, sk, u & 1, u >> 1);
-      });
-      lg_static_for<NQ>([&](auto U) {
-        constexpr int u = decltype(U)::value, w = u + DIST;
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (w < NQ) op[w % (DIST + 1)] = rd.read_rows(smem, sk, w & 1, w >> 1);
-        sacc[u & 1] = lg_mfma32(op[u % (DIST + 1)], qf[u >> 1], sacc[u & 1]);
-      });
+      auto read = [&](int u) { return rd.read_rows(smem, sk, u & 1, u >> 1); };
+      LgRing<2 * DC, LgFwdTune<D>::AHEAD> ring;
+      ring.begin(read);
+      ring.run(read, [&](int u, bf16x8_t k) { sacc[u & 1] = lg_mfma32(k, qf[u >> 1], sacc[u & 1]); });
     }
 
     // ---- online softmax (log2 domain) ----
@@ -261,18 +253,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
     if (kind != LG_TILE_DEAD) {
     // ---- O^T += V^T P^T ----
     {
-      constexpr int NPV = 4 * DB, DIST = LgFwdTune<D>::AHEAD_PV;
-      bf16x8_t op[DIST + 1];
-      lg_static_for<DIST>([&](auto U) {
-        constexpr int u = decltype(U)::value;
-        op[u] = rd.read_cols(smem, sv, u % DB, u / DB);
-      });
-      lg_static_for<NPV>([&](auto U) {
-        constexpr int u = decltype(U)::value, w = u + DIST;
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (w < NPV) op[w % (DIST + 1)] = rd.read_cols(smem, sv, w % DB, w / DB);
-        oacc[u % DB] = lg_mfma32(op[u % (DIST + 1)], pf[u / DB], oacc[u % DB]);
-      });
+      auto read = [&](int u) { return rd.read_cols(smem, sv, u % DB, u / DB); };
+      LgRing<4 * DB, LgFwdTune<D>::AHEAD_PV> ring;
+      ring.begin(read);
+      ring.run(read, [&](int u, bf16x8_t v) { oacc[u % DB] = lg_mfma32(v, pf[u / DB], oacc[u % DB]); });
     }
     }  // kind != dead
 

@@ -88,4 +88,24 @@ __device__ __forceinline__ void lg_static_for(F&& f) {
   lg_static_for_impl(std::make_integer_sequence<int, N>{}, f);
 }
 
+// NU matrix instructions whose LDS operands are requested DIST of them ahead: begin(read) asks for the first ones, run
+// calls use(u, operand) in order.  (The compiler on its own asks for an operand just before its use and waits.)
+template <int NU, int DIST>
+struct LgRing {
+  bf16x8_t op[DIST + 1];
+  template <typename R>
+  __device__ __forceinline__ void begin(R&& read) {
+    lg_static_for<DIST>([&](auto U) { op[decltype(U)::value] = read(decltype(U)::value); });
+  }
+  template <typename R, typename F>
+  __device__ __forceinline__ void run(R&& read, F&& use) {
+    lg_static_for<NU>([&](auto U) {
+      constexpr int u = decltype(U)::value, w = u + DIST;
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (w < NU) op[w % (DIST + 1)] = read(w);
+      use(u, op[u % (DIST + 1)]);
+    });
+  }
+};
+
 #endif  // LG_MFMA_H_
