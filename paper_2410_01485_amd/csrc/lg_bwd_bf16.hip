@@ -2030,12 +2030,14 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
   return e;
 }
 
-// Query tiles per column work item where there are several groups: 64, less where that leaves CUs idle.  items(chunk):
-// work items of the launch.
+// Query tiles per column work item where there are several groups: 64, less where that leaves CUs idle, but not so few
+// that more than 32 items add to the same sums, which then take longer than the products (64/8 heads of 128, 16001
+// tokens, four groups: 32 adders 218 us, 64 adders 332 us).  items(chunk): work items of the launch; longest: query
+// tiles of the longest column part; G: query heads per kv head.
 template <typename F>
-int choose_chunk(F items) {
+int choose_chunk(F items, int longest, int G) {
   int chunk = 64;
-  while (chunk > 8 && items(chunk) < 2 * CUS) chunk /= 2;
+  while (chunk > 8 && items(chunk) < 2 * CUS && (long long)G * (longest / (chunk / 2) + 1) <= 32) chunk /= 2;
   return chunk;
 }
 
@@ -2051,7 +2053,8 @@ BwdLaunch batch_launch(const LgShape& sh, const LgMask& m) {
   const Columns c = columns_of(m, sh.D);
   a.setup.btk = btk_of(sh.D);
   a.size.add(sh.N, sh.D, c);
-  a.chunk = choose_chunk([&](int chunk) { return (long long)c.items(sh.D, chunk) * sh.Hq * sh.B; });
+  a.chunk = choose_chunk([&](int chunk) { return (long long)c.items(sh.D, chunk) * sh.Hq * sh.B; },
+                         c.last - c.first, sh.Hq / sh.Hkv);
   a.citems = c.items(sh.D, a.chunk);
   (dq_wide(m, sh.D) ? a.qt_wide : a.qt_rest) = (sh.N + LG_BF16_TQ - 1) / LG_BF16_TQ;
   (dkdv_wide(m, sh.D) ? a.kt_wide : a.kt_rest) = (int)a.size.ktiles;
@@ -2127,7 +2130,10 @@ hipError_t lg_launch_bwd_bf16_pack(const void* q, const void* k, const void* v, 
       for (int y = 0; y < n; ++y) all += seq[y].c.items(sh.D, chunk);
       return all * sh.Hq;
     };
-    a.chunk = choose_chunk(citems);
+    int longest_col = 0;
+    for (int y = 0; y < n; ++y)
+      if (seq[y].c.last - seq[y].c.first > longest_col) longest_col = seq[y].c.last - seq[y].c.first;
+    a.chunk = choose_chunk(citems, longest_col, sh.Hq / sh.Hkv);
     if (citems(a.chunk) > 0x7fffffffLL) return hipErrorInvalidValue;
     double steps = 0;
     int longest = 0;
