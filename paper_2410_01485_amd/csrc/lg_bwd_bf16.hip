@@ -708,29 +708,38 @@ dkdv_bf16_kernel(
   const int voff = (wave >> 1) * T::BYTES + (wave & 1) * HALF;  // this wave's 32 V rows
 
   // (head, query tile) of a step advance incrementally: no divisions in the loop
-  auto issue_step = [&](int hq, int u, int buf) {
+  // rows of the query head whose step is requested next
+  const uint16_t* qh = q + ((size_t)(b * Hq + hq0) * m.ld + it.row0) * D;
+  const uint16_t* gh = dout + ((size_t)(b * Hq + hq0) * m.ld + it.row0) * D;
+  const float* lh = nlse + (size_t)(b * Hq + hq0) * wk.wld + it.wrow0;
+  const float* dh = ndelta + (size_t)(b * Hq + hq0) * wk.wld + it.wrow0;
+  auto next_head = [&] {
+    qh += (size_t)m.ld * D;
+    gh += (size_t)m.ld * D;
+    lh += wk.wld;
+    dh += wk.wld;
+  };
+  auto issue_step = [&](int u, int buf) {
     const int q0 = u * TQ;
-    const size_t wrow0 = (size_t)(b * Hq + hq) * wk.wld + it.wrow0;
     const uint32_t st = lds0 + VRES + buf * STAGE;
     // the small per-row loads go first: anything the compiler makes them wait for must not
     // include the tile loads issued below
     if (wave < 2) {  // wave 0: -lse / scale rows, wave 1: -Delta rows (64 floats each)
-      const float* src = (wave == 0 ? nlse : ndelta) + wrow0 + min(q0 + lane, N - 1);
+      const float* src = (wave == 0 ? lh : dh) + min(q0 + lane, N - 1);
       lg_dma_f32x64(src, st + OFF_L + wave * 256);
     }
-    const size_t row0 = (size_t)(b * Hq + hq) * m.ld + it.row0;  // in the caller's tensors
-    dma.issue(q + (row0 + q0) * D, N - q0, st);
-    dma.issue(dout + (row0 + q0) * D, N - q0, st + OFF_G);
+    dma.issue(qh + (size_t)q0 * D, N - q0, st);
+    dma.issue(gh + (size_t)q0 * D, N - q0, st + OFF_G);
   };
 
   // The query tiles [lo, hi] of a head are walked rotated: at step x the tile congruent to x
   // modulo the range length.  Neighbouring key tiles, whose ranges overlap almost completely and
   // which run side by side, then read the same Q / dO tile at the same time and share it in L2.
   const int u0 = per_head > 0 ? lo + (per_head - lo % per_head) % per_head : lo;
-  int hq_i = hq0, u_i = u0;      // step being issued
+  int u_i = u0;                  // step being issued
   int u_c = u0;                  // query tile of the step being computed
   int left_i = per_head;         // steps of the head being issued that are not issued yet
-  if (steps > 0) issue_step(hq_i, u_i, 0);
+  if (steps > 0) issue_step(u_i, 0);
   else LG_WAIT_VMCNT(0);  // (a part without rows: nothing may still be on its way to LDS when it ends)
   for (int st = 0; st < steps; ++st) {
     const int buf = st & 1;
@@ -741,9 +750,9 @@ dkdv_bf16_kernel(
       if (--left_i == 0) {  // next query head of the group: same walk again
         left_i = per_head;
         u_i = u0;
-        ++hq_i;
+        next_head();
       }
-      issue_step(hq_i, u_i, buf ^ 1);
+      issue_step(u_i, buf ^ 1);
     }
     const int q0 = u_c * TQ;
     u_c = (u_c == hi) ? lo : u_c + 1;
@@ -1197,24 +1206,33 @@ __device__ __forceinline__ void dkdv_wide_item(
   }
   const int voff = wave * T::BYTES;  // this wave's 64 V rows
 
-  auto issue_step = [&](int hq, int u, int buf) {
+  // rows of the query head whose step is requested next
+  const uint16_t* qh = q + ((size_t)(b * Hq + hq0) * m.ld + it.row0) * D;
+  const uint16_t* gh = dout + ((size_t)(b * Hq + hq0) * m.ld + it.row0) * D;
+  const float* lh = nlse + (size_t)(b * Hq + hq0) * wk.wld + it.wrow0;
+  const float* dh = ndelta + (size_t)(b * Hq + hq0) * wk.wld + it.wrow0;
+  auto next_head = [&] {
+    qh += (size_t)m.ld * D;
+    gh += (size_t)m.ld * D;
+    lh += wk.wld;
+    dh += wk.wld;
+  };
+  auto issue_step = [&](int u, int buf) {
     const int q0 = u * TQ;
-    const size_t wrow0 = (size_t)(b * Hq + hq) * wk.wld + it.wrow0;
     const uint32_t st = lds0 + VRES + buf * STAGE;
     if (wave < 2) {  // wave 0: -lse / scale rows, wave 1: -Delta rows (64 floats each)
-      const float* src = (wave == 0 ? nlse : ndelta) + wrow0 + min(q0 + lane, N - 1);
+      const float* src = (wave == 0 ? lh : dh) + min(q0 + lane, N - 1);
       lg_dma_f32x64(src, st + OFF_L + wave * 256);
     }
-    const size_t row0 = (size_t)(b * Hq + hq) * m.ld + it.row0;  // in the caller's tensors
-    dma.issue(q + (row0 + q0) * D, N - q0, st);
-    dma.issue(dout + (row0 + q0) * D, N - q0, st + OFF_G);
+    dma.issue(qh + (size_t)q0 * D, N - q0, st);
+    dma.issue(gh + (size_t)q0 * D, N - q0, st + OFF_G);
   };
 
   const int u0 = per_head > 0 ? lo + (per_head - lo % per_head) % per_head : lo;  // rotated walk, as above
-  int hq_i = hq0, u_i = u0;
+  int u_i = u0;
   int u_c = u0;
   int left_i = per_head;
-  if (steps > 0) issue_step(hq_i, u_i, 0);
+  if (steps > 0) issue_step(u_i, 0);
   else LG_WAIT_VMCNT(0);  // (a part without rows: nothing may still be on its way to LDS when it ends)
   for (int st = 0; st < steps; ++st) {
     const int buf = st & 1;
@@ -1225,9 +1243,9 @@ __device__ __forceinline__ void dkdv_wide_item(
       if (--left_i == 0) {
         left_i = per_head;
         u_i = u0;
-        ++hq_i;
+        next_head();
       }
-      issue_step(hq_i, u_i, buf ^ 1);
+      issue_step(u_i, buf ^ 1);
     }
     const int q0 = u_c * TQ;
     u_c = (u_c == hi) ? lo : u_c + 1;
