@@ -2,10 +2,8 @@
 // second paragraph: at inference the bottleneck is loading the KV cache as fast as
 // possible; the attention-sink variant keeps the window in a rolling buffer).
 //
-// One query per (b, hq); every valid cache slot is read exactly once.  Two kernels:
-//   decode_mfma_kernel  bf16, all query heads of a kv head (up to 16) at once on the matrix cores
-//   decode_kernel       float32, on vector ALUs: LPR consecutive lanes read one key row, a wave reads 64/LPR
-//                       consecutive rows per load, and U loads of K and of V are in flight per lane
+// One query per (b, hq); every valid cache slot is read exactly once, for all query heads of a kv head (up to 16) at
+// once, on the matrix cores (decode_mfma_kernel).
 // The slots of one (b, hkv) are split over workgroups so the chip is filled even for small batches; each leaves
 // its normalised result and log-sum-exp in the workspace, and the one that finishes last adds them (decode_finish).
 //
@@ -31,29 +29,6 @@
 namespace {
 
 constexpr int WAVES = 4;
-constexpr int U = 8;  // vector kernel: key rows per lane group per iteration
-
-template <int CTRL>
-__device__ __forceinline__ float dpp_f(float x) {
-  return __builtin_bit_cast(
-      float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
-}
-
-// Sum over a group of LPR consecutive lanes (LPR in {8,16,32}); every lane of the
-// group receives the total.
-template <int LPR>
-__device__ __forceinline__ float group_sum(float x) {
-  x += dpp_f<0xB1>(x);  // quad_perm [1,0,3,2]
-  x += dpp_f<0x4E>(x);  // quad_perm [2,3,0,1]
-  if constexpr (LPR == 8) {
-    x += dpp_f<0x141>(x);  // row_half_mirror: the other quad of the 8
-  } else {
-    x += dpp_f<0x124>(x);  // row_ror:4
-    x += dpp_f<0x128>(x);  // row_ror:8
-    if constexpr (LPR == 32) x += __shfl_xor(x, 16);
-  }
-  return x;
-}
 
 // E elements of T loaded as one 16-byte vector, widened to float.  The loads are marked
 // non-temporal: every cache byte is used exactly once per call, so keeping it in L2 / the
@@ -109,7 +84,7 @@ struct LgDecWork {
   unsigned long long* word;  // [rows][splits][max(GT, 2)]: epoch << 32 | log2-sum-exp of a head
   float* o;                  // [rows][splits][GT][D]: normalised partial results
 };
-constexpr int UNIT = 32, LG_DEC_SPLITS_MAX = 64;
+constexpr int LG_DEC_SPLITS_MAX = 64;
 // Workgroups with keys that a paged step aims at: three per CU, what the matrix-core kernel's registers admit, or (bf16)
 // one per CU when all rows together have so few keys that a workgroup's start and the final sum weigh more than its
 // reads.
@@ -291,150 +266,7 @@ __device__ __forceinline__ size_t lg_dec_page_row(const LgPaged& pg, int b, int 
   return (((size_t)page * Hkv + hk) << pg.page_shift) + (slot & ((1 << pg.page_shift) - 1));
 }
 
-// ---------------------------------------------------------------- float32, vector ALUs
-template <int D, int GT, int MODE>
-__global__ __launch_bounds__(WAVES * 64, 2) void decode_kernel(const float* __restrict__ q,
-                                                               const float* __restrict__ kc,
-                                                               const float* __restrict__ vc,
-                                                               float* __restrict__ out, float* __restrict__ lse,
-                                                               LgDecWork wk, int Hq, int Hkv, int C, int valid,
-                                                               float scale_log2e, LgDecSegs segs, LgPaged pg) {
-  typedef float T;
-  constexpr int E = 16 / sizeof(T);      // elements per 16-byte lane load
-  constexpr int LPR = D / E;             // lanes per key row
-  constexpr int KPW = 64 / LPR;          // key rows per wave per load
-  constexpr int GROUPS = WAVES * KPW;    // lane groups per workgroup
-  __shared__ float sM[WAVES][GT], sL[WAVES][GT];
-  __shared__ float sO[WAVES][GT][D];
-  __shared__ float scratch[GT * LG_DEC_SPLITS_MAX];
-
-  const int G = Hq / Hkv;
-  const int ngc = (G + GT - 1) / GT;  // chunks of GT query heads per kv head
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int grp = wave * KPW + lane / LPR;
-  const int dl = (lane % LPR) * E;  // first head-dim element of this lane
-  LgDecPart p;
-  if (!lg_dec_part<MODE>(wk, pg, Hkv * ngc, segs, valid, p)) return;
-  const int b = p.b, hk = p.q / ngc, gc = p.q % ngc;
-  const int ng = min(GT, G - gc * GT);
-  const int s0 = p.s0, s1 = p.s1;
-  const size_t out_row = (size_t)b * Hq + hk * G + gc * GT;
-
-  float qf[GT][E], o[GT][E], mrun[GT], lrun[GT];
-#pragma unroll
-  for (int g = 0; g < GT; ++g) {
-    Frag<T, E>::load(q + (out_row + min(g, ng - 1)) * D + dl, qf[g]);
-    mrun[g] = -INFINITY;
-    lrun[g] = 0.f;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      qf[g][e] *= scale_log2e;
-      o[g][e] = 0.f;
-    }
-  }
-
-  const T* kbase = kc + (MODE == LG_DEC_PAGED ? 0 : ((size_t)b * Hkv + hk) * C * D) + dl;
-  const T* vbase = vc + (MODE == LG_DEC_PAGED ? 0 : ((size_t)b * Hkv + hk) * C * D) + dl;
-  for (int base = s0; base < s1; base += GROUPS * U) {
-    float kf[U][E], vf[U][E];
-    bool ok[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int key = base + u * GROUPS + grp;  // index into the concatenated runs
-      ok[u] = key < s1;
-      int slot = ok[u] ? key : s1 - 1;
-      if (MODE != LG_DEC_PLAIN) slot = lg_dec_slot(segs, slot);
-      size_t off = (size_t)slot * D;
-      if (MODE == LG_DEC_PAGED) off = lg_dec_page_row(pg, b, Hkv, hk, slot) * D;
-      Frag<T, E>::load(kbase + off, kf[u]);
-      Frag<T, E>::load(vbase + off, vf[u]);
-    }
-#pragma unroll
-    for (int g = 0; g < GT; ++g) {
-      float s[U];
-      float mb = -INFINITY;
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        float a = 0.f;
-#pragma unroll
-        for (int e = 0; e < E; ++e) a = fmaf(qf[g][e], kf[u][e], a);
-        a = group_sum<LPR>(a);
-        s[u] = ok[u] ? a : -INFINITY;
-        mb = fmaxf(mb, s[u]);
-      }
-      const float mnew = fmaxf(mrun[g], mb);
-      const float msafe = (mnew == -INFINITY) ? 0.f : mnew;
-      const float alpha = exp2f(mrun[g] - msafe);
-      mrun[g] = mnew;
-      float psum = 0.f;
-#pragma unroll
-      for (int e = 0; e < E; ++e) o[g][e] *= alpha;
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const float pr = exp2f(s[u] - msafe);
-        psum += pr;
-#pragma unroll
-        for (int e = 0; e < E; ++e) o[g][e] = fmaf(pr, vf[u][e], o[g][e]);
-      }
-      lrun[g] = lrun[g] * alpha + psum;
-    }
-  }
-
-  // merge the KPW lane groups of the wave (lanes LPR apart hold the same dims)
-#pragma unroll
-  for (int g = 0; g < GT; ++g) {
-    float mall = mrun[g];
-#pragma unroll
-    for (int x = LPR; x < 64; x <<= 1) mall = fmaxf(mall, __shfl_xor(mall, x));
-    const float msafe = (mall == -INFINITY) ? 0.f : mall;
-    const float w = exp2f(mrun[g] - msafe);
-    float l = lrun[g] * w;
-#pragma unroll
-    for (int x = LPR; x < 64; x <<= 1) l += __shfl_xor(l, x);
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      float a = o[g][e] * w;
-#pragma unroll
-      for (int x = LPR; x < 64; x <<= 1) a += __shfl_xor(a, x);
-      o[g][e] = a;
-    }
-    if (lane < LPR) {
-#pragma unroll
-      for (int e = 0; e < E; ++e) sO[wave][g][dl + e] = o[g][e];
-      if (lane == 0) {
-        sM[wave][g] = mall;
-        sL[wave][g] = l;
-      }
-    }
-  }
-  __syncthreads();
-
-  // merge the waves; ng*D outputs spread over the workgroup
-  for (int idx = threadIdx.x; idx < ng * D; idx += WAVES * 64) {
-    const int g = idx / D, d = idx % D;
-    float M = -INFINITY;
-#pragma unroll
-    for (int w = 0; w < WAVES; ++w) M = fmaxf(M, sM[w][g]);
-    float L = 0.f, acc = 0.f;
-#pragma unroll
-    for (int w = 0; w < WAVES; ++w) {
-      const float f = exp2f(sM[w][g] - M);
-      L += sL[w][g] * f;
-      acc += sO[w][g][d] * f;
-    }
-    if (p.parts == 1) {
-      store_out(out + out_row * D + idx, acc / L);
-      if (lse != nullptr && d == 0) lse[out_row + g] = (M + log2f(L)) * 0.69314718055994530942f;
-    } else {
-      const size_t at = (p.row * wk.splits + p.split) * GT;
-      __hip_atomic_store(wk.o + at * D + idx, acc / L, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-  }
-  if (p.parts > 1)
-    decode_finish<T, D>(wk, p, ng, GT, out, lse, out_row, scratch, [&](int g) { return lg_lse2(sM, sL, g); });
-}
-
-// ---------------------------------------------------------------- bf16, matrix cores
+// ---------------------------------------------------------------- matrix cores
 // All G <= 16 query heads of a kv head at once.  On the vector ALUs every head costs a multiply-add per element of K
 // and V and a reduction over the lanes of a row: with 8 heads that kernel ran at 1.2 TB/s, a sixth of what it reads
 // at with one.  Here a wave takes a unit of 32 keys at a time on 16x16x32 instructions:
@@ -450,25 +282,43 @@ __global__ __launch_bounds__(WAVES * 64, 2) void decode_kernel(const float* __re
 // 16 KB (D = 128) a wave spends 512 matrix and about 600 vector cycles, several times less than the bytes take.
 // Measured (vector kernel -> this): 16 x 32 heads x 4160 slots 162 -> 159 us (6.9 TB/s); 8 x 8 kv heads of 8 query heads x 3648
 // slots 101 -> 26 us; 48 sequences of 20 .. 32768 tokens, 8 kv heads of 4 query heads, paged 109 -> 77 us.
-template <int D>
-struct LgVRow;
-template <>
-struct LgVRow<128> {
-  typedef lg_u32x4 type;
+// float32: units of 16 keys (as many bytes) on 16x16x4 float32 instructions: lane (n, h) loads dims 16 c + 4 h .. of key
+// row n (contraction step (c, e): its element e; the four lane groups together dims 16 c + e, + 4, + 8, + 12), register r
+// of S is key 4 h + r, which is the B operand of the second product's step r as it is; a lane loads dims 4 n .. (+ 64) of
+// those 4 keys of V.  A unit takes 2048 matrix cycles, a third of what its bytes take at three workgroups per CU.
+// Measured (vector kernel -> this): 8 x 8 kv heads of 8 query heads x 4160 slots 99 -> 51 us; 4 x 8 kv heads of 4 x 2112
+// slots 40 -> 18 us; 8 x 32 heads x 4160 slots 197 -> 158 us; one head of 64, 364 slots 10.3 -> 6.8 us.
+template <typename T>
+struct LgDecElem {
+  typedef T type;
 };
 template <>
-struct LgVRow<64> {
-  typedef unsigned type __attribute__((ext_vector_type(2)));
+struct LgDecElem<__hip_bfloat16> {
+  typedef uint16_t type;
+};
+template <typename T, int D>
+struct LgDecUnit {  // what a lane holds of a unit
+  static constexpr int KEYS = 32;
+  typedef unsigned vrow_t __attribute__((ext_vector_type(D / 32)));
+  lg_u32x4 k[2][D / 32];
+  vrow_t v[8];
+};
+template <int D>
+struct LgDecUnit<float, D> {
+  static constexpr int KEYS = 16;
+  f32x4_t k[D / 16];
+  f32x4_t v[4][D / 64];
 };
 
-template <int D, int MODE>
+template <typename TT, int D, int MODE>
 __global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
-    const uint16_t* __restrict__ q, const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc,
-    __hip_bfloat16* __restrict__ out, float* __restrict__ lse, LgDecWork wk, int Hq, int Hkv, int C, int valid,
-    float scale_log2e, LgDecSegs segs, LgPaged pg) {
-  constexpr int DC = D / 32, VE = D / 16;  // 32-dim contraction steps; dims per lane of a V row
-  constexpr int PAGES = 1024;              // page-table entries of a sequence kept in LDS
-  typedef typename LgVRow<D>::type vrow_t;
+    const typename LgDecElem<TT>::type* __restrict__ q, const typename LgDecElem<TT>::type* __restrict__ kc,
+    const typename LgDecElem<TT>::type* __restrict__ vc, TT* __restrict__ out, float* __restrict__ lse, LgDecWork wk,
+    int Hq, int Hkv, int C, int valid, float scale_log2e, LgDecSegs segs, LgPaged pg) {
+  constexpr bool F32 = sizeof(TT) == 4;
+  constexpr int UNIT = LgDecUnit<TT, D>::KEYS;
+  constexpr int DC = D / (F32 ? 16 : 32), VE = D / 16;  // loads of a key row; 16-dim blocks of O
+  constexpr int PAGES = 1024;                           // page-table entries of a sequence kept in LDS
   __shared__ float sO[WAVES][16][D + 4];
   __shared__ float sM[WAVES][16], sL[WAVES][16];
   __shared__ int spage[MODE == LG_DEC_PAGED ? PAGES : 1];
@@ -481,12 +331,11 @@ __global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
   if (!lg_dec_part<MODE>(wk, pg, Hkv, segs, valid, p)) return;
   const int b = p.b, hk = p.q;
   const size_t out_row = (size_t)b * Hq + hk * G;
-  bf16x8_t qf[DC];
+  uint4 qf[DC];  // (F32: dims 16 c + 4 h .., else 32 c + 8 h ..)
 #pragma unroll
   for (int c = 0; c < DC; ++c) {
-    uint4 x = make_uint4(0u, 0u, 0u, 0u);
-    if (n < G) x = *reinterpret_cast<const uint4*>(q + (out_row + n) * D + 32 * c + 8 * h);
-    qf[c] = lg_as_bf16x8(x);
+    qf[c] = make_uint4(0u, 0u, 0u, 0u);
+    if (n < G) qf[c] = *reinterpret_cast<const uint4*>(q + (out_row + n) * D + (F32 ? 16 * c + 4 * h : 32 * c + 8 * h));
   }
   f32x4_t acc[VE];
 #pragma unroll
@@ -494,8 +343,8 @@ __global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
   float mref = -INFINITY, lrow = 0.f;
 
   const size_t head = MODE == LG_DEC_PAGED ? 0 : ((size_t)b * Hkv + hk) * C * D;
-  const uint16_t* kb_ = kc + head;
-  const uint16_t* vb_ = vc + head + VE * n;
+  const auto* kb_ = kc + head;
+  const auto* vb_ = vc + head + (F32 ? 4 : VE) * n;
   const int r1 = p.s1;
   // The sequence's page-table entries go to LDS first (a table of more than PAGES entries is read in place: behind
   // each unit's loads, which keeps the next unit's waiting).
@@ -505,7 +354,7 @@ __global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
       spage[x] = min(max(pg.page_table[(size_t)b * pg.pages_per_seq + x], 0), pg.num_pages - 1);
     __syncthreads();
   }
-  // cache row of key key0 + lane % 32 of a unit; the lanes hand them round
+  // cache row of key key0 + lane % UNIT of a unit; the lanes hand them round
   auto resolve = [&](int key0, auto IN_LDS) -> unsigned {
     if (MODE == LG_DEC_PLAIN) return 0;
     const int slot = lg_dec_slot(segs, min(key0 + (lane & (UNIT - 1)), r1 - 1));
@@ -514,11 +363,21 @@ __global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
     if (!decltype(IN_LDS)::value) return lg_dec_page_row(pg, b, Hkv, hk, slot);
     return (((unsigned)spage[slot >> pg.page_shift] * Hkv + hk) << pg.page_shift) + (slot & ((1 << pg.page_shift) - 1));
   };
-    struct Unit {
-      lg_u32x4 k[2][DC];
-      vrow_t v[8];
-    };
+    using Unit = LgDecUnit<TT, D>;
     auto load = [&](Unit& t, int key0, unsigned rows) {
+      if constexpr (F32) {
+        const unsigned r = MODE == LG_DEC_PLAIN ? (unsigned)min(key0 + n, r1 - 1) : __shfl(rows, n);
+#pragma unroll
+        for (int c = 0; c < DC; ++c)
+          t.k[c] = *reinterpret_cast<const f32x4_t*>(kb_ + (size_t)r * D + 16 * c + 4 * h);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const unsigned rv = MODE == LG_DEC_PLAIN ? (unsigned)min(key0 + 4 * h + j, r1 - 1) : __shfl(rows, 4 * h + j);
+#pragma unroll
+          for (int x = 0; x < D / 64; ++x)
+            t.v[j][x] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(vb_ + (size_t)rv * D + 64 * x));
+        }
+      } else {
 #pragma unroll
       for (int x = 0; x < 2; ++x) {
         const unsigned r = MODE == LG_DEC_PLAIN ? (unsigned)min(key0 + ka + 4 * x, r1 - 1) : __shfl(rows, ka + 4 * x);
@@ -529,24 +388,33 @@ __global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const unsigned r = MODE == LG_DEC_PLAIN ? (unsigned)min(key0 + 8 * h + j, r1 - 1) : __shfl(rows, 8 * h + j);
-        t.v[j] = __builtin_nontemporal_load(reinterpret_cast<const vrow_t*>(vb_ + (size_t)r * D));
+        t.v[j] = __builtin_nontemporal_load(reinterpret_cast<const typename Unit::vrow_t*>(vb_ + (size_t)r * D));
+      }
       }
     };
+    constexpr int NX = F32 ? 1 : 2;  // 16-key blocks of S
     auto compute = [&](const Unit& t, int key0) {
-      f32x4_t s[2];
+      f32x4_t s[NX];
 #pragma unroll
-      for (int x = 0; x < 2; ++x) {
+      for (int x = 0; x < NX; ++x) {
         s[x] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int c = 0; c < DC; ++c)
-          s[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, t.k[x][c]), qf[c], s[x], 0, 0, 0);
+          if constexpr (F32) {
+            const f32x4_t qv = __builtin_bit_cast(f32x4_t, qf[c]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[x] = __builtin_amdgcn_mfma_f32_16x16x4f32(t.k[c][e], qv[e], s[x], 0, 0, 0);
+          } else {
+            s[x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, t.k[x][c]), lg_as_bf16x8(qf[c]),
+                                                           s[x], 0, 0, 0);
+          }
       }
       float mx = -INFINITY;
 #pragma unroll
-      for (int x = 0; x < 2; ++x)
+      for (int x = 0; x < NX; ++x)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          if (key0 + 8 * h + 4 * x + r >= r1) s[x][r] = -INFINITY;
+          if (key0 + 4 * NX * h + 4 * x + r >= r1) s[x][r] = -INFINITY;
           mx = fmaxf(mx, s[x][r]);
         }
       // the exponent's reference moves only when a maximum has outgrown it by 2^8
@@ -561,6 +429,19 @@ __global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
         for (int i = 0; i < VE; ++i) acc[i] *= alpha;
       }
       const float moff = mref == -INFINITY ? 0.f : mref * scale_log2e;
+      if constexpr (F32) {
+        float pr[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          pr[r] = exp2f(fmaf(s[0][r], scale_log2e, -moff));
+          lrow += pr[r];
+        }
+#pragma unroll
+        for (int i = 0; i < VE; ++i)  // dim 64 (i / 4) + 4 n + i % 4
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(t.v[r][i / 4][i % 4], pr[r], acc[i], 0, 0, 0);
+      } else {
       uint32_t w[3][4];  // P in three bf16 terms
 #pragma unroll
       for (int y = 0; y < 4; ++y) {
@@ -587,6 +468,7 @@ __global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
 #pragma unroll
         for (int z = 0; z < 3; ++z) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, pf[z], acc[i], 0, 0, 0);
       }
+      }
     };
     constexpr int STEP = UNIT * WAVES;
     auto all_units = [&](auto IN_LDS) {
@@ -602,14 +484,14 @@ __global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
     if (MODE != LG_DEC_PAGED || in_lds) all_units(std::true_type{});
     else all_units(std::false_type{});
 
-  // merge the waves: acc[i] register r is dim VE (4 h + r) + i of head n
+  // merge the waves: acc[i] register r is dim VE (4 h + r) + i of head n (float32: 64 (i / 4) + 4 (4 h + r) + i % 4)
   lrow += __shfl_xor(lrow, 16);
   lrow += lg_other_half(lrow);
   if (n < G) {
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int i = 0; i < VE; ++i) sO[wave][n][VE * (4 * h + r) + i] = acc[i][r];
+      for (int i = 0; i < VE; ++i) sO[wave][n][F32 ? 64 * (i / 4) + 4 * (4 * h + r) + i % 4 : VE * (4 * h + r) + i] = acc[i][r];
     if (h == 0) {
       sM[wave][n] = mref == -INFINITY ? -INFINITY : mref * scale_log2e;
       sL[wave][n] = lrow;
@@ -631,7 +513,11 @@ __global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
     }
     const float inv = 1.f / L;
     if (p.parts == 1) {
-      *reinterpret_cast<uint32_t*>(out + out_row * D + 2 * e) = lg_pack_bf16(a0 * inv, a1 * inv);
+      if constexpr (F32) {
+        *reinterpret_cast<float2*>(out + out_row * D + 2 * e) = make_float2(a0 * inv, a1 * inv);
+      } else {
+        *reinterpret_cast<uint32_t*>(out + out_row * D + 2 * e) = lg_pack_bf16(a0 * inv, a1 * inv);
+      }
       if (lse != nullptr && d == 0) lse[out_row + g] = (M + log2f(L)) * 0.69314718055994530942f;
     } else {
       const size_t at = (p.row * wk.splits + p.split) * G;
@@ -639,7 +525,7 @@ __global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
     }
   }
   if (p.parts > 1)  // (sO is free: the barrier in decode_finish comes first)
-    decode_finish<__hip_bfloat16, D>(wk, p, G, G, out, lse, out_row, &sO[0][0][0],
+    decode_finish<TT, D>(wk, p, G, G, out, lse, out_row, &sO[0][0][0],
                                      [&](int g) { return lg_lse2(sM, sL, g); });
 }
 
@@ -811,22 +697,17 @@ unsigned next_epoch() {
   return e;
 }
 
-// Query heads per workgroup row: all of a kv head's, or chunks of up to 8 on the vector kernel.
-int heads_per_row(int G, int dtype) {
-  if (dtype == LG_BF16 || G <= 2) return G;
-  return G <= 4 ? 4 : 8;
-}
-
 struct DecPlan {
   int rows, most, splits, chunk;
   size_t part_bytes;  // workspace per part: most * rows * part_bytes serves every context up to the one given
 };
 DecPlan dec_plan(int B, int Hq, int Hkv, int D, int valid, int dtype, bool paged) {
-  const int G = Hq / Hkv, gt = heads_per_row(G, dtype);
+  const int G = Hq / Hkv;
   DecPlan p;
-  p.rows = B * Hkv * ((G + gt - 1) / gt);
-  p.part_bytes = (gt > 2 ? gt : 2) * sizeof(unsigned long long) + (size_t)gt * D * sizeof(float);
-  const int rounds = (valid + 127) / 128;  // of four units, one per wave
+  p.rows = B * Hkv;
+  p.part_bytes = (G > 2 ? G : 2) * sizeof(unsigned long long) + (size_t)G * D * sizeof(float);
+  const int round = dtype == LG_F32 ? 64 : 128;  // keys of four units, one per wave
+  const int rounds = (valid + round - 1) / round;
   // Most parts per row: five workgroups per CU; records within LG_DECODE_STATIC_SCRATCH_BYTES as long as that leaves
   // two workgroups per CU.  (Grows with the context, never falls: a workspace for the longest serves the shorter.)
   const int wgs = paged ? 2048 : 1280;
@@ -841,12 +722,6 @@ DecPlan dec_plan(int B, int Hq, int Hkv, int D, int valid, int dtype, bool paged
   int best_per = rounds;
   if (paged) {
     best_per = (rounds + p.most - 1) / p.most;
-  } else if (dtype == LG_F32) {  // the vector kernel needs two workgroups per CU, of about 256 keys or more each
-    const int n = std::max(1, std::min({(511 + p.rows) / p.rows, p.most, (valid + 255) / 256}));
-    const int step = D == 64 ? 128 : 64;  // keys that its waves take in one round
-    p.chunk = n == 1 ? valid : ((valid + n - 1) / n + step - 1) / step * step;
-    p.splits = (valid + p.chunk - 1) / p.chunk;
-    return p;
   } else {
     // time in us: the bytes at 6.6 GB/ms, more when the last workgroups find CUs idle or crowd them, or the rounds of
     // one workgroup at their latency; then the sum over the parts
@@ -867,7 +742,7 @@ DecPlan dec_plan(int B, int Hq, int Hkv, int D, int valid, int dtype, bool paged
     }
   }
   p.splits = (rounds + best_per - 1) / best_per;
-  p.chunk = p.splits == 1 ? valid : 128 * best_per;
+  p.chunk = p.splits == 1 ? valid : round * best_per;
   return p;
 }
 
@@ -880,7 +755,7 @@ hipError_t launch_typed(const void* q, const void* kc, const void* vc, void* out
   const bool plain = segs.n == 1 && segs.start[0] == 0;
   LgPaged pg = {};
   if (paged) pg = *paged;
-  const int G = Hq / Hkv, gt = heads_per_row(G, dtype);
+  const int G = Hq / Hkv;
   const DecPlan plan = dec_plan(B, Hq, Hkv, D, valid, dtype, paged != nullptr);
   const float sl2 = scale * 1.44269504088896340736f;
   LgDecWork wk = {};
@@ -889,7 +764,7 @@ hipError_t launch_typed(const void* q, const void* kc, const void* vc, void* out
   if (plan.splits > 1) {
     wk.epoch = next_epoch();
     wk.word = (unsigned long long*)ws;
-    wk.o = (float*)(wk.word + (size_t)plan.rows * plan.splits * (gt > 2 ? gt : 2));
+    wk.o = (float*)(wk.word + (size_t)plan.rows * plan.splits * (G > 2 ? G : 2));
   }
   dim3 grid(plan.splits, plan.rows / B, B);
   if (paged) {
@@ -899,34 +774,14 @@ hipError_t launch_typed(const void* q, const void* kc, const void* vc, void* out
     const long long most = std::min<long long>((long long)plan.rows * plan.splits, (long long)DEC_FULL + plan.rows);
     grid = dim3((unsigned)most);
   }
-  const T* tq = (const T*)q;
-  const T* tk = (const T*)kc;
-  const T* tv = (const T*)vc;
-  T* to = (T*)out;
-  if constexpr (sizeof(T) == 2) {
-    const uint16_t *uq = (const uint16_t*)q, *uk = (const uint16_t*)kc, *uv = (const uint16_t*)vc;
-#define LG_DECODE_LAUNCH(MODE) \
-  decode_mfma_kernel<D, MODE><<<grid, WAVES * 64, 0, s>>>(uq, uk, uv, to, lse, wk, Hq, Hkv, C, valid, sl2, segs, pg)
-    if (paged) LG_DECODE_LAUNCH(LG_DEC_PAGED);
-    else if (plain) LG_DECODE_LAUNCH(LG_DEC_PLAIN);
-    else LG_DECODE_LAUNCH(LG_DEC_SEGS);
+  typedef typename LgDecElem<T>::type E;
+#define LG_DECODE_LAUNCH(MODE)                                                                                       \
+  decode_mfma_kernel<T, D, MODE><<<grid, WAVES * 64, 0, s>>>((const E*)q, (const E*)kc, (const E*)vc, (T*)out, lse, wk, \
+                                                             Hq, Hkv, C, valid, sl2, segs, pg)
+  if (paged) LG_DECODE_LAUNCH(LG_DEC_PAGED);
+  else if (plain) LG_DECODE_LAUNCH(LG_DEC_PLAIN);
+  else LG_DECODE_LAUNCH(LG_DEC_SEGS);
 #undef LG_DECODE_LAUNCH
-  } else {
-#define LG_DECODE_LAUNCH_M(GT, MODE) \
-  decode_kernel<D, GT, MODE><<<grid, WAVES * 64, 0, s>>>(tq, tk, tv, to, lse, wk, Hq, Hkv, C, valid, sl2, segs, pg)
-#define LG_DECODE_LAUNCH(GT)                             \
-  do {                                                   \
-    if (paged) LG_DECODE_LAUNCH_M(GT, LG_DEC_PAGED);     \
-    else if (plain) LG_DECODE_LAUNCH_M(GT, LG_DEC_PLAIN); \
-    else LG_DECODE_LAUNCH_M(GT, LG_DEC_SEGS);            \
-  } while (0)
-    if (gt == 1) LG_DECODE_LAUNCH(1);
-    else if (gt == 2) LG_DECODE_LAUNCH(2);
-    else if (gt == 4) LG_DECODE_LAUNCH(4);
-    else LG_DECODE_LAUNCH(8);
-#undef LG_DECODE_LAUNCH
-#undef LG_DECODE_LAUNCH_M
-  }
   return hipGetLastError();
 }
 

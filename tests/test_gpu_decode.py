@@ -68,6 +68,14 @@ def test_decode_parts(dtype, B, Hq, Hkv, D, window, N):
     check_decode(B, Hq, Hkv, D, 4, window, N, dtype, seed=15)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,D,window,N", [
+    # float32 units of 16 keys, four of them a round: one key short of, at and past each; 1, 3 and 16 heads per kv head
+    (1, 3, 1, 128, 200, 15), (1, 16, 1, 64, 200, 17), (2, 2, 2, 64, 200, 63), (1, 6, 2, 128, 200, 65), (1, 1, 1, 64, 200, 1),
+])
+def test_decode_float32_units(B, Hq, Hkv, D, window, N):
+    check_decode(B, Hq, Hkv, D, 4, window, N, torch.float32, seed=16)
+
+
 def test_decode_equals_last_row_of_prefill():
     # the ring cache built from a longer context by the slot map reproduces row N-1 of the forward
     B, Hq, Hkv, D, sink, window, N = 1, 4, 2, 128, 8, 120, 1000
