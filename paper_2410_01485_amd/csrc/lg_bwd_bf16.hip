@@ -30,7 +30,7 @@
 // tokens, window 512: 805 -> 644 us; 64/8 heads, 9830 tokens, window 455: 489 -> 367 us; dk/dv, 32 heads of 64, 32768
 // tokens, window 4096: 2441 -> 2104 us, window 512: 610 -> 475 us.
 //
-// For head dim 128 and windows of 16 or more tiles both kernels have a second form with 64 rows
+// For head dim 128 and long windows (dq 32 or more tiles, dk/dv 16) both kernels have a second form with 64 rows
 // (keys) per wave, one wave per SIMD and the accumulators in AGPRs (further down): every operand
 // read from LDS then feeds two matrix instructions.
 #include "../../include/longgen_attn.h"
@@ -193,29 +193,6 @@ dq_bf16_kernel(
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   const int qw0 = min(q0 + wave_s * 32, N - 1), qw1 = min(q0 + wave_s * 32 + 31, N - 1);  // this wave's rows
 
-  bf16x8_t qf[DC], gf[DC];
-  float di = 0.f;
-#pragma unroll
-  for (int dc = 0; dc < DC; ++dc) {
-    const uint4 gw = *reinterpret_cast<const uint4*>(dout + qbase + (size_t)iq * D + dc * 16 + g * 8);
-    qf[dc] = lg_as_bf16x8(*reinterpret_cast<const uint4*>(q + qbase + (size_t)iq * D + dc * 16 + g * 8));
-    gf[dc] = lg_as_bf16x8(gw);
-    di = lg_dot8(gw, *reinterpret_cast<const uint4*>(out + qbase + (size_t)iq * D + dc * 16 + g * 8), di);
-  }
-  di += lg_other_half(di);  // Delta of row i
-  const float sl2 = scale * LOG2E;
-  const float lse_i = lse[row0 + iq];
-  float lse2 = lse_i * LOG2E;
-  if (g == 0 && i < N) {
-    ndelta[wrow0 + i] = -di;
-    nlse[wrow0 + i] = -lse_i / scale;
-  }
-  // Touch everything loaded so far, so that the compiler's waits for these loads sit here and
-  // not inside the tile loop (where they would drain the direct loads kept in flight).
-#pragma unroll
-  for (int dc = 0; dc < DC; ++dc) asm volatile("" ::"v"(qf[dc]), "v"(gf[dc]));
-  asm volatile("" : "+v"(lse2), "+v"(di));
-
   f32x16_t acc[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db)
@@ -242,6 +219,31 @@ dq_bf16_kernel(
   };
   int t = next_tile(-1);
   issue(t, 0);
+
+  // (the first tile is on its way before the rows' own loads: 8 heads, window 124: 936 -> 830 us)
+  bf16x8_t qf[DC], gf[DC];
+  float di = 0.f;
+#pragma unroll
+  for (int dc = 0; dc < DC; ++dc) {
+    const uint4 gw = *reinterpret_cast<const uint4*>(dout + qbase + (size_t)iq * D + dc * 16 + g * 8);
+    qf[dc] = lg_as_bf16x8(*reinterpret_cast<const uint4*>(q + qbase + (size_t)iq * D + dc * 16 + g * 8));
+    gf[dc] = lg_as_bf16x8(gw);
+    di = lg_dot8(gw, *reinterpret_cast<const uint4*>(out + qbase + (size_t)iq * D + dc * 16 + g * 8), di);
+  }
+  di += lg_other_half(di);  // Delta of row i
+  const float sl2 = scale * LOG2E;
+  const float lse_i = lse[row0 + iq];
+  float lse2 = lse_i * LOG2E;
+  if (g == 0 && i < N) {
+    ndelta[wrow0 + i] = -di;
+    nlse[wrow0 + i] = -lse_i / scale;
+  }
+  // Touch everything loaded so far, so that the compiler's waits for these loads sit here and
+  // not inside the tile loop (where they would drain the direct loads kept in flight).
+#pragma unroll
+  for (int dc = 0; dc < DC; ++dc) asm volatile("" ::"v"(qf[dc]), "v"(gf[dc]));
+  asm volatile("" : "+v"(lse2), "+v"(di));
+
   int stage = 0;
   while (t >= 0) {
     LG_WAIT_VMCNT(0);
@@ -1798,10 +1800,11 @@ Columns columns_of(const LgMask& m, int D) {
 
 // Which kernels a sequence takes: the 64-rows-per-wave forms (head dim 128) start up and drain slower, so they
 // need a number of steps per workgroup.
-// dq: by the key tiles of an average query tile: its window, plus the strided columns below it
+// dq: by the key tiles of an average query tile: its window, plus the strided columns below it (32 heads, 32768 tokens:
+// window 900 923 us against 980 in the 64-rows form, 1300 1121 : 1185, 2048 1625 : 1617, 4096 at 65536 5941 : 5502)
 bool dq_wide(const LgMask& m, int D) {
   const int col_tiles = m.stride > 0 ? (m.N / 2) / (m.b * m.stride) * ((m.b + LG_BF16_TK - 1) / LG_BF16_TK) : 0;
-  return D == 128 && (m.wb * m.b + LG_BF16_TQ) / LG_BF16_TK + col_tiles >= 16;
+  return D == 128 && (m.wb * m.b + LG_BF16_TQ) / LG_BF16_TK + col_tiles >= 32;
 }
 // dk/dv: by the query tiles of a key tile's window part
 bool dkdv_wide(const LgMask& m, int D) { return D == 128 && (m.wb * m.b + LG_BF16_BTK) / LG_BF16_BTQ >= 16; }
