@@ -179,8 +179,8 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_f32_kernel(const floa
   __syncthreads();
   if (kh == 0 && i < N) {
     const float2 ml = sml[rg * 64 + lane];
-    const float M = fmaxf(mref, ml.x);
-    const float wa = __builtin_amdgcn_exp2f((mref - M) * c2), wb = __builtin_amdgcn_exp2f((ml.x - M) * c2);
+    const float M = fmaxf(mref, ml.x), Ms = M == -INFINITY ? 0.f : M;  // (no finite score: weights 0, lse -inf)
+    const float wa = __builtin_amdgcn_exp2f((mref - Ms) * c2), wb = __builtin_amdgcn_exp2f((ml.x - Ms) * c2);
     l = l * wa + ml.y * wb;
     const float fa = wa / l, fb = wb / l;
 #pragma unroll

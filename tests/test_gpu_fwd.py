@@ -148,3 +148,19 @@ def test_binding_rejects_mixed_dtypes_and_host_tensors():
         lg.lg_sparse_attn_bwd(qd, kd, vd, out, lse, qd, dq, dk, dv, ws, 4, 16)  # workspace in host memory
     with pytest.raises(TypeError):
         lg.lg_sparse_attn_bwd(qd, kd, vd, out, lse, qd, dq, dk.float(), dv, ws.to(DEV), 4, 16)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_rows_without_a_finite_score(dtype):
+    """Keys 0 .. 39 score -inf (a K entry of -inf against a positive query entry).  Rows that see no other key have no
+    finite score: log-sum-exp -inf, output NaN (0 / 0); the others, some with a whole half of a key tile at -inf, are
+    those of the keys that are left."""
+    q, k, v = lg_synth.prefill_inputs(1, 2, 1, 300, 64, 31, dtype)
+    q[..., 0] = q[..., 0].abs() + 0.1
+    k[:, :, :40] = 0
+    k[:, :, :40, 0] = float("-inf")
+    out, lse = run_fwd(q, k, v, 4, 64)
+    assert torch.isnan(out[:, :, :40]).all() and torch.isneginf(lse[:, :, :40]).all()
+    wo, wl = O.fwd(f32np(q), f32np(k), f32np(v), 4, 64, rows=(40, 300))
+    assert_close(f32np(out[:, :, 40:]), wo[:, :, 40:], TOL_OUT[dtype], TOL_REL[dtype], "out")
+    assert_close(f32np(lse[:, :, 40:]), wl[:, :, 40:], TOL_LSE[dtype], None, "lse")
