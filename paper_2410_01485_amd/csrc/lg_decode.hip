@@ -180,6 +180,10 @@ __device__ __forceinline__ bool lg_dec_part(const LgDecWork& wk, const LgPaged& 
   return p.s0 < valid;
 }
 
+// What exponents are taken relative to: a maximum, or 0 where no score is finite (-inf - -inf is NaN; this way every
+// weight is 0 there).
+__device__ __forceinline__ float lg_finite_ref(float m) { return m == -INFINITY ? 0.f : m; }
+
 // Called by all threads (256) of a workgroup after its stores of a part's normalised results to wk.o.  lse2(g): the
 // part's log2-sum-exp of head g < ng.  Stores them, tagged with the call's epoch, once the results have arrived in
 // memory; then reads the tagged words of all parts of the row.  The workspace comes with any contents, so only words
@@ -227,7 +231,7 @@ __device__ __forceinline__ void decode_finish(const LgDecWork& wk, const LgDecPa
     float M = l;
 #pragma unroll
     for (int y = 1; y < 64; y <<= 1) M = fmaxf(M, __shfl_xor(M, y));
-    const float w = exp2f(l - M);
+    const float w = exp2f(l - lg_finite_ref(M));
     float sum = w;
 #pragma unroll
     for (int y = 1; y < 64; y <<= 1) sum += __shfl_xor(sum, y);
@@ -253,14 +257,14 @@ __device__ __forceinline__ void decode_finish(const LgDecWork& wk, const LgDecPa
   }
 }
 
-// log2-sum-exp of head g from the waves' maxima and sums
+// log2-sum-exp of head g from the waves' maxima and sums (-inf where every score is)
 template <int N>
 __device__ __forceinline__ float lg_lse2(const float (&sM)[WAVES][N], const float (&sL)[WAVES][N], int g) {
   float M = -INFINITY, L = 0.f;
 #pragma unroll
   for (int w = 0; w < WAVES; ++w) M = fmaxf(M, sM[w][g]);
 #pragma unroll
-  for (int w = 0; w < WAVES; ++w) L += sL[w][g] * exp2f(sM[w][g] - M);
+  for (int w = 0; w < WAVES; ++w) L += sL[w][g] * exp2f(sM[w][g] - lg_finite_ref(M));
   return M + log2f(L);
 }
 
@@ -519,12 +523,12 @@ __global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
     float L = 0.f, a0 = 0.f, a1 = 0.f;
 #pragma unroll
     for (int x = 0; x < WAVES; ++x) {
-      const float f = exp2f(sM[x][g] - M);
+      const float f = exp2f(sM[x][g] - lg_finite_ref(M));
       L += sL[x][g] * f;
       a0 += sO[x][g][d] * f;
       a1 += sO[x][g][d + 1] * f;
     }
-    const float inv = 1.f / L;
+    const float inv = p.parts > 1 && L == 0.f ? 0.f : 1.f / L;  // (a part without a finite score adds nothing to its row)
     if (p.parts == 1) {
       if constexpr (F32) {
         *reinterpret_cast<float2*>(out + out_row * D + 2 * e) = make_float2(a0 * inv, a1 * inv);

@@ -242,3 +242,39 @@ def test_paged_parts(lens, Hq, Hkv, D, sink, window, page_size):
         wo, wl = O.fwd(f32np(q), f32np(k), f32np(v), sink, window, rows=(n - 1, n))
         assert_close(f32np(out[b]), wo[0, :, n - 1], TOL_OUT[dt], TOL_REL[dt], "paged seq %d of %d out" % (b, n))
         assert_close(f32np(lse[b]), wl[0, :, n - 1], TOL_LSE[dt], None, "paged seq %d of %d lse" % (b, n))
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("Hq,Hkv,D,dead", [(2, 2, 128, 1100), (8, 1, 64, 1100), (2, 1, 128, 256), (2, 1, 64, 2000)])
+def test_parts_whose_scores_are_all_minus_infinity(dtype, Hq, Hkv, D, dead):
+    """Keys 0 .. dead - 1 score -inf (a K entry of -inf against a positive query entry, zeros elsewhere), so whole parts
+    of the split over cache slots have no finite score.  They carry no weight: the result is the forward's last row, from
+    a contiguous and from a paged cache.  dead = all keys: no finite score at all, NaN and a log-sum-exp of -inf, as
+    in the forward."""
+    N, sink, window, page_size = 2000, 16, 4096, 64
+    q, k, v = lg_synth.prefill_inputs(1, Hq, Hkv, N, D, 88, dtype)
+    q[..., 0] = q[..., 0].abs() + 0.1
+    k[:, :, :dead] = 0
+    k[:, :, :dead, 0] = float("-inf")
+    qd, kd, vd = q.to(DEV), k.to(DEV), v.to(DEV)
+    fo = torch.empty_like(qd)
+    fl = torch.empty(1, Hq, N, dtype=torch.float32, device=DEV)
+    lg.lg_sparse_attn_fwd(qd, kd, vd, fo, fl, sink, window)
+    slots = lg.lg_kv_cache_slots(N, sink, window, 1, 0)
+    kc, vc = gpu_append_all(k, v, sink, window, 1, 0, [N], slots, 0.0)
+    results = [decode_cache(qd[:, :, N - 1].contiguous(), kc, vc, N, sink, window, 1, 0)]
+    n_max, table, kp, vp, _ = paged_setup([N, 40], Hq, Hkv, D, sink, window, 1, 0, page_size, dtype, 89)
+    for b, n in ((0, N), (1, 40)):
+        lg.lg_kv_paged_append(kd[:, :, N - n:].contiguous(), vd[:, :, N - n:].contiguous(), kp, vp, table[b:b + 1],
+                              torch.zeros(1, dtype=torch.int32, device=DEV), n_max, sink, window)
+    po, pl = paged_decode([q[0, :, N - 1]] * 2, kp, vp, table, [N, 40], n_max, sink, window, 1, 0)
+    results.append((po[:1], pl[:1]))
+    for name, (out, lse) in zip(("contiguous", "paged"), results):
+        if dead == N:
+            assert torch.isnan(out).all() and torch.isneginf(lse).all(), name
+            assert torch.isnan(fo[:, :, N - 1]).all() and torch.isneginf(fl[:, :, N - 1]).all()
+            continue
+        wo, wl = O.fwd(f32np(q), f32np(k), f32np(v), sink, window, rows=(N - 1, N))
+        for what, o, l in ((name, out, lse), ("forward", fo[:, :, N - 1], fl[:, :, N - 1])):
+            assert_close(f32np(o), wo[:, :, N - 1], TOL_OUT[dtype], TOL_REL[dtype], what + " out")
+            assert_close(f32np(l), wl[:, :, N - 1], TOL_LSE[dtype], None, what + " lse")
