@@ -22,6 +22,8 @@
 #include "lg_mask.h"
 #include "lg_mfma.h"
 
+#include <math.h>
+
 #include <algorithm>
 #include <atomic>
 #include <random>
@@ -331,7 +333,7 @@ template <typename TT, int D, int MODE>
 __global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
     const typename LgDecElem<TT>::type* __restrict__ q, const typename LgDecElem<TT>::type* __restrict__ kc,
     const typename LgDecElem<TT>::type* __restrict__ vc, TT* __restrict__ out, float* __restrict__ lse, LgDecWork wk,
-    int Hq, int Hkv, int C, int valid, float scale_log2e, LgDecSegs segs, LgPaged pg) {
+    int Hq, int Hkv, int C, int valid, float qmul, float scale_log2e, float scale_pow2, LgDecSegs segs, LgPaged pg) {
   constexpr bool F32 = sizeof(TT) == 4;
   constexpr int UNIT = LgDecUnit<TT, D>::KEYS;
   constexpr int DC = D / (F32 ? 16 : 32), VE = D / 16;  // loads of a key row; 16-dim blocks of O
@@ -354,10 +356,24 @@ __global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
     qf[c] = make_uint4(0u, 0u, 0u, 0u);
     if (n < G) qf[c] = *reinterpret_cast<const uint4*>(q + (out_row + n) * D + (F32 ? 16 * c + 4 * h : 32 * c + 8 * h));
   }
+  // Q takes the power of two of the scale, so that a score overflows where the scaled one does, not |1 / scale| earlier.
+  // Exact but for products below the smallest normal number: at most 2^-133 |k| per term of a scaled score.
+  auto scale_q = [&] {
+#pragma unroll
+    for (int c = 0; c < DC; ++c) {
+      uint32_t w[4] = {qf[c].x, qf[c].y, qf[c].z, qf[c].w};
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+        w[x] = F32 ? __float_as_uint(__uint_as_float(w[x]) * qmul)
+                   : lg_pack_bf16(__uint_as_float(w[x] << 16) * qmul, __uint_as_float(w[x] & 0xffff0000u) * qmul);
+      qf[c] = make_uint4(w[0], w[1], w[2], w[3]);
+    }
+  };
   f32x4_t acc[VE];
 #pragma unroll
   for (int i = 0; i < VE; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   float mref = -INFINITY, lrow = 0.f;
+  float cl = scale_log2e, moff = 0.f;  // P = exp2(S cl - moff)
 
   const size_t head = MODE == LG_DEC_PAGED ? 0 : ((size_t)b * Hkv + hk) * C * D;
   const auto* kb_ = kc + head;
@@ -441,16 +457,20 @@ __global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
         mnew = fmaxf(mnew, lg_other_half(mnew));
         const float alpha = mnew == -INFINITY ? 1.f : exp2f((mref - mnew) * scale_log2e);
         mref = mnew;
+        // From 2^30 on the rounding of mref * scale would show as a factor beyond the exponent's range.  Distinct scores
+        // are then at least 2^5 apart, and the scale's power of two, with which the product is exact, serves as well.
+        const bool far = fabsf(mref * scale_log2e) >= 0x1p30f;
+        cl = far ? scale_pow2 : scale_log2e;
+        moff = lg_finite_ref(mref) * cl;
         lrow *= alpha;
 #pragma unroll
         for (int i = 0; i < VE; ++i) acc[i] *= alpha;
       }
-      const float moff = mref == -INFINITY ? 0.f : mref * scale_log2e;
       if constexpr (F32) {
         float pr[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          pr[r] = exp2f(fmaf(s[0][r], scale_log2e, -moff));
+          pr[r] = exp2f(fmaf(s[0][r], cl, -moff));
           lrow += pr[r];
         }
 #pragma unroll
@@ -462,8 +482,8 @@ __global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
       uint32_t w[3][4];  // P in three bf16 terms
 #pragma unroll
       for (int y = 0; y < 4; ++y) {
-        float p0 = exp2f(fmaf(s[y >> 1][2 * (y & 1)], scale_log2e, -moff));
-        float p1 = exp2f(fmaf(s[y >> 1][2 * (y & 1) + 1], scale_log2e, -moff));
+        float p0 = exp2f(fmaf(s[y >> 1][2 * (y & 1)], cl, -moff));
+        float p1 = exp2f(fmaf(s[y >> 1][2 * (y & 1) + 1], cl, -moff));
         lrow += p0 + p1;
 #pragma unroll
         for (int z = 0; z < 3; ++z) {
@@ -495,6 +515,7 @@ __global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
         load(t, key, rows);
         rows = resolve(key + STEP, IN_LDS);
         __builtin_amdgcn_sched_barrier(0);  // all of the unit's loads are issued before anything waits for one
+        if (key == p.s0 + UNIT * wave) scale_q();  // (here: while the first unit's loads are on their way)
         compute(t, key);
       }
     };
@@ -775,6 +796,7 @@ hipError_t launch_typed(const void* q, const void* kc, const void* vc, void* out
   const int G = Hq / Hkv;
   const DecPlan plan = dec_plan(B, Hq, Hkv, D, valid, dtype, paged != nullptr);
   const float sl2 = scale * 1.44269504088896340736f;
+  const float qmul = sl2 < 1.f ? ldexpf(1.f, std::max(ilogbf(sl2), -126)) : 1.f, rest = sl2 / qmul;  // (exact)
   LgDecWork wk = {};
   wk.splits = plan.splits;
   wk.chunk = plan.chunk;
@@ -794,7 +816,7 @@ hipError_t launch_typed(const void* q, const void* kc, const void* vc, void* out
   typedef typename LgDecElem<T>::type E;
 #define LG_DECODE_LAUNCH(MODE)                                                                                       \
   decode_mfma_kernel<T, D, MODE><<<grid, WAVES * 64, 0, s>>>((const E*)q, (const E*)kc, (const E*)vc, (T*)out, lse, wk, \
-                                                             Hq, Hkv, C, valid, sl2, segs, pg)
+                                                             Hq, Hkv, C, valid, qmul, rest, ldexpf(1.f, ilogbf(rest)), segs, pg)
   if (paged) LG_DECODE_LAUNCH(LG_DEC_PAGED);
   else if (plain) LG_DECODE_LAUNCH(LG_DEC_PLAIN);
   else LG_DECODE_LAUNCH(LG_DEC_SEGS);

@@ -76,6 +76,22 @@ def test_decode_float32_units(B, Hq, Hkv, D, window, N):
     check_decode(B, Hq, Hkv, D, 4, window, N, torch.float32, seed=16)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("Hq,D,N,scale", [(2, 128, 300, 0.0), (2, 64, 3000, 0.0), (1, 128, 77, 3e-6), (1, 64, 77, 2.5)])
+def test_decode_scores_beyond_float32_before_scaling(dtype, Hq, D, N, scale):
+    """One key whose unscaled score is 2^130 (scale 2.5: 2^124), beyond float32, while the scaled one is not: it takes
+    all the weight, and the log-sum-exp is the scaled score."""
+    sink, window = 4, 4000
+    q, kc, vc = lg_synth.decode_inputs(1, Hq, 1, sink + window, D, 19, dtype)
+    top = 2.0 ** (62 if scale > 1 else 65)
+    q[:] = 2.0 ** 62 / D
+    kc[:, :, 50] = top * 2.0 ** 3 if scale <= 1 else top
+    out, lse = run_decode(q, kc, vc, N, sink, window, scale)
+    assert torch.equal(out.cpu(), vc[:, :, 50].expand(1, Hq, D))
+    s = float(q[0, 0, 0]) * float(kc[0, 0, 50, 0]) * D * (scale if scale > 0 else D ** -0.5)
+    assert (np.abs(f32np(lse).astype(np.float64) / s - 1) < 1e-6).all()
+
+
 def test_decode_equals_last_row_of_prefill():
     # the ring cache built from a longer context by the slot map reproduces row N-1 of the forward
     B, Hq, Hkv, D, sink, window, N = 1, 4, 2, 128, 8, 120, 1000
