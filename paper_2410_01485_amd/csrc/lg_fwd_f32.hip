@@ -50,6 +50,7 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_f32_kernel(const floa
   const size_t qbase = (size_t)(b * Hq + hq) * m.ld * D;
   const size_t kbase = (size_t)(b * Hkv + hk) * m.ld * D;
   const float c2 = scale * 1.44269504088896340736f;
+  const float c2_pow2 = __uint_as_float(__float_as_uint(c2) & 0x7f800000u);
 
   float4 qf[DC];
 #pragma unroll
@@ -61,6 +62,7 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_f32_kernel(const floa
 #pragma unroll
   for (int db = 0; db < DC; ++db) o[db] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   float mref = -INFINITY, lrow = 0.f;
+  float cl = c2, moff = 0.f;  // P = exp2(S cl - moff)
 
   Dma dma;
   dma.init(tid);
@@ -134,16 +136,19 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_f32_kernel(const floa
         const float mnew = lg_col_max(fmaxf(mx, mref));
         const float alpha = mnew == -INFINITY ? 1.f : __builtin_amdgcn_exp2f((mref - mnew) * c2);
         mref = mnew;
+        // From 2^30 on the rounding of mref * c2 would show as a factor beyond the exponent's range.  Distinct scores are
+        // then at least 2^5 apart, and c2's power of two, with which the product is exact, serves as well.
+        cl = fabsf(mref * c2) >= 0x1p30f ? c2_pow2 : c2;
+        moff = mref == -INFINITY ? 0.f : mref * cl;
         lrow *= alpha;
 #pragma unroll
         for (int db = 0; db < DC; ++db) o[db] *= alpha;
       }
-      const float moff = mref == -INFINITY ? 0.f : mref * c2;
 #pragma unroll
       for (int x = 0; x < NB; ++x)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          s[x][r] = __builtin_amdgcn_exp2f(fmaf(s[x][r], c2, -moff));
+          s[x][r] = __builtin_amdgcn_exp2f(fmaf(s[x][r], cl, -moff));
           lrow += s[x][r];
         }
 #pragma unroll

@@ -164,3 +164,18 @@ def test_rows_without_a_finite_score(dtype):
     wo, wl = O.fwd(f32np(q), f32np(k), f32np(v), 4, 64, rows=(40, 300))
     assert_close(f32np(out[:, :, 40:]), wo[:, :, 40:], TOL_OUT[dtype], TOL_REL[dtype], "out")
     assert_close(f32np(lse[:, :, 40:]), wl[:, :, 40:], TOL_LSE[dtype], None, "lse")
+
+
+@pytest.mark.parametrize("D,scale", [(64, 0.0), (128, 0.0), (64, 40.0)])
+def test_float32_scores_of_any_finite_size(D, scale):
+    """One key in both halves of a tile outscores the others by far, at 2^100: it takes all the weight of the rows that
+    see it, and the log-sum-exp is the scaled score."""
+    q, k, v = lg_synth.prefill_inputs(1, 2, 1, 200, D, 33, torch.float32)
+    q[:] = 2.0 ** 50 / D
+    for j in (70, 100):
+        k[:, :, j] = 2.0 ** 50 * (1 if j == 70 else 2)
+    out, lse = run_fwd(q, k, v, 0, 200, scale=scale)
+    sc = 2.0 ** 100 * (scale if scale > 0 else D ** -0.5)
+    for r0, r1, j in ((70, 100, 70), (100, 200, 100)):
+        assert torch.equal(out[:, :, r0:r1].cpu(), v[:, :, j:j + 1].expand(1, 2, r1 - r0, D)), j
+        assert (np.abs(f32np(lse[:, :, r0:r1]).astype(np.float64) / (sc if j == 70 else 2 * sc) - 1) < 1e-6).all()
