@@ -5,7 +5,7 @@
 // One query per (b, hq); every valid cache slot is read exactly once, for all query heads of a kv head (up to 16) at
 // once, on the matrix cores (decode_mfma_kernel).
 // The slots of one (b, hkv) are split over workgroups so the chip is filled even for small batches; each leaves
-// its normalised result and log-sum-exp in the workspace, and the one that finishes last adds them (decode_finish).
+// its normalised result and log-sum-exp in the workspace, and a second launch adds them (decode_add_kernel).
 //
 // The keys of a step are up to four runs of consecutive slots (LgDecSegs: sink tokens,
 // live part of the rolling window, retained strided blocks); the kernels walk their
@@ -25,8 +25,6 @@
 #include <math.h>
 
 #include <algorithm>
-#include <atomic>
-#include <random>
 
 namespace {
 
@@ -79,12 +77,12 @@ enum { LG_DEC_PLAIN = 0, LG_DEC_SEGS = 1, LG_DEC_PAGED = 2 };
 // ---------------------------------------------------------------- work of a decode launch
 // The keys of every (b, kv head, head chunk) -- a "row" here -- are cut into `splits` parts of `chunk` keys; a
 // workgroup takes one part.  (Paged: as many parts as the sequence's own length fills; the workgroups beyond leave.)
-// A row of several parts is added up by the last of its workgroups to finish (decode_finish).
+// Rows of several parts are added up by decode_add_kernel.
 struct LgDecWork {
-  int splits, chunk;         // (paged: the most parts of a row and the least keys of a part)
-  unsigned epoch;            // of this call, never 0
-  unsigned long long* word;  // [rows][splits][max(GT, 2)]: epoch << 32 | log2-sum-exp of a head
-  float* o;                  // [rows][splits][GT][D]: normalised partial results
+  int splits, chunk;  // (paged: the most parts of a row and the least keys of a part)
+  float* o;           // [rows][splits][G][D]: normalised results of the parts
+  float* lse2;        // [rows][splits][G]: their log2-sum-exp
+  int* parts;         // [rows], paged: parts of the row
 };
 constexpr int LG_DEC_SPLITS_MAX = 64;
 // Workgroups with keys that a paged step aims at: three per CU, what the matrix-core kernel's registers admit, or (bf16)
@@ -185,79 +183,6 @@ __device__ __forceinline__ bool lg_dec_part(const LgDecWork& wk, const LgPaged& 
 // What exponents are taken relative to: a maximum, or 0 where no score is finite (-inf - -inf is NaN; this way every
 // weight is 0 there).
 __device__ __forceinline__ float lg_finite_ref(float m) { return m == -INFINITY ? 0.f : m; }
-
-// Called by all threads (256) of a workgroup after its stores of a part's normalised results to wk.o.  lse2(g): the
-// part's log2-sum-exp of head g < ng.  Stores them, tagged with the call's epoch, once the results have arrived in
-// memory; then reads the tagged words of all parts of the row.  The workspace comes with any contents, so only words
-// under the epoch count.  A word is in memory before the others are read: the workgroup whose words arrive last sees
-// those of all parts and adds them up; should two see them all, both write the same result.  Whoever does clears the
-// words, so that a replay of the same launch from a graph starts afresh.  (A counter per row behind compare-and-swap
-// cost a memory round trip per part in series: 55 us with 33 parts.)
-// GT: heads a record has room for; scratch: LDS, GT * LG_DEC_SPLITS_MAX floats.
-template <typename T, int D, typename LSE2>
-__device__ __forceinline__ void decode_finish(const LgDecWork& wk, const LgDecPart& p, int ng, int GT,
-                                              T* __restrict__ out, float* __restrict__ lse, size_t out_row,
-                                              float* scratch, LSE2&& lse2) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, np = p.parts;
-  const int nw = GT > 2 ? GT : 2;  // words of a record (two at least: 64 bits of tag in all)
-  lg_shared_stores_done();
-  __syncthreads();
-  if (tid < nw)
-    __hip_atomic_store(wk.word + (p.row * wk.splits + p.split) * nw + tid,
-                       ((unsigned long long)wk.epoch << 32) | __float_as_uint(lse2(min(tid, ng - 1))), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-  lg_shared_stores_done();
-  __syncthreads();
-  const size_t rec = p.row * wk.splits;
-  unsigned long long* pw = wk.word + rec * nw;
-  bool here = true;
-  for (int y = tid; y < nw * np; y += WAVES * 64) {
-    const unsigned long long w = __hip_atomic_load(pw + y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    here = here && (unsigned)(w >> 32) == wk.epoch;
-    if (y % nw < GT) scratch[y / nw * GT + y % nw] = __uint_as_float((unsigned)w);
-  }
-  if (!__syncthreads_and(here)) return;
-  const float* po = wk.o + rec * GT * D;
-  constexpr int AHEAD = 8;  // loads in flight
-  f32x2_t x[AHEAD];
-  const int e_last = ng * D / 2 - 1;
-  auto load = [&](int e, int s0) {
-#pragma unroll
-    for (int u = 0; u < AHEAD; ++u) x[u] = lg_load_shared2(po + (size_t)min(s0 + u, np - 1) * GT * D + 2 * e);
-  };
-  load(min(tid, e_last), 0);  // on their way while the weights are made
-  for (int y = tid; y < nw * np; y += WAVES * 64)
-    __hip_atomic_store(pw + y, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  for (int g = wave; g < ng; g += WAVES) {  // weights of the parts of one head
-    const float l = lane < np ? scratch[lane * GT + g] : -INFINITY;
-    float M = l;
-#pragma unroll
-    for (int y = 1; y < 64; y <<= 1) M = fmaxf(M, __shfl_xor(M, y));
-    const float w = exp2f(l - lg_finite_ref(M));
-    float sum = w;
-#pragma unroll
-    for (int y = 1; y < 64; y <<= 1) sum += __shfl_xor(sum, y);
-    if (lane < np) scratch[lane * GT + g] = w / sum;
-    if (lse != nullptr && lane == 0) lse[out_row + g] = (M + log2f(sum)) * 0.69314718055994530942f;
-  }
-  __syncthreads();
-  for (int e = tid; e <= e_last; e += WAVES * 64) {
-    const int g = e / (D / 2);
-    f32x2_t acc = {0.f, 0.f};
-    for (int s0 = 0; s0 < np; s0 += AHEAD) {
-      if (e != tid || s0 > 0) load(e, s0);
-#pragma unroll
-      for (int u = 0; u < AHEAD; ++u)
-        if (s0 + u < np) {
-          const float w = scratch[(s0 + u) * GT + g];
-          acc[0] = fmaf(w, x[u][0], acc[0]);
-          acc[1] = fmaf(w, x[u][1], acc[1]);
-        }
-    }
-    store_out(out + out_row * D + 2 * e, acc[0]);
-    store_out(out + out_row * D + 2 * e + 1, acc[1]);
-  }
-}
 
 // log2-sum-exp of head g from the waves' maxima and sums (-inf where every score is)
 template <int N>
@@ -559,12 +484,56 @@ __global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
       if (lse != nullptr && d == 0) lse[out_row + g] = (M + log2f(L)) * 0.69314718055994530942f;
     } else {
       const size_t at = (p.row * wk.splits + p.split) * G;
-      lg_store_shared2(wk.o + at * D + 2 * e, a0 * inv, a1 * inv);
+      *reinterpret_cast<float2*>(wk.o + at * D + 2 * e) = make_float2(a0 * inv, a1 * inv);
     }
   }
-  if (p.parts > 1)  // (sO is free: the barrier in decode_finish comes first)
-    decode_finish<TT, D>(wk, p, G, G, out, lse, out_row, &sO[0][0][0],
-                                     [&](int g) { return lg_lse2(sM, sL, g); });
+  if (p.parts > 1 && tid < G) wk.lse2[(p.row * wk.splits + p.split) * G + tid] = lg_lse2(sM, sL, tid);
+  if (MODE == LG_DEC_PAGED && wk.splits > 1 && p.split == 0 && tid == 0) wk.parts[p.row] = p.parts;
+}
+
+// Adds the parts of a row, a wave for each query head: the weights of up to 64 parts in its lanes, D / 64 dims in each.
+// A launch of its own rather than the last of a row's workgroups to finish: nothing in the workspace is read that this
+// call has not written, and the GPU gets through it no slower (1 sequence of 32/8 heads, 1500 tokens, append and decode
+// replayed from a graph: 9.8 -> 9.1 us; 8 x 64/8 heads, 3648 slots: 27.0 -> 25.9).  A program that issues one short decode
+// after the other waits for the host's third launch (the same sequence without a graph: 10.0 -> 12.1 us).
+template <typename T, int D, bool PAGED>
+__global__ __launch_bounds__(64) void decode_add_kernel(LgDecWork wk, int G, T* __restrict__ out, float* __restrict__ lse) {
+  constexpr int E = D / 64, AHEAD = 16;  // loads in flight
+  typedef float vec_t __attribute__((ext_vector_type(E)));
+  const int lane = threadIdx.x, row = blockIdx.x / G, g = blockIdx.x - row * G;
+  const size_t rec = (size_t)row * wk.splits;
+  const float* po = wk.o + (rec * G + g) * D + E * lane;
+  // (the first parts are requested before their number is known: every address is inside the workspace)
+  const float mine = wk.lse2[(rec + min(lane, wk.splits - 1)) * G + g];
+  const int np = PAGED ? __builtin_amdgcn_readfirstlane(wk.parts[row]) : wk.splits;
+  vec_t x[AHEAD], acc = {};
+  auto load = [&](int s0) {
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) x[u] = *reinterpret_cast<const vec_t*>(po + (size_t)min(s0 + u, wk.splits - 1) * G * D);
+  };
+  load(0);
+  if (np == 1) return;  // (written by its workgroup)
+  const float l = lane < np ? mine : -INFINITY;
+  float M = l;
+#pragma unroll
+  for (int y = 1; y < 64; y <<= 1) M = fmaxf(M, __shfl_xor(M, y));
+  float w = exp2f(l - lg_finite_ref(M)), sum = w;
+#pragma unroll
+  for (int y = 1; y < 64; y <<= 1) sum += __shfl_xor(sum, y);
+  if (lse != nullptr && lane == 0) lse[(size_t)row * G + g] = (M + log2f(sum)) * 0.69314718055994530942f;
+  w /= sum;
+  for (int s0 = 0; s0 < np; s0 += AHEAD) {
+    if (s0 > 0) load(s0);
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u)
+      if (s0 + u < np) {
+        const float wu = __shfl(w, s0 + u);
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[e] = fmaf(wu, x[u][e], acc[e]);
+      }
+  }
+#pragma unroll
+  for (int e = 0; e < E; ++e) store_out(out + ((size_t)row * G + g) * D + E * lane + e, acc[e]);
 }
 
 // One thread per 16 bytes of a new token row (K and V): the token goes to its sink or ring
@@ -726,15 +695,6 @@ hipError_t launch_split_headdim(const void* q, const void* kc, const void* vc, v
   return hipGetLastError();
 }
 
-// A tag that the words of a workspace do not hold by chance: a counter from a random start.
-unsigned next_epoch() {
-  static std::atomic<unsigned> next{std::random_device{}()};
-  unsigned e;
-  do e = next.fetch_add(1, std::memory_order_relaxed);
-  while (e == 0);
-  return e;
-}
-
 struct DecPlan {
   int rows, most, splits, chunk;
   size_t part_bytes;  // workspace per part: most * rows * part_bytes serves every context up to the one given
@@ -743,7 +703,7 @@ DecPlan dec_plan(int B, int Hq, int Hkv, int D, int valid, int dtype, bool paged
   const int G = Hq / Hkv;
   DecPlan p;
   p.rows = B * Hkv;
-  p.part_bytes = (G > 2 ? G : 2) * sizeof(unsigned long long) + (size_t)G * D * sizeof(float);
+  p.part_bytes = ((size_t)G * (D + 1) + 1) * sizeof(float);  // results, log-sum-exps; LgDecWork::parts
   const int round = dtype == LG_F32 ? 64 : 128;  // keys of four units, one per wave
   const int rounds = (valid + round - 1) / round;
   // Most parts per row: five workgroups per CU; records within LG_DECODE_STATIC_SCRATCH_BYTES as long as that leaves
@@ -801,9 +761,9 @@ hipError_t launch_typed(const void* q, const void* kc, const void* vc, void* out
   wk.splits = plan.splits;
   wk.chunk = plan.chunk;
   if (plan.splits > 1) {
-    wk.epoch = next_epoch();
-    wk.word = (unsigned long long*)ws;
-    wk.o = (float*)(wk.word + (size_t)plan.rows * plan.splits * (G > 2 ? G : 2));
+    wk.o = (float*)ws;
+    wk.lse2 = wk.o + (size_t)plan.rows * plan.splits * G * D;
+    wk.parts = (int*)(wk.lse2 + (size_t)plan.rows * plan.splits * G);
   }
   dim3 grid(plan.splits, plan.rows / B, B);
   if (paged) {
@@ -821,6 +781,13 @@ hipError_t launch_typed(const void* q, const void* kc, const void* vc, void* out
   else if (plain) LG_DECODE_LAUNCH(LG_DEC_PLAIN);
   else LG_DECODE_LAUNCH(LG_DEC_SEGS);
 #undef LG_DECODE_LAUNCH
+  if (plan.splits > 1) {
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const dim3 heads((unsigned)(plan.rows * G));
+    if (paged) decode_add_kernel<T, D, true><<<heads, 64, 0, s>>>(wk, G, (T*)out, lse);
+    else decode_add_kernel<T, D, false><<<heads, 64, 0, s>>>(wk, G, (T*)out, lse);
+  }
   return hipGetLastError();
 }
 

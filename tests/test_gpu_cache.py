@@ -278,3 +278,49 @@ def test_parts_whose_scores_are_all_minus_infinity(dtype, Hq, Hkv, D, dead):
         for what, o, l in ((name, out, lse), ("forward", fo[:, :, N - 1], fl[:, :, N - 1])):
             assert_close(f32np(o), wo[:, :, N - 1], TOL_OUT[dtype], TOL_REL[dtype], what + " out")
             assert_close(f32np(l), wl[:, :, N - 1], TOL_LSE[dtype], None, what + " lse")
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("D,Hq,Hkv,N", [(128, 8, 2, 3000), (64, 3, 3, 9000), (128, 1, 1, 20000), (64, 16, 1, 700)])
+def test_any_workspace_contents_and_number_of_parts(dtype, D, Hq, Hkv, N):
+    """The workspace comes with any contents: bytes of one value, random ones, the leftovers of a call of another shape,
+    the call's own.  Same bits from each, right ones, and nothing written past its end; 2 to 64 parts per row, paged
+    with a row of a single part among them."""
+    sink, window, page_size = 4, 30000, 64
+    q, k, v = lg_synth.prefill_inputs(1, Hq, Hkv, N, D, 90, dtype)
+    code = lg.LG_BF16 if dtype == torch.bfloat16 else lg.LG_F32
+    kc, vc = gpu_append_all(k, v, sink, window, 1, 0, [N], lg.lg_kv_cache_slots(N, sink, window), 0.0)
+    n_max, table, kp, vp, _ = paged_setup([N, 40], Hq, Hkv, D, sink, window, 1, 0, page_size, dtype, 91)
+    for b, n in ((0, N), (1, 40)):
+        lg.lg_kv_paged_append(k[:, :, N - n:].contiguous().to(DEV), v[:, :, N - n:].contiguous().to(DEV), kp, vp,
+                              table[b:b + 1], torch.zeros(1, dtype=torch.int32, device=DEV), n_max, sink, window)
+    lens = torch.tensor([N, 40], dtype=torch.int32, device=DEV)
+    q1 = q[:, :, N - 1].contiguous().to(DEV)
+    need = (lg.decode_cache_workspace_bytes(1, Hq, Hkv, N, D, sink, window, 1, 0, code),
+            lg.decode_paged_workspace_bytes(2, Hq, Hkv, n_max, D, sink, window, 1, 0, code))
+    assert min(need) > 0
+
+    def run(ws):
+        res = []
+        for B, n in zip((1, 2), need):
+            out = torch.full((B, Hq, D), float("nan"), dtype=dtype, device=DEV)
+            lse = torch.full((B, Hq), float("nan"), device=DEV)
+            if B == 1:
+                lg.lg_sparse_attn_decode_cache(q1, kc, vc, out, lse, ws[:n], N, sink, window)
+            else:
+                lg.lg_sparse_attn_decode_paged(q1.expand(2, Hq, D).contiguous(), kp, vp, table, lens, out, lse, ws[:n],
+                                               n_max, sink, window)
+            res += [out, lse]
+            assert bool((ws[n:n + 64] == ws[-1]).all())
+        return res
+
+    size = max(need) + 4096
+    fills = [torch.full((size,), x, dtype=torch.uint8, device=DEV) for x in (0, 255, 127, 1)]
+    ref = run(fills[0])
+    wo, wl = O.fwd(f32np(q), f32np(k), f32np(v), sink, window, rows=(N - 1, N))
+    for out, lse in (ref[:2], ref[2:]):
+        assert_close(f32np(out[:1]), wo[:, :, N - 1], TOL_OUT[dtype], TOL_REL[dtype], "out")
+        assert_close(f32np(lse[:1]), wl[:, :, N - 1], TOL_LSE[dtype], None, "lse")
+    for ws in fills[1:] + [fills[0]]:
+        for a, b in zip(run(ws), ref):
+            assert torch.equal(a, b)
