@@ -73,6 +73,19 @@ struct LgPaged {
 };
 
 enum { LG_DEC_PLAIN = 0, LG_DEC_SEGS = 1, LG_DEC_PAGED = 2 };
+// What an instance receives beyond the common arguments, and no more: a launch with 250 bytes of arguments takes the host
+// about 0.5 us longer than one with 100, and a short step waits for the host (1 sequence of 32/8 heads, 1500 tokens 12.1 ->
+// 11.8 us; 48 paged sequences 77.2 -> 71.1, whose workgroups start with fewer scalar loads).
+template <int MODE>
+struct LgDecExtra {};
+template <>
+struct LgDecExtra<LG_DEC_SEGS> {
+  LgDecSegs segs;
+};
+template <>
+struct LgDecExtra<LG_DEC_PAGED> {
+  LgPaged pg;
+};
 
 // ---------------------------------------------------------------- work of a decode launch
 // The keys of every (b, kv head, head chunk) -- a "row" here -- are cut into `splits` parts of `chunk` keys; a
@@ -258,7 +271,7 @@ template <typename TT, int D, int MODE>
 __global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
     const typename LgDecElem<TT>::type* __restrict__ q, const typename LgDecElem<TT>::type* __restrict__ kc,
     const typename LgDecElem<TT>::type* __restrict__ vc, TT* __restrict__ out, float* __restrict__ lse, LgDecWork wk,
-    int Hq, int Hkv, int C, int valid, float qmul, float scale_log2e, float scale_pow2, LgDecSegs segs, LgPaged pg) {
+    int Hq, int Hkv, int C, int valid, float qmul, float scale_log2e, float scale_pow2, LgDecExtra<MODE> extra) {
   constexpr bool F32 = sizeof(TT) == 4;
   constexpr int UNIT = LgDecUnit<TT, D>::KEYS;
   constexpr int DC = D / (F32 ? 16 : 32), VE = D / 16;  // loads of a key row; 16-dim blocks of O
@@ -267,6 +280,10 @@ __global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
   __shared__ float sM[WAVES][16], sL[WAVES][16];
   __shared__ int spage[MODE == LG_DEC_PAGED ? PAGES : 1];
 
+  LgDecSegs segs;  // (paged: of the sequence, from lg_dec_part)
+  LgPaged pg;
+  if constexpr (MODE == LG_DEC_SEGS) segs = extra.segs;
+  if constexpr (MODE == LG_DEC_PAGED) pg = extra.pg;
   const int G = Hq / Hkv;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n = lane & 15, h = lane >> 4;
@@ -495,7 +512,7 @@ __global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
 // A launch of its own rather than the last of a row's workgroups to finish: nothing in the workspace is read that this
 // call has not written, and the GPU gets through it no slower (1 sequence of 32/8 heads, 1500 tokens, append and decode
 // replayed from a graph: 9.8 -> 9.1 us; 8 x 64/8 heads, 3648 slots: 27.0 -> 25.9).  A program that issues one short decode
-// after the other waits for the host's third launch (the same sequence without a graph: 10.0 -> 12.1 us).
+// after the other waits for the host's third launch (the same sequence without a graph: 10.0 -> 11.8 us).
 template <typename T, int D, bool PAGED>
 __global__ __launch_bounds__(64) void decode_add_kernel(LgDecWork wk, int G, T* __restrict__ out, float* __restrict__ lse) {
   constexpr int E = D / 64, AHEAD = 16;  // loads in flight
@@ -774,12 +791,13 @@ hipError_t launch_typed(const void* q, const void* kc, const void* vc, void* out
     grid = dim3((unsigned)most);
   }
   typedef typename LgDecElem<T>::type E;
-#define LG_DECODE_LAUNCH(MODE)                                                                                       \
+#define LG_DECODE_LAUNCH(MODE, ...)                                                                                  \
   decode_mfma_kernel<T, D, MODE><<<grid, WAVES * 64, 0, s>>>((const E*)q, (const E*)kc, (const E*)vc, (T*)out, lse, wk, \
-                                                             Hq, Hkv, C, valid, qmul, rest, ldexpf(1.f, ilogbf(rest)), segs, pg)
-  if (paged) LG_DECODE_LAUNCH(LG_DEC_PAGED);
+                                                             Hq, Hkv, C, valid, qmul, rest, ldexpf(1.f, ilogbf(rest)),  \
+                                                             LgDecExtra<MODE>{__VA_ARGS__})
+  if (paged) LG_DECODE_LAUNCH(LG_DEC_PAGED, pg);
   else if (plain) LG_DECODE_LAUNCH(LG_DEC_PLAIN);
-  else LG_DECODE_LAUNCH(LG_DEC_SEGS);
+  else LG_DECODE_LAUNCH(LG_DEC_SEGS, segs);
 #undef LG_DECODE_LAUNCH
   if (plan.splits > 1) {
     const hipError_t e = hipGetLastError();
