@@ -68,7 +68,8 @@
  *   LG_ERR_UNSUPPORTED  D not in {64, 128}; dtype not in lg_dtype; lg_sparse_attn_decode
  *                       with stride > 0 (use lg_sparse_attn_decode_cache); Hq/Hkv > 16
  *                       in decode
- *   LG_ERR_WORKSPACE    workspace NULL or smaller than *_workspace_bytes
+ *   LG_ERR_WORKSPACE    workspace NULL or smaller than *_workspace_bytes (lg_sparse_attn_bwd_varlen: than
+ *                       its largest sequence needs)
  *   LG_ERR_LAUNCH       the HIP runtime reported an error at launch (no GPU,
  *                       wrong architecture, ...)
  * Any N >= 1 works (ragged tails are masked), not only multiples of a tile.
@@ -169,9 +170,11 @@ int lg_debug_bwd_kernel_ms(const void* q, const void* k, const void* v, const vo
  * together; each sequence's pattern is cut to its length on the device).  The float32 forward and the
  * backward enqueue one set of launches per sequence, in order, each at the sequence's own length: there
  * the launches of short sequences (under ~64K query rows x heads) do not fill the GPU.
- * The backward workspace is shared by the sequences (size = the largest any of them needs; the
- * remarks on lg_sparse_attn_bwd's workspace apply).  On the bf16 path as many sequences as fit it run
- * side by side (its size is never below 64 MiB); a larger workspace_bytes lets more of them do so.
+ * The backward workspace is shared by the sequences (the remarks on lg_sparse_attn_bwd's workspace apply).  A call
+ * needs no more than the largest of its sequences needs by itself (lg_sparse_attn_bwd_workspace_bytes with B = 1);
+ * only less is refused.  On the bf16 path as many sequences as fit it run side by side, up to 128 in a set of
+ * launches: lg_sparse_attn_bwd_varlen_workspace_bytes asks for what that takes, up to 128 MiB, and a larger
+ * workspace_bytes lets more of them do so.
  * Errors, beyond the common ones: LG_ERR_NULL for cu_seqlens == NULL; LG_ERR_INVALID_ARG for
  * num_seqs < 1, cu_seqlens[0] != 0, a decreasing offset, a sequence longer than 2^30, or
  * Hq*T*D beyond 2^40 elements.  *_workspace_bytes returns 0 for invalid arguments.

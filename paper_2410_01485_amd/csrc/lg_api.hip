@@ -179,6 +179,14 @@ static int check_varlen(const int* cu_seqlens, int num_seqs, int Hq, int Hkv, in
   return (double)Hq * (double)*total * (double)D > 1099511627776.0 ? LG_ERR_INVALID_ARG : LG_OK;
 }
 
+// The pattern that each packed sequence cuts to its own length: nothing clamped to a length yet, a head's rows of all
+// sequences (T) side by side.
+static LgMask pack_pattern(int T, int sink, int window, int block, int stride) {
+  LgMask m = lg_make_mask(1 << 30, sink, window, block, stride);
+  m.ld = T;
+  return m;
+}
+
 int lg_sparse_attn_fwd_varlen(const void* q, const void* k, const void* v, void* out, float* lse,
                               const int* cu_seqlens, int num_seqs, int Hq, int Hkv, int D,
                               int sink, int window, int block, int stride,
@@ -194,8 +202,7 @@ int lg_sparse_attn_fwd_varlen(const void* q, const void* k, const void* v, void*
     // one launch per LG_PACK_MAX sequences: every (sequence, head, query tile) is a workgroup of the same
     // grid, so short sequences fill the GPU together
     const LgShape sh = make_shape(1, Hq, Hkv, longest > 0 ? longest : 1, D, scale);
-    LgMask tmpl = lg_make_mask(1 << 30, sink, window, block, stride);  // nothing clamped to a length yet
-    tmpl.ld = T;  // a head's rows of all sequences lie side by side
+    const LgMask tmpl = pack_pattern(T, sink, window, block, stride);
     int x = 0;
     while (x < num_seqs) {
       LgPack pack;
@@ -227,11 +234,9 @@ int lg_sparse_attn_fwd_varlen(const void* q, const void* k, const void* v, void*
   return LG_OK;
 }
 
-size_t lg_sparse_attn_bwd_varlen_workspace_bytes(const int* cu_seqlens, int num_seqs, int Hq, int Hkv, int D,
-                                                 int sink, int window, int block, int stride, int dtype) {
-  int T = 0, longest = 0;
-  if (check_varlen(cu_seqlens, num_seqs, Hq, Hkv, D, sink, window, block, stride, dtype, &T, &longest) != LG_OK)
-    return 0;
+// What the packed backward cannot do without: the most that any sequence needs by itself.
+static size_t bwd_varlen_least(const int* cu_seqlens, int num_seqs, int Hq, int Hkv, int D, int sink, int window,
+                               int block, int stride, int dtype) {
   size_t need = 256;  // never 0 for valid arguments: 0 is the error value
   for (int x = 0; x < num_seqs; ++x) {
     const int n = cu_seqlens[x + 1] - cu_seqlens[x];
@@ -241,6 +246,17 @@ size_t lg_sparse_attn_bwd_varlen_workspace_bytes(const int* cu_seqlens, int num_
     need = b > need ? b : need;
   }
   return need;
+}
+
+size_t lg_sparse_attn_bwd_varlen_workspace_bytes(const int* cu_seqlens, int num_seqs, int Hq, int Hkv, int D,
+                                                 int sink, int window, int block, int stride, int dtype) {
+  int T = 0, longest = 0;
+  if (check_varlen(cu_seqlens, num_seqs, Hq, Hkv, D, sink, window, block, stride, dtype, &T, &longest) != LG_OK)
+    return 0;
+  const size_t least = bwd_varlen_least(cu_seqlens, num_seqs, Hq, Hkv, D, sink, window, block, stride, dtype);
+  if (dtype != LG_BF16 || longest == T) return least;  // (one sequence that is not empty, or none)
+  return lg_bwd_bf16_pack_workspace_bytes(make_shape(1, Hq, Hkv, longest, D, 0.0f),
+                                          pack_pattern(T, sink, window, block, stride), cu_seqlens, num_seqs, least);
 }
 
 int lg_sparse_attn_bwd_varlen(const void* q, const void* k, const void* v, const void* out, const float* lse,
@@ -256,14 +272,13 @@ int lg_sparse_attn_bwd_varlen(const void* q, const void* k, const void* v, const
   const void* ptrs[] = {q, k, v, out, lse, dout, dq, dk, dv, workspace};
   for (const void* p : ptrs)
     if (!aligned16(p)) return LG_ERR_INVALID_ARG;
-  if (!workspace || workspace_bytes < lg_sparse_attn_bwd_varlen_workspace_bytes(
-                                          cu_seqlens, num_seqs, Hq, Hkv, D, sink, window, block, stride, dtype))
+  if (!workspace ||
+      workspace_bytes < bwd_varlen_least(cu_seqlens, num_seqs, Hq, Hkv, D, sink, window, block, stride, dtype))
     return LG_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
   if (dtype == LG_BF16) {
     const LgShape sh = make_shape(1, Hq, Hkv, longest > 0 ? longest : 1, D, scale);
-    LgMask tmpl = lg_make_mask(1 << 30, sink, window, block, stride);  // as in the forward
-    tmpl.ld = T;
+    const LgMask tmpl = pack_pattern(T, sink, window, block, stride);
     return lg_launch_bwd_bf16_pack(q, k, v, out, lse, dout, dq, dk, dv, workspace, workspace_bytes, sh, tmpl, cu_seqlens,
                                    num_seqs, s) == hipSuccess
                ? LG_OK

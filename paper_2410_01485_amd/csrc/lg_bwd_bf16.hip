@@ -33,6 +33,8 @@
 // For head dim 128 and long windows (dq 32 or more tiles, dk/dv 16) both kernels have a second form with 64 rows
 // (keys) per wave, one wave per SIMD and the accumulators in AGPRs (further down): every operand
 // read from LDS then feeds two matrix instructions.
+#include <algorithm>
+
 #include "../../include/longgen_attn.h"
 #include "lg_kernels.h"
 #include "lg_mfma.h"
@@ -1844,6 +1846,10 @@ Cut choose_cut(int D, int G, int nbh, size_t tiles, double steps, int longest, s
   }
   return best;
 }
+bool may_cut(const LgShape& sh, bool strided, size_t items) {
+  return (sh.Hq != sh.Hkv || strided) && items <= (sh.D == 128 ? 2 : 4) * CUS;
+}
+constexpr size_t MOST_PARTS = 8 * CUS;  // where the workspace is made for the cut: no limit
 // query tiles of the window parts of a sequence's key tiles
 void window_steps(const LgMask& m, int btk, double* steps, int* longest) {
   for (int k0 = 0; k0 < m.N; k0 += btk) {
@@ -2080,24 +2086,106 @@ BwdLaunch batch_launch(const LgShape& sh, const LgMask& m) {
   (dq_wide(m, sh.D) ? a.qt_wide : a.qt_rest) = (sh.N + LG_BF16_TQ - 1) / LG_BF16_TQ;
   (dkdv_wide(m, sh.D) ? a.kt_wide : a.kt_rest) = (int)a.size.ktiles;
   a.cut = {1, 1};
-  if ((sh.Hq != sh.Hkv || m.stride > 0) && a.size.ktiles * sh.B * sh.Hkv <= (sh.D == 128 ? 2 : 4) * CUS) {
+  if (may_cut(sh, m.stride > 0, a.size.ktiles * sh.B * sh.Hkv)) {
     double steps = 0;
     int longest = 0;
     window_steps(m, a.setup.btk, &steps, &longest);
-    a.cut = choose_cut(sh.D, sh.Hq / sh.Hkv, sh.B * sh.Hkv, a.size.ktiles, steps, longest, 8 * CUS);
+    a.cut = choose_cut(sh.D, sh.Hq / sh.Hkv, sh.B * sh.Hkv, a.size.ktiles, steps, longest, MOST_PARTS);
   }
   return a;
 }
+
+// The next set of launches of a pack, for the sequences from `x` on: those that fit `budget` bytes of workspace together
+// (the first one always counts as fitting), up to LG_PACK_MAX, sorted longest first.  Returns the first sequence that is
+// not in it and the bytes it uses; a->setup.n is 0 when only empty sequences were left.  -1: too many work items.
+int pack_launch(const LgShape& sh, const LgMask& tmpl, const int* cu_seqlens, int num_seqs, int x, size_t budget,
+                BwdLaunch* out, size_t* bytes) {
+  struct Seq {
+    int row0, len;
+    Columns c;
+  } seq[LG_PACK_MAX];
+  BwdLaunch& a = *out;
+  a = {};
+  a.m = tmpl;
+  a.B = 1;
+  a.Hq = sh.Hq;
+  a.Hkv = sh.Hkv;
+  a.D = sh.D;
+  a.scale = sh.scale;
+  a.cut = {1, 1};
+  a.setup.btk = btk_of(sh.D);
+  auto end = [&](const BwdSize& z) { return bwd_layout(z, 1, sh.Hq, sh.Hkv, sh.D, a.cut).end; };
+  int& n = a.setup.n;
+  for (; x < num_seqs && n < LG_PACK_MAX; ++x) {
+    const int len = cu_seqlens[x + 1] - cu_seqlens[x];
+    if (len == 0) continue;
+    const Seq one = {cu_seqlens[x], len, columns_of(lg_mask_for_length(tmpl, len), sh.D)};
+    BwdSize z = a.size;
+    z.add(len, sh.D, one.c);
+    if (n > 0 && (end(z) > budget || z.ktiles > 0xffffff || (double)z.rows * sh.Hq > 1e9)) break;
+    a.size = z;
+    int y = n++;
+    for (; y > 0 && seq[y - 1].len < len; --y) seq[y] = seq[y - 1];
+    seq[y] = one;
+  }
+  if (n == 0) return x;
+  auto citems = [&](int chunk) {
+    long long all = 0;
+    for (int y = 0; y < n; ++y) all += seq[y].c.items(sh.D, chunk);
+    return all * sh.Hq;
+  };
+  int longest_col = 0;
+  for (int y = 0; y < n; ++y)
+    if (seq[y].c.last - seq[y].c.first > longest_col) longest_col = seq[y].c.last - seq[y].c.first;
+  a.chunk = choose_chunk(citems, longest_col, sh.Hq / sh.Hkv);
+  if (citems(a.chunk) > 0x7fffffffLL) return -1;
+  double steps = 0;
+  int longest = 0;
+  bool strided = false;
+  for (int y = 0; y < n; ++y) {
+    const LgMask m = lg_mask_for_length(tmpl, seq[y].len);
+    a.setup.row0[y] = seq[y].row0;
+    a.setup.len[y] = seq[y].len;
+    a.setup.ncol[y] = seq[y].c.ncol;
+    a.setup.citems[y] = seq[y].c.items(sh.D, a.chunk);
+    a.setup.nlone[y] = seq[y].c.lone();
+    a.citems += a.setup.citems[y];
+    // (both rules are monotone in the length: the wide ones come first)
+    (dq_wide(m, sh.D) ? a.qt_wide : a.qt_rest) += (seq[y].len + LG_BF16_TQ - 1) / LG_BF16_TQ;
+    (dkdv_wide(m, sh.D) ? a.kt_wide : a.kt_rest) += (seq[y].len + a.setup.btk - 1) / a.setup.btk;
+    a.setup.nwide += dkdv_wide(m, sh.D);
+    strided = strided || m.stride > 0;
+  }
+  if (may_cut(sh, strided, a.size.ktiles * sh.Hkv)) {
+    for (int y = 0; y < n; ++y) window_steps(lg_mask_for_length(tmpl, seq[y].len), a.setup.btk, &steps, &longest);
+    const size_t tile = (size_t)sh.Hkv * a.size.ktiles * (a.setup.btk * 2 * sizeof(float)) * sh.D, used = end(a.size);
+    a.cut = choose_cut(sh.D, sh.Hq / sh.Hkv, sh.Hkv, a.size.ktiles, steps, longest,
+                       n == 1 ? MOST_PARTS : used < budget ? (budget - used) / tile : 0);
+  }
+  *bytes = end(a.size);
+  return x;
+}
 }  // namespace
 
-// Packed sequences that share a workspace fill the GPU together, so no workspace is made smaller than this: room for
-// 85000 to 500000 tokens (64 to 8 query heads) in one set of launches.
-constexpr size_t BWD_WORKSPACE_MIN = 128u << 20;
+// Sequences side by side in one set of launches are worth up to this much workspace: room for 85000 to 500000 tokens (64
+// to 8 query heads).
+constexpr size_t BWD_PACK_BYTES = 128u << 20;
 
 size_t lg_bwd_bf16_workspace_bytes(const LgShape& sh, const LgMask& m) {
   const BwdLaunch a = batch_launch(sh, m);
-  const size_t end = bwd_layout(a.size, sh.B, sh.Hq, sh.Hkv, sh.D, a.cut).end;
-  return end > BWD_WORKSPACE_MIN ? end : BWD_WORKSPACE_MIN;
+  return bwd_layout(a.size, sh.B, sh.Hq, sh.Hkv, sh.D, a.cut).end;
+}
+
+size_t lg_bwd_bf16_pack_workspace_bytes(const LgShape& sh, const LgMask& tmpl, const int* cu_seqlens, int num_seqs,
+                                        size_t least) {
+  size_t need = least;
+  BwdLaunch a;
+  for (int x = 0; x >= 0 && x < num_seqs;) {
+    size_t bytes = 0;
+    x = pack_launch(sh, tmpl, cu_seqlens, num_seqs, x, std::max(least, BWD_PACK_BYTES), &a, &bytes);
+    need = std::max(need, bytes);
+  }
+  return need;
 }
 
 hipError_t lg_launch_bwd_bf16(const void* q, const void* k, const void* v, const void* out, const float* lse,
@@ -2114,70 +2202,16 @@ hipError_t lg_launch_bwd_bf16_pack(const void* q, const void* k, const void* v, 
                                    const void* dout, void* dq, void* dk, void* dv, void* ws, size_t ws_bytes,
                                    const LgShape& sh, const LgMask& tmpl, const int* cu_seqlens, int num_seqs,
                                    hipStream_t s) {
-  int x = 0;
-  while (x < num_seqs) {
-    // the next sequences that fit the workspace together (one always does), sorted longest first
-    struct Seq {
-      int row0, len;
-      Columns c;
-    } seq[LG_PACK_MAX];
-    BwdLaunch a = {};
-    a.m = tmpl;
-    a.B = 1;
-    a.Hq = sh.Hq;
-    a.Hkv = sh.Hkv;
-    a.D = sh.D;
-    a.scale = sh.scale;
-    a.cut = {1, 1};
-    a.setup.btk = btk_of(sh.D);
-    int& n = a.setup.n;
-    for (; x < num_seqs && n < LG_PACK_MAX; ++x) {
-      const int len = cu_seqlens[x + 1] - cu_seqlens[x];
-      if (len == 0) continue;
-      const Seq one = {cu_seqlens[x], len, columns_of(lg_mask_for_length(tmpl, len), sh.D)};
-      BwdSize z = a.size;
-      z.add(len, sh.D, one.c);
-      if (n > 0 && (bwd_layout(z, 1, sh.Hq, sh.Hkv, sh.D, a.cut).end > ws_bytes || z.ktiles > 0xffffff ||
-                    (double)z.rows * sh.Hq > 1e9))
-        break;
-      a.size = z;
-      int y = n++;
-      for (; y > 0 && seq[y - 1].len < len; --y) seq[y] = seq[y - 1];
-      seq[y] = one;
-    }
-    if (n == 0) break;
-    auto citems = [&](int chunk) {
-      long long all = 0;
-      for (int y = 0; y < n; ++y) all += seq[y].c.items(sh.D, chunk);
-      return all * sh.Hq;
-    };
-    int longest_col = 0;
-    for (int y = 0; y < n; ++y)
-      if (seq[y].c.last - seq[y].c.first > longest_col) longest_col = seq[y].c.last - seq[y].c.first;
-    a.chunk = choose_chunk(citems, longest_col, sh.Hq / sh.Hkv);
-    if (citems(a.chunk) > 0x7fffffffLL) return hipErrorInvalidValue;
-    double steps = 0;
-    int longest = 0;
-    const bool may_cut = (sh.Hq != sh.Hkv || tmpl.stride > 0) && a.size.ktiles * sh.Hkv <= (sh.D == 128 ? 2 : 4) * CUS;
-    for (int y = 0; y < n; ++y) {
-      const LgMask m = lg_mask_for_length(tmpl, seq[y].len);
-      a.setup.row0[y] = seq[y].row0;
-      a.setup.len[y] = seq[y].len;
-      a.setup.ncol[y] = seq[y].c.ncol;
-      a.setup.citems[y] = seq[y].c.items(sh.D, a.chunk);
-      a.setup.nlone[y] = seq[y].c.lone();
-      a.citems += a.setup.citems[y];
-      // (both rules are monotone in the length: the wide ones come first)
-      (dq_wide(m, sh.D) ? a.qt_wide : a.qt_rest) += (seq[y].len + LG_BF16_TQ - 1) / LG_BF16_TQ;
-      (dkdv_wide(m, sh.D) ? a.kt_wide : a.kt_rest) += (seq[y].len + a.setup.btk - 1) / a.setup.btk;
-      a.setup.nwide += dkdv_wide(m, sh.D);
-      if (may_cut) window_steps(m, a.setup.btk, &steps, &longest);
-    }
-    if (may_cut) {
-      const size_t tile = (size_t)sh.Hkv * a.size.ktiles * (a.setup.btk * 2 * sizeof(float)) * sh.D;
-      a.cut = choose_cut(sh.D, sh.Hq / sh.Hkv, sh.Hkv, a.size.ktiles, steps, longest,
-                         (ws_bytes - bwd_layout(a.size, 1, sh.Hq, sh.Hkv, sh.D, a.cut).end) / tile);
-    }
+  BwdLaunch a;
+  for (int x = 0; x < num_seqs;) {
+    // (planned as for the size that was asked for, so that a workspace of that size or more gives one and the same plan
+    // up to BWD_PACK_BYTES; again for what is there if that is less)
+    size_t bytes = 0;
+    int next = pack_launch(sh, tmpl, cu_seqlens, num_seqs, x, std::max(ws_bytes, BWD_PACK_BYTES), &a, &bytes);
+    if (next >= 0 && bytes > ws_bytes) next = pack_launch(sh, tmpl, cu_seqlens, num_seqs, x, ws_bytes, &a, &bytes);
+    if (next < 0 || bytes > ws_bytes) return hipErrorInvalidValue;
+    x = next;
+    if (a.setup.n == 0) break;
     const hipError_t e =
         launch_bwd((const uint16_t*)q, (const uint16_t*)k, (const uint16_t*)v, (const uint16_t*)out, lse,
                    (const uint16_t*)dout, (uint16_t*)dq, (uint16_t*)dk, (uint16_t*)dv, ws, a, s, nullptr);

@@ -47,6 +47,9 @@ hipError_t lg_launch_fwd_bf16_pack(const void* q, const void* k, const void* v, 
 
 size_t lg_bwd_workspace_bytes(const LgShape& sh, const LgMask& m, int dtype);
 size_t lg_bwd_bf16_workspace_bytes(const LgShape& sh, const LgMask& m);
+// For the packed launch below; least: the most that any of its sequences needs by itself, with which it runs as well.
+size_t lg_bwd_bf16_pack_workspace_bytes(const LgShape& sh, const LgMask& tmpl, const int* cu_seqlens, int num_seqs,
+                                        size_t least);
 // ev: NULL, or 4 events recorded before the set-up, before the dq kernel, before the dk/dv kernels and after the
 // last one (measurement aid).
 hipError_t lg_launch_bwd_f32(const float* q, const float* k, const float* v, const float* out,

@@ -70,7 +70,7 @@ def test_bwd_argument_errors():
 
 def test_varlen_argument_errors_and_workspace():
     """The packed, different-lengths calls validate the offsets and everything else before the first HIP call;
-    a pack of empty sequences enqueues nothing and succeeds; the workspace is the largest any sequence needs."""
+    a pack of empty sequences enqueues nothing and succeeds; the workspace is at least the largest any sequence needs."""
     L = lg.lib()
 
     def cu_arr(cu):
@@ -94,14 +94,34 @@ def test_varlen_argument_errors_and_workspace():
     assert fwd_v(cu=(0, 0, 0, 0)) == 0 and fwd_v(cu=(0, 0), lse=None) == 0   # nothing to do: no HIP call made
     assert bwd_v(lse=None) == 1 and bwd_v(dq=P + 8) == 2 and bwd_v(D=48) == 3
     assert bwd_v(cu=(0, 5, 3)) == 2 and bwd_v(cu=(0, 0)) == 0
+    # what is asked for lets the sequences run side by side; refused is less than the largest of them needs by itself
     need = lg.bwd_varlen_workspace_bytes([0, 100, 300, 300, 350], 4, 2, 128, 4, 8, 1, 0, lg.LG_BF16)
-    assert need == max(lg.bwd_workspace_bytes(1, 4, 2, n, 128, 4, 8, 1, 0, lg.LG_BF16) for n in (100, 200, 50))
-    assert bwd_v(ws_bytes=need - 1, cu=(0, 100, 300, 300, 350)) == 4 and bwd_v(ws=None, cu=(0, 100, 300)) == 4
+    least = max(lg.bwd_workspace_bytes(1, 4, 2, n, 128, 4, 8, 1, 0, lg.LG_BF16) for n in (100, 200, 50))
+    assert least <= need <= 128 << 20
+    assert bwd_v(ws_bytes=least - 1, cu=(0, 100, 300, 300, 350)) == 4 and bwd_v(ws=None, cu=(0, 100, 300)) == 4
+    alone = lg.bwd_workspace_bytes(1, 4, 2, 200, 128, 4, 8, 1, 0, lg.LG_BF16)
+    assert lg.bwd_varlen_workspace_bytes([0, 0, 200, 200], 4, 2, 128, 4, 8, 1, 0, lg.LG_BF16) == alone
+    assert (lg.bwd_varlen_workspace_bytes([0, 100, 300, 350], 4, 2, 128, 4, 8, 1, 0, lg.LG_F32) ==
+            lg.bwd_workspace_bytes(1, 4, 2, 200, 128, 4, 8, 1, 0, lg.LG_F32))
     assert lg.bwd_varlen_workspace_bytes([0, 0], 4, 2, 128, 4, 8, 1, 0, lg.LG_BF16) == 256
     assert lg.bwd_varlen_workspace_bytes([0, 5, 3], 4, 2, 128, 4, 8, 1, 0, lg.LG_BF16) == 0
     assert lg.bwd_varlen_workspace_bytes([0, 5], 4, 2, 48, 4, 8, 1, 0, lg.LG_BF16) == 0
     with pytest.raises(ValueError):
         lg.bwd_varlen_workspace_bytes([0], 4, 2, 128, 4, 8, 1, 0, lg.LG_BF16)
+
+
+def test_bwd_workspace_is_what_the_call_uses():
+    """One short sequence asks for a few KB, sequences side by side for about what they need one by one, never for much
+    more than the 128 MiB that a set of launches is made for."""
+    size = lg.bwd_workspace_bytes
+    assert size(1, 1, 1, 64, 64, 4, 8, 1, 0, lg.LG_BF16) < 16 << 10
+    assert size(1, 32, 32, 4096, 128, 64, 1024, 1, 0, lg.LG_BF16) < 8 << 20
+    one = size(1, 8, 8, 1000, 128, 64, 512, 1, 0, lg.LG_BF16)
+    cu = [1000 * x for x in range(31)]
+    pack = lg.bwd_varlen_workspace_bytes(cu, 8, 8, 128, 64, 512, 1, 0, lg.LG_BF16)
+    assert one < pack <= 30 * one
+    big = lg.bwd_varlen_workspace_bytes([8000 * x for x in range(101)], 32, 32, 128, 64, 512, 1, 0, lg.LG_BF16)
+    assert big <= 128 << 20
 
 
 def test_decode_argument_errors():
