@@ -124,7 +124,8 @@ int lg_sparse_attn_fwd(const void* q, const void* k, const void* v, void* out, f
  * PyTorch): with a strided pattern or Hq > Hkv the bf16 path adds partial dk/dv sums of sink
  * and strided-column keys into it with hardware float atomics; their order is not fixed, so
  * the last bits of those dk/dv rows can differ between runs (a sink + window call with
- * Hq == Hkv uses no atomics and is bit-reproducible).
+ * Hq == Hkv uses no atomics and is bit-reproducible; there dk and dv do not depend on B either, elsewhere
+ * the number of float32 partial sums of a key does).
  */
 size_t lg_sparse_attn_bwd_workspace_bytes(int B, int Hq, int Hkv, int N, int D,
                                           int sink, int window, int block, int stride, int dtype);
@@ -163,7 +164,12 @@ int lg_debug_bwd_kernel_ms(const void* q, const void* k, const void* v, const vo
  * cu_seqlens is a HOST array of num_seqs + 1 non-decreasing offsets starting at 0, read during the
  * call only.  Every sequence is attended on its own, positions counted from its first token:
  * the results of sequence s equal lg_sparse_attn_fwd / lg_sparse_attn_bwd with B = 1 and
- * N = its length on its rows (bit for bit on the paths those calls reproduce bit for bit).
+ * N = its length on its rows.  Bit for bit: out, lse and dq; dk and dv on the float32 path and where
+ * Hq == Hkv and stride == 0.  On the bf16 path with Hq > Hkv or stride > 0, dk and dv of a key are cut into
+ * float32 partial sums as suits the key tiles of the whole set of launches and workspace_bytes, so they
+ * depend, within the rounding of float32 sums before the one to bf16, on the other sequences (a sequence
+ * that is the only one that is not empty: bit for bit, but for the sink and strided keys, which are added
+ * with atomics).
  * Empty sequences are allowed and skipped; when all are empty nothing is enqueued.
  * No work is spent on padding.  The bf16 forward puts up to 128 sequences into one launch (every
  * (sequence, head, 256-row query tile) is a workgroup of the same grid, so short sequences fill the GPU
