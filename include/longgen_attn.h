@@ -285,7 +285,10 @@ int lg_sparse_attn_decode_cache_static(const void* q, const void* k_cache, const
  *                      token); values outside [1, n_max] are clamped
  *   positions        : [B] int32 device, position of the first of the T new tokens per sequence
  * n_max bounds the context lengths: pages_per_seq * page_size >= lg_kv_cache_slots(n_max, ...)
- * is required, and the workspace is sized for it.  Every table entry a sequence can reach must be
+ * is required, and the workspace is sized for it.  How many parts a sequence's keys are split into (float32 partial
+ * softmax results, added with their log-sum-exps) is chosen on the device from the lengths of the whole batch, so that
+ * the parts fill the GPU evenly: the last bits of a sequence's result depend on the other sequences' lengths (never on
+ * their contents), as those of lg_sparse_attn_decode_cache depend on B.  Every table entry a sequence can reach must be
  * in [0, num_pages); an entry outside that range is clamped into it on the device (the result of that
  * sequence is then wrong, but nothing outside the pool is read or written).
  * lg_kv_paged_append stores k_new, v_new [B, Hkv, T, D]; a strided-block copy whose slot lies

@@ -324,3 +324,23 @@ def test_any_workspace_contents_and_number_of_parts(dtype, D, Hq, Hkv, N):
     for ws in fills[1:] + [fills[0]]:
         for a, b in zip(run(ws), ref):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_contents_of_other_paged_sequences_do_not_matter(dtype):
+    """The lengths of the batch choose the parts, the contents of the other sequences choose nothing: with their pages and
+    queries turned to Inf and NaN the sequence in the middle keeps its bits."""
+    lens, Hq, Hkv, D, sink, window, page_size = [3000, 1700, 20, 5000], 8, 2, 128, 4, 6000, 32
+    n_max, table, kp, vp, ctx = paged_setup(lens, Hq, Hkv, D, sink, window, 1, 0, page_size, dtype, 95)
+    for b, (q, k, v) in enumerate(ctx):
+        lg.lg_kv_paged_append(k.to(DEV), v.to(DEV), kp, vp, table[b:b + 1], torch.zeros(1, dtype=torch.int32, device=DEV),
+                              n_max, sink, window)
+    qs = [q[0, :, n - 1] for (q, _, _), n in zip(ctx, lens)]
+    want = paged_decode(qs, kp, vp, table, lens, n_max, sink, window, 1, 0)
+    for b, x in ((0, float("inf")), (2, float("nan")), (3, float("-inf"))):
+        kp[table[b].long()] = x
+        vp[table[b].long()] = x
+        qs[b] = torch.full_like(qs[b], x)
+    got = paged_decode(qs, kp, vp, table, lens, n_max, sink, window, 1, 0)
+    for x, y in zip(got, want):
+        assert torch.equal(x[1], y[1])
