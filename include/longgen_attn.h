@@ -336,9 +336,13 @@ int lg_debug_decode_segments(int N, int sink, int window, int block, int stride,
  * Host-only view of the block-skipping tile scheduler (Section 3.2: the mask is
  * kept in compressed-sparse-row form, O(N) memory; it is static for all heads).
  * Writes, in CSR form, the list of live kernel tiles the device code walks:
- *   transposed == 0: rows are query tiles, columns key tiles (forward, dq);
- *   transposed == 1: rows are key tiles, columns query tiles (dk/dv).
- * tq/tk receive the kernel tile sizes used for `dtype`.  row_ptr has rows+1
+ *   transposed 0, 2: rows are query tiles, columns key tiles (forward, dq);
+ *   transposed 1, 3: rows are key tiles, columns query tiles (dk/dv).
+ * tq/tk receive the kernel tile sizes used for `dtype`.  float32: 64 x 64 throughout.  bf16:
+ *   0: 256 x 64, the dq kernel with 64 rows per wave (head dim 128, long windows);
+ *   2: 128 x 64, the forward and the other dq kernel;
+ *   1: 64 x 256, the dk/dv kernels at head dim 128;      3: 64 x 128, at head dim 64.
+ * row_ptr has rows+1
  * entries; col_idx/kind have row_ptr[rows] entries; kind is 1 when every
  * (i,j) of the tile is live (no masking needed) and 0 when the predicate must
  * be applied per element.  All output pointers are HOST pointers; cap is the
@@ -356,9 +360,10 @@ int lg_debug_tile_map(int N, int sink, int window, int block, int stride, int dt
 
 /*
  * Host-only: the ORDER in which the bf16 kernels visit the live tiles of one row of the tile map
- * (row = query tile for transposed == 0, key tile for transposed == 1).  Patterns without
+ * (`transposed` as there; row = query tile for 0 and 2, key tile for 1 and 3).  Patterns without
  * strided columns walk their contiguous run of tiles rotated (see lg_debug_tile_map); for a key
- * tile the window part comes first (rotated), then the column part in increasing order.
+ * tile the window part comes first (rotated), then, where column parts are split off, the column part in
+ * increasing order.  (One query head's worth; the backward may cut a key tile's walk into parts.)
  * order: HOST array of cap entries (may be NULL with cap = 0); *count receives the number of
  * tiles.  The set of tiles equals the row of lg_debug_tile_map.
  */

@@ -513,6 +513,13 @@ int lg_debug_decode_segments(int N, int sink, int window, int block, int stride,
   return LG_OK;
 }
 
+// Tile sizes of the bf16 kernels: bit 0 of `transposed` the dk/dv kernels, bit 1 the smaller tiles.
+static void bf16_tiles(int transposed, int* tq, int* tk) {
+  const bool dkdv = (transposed & 1) != 0, small = (transposed & 2) != 0;
+  *tq = dkdv ? LG_BF16_BTQ : small ? LG_BF16_TQ32 : LG_BF16_TQ;
+  *tk = !dkdv ? LG_BF16_TK : small ? LG_BF16_BTK64 : LG_BF16_BTK;
+}
+
 int lg_debug_tile_map(int N, int sink, int window, int block, int stride, int dtype, int transposed,
                       int* tq, int* tk, int32_t* row_ptr, size_t row_cap,
                       int32_t* col_idx, uint8_t* kind, size_t cap,
@@ -521,13 +528,13 @@ int lg_debug_tile_map(int N, int sink, int window, int block, int stride, int dt
   int st = check_common(1, 1, 1, N, 64, sink, window, block, stride, dtype);
   if (st != LG_OK) return st;
   const LgMask m = lg_make_mask(N, sink, window, block, stride);
+  const bool dkdv = (transposed & 1) != 0;
   int Tq, Tk;
   if (dtype == LG_F32) {
-    Tq = transposed ? LG_F32_BTQ : LG_F32_TQ;
-    Tk = transposed ? LG_F32_BTK : LG_F32_TK;
+    Tq = dkdv ? LG_F32_BTQ : LG_F32_TQ;
+    Tk = dkdv ? LG_F32_BTK : LG_F32_TK;
   } else {
-    Tq = transposed ? LG_BF16_BTQ : LG_BF16_TQ;
-    Tk = transposed ? LG_BF16_BTK : LG_BF16_TK;
+    bf16_tiles(transposed, &Tq, &Tk);
   }
   *tq = Tq;
   *tk = Tk;
@@ -543,7 +550,7 @@ int lg_debug_tile_map(int N, int sink, int window, int block, int stride, int dt
     if (row_ptr && r < row_cap) row_ptr[r] = (int32_t)n;
     ++r;
   };
-  if (!transposed) {
+  if (!dkdv) {
     const int nq = (N + Tq - 1) / Tq;
     for (int u = 0; u < nq; ++u) {
       mark_row();
@@ -602,15 +609,17 @@ int lg_debug_tile_walk(int N, int sink, int window, int block, int stride, int t
   int st = check_common(1, 1, 1, N, 64, sink, window, block, stride, LG_BF16);
   if (st != LG_OK) return st;
   const LgMask m = lg_make_mask(N, sink, window, block, stride);
-  const int Tq = transposed ? LG_BF16_BTQ : LG_BF16_TQ, Tk = transposed ? LG_BF16_BTK : LG_BF16_TK;
-  const int nrows = transposed ? (N + Tk - 1) / Tk : (N + Tq - 1) / Tq;
+  int Tq, Tk;
+  bf16_tiles(transposed, &Tq, &Tk);
+  const bool dkdv = (transposed & 1) != 0;
+  const int nrows = dkdv ? (N + Tk - 1) / Tk : (N + Tq - 1) / Tq;
   if (row < 0 || row >= nrows) return LG_ERR_INVALID_ARG;
   size_t n = 0;
   auto emit = [&](int t) {
     if (order && n < cap) order[n] = t;
     ++n;
   };
-  if (!transposed) {
+  if (!dkdv) {
     const int q0 = row * Tq, q1 = (q0 + Tq - 1 < N - 1) ? q0 + Tq - 1 : N - 1;
     const LgQSched qs = lg_qsched_init(m, q0, q1);
     if (m.stride == 0) {  // patterns without strided columns: the rotated walk
@@ -623,14 +632,15 @@ int lg_debug_tile_walk(int N, int sink, int window, int block, int stride, int t
     const int k0 = row * Tk, k1 = (k0 + Tk - 1 < N - 1) ? k0 + Tk - 1 : N - 1;
     int lo, hi;
     lg_qtile_range(m, k0, k1, Tq, &lo, &hi);
-    const int hw = lg_qtile_window_hi(m, k1, Tq);  // window part [lo, hw], walked rotated
+    // window part [lo, hw], walked rotated (all of them where no column parts are split off)
+    const int hw = lg_bwd_bf16_splits_columns(m, Tk == LG_BF16_BTK ? 128 : 64) ? lg_qtile_window_hi(m, k1, Tq) : hi;
     const int len = hw - lo + 1;
     int u = lo + (len - lo % len) % len;
     for (int x = 0; x < len; ++x) {
       emit(u);
       u = (u == hw) ? lo : u + 1;
     }
-    for (int c = hw + 1; c <= hi; ++c) emit(c);  // column part (its own workgroups, or the same one)
+    for (int c = hw + 1; c <= hi; ++c) emit(c);  // column part (its own workgroups)
   }
   *count = n;
   return LG_OK;

@@ -44,7 +44,7 @@
 namespace {
 
 // Keys of a dk/dv workgroup.
-constexpr int btk_of(int D) { return D == 128 ? LG_BF16_BTK : 128; }
+constexpr int btk_of(int D) { return D == 128 ? LG_BF16_BTK : LG_BF16_BTK64; }
 
 constexpr float LOG2E = 1.44269504088896340736f;
 
@@ -154,7 +154,7 @@ dq_bf16_kernel(
   using T = LgSwzTile<D>;
   constexpr int NT = 256;
   using Dma = LgDma<D, NT>;
-  constexpr int TQ = 128, TK = LG_BF16_TK;
+  constexpr int TQ = LG_BF16_TQ32, TK = LG_BF16_TK;
   static_assert(LG_BF16_TQ == 2 * TQ && TK == 64, "4 waves x 32 query rows, 64-key tiles");
   constexpr int DC = D / 16, DB = D / 32;
   constexpr int STAGE = 2 * T::BYTES;  // K tile + V tile
@@ -2175,6 +2175,8 @@ size_t lg_bwd_bf16_workspace_bytes(const LgShape& sh, const LgMask& m) {
   const BwdLaunch a = batch_launch(sh, m);
   return bwd_layout(a.size, sh.B, sh.Hq, sh.Hkv, sh.D, a.cut).end;
 }
+
+bool lg_bwd_bf16_splits_columns(const LgMask& m, int D) { return columns_of(m, D).ncol > 0; }
 
 size_t lg_bwd_bf16_pack_workspace_bytes(const LgShape& sh, const LgMask& tmpl, const int* cu_seqlens, int num_seqs,
                                         size_t least) {

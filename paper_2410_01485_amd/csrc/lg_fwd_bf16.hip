@@ -25,9 +25,9 @@
 
 namespace {
 
-constexpr int TK = LG_BF16_TK;  // 64 keys per step
-constexpr int TQ = 128;         // query rows per workgroup
-constexpr int NT = TQ * 2;      // threads: one wave per 32 rows
+constexpr int TK = LG_BF16_TK;    // 64 keys per step
+constexpr int TQ = LG_BF16_TQ32;  // 128 query rows per workgroup
+constexpr int NT = TQ * 2;        // threads: one wave per 32 rows
 // Waves per SIMD, and LDS operands of the two products requested ahead of the matrix instruction that uses them, as the
 // registers of so many waves allow (168 for D = 128, 128 for D = 64)
 template <int D>

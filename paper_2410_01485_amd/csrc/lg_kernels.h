@@ -15,8 +15,10 @@
 enum {
   LG_F32_TQ = 64, LG_F32_TK = 64,        // float32 kernels, forward / dq order
   LG_F32_BTQ = 64, LG_F32_BTK = 64,      // float32 dk/dv kernel (key-tile major)
-  LG_BF16_TQ = 256, LG_BF16_TK = 64,     // bf16 MFMA dq kernels (the forward: 128 rows, same schedule)
-  LG_BF16_BTQ = 64, LG_BF16_BTK = 256    // bf16 MFMA dk/dv kernel (key-tile major)
+  LG_BF16_TQ = 256, LG_BF16_TK = 64,     // bf16 dq kernel with 64 rows per wave
+  LG_BF16_TQ32 = 128,                    // bf16 forward, dq kernel with 32 rows per wave (64 keys per step as well)
+  LG_BF16_BTQ = 64, LG_BF16_BTK = 256,   // bf16 dk/dv kernels (key-tile major), head dim 128
+  LG_BF16_BTK64 = 128                    // ... head dim 64
 };
 
 struct LgShape {
@@ -47,6 +49,8 @@ hipError_t lg_launch_fwd_bf16_pack(const void* q, const void* k, const void* v, 
 
 size_t lg_bwd_workspace_bytes(const LgShape& sh, const LgMask& m, int dtype);
 size_t lg_bwd_bf16_workspace_bytes(const LgShape& sh, const LgMask& m);
+// Are the column keys of the pattern's key tiles split off (walked by workgroups of their own)?
+bool lg_bwd_bf16_splits_columns(const LgMask& m, int D);
 // For the packed launch below; least: the most that any of its sequences needs by itself, with which it runs as well.
 size_t lg_bwd_bf16_pack_workspace_bytes(const LgShape& sh, const LgMask& tmpl, const int* cu_seqlens, int num_seqs,
                                         size_t least);

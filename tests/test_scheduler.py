@@ -28,7 +28,7 @@ def brute_tiles(mask, Tq, Tk, transposed):
 
 def check(N, sink, window, block, stride, dtype, transposed):
     tq, tk, rp, ci, kd = lg.lg_debug_tile_map(N, sink, window, block, stride, dtype, transposed)
-    want = brute_tiles(O.mask(N, sink, window, block, stride), tq, tk, transposed)
+    want = brute_tiles(O.mask(N, sink, window, block, stride), tq, tk, transposed & 1)
     assert len(rp) == len(want) + 1
     got = [[(int(ci[x]), int(kd[x])) for x in range(rp[r], rp[r + 1])] for r in range(len(want))]
     assert got == want, (N, sink, window, block, stride, dtype, transposed)
@@ -60,6 +60,26 @@ def test_tile_map_randomised():
         stride = int(rng.choice([0, 0, 1, 2, 3, 8, 50]))
         for tr in (0, 1):
             check(N, sink, window, b, stride, int(rng.integers(0, 2)), tr)
+
+
+def test_views_have_the_tiles_of_the_kernels():
+    """The bf16 kernels run in four tile shapes (sizes from the header that the kernels compile), float32 in one."""
+    for view, want in ((0, (256, 64)), (1, (64, 256)), (2, (128, 64)), (3, (64, 128))):
+        assert lg.lg_debug_tile_map(1000, 16, 128, 1, 0, lg.LG_BF16, view)[:2] == want
+        assert lg.lg_debug_tile_map(1000, 16, 128, 1, 0, lg.LG_F32, view)[:2] == (64, 64)
+
+
+@pytest.mark.parametrize("view", [2, 3])
+def test_smaller_tiles_equal_brute_force(view):
+    """The forward, the dq kernel with 32 rows per wave and dk/dv at head dim 64: the tile map against brute force, the
+    walk a permutation of its row."""
+    for c in CASES:
+        check(*c, lg.LG_BF16, view)
+    for c in CASES + [(5000, 64, 1000, 1, 0), (4000, 0, 64, 64, 4)]:
+        tq, tk, rp, ci, kd = lg.lg_debug_tile_map(*c, lg.LG_BF16, view)
+        for r in range(len(rp) - 1):
+            order = lg.lg_debug_tile_walk(*c, view, r)
+            assert sorted(order.tolist()) == ci[rp[r]:rp[r + 1]].tolist(), (c, r)
 
 
 def test_live_tile_totals_of_benchmark_configs():
@@ -100,6 +120,19 @@ def test_walk_order_visits_exactly_the_rows_tiles(N, sink, window, block, stride
     for r in range(len(rp) - 1):
         order = lg.lg_debug_tile_walk(N, sink, window, block, stride, transposed, r)
         assert sorted(order.tolist()) == ci[rp[r]:rp[r + 1]].tolist(), (r, order[:8])
+
+
+def test_short_lone_column_part_is_walked_with_its_key_tile():
+    """One strided column (block 7 of 64 tokens) in 900 tokens.  With a window of 3 blocks fewer than six query tiles come
+    after the window part: not split off, the key tile walks all of them as one rotated run.  With a window of 1 block
+    the column part follows the window part."""
+    for view, row, lo in ((1, 1, 4), (3, 3, 6)):
+        got = lg.lg_debug_tile_walk(900, 0, 192, 64, 8, view, row).tolist()
+        n = 14 - lo + 1
+        start = lo + (n - lo % n) % n
+        assert got == list(range(start, 15)) + list(range(lo, start))
+        got = lg.lg_debug_tile_walk(900, 0, 64, 64, 8, view, row).tolist()
+        assert got[-7:] == list(range(8, 15)) and sorted(got) == list(range(lo, 15))
 
 
 def test_rotated_walks_align_neighbours():
