@@ -3,8 +3,9 @@
 Tensors are torch tensors on a HIP device (contiguous, dense layouts of
 include/longgen_attn.h); their data pointers and the current stream are handed to the
 library.  The calls a program makes per step go through the extension module _lg_bind
-(csrc/lg_bind.cpp), sizes and host-only views through ctypes.  Nothing here computes: a missing or
-unbuilt library is an error, never a fallback.
+(csrc/lg_bind.cpp), or where it is not built for this interpreter through binding_ctypes.py, which
+takes the host a few microseconds longer; sizes and host-only views through ctypes.  Nothing here computes:
+a missing or unbuilt library is an error, never a fallback.
 """
 import ctypes
 import os
@@ -99,17 +100,31 @@ _ENTRIES = ("lg_sparse_attn_fwd", "lg_sparse_attn_bwd", "lg_sparse_attn_fwd_varl
 
 
 def _load_native():
-    """The extension module, told where the loaded library's entry points are."""
+    """The extension module (of the loaded library's folder, else of this one), told where the library's entry points
+    are; binding_ctypes if it is not there or this torch does not load it."""
     global _native
+    import importlib.util
+    import warnings
+
     import torch
+
+    from .build import BIND_NAME
     L = lib()
+    for folder in (os.path.dirname(os.path.abspath(_LIB_PATH)), _HERE):
+        path = os.path.join(folder, BIND_NAME)
+        if os.path.exists(path):
+            break
     try:
-        from . import _lg_bind
-    except ImportError as e:
-        raise RuntimeError("_lg_bind is not built: run `python -m paper_2410_01485_amd.build`") from e
-    _lg_bind.setup({n: ctypes.cast(getattr(L, n), _vp).value for n in _ENTRIES}, torch._C._cuda_getCurrentRawStream)
-    _native = _lg_bind
-    return _lg_bind
+        spec = importlib.util.spec_from_file_location("_lg_bind", path)
+        mod = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(mod)
+        mod.setup({n: ctypes.cast(getattr(L, n), _vp).value for n in _ENTRIES}, torch._C._cuda_getCurrentRawStream)
+    except (ImportError, FileNotFoundError) as e:
+        warnings.warn("%s does not load (%s): calls go through ctypes; run `python -m paper_2410_01485_amd.build`"
+                      % (path, e), RuntimeWarning)
+        from . import binding_ctypes as mod
+    _native = mod
+    return mod
 
 
 def status_str(status):
@@ -137,6 +152,9 @@ def _stream(t):
 def _check(t, *shape, like=None, dtype=None):
     """t must be a contiguous device tensor of this shape; like / dtype: of that tensor's / that element type
     (the library reads every buffer of a call with the one dtype code it is given)."""
+    import torch
+    if not isinstance(t, torch.Tensor):
+        raise TypeError("expected a torch tensor, got %s" % type(t).__name__)
     if not t.is_cuda or not t.is_contiguous() or tuple(t.shape) != tuple(shape):
         raise ValueError("expected a contiguous device tensor of shape %s, got %s" % (shape, tuple(t.shape)))
     want = like.dtype if like is not None else dtype

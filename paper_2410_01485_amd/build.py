@@ -1,5 +1,6 @@
 """Build liblonggen_attn.so from csrc/*.hip with hipcc for gfx950 (cross-compiles without a GPU) and the extension
-module _lg_bind.so, the tensor side of the binding, from csrc/lg_bind.cpp with g++.
+module _lg_bind, the tensor side of the binding, from csrc/lg_bind.cpp with the C++ compiler that hipcc drives (it needs
+the headers of Python and torch; without the module the binding goes through ctypes).
 
     python -m paper_2410_01485_amd.build
 """
@@ -7,12 +8,16 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblonggen_attn.so")
-BIND = os.path.join(HERE, "_lg_bind.so")
+# (the interpreter's tag in the name: another one's build is not found instead of being loaded)
+BIND_NAME = "_lg_bind" + sysconfig.get_config_var("EXT_SUFFIX")
+BIND_SRC = os.path.join(CSRC, "lg_bind.cpp")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+CXX = os.path.join(os.path.dirname(HIPCC), "..", "lib", "llvm", "bin", "clang++")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          # packed-fp32 instructions are kept out of the generated code on purpose
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -28,34 +33,42 @@ def sources():
 SAN_COMPILE = ["-O1", "-g", "-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined",
                "-Xarch_host", "-fno-sanitize-recover=undefined"]
 SAN_LINK = ["-fno-gpu-sanitize", "-fsanitize=address", "-fsanitize=undefined", "-shared-libsan"]
+# (no check of dynamic types: it would need the type information of torch's own libraries)
+SAN_BIND = ["-O1", "-g", "-fsanitize=address", "-fsanitize=undefined", "-fno-sanitize=vptr",
+            "-fno-sanitize-recover=undefined", "-shared-libsan"]
 
 
-def start_bind():
+def start_bind(out, sanitize=False):
     """Start compiling the extension module (host code only; torch's C++ headers, no library of ours linked)."""
-    import sysconfig
     import torch
     from torch.utils import cpp_extension
-    tmp = BIND + ".tmp%d" % os.getpid()
-    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
-           os.path.join(CSRC, "lg_bind.cpp"), "-o", tmp, "-I", sysconfig.get_paths()["include"]]
+    cmd = [CXX if os.path.exists(CXX) else "g++"] + (SAN_BIND if sanitize else ["-O2"])
+    cmd += ["-std=c++17", "-fPIC", "-shared", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+            BIND_SRC, "-o", out, "-I", sysconfig.get_paths()["include"]]
     for d in cpp_extension.include_paths():
         cmd += ["-isystem", d]
     for d in cpp_extension.library_paths():
         cmd += ["-L", d]
     cmd += ["-ltorch_python", "-ltorch_cpu", "-lc10"]
-    return tmp, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    return subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
 
 
 def build(verbose=True, jobs=8, sanitize_host=False, out=None):
-    """Compile every translation unit (in parallel) and link the shared library.
+    """Compile every translation unit (in parallel) and link the shared library; the extension module next to it.
 
-    sanitize_host: build a second library (path `out`) whose HOST code runs under ASan + UBSan; a process
-    that loads it must have the clang ASan runtime preloaded (tests/test_sanitized_host.py does that)."""
+    sanitize_host: build a second library (path `out`) whose HOST code, and the module's, runs under ASan + UBSan; a
+    process that loads it must have the clang ASan runtime preloaded (tests/test_sanitized_host.py does that).
+    If only the module fails, the library is in place before this raises."""
     lib = out or LIB
     objdir = os.path.join(HERE, "_build_san" if sanitize_host else "_build")
     os.makedirs(objdir, exist_ok=True)
     flags = FLAGS + (SAN_COMPILE if sanitize_host else [])
-    bind = None if sanitize_host else start_bind()
+    bind = os.path.join(os.path.dirname(os.path.abspath(lib)), BIND_NAME)
+    bind_tmp = bind + ".tmp%d" % os.getpid()
+    try:
+        bind_proc, bind_out = start_bind(bind_tmp, sanitize_host), ""
+    except (ImportError, OSError) as e:  # no torch, no compiler
+        bind_proc, bind_out = None, str(e)
     procs = []
     objs = []
     for src in sources():
@@ -76,13 +89,8 @@ def build(verbose=True, jobs=8, sanitize_host=False, out=None):
             print("FAILED: %s\n%s" % (src, out), file=sys.stderr)
         elif verbose and out.strip():
             print(out)
-    if bind is not None:
-        out = bind[1].communicate()[0].decode()
-        if bind[1].returncode != 0:
-            failed = True
-            print("FAILED: lg_bind.cpp\n%s" % out, file=sys.stderr)
-        else:
-            os.replace(bind[0], BIND)
+    if bind_proc is not None:
+        bind_out = bind_proc.communicate()[0].decode()
     if failed:
         raise RuntimeError("compilation failed")
     tmp = lib + ".tmp%d" % os.getpid()
@@ -91,6 +99,9 @@ def build(verbose=True, jobs=8, sanitize_host=False, out=None):
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
     os.replace(tmp, lib)
+    if bind_proc is None or bind_proc.returncode != 0:
+        raise RuntimeError("%s is built, the extension module is not (calls go through ctypes):\n%s" % (lib, bind_out))
+    os.replace(bind_tmp, bind)
     return lib
 
 

@@ -1,9 +1,10 @@
 """The host-side code under AddressSanitizer + UndefinedBehaviorSanitizer (CPU only).
 
-Builds a copy of the fp64 oracle (oracle/lg_oracle.c) and a copy of liblonggen_attn.so whose HOST code
+Builds a copy of the fp64 oracle (oracle/lg_oracle.c), a copy of liblonggen_attn.so whose HOST code
 (argument checks, the host build of the tile scheduler and cache geometry in csrc/lg_mask.h, launch set-up)
-are compiled with -fsanitize=address,undefined, then runs the mask / scheduler / cache pins and the host ABI
-checks against those copies in a child process with the sanitizer runtime preloaded.  Any report (out-of-bounds
+and a copy of the extension module (csrc/lg_bind.cpp) compiled with -fsanitize=address,undefined, then runs the
+mask / scheduler / cache pins, the host ABI checks and the binding's against those copies in a child process with
+the sanitizer runtime preloaded.  Any report (out-of-bounds
 access, use after free, signed overflow, invalid shift, misaligned access ...) aborts the child."""
 import glob
 import os
@@ -15,7 +16,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CLANG = "/opt/rocm/lib/llvm/bin/clang"
 PINS = ["tests/test_oracle_mask.py", "tests/test_oracle_cache.py", "tests/test_scheduler.py",
-        "tests/test_cache_host.py", "tests/test_host_abi.py"]
+        "tests/test_cache_host.py", "tests/test_host_abi.py", "tests/test_binding.py::test_same_errors"]
 
 
 def asan_runtime():
@@ -46,3 +47,5 @@ def test_pins_pass_with_sanitized_host_code(tmp_path):
     assert r.returncode == 0, tail
     assert "runtime error" not in r.stdout and "AddressSanitizer" not in r.stdout, tail
     assert " passed" in tail
+    # the module that the binding's tests used is the one beside the library
+    assert os.path.exists(os.path.join(str(tmp_path), lg_build.BIND_NAME))
