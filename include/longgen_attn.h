@@ -140,11 +140,12 @@ int lg_sparse_attn_bwd(const void* q, const void* k, const void* v, const void* 
  * Measurement aid (benchmarks only): lg_sparse_attn_bwd with each of its three kernels
  * bracketed by HIP events on hip_stream.  Synchronises the stream and writes the kernel
  * durations in milliseconds to the HOST array kernel_ms[3] = {set-up, dq, dk/dv}:
- *   set-up  bf16 path: the kernel that clears the work-queue counters (a few microseconds); float32
- *           path: nothing (on both paths Delta is formed inside the dq kernel)
+ *   set-up  bf16 path: the kernel that clears the work-queue counters and the partial sums and writes the
+ *           column tables (a few microseconds); float32 path: nothing (on both paths Delta is formed inside the
+ *           dq kernel)
  *   dq      the dq kernel
- *   dk/dv   the dk/dv kernel and, for strided patterns and GQA, what precedes it: the column-table
- *           kernel, the clearing of the partial sums and the column instance
+ *   dk/dv   the dk/dv kernel with the kernels of the split-off column parts before it and, where window parts are
+ *           cut, the one that adds the parts after it
  * Creates and destroys its events; results are those of lg_sparse_attn_bwd.
  */
 int lg_debug_bwd_kernel_ms(const void* q, const void* k, const void* v, const void* out, const float* lse,
@@ -172,10 +173,11 @@ int lg_debug_bwd_kernel_ms(const void* q, const void* k, const void* v, const vo
  * with atomics).
  * Empty sequences are allowed and skipped; when all are empty nothing is enqueued.
  * No work is spent on padding.  The bf16 forward puts up to 128 sequences into one launch (every
- * (sequence, head, 256-row query tile) is a workgroup of the same grid, so short sequences fill the GPU
- * together; each sequence's pattern is cut to its length on the device).  The float32 forward and the
- * backward enqueue one set of launches per sequence, in order, each at the sequence's own length: there
- * the launches of short sequences (under ~64K query rows x heads) do not fill the GPU.
+ * (sequence, head, 128-row query tile) is a workgroup of the same grid, so short sequences fill the GPU
+ * together; each sequence's pattern is cut to its length on the device), the bf16 backward up to 128 into one
+ * set of launches, as far as the workspace has room for them.  The float32 calls enqueue one set of launches
+ * per sequence, in order, each at the sequence's own length: there the launches of short sequences (under
+ * ~64K query rows x heads) do not fill the GPU.
  * The backward workspace is shared by the sequences (the remarks on lg_sparse_attn_bwd's workspace apply).  A call
  * needs no more than the largest of its sequences needs by itself (lg_sparse_attn_bwd_workspace_bytes with B = 1);
  * only less is refused.  On the bf16 path as many sequences as fit it run side by side, up to 128 in a set of

@@ -198,7 +198,7 @@ def lg_sparse_attn_bwd(q, k, v, out, lse, dout, dq, dk, dv, workspace, sink, win
 
 def lg_debug_bwd_kernel_ms(q, k, v, out, lse, dout, dq, dk, dv, workspace, sink, window, block=1, stride=0,
                            scale=0.0):
-    """lg_sparse_attn_bwd with per-kernel HIP-event timing: returns [delta_ms, dq_ms, dkdv_ms]."""
+    """lg_sparse_attn_bwd with per-kernel HIP-event timing: returns [set-up ms, dq ms, dk/dv ms]."""
     B, Hq, N, D = q.shape
     Hkv = k.shape[1]
     ms = (_f * 3)()

@@ -324,8 +324,8 @@ dq_bf16_kernel(
 // The query range of a key tile therefore has a dense window part (like every tile) and, if it
 // holds column keys, a long column part: all later rows, but only its column keys live.
 // The column parts are split off.  Where there are several column groups of 64 keys (strided patterns), the COLUMN
-// instance of the kernel packs them four at a time into virtual 256-key tiles, so that all 8 waves have live keys and
-// a Q / dO tile is used by 256 keys again, cuts their query range into chunks that run as separate workgroups, and adds
+// instance of the kernel packs them into virtual tiles of the kernel's own size (four groups at head dim 128, two at
+// 64), so that all waves have live keys and a Q / dO tile is used by as many keys again, cuts their query range into chunks that run as separate workgroups, and adds
 // float32 sums into the workspace with hardware atomics (their order is not fixed, so the last bits of dk/dv of column
 // keys can differ from run to run).  A lone group (the sink of a sink + window pattern) has a kernel of its own
 // (dkdv_lone_bf16_kernel), without atomics where Hq == Hkv.  The main instance then handles the window part of every
@@ -1069,10 +1069,10 @@ __device__ __forceinline__ int lg_queue_take(int* __restrict__ queue, int nitems
 // matrix instructions of a function, so the instructions are written out with their register
 // classes here; that leaves their dependency waits, which the compiler otherwise provides, to
 // this code (see the notes at lg_tie and in the step).
-// COLUMN: the instance for the split-off column parts, as in the 8-wave kernel: a virtual tile of
+// COLUMN: the instance for the split-off column parts, as in the 32-keys-per-wave kernel: a virtual tile of
 // four 64-key column groups, one group per wave, one chunk of the query range per workgroup,
 // float32 atomics into the partial sums.
-// bid: the work item, numbered like the block ids of the 8-wave kernel's grid.
+// bid: the work item, numbered like the block ids of the 32-keys-per-wave kernel's grid.
 template <bool TOKEN, bool COLUMN>
 __device__ __forceinline__ void dkdv_wide_item(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
@@ -1483,12 +1483,12 @@ __global__ __launch_bounds__(256) void dkdv_wide_bf16_kernel_q(
 
 // ------------------------------------------------- dq: 64 query rows per wave (D = 128)
 // Same idea as the wide dk/dv kernel: four waves of 64 query rows, so that every K / V operand
-// read from LDS feeds two matrix instructions; same tile walk as the 8-wave kernel, the 4-stage ring
+// read from LDS feeds two matrix instructions; same tile walk as the 32-rows-per-wave kernel, a 4-stage ring
 // used as two pairs of tiles with one barrier per pair.  The AGPR half of the register file holds the dq
 // accumulators (blocks 0..7 = a[0:127]: row block rb, dim block db -> block 4 rb + db) and the
 // wave's Q and dO fragments (a[128:255], four registers per 32 rows x 16 dims), which the matrix
 // instructions read as their second operand straight from there.
-// bid: the work item, numbered like the block ids of the 8-wave kernel's grid.
+// bid: the work item, numbered like the block ids of the 32-rows-per-wave kernel's grid.
 template <bool TOKEN>
 __device__ __forceinline__ void dq_wide_item(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,

@@ -141,7 +141,7 @@ __device__ __forceinline__ bool lg_dec_part(const LgDecWork& wk, const LgPaged& 
   const int chunk = max(wk.chunk, 128 * __builtin_amdgcn_readfirstlane((int)ceilf(all / (128.f * target))));
   // Rows are cut evenly.  What is left over goes to the others where the reads decide, up to a quarter of a part, and to a
   // row's only part always (no sum over parts then): a part of a few keys costs a workgroup's place for nothing (48
-  // sequences of 20 .. 32768 tokens, 8 kv heads: 73.4 -> 70.8 us; 24 x 32 heads of 64: 96 -> 89 us).
+  // sequences of 20 .. 32768 tokens, 8 kv heads, with the append: 75.7 -> 71.3 us).
   const int spare = all > DEC_MANY_KEYS ? chunk >> 2 : 0;
   auto nparts = [&](int k) { return k <= chunk + (chunk >> 2) ? 1 : (k - spare + chunk - 1) / chunk; };
   const int w = blockIdx.x;
@@ -237,8 +237,8 @@ __device__ __forceinline__ size_t lg_dec_page_row(const LgPaged& pg, int b, int 
 // K, V and Q are used as stored, sums are float32.  V goes past the caches (every byte is used once); K is read in
 // half lines by two loads each, so it does not (both non-temporal: 94 instead of 86 us at 545 MB).  Bound: memory; per
 // 16 KB (D = 128) a wave spends 512 matrix and about 600 vector cycles, several times less than the bytes take.
-// Measured (vector kernel -> this): 16 x 32 heads x 4160 slots 162 -> 159 us (6.9 TB/s); 8 x 8 kv heads of 8 query heads x 3648
-// slots 101 -> 26 us; 48 sequences of 20 .. 32768 tokens, 8 kv heads of 4 query heads, paged 109 -> 77 us.
+// Measured with the append (vector kernel -> this): 16 x 32 heads x 4160 slots 164 -> 161 us (6.8 TB/s); 8 x 8 kv heads of
+// 8 query heads x 3648 slots 102 -> 26 us; 48 sequences of 20 .. 32768 tokens, 8 kv heads of 4 query heads, paged 112 -> 71.
 // float32: units of 16 keys (as many bytes) on 16x16x4 float32 instructions: lane (n, h) loads dims 16 c + 4 h .. of key
 // row n (contraction step (c, e): its element e; the four lane groups together dims 16 c + e, + 4, + 8, + 12), register r
 // of S is key 4 h + r, which is the B operand of the second product's step r as it is; a lane loads dims 4 n .. (+ 64) of

@@ -117,7 +117,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
 
   auto issue_k = [&](int t, int buf) { dma.issue(kh + (size_t)t * TK * D, N - t * TK, lds0 + buf * T::BYTES); };
   auto issue_v = [&](int t) { dma.issue(vh + (size_t)t * TK * D, N - t * TK, lds0 + 2 * T::BYTES); };
-  // ring: tiles are issued up to 3 ahead of the one being computed
+  // K tiles are requested up to two ahead of the one being computed, its own V tile behind the barrier that opens it
   const LgQSched qs = lg_qsched_init(m, q0, q1);
   // patterns without strided columns walk the window run rotated (L2 sharing between neighbours)
   const LgQWalk qw = lg_qwalk_init(qs);

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("window,stride", [
-    (128, 4),     # short window: the 8-wave backward kernels; column parts
+    (128, 4),     # short window: the 32-rows-per-wave backward kernels; column parts
     (1024, 8),    # long window at head dim 128: the 64-rows-per-wave backward kernels; column parts
 ])
 def test_graph_replay_matches_eager(window, stride):

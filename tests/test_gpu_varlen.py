@@ -179,8 +179,8 @@ def test_many_short_sequences_in_shared_launches(D, sink, window, block, stride)
 
 def test_long_sequences_take_the_resident_kernels():
     """Head dim 128, window 4096: the sequences of 5000 and 9000 tokens run the 64-rows-per-wave backward
-    kernels (one resident workgroup per CU, work queue in the shared workspace, cleared per sequence), the
-    700-token one in between the same instances at a short length.  No GQA, no stride: everything is
+    kernels (one resident workgroup per CU, work queue in the shared workspace) side by side, the
+    700-token one the 32-rows-per-wave ones.  No GQA, no stride: everything is
     bit-reproducible, so the whole pack must equal the fixed-length calls bit for bit; forward rows of the
     long sequences are sampled against the oracle, the short one is compared in full."""
     check_pack([5000, 700, 9000], 2, 2, 128, 64, 4096, 1, 0, torch.bfloat16, 403, oracle_rows=2000)
