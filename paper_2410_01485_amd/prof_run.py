@@ -1,7 +1,7 @@
 """Run one entry point on one benchmark workload a few times, for rocprofv3.
 
     rocprofv3 --kernel-trace --stats --output-format csv -d OUT -o NAME -- \
-        python3 paper_2410_01485_amd/prof_run.py {fwd|bwd|bwd_strided|decode|fwd_strided|fwd_gqa|copy} [reps]
+        python3 paper_2410_01485_amd/prof_run.py {fwd|bwd|bwd_strided|decode|fwd_strided|fwd_gqa|copy|product} [reps]
 
 fwd / bwd   : B1 H32 D128 N131072 bf16, sink 64 + window 4096 (the training-step workload)
 bwd_strided : B1 H32 D128 N131072 bf16, 64-token blocks: sink block, window 2048, every 64th block
@@ -10,6 +10,8 @@ fwd_gqa     : B1 Hq64/Hkv8 D128 N131072 bf16, sink 64 + window 4096
 decode      : B16 H32 D128 bf16, 64 + 4096 cache slots, three rotating cache sets
 copy        : a plain elementwise pass over 1 GiB (reads 2^30 bytes, writes 2^30 bytes): the yardstick
               that FETCH_SIZE / WRITE_SIZE counter readings are scaled by
+product     : torch's product of two 8192 x 8192 matrices, bf16 and float32: the rates that a large library
+              product reaches on the card
 Inputs are filled on the device (values do not matter to a profile).
 """
 import os
@@ -36,6 +38,12 @@ def main():
         b = torch.empty_like(a)
         for _ in range(reps):
             torch.add(a, 1.0, out=b)   # an elementwise kernel: reads 2^30 bytes, writes 2^30 bytes
+    elif what == "product":
+        for dtype in (bf, torch.float32):
+            a, b = rnd(8192, 8192).to(dtype), rnd(8192, 8192).to(dtype)
+            c = torch.empty_like(a)
+            for _ in range(reps):
+                torch.mm(a, b, out=c)
     elif what in ("fwd", "bwd", "bwd_strided", "fwd_strided", "fwd_gqa"):
         Hq, Hkv, N, sink, window, block, stride = 32, 32, 131072, 64, 4096, 1, 0
         if what == "fwd_strided":
