@@ -73,9 +73,10 @@ struct LgPaged {
 };
 
 enum { LG_DEC_PLAIN = 0, LG_DEC_SEGS = 1, LG_DEC_PAGED = 2 };
-// What an instance receives beyond the common arguments, and no more: a launch with 250 bytes of arguments takes the host
-// about 0.5 us longer than one with 100, and a short step waits for the host (1 sequence of 32/8 heads, 1500 tokens 12.1 ->
-// 11.8 us; 48 paged sequences 77.2 -> 71.1, whose workgroups start with fewer scalar loads).
+// What an instance receives beyond the common arguments, and no more: a launch with 260 bytes of arguments takes the host
+// 0.2 us longer than one with 12 (1 us when launches follow each other without a pause), and a short step waits for the
+// host; with nothing but its own, the paged instance also needs fewer registers' worth of scalar loads (48 sequences of
+// 20 .. 32768 tokens, 8 kv heads, with the append: 77.2 -> 71.1 us).
 template <int MODE>
 struct LgDecExtra {};
 template <>
@@ -512,7 +513,7 @@ __global__ __launch_bounds__(WAVES * 64, 3) void decode_mfma_kernel(
 // A launch of its own rather than the last of a row's workgroups to finish: nothing in the workspace is read that this
 // call has not written, and the GPU gets through it no slower (1 sequence of 32/8 heads, 1500 tokens, append and decode
 // replayed from a graph: 9.8 -> 9.1 us; 8 x 64/8 heads, 3648 slots: 27.0 -> 25.9).  A program that issues one short decode
-// after the other waits for the host's third launch (the same sequence without a graph: 10.0 -> 11.8 us).
+// after the other waits for the host's third launch (the same sequence without a graph: 10.0 -> 12 us).
 template <typename T, int D, bool PAGED>
 __global__ __launch_bounds__(64) void decode_add_kernel(LgDecWork wk, int G, T* __restrict__ out, float* __restrict__ lse) {
   constexpr int E = D / 64, AHEAD = 16;  // loads in flight
