@@ -102,6 +102,9 @@ def build(verbose=True, jobs=8, sanitize_host=False, out=None):
     if bind_proc is None or bind_proc.returncode != 0:
         raise RuntimeError("%s is built, the extension module is not (calls go through ctypes):\n%s" % (lib, bind_out))
     os.replace(bind_tmp, bind)
+    untagged = os.path.join(os.path.dirname(bind), "_lg_bind.so")  # of an earlier build
+    if os.path.exists(untagged):
+        os.remove(untagged)
     return lib
 
 

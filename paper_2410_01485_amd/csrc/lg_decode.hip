@@ -523,7 +523,7 @@ __global__ __launch_bounds__(64) void decode_add_kernel(LgDecWork wk, int G, T* 
   const float* po = wk.o + (rec * G + g) * D + E * lane;
   // (the first parts are requested before their number is known: every address is inside the workspace)
   const float mine = wk.lse2[(rec + min(lane, wk.splits - 1)) * G + g];
-  const int np = PAGED ? __builtin_amdgcn_readfirstlane(wk.parts[row]) : wk.splits;
+  const int np = PAGED ? min(__builtin_amdgcn_readfirstlane(wk.parts[row]), wk.splits) : wk.splits;
   vec_t x[AHEAD], acc = {};
   auto load = [&](int s0) {
 #pragma unroll
