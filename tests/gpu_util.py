@@ -117,6 +117,15 @@ def assert_close(got, want, tol, rel=None, what="", by_tensor_max=False, dtype=N
     return err
 
 
+def assert_same_sums(x, y, what):
+    """bf16 results of the same float32 terms added in another order: each off by half a unit in the last place (2^-9 of
+    the value) from sums that differ by float32 rounding, which is far below 1e-4 of the tensor's rms even where
+    thousands of terms cancel."""
+    x, y = x.float(), y.float()
+    bound = 2.0 ** -7 * torch.maximum(x.abs(), y.abs()) + 1e-4 * y.square().mean().sqrt()
+    assert bool(((x - y).abs() <= bound).all()), what + ": differs by more than the order of its sums"
+
+
 def check_fwd(B, Hq, Hkv, N, D, sink, window, block=1, stride=0, dtype=torch.bfloat16, seed=1, q_mul=1.0,
               scale=0.0):
     q, k, v = lg_synth.prefill_inputs(B, Hq, Hkv, N, D, seed, dtype, q_mul=q_mul)

@@ -6,7 +6,7 @@ import torch
 
 import lg_synth
 import paper_2410_01485_amd as lg
-from gpu_util import DEV
+from gpu_util import DEV, assert_same_sums
 
 pytestmark = pytest.mark.gpu
 
@@ -58,7 +58,10 @@ def test_graph_replay_matches_eager(window, stride):
         torch.cuda.synchronize()
         for name, a, b in zip(("out", "lse", "dq", "dk", "dv", "decode out", "decode lse"), got,
                               (out, lse, dq, dk, dv, o1, l1)):
-            if name in ("dk", "dv"):   # column keys are summed with float atomics: order-dependent last bits
-                assert torch.allclose(a.float(), b.float(), rtol=2e-2, atol=2e-2), (rep, name)
+            if name in ("dk", "dv"):   # column keys are summed with float atomics, in any order; the others are not
+                kb = torch.arange(N, device=DEV) // block
+                column = (torch.arange(N, device=DEV) < sink) | (kb % stride == stride - 1)
+                assert torch.equal(a[:, :, ~column], b[:, :, ~column]), (rep, name)
+                assert_same_sums(a[:, :, column], b[:, :, column], "%s, replay %d" % (name, rep))
             else:
                 assert torch.equal(a, b), (rep, name)

@@ -9,7 +9,7 @@ import torch
 
 import lg_synth
 import paper_2410_01485_amd as lg
-from gpu_util import DEV, TOL_LSE, TOL_OUT, TOL_REL, assert_close, dq_delta_allowance, f32np
+from gpu_util import DEV, TOL_LSE, TOL_OUT, TOL_REL, assert_close, assert_same_sums, dq_delta_allowance, f32np
 from oracle import lg_oracle as O
 
 pytestmark = pytest.mark.gpu
@@ -45,15 +45,6 @@ def run_varlen(packed, cu, sink, window, block, stride, scale=0.0, least_workspa
     torch.cuda.synchronize()
     assert bool((ws[-256:] == 0xa5).all()), "written past the workspace"
     return out, lse, dq, dk, dv
-
-
-def assert_same_sums(x, y, what):
-    """bf16 results of the same float32 terms added in another order: each off by half a unit in the last place (2^-9 of
-    the value) from sums that differ by float32 rounding, which is far below 1e-4 of the tensor's rms even where
-    thousands of terms cancel."""
-    x, y = x.float(), y.float()
-    bound = 2.0 ** -7 * torch.maximum(x.abs(), y.abs()) + 1e-4 * y.square().mean().sqrt()
-    assert bool(((x - y).abs() <= bound).all()), what + ": differs by more than the order of its sums"
 
 
 def run_fixed(seq, sink, window, block, stride, scale=0.0):
