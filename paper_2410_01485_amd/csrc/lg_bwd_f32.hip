@@ -35,8 +35,8 @@ template <int D>
 __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void dq_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
     const float* __restrict__ out, const float* __restrict__ dout, const float* __restrict__ lse,
-    float* __restrict__ delta, float* __restrict__ dq, int Hq, int Hkv, float scale, LgMask m, int nqt, int total,
-    int run, unsigned* __restrict__ arrived, int ncounters) {
+    float* __restrict__ delta, float* __restrict__ dq, int Hq, int Hkv, float scale, LgMask m, LgItems items,
+    unsigned* __restrict__ arrived, int ncounters) {
   using T = LgF32Tile<D>;
   using Dma = LgTileDma<T, NT>;
   constexpr int TQ = LG_F32_TQ, TK = LG_F32_TK, DC = D / 16;
@@ -45,12 +45,10 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void dq_f32_kernel(
 
   const int tid = threadIdx.x;
   for (long long x = (long long)blockIdx.x * NT + tid; x < ncounters; x += (long long)gridDim.x * NT) arrived[x] = 0u;
-  const int L = lg_item_of(blockIdx.x, run);
-  if (L >= total) return;
-  const int G = Hq / Hkv;
-  const int gq = L % G, rest = L / G;
-  const int qt = nqt - 1 - rest % nqt, bhk = rest / nqt;
-  const int b = bhk / Hkv, hk = bhk % Hkv, hq = hk * G + gq;
+  const int L = lg_item_of(blockIdx.x, items.run);
+  if (L >= items.total) return;
+  const LgItem it = lg_item(items, L);
+  const int b = it.b, hk = it.hk, hq = it.hq, qt = (int)items.nqt.d - 1 - it.x;
   const int N = m.N;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, h = lane >> 4;
@@ -550,7 +548,7 @@ hipError_t launch_bwd(const float* q, const float* k, const float* v, const floa
   }
   const int total = (int)tl, run = lg_run_length(m, total, sh.B * sh.Hkv, 4 * (sh.Hq / sh.Hkv), false);
   dq_f32_kernel<D><<<dim3((unsigned)lg_run_grid(total, run)), NT, 0, s>>>(q, k, v, out, dout, lse, delta, dq, sh.Hq, sh.Hkv, sh.scale, m,
-                                                    pt.nqt, total, run, arrived, (int)ncnt);
+                                                    lg_make_items(total, run, pt.nqt, sh.Hq, sh.Hkv), arrived, (int)ncnt);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (ev) (void)hipEventRecord(ev[2], s);

@@ -16,7 +16,12 @@
 // tile, 48 KB / 24 KB; K of tile t + 2 and V of tile t + 1 are requested as soon as tile t has left their place).
 // One workgroup of 8 waves in step (two per SIMD) with a 128 KB ring needed 30 % more cycles; 6 or 12 waves per
 // workgroup are slower as well, 6 because they do not spread evenly over four SIMDs.  Smaller workgroups also waste
-// less on short sequences.  32 heads of 128, 131072 tokens, window 4096: 9.1 -> 8.45 ms (1040 TFLOP/s, the clock now
+// less on short sequences.  Rows of few tiles are bound by what a workgroup does besides tiles, so Q and O go through LDS
+// in pieces of 1 KB (a lane's own row, 16 bytes at a time, is 32 rows per instruction: address and cache-line work of 2000
+// cycles each way) and items are found without divisions: 32 heads of 128, window 64 at 32768 tokens 216 -> 198 us (5.4
+// TB/s), 256 291 -> 265, 1024 633 -> 609; 64 x 512 tokens 300 -> 269 us; 2 x 16 heads of 64, 1003 tokens 17.2 -> 16.5.
+// (Asking for the next item's Q lines while a tile is computed, so that they wait in L2, was slower: 198 -> 207 us.)
+// 32 heads of 128, 131072 tokens, window 4096: 9.1 -> 8.45 ms (1040 TFLOP/s, the clock now
 // settles at 1.8 GHz instead of 2.2 under the power limit); 8 x 1024 tokens: 144 -> 116 us; 2 x 16 heads of 64, 1003
 // tokens: 26 -> 18 us.
 #include "lg_kernels.h"
@@ -38,8 +43,8 @@ struct LgFwdTune {
 // TOKEN: the pattern is token-granular without strided columns (block <= 1, stride 0).  The
 // mask fields that are then known let the compiler drop the block / stride arithmetic from
 // the per-tile scheduler, and partial tiles are masked with two compares per element.
-// PackT: LgNoPack for the batch layout (every (b, head) has nqt query tiles of one length), LgPack for
-// sequences of different lengths side by side in each head (nqt = all their query tiles; B = 1).
+// PackT: LgNoPack for the batch layout (every (b, head) has the same query tiles), LgPack for
+// sequences of different lengths side by side in each head (B = 1).
 struct LgNoPack {};
 template <int D, bool TOKEN, typename PackT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>::WAVES, LgFwdTune<D>::WAVES))) void fwd_bf16_kernel(const uint16_t* __restrict__ q,
@@ -47,8 +52,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
                                                       const uint16_t* __restrict__ v,
                                                       uint16_t* __restrict__ out,
                                                       float* __restrict__ lse, int Hq, int Hkv,
-                                                      float scale_log2e, LgMask m_in, int nqt,
-                                                      int total, int run, PackT pack) {
+                                                      float scale_log2e, LgMask m_in, LgItems items,
+                                                      PackT pack) {
   constexpr bool PACK = !__is_same(PackT, LgNoPack);
   LgMask m = m_in;
   if (TOKEN) {
@@ -65,16 +70,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
   constexpr int DB = D / 32;            // 32-row blocks of O^T
   __shared__ __attribute__((aligned(1024))) unsigned char smem[3 * T::BYTES];  // two K tiles, a V tile
 
-  const int L = lg_item_of(blockIdx.x, run);
-  if (L >= total) return;
-  // logical order: (b, kv head) slowest, then query tile (longest rows first), then the query
-  // heads of the GQA group: the G workgroups that walk the same K/V tiles run side by side
-  const int G = Hq / Hkv;
-  const int gq = L % G, rest = L / G;
-  int qt = nqt - 1 - (rest % nqt);
-  const int bhk = rest / nqt;
-  const int b = bhk / Hkv, hk = bhk % Hkv;
-  const int hq = hk * G + gq;
+  const int L = lg_item_of(blockIdx.x, items.run);
+  if (L >= items.total) return;
+  const LgItem it = lg_item(items, L);
+  const int b = it.b, hk = it.hk, hq = it.hq;
+  int qt = (int)items.nqt.d - 1 - it.x;
   int seq_row0 = 0;  // first row of the sequence inside its head
   if constexpr (PACK) {
     // the sequence that owns query tile qt of the launch: the last one whose first tile is <= qt
@@ -126,24 +126,25 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
     return lg_qsched_next(m, qs, prev);
   };
   int t = next_tile(-1);  // tile to compute next
-  int t1 = -1;
-  if (t >= 0) {
-    issue_k(t, 0);
-    t1 = next_tile(t);
-    if (t1 >= 0) issue_k(t1, 1);
-  }
-  // Q fragments (B operand): lane (n, g) holds dims 16*dc + 8g .. +7 of its row.
+  const int t1_first = next_tile(t);
+  issue_k(t, 0);
+  // Q fragments (B operand): lane (n, g) holds dims 16*dc + 8g .. +7 of its row.  The workgroup's rows come through the
+  // places of the second K tile and of V (loaded by each lane from its own row, an instruction touches 32 rows).
   bf16x8_t qf[DC];
-  {
-    const uint16_t* qr = q + qbase + (size_t)min(i, N - 1) * D + g * 8;
 #pragma unroll
-    for (int dc = 0; dc < DC; ++dc) qf[dc] = lg_as_bf16x8(*reinterpret_cast<const uint4*>(qr + dc * 16));
-    // Touch the fragments here so that the compiler's own wait for these loads sits before
-    // the tile ring starts: a wait placed inside the loop would also drain the direct loads
-    // that are meant to stay in flight.
-#pragma unroll
-    for (int dc = 0; dc < DC; ++dc) asm volatile("" ::"v"(qf[dc]));
+  for (int x = 0; x < 2; ++x) {
+    const int r0 = min(q0 + 64 * x, N - 1);  // (rows past the end repeat the last one)
+    dma.issue(q + qbase + (size_t)r0 * D, N - r0, lds0 + (1 + x) * T::BYTES);
   }
+  LG_WAIT_VMCNT(0);
+  __syncthreads();
+#pragma unroll
+  for (int dc = 0; dc < DC; ++dc) qf[dc] = rd.read_rows(smem, (1 + (wave_s >> 1)) * T::BYTES, wave_s & 1, dc);
+#pragma unroll
+  for (int dc = 0; dc < DC; ++dc) asm volatile("" ::"v"(qf[dc]));
+  __syncthreads();
+  int t1 = t1_first;
+  if (t1 >= 0) issue_k(t1, 1);
 
   int buf = 0;
   while (t >= 0) {
@@ -268,20 +269,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
   // ---- epilogue: normalise, write O (bf16) and LSE (natural log) ----
   const float l = lrow + lg_other_half(lrow);
   const float inv = 1.f / l;
-  if (i < N) {
-    uint16_t* orow = out + qbase + (size_t)i * D + 4 * g;
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        uint2 w;
-        w.x = lg_pack_bf16(oacc[db][4 * r4 + 0] * inv, oacc[db][4 * r4 + 1] * inv);
-        w.y = lg_pack_bf16(oacc[db][4 * r4 + 2] * inv, oacc[db][4 * r4 + 3] * inv);
-        *reinterpret_cast<uint2*>(orow + db * 32 + 8 * r4) = w;
-      }
-    if (lse != nullptr && g == 0)
-      lse[(size_t)(b * Hq + hq) * m.ld + seq_row0 + i] = (mref * scale_log2e + log2f(l)) * 0.69314718055994530942f;
-  }
+  // (the K tiles' place is free: nobody reads it behind the last tile's second barrier)
+  lg_store_rows<D>(smem + wave_s * (32 * T::ROW_BYTES), out + qbase + (size_t)(q0 + wave_s * 32) * D, N - (q0 + wave_s * 32), lane,
+                   [&](int db, int r4) {
+                     return make_uint2(lg_pack_bf16(oacc[db][4 * r4 + 0] * inv, oacc[db][4 * r4 + 1] * inv),
+                                       lg_pack_bf16(oacc[db][4 * r4 + 2] * inv, oacc[db][4 * r4 + 3] * inv));
+                   });
+  if (lse != nullptr && g == 0 && i < N)
+    lse[(size_t)(b * Hq + hq) * m.ld + seq_row0 + i] = (mref * scale_log2e + log2f(l)) * 0.69314718055994530942f;
 }
 
 }  // namespace
@@ -294,12 +289,13 @@ hipError_t lg_launch_fwd_bf16(const void* q, const void* k, const void* v, void*
   const int total = (int)total_ll;
   const int run = lg_run_length(m, total, sh.B * sh.Hkv, 16 * (sh.Hq / sh.Hkv), false);
   const float sl2 = sh.scale * 1.44269504088896340736f;
+  const LgItems items = lg_make_items(total, run, nqt, sh.Hq, sh.Hkv);
   const dim3 grid((unsigned)lg_run_grid(total, run));
   const bool token = m.b == 1 && m.stride == 0;
 #define LG_FWD_LAUNCH(DD, TT)                                                                            \
   fwd_bf16_kernel<DD, TT, LgNoPack><<<grid, NT, 0, s>>>((const uint16_t*)q, (const uint16_t*)k,          \
                                                         (const uint16_t*)v, (uint16_t*)out, lse, sh.Hq,  \
-                                                        sh.Hkv, sl2, m, nqt, total, run, LgNoPack{})
+                                                        sh.Hkv, sl2, m, items, LgNoPack{})
   if (sh.D == 64) {
     if (token) LG_FWD_LAUNCH(64, true);
     else LG_FWD_LAUNCH(64, false);
@@ -330,12 +326,13 @@ hipError_t lg_launch_fwd_bf16_pack(const void* q, const void* k, const void* v, 
   const int total = (int)total_ll;
   const int run = lg_run_length(tmpl, total, sh.Hkv, 16 * (sh.Hq / sh.Hkv), true);
   const float sl2 = sh.scale * 1.44269504088896340736f;
+  const LgItems items = lg_make_items(total, run, nqt, sh.Hq, sh.Hkv);
   const dim3 grid((unsigned)lg_run_grid(total, run));
   const bool token = tmpl.b == 1 && tmpl.stride == 0;
 #define LG_FWD_LAUNCH(DD, TT)                                                                          \
   fwd_bf16_kernel<DD, TT, LgPack><<<grid, NT, 0, s>>>((const uint16_t*)q, (const uint16_t*)k,          \
                                                       (const uint16_t*)v, (uint16_t*)out, lse, sh.Hq,  \
-                                                      sh.Hkv, sl2, tmpl, nqt, total, run, pack)
+                                                      sh.Hkv, sl2, tmpl, items, pack)
   if (sh.D == 64) {
     if (token) LG_FWD_LAUNCH(64, true);
     else LG_FWD_LAUNCH(64, false);

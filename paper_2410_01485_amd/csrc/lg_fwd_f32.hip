@@ -26,20 +26,17 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_f32_kernel(const floa
                                                                       const float* __restrict__ v,
                                                                       float* __restrict__ out,
                                                                       float* __restrict__ lse, int Hq, int Hkv,
-                                                                      float scale, LgMask m, int nqt, int total,
-                                                                      int run) {
+                                                                      float scale, LgMask m, LgItems items) {
   using T = LgF32Tile<D>;
   using Dma = LgTileDma<T, NT>;
   constexpr int DC = D / 16;
   constexpr int STAGE = 2 * T::BYTES, LPT = 2 * Dma::CH;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * STAGE];
 
-  const int L = lg_item_of(blockIdx.x, run);
-  if (L >= total) return;
-  const int G = Hq / Hkv;
-  const int gq = L % G, rest = L / G;
-  const int qt = nqt - 1 - rest % nqt, bhk = rest / nqt;
-  const int b = bhk / Hkv, hk = bhk % Hkv, hq = hk * G + gq;
+  const int L = lg_item_of(blockIdx.x, items.run);
+  if (L >= items.total) return;
+  const LgItem it = lg_item(items, L);
+  const int b = it.b, hk = it.hk, hq = it.hq, qt = (int)items.nqt.d - 1 - it.x;
   const int N = m.N;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, h = lane >> 4;
@@ -207,10 +204,11 @@ hipError_t lg_launch_fwd_f32(const float* q, const float* k, const float* v, flo
   const long long tl = (long long)nqt * sh.Hq * sh.B;
   if (tl > 0x7fffffffLL - 8) return hipErrorInvalidValue;
   const int total = (int)tl, run = lg_run_length(m, total, sh.B * sh.Hkv, 4 * (sh.Hq / sh.Hkv), false);
+  const LgItems items = lg_make_items(total, run, nqt, sh.Hq, sh.Hkv);
   const dim3 grid((unsigned)lg_run_grid(total, run));
   if (sh.D == 64)
-    fwd_f32_kernel<64><<<grid, NT, 0, s>>>(q, k, v, out, lse, sh.Hq, sh.Hkv, sh.scale, m, nqt, total, run);
+    fwd_f32_kernel<64><<<grid, NT, 0, s>>>(q, k, v, out, lse, sh.Hq, sh.Hkv, sh.scale, m, items);
   else
-    fwd_f32_kernel<128><<<grid, NT, 0, s>>>(q, k, v, out, lse, sh.Hq, sh.Hkv, sh.scale, m, nqt, total, run);
+    fwd_f32_kernel<128><<<grid, NT, 0, s>>>(q, k, v, out, lse, sh.Hq, sh.Hkv, sh.scale, m, items);
   return hipGetLastError();
 }

@@ -137,6 +137,28 @@ struct LgSwzReader {
   }
 };
 
+// The 32 x D result of a wave, held as its accumulators hold it (lane = 32g + n: row n, dims 32 db + 8 r4 + 4g .. +3 in
+// words(db, r4)), to `rows` consecutive rows in memory: through 32 rows of LDS of the wave's own, so that an instruction
+// writes 1 KB in one piece instead of 16 bytes of each of 32 rows.  The 16-byte chunks of a row are XOR-swizzled as in a
+// tile: no bank conflicts either way.
+template <int D, typename W>
+__device__ __forceinline__ void lg_store_rows(unsigned char* lds, uint16_t* __restrict__ dst, int rows, int lane, W&& words) {
+  using T = LgSwzTile<D>;
+  const int n = lane & 31, g = lane >> 5;
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4)
+      *reinterpret_cast<uint2*>(lds + n * T::ROW_BYTES + (((4 * db + r4) ^ T::pi(n)) << 4) + 8 * g) = words(db, r4);
+  constexpr int RPI = 64 / T::CPR;  // rows per instruction
+#pragma unroll
+  for (int x = 0; x < 32 / RPI; ++x) {
+    const int row = x * RPI + lane / T::CPR, c = lane % T::CPR;
+    const uint4 w = *reinterpret_cast<const uint4*>(lds + row * T::ROW_BYTES + ((c ^ T::pi(row)) << 4));
+    if (row < rows) *reinterpret_cast<uint4*>(dst + (size_t)row * D + c * 8) = w;
+  }
+}
+
 // Pack accumulator registers 8h..8h+7 (rounded to bf16) as a B operand.
 __device__ __forceinline__ bf16x8_t lg_pack8(const float* p) {
   uint4 w;
