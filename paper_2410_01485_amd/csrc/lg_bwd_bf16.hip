@@ -88,6 +88,7 @@ struct LgBwdWork {
   float* lonepart;        // Hq == Hkv: [b x kv head][lone chunks of all sequences] group slots
   int nlone_all;          // lone chunks of all sequences
   unsigned* arrived;      // Hq == Hkv: [b x kv head][sequence] chunks of a lone group that are done
+  bool turn;              // lg_may_turn
   bool by_tile;           // dk/dv items: heads innermost (always for packed sequences and cut window parts)
   // window parts cut into `heads_cut` sets of query heads times `rows_cut` runs of query tiles
   int heads_cut, rows_cut;
@@ -166,9 +167,12 @@ dq_bf16_kernel(
   // heads of the GQA group: the G workgroups that walk the same K/V tiles run side by side
   const int G = Hq / Hkv;
   const int gq = L % G, rest = L / G;
-  const int half = 1 - (rest & 1), x = (rest >> 1) % nqt;  // (nqt, qtile0: in LG_BF16_TQ rows, two workgroups each)
-  int qt = nqt - 1 - x;
+  // (nqt, qtile0: in LG_BF16_TQ rows, two workgroups each)
   const int bhk = (rest >> 1) / nqt;
+  int y = rest - bhk * 2 * nqt;
+  if (wk.turn && lg_turned(bhk)) y = 2 * nqt - 1 - y;
+  const int half = 1 - (y & 1), x = y >> 1;
+  int qt = nqt - 1 - x;
   const int b = bhk / Hkv, hk = bhk % Hkv;
   const int hq = hk * G + gq;
   int srow = 0, swrow = 0;  // packed: first row of the sequence inside its head, in the workspace
@@ -491,6 +495,7 @@ __device__ __forceinline__ bool lg_bwd_main(const LgBwdWork& wk, int bid, int nk
   const int L = lg_item_of(bid, run);
   w.bh = L / nkt;
   w.kt = L % nkt;
+  if (wk.turn && lg_turned(w.bh)) w.kt = nkt - 1 - w.kt;
   return L < total;
 }
 // The query tiles [lo, hi] and query heads of the part: the window part of keys [k0, k1] (all query tiles that see them
@@ -1973,6 +1978,7 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
   wk.heads_cut = a.cut.heads;
   wk.rows_cut = a.cut.rows;
   wk.parts = (float*)(w + l.parts);
+  wk.turn = false;
   if (a.qt_wide > 0) {
     const int total = a.qt_wide * Hq * a.B, run = lg_run_length(m, total, nbh, 8 * (Hq / Hkv), packed);
     const int nitems = (int)lg_run_grid(total, run);
@@ -1988,6 +1994,7 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
     const int total = 2 * a.qt_rest * Hq * a.B, run = lg_run_length(m, total, nbh, 16 * (Hq / Hkv), packed);
     const dim3 grid((unsigned)lg_run_grid(total, run));
     wk.qt_first = a.qt_wide;
+    wk.turn = lg_may_turn(nbh, 2 * a.qt_rest);
 #define LG_DQ_LAUNCH(DD, TT)                                                                                           \
   dq_bf16_kernel<DD, TT><<<grid, 256, 0, s>>>(uq, uk, uv, uo, ug, lse, ndelta, nlse, dq, Hq, Hkv, scale, m, a.qt_rest, \
                                               total, run, wk)
@@ -2025,6 +2032,7 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
   }
   if (a.kt_wide > 0) {
     // one resident workgroup per CU, work items from the second queue
+    wk.turn = false;  // (a queue hands them out)
     const int nkt = a.kt_wide, total = nkt * nbh, run = lg_run_length(m, total, nbh, 8, false);
     const int nitems = wk.by_tile ? total * nparts : (int)lg_run_grid(total, run);
     const dim3 grid((unsigned)(nitems < cus ? nitems : cus));
@@ -2037,6 +2045,7 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
     const int nkt = a.kt_rest, total = nkt * nbh, run = lg_run_length(m, total, nbh, 8, false);
     const dim3 grid((unsigned)(wk.by_tile ? total * nparts : (int)lg_run_grid(total, run)));
     wk.items = items + a.kt_wide;
+    wk.turn = lg_may_turn(nbh, nkt);
     if (a.D == 64) {
       if (token) LG_DKDV_LAUNCH(64, true, false, grid);
       else LG_DKDV_LAUNCH(64, false, false, grid);

@@ -84,7 +84,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
       if (pack.tile0[mid] <= qt) lo = mid;
       else hi = mid;
     }
+    const int nt = pack.tile0[lo + 1] - pack.tile0[lo];
     qt -= pack.tile0[lo];
+    if (nt % 2 == 0 && nt <= 64 && lg_turned(lo ^ 2)) qt = nt - 1 - qt;  // (as lg_may_turn; sequence 0 comes last)
     seq_row0 = pack.row0[lo];
     m = lg_mask_for_length(m, pack.row0[lo + 1] - seq_row0);
   }

@@ -152,14 +152,25 @@ LG_HD int lg_run_length(const LgMask& m, int total, int heads, int few, bool var
   const bool even = heads % 8 == 0 || (!varied && m.stride == 0 && m.window <= m.N / 4);
   return even || few >= each ? each : few;
 }
+// Within an XCD the hardware deals workgroups to its four shader engines strictly in turn, whatever they still have to do.
+// Where the rows of a head differ in cost and its tiles are an even number, the same engines get the long ones every time
+// (8 tiles of a causal head: 3072 : 2560 : 2048 : 1536 key tiles, 2.0 of 3 workgroups of a CU in flight on average).  So
+// two heads in four take their tiles in the other order; not the last two of an XCD's heads, so that its last items are
+// short ones.  Not for odd numbers, which mix by themselves (3 tiles turned: 215 -> 258 us), nor beyond 64 tiles, where the
+// engines' shares differ by less than 5 % and a turned head would end on a long row, nor for kernels that take items from
+// a queue.
+LG_HD bool lg_may_turn(int heads, int tiles) { return heads % 32 == 0 && tiles % 2 == 0 && tiles <= 64; }
+LG_HD bool lg_turned(int head) { return (head & 2) == 0; }
+
 // The items of kernels that take query tiles: (b, kv head) slowest, then the query tile, longest rows first, then the
 // query heads of the group, so that the G workgroups that walk the same K/V tiles run side by side.
 struct LgItems {
   int total;
+  bool turn;
   LgDiv run, G, nqt, Hkv;  // nqt: query tiles of a head (all packed sequences together)
 };
 inline LgItems lg_make_items(int total, int run, int nqt, int Hq, int Hkv) {
-  return LgItems{total, lg_make_div(run), lg_make_div(Hq / Hkv), lg_make_div(nqt), lg_make_div(Hkv)};
+  return LgItems{total, lg_may_turn(total / (nqt * (Hq / Hkv)), nqt), lg_make_div(run), lg_make_div(Hq / Hkv), lg_make_div(nqt), lg_make_div(Hkv)};
 }
 struct LgItem {
   int b, hk, hq, x;  // x: query tile, counted from the last one
@@ -168,6 +179,7 @@ LG_HD LgItem lg_item(const LgItems& w, int L) {
   LgItem it;
   int gq;
   const int rest = lg_divmod(w.G, L, &gq), bhk = lg_divmod(w.nqt, rest, &it.x);
+  if (w.turn && lg_turned(bhk)) it.x = (int)w.nqt.d - 1 - it.x;
   it.b = lg_divmod(w.Hkv, bhk, &it.hk);
   it.hq = it.hk * (int)w.G.d + gq;
   return it;

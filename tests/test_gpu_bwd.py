@@ -8,7 +8,7 @@ import torch
 
 import lg_synth
 import paper_2410_01485_amd as lg
-from gpu_util import DEV, TOL_LSE, TOL_OUT, TOL_REL, assert_close, dq_delta_allowance, f32np
+from gpu_util import DEV, TOL_LSE, TOL_OUT, TOL_REL, assert_close, check_fwd, dq_delta_allowance, f32np
 from oracle import lg_oracle as O
 
 pytestmark = pytest.mark.gpu
@@ -61,6 +61,13 @@ def test_sink_window_ragged_gqa(D, dtype):
 ])
 def test_patterns_and_edges(dtype, N, sink, window, block, stride):
     check_bwd(1, 2, 1, N, 128, sink, window, block, stride, dtype=dtype, seed=3)
+
+
+@pytest.mark.parametrize("Hq,N,D,window", [(16, 500, 128, 500), (16, 500, 64, 200), (32, 250, 64, 250), (16, 300, 128, 300)])
+def test_heads_that_take_their_tiles_in_the_other_order(Hq, N, D, window):
+    """32 kv heads and an even number of tiles (forward and dq 2 or 4, dk/dv 2 or 4)."""
+    check_fwd(2, Hq, 16, N, D, 0, window, seed=6)
+    check_bwd(2, Hq, 16, N, D, 0, window, seed=6)
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])

@@ -181,6 +181,7 @@ def test_long_sequences_take_the_resident_kernels():
     (128, [300, 1500, 6000, 1, 0, 257, 5000, 769], 4, 2, 64, 1024, 1, 0),   # both forms of dq and dk/dv, lone columns
     (128, [2500, 64, 4000, 700], 4, 1, 64, 256, 64, 8),                     # dq forms differ by the strided columns
     (64, [1800, 255, 0, 3000], 2, 2, 64, 128, 64, 2),
+    (128, [512, 200, 512, 0, 300, 512, 1000, 500], 2, 2, 0, 512, 1, 0),     # even numbers of tiles: turned and not
     (128, [5 + (37 * s) % 90 for s in range(140)], 2, 2, 4, 16, 1, 0),      # more sequences than one set of launches takes
 ])
 def test_packed_backward_mix(D, lens, Hq, Hkv, sink, window, block, stride):

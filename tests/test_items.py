@@ -24,7 +24,7 @@ int main() {
       if (x != n / d || rem != n % d) { std::printf("%lld / %d = %d rest %d\n", n, d, x, rem); return 1; }
     }
   }
-  const int shapes[][5] = {{1, 1, 1, 1, 1}, {2, 8, 2, 5, 3}, {3, 6, 6, 7, 16}, {1, 64, 8, 129, 1000}, {4, 4, 1, 2, 2}};
+  const int shapes[][5] = {{1, 1, 1, 1, 1}, {2, 8, 2, 5, 3}, {3, 6, 6, 7, 16}, {1, 64, 8, 129, 1000}, {4, 4, 1, 2, 2}, {4, 16, 16, 8, 7}, {4, 32, 16, 2, 300}};
   for (auto& s : shapes) {
     const int B = s[0], Hq = s[1], Hkv = s[2], nqt = s[3], run = s[4], total = B * Hq * nqt;
     const LgItems w = lg_make_items(total, run, nqt, Hq, Hkv);
