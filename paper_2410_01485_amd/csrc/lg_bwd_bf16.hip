@@ -30,6 +30,12 @@
 // tokens, window 512: 805 -> 644 us; 64/8 heads, 9830 tokens, window 455: 489 -> 367 us; dk/dv, 32 heads of 64, 32768
 // tokens, window 4096: 2441 -> 2104 us, window 512: 610 -> 475 us.
 //
+// What a workgroup reads and writes once (Q, dO, out, K; dq, dk, dv) goes through LDS in pieces of 1 KB: loaded or stored
+// by each lane from or to its own row, an instruction touches 32 rows, and these instructions took as long as several
+// tiles, with one workgroup per CU with nothing beside them.  32 heads of 128, 32768 tokens: window 64 dq 374 -> 328, dk/dv
+// 461 -> 390 us; 512 590 -> 570, 830 -> 782; 2048 (64 rows per wave) 1545 -> 1493, 1910 -> 1875; 64 x 512 tokens 465 -> 380,
+// 630 -> 495 (some of that from the order of the tiles, lg_may_turn).
+//
 // For head dim 128 and long windows (dq 32 or more tiles, dk/dv 16) both kernels have a second form with 64 rows
 // (keys) per wave, one wave per SIMD and the accumulators in AGPRs (further down): every operand
 // read from LDS then feeds two matrix instructions.
@@ -127,6 +133,42 @@ __device__ __forceinline__ float lg_dot8(uint4 x, uint4 y, float s) {
   return s;
 }
 
+// Sum over the aligned group of N lanes (8 or 16) that a lane is in.
+template <int N>
+__device__ __forceinline__ float lg_group_sum(float x) {
+  auto add = [&](auto ctrl) {
+    x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), decltype(ctrl)::value, 0xf, 0xf, false));
+  };
+  add(std::integral_constant<int, 0xB1>{});   // lane ^ 1
+  add(std::integral_constant<int, 0x4E>{});   // lane ^ 2
+  add(std::integral_constant<int, 0x141>{});  // 7 - lane, inside the group of 8
+  if (N == 16) add(std::integral_constant<int, 0x140>{});  // 15 - lane
+  return x;
+}
+
+// Delta = <dout, out> and the log-sum-exp of the ROWS rows from q0 on to LDS, by a workgroup of 256: dout from its tiles in
+// LDS, out in pieces of 16 bytes, consecutive lanes consecutive pieces.  Rows past the end repeat the last one.
+template <int D, int ROWS>
+__device__ __forceinline__ void lg_delta_rows(const unsigned char* tiles, const uint4 (&o)[ROWS * D / 2048], float* s_delta) {
+  using T = LgSwzTile<D>;
+  const int tid = threadIdx.x, c = tid % T::CPR;
+#pragma unroll
+  for (int x = 0; x < ROWS * D / 2048; ++x) {
+    const int r = x * (256 / T::CPR) + tid / T::CPR;
+    const uint4 gw = *reinterpret_cast<const uint4*>(tiles + r * T::ROW_BYTES + ((c ^ T::pi(r & 63)) << 4));
+    const float s = lg_group_sum<T::CPR>(lg_dot8(gw, o[x], 0.f));
+    if (c == 0) s_delta[r] = s;
+  }
+}
+template <int D, int ROWS>
+__device__ __forceinline__ void lg_load_pieces(const uint16_t* __restrict__ rows, int last, uint4 (&o)[ROWS * D / 2048]) {
+  using T = LgSwzTile<D>;
+  const int tid = threadIdx.x;
+#pragma unroll
+  for (int x = 0; x < ROWS * D / 2048; ++x)
+    o[x] = *reinterpret_cast<const uint4*>(rows + (size_t)min(x * (256 / T::CPR) + tid / T::CPR, last) * D + tid % T::CPR * 8);
+}
+
 // Both dq kernels also form Delta_i = <dout_i, out_i> of their rows (a lane and its partner in
 // the other half of the wave hold the whole row of dout anyway) and leave -Delta and -lse / scale
 // in the workspace for the dk/dv kernels, which run after them on the same stream.
@@ -160,6 +202,7 @@ dq_bf16_kernel(
   constexpr int DC = D / 16, DB = D / 32;
   constexpr int STAGE = 2 * T::BYTES;  // K tile + V tile
   __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * STAGE];
+  __shared__ float s_rows[2][TQ];  // Delta, log-sum-exp
 
   const int L = lg_item_of(blockIdx.x, run);
   if (L >= total) return;
@@ -223,31 +266,43 @@ dq_bf16_kernel(
     if (TOKEN || m.stride == 0) return prev < 0 ? lg_qwalk_first(qw) : lg_qwalk_next(qw, prev);
     return lg_qsched_next(m, qs, prev);
   };
-  int t = next_tile(-1);
-  issue(t, 0);
-
-  // (the first tile is on its way before the rows' own loads: 8 heads, window 124: 936 -> 830 us)
+  // Q and dO rows through the two stages' places into registers, out and the log-sum-exp once per row
+#pragma unroll
+  for (int y = 0; y < 2; ++y)
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      const int rc = min(q0 + 64 * x, N - 1);  // a tile wholly past the end repeats the last row
+      dma.issue((y ? q : dout) + qbase + (size_t)rc * D, N - rc, lds0 + y * STAGE + x * T::BYTES);
+    }
+  const int my_row = min(q0 + (tid & (TQ - 1)), N - 1);
+  const float my_lse = lse[row0 + my_row];
+  {
+    uint4 o[TQ * D / 2048];
+    lg_load_pieces<D, TQ>(out + qbase + (size_t)q0 * D, N - 1 - q0, o);
+    LG_WAIT_VMCNT(0);
+    __syncthreads();
+    lg_delta_rows<D, TQ>(smem, o, s_rows[0]);
+    if (tid < TQ) s_rows[1][tid] = my_lse;
+  }
   bf16x8_t qf[DC], gf[DC];
-  float di = 0.f;
 #pragma unroll
   for (int dc = 0; dc < DC; ++dc) {
-    const uint4 gw = *reinterpret_cast<const uint4*>(dout + qbase + (size_t)iq * D + dc * 16 + g * 8);
-    qf[dc] = lg_as_bf16x8(*reinterpret_cast<const uint4*>(q + qbase + (size_t)iq * D + dc * 16 + g * 8));
-    gf[dc] = lg_as_bf16x8(gw);
-    di = lg_dot8(gw, *reinterpret_cast<const uint4*>(out + qbase + (size_t)iq * D + dc * 16 + g * 8), di);
-  }
-  di += lg_other_half(di);  // Delta of row i
-  const float sl2 = scale * LOG2E;
-  const float lse_i = lse[row0 + iq];
-  float lse2 = lse_i * LOG2E;
-  if (g == 0 && i < N) {
-    ndelta[wrow0 + i] = -di;
-    nlse[wrow0 + i] = -lse_i / scale;
+    gf[dc] = rd.read_rows(smem, (wave_s >> 1) * T::BYTES, wave_s & 1, dc);
+    qf[dc] = rd.read_rows(smem, STAGE + (wave_s >> 1) * T::BYTES, wave_s & 1, dc);
   }
   // Touch everything loaded so far, so that the compiler's waits for these loads sit here and
   // not inside the tile loop (where they would drain the direct loads kept in flight).
 #pragma unroll
   for (int dc = 0; dc < DC; ++dc) asm volatile("" ::"v"(qf[dc]), "v"(gf[dc]));
+  __syncthreads();
+  int t = next_tile(-1);
+  issue(t, 0);
+  const float sl2 = scale * LOG2E;
+  float di = s_rows[0][wave * 32 + n], lse2 = s_rows[1][wave * 32 + n] * LOG2E;
+  if (tid < TQ && q0 + tid < N) {
+    ndelta[wrow0 + q0 + tid] = -s_rows[0][tid];
+    nlse[wrow0 + q0 + tid] = -my_lse / scale;
+  }
   asm volatile("" : "+v"(lse2), "+v"(di));
 
   int stage = 0;
@@ -310,17 +365,16 @@ dq_bf16_kernel(
     stage ^= 1;
   }
 
-  if (i < N) {
+  // (everyone is done with the stage before the last tile's)
+  unsigned char* rows = smem + stage * STAGE + wave_s * (32 * T::ROW_BYTES);
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+  for (int db = 0; db < DB; ++db) {
+    float a[16];
 #pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        uint2 w;
-        w.x = lg_pack_bf16(acc[db][4 * r4 + 0] * scale, acc[db][4 * r4 + 1] * scale);
-        w.y = lg_pack_bf16(acc[db][4 * r4 + 2] * scale, acc[db][4 * r4 + 3] * scale);
-        *reinterpret_cast<uint2*>(dq + qbase + (size_t)i * D + db * 32 + 8 * r4 + 4 * g) = w;
-      }
+    for (int r = 0; r < 16; ++r) a[r] = acc[db][r];
+    lg_rows_put<D>(rows, lane, db, a, scale);
   }
+  lg_rows_write<D>(rows, lane, dq + qbase + (size_t)(q0 + wave_s * 32) * D, N - (q0 + wave_s * 32));
 }
 
 // ---------------------------------------------------------------------- dk, dv
@@ -666,14 +720,6 @@ dkdv_bf16_kernel(
     r0_w = (lg_qtile_window_hi(m, t1, TQ) + 1) * TQ;
   }
   const int j = kw0 + n;  // this lane's key
-  const int jk = min(j, N - 1);
-
-  bf16x8_t kf[DC];
-#pragma unroll
-  for (int dc = 0; dc < DC; ++dc)
-    kf[dc] = lg_as_bf16x8(*reinterpret_cast<const uint4*>(k + kbase + (size_t)jk * D + dc * 16 + g * 8));
-#pragma unroll
-  for (int dc = 0; dc < DC; ++dc) asm volatile("" ::"v"(kf[dc]));
 
   f32x16_t ak[DB], av[DB];
 #pragma unroll
@@ -702,19 +748,42 @@ dkdv_bf16_kernel(
   const int per_head = hi - lo + 1;
   const int steps = per_head * nheads;
 
+  const int voff = (wave >> 1) * T::BYTES + (wave & 1) * HALF;  // this wave's 32 V rows
   Dma dma;
   dma.init(tid);
   LgSwzReader<D> rd;
   rd.init(n, g);
   const uint32_t lds0 = (uint32_t)(uintptr_t)LG_LDS_PTR(unsigned char, smem);
-  // the workgroup's V rows, resident for the whole kernel
+  // K rows to registers, V rows resident.  K of head dim 64 goes through the stages' place; at 128, where one
+  // workgroup fits a CU, its two barriers cost more than they save (window 256, 32768 tokens, 32 heads: 545 us direct, 568 through LDS; at 64 247 direct, 243).
+  constexpr bool K_LDS = D == 64;
+  static_assert(!K_LDS || NG * T::BYTES <= 2 * STAGE, "K rows fit the stages");
+  bf16x8_t kf[DC];
+  if constexpr (!K_LDS) {
+    const int jk = min(j, N - 1);
 #pragma unroll
-  for (int x = 0; x < NG; ++x) {
-    const int r0 = COLUMN ? 64 * clist[min(NG * vt + x, ncol - 1)] : k0 + 64 * x;
-    const int rc = min(r0, N - 1);  // a tile wholly past the end repeats the last row
-    dma.issue(v + kbase + (size_t)rc * D, r0 < N ? N - r0 : 1, lds0 + x * T::BYTES);
+    for (int dc = 0; dc < DC; ++dc)
+      kf[dc] = lg_as_bf16x8(*reinterpret_cast<const uint4*>(k + kbase + (size_t)jk * D + dc * 16 + g * 8));
+#pragma unroll
+    for (int dc = 0; dc < DC; ++dc) asm volatile("" ::"v"(kf[dc]));
   }
-  const int voff = (wave >> 1) * T::BYTES + (wave & 1) * HALF;  // this wave's 32 V rows
+#pragma unroll
+  for (int kv = K_LDS ? 0 : 1; kv < 2; ++kv)
+#pragma unroll
+    for (int x = 0; x < NG; ++x) {
+      const int r0 = COLUMN ? 64 * clist[min(NG * vt + x, ncol - 1)] : k0 + 64 * x;
+      const int rc = min(r0, N - 1);  // a tile wholly past the end repeats the last row
+      dma.issue((kv ? v : k) + kbase + (size_t)rc * D, r0 < N ? N - r0 : 1, lds0 + (kv ? 0 : VRES) + x * T::BYTES);
+    }
+  if constexpr (K_LDS) {
+    LG_WAIT_VMCNT(NG * Dma::CH);
+    __syncthreads();
+#pragma unroll
+    for (int dc = 0; dc < DC; ++dc) kf[dc] = rd.read_rows(smem, VRES + (wave_s >> 1) * T::BYTES, wave_s & 1, dc);
+#pragma unroll
+    for (int dc = 0; dc < DC; ++dc) asm volatile("" ::"v"(kf[dc]));
+    __syncthreads();
+  }
 
   // (head, query tile) of a step advance incrementally: no divisions in the loop
   // rows of the query head whose step is requested next
@@ -830,19 +899,17 @@ dkdv_bf16_kernel(
       }
     }
   }
-  if (j < N) {
+  unsigned char* rows = smem + voff;  // (its V rows' place: no other wave reads them)
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+  for (int which = 0; which < 2; ++which) {
 #pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        uint2 w;
-        w.x = lg_pack_bf16(ak[db][4 * r4 + 0] * scale, ak[db][4 * r4 + 1] * scale);
-        w.y = lg_pack_bf16(ak[db][4 * r4 + 2] * scale, ak[db][4 * r4 + 3] * scale);
-        *reinterpret_cast<uint2*>(dk + kbase + (size_t)j * D + db * 32 + 8 * r4 + 4 * g) = w;
-        w.x = lg_pack_bf16(av[db][4 * r4 + 0], av[db][4 * r4 + 1]);
-        w.y = lg_pack_bf16(av[db][4 * r4 + 2], av[db][4 * r4 + 3]);
-        *reinterpret_cast<uint2*>(dv + kbase + (size_t)j * D + db * 32 + 8 * r4 + 4 * g) = w;
-      }
+    for (int db = 0; db < DB; ++db) {
+      float a[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) a[r] = which ? av[db][r] : ak[db][r];
+      lg_rows_put<D>(rows, lane, db, a, which ? 1.f : scale);
+    }
+    lg_rows_write<D>(rows, lane, (which ? dv : dk) + kbase + (size_t)kw0 * D, N - kw0);
   }
 }
 
@@ -1160,19 +1227,6 @@ __device__ __forceinline__ void dkdv_wide_item(
   }
   const int j = kw0 + n;
 
-  bf16x8_t kf[2][DC];
-#pragma unroll
-  for (int kb = 0; kb < 2; ++kb) {
-    const int jk = min(j + 32 * kb, N - 1);
-#pragma unroll
-    for (int dc = 0; dc < DC; ++dc)
-      kf[kb][dc] = lg_as_bf16x8(*reinterpret_cast<const uint4*>(k + kbase + (size_t)jk * D + dc * 16 + g * 8));
-  }
-#pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-    for (int dc = 0; dc < DC; ++dc) asm volatile("" ::"v"(kf[kb][dc]));
-
   // accumulators: dk of key block kb, dim block db = block kb * 4 + db; dv = block 8 + kb * 4 + db
   bf16x8_t zero8 = lg_as_bf16x8(make_uint4(0u, 0u, 0u, 0u));
   // A matrix instruction must not read a register that a vector instruction wrote just before it
@@ -1207,12 +1261,29 @@ __device__ __forceinline__ void dkdv_wide_item(
   LgSwzReader<D> rd;
   rd.init(n, g);
   const uint32_t lds0 = (uint32_t)(uintptr_t)LG_LDS_PTR(unsigned char, smem);
+  // K rows through the stages' place into registers, V rows resident
+  static_assert(4 * T::BYTES <= 2 * STAGE, "K rows fit the stages");
 #pragma unroll
-  for (int x = 0; x < 4; ++x) {
-    const int r0 = COLUMN ? 64 * clist[min(4 * vt + x, ncol - 1)] : k0 + 64 * x;
-    const int rc = min(r0, N - 1);  // a tile wholly past the end repeats the last row
-    dma.issue(v + kbase + (size_t)rc * D, r0 < N ? N - r0 : 1, lds0 + x * T::BYTES);
-  }
+  for (int kv = 0; kv < 2; ++kv)
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      const int r0 = COLUMN ? 64 * clist[min(4 * vt + x, ncol - 1)] : k0 + 64 * x;
+      const int rc = min(r0, N - 1);  // a tile wholly past the end repeats the last row
+      dma.issue((kv ? v : k) + kbase + (size_t)rc * D, r0 < N ? N - r0 : 1, lds0 + (kv ? 0 : VRES) + x * T::BYTES);
+    }
+  LG_WAIT_VMCNT(4 * Dma::CH);
+  __syncthreads();
+  bf16x8_t kf[2][DC];
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int dc = 0; dc < DC; ++dc) kf[kb][dc] = rd.read_rows(smem, VRES + wave_s * T::BYTES, kb, dc);
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int dc = 0; dc < DC; ++dc) asm volatile("" ::"v"(kf[kb][dc]));
+  __syncthreads();
+
   const int voff = wave * T::BYTES;  // this wave's 64 V rows
 
   // rows of the query head whose step is requested next
@@ -1399,6 +1470,7 @@ __device__ __forceinline__ void dkdv_wide_item(
   // the last matrix results must have landed before the blocks are copied out
   asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
   using Slot = LgSlot<D>;
+  unsigned char* rows = smem + voff;  // (its V rows' place: no other wave reads them)
   const bool cut = !COLUMN && wk.heads_cut * wk.rows_cut > 1;
   if (COLUMN && !active) return;
   float* slot = (cut ? lg_bwd_part_slot<D>(wk, it, w, total / nkt) + wave_s * Slot::FLOATS
@@ -1407,7 +1479,6 @@ __device__ __forceinline__ void dkdv_wide_item(
   const float* csum = wk.colpart + ((size_t)bh * wk.ncol + it.col0 + max(cid, 0)) * Slot::FLOATS + lane;
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb) {
-    const int jj = j + 32 * kb;
     float c[2 * DB][16];  // the column part's sums, all of a key block in flight at once
     if (cid >= 0)
 #pragma unroll
@@ -1440,19 +1511,13 @@ __device__ __forceinline__ void dkdv_wide_item(
             akv[r] += c[2 * db][r];
             avv[r] += c[2 * db + 1][r];
           }
-        if (jj < N)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          const float *a4 = akv + 4 * r4, *v4 = avv + 4 * r4;
-          uint2 w;
-          w.x = lg_pack_bf16(a4[0] * scale, a4[1] * scale);
-          w.y = lg_pack_bf16(a4[2] * scale, a4[3] * scale);
-          *reinterpret_cast<uint2*>(dk + kbase + (size_t)jj * D + db * 32 + 8 * r4 + 4 * g) = w;
-          w.x = lg_pack_bf16(v4[0], v4[1]);
-          w.y = lg_pack_bf16(v4[2], v4[3]);
-          *reinterpret_cast<uint2*>(dv + kbase + (size_t)jj * D + db * 32 + 8 * r4 + 4 * g) = w;
-        }
+        lg_rows_put<D>(rows, lane, db, akv, scale);
+        lg_rows_put<D>(rows + 32 * T::ROW_BYTES, lane, db, avv, 1.f);
       }
+    }
+    if (!COLUMN && !cut) {
+      lg_rows_write<D>(rows, lane, dk + kbase + (size_t)(kw0 + 32 * kb) * D, N - (kw0 + 32 * kb));
+      lg_rows_write<D>(rows + 32 * T::ROW_BYTES, lane, dv + kbase + (size_t)(kw0 + 32 * kb) * D, N - (kw0 + 32 * kb));
     }
   }
 }
@@ -1518,6 +1583,7 @@ __device__ __forceinline__ void dq_wide_item(
   constexpr int DC = D / 16, DB = D / 32;
   constexpr int STAGE = 2 * T::BYTES;  // K tile + V tile
   __shared__ __attribute__((aligned(1024))) unsigned char smem[STAGES * STAGE];
+  __shared__ float s_rows[2][TQ];  // Delta, log-sum-exp
 
   const int L = lg_item_of(bid, run);
   if (L >= total) return;
@@ -1549,49 +1615,35 @@ __device__ __forceinline__ void dq_wide_item(
   const int qw0 = min(q0 + wave_s * 64, N - 1), qw1 = min(q0 + wave_s * 64 + 63, N - 1);  // this wave's rows
   const int i0 = q0 + wave * 64 + n;  // this lane's row of row block 0 (block 1: + 32)
 
-  // fragments: Q of (rb, dc) -> fragment 8 rb + dc, dO -> 16 + 8 rb + dc
-  float lse2[2], lse_i[2];
-  f32x16_t ndl[2];  // -Delta of the lane's row in all 16 registers: the addend dP^T starts from
-#pragma unroll
-  for (int rb = 0; rb < 2; ++rb) {
-    const int iq = min(i0 + 32 * rb, N - 1);
-    float di = 0.f;
-#pragma unroll
-    for (int dc = 0; dc < DC; ++dc) {
-      const uint4 gw = *reinterpret_cast<const uint4*>(dout + qbase + (size_t)iq * D + dc * 16 + g * 8);
-      lg_frag_set(8 * rb + dc, *reinterpret_cast<const uint4*>(q + qbase + (size_t)iq * D + dc * 16 + g * 8));
-      lg_frag_set(16 + 8 * rb + dc, gw);
-      di = lg_dot8(gw, *reinterpret_cast<const uint4*>(out + qbase + (size_t)iq * D + dc * 16 + g * 8), di);
-    }
-    di += lg_other_half(di);  // Delta of the row
-    lse_i[rb] = lse[row0 + iq];
-    lse2[rb] = lse_i[rb] * LOG2E;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) ndl[rb][r] = -di;
-  }
-  const float sl2 = scale * LOG2E;
-  asm volatile("" : "+v"(lse2[0]), "+v"(lse2[1]), "+v"(ndl[0]), "+v"(ndl[1]));
-  {  // The rows' -Delta and -lse / scale for the dk/dv kernels.  Every lane stores, without a branch:
-     // the two lanes of a row store the same values, and lanes past the end hold (and store) those
-     // of row N - 1, whose data they loaded.
-    const float inv_scale = 1.f / scale;
-#pragma unroll
-    for (int rb = 0; rb < 2; ++rb) {
-      const size_t row = wrow0 + min(i0 + 32 * rb, N - 1);
-      ndelta[row] = ndl[rb][0];
-      nlse[row] = -lse_i[rb] * inv_scale;
-    }
-  }
-  bf16x8_t zero8 = lg_as_bf16x8(make_uint4(0u, 0u, 0u, 0u));
-  asm volatile("s_nop 15" : "+v"(zero8));  // as in the dk/dv kernel: written well before it is read
-#pragma unroll
-  for (int x = 0; x < 8; ++x) lg_acc_zero(x, zero8);
-
+  // Q and dO rows through the ring's place into fragments: Q of (rb, dc) -> fragment 8 rb + dc, dO -> 16 + 8 rb + dc
   Dma dma;
   dma.init(tid);
   LgSwzReader<D> rd;
   rd.init(n, g);
   const uint32_t lds0 = (uint32_t)(uintptr_t)LG_LDS_PTR(unsigned char, smem);
+#pragma unroll
+  for (int y = 0; y < 2; ++y)
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      const int rc = min(q0 + 64 * x, N - 1);  // a tile wholly past the end repeats the last row
+      dma.issue((y ? q : dout) + qbase + (size_t)rc * D, N - rc, lds0 + (4 * y + x) * T::BYTES);
+    }
+  const float my_lse = lse[row0 + min(q0 + tid, N - 1)];
+  {
+    uint4 o[16];
+    lg_load_pieces<D, TQ>(out + qbase + (size_t)q0 * D, N - 1 - q0, o);
+    LG_WAIT_VMCNT(0);
+    __syncthreads();
+    lg_delta_rows<D, TQ>(smem, o, s_rows[0]);
+    s_rows[1][tid] = my_lse;
+  }
+#pragma unroll
+  for (int x = 0; x < 4; ++x)
+#pragma unroll
+    for (int dc = 0; dc < DC; ++dc)
+      lg_frag_set((x < 2 ? 16 : 0) + 8 * (x & 1) + dc,
+                  __builtin_bit_cast(uint4, rd.read_rows(smem, ((x < 2 ? 0 : 4) + wave_s) * T::BYTES, x & 1, dc)));
+  __syncthreads();
   const LgQSched qs = lg_qsched_init(m, q0, q1);
   auto issue = [&](int t, int stage) {
     const size_t off = (size_t)t * TK * D;
@@ -1612,6 +1664,29 @@ __device__ __forceinline__ void dq_wide_item(
     issue(t_issue, x);
     t_issue = next_tile(t_issue);
   }
+  float lse2[2];
+  f32x16_t ndl[2];  // -Delta of the lane's row in all 16 registers: the addend dP^T starts from
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb) {
+    const int row = wave * 64 + 32 * rb + n;
+    lse2[rb] = s_rows[1][row] * LOG2E;
+    const float di = s_rows[0][row];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) ndl[rb][r] = -di;
+  }
+  const float sl2 = scale * LOG2E;
+  asm volatile("" : "+v"(lse2[0]), "+v"(lse2[1]), "+v"(ndl[0]), "+v"(ndl[1]));
+  {  // The rows' -Delta and -lse / scale for the dk/dv kernels.  Every thread stores, without a branch: those past the end
+     // hold (and store) the values of row N - 1, whose data they loaded.
+    const size_t row = wrow0 + min(q0 + tid, N - 1);
+    ndelta[row] = -s_rows[0][tid];
+    nlse[row] = -my_lse * (1.f / scale);
+  }
+  bf16x8_t zero8 = lg_as_bf16x8(make_uint4(0u, 0u, 0u, 0u));
+  asm volatile("s_nop 15" : "+v"(zero8));  // as in the dk/dv kernel: written well before it is read
+#pragma unroll
+  for (int x = 0; x < 8; ++x) lg_acc_zero(x, zero8);
+
   int stage = 0;
   while (t >= 0) {
     if ((stage & 1) == 0) {
@@ -1732,22 +1807,18 @@ __device__ __forceinline__ void dq_wide_item(
 
   // the last matrix results must have landed before the blocks are copied out
   asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+  // (into the stages of the pair before the last one, which everyone is done with)
+  unsigned char* rows = smem + (((stage + 1) / 2 * 2) % STAGES) * STAGE + wave_s * (64 * T::ROW_BYTES);
 #pragma unroll
   for (int rb = 0; rb < 2; ++rb) {
-    const int i = i0 + 32 * rb;
 #pragma unroll
     for (int db = 0; db < DB; ++db) {
       float a[16];
       lg_acc_get(4 * rb + db, a);
-      if (i < N)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          uint2 w;
-          w.x = lg_pack_bf16(a[4 * r4 + 0] * scale, a[4 * r4 + 1] * scale);
-          w.y = lg_pack_bf16(a[4 * r4 + 2] * scale, a[4 * r4 + 3] * scale);
-          *reinterpret_cast<uint2*>(dq + qbase + (size_t)i * D + db * 32 + 8 * r4 + 4 * g) = w;
-        }
+      lg_rows_put<D>(rows + rb * (32 * T::ROW_BYTES), lane, db, a, scale);
     }
+    const int r0 = q0 + wave_s * 64 + 32 * rb;
+    lg_rows_write<D>(rows + rb * (32 * T::ROW_BYTES), lane, dq + qbase + (size_t)r0 * D, N - r0);
   }
 }
 

@@ -272,11 +272,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
   const float l = lrow + lg_other_half(lrow);
   const float inv = 1.f / l;
   // (the K tiles' place is free: nobody reads it behind the last tile's second barrier)
-  lg_store_rows<D>(smem + wave_s * (32 * T::ROW_BYTES), out + qbase + (size_t)(q0 + wave_s * 32) * D, N - (q0 + wave_s * 32), lane,
-                   [&](int db, int r4) {
-                     return make_uint2(lg_pack_bf16(oacc[db][4 * r4 + 0] * inv, oacc[db][4 * r4 + 1] * inv),
-                                       lg_pack_bf16(oacc[db][4 * r4 + 2] * inv, oacc[db][4 * r4 + 3] * inv));
-                   });
+  unsigned char* rows = smem + wave_s * (32 * T::ROW_BYTES);
+#pragma unroll
+  for (int db = 0; db < DB; ++db) {
+    float o[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[r] = oacc[db][r];
+    lg_rows_put<D>(rows, lane, db, o, inv);
+  }
+  lg_rows_write<D>(rows, lane, out + qbase + (size_t)(q0 + wave_s * 32) * D, N - (q0 + wave_s * 32));
   if (lse != nullptr && g == 0 && i < N)
     lse[(size_t)(b * Hq + hq) * m.ld + seq_row0 + i] = (mref * scale_log2e + log2f(l)) * 0.69314718055994530942f;
 }

@@ -137,19 +137,22 @@ struct LgSwzReader {
   }
 };
 
-// The 32 x D result of a wave, held as its accumulators hold it (lane = 32g + n: row n, dims 32 db + 8 r4 + 4g .. +3 in
-// words(db, r4)), to `rows` consecutive rows in memory: through 32 rows of LDS of the wave's own, so that an instruction
-// writes 1 KB in one piece instead of 16 bytes of each of 32 rows.  The 16-byte chunks of a row are XOR-swizzled as in a
-// tile: no bank conflicts either way.
-template <int D, typename W>
-__device__ __forceinline__ void lg_store_rows(unsigned char* lds, uint16_t* __restrict__ dst, int rows, int lane, W&& words) {
+// The 32 x D result of a wave, held as its accumulators hold it (lane = 32g + n: row n; register 4 r4 + x of block db: dim
+// 32 db + 8 r4 + 4g + x), to `rows` consecutive rows in memory: put block by block into 32 rows of LDS of the wave's own
+// (multiplied by f and rounded), then written 1 KB in one piece per instruction instead of 8 bytes of each of 32 rows
+// twice.  The 16-byte chunks of a row are XOR-swizzled as in a tile: no bank conflicts either way.
+template <int D>
+__device__ __forceinline__ void lg_rows_put(unsigned char* lds, int lane, int db, const float* a, float f) {
   using T = LgSwzTile<D>;
   const int n = lane & 31, g = lane >> 5;
 #pragma unroll
-  for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-    for (int r4 = 0; r4 < 4; ++r4)
-      *reinterpret_cast<uint2*>(lds + n * T::ROW_BYTES + (((4 * db + r4) ^ T::pi(n)) << 4) + 8 * g) = words(db, r4);
+  for (int r4 = 0; r4 < 4; ++r4)
+    *reinterpret_cast<uint2*>(lds + n * T::ROW_BYTES + (((4 * db + r4) ^ T::pi(n)) << 4) + 8 * g) =
+        make_uint2(lg_pack_bf16(a[4 * r4 + 0] * f, a[4 * r4 + 1] * f), lg_pack_bf16(a[4 * r4 + 2] * f, a[4 * r4 + 3] * f));
+}
+template <int D>
+__device__ __forceinline__ void lg_rows_write(const unsigned char* lds, int lane, uint16_t* __restrict__ dst, int rows) {
+  using T = LgSwzTile<D>;
   constexpr int RPI = 64 / T::CPR;  // rows per instruction
 #pragma unroll
   for (int x = 0; x < 32 / RPI; ++x) {
