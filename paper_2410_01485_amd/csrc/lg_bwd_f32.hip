@@ -6,9 +6,14 @@
 //   dq_i = scale sum_j dS_ij k_j        (query-tile major, same tile walk as the forward; forms Delta too)
 //   dk_j = scale sum_i dS_ij q_i,  dv_j = sum_i P_ij dout_i   (key-tile major, summed over the query heads of
 //          the group)
-// Precision path for float32 data: every product on the float32 matrix instruction (lg_f32.h).  Both kernels use
-// 8 waves per 64 x 64 tile: 4 groups of 16 rows (keys) x 2 halves of the tile's other axis, summed through LDS at
-// the end, so that two waves share a SIMD.
+// Precision path for float32 data: every product on the float32 matrix instruction (lg_f32.h).  dq uses 8 waves per
+// 64 x 64 tile: 4 groups of 16 rows x 2 halves of the tile's keys, summed through LDS at the end, so that two waves
+// share a SIMD.  dk/dv uses 4 waves per 32 keys: 2 groups of 16 keys x 2 halves of a step's query rows (64, at head dim
+// 128 32), two workgroups per CU: as 8 waves per 64 keys one workgroup fitted a CU (167 registers, 66 KB; at head dim 128
+// 256 with spills), so that 280 work items were two rounds on 256 CUs, and every window had to be cut in two.  16/8 heads
+// of 64, 1024 tokens, window 128: dk/dv 44 -> 29 us (of that 3 from the masks, LgF32Rows); 4 heads of 128, 4096 tokens,
+// window 512: 168 -> 120.  Bound: the float32 matrix rate, 4096 cycles of a step's 6600; the rest is what one wave per
+// SIMD cannot hide (masks, the next copies' issue, the barriers).
 //
 // The dk/dv work of a key tile is cut into parts: its window part (nsp equal runs of (head, query tile) steps,
 // more than one only where key tiles x kv heads would leave CUs idle) and, for keys that every later query sees
@@ -27,7 +32,8 @@ constexpr int NT = 512;
 using I0 = std::integral_constant<int, 0>;
 using I1 = std::integral_constant<int, 1>;
 using I2 = std::integral_constant<int, 2>;
-static_assert(LG_F32_TQ == 64 && LG_F32_TK == 64 && LG_F32_BTQ == 64 && LG_F32_BTK == 64, "64 x 64 tiles");
+static_assert(LG_F32_TQ == 64 && LG_F32_TK == 64, "64 x 64 tiles");
+static_assert(LG_F32_KEYS == 32, "two groups of 16 keys");
 
 // ------------------------------------------------------------------------- dq
 // Also forms Delta for the dk/dv kernel and clears its arrival counters.
@@ -97,6 +103,8 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void dq_f32_kernel(
     dma.issue(v + kbase + (size_t)t * TK * D, N - t * TK, lds0 + stage * STAGE + T::BYTES);
   };
   const LgQSched qs = lg_qsched_init(m, q0, q1);
+  LgF32Rows lr;
+  lr.init(m, qw0, qw1, i);
   int t = lg_qsched_next(m, qs, -1);
   issue(t, 0);
   int tn = lg_qsched_next(m, qs, t);
@@ -109,8 +117,8 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void dq_f32_kernel(
     const int rb0 = 2 * kh, kk = t * TK + 32 * kh;
     int kind0 = LG_TILE_FULL, kind1 = LG_TILE_FULL;  // of the wave's two 16-key blocks
     if (!lg_qsched_full(m, qs, t)) {
-      kind0 = lg_tile_kind(m, qw0, qw1, kk, kk + 15);
-      kind1 = lg_tile_kind(m, qw0, qw1, kk + 16, kk + 31);
+      kind0 = lr.kind(m, kk);
+      kind1 = lr.kind(m, kk + 16);
     }
     const bool masked = kind0 == LG_TILE_PARTIAL || kind1 == LG_TILE_PARTIAL;
     // as in the forward: units of matrix instructions, their LDS operands requested one unit ahead
@@ -164,7 +172,7 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void dq_f32_kernel(
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           float p = __builtin_amdgcn_exp2f(fmaf(s[x][r], c2, -lse2));
-          if (masked && !lg_live(m, i, kk + 16 * (B0 + x) + 4 * h + r)) p = 0.f;
+          if (masked && !lr.live(m, kk + 16 * (B0 + x) + 4 * h + r)) p = 0.f;
           s[x][r] = p * (dp[x][r] - di);
         }
 #pragma unroll
@@ -205,31 +213,46 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void dq_f32_kernel(
 // How the dk/dv work is cut (a function of the shape and the pattern alone, so that a sequence's results do not
 // depend on what else runs).
 struct F32Parts {
-  int nkt, nqt;
+  int nkt, nqt;  // key tiles; query tiles of a dk/dv step's size
   int nsp;    // window parts per key tile
   int ncand;  // leading key tiles that may hold column keys
   int ncc;    // column parts per such tile
+  LgDiv heads, Hkv, dsp, dcc;  // divisions by the kv heads of the batch, of a sequence, by nsp and ncc
   size_t counters_off, part_off, end;  // workspace: Delta | arrival counters | partial dk, dv
 };
 
-__host__ __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
+__host__ __device__ __forceinline__ int ceil_div(int a, int b) { return (int)(((unsigned)a + (unsigned)b - 1u) / (unsigned)b); }
+// query rows of a step of the dk/dv kernel: two stages of Q and dO then take 66 KB, and two workgroups fit a CU
+__host__ __device__ constexpr int btq_of(int D) { return D == 64 ? 64 : 32; }
 
 F32Parts f32_parts(const LgShape& sh, const LgMask& m) {
   F32Parts p;
-  p.nkt = p.nqt = ceil_div(sh.N, 64);
+  const int TK = LG_F32_KEYS, TQ = btq_of(sh.D);
+  p.nkt = ceil_div(sh.N, TK);
+  p.nqt = ceil_div(sh.N, TQ);
   const int G = sh.Hq / sh.Hkv;
   const long long base = (long long)p.nkt * sh.Hkv * sh.B;
-  int w = (m.wb * m.b + 63) / 64 + 1;  // query tiles the window of a key tile reaches
+  int w = (m.wb * m.b + TQ - 1) / TQ + 1;  // query tiles the window of a key tile reaches
   if (w > p.nqt) w = p.nqt;
   const long long steps = (long long)w * G;
-  // two workgroups per CU, as long as a part keeps three steps
-  long long nsp = (512 + base - 1) / base;
-  if (nsp > steps / 3) nsp = steps / 3;
-  p.nsp = nsp < 1 ? 1 : (int)nsp;
+  // In steps (2 us): the longest part, or all of them over the CUs (two workgroups on one share its matrix pipes, but one's
+  // start and end run beside the other's steps).  Starting costs two steps, partial sums and their addition three more.
+  const double total = base * G * (w - 0.5 * w * w / p.nqt);
+  double least = 0;
+  p.nsp = 1;
+  for (int n = 1; n <= steps / 3 + 1 && n <= 64; ++n) {
+    const double one = (double)((steps + n - 1) / n) + (n > 1 ? 5 : 2);
+    const double all = (total + base * n * (n > 1 ? 3 : 1.5)) / 256;
+    const double t = one > all ? one : all;
+    if (n == 1 || t < least) {
+      least = t;
+      p.nsp = n;
+    }
+  }
   // (the window of key tile 0 ends first: if it reaches the last row, no tile has a column part)
-  const int whi0 = lg_qtile_window_hi(m, sh.N < 64 ? sh.N - 1 : 63, 64);
+  const int whi0 = lg_qtile_window_hi(m, sh.N < TK ? sh.N - 1 : TK - 1, TQ);
   p.ncand = 0;
-  if (whi0 < p.nqt - 1) p.ncand = m.stride > 0 ? p.nkt : ceil_div(m.sink, 64);
+  if (whi0 < p.nqt - 1) p.ncand = m.stride > 0 ? p.nkt : ceil_div(m.sink, TK);
   if (p.ncand > p.nkt) p.ncand = p.nkt;
   // A column part is about as long as a window part, four steps at least (below that its own start and the final
   // sum weigh more).  Strided patterns have many column tiles: a few parts each fill the GPU and keep the partial
@@ -237,28 +260,33 @@ F32Parts f32_parts(const LgShape& sh, const LgMask& m) {
   const long long csteps = (long long)(p.nqt - 1 - whi0) * G;
   long long len = (steps + p.nsp - 1) / p.nsp;
   if (len < 4) len = 4;
-  if (m.stride == 0 && m.sink <= 16) len *= 3;  // (a step with one key group takes a third of the time)
+  if (m.stride == 0 && m.sink <= 16 && sh.D == 64) len *= 2;  // (a step with one key group takes half the time)
   long long ncc = (csteps + len - 1) / len;
   const int most = m.stride > 0 ? 8 : 64;
   p.ncc = p.ncand == 0 ? 0 : (int)(ncc < 1 ? 1 : ncc > most ? most : ncc);
   const size_t rows = (((size_t)sh.B * sh.Hq * sh.N * sizeof(float)) + 255) & ~(size_t)255;
   const bool split = p.nsp > 1 || p.ncand > 0;
   const size_t heads = (size_t)sh.B * sh.Hkv;
+  p.heads = lg_make_div((int)heads);
+  p.Hkv = lg_make_div(sh.Hkv);
+  p.dsp = lg_make_div(p.nsp);
+  p.dcc = lg_make_div(p.ncc > 0 ? p.ncc : 1);
   p.counters_off = rows;
   p.part_off = p.counters_off + (split ? (heads * p.nkt * sizeof(unsigned) + 255) & ~(size_t)255 : 0);
-  p.end = p.part_off + (split ? heads * ((size_t)p.nkt * p.nsp + (size_t)p.ncand * p.ncc) * 2 * 64 * sh.D * sizeof(float) : 0);
+  p.end = p.part_off + (split ? heads * ((size_t)p.nkt * p.nsp + (size_t)p.ncand * p.ncc) * 2 * TK * sh.D * sizeof(float) : 0);
   return p;
 }
 
+constexpr int BNT = 256;
 template <int D>
-__global__ __launch_bounds__(NT, 2) void dkdv_f32_kernel(
+__global__ __launch_bounds__(BNT, 2) void dkdv_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
     const float* __restrict__ dout, const float* __restrict__ lse, const float* __restrict__ delta,
     float* __restrict__ dk, float* __restrict__ dv, int Hq, int Hkv, float scale, LgMask m, F32Parts pt, int heads,
     unsigned* __restrict__ arrived, float* __restrict__ part) {
-  using T = LgF32Tile<D>;
-  using Dma = LgTileDma<T, NT>;
-  constexpr int TQ = LG_F32_BTQ, TK = LG_F32_BTK, DC = D / 16;
+  constexpr int TQ = btq_of(D), TK = LG_F32_KEYS, DC = D / 16, NB2 = TQ / 32;  // NB2: 16-row blocks of a wave
+  using T = LgF32Tile<D, TQ>;
+  using Dma = LgTileDma<T, BNT>;
   constexpr int OFF_G = T::BYTES, OFF_L = 2 * T::BYTES, STAGE = 2 * T::BYTES + 1024, LPT = 2 * Dma::CH;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * STAGE];
   __shared__ unsigned s_before;
@@ -267,57 +295,56 @@ __global__ __launch_bounds__(NT, 2) void dkdv_f32_kernel(
   const int G = Hq / Hkv, N = m.N;
   const int ncol = heads * pt.ncand * pt.ncc;
   const bool column = (int)blockIdx.x < ncol;
-  int x = column ? blockIdx.x : blockIdx.x - ncol;
-  const int np = column ? pt.ncc : pt.nsp;
   // heads innermost, first key tiles (the longest, where the window is) first
-  const int bh = x % heads;
-  x /= heads;
-  const int pi = x % np, kt = x / np;
-  const int b = bh / Hkv, hk = bh % Hkv;
+  int bh, pi, hk;
+  const int x = lg_divmod(pt.heads, column ? blockIdx.x : blockIdx.x - ncol, &bh);
+  const LgDiv np = column ? pt.dcc : pt.dsp;
+  const int kt = lg_divmod(np, x, &pi), b = lg_divmod(pt.Hkv, bh, &hk);
   const int k0 = kt * TK, k1 = min(k0 + TK - 1, N - 1);
   const int wlo = k0 / TQ, whi = lg_qtile_window_hi(m, k1, TQ);
   const bool has_col = pt.ncand > 0 && whi < pt.nqt - 1 && lg_has_column_key(m, k0, k1);
   if (column && !has_col) return;
   // steps of the whole part group: (query head, query tile), head slowest
   const int lo = column ? whi + 1 : wlo, per_head = column ? pt.nqt - 1 - whi : whi - wlo + 1;
-  const int steps = per_head * G, len = ceil_div(steps, np);
+  const int steps = per_head * G, len = lg_div(np, steps + (int)np.d - 1);
   const int s0 = pi * len, s1 = min(steps, s0 + len);
   if (s0 >= s1) return;
   const int wsteps = (whi - wlo + 1) * G, csteps = has_col ? (pt.nqt - 1 - whi) * G : 0;
-  const int nmain = ceil_div(wsteps, ceil_div(wsteps, pt.nsp));
-  const int ncols = has_col ? ceil_div(csteps, ceil_div(csteps, pt.ncc)) : 0;
+  const int nmain = pt.nsp > 1 ? ceil_div(wsteps, lg_div(pt.dsp, wsteps + pt.nsp - 1)) : 1;
+  const int ncols = has_col ? ceil_div(csteps, lg_div(pt.dcc, csteps + pt.ncc - 1)) : 0;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, h = lane >> 4;
-  // A wave's 16 keys and its row blocks of a 64-row step: key group wave % 4 and two of the four blocks, or, in a
-  // column part with column keys in one group only (a sink of up to 16 tokens), that group for waves 0..3 with one
-  // block each: as one wave pair the group ran on one SIMD of the four.
-  int kg = wave & 3, ngrp = 0;
-  for (int x = 0; x < 4; ++x)
+  // A wave's 16 keys and its row blocks of a step: key group wave % 2 and half of the blocks, or, in a column part with
+  // column keys in one group only (a sink of up to 16 tokens), that group, with one block for each wave there is one for.
+  int kg = wave & 1, ngrp = 0;
+  for (int x = 0; x < 2; ++x)
     if (column && k0 + 16 * x < N && lg_has_column_key(m, k0 + 16 * x, min(k0 + 16 * x + 15, N - 1))) {
       ++ngrp;
       kg = x;
     }
   const bool narrow = ngrp == 1;
-  if (!narrow) kg = wave & 3;
-  const int rb0 = narrow ? wave & 3 : 2 * (wave >> 2);
-  const bool owner = narrow ? wave == 0 : wave < 4;  // holds the sum over the row blocks at the end
+  if (!narrow) kg = wave & 1;
+  const int rb0 = narrow ? wave : NB2 * (wave >> 1);
+  const bool idle = narrow && wave >= TQ / 16;
+  const bool owner = narrow ? wave == 0 : wave < 2;  // holds the sum over the row blocks at the end
   const int j = k0 + 16 * kg + n, jk = min(j, N - 1);
-  const int kw0 = min(k0 + 16 * kg, N - 1), kw1 = k0 + 16 * kg + 15;  // this wave's keys
+  // The rows that see the lane's key are one run (as in lg_row_bits): from j on, `seen` of them.  Of the wave's keys: the
+  // first and the last one, the ends of the run that ends first and of the one that ends last.
+  const int kw0 = k0 + 16 * kg, kw1 = kw0 + 15, kbj = lg_div_b(m, jk);
+  const bool to_end = jk < m.sink || (m.stride > 0 && lg_strided(m, kbj)) || kbj + m.wb >= lg_div_b(m, N - 1) + 1;
+  const int end_j = j >= N ? 0 : to_end ? N : (kbj + m.wb) * m.b;
+  const unsigned seen = (unsigned)max(end_j - j, 0);
+  int first_end = end_j, last_end = end_j;
+#pragma unroll
+  for (int x = 1; x < 16; x <<= 1) {
+    first_end = min(first_end, __shfl_xor(first_end, x));
+    last_end = max(last_end, __shfl_xor(last_end, x));
+  }
+  first_end = __builtin_amdgcn_readfirstlane(first_end);
+  last_end = __builtin_amdgcn_readfirstlane(last_end);
   const size_t kbase = (size_t)(b * Hkv + hk) * m.ld * D;
   const float c2 = scale * LOG2E;
-
-  float4 kf[DC], vf[DC];
-#pragma unroll
-  for (int c = 0; c < DC; ++c) {
-    kf[c] = *reinterpret_cast<const float4*>(k + kbase + (size_t)jk * D + 16 * c + 4 * h);
-    vf[c] = *reinterpret_cast<const float4*>(v + kbase + (size_t)jk * D + 16 * c + 4 * h);
-  }
-#pragma unroll
-  for (int c = 0; c < DC; ++c) asm volatile("" ::"v"(kf[c].x), "v"(vf[c].x));
-  f32x4_t ak[DC], av[DC];
-#pragma unroll
-  for (int db = 0; db < DC; ++db) ak[db] = av[db] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   Dma dma;
   dma.init(tid);
@@ -335,7 +362,8 @@ __global__ __launch_bounds__(NT, 2) void dkdv_f32_kernel(
     dma.issue(q + (urow + q0) * D, N - q0, st);
     dma.issue(dout + (urow + q0) * D, N - q0, st + OFF_G);
   };
-  int hq_c = hk * G + s0 / per_head, u_c = lo + s0 % per_head;  // step being computed
+  const int hq_0 = (unsigned)s0 / (unsigned)per_head;
+  int hq_c = hk * G + hq_0, u_c = lo + s0 - hq_0 * per_head;    // step being computed
   int hq_i = hq_c, u_i = u_c;                                   // step being issued
   auto advance = [&](int& hq, int& u) {
     if (++u == lo + per_head) {
@@ -346,6 +374,19 @@ __global__ __launch_bounds__(NT, 2) void dkdv_f32_kernel(
   issue(hq_i, u_i, 0);
   advance(hq_i, u_i);
   if (s0 + 1 < s1) issue(hq_i, u_i, 1);
+  // (K and V rows to registers, behind the first steps' copies)
+  float4 kf[DC], vf[DC];
+#pragma unroll
+  for (int c = 0; c < DC; ++c) {
+    kf[c] = *reinterpret_cast<const float4*>(k + kbase + (size_t)jk * D + 16 * c + 4 * h);
+    vf[c] = *reinterpret_cast<const float4*>(v + kbase + (size_t)jk * D + 16 * c + 4 * h);
+  }
+#pragma unroll
+  for (int c = 0; c < DC; ++c) asm volatile("" ::"v"(kf[c].x), "v"(vf[c].x));
+  f32x4_t ak[DC], av[DC];
+#pragma unroll
+  for (int db = 0; db < DC; ++db) ak[db] = av[db] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
   for (int st = s0; st < s1; ++st) {
     const int stage = (st - s0) & 1;
     if (st + 1 < s1) LG_WAIT_VMCNT(LPT);
@@ -354,10 +395,10 @@ __global__ __launch_bounds__(NT, 2) void dkdv_f32_kernel(
     const int sq = stage * STAGE, sg = sq + OFF_G;
     const float* sL = reinterpret_cast<const float*>(smem + sq + OFF_L);
     const int r0 = u_c * TQ + 16 * rb0;
-    // this wave's two 16-row blocks (narrow: one) against its 16 keys
-    const int kind0 = r0 < N && !(narrow && wave > 3) ? lg_tile_kind(m, r0, min(r0 + 15, N - 1), kw0, kw1) : (int)LG_TILE_DEAD;
-    const int kind1 = r0 + 16 < N && !narrow ? lg_tile_kind(m, r0 + 16, min(r0 + 31, N - 1), kw0, kw1) : (int)LG_TILE_DEAD;
-    const bool masked = kind0 == LG_TILE_PARTIAL || kind1 == LG_TILE_PARTIAL || r0 + 31 >= N;
+    // this wave's 16-row blocks (two; narrow, and at head dim 128: one) against its 16 keys
+    auto some_live = [&](int r) { return r + 15 >= kw0 && r < last_end; };
+    const bool on0 = !idle && some_live(r0), on1 = NB2 == 2 && !narrow && some_live(r0 + 16);
+    const bool masked = r0 < kw1 || r0 + 16 * NB2 > first_end;
     auto run = [&](auto B0_, auto NB_) {
       constexpr int B0 = decltype(B0_)::value, NB = decltype(NB_)::value;
       f32x4_t s[NB], dp[NB];
@@ -418,7 +459,7 @@ __global__ __launch_bounds__(NT, 2) void dkdv_f32_kernel(
         for (int r = 0; r < 4; ++r) {
           const int row = r0 + 16 * (B0 + x) + 4 * h + r;
           float p = __builtin_amdgcn_exp2f(fmaf(s[x][r], c2, -ls[r] * LOG2E));
-          if (masked && !(row < N && lg_live(m, row, j))) p = 0.f;
+          if (masked && !((unsigned)(row - j) < seen)) p = 0.f;
           s[x][r] = p;
           dp[x][r] = p * (dp[x][r] - de[r]);
         }
@@ -434,9 +475,13 @@ __global__ __launch_bounds__(NT, 2) void dkdv_f32_kernel(
         }
       }
     };
-    if (kind0 != LG_TILE_DEAD && kind1 != LG_TILE_DEAD) run(I0{}, I2{});
-    else if (kind0 != LG_TILE_DEAD) run(I0{}, I1{});
-    else if (kind1 != LG_TILE_DEAD) run(I1{}, I1{});
+    if constexpr (NB2 == 2) {
+      if (on0 && on1) run(I0{}, I2{});
+      else if (on0) run(I0{}, I1{});
+      else if (on1) run(I1{}, I1{});
+    } else {
+      if (on0) run(I0{}, I1{});
+    }
     __syncthreads();  // everyone is done with this stage
     advance(hq_c, u_c);
     if (st + 2 < s1) {
@@ -447,8 +492,10 @@ __global__ __launch_bounds__(NT, 2) void dkdv_f32_kernel(
 
   // add the row blocks
   float4* so = reinterpret_cast<float4*>(smem);
-  const int give = narrow ? wave - 1 : wave - 4;  // LDS slot of a wave that is not an owner
-  if (!owner && !(narrow && wave > 3))
+  constexpr int GIVERS = TQ / 16 - 1;             // narrow: waves that are neither the owner nor idle
+  static_assert((GIVERS > 2 ? GIVERS : 2) * 2 * DC * 1024 <= 2 * STAGE, "their sums fit");
+  const int give = narrow ? wave - 1 : wave - 2;  // LDS slot of a wave that is not an owner
+  if (!owner && !idle)
 #pragma unroll
     for (int db = 0; db < DC; ++db) {
       so[(give * 2 * DC + db) * 64 + lane] = make_float4(ak[db][0], ak[db][1], ak[db][2], ak[db][3]);
@@ -456,7 +503,7 @@ __global__ __launch_bounds__(NT, 2) void dkdv_f32_kernel(
     }
   __syncthreads();
   if (owner)
-    for (int y = narrow ? 0 : wave; y < (narrow ? 3 : wave + 1); ++y)
+    for (int y = narrow ? 0 : wave; y < (narrow ? GIVERS : wave + 1); ++y)
 #pragma unroll
       for (int db = 0; db < DC; ++db) {
         const float4 a = so[(y * 2 * DC + db) * 64 + lane], c = so[(y * 2 * DC + DC + db) * 64 + lane];
@@ -475,7 +522,7 @@ __global__ __launch_bounds__(NT, 2) void dkdv_f32_kernel(
     return;
   }
   // partial sums: slot of (tile, part), then [dk | dv][key group][dim block][lane] float4
-  const size_t pslot = 2 * (size_t)64 * D;
+  const size_t pslot = 2 * (size_t)TK * D;
   const size_t main0 = ((size_t)bh * pt.nkt + kt) * pt.nsp;
   const size_t col0 = (size_t)heads * pt.nkt * pt.nsp + ((size_t)bh * pt.ncand + kt) * pt.ncc;
   // does a column part serve keys of group g?  (no other group's slot of a column part is written or read)
@@ -488,7 +535,7 @@ __global__ __launch_bounds__(NT, 2) void dkdv_f32_kernel(
 #pragma unroll
     for (int db = 0; db < DC; ++db) {
       lg_store_shared4(mine + ((kg * DC + db) * 64 + lane) * 4, ak[db]);
-      lg_store_shared4(mine + (((4 + kg) * DC + db) * 64 + lane) * 4, av[db]);
+      lg_store_shared4(mine + (((2 + kg) * DC + db) * 64 + lane) * 4, av[db]);
     }
   lg_shared_stores_done();
   __syncthreads();
@@ -498,7 +545,7 @@ __global__ __launch_bounds__(NT, 2) void dkdv_f32_kernel(
   if (s_before != (unsigned)(nmain + ncols - 1)) return;  // another part will be the last
   // the last one adds all parts in their order: wave = (key group, half of the dims), four parts' loads in flight
   constexpr int HB = DC / 2, AHEAD = 4;
-  const int g = wave & 3, db0 = (wave >> 2) * HB;
+  const int g = wave & 1, db0 = (wave >> 1) * HB;
   const int nsum = nmain + (col_group(g) ? ncols : 0);
   f32x4_t sk_[HB], sv_[HB];
 #pragma unroll
@@ -512,7 +559,7 @@ __global__ __launch_bounds__(NT, 2) void dkdv_f32_kernel(
 #pragma unroll
       for (int y = 0; y < HB; ++y) {
         a[x][y] = lg_load_shared4(src + ((g * DC + db0 + y) * 64 + lane) * 4);
-        c[x][y] = lg_load_shared4(src + (((4 + g) * DC + db0 + y) * 64 + lane) * 4);
+        c[x][y] = lg_load_shared4(src + (((2 + g) * DC + db0 + y) * 64 + lane) * 4);
       }
     }
 #pragma unroll
@@ -539,7 +586,8 @@ hipError_t launch_bwd(const float* q, const float* k, const float* v, const floa
   unsigned* arrived = (unsigned*)((char*)ws + pt.counters_off);
   float* part = (float*)((char*)ws + pt.part_off);
   const long long ncnt = pt.part_off > pt.counters_off ? (long long)heads * pt.nkt : 0;
-  const long long tl = (long long)pt.nqt * sh.Hq * sh.B;
+  const int nqt = ceil_div(sh.N, LG_F32_TQ);
+  const long long tl = (long long)nqt * sh.Hq * sh.B;
   const long long items = (long long)heads * ((long long)pt.nkt * pt.nsp + (long long)pt.ncand * pt.ncc);
   if (tl > 0x7fffffffLL - 8 || items > 0x7fffffffLL || ncnt > 0x7fffffffLL) return hipErrorInvalidValue;
   if (ev) {  // (nothing to set up on this path)
@@ -548,11 +596,11 @@ hipError_t launch_bwd(const float* q, const float* k, const float* v, const floa
   }
   const int total = (int)tl, run = lg_run_length(m, total, sh.B * sh.Hkv, 4 * (sh.Hq / sh.Hkv), false);
   dq_f32_kernel<D><<<dim3((unsigned)lg_run_grid(total, run)), NT, 0, s>>>(q, k, v, out, dout, lse, delta, dq, sh.Hq, sh.Hkv, sh.scale, m,
-                                                    lg_make_items(total, run, pt.nqt, sh.Hq, sh.Hkv), arrived, (int)ncnt);
+                                                    lg_make_items(total, run, nqt, sh.Hq, sh.Hkv), arrived, (int)ncnt);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (ev) (void)hipEventRecord(ev[2], s);
-  dkdv_f32_kernel<D><<<dim3((unsigned)items), NT, 0, s>>>(q, k, v, dout, lse, delta, dk, dv, sh.Hq, sh.Hkv, sh.scale,
+  dkdv_f32_kernel<D><<<dim3((unsigned)items), BNT, 0, s>>>(q, k, v, dout, lse, delta, dk, dv, sh.Hq, sh.Hkv, sh.scale,
                                                           m, pt, heads, arrived, part);
   e = hipGetLastError();
   if (ev) (void)hipEventRecord(ev[3], s);

@@ -14,7 +14,8 @@
 // `block`: they never change results, only which tiles count as PARTIAL.
 enum {
   LG_F32_TQ = 64, LG_F32_TK = 64,        // float32 kernels, forward / dq order
-  LG_F32_BTQ = 64, LG_F32_BTK = 64,      // float32 dk/dv kernel (key-tile major)
+  LG_F32_BTQ = 64, LG_F32_BTK = 64,      // float32 dk/dv (key-tile major), as listed by the host view:
+  LG_F32_KEYS = 32,                      // a workgroup takes half of such a tile's keys (at head dim 128 half its rows a step)
   LG_BF16_TQ = 256, LG_BF16_TK = 64,     // bf16 dq kernel with 64 rows per wave
   LG_BF16_TQ32 = 128,                    // bf16 forward, dq kernel with 32 rows per wave (64 keys per step as well)
   LG_BF16_BTQ = 64, LG_BF16_BTK = 256,   // bf16 dk/dv kernels (key-tile major), head dim 128

@@ -70,6 +70,16 @@ def test_heads_that_take_their_tiles_in_the_other_order(Hq, N, D, window):
     check_bwd(2, Hq, 16, N, D, 0, window, seed=6)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv,N,sink,window,block,stride", [
+    (2, 1, 31, 0, 31, 1, 0), (2, 2, 33, 16, 5, 1, 0), (3, 1, 65, 0, 40, 1, 0), (1, 1, 97, 17, 8, 1, 0),
+    (2, 1, 700, 0, 700, 1, 0), (4, 2, 900, 16, 64, 1, 0), (2, 1, 900, 33, 64, 1, 0), (2, 1, 530, 16, 48, 16, 3)])
+def test_float32_key_tiles(Hq, Hkv, N, sink, window, block, stride, D):
+    """32 keys per workgroup: lengths around the tile and the step, window and column parts (a sink of one group of 16
+    keys, of two, of two tiles), cut where few tiles leave the chip idle."""
+    check_bwd(1, Hq, Hkv, N, D, sink, window, block, stride, dtype=torch.float32, seed=8)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_peaked_scores_and_custom_scale(dtype):
     check_bwd(1, 2, 2, 600, 128, 16, 100, dtype=dtype, seed=4, q_mul=4.0, by_tensor_max=True)
