@@ -54,10 +54,15 @@ constexpr int btk_of(int D) { return D == 128 ? LG_BF16_BTK : LG_BF16_BTK64; }
 
 constexpr float LOG2E = 1.44269504088896340736f;
 
-// TOKEN (both kernels): the pattern is token-granular without strided columns (block <= 1,
-// stride 0).  The mask fields that are then known let the compiler drop the block / stride
-// arithmetic from the per-tile scheduling, and partial tiles are masked with two compares per
-// element instead of a per-element evaluation of the general predicate.
+// TOKEN (the 64-rows-per-wave kernels): the pattern is token-granular without strided columns (block <= 1, stride 0).  The
+// mask fields that are then known let the compiler drop the block / stride arithmetic from the per-tile scheduling.
+//
+// Masks.  A lane's live pairs of a PARTIAL tile are runs: in dq a few of its 32 registers (lg_key_bits), in dk/dv one run of
+// rows from its key on.  They are applied behind a real branch: as selects, which the compiler makes of a short condition
+// on `full`, they cost every whole tile (dq, 32 heads of 128, window 512: 574 -> 517 us; head dim 64, window 1024: 503 ->
+// 471).  A wave's class of a tile comes from bounds that it works out once (LgRows, LgKeys), and of the two blocks of 32
+// that a PARTIAL tile has a dead one is left out (dk/dv 64 x 512 tokens 482 -> 460 us, with 64/8 heads of 64 and strided
+// columns 1400 -> 1146).  With that, instances for token-granular patterns bring the 32-rows kernels nothing.
 
 // Sequences of different lengths side by side in each head, in one set of launches, longest first: those that take
 // the 64-rows-per-wave kernels are then the first ones, and long work items start first.  Lives in the workspace;
@@ -178,7 +183,7 @@ template <int D>
 struct LgDqTune {
   static constexpr int WAVES = D == 128 ? 2 : 3, AHEAD = D == 128 ? 3 : 2;
 };
-template <int D, bool TOKEN>
+template <int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LgDqTune<D>::WAVES, LgDqTune<D>::WAVES))) void
 dq_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
@@ -186,14 +191,6 @@ dq_bf16_kernel(
     float* __restrict__ ndelta, float* __restrict__ nlse, uint16_t* __restrict__ dq, int Hq, int Hkv, float scale,
     LgMask m_in, int nqt, int total, int run, LgBwdWork wk) {
   LgMask m = m_in;
-  if (TOKEN) {
-    m.b = 1;
-    m.stride = 0;
-    m.bshift = 0;
-    m.smask = -1;
-    m.sb = m.sink;
-    m.wb = m.window;
-  }
   using T = LgSwzTile<D>;
   constexpr int NT = 256;
   using Dma = LgDma<D, NT>;
@@ -254,6 +251,7 @@ dq_bf16_kernel(
   rd.init(n, g);
   const uint32_t lds0 = (uint32_t)(uintptr_t)LG_LDS_PTR(unsigned char, smem);
   const LgQSched qs = lg_qsched_init(m, q0, q1);
+  const LgRows wrows = lg_rows(m, qw0, qw1);
   auto issue = [&](int t, int stage) {
     const size_t off = (size_t)t * TK * D;
     dma.issue(kh + off, N - t * TK, lds0 + stage * STAGE);
@@ -263,7 +261,7 @@ dq_bf16_kernel(
   // patterns without strided columns walk the window run rotated (L2 sharing between neighbours)
   const LgQWalk qw = lg_qwalk_init(qs);
   auto next_tile = [&](int prev) -> int {
-    if (TOKEN || m.stride == 0) return prev < 0 ? lg_qwalk_first(qw) : lg_qwalk_next(qw, prev);
+    if (m.stride == 0) return prev < 0 ? lg_qwalk_first(qw) : lg_qwalk_next(qw, prev);
     return lg_qsched_next(m, qs, prev);
   };
   // Q and dO rows through the two stages' places into registers, out and the log-sum-exp once per row
@@ -315,28 +313,16 @@ dq_bf16_kernel(
     // A tile that is not live throughout for the workgroup's 128 rows is classified again for
     // this wave's 32 rows: most waves then find it wholly live or wholly dead (they sit it out).
     int kind = LG_TILE_FULL;
-    if (!lg_qsched_full(m, qs, t)) kind = lg_tile_kind(m, qw0, qw1, k0, k0 + TK - 1);
+    if (!lg_qsched_full(m, qs, t)) kind = lg_rows_kind(m, wrows, k0, k0 + TK - 1);
     const bool full = kind == LG_TILE_FULL;
     const int sk = stage * STAGE, sv = sk + T::BYTES;
-    uint32_t bits = 0xffffffffu;
-    if (kind == LG_TILE_PARTIAL && !TOKEN) bits = lg_key_bits(m, iq, k0, g);
-    // Token mode: row i sees the keys [i - window + 1, i] and the sink keys below
-    // min(sink, i + 1).  In tile coordinates (key = k0 + 4g + c, c a compile-time constant):
-    const int hi = i - k0 - 4 * g;         // c <= hi           : causal
-    const int lo = hi - (m.window - 1);    // c >= lo           : inside the window
-    const int se = m.sink - k0 - 4 * g;    // c < se (&& c <= hi): a sink key
-    const bool has_sink = k0 < m.sink;     // wave-uniform
-    auto dead = [&](int kb, int r) -> bool {
-      if (!TOKEN) return !(bits & (1u << (kb * 16 + r)));
-      const int c = 32 * kb + lg_crow(r, 0);
-      bool live = (unsigned)(c - lo) < (unsigned)m.window;
-      if (has_sink) live |= c < se && c <= hi;
-      return !live;
-    };
+    const uint32_t bits = full ? ~0u : lg_key_bits(m, iq, k0, g);  // bit 16 kb + r: the key of register r of block kb is live
 
     if (kind != LG_TILE_DEAD)
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
+      // (a PARTIAL tile may have a half without live pairs)
+      if (!full && __builtin_amdgcn_ballot_w64(((bits >> (16 * kb)) & 0xffffu) != 0) == 0) continue;
       constexpr int AHEAD = LgDqTune<D>::AHEAD;
       f32x16_t sc, dp;
 #pragma unroll
@@ -353,11 +339,15 @@ dq_bf16_kernel(
       cols.begin(read_cols);
       float ds[16];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        float p = __builtin_amdgcn_exp2f(fmaf(sc[r], sl2, -lse2));
-        if (!full && dead(kb, r)) p = 0.f;
-        ds[r] = p * (dp[r] - di);
+      for (int r = 0; r < 16; ++r) ds[r] = __builtin_amdgcn_exp2f(fmaf(sc[r], sl2, -lse2));
+      if (!full) {
+        asm volatile("; masked" ::: "memory");  // (a real branch: as selects the masks slowed whole tiles)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (!((bits >> (kb * 16 + r)) & 1)) ds[r] = 0.f;
       }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) ds[r] *= dp[r] - di;
       const bf16x8_t bop[2] = {lg_pack8(ds), lg_pack8(ds + 8)};
       cols.run(read_cols, [&](int u, bf16x8_t a) { acc[u % DB] = lg_mfma32(a, bop[u / DB], acc[u % DB]); });
     }
@@ -572,6 +562,13 @@ __device__ __forceinline__ float* lg_bwd_part_slot(const LgBwdWork& wk, const Lg
                         (btk_of(D) / 64 * LgSlot<D>::FLOATS);
 }
 
+// How many rows, from row j on, see key j (0 for keys past the end).
+__device__ __forceinline__ unsigned lg_rows_seeing(const LgMask& m, int j) {
+  if (j >= m.N) return 0;
+  const bool column = j < m.sink || (m.stride > 0 && lg_strided(m, lg_div_b(m, j)));
+  return (unsigned)((column ? m.N : lg_window_end(m, j)) - j);
+}
+
 // 32 query rows against the wave's 32 keys, in an order that keeps few values alive at a time:
 // S -> P -> (dV += dO^T P) -> dP -> dS -> (dK += Q^T dS).  sq, sg: the rows of Q and dO in LDS; sL: their -lse / scale,
 // 64 floats further on their -Delta; voff: the V rows of the wave's keys.
@@ -599,10 +596,12 @@ __device__ __forceinline__ void lg_dkdv_block(const unsigned char* smem, const L
     rows.run(q_rows, [&](int u, bf16x8_t a) { sc = lg_mfma32(a, kf[u], sc); });
     cols.begin(g_cols);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      float pv = __builtin_amdgcn_exp2f(sc[r] * sl2);
-      if (!full && dead(r)) pv = 0.f;
-      p[r] = pv;
+    for (int r = 0; r < 16; ++r) p[r] = __builtin_amdgcn_exp2f(sc[r] * sl2);
+    if (!full) {
+      asm volatile("; masked" ::: "memory");  // (a real branch: as selects the masks cost whole tiles 5 % at head dim 64)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (dead(r)) p[r] = 0.f;
     }
   }
   {
@@ -641,7 +640,7 @@ __device__ __forceinline__ void lg_dkdv_block(const unsigned char* smem, const L
   }
 }
 
-template <int D, bool TOKEN, bool COLUMN>
+template <int D, bool COLUMN>
 __global__ __launch_bounds__(btk_of(D) * 2) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 3, D == 128 ? 2 : 3))) void
 dkdv_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
@@ -649,14 +648,6 @@ dkdv_bf16_kernel(
     uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int Hq, int Hkv, float scale, LgMask m_in,
     int nkt, int total, int run, LgBwdWork wk) {
   LgMask m = m_in;
-  if (TOKEN) {
-    m.b = 1;
-    m.stride = 0;
-    m.bshift = 0;
-    m.smask = -1;
-    m.sb = m.sink;
-    m.wb = m.window;
-  }
   using T = LgSwzTile<D>;
   constexpr int TQ = LG_BF16_BTQ, TK = btk_of(D), NT = 2 * TK, NG = TK / 64;
   using Dma = LgDma<D, NT>;
@@ -720,6 +711,8 @@ dkdv_bf16_kernel(
     r0_w = (lg_qtile_window_hi(m, t1, TQ) + 1) * TQ;
   }
   const int j = kw0 + n;  // this lane's key
+  const LgKeys wkeys = lg_keys(m, kw0, kw0 + 31);
+  const unsigned seen = lg_rows_seeing(m, j);
 
   f32x16_t ak[DB], av[DB];
 #pragma unroll
@@ -834,32 +827,24 @@ dkdv_bf16_kernel(
     }
     const int q0 = u_c * TQ;
     u_c = (u_c == hi) ? lo : u_c + 1;
-    const int q1 = min(q0 + TQ - 1, N - 1);
-    // this wave's 32 keys against the step's 64 queries: a wave with no live pair sits the step
-    // out (most waves of the sink key tile do, once the queries are past its window)
+    // this wave's 32 keys against the step's two blocks of 32 queries, as far as they have live pairs (in most steps of the
+    // sink key tile, once the queries are past its window, most waves have none)
     if (COLUMN && (!active || q0 < r0_w)) continue;  // no group, or rows of its window part
-    const int kind = lg_tile_kind(m, q0, q1, kw0, kw0 + 31);
+    const int kind = lg_keys_kind(wkeys, q0, q0 + TQ - 1);
     if (kind == LG_TILE_DEAD) continue;
-    const bool full = kind == LG_TILE_FULL && q0 + TQ <= N;
     const int sq = VRES + buf * STAGE, sg = sq + OFF_G;
     const float* sL = reinterpret_cast<const float*>(smem + sq + OFF_L);
-    uint32_t bits = ~0u;
-    if (!full && !TOKEN) bits = lg_row_bits(m, j, q0, g);
-    // Token mode: key j is seen by the rows [j, j + window - 1] (by every row >= j if it is a
-    // sink key), below N.  In tile coordinates (row = q0 + 4g + c, c a compile-time constant):
-    const int lo_c = j - q0 - 4 * g;                                   // c >= lo_c : causal
-    const unsigned w_eff = j < m.sink ? 0x7fffffffu : (unsigned)m.window;  // c < lo_c + w_eff
-    const int n_c = N - q0 - 4 * g;                                    // c < n_c   : row exists
-    auto dead = [&](int qb, int r) -> bool {
-      if (!TOKEN) return !((bits >> (qb * 16 + r)) & 1);
-      const int c = 32 * qb + lg_crow(r, 0);
-      return !((unsigned)(c - lo_c) < w_eff && c < n_c);
-    };
-
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb)
+    auto block = [&](int qb, bool full) {
+      // register r: row r0 + 4g + c, which sees the key if it is one of the `seen` rows from j on
+      const int from = q0 + 32 * qb + 4 * g - j;
       lg_dkdv_block<D>(smem, rd, sq + qb * HALF, sg + qb * HALF, voff, sL + qb * 32, kf, ak, av, sl2, g, full,
-                       [&](int r) { return dead(qb, r); });
+                       [&](int r) { return !((unsigned)(from + lg_crow(r, 0)) < seen); });
+    };
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+      if (kind != LG_TILE_FULL && lg_keys_kind(wkeys, q0 + 32 * qb, q0 + 32 * qb + 31) == LG_TILE_DEAD) continue;
+      block(qb, kind == LG_TILE_FULL);
+    }
   }
 
   using Slot = LgSlot<D>;
@@ -1285,6 +1270,7 @@ __device__ __forceinline__ void dkdv_wide_item(
   __syncthreads();
 
   const int voff = wave * T::BYTES;  // this wave's 64 V rows
+  const LgKeys wkeys = lg_keys(m, kw0, kw0 + 63);
 
   // rows of the query head whose step is requested next
   const uint16_t* qh = q + ((size_t)(b * Hq + hq0) * m.ld + it.row0) * D;
@@ -1329,11 +1315,10 @@ __device__ __forceinline__ void dkdv_wide_item(
     }
     const int q0 = u_c * TQ;
     u_c = (u_c == hi) ? lo : u_c + 1;
-    const int q1 = min(q0 + TQ - 1, N - 1);
     if (COLUMN && (!active || q0 < r0_w)) continue;  // no group, or rows of its window part
-    const int kind = lg_tile_kind(m, q0, q1, kw0, kw0 + 63);
+    const int kind = lg_keys_kind(wkeys, q0, q0 + TQ - 1);
     if (kind == LG_TILE_DEAD) continue;
-    const bool full = kind == LG_TILE_FULL && q0 + TQ <= N;
+    const bool full = kind == LG_TILE_FULL;
     const int sq = VRES + buf * STAGE, sg = sq + OFF_G;
     const float* sL = reinterpret_cast<const float*>(smem + sq + OFF_L);
     // bit 16 qb + r of bits[kb]: pair (row of register r of query block qb, key j + 32 kb) is live
@@ -1645,6 +1630,7 @@ __device__ __forceinline__ void dq_wide_item(
                   __builtin_bit_cast(uint4, rd.read_rows(smem, ((x < 2 ? 0 : 4) + wave_s) * T::BYTES, x & 1, dc)));
   __syncthreads();
   const LgQSched qs = lg_qsched_init(m, q0, q1);
+  const LgRows wrows = lg_rows(m, qw0, qw1);
   auto issue = [&](int t, int stage) {
     const size_t off = (size_t)t * TK * D;
     dma.issue(kh + off, N - t * TK, lds0 + stage * STAGE);
@@ -1701,7 +1687,7 @@ __device__ __forceinline__ void dq_wide_item(
     }
     const int k0 = t * TK;
     int kind = LG_TILE_FULL;
-    if (!lg_qsched_full(m, qs, t)) kind = lg_tile_kind(m, qw0, qw1, k0, k0 + TK - 1);
+    if (!lg_qsched_full(m, qs, t)) kind = lg_rows_kind(m, wrows, k0, k0 + TK - 1);
     const int sk = stage * STAGE, sv = sk + T::BYTES;
     t = next_tile(t);
     stage = (stage + 1) % STAGES;
@@ -2066,16 +2052,11 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
     const dim3 grid((unsigned)lg_run_grid(total, run));
     wk.qt_first = a.qt_wide;
     wk.turn = lg_may_turn(nbh, 2 * a.qt_rest);
-#define LG_DQ_LAUNCH(DD, TT)                                                                                           \
-  dq_bf16_kernel<DD, TT><<<grid, 256, 0, s>>>(uq, uk, uv, uo, ug, lse, ndelta, nlse, dq, Hq, Hkv, scale, m, a.qt_rest, \
+#define LG_DQ_LAUNCH(DD)                                                                                               \
+  dq_bf16_kernel<DD><<<grid, 256, 0, s>>>(uq, uk, uv, uo, ug, lse, ndelta, nlse, dq, Hq, Hkv, scale, m, a.qt_rest, \
                                               total, run, wk)
-    if (a.D == 64) {
-      if (token) LG_DQ_LAUNCH(64, true);
-      else LG_DQ_LAUNCH(64, false);
-    } else {
-      if (token) LG_DQ_LAUNCH(128, true);
-      else LG_DQ_LAUNCH(128, false);
-    }
+    if (a.D == 64) LG_DQ_LAUNCH(64);
+    else LG_DQ_LAUNCH(128);
 #undef LG_DQ_LAUNCH
   }
   hipError_t e = hipGetLastError();
@@ -2083,8 +2064,8 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
   if (ev) (void)hipEventRecord(ev[2], s);
 
 #define LG_DKDV_ARGS uq, uk, uv, ug, nlse, ndelta, dk, dv, Hq, Hkv, scale, m
-#define LG_DKDV_LAUNCH(DD, TT, CC, GRID) \
-  dkdv_bf16_kernel<DD, TT, CC><<<GRID, 2 * btk_of(DD), 0, s>>>(LG_DKDV_ARGS, nkt, total, run, wk)
+#define LG_DKDV_LAUNCH(DD, CC, GRID) \
+  dkdv_bf16_kernel<DD, CC><<<GRID, 2 * btk_of(DD), 0, s>>>(LG_DKDV_ARGS, nkt, total, run, wk)
   if (nlone > 0) {
     const dim3 grid((unsigned)(nlone * Hq * a.B));
     if (a.D == 64) dkdv_lone_bf16_kernel<64><<<grid, 512, 0, s>>>(uq, uk, uv, ug, nlse, ndelta, Hq, Hkv, scale, m, wk);
@@ -2097,7 +2078,7 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
     const dim3 grid((unsigned)(a.citems * Hq * a.B));
     // column parts are long whatever the window is: the 64-keys form whenever it exists
     if (a.D == 128) dkdv_wide_bf16_kernel<false, true><<<grid, 256, 0, s>>>(LG_DKDV_ARGS, nkt, total, run, wk);
-    else LG_DKDV_LAUNCH(64, false, true, grid);
+    else LG_DKDV_LAUNCH(64, true, grid);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -2117,13 +2098,8 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
     const dim3 grid((unsigned)(wk.by_tile ? total * nparts : (int)lg_run_grid(total, run)));
     wk.items = items + a.kt_wide;
     wk.turn = lg_may_turn(nbh, nkt);
-    if (a.D == 64) {
-      if (token) LG_DKDV_LAUNCH(64, true, false, grid);
-      else LG_DKDV_LAUNCH(64, false, false, grid);
-    } else {
-      if (token) LG_DKDV_LAUNCH(128, true, false, grid);
-      else LG_DKDV_LAUNCH(128, false, false, grid);
-    }
+    if (a.D == 64) LG_DKDV_LAUNCH(64, false, grid);
+    else LG_DKDV_LAUNCH(128, false, grid);
   }
 #undef LG_DKDV_LAUNCH
 #undef LG_DKDV_ARGS

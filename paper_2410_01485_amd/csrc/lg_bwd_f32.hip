@@ -11,7 +11,7 @@
 // share a SIMD.  dk/dv uses 4 waves per 32 keys: 2 groups of 16 keys x 2 halves of a step's query rows (64, at head dim
 // 128 32), two workgroups per CU: as 8 waves per 64 keys one workgroup fitted a CU (167 registers, 66 KB; at head dim 128
 // 256 with spills), so that 280 work items were two rounds on 256 CUs, and every window had to be cut in two.  16/8 heads
-// of 64, 1024 tokens, window 128: dk/dv 44 -> 29 us (of that 3 from the masks, LgF32Rows); 4 heads of 128, 4096 tokens,
+// of 64, 1024 tokens, window 128: dk/dv 44 -> 29 us (of that 3 from the masks, LgF32Row); 4 heads of 128, 4096 tokens,
 // window 512: 168 -> 120.  Bound: the float32 matrix rate, 4096 cycles of a step's 6600; the rest is what one wave per
 // SIMD cannot hide (masks, the next copies' issue, the barriers).
 //
@@ -103,8 +103,9 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void dq_f32_kernel(
     dma.issue(v + kbase + (size_t)t * TK * D, N - t * TK, lds0 + stage * STAGE + T::BYTES);
   };
   const LgQSched qs = lg_qsched_init(m, q0, q1);
-  LgF32Rows lr;
-  lr.init(m, qw0, qw1, i);
+  const LgRows rows = lg_rows(m, qw0, qw1);
+  LgF32Row row;
+  row.init(m, i);
   int t = lg_qsched_next(m, qs, -1);
   issue(t, 0);
   int tn = lg_qsched_next(m, qs, t);
@@ -117,8 +118,8 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void dq_f32_kernel(
     const int rb0 = 2 * kh, kk = t * TK + 32 * kh;
     int kind0 = LG_TILE_FULL, kind1 = LG_TILE_FULL;  // of the wave's two 16-key blocks
     if (!lg_qsched_full(m, qs, t)) {
-      kind0 = lr.kind(m, kk);
-      kind1 = lr.kind(m, kk + 16);
+      kind0 = lg_rows_kind(m, rows, kk, kk + 15);
+      kind1 = lg_rows_kind(m, rows, kk + 16, kk + 31);
     }
     const bool masked = kind0 == LG_TILE_PARTIAL || kind1 == LG_TILE_PARTIAL;
     // as in the forward: units of matrix instructions, their LDS operands requested one unit ahead
@@ -170,11 +171,19 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void dq_f32_kernel(
 #pragma unroll
       for (int x = 0; x < NB; ++x)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          float p = __builtin_amdgcn_exp2f(fmaf(s[x][r], c2, -lse2));
-          if (masked && !lr.live(m, kk + 16 * (B0 + x) + 4 * h + r)) p = 0.f;
-          s[x][r] = p * (dp[x][r] - di);
-        }
+        for (int r = 0; r < 4; ++r) s[x][r] = __builtin_amdgcn_exp2f(fmaf(s[x][r], c2, -lse2));
+      if (masked) {
+        asm volatile("; masked" ::: "memory");  // (a real branch: nothing of it in whole tiles)
+#pragma unroll
+        for (int x = 0; x < NB; ++x)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (!row.live(m, kk + 16 * (B0 + x) + 4 * h + r)) s[x][r] = 0.f;
+      }
+#pragma unroll
+      for (int x = 0; x < NB; ++x)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s[x][r] *= dp[x][r] - di;
 #pragma unroll
       for (int u = 0; u < 4 * NB; ++u) {
         if (u + 1 < 4 * NB) read_cols(u + 1);
@@ -454,15 +463,23 @@ __global__ __launch_bounds__(BNT, 2) void dkdv_f32_kernel(
       }
 #pragma unroll
       for (int x = 0; x < NB; ++x) {
-        const float ls[4] = {l4[x].x, l4[x].y, l4[x].z, l4[x].w}, de[4] = {d4[x].x, d4[x].y, d4[x].z, d4[x].w};
+        const float ls[4] = {l4[x].x, l4[x].y, l4[x].z, l4[x].w};
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = r0 + 16 * (B0 + x) + 4 * h + r;
-          float p = __builtin_amdgcn_exp2f(fmaf(s[x][r], c2, -ls[r] * LOG2E));
-          if (masked && !((unsigned)(row - j) < seen)) p = 0.f;
-          s[x][r] = p;
-          dp[x][r] = p * (dp[x][r] - de[r]);
-        }
+        for (int r = 0; r < 4; ++r) s[x][r] = __builtin_amdgcn_exp2f(fmaf(s[x][r], c2, -ls[r] * LOG2E));
+      }
+      if (masked) {
+        asm volatile("; masked" ::: "memory");
+#pragma unroll
+        for (int x = 0; x < NB; ++x)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (!((unsigned)(r0 + 16 * (B0 + x) + 4 * h + r - j) < seen)) s[x][r] = 0.f;
+      }
+#pragma unroll
+      for (int x = 0; x < NB; ++x) {
+        const float de[4] = {d4[x].x, d4[x].y, d4[x].z, d4[x].w};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dp[x][r] = s[x][r] * (dp[x][r] - de[r]);
       }
 #pragma unroll
       for (int u = 0; u < 4 * NB; ++u) {

@@ -52,26 +52,13 @@ struct LgF32Reader {
   }
 };
 
-// The live keys of a wave's 16 query rows, as the forward and dq kernels ask for them once per block of 16 keys (class)
-// and once per element (mask): what a row's or the wave's window begins with is worked out once.  By lg_tile_kind and
-// lg_live for every block and element it was 1000 and 1500 of a step's 8900 cycles.
-struct LgF32Rows {
-  int q0, q1;    // the wave's rows
-  int w0, w1;    // first key of the first and of the last row's window
-  int i, w;      // the lane's row, the first key of its window
-  __device__ __forceinline__ void init(const LgMask& m, int qw0, int qw1, int row) {
-    q0 = qw0;
-    q1 = qw1;
-    w0 = (lg_div_b(m, qw0) - m.wb + 1) * m.b;
-    w1 = (lg_div_b(m, qw1) - m.wb + 1) * m.b;
+// The live keys of a lane's query row, as the forward and dq kernels ask for them per element of PARTIAL blocks.  With
+// lg_tile_kind and lg_live for every block and element, class and mask were 1000 and 1500 of a dk/dv step's 8900 cycles.
+struct LgF32Row {
+  int i, w;  // the row, the first key of its window
+  __device__ __forceinline__ void init(const LgMask& m, int row) {
     i = row;
     w = (lg_div_b(m, min(row, m.N - 1)) - m.wb + 1) * m.b;
-  }
-  // as lg_tile_kind(m, q0, q1, k, k + 15), but a block of sink keys and others may be PARTIAL where it is FULL
-  __device__ __forceinline__ int kind(const LgMask& m, int k) const {
-    if (m.stride > 0) return lg_tile_kind(m, q0, q1, k, k + 15);
-    if (k > q1 || (k + 15 < w0 && k >= m.sink)) return LG_TILE_DEAD;
-    return k + 15 <= q0 && (k >= w1 || k + 15 < m.sink) ? LG_TILE_FULL : LG_TILE_PARTIAL;
   }
   __device__ __forceinline__ bool live(const LgMask& m, int key) const {  // as lg_live(m, i, key) for rows below N
     return key <= i && (key >= w || key < m.sink || (m.stride > 0 && lg_strided(m, lg_div_b(m, key))));

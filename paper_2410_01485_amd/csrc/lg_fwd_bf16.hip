@@ -40,13 +40,10 @@ struct LgFwdTune {
     static constexpr int WAVES = D == 128 ? 3 : 4, AHEAD = D == 128 ? 2 : 3, AHEAD_PV = 4;
 };
 
-// TOKEN: the pattern is token-granular without strided columns (block <= 1, stride 0).  The
-// mask fields that are then known let the compiler drop the block / stride arithmetic from
-// the per-tile scheduler, and partial tiles are masked with two compares per element.
 // PackT: LgNoPack for the batch layout (every (b, head) has the same query tiles), LgPack for
 // sequences of different lengths side by side in each head (B = 1).
 struct LgNoPack {};
-template <int D, bool TOKEN, typename PackT>
+template <int D, typename PackT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>::WAVES, LgFwdTune<D>::WAVES))) void fwd_bf16_kernel(const uint16_t* __restrict__ q,
                                                       const uint16_t* __restrict__ k,
                                                       const uint16_t* __restrict__ v,
@@ -56,14 +53,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
                                                       PackT pack) {
   constexpr bool PACK = !__is_same(PackT, LgNoPack);
   LgMask m = m_in;
-  if (TOKEN) {
-    m.b = 1;
-    m.stride = 0;
-    m.bshift = 0;
-    m.smask = -1;
-    m.sb = m.sink;
-    m.wb = m.window;
-  }
   using T = LgSwzTile<D>;
   using Dma = LgDma<D, NT>;
   constexpr int DC = D / 16;            // 16-wide contraction chunks of the head dim
@@ -121,10 +110,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
   auto issue_v = [&](int t) { dma.issue(vh + (size_t)t * TK * D, N - t * TK, lds0 + 2 * T::BYTES); };
   // K tiles are requested up to two ahead of the one being computed, its own V tile behind the barrier that opens it
   const LgQSched qs = lg_qsched_init(m, q0, q1);
+  const LgRows wrows = lg_rows(m, qw0, qw1);
   // patterns without strided columns walk the window run rotated (L2 sharing between neighbours)
   const LgQWalk qw = lg_qwalk_init(qs);
   auto next_tile = [&](int prev) -> int {
-    if (TOKEN || m.stride == 0) return prev < 0 ? lg_qwalk_first(qw) : lg_qwalk_next(qw, prev);
+    if (m.stride == 0) return prev < 0 ? lg_qwalk_first(qw) : lg_qwalk_next(qw, prev);
     return lg_qsched_next(m, qs, prev);
   };
   int t = next_tile(-1);  // tile to compute next
@@ -160,7 +150,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
     // A tile that is not live throughout for the workgroup's 128 rows is classified again for
     // this wave's 32 rows: most waves then find it wholly live or wholly dead (they sit it out).
     int kind = LG_TILE_FULL;
-    if (!lg_qsched_full(m, qs, t)) kind = lg_tile_kind(m, qw0, qw1, k0, k0 + TK - 1);
+    if (!lg_qsched_full(m, qs, t)) kind = lg_rows_kind(m, wrows, k0, k0 + TK - 1);
     const bool full = kind == LG_TILE_FULL;
     const int sk = buf * T::BYTES;   // byte offsets of the K and V tiles inside smem
     const int sv = 2 * T::BYTES;
@@ -184,23 +174,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
     }
 
     // ---- online softmax (log2 domain) ----
-    if (!full && TOKEN) {
-      // Row i sees the keys [i - window + 1, i] and the sink keys below min(sink, i + 1).  In
-      // tile coordinates (key = k0 + 4g + c, c a compile-time constant per register):
-      const int hi = i - k0 - 4 * g;           // c <= hi          : causal
-      const int lo = hi - (m.window - 1);      // c >= lo          : inside the window
-      const int se = m.sink - k0 - 4 * g;      // c < se (&& c <= hi): a sink key
-      const bool has_sink = k0 < m.sink;       // wave-uniform
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int c = 32 * kb + lg_crow(r, 0);
-          bool live = (unsigned)(c - lo) < (unsigned)m.window;
-          if (has_sink) live |= c < se && c <= hi;
-          if (!live) sacc[kb][r] = -INFINITY;
-        }
-    } else if (!full) {
+    if (!full) {
       const uint32_t bits = lg_key_bits(m, min(i, N - 1), k0, g);  // a few runs of registers, in closed form
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
@@ -297,18 +271,12 @@ hipError_t lg_launch_fwd_bf16(const void* q, const void* k, const void* v, void*
   const float sl2 = sh.scale * 1.44269504088896340736f;
   const LgItems items = lg_make_items(total, run, nqt, sh.Hq, sh.Hkv);
   const dim3 grid((unsigned)lg_run_grid(total, run));
-  const bool token = m.b == 1 && m.stride == 0;
-#define LG_FWD_LAUNCH(DD, TT)                                                                            \
-  fwd_bf16_kernel<DD, TT, LgNoPack><<<grid, NT, 0, s>>>((const uint16_t*)q, (const uint16_t*)k,          \
+#define LG_FWD_LAUNCH(DD)                                                                                \
+  fwd_bf16_kernel<DD, LgNoPack><<<grid, NT, 0, s>>>((const uint16_t*)q, (const uint16_t*)k,          \
                                                         (const uint16_t*)v, (uint16_t*)out, lse, sh.Hq,  \
                                                         sh.Hkv, sl2, m, items, LgNoPack{})
-  if (sh.D == 64) {
-    if (token) LG_FWD_LAUNCH(64, true);
-    else LG_FWD_LAUNCH(64, false);
-  } else {
-    if (token) LG_FWD_LAUNCH(128, true);
-    else LG_FWD_LAUNCH(128, false);
-  }
+  if (sh.D == 64) LG_FWD_LAUNCH(64);
+  else LG_FWD_LAUNCH(128);
 #undef LG_FWD_LAUNCH
   return hipGetLastError();
 }
@@ -334,18 +302,12 @@ hipError_t lg_launch_fwd_bf16_pack(const void* q, const void* k, const void* v, 
   const float sl2 = sh.scale * 1.44269504088896340736f;
   const LgItems items = lg_make_items(total, run, nqt, sh.Hq, sh.Hkv);
   const dim3 grid((unsigned)lg_run_grid(total, run));
-  const bool token = tmpl.b == 1 && tmpl.stride == 0;
-#define LG_FWD_LAUNCH(DD, TT)                                                                          \
-  fwd_bf16_kernel<DD, TT, LgPack><<<grid, NT, 0, s>>>((const uint16_t*)q, (const uint16_t*)k,          \
+#define LG_FWD_LAUNCH(DD)                                                                              \
+  fwd_bf16_kernel<DD, LgPack><<<grid, NT, 0, s>>>((const uint16_t*)q, (const uint16_t*)k,          \
                                                       (const uint16_t*)v, (uint16_t*)out, lse, sh.Hq,  \
                                                       sh.Hkv, sl2, tmpl, items, pack)
-  if (sh.D == 64) {
-    if (token) LG_FWD_LAUNCH(64, true);
-    else LG_FWD_LAUNCH(64, false);
-  } else {
-    if (token) LG_FWD_LAUNCH(128, true);
-    else LG_FWD_LAUNCH(128, false);
-  }
+  if (sh.D == 64) LG_FWD_LAUNCH(64);
+  else LG_FWD_LAUNCH(128);
 #undef LG_FWD_LAUNCH
   return hipGetLastError();
 }

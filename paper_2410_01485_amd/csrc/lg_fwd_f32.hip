@@ -71,8 +71,9 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_f32_kernel(const floa
     dma.issue(v + kbase + (size_t)t * TK * D, N - t * TK, lds0 + stage * STAGE + T::BYTES);
   };
   const LgQSched qs = lg_qsched_init(m, q0, q1);
-  LgF32Rows lr;
-  lr.init(m, qw0, qw1, i);
+  const LgRows rows = lg_rows(m, qw0, qw1);
+  LgF32Row row;
+  row.init(m, i);
   int t = lg_qsched_next(m, qs, -1);
   issue(t, 0);
   int tn = lg_qsched_next(m, qs, t);
@@ -85,8 +86,8 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_f32_kernel(const floa
     const int rb0 = 2 * kh, kk = t * TK + 32 * kh;
     int kind0 = LG_TILE_FULL, kind1 = LG_TILE_FULL;  // of the wave's two 16-key blocks
     if (!lg_qsched_full(m, qs, t)) {
-      kind0 = lr.kind(m, kk);
-      kind1 = lr.kind(m, kk + 16);
+      kind0 = lg_rows_kind(m, rows, kk, kk + 15);
+      kind1 = lg_rows_kind(m, rows, kk + 16, kk + 31);
     }
     const bool masked = kind0 == LG_TILE_PARTIAL || kind1 == LG_TILE_PARTIAL;
     // Blocks B0 .. B0 + NB - 1 of the half tile, as a straight sequence of units whose LDS operands are requested one
@@ -126,7 +127,7 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_f32_kernel(const floa
         for (int x = 0; x < NB; ++x)
 #pragma unroll
           for (int r = 0; r < 4; ++r)
-            if (!lr.live(m, kk + 16 * (B0 + x) + 4 * h + r)) s[x][r] = -INFINITY;
+            if (!row.live(m, kk + 16 * (B0 + x) + 4 * h + r)) s[x][r] = -INFINITY;
       float mx = -INFINITY;
 #pragma unroll
       for (int x = 0; x < NB; ++x) mx = fmaxf(mx, fmaxf(fmaxf(s[x][0], s[x][1]), fmaxf(s[x][2], s[x][3])));

@@ -216,6 +216,22 @@ LG_HD int lg_tile_kind(const LgMask& m, int q0, int q1, int k0, int k1) {
   return (lg_div_b(m, q1) - lg_div_b(m, j) < m.wb) ? LG_TILE_FULL : LG_TILE_PARTIAL;
 }
 
+// The same for query rows [q0, q1] that many tiles are asked about (a wave's rows): their windows' first keys are worked
+// out once, and without strided columns a tile takes four comparisons where lg_tile_kind takes 500 cycles.
+struct LgRows {
+  int q0, q1;
+  int w0, w1;  // first key of the first and of the last row's window
+};
+LG_HD LgRows lg_rows(const LgMask& m, int q0, int q1) {
+  return LgRows{q0, q1, (lg_div_b(m, q0) - m.wb + 1) * m.b, (lg_div_b(m, q1) - m.wb + 1) * m.b};
+}
+LG_HD int lg_rows_kind(const LgMask& m, const LgRows& r, int k0, int k1) {
+  if (m.stride > 0) return lg_tile_kind(m, r.q0, r.q1, k0, k1);
+  if (k0 > r.q1 || (k0 >= m.sink && k1 < r.w0)) return LG_TILE_DEAD;
+  const int j = k0 > m.sink ? k0 : m.sink;  // first key that is not a sink key
+  return k1 <= r.q0 && (j > k1 || j >= r.w1) ? LG_TILE_FULL : LG_TILE_PARTIAL;
+}
+
 // Next live key tile (tile = keys [t*Tk, t*Tk+Tk-1]) after tile `prev` for the query
 // rows [q0, q1]; pass prev = -1 to get the first.  Returns -1 when there is none.
 // Tk must be a power of two.
@@ -398,6 +414,37 @@ LG_HD uint32_t lg_row_bits(const LgMask& m, int j, int q0, int g) {
   const int qe = kb + m.wb;                 // first block whose rows no longer see the key through the window
   const int end = (column || qe >= nb) ? m.N : qe * m.b;
   return lg_reg_run(lg_clamp_off(j - off), lg_clamp_off(end - off));
+}
+
+// The rows that see a key are one run, from the key to an end; of the keys [k0, k1] that many steps of query rows are asked
+// about (a wave's keys, k1 may run past N - 1): the ends of the runs that end first and last, worked out once.
+struct LgKeys {
+  int k0, k1;
+  int first_end, last_end;  // (first_end: 0 where k1 runs past N - 1; a window's end where some keys are columns)
+};
+LG_HD int lg_window_end(const LgMask& m, int k) {
+  const int e = lg_div_b(m, k) + m.wb;
+  return e >= lg_div_b(m, m.N - 1) + 1 ? m.N : e * m.b;
+}
+LG_HD LgKeys lg_keys(const LgMask& m, int k0, int k1) {
+  LgKeys r = {k0, k1, 0, 0};
+  if (k0 >= m.N) return r;
+  const int kl = k1 < m.N - 1 ? k1 : m.N - 1;
+  bool any = k0 < m.sink, all = kl < m.sink;  // column keys
+  if (m.stride > 0) {
+    const int kb = lg_div_b(m, k0), f = lg_next_strided_block(m, kb), kbl = lg_div_b(m, kl);
+    any = any || f <= kbl;
+    all = all || m.stride == 1 || (f == kb && kbl == kb);
+  }
+  r.last_end = any ? m.N : lg_window_end(m, kl);
+  r.first_end = k1 > kl ? 0 : all ? m.N : lg_window_end(m, k0);
+  return r;
+}
+// Rows [q0, q1] (q1 may run past N - 1: never FULL) against those keys.  As lg_tile_kind, but PARTIAL for keys that are
+// FULL only because some of them are columns.
+LG_HD int lg_keys_kind(const LgKeys& r, int q0, int q1) {
+  if (q1 < r.k0 || q0 >= r.last_end) return LG_TILE_DEAD;
+  return q0 >= r.k1 && q1 < r.first_end ? LG_TILE_FULL : LG_TILE_PARTIAL;
 }
 
 // ---------------------------------------------------------------------------------

@@ -70,6 +70,26 @@ def test_heads_that_take_their_tiles_in_the_other_order(Hq, N, D, window):
     check_bwd(2, Hq, 16, N, D, 0, window, seed=6)
 
 
+@pytest.mark.parametrize("N,sink,window,block,stride", [(3200, 0, 2600, 1, 0), (3140, 64, 2624, 64, 0), (3100, 64, 2304, 64, 8)])
+def test_dq_in_64_row_form(N, sink, window, block, stride):
+    """32 heads, 42 or more key tiles per query tile and a ragged length: dq with 64 rows per wave.  Sampled rows and keys of
+    single heads: the first rows, the sink keys, where the window starts to slide, the last rows."""
+    Hq, Hkv, D = 32, 8, 128
+    q, k, v, g = lg_synth.prefill_inputs(1, Hq, Hkv, N, D, 9, torch.bfloat16, with_dout=True, device=DEV)
+    dq, dk, dv = run_fwd_bwd(q, k, v, g, sink, window, block, stride)
+    tol, rel = TOL_OUT[torch.bfloat16], TOL_REL[torch.bfloat16]
+    for h, r0, r1 in ((0, 0, 40), (13, 2590, 2640), (31, N - 50, N)):
+        a = [f32np(x) for x in (q[:, h:h + 1], k[:, h // 4:h // 4 + 1], v[:, h // 4:h // 4 + 1], g[:, h:h + 1])]
+        w = O.bwd(*a, sink, window, block, stride, rows=(r0, r1), keys=(0, 1))
+        al = dq_delta_allowance(a[0], a[1], a[3], w["out"], sink, window, block, stride, rows=(r0, r1))
+        assert_close(f32np(dq[0, h, r0:r1]), w["dq"][0, 0, r0:r1], tol, rel, "dq head %d" % h, allow=al[0, 0, r0:r1])
+    for hk, k0, k1 in ((0, 0, 30), (5, 700, 730), (7, N - 30, N)):  # (a kv head's gradients: four query heads)
+        a = [f32np(x) for x in (q[:, 4 * hk:4 * hk + 4], k[:, hk:hk + 1], v[:, hk:hk + 1], g[:, 4 * hk:4 * hk + 4])]
+        w = O.bwd(*a, sink, window, block, stride, rows=(0, 1), keys=(k0, k1))
+        assert_close(f32np(dk[0, hk, k0:k1]), w["dk"][0, 0, k0:k1], tol, rel, "dk head %d" % hk)
+        assert_close(f32np(dv[0, hk, k0:k1]), w["dv"][0, 0, k0:k1], tol, rel, "dv head %d" % hk)
+
+
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("Hq,Hkv,N,sink,window,block,stride", [
     (2, 1, 31, 0, 31, 1, 0), (2, 2, 33, 16, 5, 1, 0), (3, 1, 65, 0, 40, 1, 0), (1, 1, 97, 17, 8, 1, 0),

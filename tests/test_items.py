@@ -1,4 +1,5 @@
-"""Which item a workgroup takes: division by multiplication, and the items of a launch each taken exactly once."""
+"""Which item a workgroup takes: division by multiplication, and the items of a launch each taken exactly once; classes of
+tiles and live rows from bounds that a wave works out once."""
 import os
 import subprocess
 
@@ -43,11 +44,56 @@ int main() {
 }
 """
 
+KINDS = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "lg_mask.h"
+// classes and runs from bounds worked out once, against the general class and the predicate
+int main() {
+  std::srand(5);
+  auto rnd = [](int n) { return std::rand() % n; };
+  const int blocks[] = {1, 1, 2, 16, 48, 64, 100}, strides[] = {0, 0, 0, 1, 2, 3, 8}, lens[] = {16, 32, 64};
+  for (int it = 0; it < 400000; ++it) {
+    const int N = 1 + rnd(it % 3 ? 300 : 3000), b = blocks[rnd(7)], st = strides[rnd(7)];
+    const LgMask m = lg_make_mask(N, b * rnd(6), b * (1 + rnd(20)), b, st);
+    const int q0 = rnd(N), q1 = q0 + lens[rnd(3)] - 1 < N ? q0 + lens[rnd(3)] - 1 : N - 1, qe = q1 < q0 ? q0 : (q1 < N ? q1 : N - 1);
+    const int k0 = rnd(N), k1 = k0 + lens[rnd(3)] - 1;
+    const int want = lg_tile_kind(m, q0, qe, k0, k1);
+    if (lg_rows_kind(m, lg_rows(m, q0, qe), k0, k1) != want) { std::printf("rows: N %d b %d st %d q %d..%d k %d..%d\n", N, b, st, q0, qe, k0, k1); return 1; }
+    const LgKeys ks = lg_keys(m, k0, k1);
+    const int got = lg_keys_kind(ks, q0, qe);
+    // (PARTIAL is allowed for FULL where some of the keys are columns; nothing else)
+    if (got != want && !(got == LG_TILE_PARTIAL && want == LG_TILE_FULL && lg_has_column_key(m, k0, k1 < N ? k1 : N - 1))) {
+      std::printf("keys: N %d b %d st %d q %d..%d k %d..%d got %d want %d\n", N, b, st, q0, qe, k0, k1, got, want);
+      return 2;
+    }
+    if (lg_keys_kind(ks, N - 1 - rnd(N), N) == LG_TILE_FULL) return 3;  // rows past the end
+    if (lg_keys_kind(lg_keys(m, N + rnd(50), N + 100), q0, qe) != LG_TILE_DEAD) return 4;  // keys past the end
+    const int j = rnd(N), i = rnd(N);
+    const bool column = j < m.sink || (m.stride > 0 && lg_strided(m, lg_div_b(m, j)));
+    const unsigned seen = (unsigned)((column ? m.N : lg_window_end(m, j)) - j);
+    if (((unsigned)(i - j) < seen) != lg_live(m, i, j)) { std::printf("seen: N %d b %d st %d i %d j %d\n", N, b, st, i, j); return 5; }
+    const int w = (lg_div_b(m, i) - m.wb + 1) * m.b;
+    const bool live = j <= i && (j >= w || j < m.sink || (m.stride > 0 && lg_strided(m, lg_div_b(m, j))));
+    if (live != lg_live(m, i, j)) return 6;
+  }
+  return 0;
+}
+"""
 
-@pytest.mark.parametrize("opt", ["-O0", "-O2"])
-def test_division_by_multiplication_and_items(tmp_path, opt):
-    src, exe = tmp_path / "items.cpp", tmp_path / "items"
-    src.write_text(PROGRAM)
+
+def run(tmp_path, program, opt):
+    src, exe = tmp_path / "program.cpp", tmp_path / "program"
+    src.write_text(program)
     subprocess.check_call(["g++", "-std=c++17", opt, "-I", CSRC, str(src), "-o", str(exe)])
     r = subprocess.run([str(exe)], stdout=subprocess.PIPE, text=True)
     assert r.returncode == 0, (r.returncode, r.stdout)
+
+
+def test_classes_and_runs_from_bounds(tmp_path):
+    run(tmp_path, KINDS, "-O2")
+
+
+@pytest.mark.parametrize("opt", ["-O0", "-O2"])
+def test_division_by_multiplication_and_items(tmp_path, opt):
+    run(tmp_path, PROGRAM, opt)
