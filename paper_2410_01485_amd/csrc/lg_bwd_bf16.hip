@@ -36,7 +36,7 @@
 // 461 -> 390 us; 512 590 -> 570, 830 -> 782; 2048 (64 rows per wave) 1545 -> 1493, 1910 -> 1875; 64 x 512 tokens 465 -> 380,
 // 630 -> 495 (some of that from the order of the tiles, lg_may_turn).
 //
-// For head dim 128 and long windows (dq 32 or more tiles, dk/dv 16) both kernels have a second form with 64 rows
+// For head dim 128 and long windows (dq 42 or more tiles, dk/dv 20) both kernels have a second form with 64 rows
 // (keys) per wave, one wave per SIMD and the accumulators in AGPRs (further down): every operand
 // read from LDS then feeds two matrix instructions.
 #include <algorithm>
@@ -1864,14 +1864,17 @@ Columns columns_of(const LgMask& m, int D) {
 
 // Which kernels a sequence takes: the 64-rows-per-wave forms (head dim 128) start up and drain slower, so they
 // need a number of steps per workgroup.
-// dq: by the key tiles of an average query tile: its window, plus the strided columns below it (32 heads, 32768 tokens:
-// window 900 923 us against 980 in the 64-rows form, 1300 1121 : 1185, 2048 1625 : 1617, 4096 at 65536 5941 : 5502)
-bool dq_wide(const LgMask& m, int D) {
+// dq: by the key tiles of an average query tile: its window, plus the strided columns below it (32 heads, 32768 tokens, 32
+// rows per wave : 64: window 2048 1458 us : 1471, 2600 1822 : 1792, 4096 2682 : 2547; 64-token blocks, window 192 and every
+// 8th block a column 1662 : 1718), and only with enough work items of 256 rows (4 heads, 6000 tokens, causal 150 : 192).
+bool dq_wide(const LgMask& m, int D, int Hq) {
   const int col_tiles = m.stride > 0 ? (m.N / 2) / (m.b * m.stride) * ((m.b + LG_BF16_TK - 1) / LG_BF16_TK) : 0;
-  return D == 128 && (m.wb * m.b + LG_BF16_TQ) / LG_BF16_TK + col_tiles >= 32;
+  return D == 128 && (m.wb * m.b + LG_BF16_TQ) / LG_BF16_TK + col_tiles >= 42 &&
+         (long long)Hq * ((m.N + LG_BF16_TQ - 1) / LG_BF16_TQ) >= 384;
 }
-// dk/dv: by the query tiles of a key tile's window part
-bool dkdv_wide(const LgMask& m, int D) { return D == 128 && (m.wb * m.b + LG_BF16_BTK) / LG_BF16_BTQ >= 16; }
+// dk/dv: by the query tiles of a key tile's window part (the same, 32 keys per wave : 64: window 900 1072 us : 1092, 1100
+// 1255 : 1252, 1300 1414 : 1398)
+bool dkdv_wide(const LgMask& m, int D) { return D == 128 && (m.wb * m.b + LG_BF16_BTK) / LG_BF16_BTQ >= 20; }
 
 constexpr int CUS = 256;  // compute units the cuts below are made for (they also decide the workspace's size)
 
@@ -2139,7 +2142,7 @@ BwdLaunch batch_launch(const LgShape& sh, const LgMask& m) {
   a.chunk = choose_chunk([&](int chunk) { return (long long)c.items(sh.D, chunk) * sh.Hq * sh.B; },
                          c.last - c.first, sh.Hq / sh.Hkv);
   a.citems = c.items(sh.D, a.chunk);
-  (dq_wide(m, sh.D) ? a.qt_wide : a.qt_rest) = (sh.N + LG_BF16_TQ - 1) / LG_BF16_TQ;
+  (dq_wide(m, sh.D, sh.Hq) ? a.qt_wide : a.qt_rest) = (sh.N + LG_BF16_TQ - 1) / LG_BF16_TQ;
   (dkdv_wide(m, sh.D) ? a.kt_wide : a.kt_rest) = (int)a.size.ktiles;
   a.cut = {1, 1};
   if (may_cut(sh, m.stride > 0, a.size.ktiles * sh.B * sh.Hkv)) {
@@ -2207,7 +2210,7 @@ int pack_launch(const LgShape& sh, const LgMask& tmpl, const int* cu_seqlens, in
     a.setup.nlone[y] = seq[y].c.lone();
     a.citems += a.setup.citems[y];
     // (both rules are monotone in the length: the wide ones come first)
-    (dq_wide(m, sh.D) ? a.qt_wide : a.qt_rest) += (seq[y].len + LG_BF16_TQ - 1) / LG_BF16_TQ;
+    (dq_wide(m, sh.D, sh.Hq) ? a.qt_wide : a.qt_rest) += (seq[y].len + LG_BF16_TQ - 1) / LG_BF16_TQ;
     (dkdv_wide(m, sh.D) ? a.kt_wide : a.kt_rest) += (seq[y].len + a.setup.btk - 1) / a.setup.btk;
     a.setup.nwide += dkdv_wide(m, sh.D);
     strided = strided || m.stride > 0;

@@ -177,6 +177,17 @@ def test_long_sequences_take_the_resident_kernels():
     check_pack([5000, 700, 9000], 2, 2, 128, 64, 4096, 1, 0, torch.bfloat16, 403, oracle_rows=2000)
 
 
+def test_sequences_of_both_dq_forms_side_by_side():
+    """32 heads, window 2600: the sequences of 3200 and 3100 tokens take dq with 64 rows per wave, those of 2700 (too few
+    rows) and 300 with 32; out, lse, dq, dk, dv equal the fixed-length calls bit for bit."""
+    lens, H, D, sink, window = [2700, 3200, 300, 3100], 32, 128, 64, 2600
+    packed, seqs, cu = pack(lens, H, H, D, torch.bfloat16, 411)
+    got = run_varlen(packed, cu, sink, window, 1, 0)
+    for s in range(len(lens)):
+        for name, x, y in zip(("out", "lse", "dq", "dk", "dv"), got, run_fixed(seqs[s], sink, window, 1, 0)):
+            assert torch.equal(x[:, cu[s]:cu[s + 1]], y), (name, s)
+
+
 @pytest.mark.parametrize("D,lens,Hq,Hkv,sink,window,block,stride", [
     (128, [300, 1500, 6000, 1, 0, 257, 5000, 769], 4, 2, 64, 1024, 1, 0),   # both forms of dq and dk/dv, lone columns
     (128, [2500, 64, 4000, 700], 4, 1, 64, 256, 64, 8),                     # dq forms differ by the strided columns
