@@ -36,7 +36,7 @@
 // 461 -> 390 us; 512 590 -> 570, 830 -> 782; 2048 (64 rows per wave) 1545 -> 1493, 1910 -> 1875; 64 x 512 tokens 465 -> 380,
 // 630 -> 495 (some of that from the order of the tiles, lg_may_turn).
 //
-// For head dim 128 and long windows (dq 42 or more tiles, dk/dv 20) both kernels have a second form with 64 rows
+// For head dim 128 and long windows (dq 32 or more tiles, dk/dv 16) both kernels have a second form with 64 rows
 // (keys) per wave, one wave per SIMD and the accumulators in AGPRs (further down): every operand
 // read from LDS then feeds two matrix instructions.
 #include <algorithm>
@@ -1864,17 +1864,18 @@ Columns columns_of(const LgMask& m, int D) {
 
 // Which kernels a sequence takes: the 64-rows-per-wave forms (head dim 128) start up and drain slower, so they
 // need a number of steps per workgroup.
-// dq: by the key tiles of an average query tile: its window, plus the strided columns below it (32 heads, 32768 tokens, 32
-// rows per wave : 64: window 2048 1458 us : 1471, 2600 1822 : 1792, 4096 2682 : 2547; 64-token blocks, window 192 and every
-// 8th block a column 1662 : 1718), and only with enough work items of 256 rows (4 heads, 6000 tokens, causal 150 : 192).
+// dq: by the key tiles of an average query tile: its window, plus the strided columns below it.  In short runs the 32-rows
+// form is the faster one up to 40 tiles (64/8 heads, 16001 tokens, window 2048 and strided columns 1415 : 1471 us), in long
+// ones, at the power limit, what it draws more slows the kernels beside it (that whole training pass 4575 : 4515 us; 32
+// heads, 32768 tokens, window 2048 4625 : 4619, 1100 2974 : 3017).  And only with enough work items of 256 rows (4 heads,
+// 6000 tokens, causal 150 : 192).
 bool dq_wide(const LgMask& m, int D, int Hq) {
   const int col_tiles = m.stride > 0 ? (m.N / 2) / (m.b * m.stride) * ((m.b + LG_BF16_TK - 1) / LG_BF16_TK) : 0;
-  return D == 128 && (m.wb * m.b + LG_BF16_TQ) / LG_BF16_TK + col_tiles >= 42 &&
+  return D == 128 && (m.wb * m.b + LG_BF16_TQ) / LG_BF16_TK + col_tiles >= 32 &&
          (long long)Hq * ((m.N + LG_BF16_TQ - 1) / LG_BF16_TQ) >= 384;
 }
-// dk/dv: by the query tiles of a key tile's window part (the same, 32 keys per wave : 64: window 900 1072 us : 1092, 1100
-// 1255 : 1252, 1300 1414 : 1398)
-bool dkdv_wide(const LgMask& m, int D) { return D == 128 && (m.wb * m.b + LG_BF16_BTK) / LG_BF16_BTQ >= 20; }
+// dk/dv: by the query tiles of a key tile's window part
+bool dkdv_wide(const LgMask& m, int D) { return D == 128 && (m.wb * m.b + LG_BF16_BTK) / LG_BF16_BTQ >= 16; }
 
 constexpr int CUS = 256;  // compute units the cuts below are made for (they also decide the workspace's size)
 

@@ -72,7 +72,7 @@ def test_heads_that_take_their_tiles_in_the_other_order(Hq, N, D, window):
 
 @pytest.mark.parametrize("N,sink,window,block,stride", [(3200, 0, 2600, 1, 0), (3140, 64, 2624, 64, 0), (3100, 64, 2304, 64, 8)])
 def test_dq_in_64_row_form(N, sink, window, block, stride):
-    """32 heads, 42 or more key tiles per query tile and a ragged length: dq with 64 rows per wave.  Sampled rows and keys of
+    """32 heads, 32 or more key tiles per query tile and a ragged length: dq with 64 rows per wave.  Sampled rows and keys of
     single heads: the first rows, the sink keys, where the window starts to slide, the last rows."""
     Hq, Hkv, D = 32, 8, 128
     q, k, v, g = lg_synth.prefill_inputs(1, Hq, Hkv, N, D, 9, torch.bfloat16, with_dout=True, device=DEV)
