@@ -557,31 +557,36 @@ __global__ __launch_bounds__(64) void decode_add_kernel(LgDecWork wk, int G, T* 
 // One thread per 16 bytes of a new token row (K and V): the token goes to its sink or ring
 // slot unless a later token of the same call lands on that ring slot, and to its retained-block
 // slot when its block is a strided column.  No two threads write the same bytes.
+// Only rows that are stored are read, and without strided columns only they have threads (first: kept tokens at the start
+// of the call, second: the first of those at its end): of a prompt longer than the window few are (1 x 32 heads of 128,
+// 32768 tokens, window 4096: 110 -> 21 us; 1 x 16 heads of 64, 54868, window 741: 32 -> 3).
 template <int LPR>
 __global__ __launch_bounds__(256) void lg_kv_append_kernel(const uint4* __restrict__ kn,
                                                            const uint4* __restrict__ vn,
                                                            uint4* __restrict__ kc, uint4* __restrict__ vc,
-                                                           int T, int pos, int slots, LgMask m) {
-  const int ti = blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
+                                                           int T, int pos, int slots, LgMask m, int first, int second) {
+  int ti = blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
+  if (ti >= first) ti += second - first;
   if (ti >= T) return;
   const int c = threadIdx.x % LPR;
   const size_t head = (size_t)blockIdx.z * gridDim.y + blockIdx.y;
   const size_t src = (head * T + ti) * LPR + c;
-  const uint4 kx = kn[src], vx = vn[src];
   const int p = pos + ti, last = pos + T - 1;
   const size_t row0 = head * slots;
-  if (p < m.sink || (long long)p + m.window > last) {
+  const bool ring = p < m.sink || (long long)p + m.window > last;
+  const int kb = m.stride > 0 ? lg_div_b(m, p) : 0;
+  const bool retained = m.stride > 0 && lg_strided(m, kb);
+  if (!ring && !retained) return;
+  const uint4 kx = kn[src], vx = vn[src];
+  if (ring) {
     const int slot = p < m.sink ? p : m.sink + (p - m.sink) % m.window;
     kc[(row0 + slot) * LPR + c] = kx;
     vc[(row0 + slot) * LPR + c] = vx;
   }
-  if (m.stride > 0) {
-    const int kb = lg_div_b(m, p);
-    if (lg_strided(m, kb)) {
-      const int slot = m.sink + m.window + (kb / m.stride) * m.b + (p - kb * m.b);
-      kc[(row0 + slot) * LPR + c] = kx;
-      vc[(row0 + slot) * LPR + c] = vx;
-    }
+  if (retained) {
+    const int slot = m.sink + m.window + (kb / m.stride) * m.b + (p - kb * m.b);
+    kc[(row0 + slot) * LPR + c] = kx;
+    vc[(row0 + slot) * LPR + c] = vx;
   }
 }
 
@@ -888,13 +893,19 @@ hipError_t lg_launch_kv_append(const void* k_new, const void* v_new, void* k_cac
                                int B, int Hkv, int row_bytes, int T, int pos, int slots,
                                const LgMask& m, hipStream_t s) {
   const int lpr = row_bytes / 16;  // 8, 16 or 32 lanes per token row
-  const dim3 grid((T + 256 / lpr - 1) / (256 / lpr), Hkv, B);
+  int first = T, second = T;
+  if (m.stride == 0) {  // the sink tokens of the call, and the last `window` of the others
+    first = std::min(T, std::max(0, m.sink - pos));
+    second = std::max(first, T - std::min(T, m.window));
+  }
+  const int kept = first + T - second;
+  const dim3 grid((kept + 256 / lpr - 1) / (256 / lpr), Hkv, B);
   const uint4* kn = (const uint4*)k_new;
   const uint4* vn = (const uint4*)v_new;
   uint4* kc = (uint4*)k_cache;
   uint4* vc = (uint4*)v_cache;
-  if (lpr == 8) lg_kv_append_kernel<8><<<grid, 256, 0, s>>>(kn, vn, kc, vc, T, pos, slots, m);
-  else if (lpr == 16) lg_kv_append_kernel<16><<<grid, 256, 0, s>>>(kn, vn, kc, vc, T, pos, slots, m);
-  else lg_kv_append_kernel<32><<<grid, 256, 0, s>>>(kn, vn, kc, vc, T, pos, slots, m);
+  if (lpr == 8) lg_kv_append_kernel<8><<<grid, 256, 0, s>>>(kn, vn, kc, vc, T, pos, slots, m, first, second);
+  else if (lpr == 16) lg_kv_append_kernel<16><<<grid, 256, 0, s>>>(kn, vn, kc, vc, T, pos, slots, m, first, second);
+  else lg_kv_append_kernel<32><<<grid, 256, 0, s>>>(kn, vn, kc, vc, T, pos, slots, m, first, second);
   return hipGetLastError();
 }

@@ -62,6 +62,19 @@ def oracle_append_all(k, v, sink, window, block, stride, slots, fill):
     return kc, vc
 
 
+@pytest.mark.parametrize("sink,window,block", [(5, 7, 1), (0, 16, 1), (40, 3, 1), (32, 48, 16)])
+def test_append_of_kept_tokens_only(sink, window, block):
+    """Calls that end inside the sink, at its end, and are shorter than, as long as and longer than the window: without
+    strided columns only the kept tokens have threads."""
+    for chunks in ([3, 2, 7, 8, 1, 20], [4, 2, 6, 15, 100], [39, 1, 3, 4, 16, 17, 48, 49, 200], [60, 1, 47], [1000]):
+        N = sum(chunks)
+        _, k, v = lg_synth.prefill_inputs(1, 2, 2, N, 64, 41 + N, torch.bfloat16)
+        slots = lg.lg_kv_cache_slots(N, sink, window, block, 0) + 3
+        kc, vc = gpu_append_all(k, v, sink, window, block, 0, chunks, slots, 7.0)
+        wk, wv = oracle_append_all(k, v, sink, window, block, 0, slots, 7.0)
+        assert np.array_equal(bits(kc), wk) and np.array_equal(bits(vc), wv), chunks
+
+
 @pytest.mark.parametrize("dtype,D", [(torch.bfloat16, 128), (torch.bfloat16, 64), (torch.float32, 128), (torch.float32, 64)])
 @pytest.mark.parametrize("N,sink,window,block,stride", PATTERNS)
 def test_append_is_bit_exact(dtype, D, N, sink, window, block, stride):
