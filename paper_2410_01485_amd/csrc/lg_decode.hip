@@ -25,6 +25,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 namespace {
 
@@ -99,10 +100,12 @@ struct LgDecWork {
   int* parts;         // [rows], paged: parts of the row
 };
 constexpr int LG_DEC_SPLITS_MAX = 64;
-// Workgroups with keys that a paged step aims at: three per CU, what the matrix-core kernel's registers admit, or (bf16)
-// one per CU when all rows together have so few keys that a workgroup's start and the final sum weigh more than its
-// reads.
-constexpr int DEC_FULL = 768, DEC_FEW = 256;
+// Workgroups with keys that a paged step aims at: a little below three per CU, what the matrix-core kernel's registers
+// admit, or (bf16) one per CU when all rows together have so few keys that a workgroup's start and the final sum weigh
+// more than its reads.  Rounding gives up to a tenth more than aimed at: with 768 the last of 900 workgroups ran after the
+// others (64 sequences of 2000 .. 60000 tokens, 8 kv heads: 186 us, with 720 164; 48 of 20 .. 32768: 68.7 and 68.2; with
+// 640 73.7, whole rounds missing on part of the CUs).
+constexpr int DEC_FULL = 720, DEC_FEW = 256;
 constexpr float DEC_MANY_KEYS = 300000.f;
 
 struct LgDecPart {
@@ -111,6 +114,22 @@ struct LgDecPart {
   int split, parts;   // of the row
   size_t row;
 };
+
+// Sums over the lanes up to and including each one (as shifts between the lanes of a row, no trip through LDS).
+template <typename T>
+__device__ __forceinline__ T lg_wave_scan(T x) {
+  auto add = [&](auto ctrl, auto rows) {
+    const int y = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
+    x += __builtin_bit_cast(T, y);
+  };
+  add(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xf>{});  // lane - 1, in rows of 16 lanes
+  add(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xf>{});  // lane - 2
+  add(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xf>{});  // lane - 4
+  add(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xf>{});  // lane - 8
+  add(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});  // last lane of row 0 to row 1, of 2 to 3
+  add(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});  // lane 31 to rows 2 and 3
+  return x;
+}
 
 // The part of this workgroup; false: none.  Grid: splits x rows of a sequence x B.  Paged (heads: rows of a sequence):
 // one dimension, the parts of all sequences one after the other; segs receives the sequence's runs.
@@ -131,13 +150,12 @@ __device__ __forceinline__ bool lg_dec_part(const LgDecWork& wk, const LgPaged& 
   // step that is over in a few rounds anyway), no more parts per row than the workspace has room for.  As a grid of
   // (parts of the longest) x rows, with workgroups that find nothing to do, the others came out uneven over the CUs.
   const int lane = threadIdx.x & 63, B = pg.B;
-  auto keys = [&](int x) { return x < B ? min(max(pg.seq_lens[x], 1), pg.keys_max) : 0; };  // never too few
-  const int first = keys(lane);  // (a batch of up to 64: the only look at the lengths)
+  auto length = [&](int x) { return x < B ? pg.seq_lens[x] : 0; };
+  auto keys = [&](int x, int n) { return x < B ? min(max(n, 1), pg.keys_max) : 0; };  // never too few
+  const int first_n = length(lane), first = keys(lane, first_n);  // (a batch of up to 64: the only look at the lengths)
   float sum = (float)first;
-  for (int x = 64 + lane; x < B; x += 64) sum += (float)keys(x);
-#pragma unroll
-  for (int x = 1; x < 64; x <<= 1) sum += __shfl_xor(sum, x);
-  const float all = sum * heads;
+  for (int x = 64 + lane; x < B; x += 64) sum += (float)keys(x, length(x));
+  const float all = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(lg_wave_scan(sum)), 63)) * heads;
   const float target = all > DEC_MANY_KEYS ? fmaxf(DEC_FULL - 0.25f * B * heads, DEC_FEW) : (float)pg.few;
   const int chunk = max(wk.chunk, 128 * __builtin_amdgcn_readfirstlane((int)ceilf(all / (128.f * target))));
   // Rows are cut evenly.  What is left over goes to the others where the reads decide, up to a quarter of a part, and to a
@@ -146,20 +164,15 @@ __device__ __forceinline__ bool lg_dec_part(const LgDecWork& wk, const LgPaged& 
   const int spare = all > DEC_MANY_KEYS ? chunk >> 2 : 0;
   auto nparts = [&](int k) { return k <= chunk + (chunk >> 2) ? 1 : (k - spare + chunk - 1) / chunk; };
   const int w = blockIdx.x;
-  int before = 0;
+  int before = 0, N = 0;
   for (int c = 0; c < B; c += 64) {
-    const int k = c == 0 ? first : keys(c + lane);
-    const int mine = k > 0 ? nparts(k) * heads : 0;
-    int upto = mine;
-#pragma unroll
-    for (int x = 1; x < 64; x <<= 1) {
-      const int y = __shfl_up(upto, x);
-      if (lane >= x) upto += y;
-    }
+    const int n = c == 0 ? first_n : length(c + lane), k = keys(c + lane, n);
+    const int mine = k > 0 ? nparts(k) * heads : 0, upto = lg_wave_scan(mine);
     const unsigned long long past = __builtin_amdgcn_ballot_w64(before + upto > w);
     if (past != 0ull) {
       const int x = __builtin_ctzll(past);
       p.b = c + x;
+      N = min(max(__builtin_amdgcn_readlane(n, x), 1), pg.n_max);
       const int at = w - before - __builtin_amdgcn_readlane(upto - mine, x);
       p.split = at / heads;
       p.q = at - p.split * heads;
@@ -169,7 +182,6 @@ __device__ __forceinline__ bool lg_dec_part(const LgDecWork& wk, const LgPaged& 
     if (c + 64 >= B) return false;
   }
   p.row = (size_t)p.b * heads + p.q;
-  const int N = __builtin_amdgcn_readfirstlane(min(max(pg.seq_lens[p.b], 1), pg.n_max));
   if (pg.cm.b == 1 && pg.cm.stride == 0) {  // token-granular: the slots in use are one run
     valid = min(N, pg.cm.sink + pg.cm.window);
     segs.start[0] = 0;
