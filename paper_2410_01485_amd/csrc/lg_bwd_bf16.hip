@@ -153,17 +153,31 @@ __device__ __forceinline__ float lg_group_sum(float x) {
 
 // Delta = <dout, out> and the log-sum-exp of the ROWS rows from q0 on to LDS, by a workgroup of 256: dout from its tiles in
 // LDS, out in pieces of 16 bytes, consecutive lanes consecutive pieces.  Rows past the end repeat the last one.
+// Eight rows' products side by side and one store at the end: row after row, with a branch each, they waited for LDS and for
+// each sum's steps (with the 64-rows-per-wave form's fragments read one by one as well 8000 cycles of an item's start, now
+// 4900; 32 heads of 128: 32768 tokens, window 256 370 -> 363 us, 51 x 640 tokens 387 -> 383, 32 x 1024 497 -> 487).
 template <int D, int ROWS>
 __device__ __forceinline__ void lg_delta_rows(const unsigned char* tiles, const uint4 (&o)[ROWS * D / 2048], float* s_delta) {
   using T = LgSwzTile<D>;
+  constexpr int P = ROWS * D / 2048, RPP = 256 / T::CPR, AT = P < 8 ? P : 8;  // pieces, rows of one; pieces side by side
+  static_assert(P <= T::CPR, "a lane keeps one row");
   const int tid = threadIdx.x, c = tid % T::CPR;
+  float mine = 0.f;
 #pragma unroll
-  for (int x = 0; x < ROWS * D / 2048; ++x) {
-    const int r = x * (256 / T::CPR) + tid / T::CPR;
-    const uint4 gw = *reinterpret_cast<const uint4*>(tiles + r * T::ROW_BYTES + ((c ^ T::pi(r & 63)) << 4));
-    const float s = lg_group_sum<T::CPR>(lg_dot8(gw, o[x], 0.f));
-    if (c == 0) s_delta[r] = s;
+  for (int x0 = 0; x0 < P; x0 += AT) {
+    uint4 gw[AT];
+#pragma unroll
+    for (int x = 0; x < AT; ++x) {
+      const int r = (x0 + x) * RPP + tid / T::CPR;
+      gw[x] = *reinterpret_cast<const uint4*>(tiles + r * T::ROW_BYTES + ((c ^ T::pi(r & 63)) << 4));
+    }
+#pragma unroll
+    for (int x = 0; x < AT; ++x) {
+      const float s = lg_group_sum<T::CPR>(lg_dot8(gw[x], o[x0 + x], 0.f));
+      mine = c == x0 + x ? s : mine;
+    }
   }
+  if (c < P) s_delta[c * RPP + tid / T::CPR] = mine;
 }
 template <int D, int ROWS>
 __device__ __forceinline__ void lg_load_pieces(const uint16_t* __restrict__ rows, int last, uint4 (&o)[ROWS * D / 2048]) {
@@ -1614,6 +1628,14 @@ __device__ __forceinline__ void dq_wide_item(
       dma.issue((y ? q : dout) + qbase + (size_t)rc * D, N - rc, lds0 + (4 * y + x) * T::BYTES);
     }
   const float my_lse = lse[row0 + min(q0 + tid, N - 1)];
+  const LgQSched qs = lg_qsched_init(m, q0, q1);
+  const LgRows wrows = lg_rows(m, qw0, qw1);
+  const LgQWalk qw = lg_qwalk_init(qs);
+  auto next_tile = [&](int prev) -> int {
+    if (TOKEN || m.stride == 0) return prev < 0 ? lg_qwalk_first(qw) : lg_qwalk_next(qw, prev);
+    return lg_qsched_next(m, qs, prev);
+  };
+  int t = next_tile(-1);  // (while the rows are on their way)
   {
     uint4 o[16];
     lg_load_pieces<D, TQ>(out + qbase + (size_t)q0 * D, N - 1 - q0, o);
@@ -1623,28 +1645,23 @@ __device__ __forceinline__ void dq_wide_item(
     s_rows[1][tid] = my_lse;
   }
 #pragma unroll
-  for (int x = 0; x < 4; ++x)
+  for (int x = 0; x < 4; ++x) {
+    bf16x8_t f[DC];  // (all of a row block's reads in flight at once)
 #pragma unroll
-    for (int dc = 0; dc < DC; ++dc)
-      lg_frag_set((x < 2 ? 16 : 0) + 8 * (x & 1) + dc,
-                  __builtin_bit_cast(uint4, rd.read_rows(smem, ((x < 2 ? 0 : 4) + wave_s) * T::BYTES, x & 1, dc)));
+    for (int dc = 0; dc < DC; ++dc) f[dc] = rd.read_rows(smem, ((x < 2 ? 0 : 4) + wave_s) * T::BYTES, x & 1, dc);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int dc = 0; dc < DC; ++dc) lg_frag_set((x < 2 ? 16 : 0) + 8 * (x & 1) + dc, __builtin_bit_cast(uint4, f[dc]));
+  }
   __syncthreads();
-  const LgQSched qs = lg_qsched_init(m, q0, q1);
-  const LgRows wrows = lg_rows(m, qw0, qw1);
   auto issue = [&](int t, int stage) {
     const size_t off = (size_t)t * TK * D;
     dma.issue(kh + off, N - t * TK, lds0 + stage * STAGE);
     dma.issue(vh + off, N - t * TK, lds0 + stage * STAGE + T::BYTES);
   };
-  const LgQWalk qw = lg_qwalk_init(qs);
-  auto next_tile = [&](int prev) -> int {
-    if (TOKEN || m.stride == 0) return prev < 0 ? lg_qwalk_first(qw) : lg_qwalk_next(qw, prev);
-    return lg_qsched_next(m, qs, prev);
-  };
   // Tiles are handled in pairs: one barrier per two tiles (with one wave per SIMD nothing hides the
   // wait for the slowest wave, so fewer barriers matter more than a deeper ring).  Pair p lives in
   // stages 2 (p % 2), + 1; at its start the loads of pair p + 1 go into the other two stages.
-  int t = next_tile(-1);
   int t_issue = t;
   for (int x = 0; x < 2 && t_issue >= 0; ++x) {
     issue(t_issue, x);
