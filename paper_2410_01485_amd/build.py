@@ -23,6 +23,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]
 
+# flags of one file: the forward's tile loop runs up to 5 % slower where its code happens to start off a 64-byte boundary
+# (the backward kernels' unrolled steps do not: within 0.3 %)
+FILE_FLAGS = {"lg_fwd_bf16.hip": ["-falign-loops=64"]}
+
 
 def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
@@ -74,7 +78,7 @@ def build(verbose=True, jobs=8, sanitize_host=False, out=None):
     for src in sources():
         obj = os.path.join(objdir, os.path.basename(src)[:-4] + ".o")
         objs.append(obj)
-        cmd = [HIPCC] + flags + ["-c", src, "-o", obj]
+        cmd = [HIPCC] + flags + FILE_FLAGS.get(os.path.basename(src), []) + ["-c", src, "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))

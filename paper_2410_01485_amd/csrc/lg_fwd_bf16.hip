@@ -21,6 +21,10 @@
 // cycles each way) and items are found without divisions: 32 heads of 128, window 64 at 32768 tokens 216 -> 198 us (5.4
 // TB/s), 256 291 -> 265, 1024 633 -> 609; 64 x 512 tokens 300 -> 269 us; 2 x 16 heads of 64, 1003 tokens 17.2 -> 16.5.
 // (Asking for the next item's Q lines while a tile is computed, so that they wait in L2, was slower: 198 -> 207 us.)
+// What whole tiles cost depends on where the tile loop's code falls (5 % for 24055 tokens of 2 heads of 64, from a change
+// that touched only the masks of PARTIAL tiles): this file is compiled with loops at 64-byte boundaries.  With masks of two
+// instructions per score instead of four 163 x 200 tokens 218 -> 214 us, 109 x 300 243 -> 240, 2 x 16 heads of 64, 1003
+// tokens 15.6 -> 15.2, 2 x 4 heads of 128, 1603 tokens 36.1 -> 35.4; windows of 1024 tokens and more as before.
 // 32 heads of 128, 131072 tokens, window 4096: 9.1 -> 8.45 ms (1040 TFLOP/s, the clock now
 // settles at 1.8 GHz instead of 2.2 under the power limit); 8 x 1024 tokens: 144 -> 116 us; 2 x 16 heads of 64, 1003
 // tokens: 26 -> 18 us.
@@ -175,12 +179,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
 
     // ---- online softmax (log2 domain) ----
     if (!full) {
+      asm volatile("; masked" ::: "memory");  // (a real branch: nothing of it in whole tiles)
       const uint32_t bits = lg_key_bits(m, min(i, N - 1), k0, g);  // a few runs of registers, in closed form
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
-          if (!(bits & (1u << (kb * 16 + r)))) sacc[kb][r] = -INFINITY;
+          sacc[kb][r] = lg_keep_or(sacc[kb][r], bits, kb * 16 + r, -INFINITY);
     }
     float mx = -INFINITY;
 #pragma unroll

@@ -46,6 +46,13 @@ __device__ __forceinline__ uint32_t lg_pack_bf16(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, h);
 }
 
+// x where bit k of `bits` is set, otherwise `other`: the bit spread over a register and a bitwise operation (a compare and a
+// select through a scalar mask are three instructions and a wait).
+__device__ __forceinline__ float lg_keep_or(float x, uint32_t bits, int k, float other) {
+  const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe((int)bits, k, 1);
+  return __uint_as_float((__float_as_uint(x) & keep) | (__float_as_uint(other) & ~keep));
+}
+
 // Values that one workgroup leaves for another of the same launch (partial results summed by whichever finishes
 // last): device-scope accesses, which go through to memory the workgroups of all XCDs see, instead of device-wide
 // fences, which write back and invalidate a whole L2 (in the float32 dk/dv kernel such a fence per wave cost 87 of
