@@ -13,7 +13,7 @@
 // Kernel tile sizes (query rows x keys per step).  Independent of the pattern's
 // `block`: they never change results, only which tiles count as PARTIAL.
 enum {
-  LG_F32_TQ = 64, LG_F32_TK = 64,        // float32 kernels, forward / dq order
+  LG_F32_TQ = 64, LG_F32_TK = 64,        // float32 kernels, forward / dq order (few workgroups: half the rows each)
   LG_F32_BTQ = 64, LG_F32_BTK = 64,      // float32 dk/dv (key-tile major), as listed by the host view:
   LG_F32_KEYS = 32,                      // a workgroup takes half of such a tile's keys (at head dim 128 half its rows a step)
   LG_BF16_TQ = 256, LG_BF16_TK = 64,     // bf16 dq kernel with 64 rows per wave
@@ -26,6 +26,20 @@ struct LgShape {
   int B, Hq, Hkv, N, D;
   float scale;  // already resolved (> 0)
 };
+
+// float32 forward and dq: among how many waves a tile's keys are divided; 2: 64 query rows per workgroup, 4: 32 rows.  Four
+// shorten a row's chain of tiles and give twice the workgroups, but load the keys twice as often.  They pay where 64 rows
+// leave CUs without work: up to 128 workgroups (forward / dq, us: 1 head of 64, 2000 tokens, causal 83 -> 51 / 115 -> 71; 4
+// heads of 64, 2048 tokens, window 300 22 -> 15 / 31 -> 22; 192 workgroups 84 -> 79 / 114 -> 116, at head dim 128 156 -> 173 /
+// 212 -> 230), and where they would need a second round for less than half the CUs and rows are long enough for that to
+// matter (34 x 500 tokens of 64 42 -> 33 / 61 -> 49; 384 workgroups, window 1000 82 -> 71 / 116 -> 101, window 100
+// 22 -> 25 / 33 -> 38; 512 workgroups, window 300 36 -> 42 / 53 -> 59).  The shape alone decides, so that a sequence of a
+// pack, which has launches of its own, gets what it gets by itself.
+inline int lg_f32_split(const LgShape& sh, const LgMask& m) {
+  const long long n = (long long)sh.B * sh.Hq * ((sh.N + LG_F32_TQ - 1) / LG_F32_TQ);
+  const long long reach = (long long)m.wb * m.b < sh.N ? (long long)m.wb * m.b : sh.N;
+  return n <= 128 || (n > 256 && n <= 384 && reach >= 256) ? 4 : 2;
+}
 
 // Each launcher enqueues on `s` and returns hipGetLastError().
 hipError_t lg_launch_fwd_f32(const float* q, const float* k, const float* v, float* out, float* lse,

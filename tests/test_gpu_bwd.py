@@ -100,6 +100,14 @@ def test_float32_key_tiles(Hq, Hkv, N, sink, window, block, stride, D):
     check_bwd(1, Hq, Hkv, N, D, sink, window, block, stride, dtype=torch.float32, seed=8)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,N,D,sink,window", [
+    (1, 2, 1, 33, 64, 4, 9), (1, 1, 1, 700, 128, 16, 90), (2, 32, 32, 128, 128, 0, 128), (2, 32, 16, 129, 64, 4, 40),
+    (2, 26, 13, 300, 64, 0, 300), (2, 32, 8, 384, 64, 16, 256), (2, 32, 8, 384, 128, 16, 255)])
+def test_float32_dq_rows_per_workgroup(B, Hq, Hkv, N, D, sink, window):
+    """32 or 64 query rows per workgroup, by the number of workgroups (up to 128, and 257 .. 384 with a reach of 256)."""
+    check_bwd(B, Hq, Hkv, N, D, sink, window, dtype=torch.float32, seed=13)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_peaked_scores_and_custom_scale(dtype):
     check_bwd(1, 2, 2, 600, 128, 16, 100, dtype=dtype, seed=4, q_mul=4.0, by_tensor_max=True)

@@ -16,6 +16,18 @@ def test_config1_fp32_sink_window():
     check_fwd(1, 1, 1, 1024, 64, 16, 128, dtype=torch.float32, seed=20241002)
 
 
+# float32: 32 or 64 query rows per workgroup, by the number of workgroups (up to 128, and 257 .. 384 with a reach of 256)
+F32_ROWS = [(1, 1, 1, 31, 0, 31, 1, 0), (1, 2, 1, 33, 4, 9, 1, 0), (1, 1, 1, 95, 16, 20, 1, 0), (1, 3, 1, 700, 16, 96, 16, 3),
+            (2, 32, 32, 128, 0, 128, 1, 0), (2, 32, 16, 129, 4, 40, 1, 0), (2, 26, 13, 300, 0, 300, 1, 0), (2, 32, 8, 384, 16, 256, 1, 0),
+            (2, 32, 8, 384, 16, 255, 1, 0), (2, 32, 8, 385, 16, 300, 1, 0)]
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("B,Hq,Hkv,N,sink,window,block,stride", F32_ROWS)
+def test_float32_rows_per_workgroup(B, Hq, Hkv, N, sink, window, block, stride, D):
+    check_fwd(B, Hq, Hkv, N, D, sink, window, block, stride, dtype=torch.float32, seed=12)
+
+
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_sink_window_ragged_gqa(D, dtype):
