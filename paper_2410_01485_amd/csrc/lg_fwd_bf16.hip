@@ -39,16 +39,25 @@ constexpr int TQ = LG_BF16_TQ32;  // 128 query rows per workgroup
 constexpr int NT = TQ * 2;        // threads: one wave per 32 rows
 // Waves per SIMD, and LDS operands of the two products requested ahead of the matrix instruction that uses them, as the
 // registers of so many waves allow (168 for D = 128, 128 for D = 64)
-template <int D>
+template <int D, bool FEW>
 struct LgFwdTune {
-    static constexpr int WAVES = D == 128 ? 3 : 4, AHEAD = D == 128 ? 2 : 3, AHEAD_PV = 4;
+    static constexpr int WAVES = FEW ? 2 : D == 128 ? 3 : 4, AHEAD = FEW ? 4 : D == 128 ? 2 : 3, AHEAD_PV = 4;
 };
 
+// FEW: the instance for launches that leave every SIMD with one wave at most (LG_FWD_FEW work items, a workgroup per CU).
+// Nothing then hides a wave's own waits: with the registers of two waves K is read four matrix instructions ahead, K and V of
+// the next tile are both requested behind the one barrier of a tile (four tiles in LDS), for D = 128 between the matrix
+// instructions of the first product, and V's first reads go out before the softmax.  Same operations in the same order on
+// every row, so the results are those of the other instance bit for bit.  2 x 16 heads of 64, 1003 tokens 15.3 -> 14.5 us, of
+// 128 19.6 -> 18.5; 4/1 heads of 128, 5000 tokens, causal 96.2 -> 88.8, of 64 73.4 -> 68.1; where workgroups share a CU it is
+// slower (640 of them, D = 128: 90 -> 101).  Requests in between are slower for D = 64, as are reads further ahead; the second
+// product in one phase with the next tile's exponentials was slower as well (98 -> 108: they do not overlap within a wave).
+constexpr int LG_FWD_FEW = 256;
 // PackT: LgNoPack for the batch layout (every (b, head) has the same query tiles), LgPack for
 // sequences of different lengths side by side in each head (B = 1).
 struct LgNoPack {};
-template <int D, typename PackT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>::WAVES, LgFwdTune<D>::WAVES))) void fwd_bf16_kernel(const uint16_t* __restrict__ q,
+template <int D, typename PackT, bool FEW>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D, FEW>::WAVES, LgFwdTune<D, FEW>::WAVES))) void fwd_bf16_kernel(const uint16_t* __restrict__ q,
                                                       const uint16_t* __restrict__ k,
                                                       const uint16_t* __restrict__ v,
                                                       uint16_t* __restrict__ out,
@@ -61,7 +70,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
   using Dma = LgDma<D, NT>;
   constexpr int DC = D / 16;            // 16-wide contraction chunks of the head dim
   constexpr int DB = D / 32;            // 32-row blocks of O^T
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[3 * T::BYTES];  // two K tiles, a V tile
+  using Tune = LgFwdTune<D, FEW>;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[(FEW ? 4 : 3) * T::BYTES];  // two K tiles, a V tile (FEW: two)
 
   const int L = lg_item_of(blockIdx.x, items.run);
   if (L >= items.total) return;
@@ -111,7 +121,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
   const bf16x2_t ones = {(__bf16)1.0f, (__bf16)1.0f};
 
   auto issue_k = [&](int t, int buf) { dma.issue(kh + (size_t)t * TK * D, N - t * TK, lds0 + buf * T::BYTES); };
-  auto issue_v = [&](int t) { dma.issue(vh + (size_t)t * TK * D, N - t * TK, lds0 + 2 * T::BYTES); };
+  auto issue_v = [&](int t, int buf) { dma.issue(vh + (size_t)t * TK * D, N - t * TK, lds0 + (2 + buf) * T::BYTES); };
   // K tiles are requested up to two ahead of the one being computed, its own V tile behind the barrier that opens it
   const LgQSched qs = lg_qsched_init(m, q0, q1);
   const LgRows wrows = lg_rows(m, qw0, qw1);
@@ -140,14 +150,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
   for (int dc = 0; dc < DC; ++dc) asm volatile("" ::"v"(qf[dc]));
   __syncthreads();
   int t1 = t1_first;
-  if (t1 >= 0) issue_k(t1, 1);
+  if (FEW) issue_v(t, 0);
+  else if (t1 >= 0) issue_k(t1, 1);
 
   int buf = 0;
   while (t >= 0) {
-    if (t1 >= 0) LG_WAIT_VMCNT(Dma::CH);
+    if (!FEW && t1 >= 0) LG_WAIT_VMCNT(Dma::CH);
     else LG_WAIT_VMCNT(0);
-    __syncthreads();  // K(t) landed; everyone is done with V(t-1)
-    issue_v(t);
+    __syncthreads();  // K(t) landed; everyone is done with V(t-1); (FEW) V(t) landed as well
+    if (!FEW) issue_v(t, 0);
     const int t2 = t1 >= 0 ? next_tile(t1) : -1;
 
     const int k0 = t * TK;
@@ -157,7 +168,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
     if (!lg_qsched_full(m, qs, t)) kind = lg_rows_kind(m, wrows, k0, k0 + TK - 1);
     const bool full = kind == LG_TILE_FULL;
     const int sk = buf * T::BYTES;   // byte offsets of the K and V tiles inside smem
-    const int sv = 2 * T::BYTES;
+    const int sv = (FEW ? 2 + buf : 2) * T::BYTES;
+    auto read_v = [&](int u) { return rd.read_cols(smem, sv, u % DB, u / DB); };
+    LgRing<4 * DB, Tune::AHEAD_PV> vring;
+    // (FEW) the next tiles' requests go between the matrix instructions of the first product, if both are whole
+    const bool between = FEW && D == 128 && kind != LG_TILE_DEAD && t1 >= 0 && N - t1 * TK >= TK;
+    if (FEW && t1 >= 0 && !between) {
+      issue_k(t1, buf ^ 1);
+      issue_v(t1, buf ^ 1);
+    }
     bf16x8_t pf[4];  // P^T as bf16, B operand of the second product, per 16-key group
     if (kind != LG_TILE_DEAD) {
 
@@ -172,11 +191,23 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
     // at 128K tokens, 10 % where a SIMD has one wave).
     {
       auto read = [&](int u) { return rd.read_rows(smem, sk, u & 1, u >> 1); };
-      LgRing<2 * DC, LgFwdTune<D>::AHEAD> ring;
+      LgRing<2 * DC, Tune::AHEAD> ring;
       ring.begin(read);
-      ring.run(read, [&](int u, bf16x8_t k) { sacc[u & 1] = lg_mfma32(k, qf[u >> 1], sacc[u & 1]); });
+      if (between) {
+        const uint16_t *k1 = kh + (size_t)t1 * TK * D, *v1 = vh + (size_t)t1 * TK * D;
+        const uint32_t to = lds0 + (buf ^ 1) * T::BYTES;
+        ring.run(read, [&](int u, bf16x8_t k) {
+          sacc[u & 1] = lg_mfma32(k, qf[u >> 1], sacc[u & 1]);
+          static_assert(2 * Dma::CH == DC, "a request per two matrix instructions");
+          const int x = u >> 1;
+          if (u & 1) dma.load(x < Dma::CH ? k1 : v1, dma.voff[x % Dma::CH], to + (x < Dma::CH ? 0 : 2 * T::BYTES), x % Dma::CH);
+        });
+      } else {
+        ring.run(read, [&](int u, bf16x8_t k) { sacc[u & 1] = lg_mfma32(k, qf[u >> 1], sacc[u & 1]); });
+      }
     }
 
+    if (FEW) vring.begin(read_v);
     // ---- online softmax (log2 domain) ----
     if (!full) {
       asm volatile("; masked" ::: "memory");  // (a real branch: nothing of it in whole tiles)
@@ -229,17 +260,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
       }
     lrow += psum;
     }
-    LG_WAIT_VMCNT(0);
-    __syncthreads();  // V(t) landed; everyone is done with K(t)
-    if (t2 >= 0) issue_k(t2, buf);
+    if (!FEW) {
+      LG_WAIT_VMCNT(0);
+      __syncthreads();  // V(t) landed; everyone is done with K(t)
+      if (t2 >= 0) issue_k(t2, buf);
+    }
     if (kind != LG_TILE_DEAD) {
     // ---- O^T += V^T P^T ----
-    {
-      auto read = [&](int u) { return rd.read_cols(smem, sv, u % DB, u / DB); };
-      LgRing<4 * DB, LgFwdTune<D>::AHEAD_PV> ring;
-      ring.begin(read);
-      ring.run(read, [&](int u, bf16x8_t v) { oacc[u % DB] = lg_mfma32(v, pf[u / DB], oacc[u % DB]); });
-    }
+      if (!FEW) vring.begin(read_v);
+      vring.run(read_v, [&](int u, bf16x8_t v) { oacc[u % DB] = lg_mfma32(v, pf[u / DB], oacc[u % DB]); });
     }  // kind != dead
 
     t = t1;
@@ -247,6 +276,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D>
     buf ^= 1;
   }
 
+  if (FEW) __syncthreads();  // everyone is done with the K tiles
   // ---- epilogue: normalise, write O (bf16) and LSE (natural log) ----
   const float l = lrow + lg_other_half(lrow);
   const float inv = 1.f / l;
@@ -276,12 +306,15 @@ hipError_t lg_launch_fwd_bf16(const void* q, const void* k, const void* v, void*
   const float sl2 = sh.scale * 1.44269504088896340736f;
   const LgItems items = lg_make_items(total, run, nqt, sh.Hq, sh.Hkv);
   const dim3 grid((unsigned)lg_run_grid(total, run));
-#define LG_FWD_LAUNCH(DD)                                                                                \
-  fwd_bf16_kernel<DD, LgNoPack><<<grid, NT, 0, s>>>((const uint16_t*)q, (const uint16_t*)k,          \
+#define LG_FWD_LAUNCH(DD, FEW)                                                                             \
+  fwd_bf16_kernel<DD, LgNoPack, FEW><<<grid, NT, 0, s>>>((const uint16_t*)q, (const uint16_t*)k,          \
                                                         (const uint16_t*)v, (uint16_t*)out, lse, sh.Hq,  \
                                                         sh.Hkv, sl2, m, items, LgNoPack{})
-  if (sh.D == 64) LG_FWD_LAUNCH(64);
-  else LG_FWD_LAUNCH(128);
+  const bool few = total <= LG_FWD_FEW;
+  if (sh.D == 64 && few) LG_FWD_LAUNCH(64, true);
+  else if (sh.D == 64) LG_FWD_LAUNCH(64, false);
+  else if (few) LG_FWD_LAUNCH(128, true);
+  else LG_FWD_LAUNCH(128, false);
 #undef LG_FWD_LAUNCH
   return hipGetLastError();
 }
@@ -307,12 +340,15 @@ hipError_t lg_launch_fwd_bf16_pack(const void* q, const void* k, const void* v, 
   const float sl2 = sh.scale * 1.44269504088896340736f;
   const LgItems items = lg_make_items(total, run, nqt, sh.Hq, sh.Hkv);
   const dim3 grid((unsigned)lg_run_grid(total, run));
-#define LG_FWD_LAUNCH(DD)                                                                              \
-  fwd_bf16_kernel<DD, LgPack><<<grid, NT, 0, s>>>((const uint16_t*)q, (const uint16_t*)k,          \
+#define LG_FWD_LAUNCH(DD, FEW)                                                                           \
+  fwd_bf16_kernel<DD, LgPack, FEW><<<grid, NT, 0, s>>>((const uint16_t*)q, (const uint16_t*)k,          \
                                                       (const uint16_t*)v, (uint16_t*)out, lse, sh.Hq,  \
                                                       sh.Hkv, sl2, tmpl, items, pack)
-  if (sh.D == 64) LG_FWD_LAUNCH(64);
-  else LG_FWD_LAUNCH(128);
+  const bool few = total <= LG_FWD_FEW;
+  if (sh.D == 64 && few) LG_FWD_LAUNCH(64, true);
+  else if (sh.D == 64) LG_FWD_LAUNCH(64, false);
+  else if (few) LG_FWD_LAUNCH(128, true);
+  else LG_FWD_LAUNCH(128, false);
 #undef LG_FWD_LAUNCH
   return hipGetLastError();
 }

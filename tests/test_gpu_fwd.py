@@ -29,6 +29,24 @@ def test_float32_rows_per_workgroup(B, Hq, Hkv, N, sink, window, block, stride, 
 
 
 @pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv,N,sink,window,block,stride", [
+    (2, 1, 1, 0, 1, 1, 0), (2, 2, 64, 0, 64, 1, 0), (2, 1, 129, 4, 60, 1, 0), (4, 2, 700, 64, 200, 1, 0), (2, 2, 640, 0, 640, 1, 0),
+    (2, 1, 1000, 64, 128, 64, 4), (2, 2, 1090, 16, 100, 1, 0)])
+def test_few_work_items_give_the_same_bits(Hq, Hkv, N, sink, window, block, stride, D):
+    """Up to 256 work items of 128 rows take an instance of their own: the same bits as in a batch of more, to which the oracle
+    is close."""
+    check_fwd(1, Hq, Hkv, N, D, sink, window, block, stride, seed=15)
+    q, k, v = (x.to(DEV) for x in lg_synth.prefill_inputs(1, Hq, Hkv, N, D, 15, torch.bfloat16))
+    out, lse = torch.empty_like(q), torch.empty(1, Hq, N, dtype=torch.float32, device=DEV)
+    lg.lg_sparse_attn_fwd(q, k, v, out, lse, sink, window, block, stride)
+    many = 256 // (Hq * ((N + 127) // 128)) + 1
+    qm, km, vm = (x.repeat(many, 1, 1, 1) for x in (q, k, v))
+    om, lm = torch.empty_like(qm), torch.empty(many, Hq, N, dtype=torch.float32, device=DEV)
+    lg.lg_sparse_attn_fwd(qm, km, vm, om, lm, sink, window, block, stride)
+    assert torch.equal(om, out.expand_as(om)) and torch.equal(lm, lse.expand_as(lm))
+
+
+@pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_sink_window_ragged_gqa(D, dtype):
     check_fwd(2, 4, 2, 700, D, 64, 200, dtype=dtype, seed=2)
