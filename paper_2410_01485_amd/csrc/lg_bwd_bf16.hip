@@ -328,9 +328,10 @@ dq_bf16_kernel(
     int kind = LG_TILE_FULL;
     if (!lg_qsched_full(m, qs, t)) kind = lg_rows_kind(m, wrows, k0, k0 + TK - 1);
     const bool full = kind == LG_TILE_FULL;
-    // Whole tiles request the next one between matrix instructions instead of before them (D = 128; 32 heads, 16 x 2048
-    // tokens, causal 846 -> 826 us, 32 x 1024 499 -> 489, 2 of 24055 tokens, window 4032 160.8 -> 156.6).
-    const bool between = D == 128 && full && t_next >= 0 && N - t_next * TK >= TK;
+    // Whole tiles request the next one between matrix instructions instead of before them (32 heads of 128, 16 x 2048
+    // tokens, causal 846 -> 826 us, 32 x 1024 499 -> 489, 2 of 24055 tokens, window 4032 160.8 -> 156.6; heads of 64: 482 ->
+    // 470, 285 -> 279, 100.7 -> 96.8).
+    const bool between = full && t_next >= 0 && N - t_next * TK >= TK;
     if (t_next >= 0 && !between) issue(t_next, stage ^ 1);
     const int sk = stage * STAGE, sv = sk + T::BYTES;
     const uint32_t bits = full ? ~0u : lg_key_bits(m, iq, k0, g);  // bit 16 kb + r: the key of register r of block kb is live
