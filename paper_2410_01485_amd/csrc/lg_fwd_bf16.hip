@@ -107,13 +107,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D,
   const int qw0 = min(q0 + wave_s * 32, N - 1), qw1 = min(q0 + wave_s * 32 + 31, N - 1);  // this wave's rows
 
   // Rows that grow along the sequence, hardly more of them than places: the longest decide when the launch ends, so they go
-  // before their neighbours on the CU, the more the longer (full causal, 2 heads of 64, 113471 tokens 4.35 -> 4.12 ms; 2 of
-  // 128, 50000 tokens 1.50 -> 1.41; with 2.7 times as many items as places it costs 5 %).
+  // before their neighbours on the CU, the more the longer (full causal, heads of 64: 2 of 113471 tokens 4.15 -> 3.94 ms, 4 of
+  // 65536 3.02 -> 2.88; 2 of 128, 50000 tokens 1.50 -> 1.37; with 2.7 times as many items as places it costs 5 %).
   if (!PACK && !FEW && items.total <= 2 * 256 * Tune::WAVES && 2 * (long long)m.wb * m.b >= N) {
-    const int quarter = (int)(4LL * q0 / N);
-    if (quarter == 3) __builtin_amdgcn_s_setprio(3);
-    else if (quarter == 2) __builtin_amdgcn_s_setprio(2);
-    else if (quarter == 1) __builtin_amdgcn_s_setprio(1);
+    const int third = (int)(3LL * q0 / N);
+    if (third == 2) __builtin_amdgcn_s_setprio(2);
+    else if (third == 1) __builtin_amdgcn_s_setprio(1);
   }
   f32x16_t oacc[DB];
 #pragma unroll
