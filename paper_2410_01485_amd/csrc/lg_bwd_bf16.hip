@@ -203,7 +203,7 @@ dq_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const uint16_t* __restrict__ out, const uint16_t* __restrict__ dout, const float* __restrict__ lse,
     float* __restrict__ ndelta, float* __restrict__ nlse, uint16_t* __restrict__ dq, int Hq, int Hkv, float scale,
-    LgMask m_in, int nqt, int total, int run, LgBwdWork wk) {
+    LgMask m_in, int nqt, int total, LgRuns runs, LgBwdWork wk) {
   LgMask m = m_in;
   using T = LgSwzTile<D>;
   constexpr int NT = 256;
@@ -215,8 +215,8 @@ dq_bf16_kernel(
   __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * STAGE];
   __shared__ float s_rows[2][TQ];  // Delta, log-sum-exp
 
-  const int L = lg_item_of(blockIdx.x, run);
-  if (L >= total) return;
+  const int L = lg_item_of(blockIdx.x, runs);
+  if (L < 0 || L >= total) return;
   // logical order: (b, kv head) slowest, then query tile (longest rows first), then the query
   // heads of the GQA group: the G workgroups that walk the same K/V tiles run side by side
   const int G = Hq / Hkv;
@@ -2085,13 +2085,14 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
                                                       a.qt_wide, total, run, wk, queue, nitems);
   }
   if (a.qt_rest > 0) {
-    const int total = 2 * a.qt_rest * Hq * a.B, run = lg_run_length(m, total, nbh, 16 * (Hq / Hkv), packed);
-    const dim3 grid((unsigned)lg_run_grid(total, run));
+    const int total = 2 * a.qt_rest * Hq * a.B;
+    const LgRuns runs = lg_runs(m, nbh, 2 * a.qt_rest, Hq / Hkv, packed);
+    const dim3 grid((unsigned)lg_run_grid(runs, total));
     wk.qt_first = a.qt_wide;
     wk.turn = lg_may_turn(nbh, 2 * a.qt_rest);
 #define LG_DQ_LAUNCH(DD)                                                                                               \
   dq_bf16_kernel<DD><<<grid, 256, 0, s>>>(uq, uk, uv, uo, ug, lse, ndelta, nlse, dq, Hq, Hkv, scale, m, a.qt_rest, \
-                                              total, run, wk)
+                                              total, runs, wk)
     if (a.D == 64) LG_DQ_LAUNCH(64);
     else LG_DQ_LAUNCH(128);
 #undef LG_DQ_LAUNCH

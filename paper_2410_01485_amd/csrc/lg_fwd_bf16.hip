@@ -73,8 +73,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D,
   using Tune = LgFwdTune<D, FEW>;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[(FEW ? 4 : 3) * T::BYTES];  // two K tiles, a V tile (FEW: two)
 
-  const int L = lg_item_of(blockIdx.x, items.run);
-  if (L >= items.total) return;
+  const int L = lg_item_of(blockIdx.x, items);
+  if (L < 0 || L >= items.total) return;
   const LgItem it = lg_item(items, L);
   const int b = it.b, hk = it.hk, hq = it.hq;
   int qt = (int)items.nqt.d - 1 - it.x;
@@ -310,10 +310,10 @@ hipError_t lg_launch_fwd_bf16(const void* q, const void* k, const void* v, void*
   const long long total_ll = (long long)nqt * sh.Hq * sh.B;
   if (total_ll > 0x7fffffffLL - 8) return hipErrorInvalidValue;
   const int total = (int)total_ll;
-  const int run = lg_run_length(m, total, sh.B * sh.Hkv, 16 * (sh.Hq / sh.Hkv), false);
+  const LgRuns runs = lg_runs(m, sh.B * sh.Hkv, nqt, sh.Hq / sh.Hkv, false);
   const float sl2 = sh.scale * 1.44269504088896340736f;
-  const LgItems items = lg_make_items(total, run, nqt, sh.Hq, sh.Hkv);
-  const dim3 grid((unsigned)lg_run_grid(total, run));
+  const LgItems items = lg_make_items(total, runs, nqt, sh.Hq, sh.Hkv);
+  const dim3 grid((unsigned)lg_run_grid(runs, total));
 #define LG_FWD_LAUNCH(DD, FEW)                                                                             \
   fwd_bf16_kernel<DD, LgNoPack, FEW><<<grid, NT, 0, s>>>((const uint16_t*)q, (const uint16_t*)k,          \
                                                         (const uint16_t*)v, (uint16_t*)out, lse, sh.Hq,  \

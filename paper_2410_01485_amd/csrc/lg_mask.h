@@ -147,10 +147,43 @@ LG_HD int lg_item_of(int id, const LgDiv& run) {
 // well below the length, no strided columns).  Otherwise (causal or strided rows that grow along the sequence; packed
 // sequences: m.N is a length none reaches, varied = true) the XCD with the longest rows would run almost twice as long
 // as the average, and runs of `few` items are dealt.
+LG_HD bool lg_even_runs(const LgMask& m, int heads, bool varied) {
+  return heads % 8 == 0 || (!varied && m.stride == 0 && m.window <= m.N / 4);
+}
 LG_HD int lg_run_length(const LgMask& m, int total, int heads, int few, bool varied) {
   const int each = (total + 7) / 8;
-  const bool even = heads % 8 == 0 || (!varied && m.stride == 0 && m.window <= m.N / 4);
-  return even || few >= each ? each : few;
+  return lg_even_runs(m, heads, varied) || few >= each ? each : few;
+}
+LG_HD long long lg_run_grid(int total, int run) { return ((long long)total + 8LL * run - 1) / (8LL * run) * (8LL * run); }
+
+// Runs of the bf16 kernels that the hardware deals their items (not a queue).  Where rows grow the runs of all heads take
+// turns, longest rows first: head by head the longest rows of the last head start when the others are nearly done and end
+// the launch alone, and a dozen long runs leave some XCDs twice the work of others.  Full causal, forward: 3 heads of 64,
+// 80000 tokens 3003 -> 2553 us, 2 of 128, 48000 tokens 1370 -> 1245, 12/4 of 128, 16000 tokens 1178 -> 770; dq with 32 rows
+// per wave: 8/2 heads of 128, 12000 tokens 652 -> 440 us, 12/4 of 128, 1500 tokens 81 -> 71.  A run is up to 16 tiles of a
+// head, fewer where the XCDs would get less than four runs each, in equal parts so that few workgroups stay without an item.
+struct LgRuns {
+  int run;    // items of a run
+  int heads;  // of the launch, where they take turns; 0: listed head by head
+  int each;   // items of a head
+};
+inline LgRuns lg_runs(const LgMask& m, int heads, int tiles, int G, bool varied) {
+  const int each = tiles * G;
+  if (lg_even_runs(m, heads, varied)) return LgRuns{(int)(((long long)heads * each + 7) / 8), 0, each};
+  const long long most = ((long long)tiles * heads + 31) / 32;
+  const int parts = most < 16 ? (int)((tiles + most - 1) / most) : (tiles + 15) / 16;
+  return LgRuns{(tiles + parts - 1) / parts * G, heads, each};
+}
+inline long long lg_run_grid(const LgRuns& w, int total) {
+  const long long padded = w.heads > 0 ? (long long)w.heads * ((w.each + w.run - 1) / w.run) * w.run : total;
+  return (padded + 8LL * w.run - 1) / (8LL * w.run) * (8LL * w.run);
+}
+// The item of workgroup `id`, as numbered head by head; -1 or past the end: none.
+LG_HD int lg_item_of(int id, const LgRuns& w) {
+  const int x = id >> 3, r = x / w.run * 8 + (id & 7), in_run = x % w.run;
+  if (w.heads == 0) return r * w.run + in_run;
+  const int at = r / w.heads * w.run + in_run;
+  return at < w.each ? r % w.heads * w.each + at : -1;
 }
 // Within an XCD the hardware deals workgroups to its four shader engines strictly in turn, whatever they still have to do.
 // Where the rows of a head differ in cost and its tiles are an even number, the same engines get the long ones every time
@@ -167,10 +200,24 @@ LG_HD bool lg_turned(int head) { return (head & 2) == 0; }
 struct LgItems {
   int total;
   bool turn;
-  LgDiv run, G, nqt, Hkv;  // nqt: query tiles of a head (all packed sequences together)
+  bool mix;                       // the heads' runs take turns (LgRuns)
+  LgDiv run, G, nqt, Hkv, heads;  // nqt: query tiles of a head (all packed sequences together)
 };
 inline LgItems lg_make_items(int total, int run, int nqt, int Hq, int Hkv) {
-  return LgItems{total, lg_may_turn(total / (nqt * (Hq / Hkv)), nqt), lg_make_div(run), lg_make_div(Hq / Hkv), lg_make_div(nqt), lg_make_div(Hkv)};
+  const int heads = total / (nqt * (Hq / Hkv));
+  return LgItems{total, lg_may_turn(heads, nqt), false, lg_make_div(run), lg_make_div(Hq / Hkv), lg_make_div(nqt), lg_make_div(Hkv), lg_make_div(heads)};
+}
+inline LgItems lg_make_items(int total, const LgRuns& runs, int nqt, int Hq, int Hkv) {
+  LgItems w = lg_make_items(total, runs.run, nqt, Hq, Hkv);
+  w.mix = runs.heads > 0;
+  return w;
+}
+LG_HD int lg_item_of(int id, const LgItems& w) {  // as lg_item_of(id, LgRuns)
+  int in_run, head;
+  const int r = lg_divmod(w.run, id >> 3, &in_run) * 8 + (id & 7);
+  if (!w.mix) return r * (int)w.run.d + in_run;
+  const int at = lg_divmod(w.heads, r, &head) * (int)w.run.d + in_run, each = (int)(w.nqt.d * w.G.d);
+  return at < each ? head * each + at : -1;
 }
 struct LgItem {
   int b, hk, hq, x;  // x: query tile, counted from the last one
@@ -184,7 +231,6 @@ LG_HD LgItem lg_item(const LgItems& w, int L) {
   it.hq = it.hk * (int)w.G.d + gq;
   return it;
 }
-LG_HD long long lg_run_grid(int total, int run) { return ((long long)total + 8LL * run - 1) / (8LL * run) * (8LL * run); }
 
 enum { LG_TILE_DEAD = 0, LG_TILE_PARTIAL = 1, LG_TILE_FULL = 2 };
 

@@ -44,6 +44,56 @@ int main() {
 }
 """
 
+RUNS = r"""
+#include <cstdio>
+#include <vector>
+#include "lg_mask.h"
+// B, Hq, Hkv, N, sink, window, block, stride: causal, windowed and strided, few heads and many, one tile and hundreds
+int main() {
+  const int shapes[][8] = {{1, 8, 2, 12000, 0, 12000, 1, 0}, {1, 12, 4, 16000, 0, 16000, 1, 0}, {1, 16, 4, 5000, 64, 2600, 1, 0},
+                           {2, 4, 1, 12000, 0, 12000, 1, 0}, {3, 2, 2, 30000, 0, 30000, 1, 0}, {1, 4, 2, 9000, 64, 512, 64, 8}, {1, 1, 1, 9000, 0, 9000, 1, 0},
+                           {1, 1, 1, 70, 0, 70, 1, 0}, {100, 3, 1, 300, 0, 300, 1, 0}, {1, 6, 6, 2200, 0, 2200, 1, 0}, {5, 3, 3, 128, 0, 128, 1, 0},
+                           {1, 7, 1, 4000, 0, 600, 1, 0}, {2, 16, 4, 3000, 16, 3000, 1, 0}, {4, 8, 4, 1000, 0, 1000, 1, 0}, {1, 64, 4, 33000, 64, 9000, 1, 0}};
+  for (auto& s : shapes) {
+    const int B = s[0], Hq = s[1], Hkv = s[2], N = s[3], G = Hq / Hkv, tiles = (N + 127) / 128, total = tiles * Hq * B;
+    const LgMask m = lg_make_mask(N, s[4], s[5], s[6], s[7]);
+    for (int varied = 0; varied < 2; ++varied) {
+      const LgRuns w = lg_runs(m, B * Hkv, tiles, G, varied);
+      const LgItems items = lg_make_items(total, w, tiles, Hq, Hkv);
+      const long long grid = lg_run_grid(w, total);
+      std::vector<int> seen(total, 0);
+      double work[8] = {}, all = 0, longest = 0;
+      for (long long id = 0; id < grid; ++id) {
+        const int L = lg_item_of((int)id, w);
+        if (L != lg_item_of((int)id, items)) return 1;
+        if (L < 0 || L >= total) continue;
+        ++seen[L];
+        const LgItem it = lg_item(items, L);
+        const int qt = tiles - 1 - it.x, q0 = qt * 128, q1 = q0 + 127 < N - 1 ? q0 + 127 : N - 1;
+        const LgQSched qs = lg_qsched_init(m, q0, q1);
+        double keys = 4;  // (start and end of an item, in tiles)
+        for (int t = lg_qsched_next(m, qs, -1); t >= 0; t = lg_qsched_next(m, qs, t)) ++keys;
+        work[id & 7] += keys;
+        all += keys;
+        longest = keys > longest ? keys : longest;
+      }
+      for (int x : seen)
+        if (x != 1) return 2;
+      // workgroups without an item: less than an eighth, beyond the padding to whole rounds of runs
+      if (grid > total + total / 8 + 8LL * w.run) { std::printf("grid %lld for %d items\n", grid, total); return 3; }
+      // no XCD has much more than its share (a launch that each XCD gets a few rows of: not more than those)
+      double most = 0;
+      for (double x : work) most = x > most ? x : most;
+      if (!varied && most > 1.3 * all / 8 && most > 8 * longest) {
+        std::printf("B %d Hq %d Hkv %d N %d: an XCD has %.0f of %.0f tiles\n", B, Hq, Hkv, N, most, all / 8);
+        return 4;
+      }
+    }
+  }
+  return 0;
+}
+"""
+
 KINDS = r"""
 #include <cstdio>
 #include <cstdlib>
@@ -92,6 +142,12 @@ def run(tmp_path, program, opt):
 
 def test_classes_and_runs_from_bounds(tmp_path):
     run(tmp_path, KINDS, "-O2")
+
+
+@pytest.mark.parametrize("opt", ["-O0", "-O2"])
+def test_runs_cover_every_item_once_and_give_the_xcds_even_shares(tmp_path, opt):
+    """Where rows grow and heads are few: with runs of 16 tiles listed head by head an XCD had up to twice its share."""
+    run(tmp_path, RUNS, opt)
 
 
 @pytest.mark.parametrize("opt", ["-O0", "-O2"])
