@@ -34,7 +34,7 @@
 // by each lane from or to its own row, an instruction touches 32 rows, and these instructions took as long as several
 // tiles, with one workgroup per CU with nothing beside them.  32 heads of 128, 32768 tokens: window 64 dq 374 -> 328, dk/dv
 // 461 -> 390 us; 512 590 -> 570, 830 -> 782; 2048 (64 rows per wave) 1545 -> 1493, 1910 -> 1875; 64 x 512 tokens 465 -> 380,
-// 630 -> 495 (some of that from the order of the tiles, lg_may_turn).
+// 630 -> 495 (some of that from the order of the tiles, lg_order).
 //
 // For head dim 128 and long windows (dq 32 or more tiles, dk/dv 16) both kernels have a second form with 64 rows
 // (keys) per wave, one wave per SIMD and the accumulators in AGPRs (further down): every operand
@@ -99,7 +99,7 @@ struct LgBwdWork {
   float* lonepart;        // Hq == Hkv: [b x kv head][lone chunks of all sequences] group slots
   int nlone_all;          // lone chunks of all sequences
   unsigned* arrived;      // Hq == Hkv: [b x kv head][sequence] chunks of a lone group that are done
-  bool turn;              // lg_may_turn
+  int order;              // lg_order
   bool by_tile;           // dk/dv items: heads innermost (always for packed sequences and cut window parts)
   // window parts cut into `heads_cut` sets of query heads times `rows_cut` runs of query tiles
   int heads_cut, rows_cut;
@@ -222,9 +222,9 @@ dq_bf16_kernel(
   const int G = Hq / Hkv;
   const int gq = L % G, rest = L / G;
   // (nqt, qtile0: in LG_BF16_TQ rows, two workgroups each)
-  const int bhk = (rest >> 1) / nqt;
-  int y = rest - bhk * 2 * nqt;
-  if (wk.turn && lg_turned(bhk)) y = 2 * nqt - 1 - y;
+  const int at = lg_order_at(wk.order, rest);
+  int bhk = (at >> 1) / nqt, y = at - bhk * 2 * nqt;
+  lg_in_order(wk.order, rest, 2 * nqt, &bhk, &y);
   const int half = 1 - (y & 1), x = y >> 1;
   int qt = nqt - 1 - x;
   const int b = bhk / Hkv, hk = bhk % Hkv;
@@ -567,9 +567,10 @@ __device__ __forceinline__ bool lg_bwd_main(const LgBwdWork& wk, int bid, int nk
     return true;
   }
   const int L = lg_item_of(bid, run);
-  w.bh = L / nkt;
-  w.kt = L % nkt;
-  if (wk.turn && lg_turned(w.bh)) w.kt = nkt - 1 - w.kt;
+  const int at = lg_order_at(wk.order, L);
+  w.bh = at / nkt;
+  w.kt = at % nkt;
+  lg_in_order(wk.order, L, nkt, &w.bh, &w.kt);
   return L < total;
 }
 // The query tiles [lo, hi] and query heads of the part: the window part of keys [k0, k1] (all query tiles that see them
@@ -2072,7 +2073,7 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
   wk.heads_cut = a.cut.heads;
   wk.rows_cut = a.cut.rows;
   wk.parts = (float*)(w + l.parts);
-  wk.turn = false;
+  wk.order = LG_BY_HEAD;
   if (a.qt_wide > 0) {
     const int total = a.qt_wide * Hq * a.B, run = lg_run_length(m, total, nbh, 8 * (Hq / Hkv), packed);
     const int nitems = (int)lg_run_grid(total, run);
@@ -2089,7 +2090,7 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
     const LgRuns runs = lg_runs(m, nbh, 2 * a.qt_rest, Hq / Hkv, packed);
     const dim3 grid((unsigned)lg_run_grid(runs, total));
     wk.qt_first = a.qt_wide;
-    wk.turn = lg_may_turn(nbh, 2 * a.qt_rest);
+    wk.order = lg_order(nbh, 2 * a.qt_rest);
 #define LG_DQ_LAUNCH(DD)                                                                                               \
   dq_bf16_kernel<DD><<<grid, 256, 0, s>>>(uq, uk, uv, uo, ug, lse, ndelta, nlse, dq, Hq, Hkv, scale, m, a.qt_rest, \
                                               total, runs, wk)
@@ -2122,7 +2123,7 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
   }
   if (a.kt_wide > 0) {
     // one resident workgroup per CU, work items from the second queue
-    wk.turn = false;  // (a queue hands them out)
+    wk.order = LG_BY_HEAD;  // (a queue hands them out)
     const int nkt = a.kt_wide, total = nkt * nbh, run = lg_run_length(m, total, nbh, 8, false);
     const int nitems = wk.by_tile ? total * nparts : (int)lg_run_grid(total, run);
     const dim3 grid((unsigned)(nitems < cus ? nitems : cus));
@@ -2135,7 +2136,7 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
     const int nkt = a.kt_rest, total = nkt * nbh, run = lg_run_length(m, total, nbh, 8, false);
     const dim3 grid((unsigned)(wk.by_tile ? total * nparts : (int)lg_run_grid(total, run)));
     wk.items = items + a.kt_wide;
-    wk.turn = lg_may_turn(nbh, nkt);
+    wk.order = lg_order(nbh, nkt);
     if (a.D == 64) LG_DKDV_LAUNCH(64, false, grid);
     else LG_DKDV_LAUNCH(128, false, grid);
   }

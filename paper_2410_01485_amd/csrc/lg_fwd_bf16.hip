@@ -89,7 +89,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D,
     }
     const int nt = pack.tile0[lo + 1] - pack.tile0[lo];
     qt -= pack.tile0[lo];
-    if (nt % 2 == 0 && nt <= 64 && lg_turned(lo ^ 2)) qt = nt - 1 - qt;  // (as lg_may_turn; sequence 0 comes last)
+    // two sequences in four the other way round where their tiles are an even number (lg_order says why; sequence 0 comes last)
+    if (nt % 2 == 0 && nt <= 64 && (lo & 2) != 0) qt = nt - 1 - qt;
     seq_row0 = pack.row0[lo];
     m = lg_mask_for_length(m, pack.row0[lo + 1] - seq_row0);
   }

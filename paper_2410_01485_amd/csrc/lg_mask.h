@@ -185,27 +185,39 @@ LG_HD int lg_item_of(int id, const LgRuns& w) {
   const int at = r / w.heads * w.run + in_run;
   return at < w.each ? r % w.heads * w.each + at : -1;
 }
-// Within an XCD the hardware deals workgroups to its four shader engines strictly in turn, whatever they still have to do.
-// Where the rows of a head differ in cost and its tiles are an even number, the same engines get the long ones every time
-// (8 tiles of a causal head: 3072 : 2560 : 2048 : 1536 key tiles, 2.0 of 3 workgroups of a CU in flight on average).  So
-// two heads in four take their tiles in the other order; not the last two of an XCD's heads, so that its last items are
-// short ones.  Not for odd numbers, which mix by themselves (3 tiles turned: 215 -> 258 us), nor beyond 64 tiles, where the
-// engines' shares differ by less than 5 % and a turned head would end on a long row, nor for kernels that take items from
-// a queue.
-LG_HD bool lg_may_turn(int heads, int tiles) { return heads % 32 == 0 && tiles % 2 == 0 && tiles <= 64; }
-LG_HD bool lg_turned(int head) { return (head & 2) == 0; }
+// Within an XCD the hardware deals workgroups to its four shader engines strictly in turn, whatever they still have to do,
+// and an engine's to its CUs in turn.  Where the rows of a head differ in cost, one head after the other gives the same
+// engines the long rows every time (8 tiles of a causal head: 3072 : 2560 : 2048 : 1536 key tiles, 2.0 of 3 workgroups of a
+// CU in flight on average) and in launches of one or two rounds the same CUs.  So heads go four by four, their tiles side by
+// side, longest rows first, and with an even number of fours for each XCD every other four the other way round: what a CU
+// gets of two of them adds up evenly.  Forward, 32 heads: 1 x 4500 tokens of 128 196 us head by head, with two heads in four
+// the other way round 219, so 182; 1 x 6000 of 64 197 -> 163; 2 x 2048 of 64 72, 50, 48; 64 x 512 of 128 278, 249, 247; 8 x
+// 4096 1155, 1125, 1125.  Beyond 64 tiles the engines' shares differ by less than 5 %, and tiles side by side are no
+// neighbours any more.  Not for kernels that take items from a queue.
+enum { LG_BY_HEAD = 0, LG_BY_FOUR = 1, LG_BY_FOUR_TURNED = 2 };
+LG_HD int lg_order(int heads, int tiles) {
+  return heads % 32 != 0 || tiles > 64 ? LG_BY_HEAD : heads % 64 != 0 ? LG_BY_FOUR : LG_BY_FOUR_TURNED;
+}
+// Item `at` of a launch with `tiles` items a head: divide lg_order_at by `tiles`, then lg_in_order makes head and tile of
+// quotient and remainder.
+LG_HD int lg_order_at(int order, int at) { return order == LG_BY_HEAD ? at : at >> 2; }
+LG_HD void lg_in_order(int order, int at, int tiles, int* head, int* x) {
+  if (order == LG_BY_HEAD) return;
+  if (order == LG_BY_FOUR_TURNED && (*head & 1) == 0) *x = tiles - 1 - *x;
+  *head = 4 * *head + (at & 3);
+}
 
-// The items of kernels that take query tiles: (b, kv head) slowest, then the query tile, longest rows first, then the
-// query heads of the group, so that the G workgroups that walk the same K/V tiles run side by side.
+// The items of kernels that take query tiles: (b, kv head) slowest (but see lg_order), then the query tile, longest rows
+// first, then the query heads of the group, so that the G workgroups that walk the same K/V tiles run side by side.
 struct LgItems {
   int total;
-  bool turn;
+  int order;                      // lg_order
   bool mix;                       // the heads' runs take turns (LgRuns)
   LgDiv run, G, nqt, Hkv, heads;  // nqt: query tiles of a head (all packed sequences together)
 };
 inline LgItems lg_make_items(int total, int run, int nqt, int Hq, int Hkv) {
   const int heads = total / (nqt * (Hq / Hkv));
-  return LgItems{total, lg_may_turn(heads, nqt), false, lg_make_div(run), lg_make_div(Hq / Hkv), lg_make_div(nqt), lg_make_div(Hkv), lg_make_div(heads)};
+  return LgItems{total, lg_order(heads, nqt), false, lg_make_div(run), lg_make_div(Hq / Hkv), lg_make_div(nqt), lg_make_div(Hkv), lg_make_div(heads)};
 }
 inline LgItems lg_make_items(int total, const LgRuns& runs, int nqt, int Hq, int Hkv) {
   LgItems w = lg_make_items(total, runs.run, nqt, Hq, Hkv);
@@ -225,8 +237,9 @@ struct LgItem {
 LG_HD LgItem lg_item(const LgItems& w, int L) {
   LgItem it;
   int gq;
-  const int rest = lg_divmod(w.G, L, &gq), bhk = lg_divmod(w.nqt, rest, &it.x);
-  if (w.turn && lg_turned(bhk)) it.x = (int)w.nqt.d - 1 - it.x;
+  const int rest = lg_divmod(w.G, L, &gq);
+  int bhk = lg_divmod(w.nqt, lg_order_at(w.order, rest), &it.x);
+  lg_in_order(w.order, rest, (int)w.nqt.d, &bhk, &it.x);
   it.b = lg_divmod(w.Hkv, bhk, &it.hk);
   it.hq = it.hk * (int)w.G.d + gq;
   return it;

@@ -65,9 +65,32 @@ def test_patterns_and_edges(dtype, N, sink, window, block, stride):
 
 @pytest.mark.parametrize("Hq,N,D,window", [(16, 500, 128, 500), (16, 500, 64, 200), (32, 250, 64, 250), (16, 300, 128, 300)])
 def test_heads_that_take_their_tiles_in_the_other_order(Hq, N, D, window):
-    """32 kv heads and an even number of tiles (forward and dq 2 or 4, dk/dv 2 or 4)."""
+    """32 kv heads, which the forward and dq take four by four, 2 to 4 tiles each.  (dk/dv takes so few key tiles head by
+    head: test_heads_four_by_four.)"""
     check_fwd(2, Hq, 16, N, D, 0, window, seed=6)
     check_bwd(2, Hq, 16, N, D, 0, window, seed=6)
+
+
+@pytest.mark.parametrize("B,Hq,N,D,window", [
+    (33, 32, 500, 128, 500), (34, 32, 500, 128, 200), (17, 32, 500, 64, 500), (18, 32, 385, 64, 100), (33, 32, 600, 128, 600), (17, 64, 300, 128, 80)])
+def test_heads_four_by_four(B, Hq, N, D, window):
+    """More than 2048 (key tile, kv head) pairs of 32 or 64 heads each: dk/dv, dq and the forward take heads four by four, every
+    other four the other way round where the heads are a multiple of 64; odd and even numbers of tiles.  Without a sink and
+    groups of query heads the same bits as each sequence by itself, which takes other orders and is close to the oracle."""
+    gen = torch.Generator(device=DEV).manual_seed(61)
+    q, k, v, g = (torch.randn(B, Hq, N, D, generator=gen, device=DEV, dtype=torch.bfloat16) for _ in range(4))
+    assert Hq * B % 32 == 0 and Hq * B * -(-N // (256 if D == 128 else 128)) > 2048
+    got = run_fwd_bwd(q, k, v, g, 0, window)
+    for b in range(B):
+        one = [x[b:b + 1].contiguous() for x in (q, k, v, g)]
+        for name, x, y in zip(("dq", "dk", "dv"), got, run_fwd_bwd(*one, 0, window)):
+            assert torch.equal(x[b:b + 1], y), (name, b)
+    h = [f32np(x[1:2, 5:7]) for x in (q, k, v, g)]
+    w = O.bwd(*h, 0, window)
+    al = dq_delta_allowance(h[0], h[1], h[3], w["out"], 0, window, 1, 0)
+    for name, x in zip(("dq", "dk", "dv"), got):
+        assert_close(f32np(x[1:2, 5:7]), w[name], TOL_OUT[torch.bfloat16], TOL_REL[torch.bfloat16], name,
+                     allow=al if name == "dq" else None)
 
 
 @pytest.mark.parametrize("N,sink,window,block,stride", [(3200, 0, 2600, 1, 0), (3140, 64, 2624, 64, 0), (3100, 64, 2304, 64, 8)])

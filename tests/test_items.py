@@ -25,7 +25,7 @@ int main() {
       if (x != n / d || rem != n % d) { std::printf("%lld / %d = %d rest %d\n", n, d, x, rem); return 1; }
     }
   }
-  const int shapes[][5] = {{1, 1, 1, 1, 1}, {2, 8, 2, 5, 3}, {3, 6, 6, 7, 16}, {1, 64, 8, 129, 1000}, {4, 4, 1, 2, 2}, {4, 16, 16, 8, 7}, {4, 32, 16, 2, 300}};
+  const int shapes[][5] = {{1, 1, 1, 1, 1}, {2, 8, 2, 5, 3}, {3, 6, 6, 7, 16}, {1, 64, 8, 129, 1000}, {4, 4, 1, 2, 2}, {4, 16, 16, 8, 7}, {4, 32, 16, 2, 300}, {1, 32, 32, 5, 20}, {3, 64, 32, 6, 144}, {2, 32, 32, 1, 8}, {4, 24, 24, 64, 768}, {1, 32, 32, 65, 260}};
   for (auto& s : shapes) {
     const int B = s[0], Hq = s[1], Hkv = s[2], nqt = s[3], run = s[4], total = B * Hq * nqt;
     const LgItems w = lg_make_items(total, run, nqt, Hq, Hkv);
@@ -94,6 +94,41 @@ int main() {
 }
 """
 
+ORDER = r"""
+#include <cstdio>
+#include <vector>
+#include "lg_mask.h"
+// Causal heads, every XCD an eighth of them: the shares of its four shader engines, which get workgroups in turn, and, where
+// all are in flight at once, of its 32 CUs.
+int main() {
+  const int heads_[] = {32, 64, 128, 512, 2048}, tiles_[] = {3, 4, 8, 16, 24, 28, 36, 47, 64};
+  for (int heads : heads_)
+    for (int tiles : tiles_) {
+      const int total = heads * tiles, each = total / 8;
+      const LgItems w = lg_make_items(total, each, tiles, heads, heads);
+      double se[4] = {}, cu[32] = {}, all = 0;
+      std::vector<int> seen(total, 0);
+      for (int i = 0; i < each; ++i) {
+        const LgItem it = lg_item(w, lg_item_of(8 * i, w));  // XCD 0
+        if (it.hk >= heads / 8) return 1;                    // whole heads
+        const double cost = tiles - it.x + 1;
+        ++seen[it.hk * tiles + it.x];
+        se[i % 4] += cost;
+        cu[i % 32] += cost;
+        all += cost;
+      }
+      for (int x = 0; x < each; ++x)
+        if (seen[x] != 1) return 2;
+      for (double x : se)
+        if (x > 1.08 * all / 4) { std::printf("%d heads of %d tiles: an engine has %.0f of %.0f\n", heads, tiles, x, all / 4); return 3; }
+      if (each == 96 || each == 128)
+        for (double x : cu)
+          if (x > 1.3 * all / 32) { std::printf("%d heads of %d tiles: a CU has %.0f of %.1f\n", heads, tiles, x, all / 32); return 4; }
+    }
+  return 0;
+}
+"""
+
 KINDS = r"""
 #include <cstdio>
 #include <cstdlib>
@@ -148,6 +183,11 @@ def test_classes_and_runs_from_bounds(tmp_path):
 def test_runs_cover_every_item_once_and_give_the_xcds_even_shares(tmp_path, opt):
     """Where rows grow and heads are few: with runs of 16 tiles listed head by head an XCD had up to twice its share."""
     run(tmp_path, RUNS, opt)
+
+
+def test_engines_and_cus_get_even_shares(tmp_path):
+    """With two heads in four the other way round the CUs of launches of one or two rounds got up to 1.5 times their share."""
+    run(tmp_path, ORDER, "-O2")
 
 
 @pytest.mark.parametrize("opt", ["-O0", "-O2"])
