@@ -125,7 +125,8 @@ int lg_sparse_attn_fwd(const void* q, const void* k, const void* v, void* out, f
  * and strided-column keys into it with hardware float atomics; their order is not fixed, so
  * the last bits of those dk/dv rows can differ between runs (a sink + window call with
  * Hq == Hkv uses no atomics and is bit-reproducible; there dk and dv do not depend on B either, elsewhere
- * the number of float32 partial sums of a key does).
+ * and on the float32 path the number of float32 partial sums of a key does).  out, lse and dq of a sequence have the same bits
+ * in every batch, on both paths.
  */
 size_t lg_sparse_attn_bwd_workspace_bytes(int B, int Hq, int Hkv, int N, int D,
                                           int sink, int window, int block, int stride, int dtype);

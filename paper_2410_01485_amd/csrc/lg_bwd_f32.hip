@@ -6,9 +6,8 @@
 //   dq_i = scale sum_j dS_ij k_j        (query-tile major, same tile walk as the forward; forms Delta too)
 //   dk_j = scale sum_i dS_ij q_i,  dv_j = sum_i P_ij dout_i   (key-tile major, summed over the query heads of
 //          the group)
-// Precision path for float32 data: every product on the float32 matrix instruction (lg_f32.h).  dq uses 8 waves, as the
-// forward: 4 groups of 16 rows x 2 halves of a tile's keys, or 2 x 4 (SPLIT), summed through LDS at the end, so that two waves
-// share a SIMD.  dk/dv uses 4 waves per 32 keys: 2 groups of 16 keys x 2 halves of a step's query rows (64, at head dim
+// Precision path for float32 data: every product on the float32 matrix instruction (lg_f32.h).  dq uses 8 or 4 waves, as
+// the forward: 4 or 2 groups of 16 rows x 2 halves of a tile's keys, summed through LDS at the end.  dk/dv uses 4 waves per 32 keys: 2 groups of 16 keys x 2 halves of a step's query rows (64, at head dim
 // 128 32), two workgroups per CU: as 8 waves per 64 keys one workgroup fitted a CU (167 registers, 66 KB; at head dim 128
 // 256 with spills), so that 280 work items were two rounds on 256 CUs, and every window had to be cut in two.  16/8 heads
 // of 64, 1024 tokens, window 128: dk/dv 44 -> 29 us (of that 3 from the masks, LgF32Row); 4 heads of 128, 4096 tokens,
@@ -28,24 +27,23 @@
 namespace {
 
 constexpr float LOG2E = 1.44269504088896340736f;
-constexpr int NT = 512;
 using I0 = std::integral_constant<int, 0>;
 using I1 = std::integral_constant<int, 1>;
 using I2 = std::integral_constant<int, 2>;
-static_assert(LG_F32_TQ == 64 && LG_F32_TK == 64, "64 x 64 tiles");
+static_assert(LG_F32_TK == 64, "two key halves of 32");
 static_assert(LG_F32_KEYS == 32, "two groups of 16 keys");
 
 // ------------------------------------------------------------------------- dq
 // Also forms Delta for the dk/dv kernel and clears its arrival counters.
-template <int D, int SPLIT>
-__global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void dq_f32_kernel(
+template <int D, int TQ>
+__global__ __launch_bounds__(8 * TQ, (D == 64 ? 4 : 2) * TQ / 64) void dq_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
     const float* __restrict__ out, const float* __restrict__ dout, const float* __restrict__ lse,
     float* __restrict__ delta, float* __restrict__ dq, int Hq, int Hkv, float scale, LgMask m, LgItems items,
     unsigned* __restrict__ arrived, int ncounters) {
   using T = LgF32Tile<D>;
+  constexpr int RG = TQ / 16, NT = 128 * RG;  // as in the forward
   using Dma = LgTileDma<T, NT>;
-  constexpr int RG = 8 / SPLIT, TQ = 16 * RG, BLOCKS = 4 / SPLIT;  // as in the forward
   constexpr int TK = LG_F32_TK, DC = D / 16;
   constexpr int STAGE = 2 * T::BYTES, LPT = 2 * Dma::CH;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * STAGE];
@@ -116,11 +114,11 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void dq_f32_kernel(
     else LG_WAIT_VMCNT(0);
     __syncthreads();
     const int sk = stage * STAGE, sv = sk + T::BYTES;
-    const int rb0 = BLOCKS * kh, kk = t * TK + 16 * rb0;
-    int kind0 = LG_TILE_FULL, kind1 = BLOCKS == 2 ? LG_TILE_FULL : LG_TILE_DEAD;  // of the wave's 16-key blocks
+    const int rb0 = 2 * kh, kk = t * TK + 32 * kh;
+    int kind0 = LG_TILE_FULL, kind1 = LG_TILE_FULL;  // of the wave's two 16-key blocks
     if (!lg_qsched_full(m, qs, t)) {
       kind0 = lg_rows_kind(m, rows, kk, kk + 15);
-      if (BLOCKS == 2) kind1 = lg_rows_kind(m, rows, kk + 16, kk + 31);
+      kind1 = lg_rows_kind(m, rows, kk + 16, kk + 31);
     }
     const bool masked = kind0 == LG_TILE_PARTIAL || kind1 == LG_TILE_PARTIAL;
     // as in the forward: units of matrix instructions, their LDS operands requested one unit ahead
@@ -193,13 +191,9 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void dq_f32_kernel(
         for (int db = 0; db < DC; ++db) acc[db] = lg_mfma16(kc[u & 1][db], s[u >> 2][u & 3], acc[db]);
       }
     };
-    if constexpr (BLOCKS == 1) {
-      if (kind0 != LG_TILE_DEAD) run(I0{}, I1{});
-    } else {
-      if (kind0 != LG_TILE_DEAD && kind1 != LG_TILE_DEAD) run(I0{}, I2{});
-      else if (kind0 != LG_TILE_DEAD) run(I0{}, I1{});
-      else if (kind1 != LG_TILE_DEAD) run(I1{}, I1{});
-    }
+    if (kind0 != LG_TILE_DEAD && kind1 != LG_TILE_DEAD) run(I0{}, I2{});
+    else if (kind0 != LG_TILE_DEAD) run(I0{}, I1{});
+    else if (kind1 != LG_TILE_DEAD) run(I1{}, I1{});
     __syncthreads();  // everyone is done with this stage
     const int t2 = tn >= 0 ? lg_qsched_next(m, qs, tn) : -1;
     if (t2 >= 0) issue(t2, stage);
@@ -207,27 +201,19 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void dq_f32_kernel(
     tn = t2;
   }
 
-  float4* so = reinterpret_cast<float4*>(smem);  // add the key shares
-  static_assert((SPLIT - 1) * RG * DC * 64 * 16 <= 2 * STAGE, "the shares fit the stages");
-  if (kh > 0)
+  float4* so = reinterpret_cast<float4*>(smem);  // add the two key halves
+  if (kh == 1)
 #pragma unroll
     for (int db = 0; db < DC; ++db)
-      so[(((kh - 1) * RG + rg) * DC + db) * 64 + lane] = make_float4(acc[db][0], acc[db][1], acc[db][2], acc[db][3]);
+      so[(rg * DC + db) * 64 + lane] = make_float4(acc[db][0], acc[db][1], acc[db][2], acc[db][3]);
   __syncthreads();
   if (kh == 0 && i < N)
 #pragma unroll
     for (int db = 0; db < DC; ++db) {
-      f32x4_t r = acc[db];
-#pragma unroll
-      for (int x = 0; x < SPLIT - 1; ++x) {
-        const float4 y = so[((x * RG + rg) * DC + db) * 64 + lane];
-        r[0] += y.x;
-        r[1] += y.y;
-        r[2] += y.z;
-        r[3] += y.w;
-      }
+      const float4 x = so[(rg * DC + db) * 64 + lane];
       *reinterpret_cast<float4*>(dq + qbase + (size_t)i * D + 16 * db + 4 * h) =
-          make_float4(r[0] * scale, r[1] * scale, r[2] * scale, r[3] * scale);
+          make_float4((acc[db][0] + x.x) * scale, (acc[db][1] + x.y) * scale, (acc[db][2] + x.z) * scale,
+                      (acc[db][3] + x.w) * scale);
     }
 }
 
@@ -616,7 +602,7 @@ hipError_t launch_bwd(const float* q, const float* k, const float* v, const floa
   unsigned* arrived = (unsigned*)((char*)ws + pt.counters_off);
   float* part = (float*)((char*)ws + pt.part_off);
   const long long ncnt = pt.part_off > pt.counters_off ? (long long)heads * pt.nkt : 0;
-  const int split = lg_f32_split(sh, m), nqt = ceil_div(sh.N, 128 / split);
+  const int TQ = lg_f32_rows(sh, m), nqt = ceil_div(sh.N, TQ);
   const long long tl = (long long)nqt * sh.Hq * sh.B;
   const long long items = (long long)heads * ((long long)pt.nkt * pt.nsp + (long long)pt.ncand * pt.ncc);
   if (tl > 0x7fffffffLL - 8 || items > 0x7fffffffLL || ncnt > 0x7fffffffLL) return hipErrorInvalidValue;
@@ -624,9 +610,9 @@ hipError_t launch_bwd(const float* q, const float* k, const float* v, const floa
     (void)hipEventRecord(ev[0], s);
     (void)hipEventRecord(ev[1], s);
   }
-  const int total = (int)tl, run = lg_run_length(m, total, sh.B * sh.Hkv, 2 * split * (sh.Hq / sh.Hkv), false);
-  const auto kernel = split == 2 ? dq_f32_kernel<D, 2> : dq_f32_kernel<D, 4>;
-  kernel<<<dim3((unsigned)lg_run_grid(total, run)), NT, 0, s>>>(q, k, v, out, dout, lse, delta, dq, sh.Hq, sh.Hkv, sh.scale, m,
+  const int total = (int)tl, run = lg_run_length(m, total, sh.B * sh.Hkv, 256 / TQ * (sh.Hq / sh.Hkv), false);
+  const auto kernel = TQ == 64 ? dq_f32_kernel<D, 64> : dq_f32_kernel<D, 32>;
+  kernel<<<dim3((unsigned)lg_run_grid(total, run)), 8 * TQ, 0, s>>>(q, k, v, out, dout, lse, delta, dq, sh.Hq, sh.Hkv, sh.scale, m,
                                                     lg_make_items(total, run, nqt, sh.Hq, sh.Hkv), arrived, (int)ncnt);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -6,8 +6,8 @@
 // (D = 64, window 128) took 86 us; this form takes 17.
 //
 // One workgroup = 8 waves = 4 groups of 16 query rows of one (b, hq) x 2 halves of every 64-key tile (two waves per SIMD: one's
-// softmax runs under the other's matrix work), or, where that is few workgroups, 2 groups x 4 quarters (SPLIT, lg_f32_split);
-// merged at the end.  Per wave and 16-key block:
+// softmax runs under the other's matrix work), merged at the end; where that is few workgroups 4 waves = 2 groups x 2 halves
+// (lg_f32_rows).  What a wave does, and with it every bit of the result, is the same in both.  Per wave and 16-key block:
 //   S^T = K Q^T (keys x queries), online softmax with a lane owning one query, O^T += V^T P^T with P^T straight
 //   from the accumulator registers.
 // Bound: the float32 matrix rate (4096 cycles per 64 x 64 tile at D = 64); measured 98 TFLOP/s on full causal
@@ -17,20 +17,20 @@
 
 namespace {
 
-constexpr int TK = LG_F32_TK, NT = 512;
-static_assert(LG_F32_TQ == 64 && TK == 64, "4 row groups of 16, two key halves of 32");
+constexpr int TK = LG_F32_TK;
+static_assert(TK == 64, "two key halves of 32");
 
-// two workgroups per CU where LDS allows it (D = 64: 64 KB each)
-template <int D, int SPLIT>
-__global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_f32_kernel(const float* __restrict__ q,
+// TQ: query rows of a workgroup, 64 or 32.  Two workgroups per CU where LDS allows it (D = 64: 64 KB each)
+template <int D, int TQ>
+__global__ __launch_bounds__(8 * TQ, (D == 64 ? 4 : 2) * TQ / 64) void fwd_f32_kernel(const float* __restrict__ q,
                                                                       const float* __restrict__ k,
                                                                       const float* __restrict__ v,
                                                                       float* __restrict__ out,
                                                                       float* __restrict__ lse, int Hq, int Hkv,
                                                                       float scale, LgMask m, LgItems items) {
   using T = LgF32Tile<D>;
+  constexpr int RG = TQ / 16, NT = 128 * RG;  // row groups of two waves each
   using Dma = LgTileDma<T, NT>;
-  constexpr int RG = 8 / SPLIT, TQ = 16 * RG, BLOCKS = 4 / SPLIT;  // row groups, rows, 16-key blocks of a wave per tile
   constexpr int DC = D / 16;
   constexpr int STAGE = 2 * T::BYTES, LPT = 2 * Dma::CH;
   __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * STAGE];
@@ -85,11 +85,11 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_f32_kernel(const floa
     else LG_WAIT_VMCNT(0);
     __syncthreads();
     const int sk = stage * STAGE, sv = sk + T::BYTES;
-    const int rb0 = BLOCKS * kh, kk = t * TK + 16 * rb0;
-    int kind0 = LG_TILE_FULL, kind1 = BLOCKS == 2 ? LG_TILE_FULL : LG_TILE_DEAD;  // of the wave's 16-key blocks
+    const int rb0 = 2 * kh, kk = t * TK + 32 * kh;
+    int kind0 = LG_TILE_FULL, kind1 = LG_TILE_FULL;  // of the wave's two 16-key blocks
     if (!lg_qsched_full(m, qs, t)) {
       kind0 = lg_rows_kind(m, rows, kk, kk + 15);
-      if (BLOCKS == 2) kind1 = lg_rows_kind(m, rows, kk + 16, kk + 31);
+      kind1 = lg_rows_kind(m, rows, kk + 16, kk + 31);
     }
     const bool masked = kind0 == LG_TILE_PARTIAL || kind1 == LG_TILE_PARTIAL;
     // Blocks B0 .. B0 + NB - 1 of the half tile, as a straight sequence of units whose LDS operands are requested one
@@ -164,13 +164,9 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_f32_kernel(const floa
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
-    if constexpr (BLOCKS == 1) {
-      if (kind0 != LG_TILE_DEAD) run(I0{}, I1{});
-    } else {
-      if (kind0 != LG_TILE_DEAD && kind1 != LG_TILE_DEAD) run(I0{}, I2{});
-      else if (kind0 != LG_TILE_DEAD) run(I0{}, I1{});
-      else if (kind1 != LG_TILE_DEAD) run(I1{}, I1{});
-    }
+    if (kind0 != LG_TILE_DEAD && kind1 != LG_TILE_DEAD) run(I0{}, I2{});
+    else if (kind0 != LG_TILE_DEAD) run(I0{}, I1{});
+    else if (kind1 != LG_TILE_DEAD) run(I1{}, I1{});
     __syncthreads();  // everyone is done with this stage
     const int t2 = tn >= 0 ? lg_qsched_next(m, qs, tn) : -1;
     if (t2 >= 0) issue(t2, stage);
@@ -178,50 +174,28 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_f32_kernel(const floa
     tn = t2;
   }
 
-  // merge the key shares of the rows
-  constexpr int OTHERS = SPLIT - 1;
+  // merge the two key halves of the rows
   float l = lg_col_sum(lrow);
   float4* so = reinterpret_cast<float4*>(smem);
-  float2* sml = reinterpret_cast<float2*>(smem + OTHERS * RG * DC * 64 * 16);
-  static_assert(OTHERS * RG * (DC * 64 * 16 + 64 * 8) <= 2 * STAGE, "the shares fit the stages");
-  if (kh > 0) {
-    const int x = (kh - 1) * RG + rg;
+  float2* sml = reinterpret_cast<float2*>(smem + RG * DC * 64 * 16);
+  static_assert(RG * (DC * 64 * 16 + 64 * 8) <= 2 * STAGE, "a half's results fit the stages");
+  if (kh == 1) {
 #pragma unroll
-    for (int db = 0; db < DC; ++db) so[(x * DC + db) * 64 + lane] = make_float4(o[db][0], o[db][1], o[db][2], o[db][3]);
-    sml[x * 64 + lane] = make_float2(mref, l);
+    for (int db = 0; db < DC; ++db) so[(rg * DC + db) * 64 + lane] = make_float4(o[db][0], o[db][1], o[db][2], o[db][3]);
+    sml[rg * 64 + lane] = make_float2(mref, l);
   }
   __syncthreads();
   if (kh == 0 && i < N) {
-    float2 ml[OTHERS];
-    float M = mref;
-#pragma unroll
-    for (int x = 0; x < OTHERS; ++x) {
-      ml[x] = sml[(x * RG + rg) * 64 + lane];
-      M = fmaxf(M, ml[x].x);
-    }
-    const float Ms = M == -INFINITY ? 0.f : M;  // (no finite score: weights 0, lse -inf)
-    float f[SPLIT];
-    f[0] = __builtin_amdgcn_exp2f((mref - Ms) * c2);
-    l *= f[0];
-#pragma unroll
-    for (int x = 0; x < OTHERS; ++x) {
-      f[x + 1] = __builtin_amdgcn_exp2f((ml[x].x - Ms) * c2);
-      l += ml[x].y * f[x + 1];
-    }
-#pragma unroll
-    for (int x = 0; x < SPLIT; ++x) f[x] /= l;
+    const float2 ml = sml[rg * 64 + lane];
+    const float M = fmaxf(mref, ml.x), Ms = M == -INFINITY ? 0.f : M;  // (no finite score: weights 0, lse -inf)
+    const float wa = __builtin_amdgcn_exp2f((mref - Ms) * c2), wb = __builtin_amdgcn_exp2f((ml.x - Ms) * c2);
+    l = l * wa + ml.y * wb;
+    const float fa = wa / l, fb = wb / l;
 #pragma unroll
     for (int db = 0; db < DC; ++db) {
-      f32x4_t r = o[db] * f[0];
-#pragma unroll
-      for (int x = 0; x < OTHERS; ++x) {
-        const float4 y = so[((x * RG + rg) * DC + db) * 64 + lane];
-        r[0] += y.x * f[x + 1];
-        r[1] += y.y * f[x + 1];
-        r[2] += y.z * f[x + 1];
-        r[3] += y.w * f[x + 1];
-      }
-      *reinterpret_cast<float4*>(out + qbase + (size_t)i * D + 16 * db + 4 * h) = make_float4(r[0], r[1], r[2], r[3]);
+      const float4 x = so[(rg * DC + db) * 64 + lane];
+      *reinterpret_cast<float4*>(out + qbase + (size_t)i * D + 16 * db + 4 * h) =
+          make_float4(o[db][0] * fa + x.x * fb, o[db][1] * fa + x.y * fb, o[db][2] * fa + x.z * fb, o[db][3] * fa + x.w * fb);
     }
     if (lse != nullptr && h == 0)
       lse[(size_t)(b * Hq + hq) * m.ld + i] = (M * c2 + log2f(l)) * 0.69314718055994530942f;
@@ -232,18 +206,18 @@ __global__ __launch_bounds__(NT, D == 64 ? 4 : 2) void fwd_f32_kernel(const floa
 
 hipError_t lg_launch_fwd_f32(const float* q, const float* k, const float* v, float* out, float* lse,
                              const LgShape& sh, const LgMask& m, hipStream_t s) {
-  const int split = lg_f32_split(sh, m), TQ = 128 / split, nqt = (sh.N + TQ - 1) / TQ;
+  const int TQ = lg_f32_rows(sh, m), nqt = (sh.N + TQ - 1) / TQ;
   const long long tl = (long long)nqt * sh.Hq * sh.B;
   if (tl > 0x7fffffffLL - 8) return hipErrorInvalidValue;
-  const int total = (int)tl, run = lg_run_length(m, total, sh.B * sh.Hkv, 2 * split * (sh.Hq / sh.Hkv), false);
+  const int total = (int)tl, run = lg_run_length(m, total, sh.B * sh.Hkv, 256 / TQ * (sh.Hq / sh.Hkv), false);
   const LgItems items = lg_make_items(total, run, nqt, sh.Hq, sh.Hkv);
   const dim3 grid((unsigned)lg_run_grid(total, run));
-#define LG_FWD_LAUNCH(DD, SPLIT) \
-  fwd_f32_kernel<DD, SPLIT><<<grid, NT, 0, s>>>(q, k, v, out, lse, sh.Hq, sh.Hkv, sh.scale, m, items)
-  if (sh.D == 64 && split == 2) LG_FWD_LAUNCH(64, 2);
-  else if (sh.D == 64) LG_FWD_LAUNCH(64, 4);
-  else if (split == 2) LG_FWD_LAUNCH(128, 2);
-  else LG_FWD_LAUNCH(128, 4);
+#define LG_FWD_LAUNCH(DD, ROWS) \
+  fwd_f32_kernel<DD, ROWS><<<grid, 8 * ROWS, 0, s>>>(q, k, v, out, lse, sh.Hq, sh.Hkv, sh.scale, m, items)
+  if (sh.D == 64 && TQ == 64) LG_FWD_LAUNCH(64, 64);
+  else if (sh.D == 64) LG_FWD_LAUNCH(64, 32);
+  else if (TQ == 64) LG_FWD_LAUNCH(128, 64);
+  else LG_FWD_LAUNCH(128, 32);
 #undef LG_FWD_LAUNCH
   return hipGetLastError();
 }

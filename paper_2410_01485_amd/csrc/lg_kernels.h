@@ -27,18 +27,19 @@ struct LgShape {
   float scale;  // already resolved (> 0)
 };
 
-// float32 forward and dq: among how many waves a tile's keys are divided; 2: 64 query rows per workgroup, 4: 32 rows.  Four
-// shorten a row's chain of tiles and give twice the workgroups, but load the keys twice as often.  They pay where 64 rows
-// leave CUs without work: up to 128 workgroups (forward / dq, us: 1 head of 64, 2000 tokens, causal 83 -> 51 / 115 -> 71; 4
-// heads of 64, 2048 tokens, window 300 22 -> 15 / 31 -> 22; 192 workgroups 84 -> 79 / 114 -> 116, at head dim 128 156 -> 173 /
-// 212 -> 230), and where they would need a second round for less than half the CUs and rows are long enough for that to
-// matter (34 x 500 tokens of 64 42 -> 33 / 61 -> 49; 384 workgroups, window 1000 82 -> 71 / 116 -> 101, window 100
-// 22 -> 25 / 33 -> 38; 512 workgroups, window 300 36 -> 42 / 53 -> 59).  The shape alone decides, so that a sequence of a
-// pack, which has launches of its own, gets what it gets by itself.
-inline int lg_f32_split(const LgShape& sh, const LgMask& m) {
+// float32 forward and dq: query rows of a workgroup, 64 (8 waves) or 32 (4 waves, which do the same work each: every bit of a
+// sequence's results is the same in both, so the choice may depend on the batch).  32 halve the time of a row's chain of tiles,
+// whose matrix instructions two waves of a SIMD otherwise share, and give twice the workgroups, but load the keys twice as
+// often.  They pay where 64 rows leave CUs without work: up to 128 workgroups (forward / dq, us: 1 head of 64, 2000 tokens,
+// causal 84 -> 53 / 115 -> 70; 4 heads of 64, 2048 tokens, window 300 22.6 -> 16.4 / 32.7 -> 23.1; of 128 38 -> 27 / 55 -> 39; 192
+// workgroups, causal, of 128 160 -> 186 / 229 -> 254), and where they would need a second round for less than half the CUs
+// and rows are long enough for that to matter (34 x 500 tokens of 64 43 -> 34 / 64 -> 48, of 128 88 -> 71 / 127 -> 98; 384
+// workgroups, window 1000, of 64 87 -> 82 / 128 -> 112, of 128 180 -> 170 / 261 -> 238; window 100, of 64 23 -> 26 / 35 -> 37;
+// 512 workgroups, window 300, of 64 39 -> 45 / 59 -> 64).
+inline int lg_f32_rows(const LgShape& sh, const LgMask& m) {
   const long long n = (long long)sh.B * sh.Hq * ((sh.N + LG_F32_TQ - 1) / LG_F32_TQ);
   const long long reach = (long long)m.wb * m.b < sh.N ? (long long)m.wb * m.b : sh.N;
-  return n <= 128 || (n > 256 && n <= 384 && reach >= 256) ? 4 : 2;
+  return n <= 128 || (n > 256 && n <= 384 && reach >= 256) ? LG_F32_TQ / 2 : LG_F32_TQ;
 }
 
 // Each launcher enqueues on `s` and returns hipGetLastError().

@@ -131,6 +131,30 @@ def test_float32_dq_rows_per_workgroup(B, Hq, Hkv, N, D, sink, window):
     check_bwd(B, Hq, Hkv, N, D, sink, window, dtype=torch.float32, seed=13)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv,N,sink,window,block,stride", [
+    (2, 1, 700, 16, 90, 1, 0), (4, 4, 385, 0, 385, 1, 0), (8, 2, 200, 16, 48, 16, 3), (1, 1, 97, 17, 30, 1, 0)])
+def test_float32_rows_do_not_depend_on_the_batch(Hq, Hkv, N, sink, window, block, stride, D):
+    """Alone a sequence has up to 128 workgroups of 64 rows and takes 32 rows each, in a batch of more it takes 64: out, lse and
+    dq have the same bits."""
+    many = 128 // (Hq * -(-N // 64)) + 1
+    gen = torch.Generator(device=DEV).manual_seed(14)
+    q, k, v, g = (torch.randn(many, h, N, D, generator=gen, device=DEV) for h in (Hq, Hkv, Hkv, Hq))
+
+    def run(*x):
+        B = x[0].shape[0]
+        out, lse, dq, dk, dv = torch.empty_like(x[0]), torch.empty(B, Hq, N, device=DEV), *(torch.empty_like(y) for y in x[:3])
+        lg.lg_sparse_attn_fwd(*x[:3], out, lse, sink, window, block, stride)
+        ws = torch.empty(lg.bwd_workspace_bytes(B, Hq, Hkv, N, D, sink, window, block, stride, lg.LG_F32), dtype=torch.uint8, device=DEV)
+        lg.lg_sparse_attn_bwd(*x[:3], out, lse, x[3], dq, dk, dv, ws, sink, window, block, stride)
+        return out, lse, dq
+
+    got = run(q, k, v, g)
+    for b in (0, many - 1):
+        for name, x, y in zip(("out", "lse", "dq"), got, run(*(t[b:b + 1].contiguous() for t in (q, k, v, g)))):
+            assert torch.equal(x[b:b + 1], y), (name, b)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_peaked_scores_and_custom_scale(dtype):
     check_bwd(1, 2, 2, 600, 128, 16, 100, dtype=dtype, seed=4, q_mul=4.0, by_tensor_max=True)
