@@ -2090,7 +2090,7 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
     const LgRuns runs = lg_runs(m, nbh, 2 * a.qt_rest, Hq / Hkv, packed);
     const dim3 grid((unsigned)lg_run_grid(runs, total));
     wk.qt_first = a.qt_wide;
-    wk.order = lg_order(nbh, 2 * a.qt_rest);
+    wk.order = lg_order(nbh, 2 * a.qt_rest, Hq / Hkv, a.D);
 #define LG_DQ_LAUNCH(DD)                                                                                               \
   dq_bf16_kernel<DD><<<grid, 256, 0, s>>>(uq, uk, uv, uo, ug, lse, ndelta, nlse, dq, Hq, Hkv, scale, m, a.qt_rest, \
                                               total, runs, wk)
@@ -2136,7 +2136,7 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
     const int nkt = a.kt_rest, total = nkt * nbh, run = lg_run_length(m, total, nbh, 8, false);
     const dim3 grid((unsigned)(wk.by_tile ? total * nparts : (int)lg_run_grid(total, run)));
     wk.items = items + a.kt_wide;
-    wk.order = lg_order(nbh, nkt);
+    wk.order = lg_order(nbh, nkt, 1, a.D);
     if (a.D == 64) LG_DKDV_LAUNCH(64, false, grid);
     else LG_DKDV_LAUNCH(128, false, grid);
   }

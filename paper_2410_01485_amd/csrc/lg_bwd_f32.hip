@@ -613,7 +613,7 @@ hipError_t launch_bwd(const float* q, const float* k, const float* v, const floa
   const int total = (int)tl, run = lg_run_length(m, total, sh.B * sh.Hkv, 256 / TQ * (sh.Hq / sh.Hkv), false);
   const auto kernel = TQ == 64 ? dq_f32_kernel<D, 64> : dq_f32_kernel<D, 32>;
   kernel<<<dim3((unsigned)lg_run_grid(total, run)), 8 * TQ, 0, s>>>(q, k, v, out, dout, lse, delta, dq, sh.Hq, sh.Hkv, sh.scale, m,
-                                                    lg_make_items(total, run, nqt, sh.Hq, sh.Hkv), arrived, (int)ncnt);
+                                                    lg_make_items(total, run, nqt, sh.Hq, sh.Hkv, sh.D), arrived, (int)ncnt);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (ev) (void)hipEventRecord(ev[2], s);

@@ -313,7 +313,7 @@ hipError_t lg_launch_fwd_bf16(const void* q, const void* k, const void* v, void*
   const int total = (int)total_ll;
   const LgRuns runs = lg_runs(m, sh.B * sh.Hkv, nqt, sh.Hq / sh.Hkv, false);
   const float sl2 = sh.scale * 1.44269504088896340736f;
-  const LgItems items = lg_make_items(total, runs, nqt, sh.Hq, sh.Hkv);
+  const LgItems items = lg_make_items(total, runs, nqt, sh.Hq, sh.Hkv, sh.D);
   const dim3 grid((unsigned)lg_run_grid(runs, total));
 #define LG_FWD_LAUNCH(DD, FEW)                                                                             \
   fwd_bf16_kernel<DD, LgNoPack, FEW><<<grid, NT, 0, s>>>((const uint16_t*)q, (const uint16_t*)k,          \
@@ -347,7 +347,7 @@ hipError_t lg_launch_fwd_bf16_pack(const void* q, const void* k, const void* v, 
   const int total = (int)total_ll;
   const int run = lg_run_length(tmpl, total, sh.Hkv, 16 * (sh.Hq / sh.Hkv), true);
   const float sl2 = sh.scale * 1.44269504088896340736f;
-  const LgItems items = lg_make_items(total, run, nqt, sh.Hq, sh.Hkv);
+  const LgItems items = lg_make_items(total, run, nqt, sh.Hq, sh.Hkv, sh.D);
   const dim3 grid((unsigned)lg_run_grid(total, run));
 #define LG_FWD_LAUNCH(DD, FEW)                                                                           \
   fwd_bf16_kernel<DD, LgPack, FEW><<<grid, NT, 0, s>>>((const uint16_t*)q, (const uint16_t*)k,          \

@@ -210,7 +210,7 @@ hipError_t lg_launch_fwd_f32(const float* q, const float* k, const float* v, flo
   const long long tl = (long long)nqt * sh.Hq * sh.B;
   if (tl > 0x7fffffffLL - 8) return hipErrorInvalidValue;
   const int total = (int)tl, run = lg_run_length(m, total, sh.B * sh.Hkv, 256 / TQ * (sh.Hq / sh.Hkv), false);
-  const LgItems items = lg_make_items(total, run, nqt, sh.Hq, sh.Hkv);
+  const LgItems items = lg_make_items(total, run, nqt, sh.Hq, sh.Hkv, sh.D);
   const dim3 grid((unsigned)lg_run_grid(total, run));
 #define LG_FWD_LAUNCH(DD, ROWS) \
   fwd_f32_kernel<DD, ROWS><<<grid, 8 * ROWS, 0, s>>>(q, k, v, out, lse, sh.Hq, sh.Hkv, sh.scale, m, items)

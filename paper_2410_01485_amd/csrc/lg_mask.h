@@ -187,24 +187,31 @@ LG_HD int lg_item_of(int id, const LgRuns& w) {
 }
 // Within an XCD the hardware deals workgroups to its four shader engines strictly in turn, whatever they still have to do,
 // and an engine's to its CUs in turn.  Where the rows of a head differ in cost, one head after the other gives the same
-// engines the long rows every time (8 tiles of a causal head: 3072 : 2560 : 2048 : 1536 key tiles, 2.0 of 3 workgroups of a
-// CU in flight on average) and in launches of one or two rounds the same CUs.  So heads go four by four, their tiles side by
-// side, longest rows first, and with an even number of fours for each XCD every other four the other way round: what a CU
-// gets of two of them adds up evenly.  Forward, 32 heads: 1 x 4500 tokens of 128 196 us head by head, with two heads in four
-// the other way round 219, so 182; 1 x 6000 of 64 197 -> 163; 2 x 2048 of 64 72, 50, 48; 64 x 512 of 128 278, 249, 247; 8 x
-// 4096 1155, 1125, 1125.  Beyond 64 tiles the engines' shares differ by less than 5 %, and tiles side by side are no
-// neighbours any more.  Not for kernels that take items from a queue.
-enum { LG_BY_HEAD = 0, LG_BY_FOUR = 1, LG_BY_FOUR_TURNED = 2 };
-LG_HD int lg_order(int heads, int tiles) {
-  return heads % 32 != 0 || tiles > 64 ? LG_BY_HEAD : heads % 64 != 0 ? LG_BY_FOUR : LG_BY_FOUR_TURNED;
+// engines the long rows every time if its tiles are an even number (8 tiles of a causal head: 3072 : 2560 : 2048 : 1536 key
+// tiles, 2.0 of 3 workgroups of a CU in flight on average), and in launches of a few rounds the same CUs.
+//   Few rounds: heads four by four, their tiles side by side, longest rows first, and with an even number of fours for each
+// XCD every other four the other way round: what a CU gets of two of them adds up evenly.
+//   More rounds: two heads in four take their tiles in the other order, not the last two of an XCD's heads, so that its last
+// items are short ones; odd numbers of tiles mix by themselves (3 tiles turned: 215 -> 258 us).  Four heads' keys side by
+// side outgrow an XCD's L2 there.
+// Causal forward, us, head by head : two in four : four by four; 1 x 32 heads, 4500 tokens of 128 196 : 219 : 182, 6000 of 64
+// 197 : 202 : 163, 4 x 32, 2048 of 128 171 : 163 : 151, 4096 of 64 342 : 333 : 305; but 16 x 16, 4096 of 128 1101 : 1067 : 1091
+// (forward and backward 4530 : 4457 : 4588), 16 x 8, 8192 of 128, window 4096 1541 : 1530 : 1632; 64 x 32, 512 of 128 268 : 239 :
+// 238.  Beyond 64 tiles the engines' shares differ by less than 5 % and a turned head would end on a long row.  Not for
+// kernels that take items from a queue.
+enum { LG_BY_HEAD = 0, LG_TURNED = 1, LG_BY_FOUR = 2, LG_BY_FOUR_TURNED = 3 };
+// heads: of keys and values; group: items of a (head, tile).  Places: 768 (head dim 128) or 1024 workgroups in flight.
+LG_HD int lg_order(int heads, int tiles, int group, int D) {
+  if (heads % 32 != 0 || tiles > 64) return LG_BY_HEAD;
+  if ((long long)heads * tiles * group <= (D == 64 ? 4096 : 3072)) return heads % 64 != 0 ? LG_BY_FOUR : LG_BY_FOUR_TURNED;
+  return tiles % 2 == 0 ? LG_TURNED : LG_BY_HEAD;
 }
 // Item `at` of a launch with `tiles` items a head: divide lg_order_at by `tiles`, then lg_in_order makes head and tile of
 // quotient and remainder.
-LG_HD int lg_order_at(int order, int at) { return order == LG_BY_HEAD ? at : at >> 2; }
+LG_HD int lg_order_at(int order, int at) { return order >= LG_BY_FOUR ? at >> 2 : at; }
 LG_HD void lg_in_order(int order, int at, int tiles, int* head, int* x) {
-  if (order == LG_BY_HEAD) return;
-  if (order == LG_BY_FOUR_TURNED && (*head & 1) == 0) *x = tiles - 1 - *x;
-  *head = 4 * *head + (at & 3);
+  if ((order == LG_TURNED && (*head & 2) == 0) || (order == LG_BY_FOUR_TURNED && (*head & 1) == 0)) *x = tiles - 1 - *x;
+  if (order >= LG_BY_FOUR) *head = 4 * *head + (at & 3);
 }
 
 // The items of kernels that take query tiles: (b, kv head) slowest (but see lg_order), then the query tile, longest rows
@@ -215,12 +222,12 @@ struct LgItems {
   bool mix;                       // the heads' runs take turns (LgRuns)
   LgDiv run, G, nqt, Hkv, heads;  // nqt: query tiles of a head (all packed sequences together)
 };
-inline LgItems lg_make_items(int total, int run, int nqt, int Hq, int Hkv) {
+inline LgItems lg_make_items(int total, int run, int nqt, int Hq, int Hkv, int D) {
   const int heads = total / (nqt * (Hq / Hkv));
-  return LgItems{total, lg_order(heads, nqt), false, lg_make_div(run), lg_make_div(Hq / Hkv), lg_make_div(nqt), lg_make_div(Hkv), lg_make_div(heads)};
+  return LgItems{total, lg_order(heads, nqt, Hq / Hkv, D), false, lg_make_div(run), lg_make_div(Hq / Hkv), lg_make_div(nqt), lg_make_div(Hkv), lg_make_div(heads)};
 }
-inline LgItems lg_make_items(int total, const LgRuns& runs, int nqt, int Hq, int Hkv) {
-  LgItems w = lg_make_items(total, runs.run, nqt, Hq, Hkv);
+inline LgItems lg_make_items(int total, const LgRuns& runs, int nqt, int Hq, int Hkv, int D) {
+  LgItems w = lg_make_items(total, runs.run, nqt, Hq, Hkv, D);
   w.mix = runs.heads > 0;
   return w;
 }
