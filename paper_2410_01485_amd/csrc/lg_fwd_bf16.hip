@@ -108,9 +108,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D,
   const int qw0 = min(q0 + wave_s * 32, N - 1), qw1 = min(q0 + wave_s * 32 + 31, N - 1);  // this wave's rows
 
   // Rows that grow along the sequence, hardly more of them than places: the longest decide when the launch ends, so they go
-  // before their neighbours on the CU, the more the longer (full causal, heads of 64: 2 of 113471 tokens 4.15 -> 3.94 ms, 4 of
-  // 65536 3.02 -> 2.88; 2 of 128, 50000 tokens 1.50 -> 1.37; with 2.7 times as many items as places it costs 5 %).
-  if (!PACK && !FEW && items.total <= 2 * 256 * Tune::WAVES && 2 * (long long)m.wb * m.b >= N) {
+  // before their neighbours on the CU, the more the longer.  Full causal, without and with, us, and the rounds: 24 heads of 64,
+  // 6000 tokens 169, 146 (1.1); 40, 3000 88, 74 (0.9); 24 of 128, 5400 tokens 204, 193 (1.3); 100 x 4, 300 30.2, 34.5 (1.6); four
+  // heads side by side (lg_order), which even out by themselves: 2 x 32 of 64, 1300 tokens 29.4, 28.3 (0.7); of 128, 2048
+  // tokens 76.8, 79.9 (1.3); 4 x 32 of 64, 2048 105, 115 (2).
+  if (!PACK && !FEW && 5 * items.total <= (items.order >= LG_BY_FOUR ? 6 : 7) * 256 * Tune::WAVES && 2 * (long long)m.wb * m.b >= N) {
     const int third = (int)(3LL * q0 / N);
     if (third == 2) __builtin_amdgcn_s_setprio(2);
     else if (third == 1) __builtin_amdgcn_s_setprio(1);
