@@ -93,24 +93,43 @@ def test_heads_four_by_four(B, Hq, N, D, window):
                      allow=al if name == "dq" else None)
 
 
-@pytest.mark.parametrize("N,sink,window,block,stride", [(3200, 0, 2600, 1, 0), (3140, 64, 2624, 64, 0), (3100, 64, 2304, 64, 8)])
-def test_dq_in_64_row_form(N, sink, window, block, stride):
-    """32 heads, 32 or more key tiles per query tile and a ragged length: dq with 64 rows per wave.  Sampled rows and keys of
-    single heads: the first rows, the sink keys, where the window starts to slide, the last rows."""
-    Hq, Hkv, D = 32, 8, 128
+@pytest.mark.parametrize("Hq,N,sink,window,block,stride", [
+    (32, 3200, 0, 2600, 1, 0), (32, 3140, 64, 2624, 64, 0), (32, 3100, 64, 2304, 64, 8),
+    (44, 2049, 0, 2048, 1, 0), (32, 9000, 64, 1024, 64, 5)])  # a last query tile of one row; 29 strided columns
+def test_dq_in_64_row_form(Hq, N, sink, window, block, stride):
+    """32 or more key tiles per query tile, 384 or more tiles of 256 rows and a ragged length: dq with 64 rows per wave.
+    Sampled rows and keys of single heads: the first rows, the sink keys, where the window starts to slide, the last rows."""
+    Hkv, D = Hq // 4, 128
+    assert Hq * -(-N // 256) >= 384
     q, k, v, g = lg_synth.prefill_inputs(1, Hq, Hkv, N, D, 9, torch.bfloat16, with_dout=True, device=DEV)
     dq, dk, dv = run_fwd_bwd(q, k, v, g, sink, window, block, stride)
     tol, rel = TOL_OUT[torch.bfloat16], TOL_REL[torch.bfloat16]
-    for h, r0, r1 in ((0, 0, 40), (13, 2590, 2640), (31, N - 50, N)):
+    mid = min(2590, N - 101)
+    for h, r0, r1 in ((0, 0, 40), (13, mid, mid + 50), (Hq - 1, N - 50, N)):
         a = [f32np(x) for x in (q[:, h:h + 1], k[:, h // 4:h // 4 + 1], v[:, h // 4:h // 4 + 1], g[:, h:h + 1])]
         w = O.bwd(*a, sink, window, block, stride, rows=(r0, r1), keys=(0, 1))
         al = dq_delta_allowance(a[0], a[1], a[3], w["out"], sink, window, block, stride, rows=(r0, r1))
         assert_close(f32np(dq[0, h, r0:r1]), w["dq"][0, 0, r0:r1], tol, rel, "dq head %d" % h, allow=al[0, 0, r0:r1])
-    for hk, k0, k1 in ((0, 0, 30), (5, 700, 730), (7, N - 30, N)):  # (a kv head's gradients: four query heads)
+    for hk, k0, k1 in ((0, 0, 30), (5, 700, 730), (Hkv - 1, N - 30, N)):  # (a kv head's gradients: four query heads)
         a = [f32np(x) for x in (q[:, 4 * hk:4 * hk + 4], k[:, hk:hk + 1], v[:, hk:hk + 1], g[:, 4 * hk:4 * hk + 4])]
         w = O.bwd(*a, sink, window, block, stride, rows=(0, 1), keys=(k0, k1))
         assert_close(f32np(dk[0, hk, k0:k1]), w["dk"][0, 0, k0:k1], tol, rel, "dk head %d" % hk)
         assert_close(f32np(dv[0, hk, k0:k1]), w["dv"][0, 0, k0:k1], tol, rel, "dv head %d" % hk)
+
+
+@pytest.mark.parametrize("B,Hq,N,window", [(3, 32, 3100, 2600), (2, 48, 2100, 2100)])
+def test_work_queues_over_a_batch(B, Hq, N, window):
+    """dq with 64 rows per wave and dk/dv with 64 keys per wave, whose work items of all sequences one queue hands out: the
+    bits of each sequence by itself."""
+    D = 128
+    gen = torch.Generator(device=DEV).manual_seed(16)
+    q, k, v, g = (torch.randn(B, Hq, N, D, generator=gen, device=DEV, dtype=torch.bfloat16) for _ in range(4))
+    assert Hq * -(-N // 256) >= 384 and (window + 256) // 64 >= 32
+    got = run_fwd_bwd(q, k, v, g, 0, window)
+    for b in range(B):
+        one = [x[b:b + 1].contiguous() for x in (q, k, v, g)]
+        for name, x, y in zip(("dq", "dk", "dv"), got, run_fwd_bwd(*one, 0, window)):
+            assert torch.equal(x[b:b + 1], y), (name, b)
 
 
 @pytest.mark.parametrize("D", [64, 128])
@@ -237,7 +256,8 @@ def test_strided_columns_long_context(B, Hq, Hkv, N, D, sink, window, block, str
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,N,D,sink,window,block,stride", [
-    # windows of 16 or more tiles at D = 128 select the kernels with 64 query rows / 64 keys per wave:
+    # windows of 16 or more tiles at D = 128 select dk/dv with 64 keys per wave (dq stays with 32 rows per wave, with too few
+    # tiles of rows for the other form: test_dq_in_64_row_form):
     # token-granular with a ragged end (sink tile handled by the main instance); GQA with batch
     # (column instance + partial sums folded into the main instance); block-granular; block-strided
     # (both instances in the 64-keys form); no sink and a window longer than most rows

@@ -169,28 +169,35 @@ def test_many_short_sequences_in_shared_launches(D, sink, window, block, stride)
 
 
 def test_long_sequences_take_the_resident_kernels():
-    """Head dim 128, window 4096: the sequences of 5000 and 9000 tokens run the 64-rows-per-wave backward
-    kernels (one resident workgroup per CU, work queue in the shared workspace) side by side, the
-    700-token one the 32-rows-per-wave ones.  No GQA, no stride: everything is
+    """Head dim 128, window 4096: dk/dv of the sequences of 5000 and 9000 tokens run the 64-keys-per-wave kernel (one resident
+    workgroup per CU, work queue in the shared workspace) side by side, the 700-token one the 32-keys-per-wave one; dq has
+    too few tiles of rows for its resident form (test_sequences_of_both_dq_forms_side_by_side).  No GQA, no stride: everything is
     bit-reproducible, so the whole pack must equal the fixed-length calls bit for bit; forward rows of the
     long sequences are sampled against the oracle, the short one is compared in full."""
     check_pack([5000, 700, 9000], 2, 2, 128, 64, 4096, 1, 0, torch.bfloat16, 403, oracle_rows=2000)
 
 
-def test_sequences_of_both_dq_forms_side_by_side():
-    """32 heads, window 2600: the sequences of 3200 and 3100 tokens take dq with 64 rows per wave, those of 2700 (too few
-    rows) and 300 with 32; out, lse, dq, dk, dv equal the fixed-length calls bit for bit."""
-    lens, H, D, sink, window = [2700, 3200, 300, 3100], 32, 128, 64, 2600
+@pytest.mark.parametrize("lens,sink,window,block,stride", [
+    ([2700, 3200, 300, 3100], 64, 2600, 1, 0), ([2600, 3330, 100, 3073], 64, 2624, 64, 0), ([3200, 4200, 300, 4100], 64, 1536, 64, 8)])
+def test_sequences_of_both_dq_forms_side_by_side(lens, sink, window, block, stride):
+    """32 heads: the second and the last sequence take dq with 64 rows per wave, the others (too few rows; with strided columns
+    the first one too few keys a row) with 32; out, lse, dq, dk, dv equal the fixed-length calls bit for bit (with strided
+    columns, whose keys' sums are added with atomics, dk and dv but for the order of those)."""
+    H, D = 32, 128
     packed, seqs, cu = pack(lens, H, H, D, torch.bfloat16, 411)
-    got = run_varlen(packed, cu, sink, window, 1, 0)
+    got = run_varlen(packed, cu, sink, window, block, stride)
     for s in range(len(lens)):
-        for name, x, y in zip(("out", "lse", "dq", "dk", "dv"), got, run_fixed(seqs[s], sink, window, 1, 0)):
-            assert torch.equal(x[:, cu[s]:cu[s + 1]], y), (name, s)
+        for name, x, y in zip(("out", "lse", "dq", "dk", "dv"), got, run_fixed(seqs[s], sink, window, block, stride)):
+            x = x[:, cu[s]:cu[s + 1]]
+            if stride > 0 and name in ("dk", "dv"):
+                assert_same_sums(x, y, "%s of sequence %d" % (name, s))
+            else:
+                assert torch.equal(x, y), (name, s)
 
 
 @pytest.mark.parametrize("D,lens,Hq,Hkv,sink,window,block,stride", [
-    (128, [300, 1500, 6000, 1, 0, 257, 5000, 769], 4, 2, 64, 1024, 1, 0),   # both forms of dq and dk/dv, lone columns
-    (128, [2500, 64, 4000, 700], 4, 1, 64, 256, 64, 8),                     # dq forms differ by the strided columns
+    (128, [300, 1500, 6000, 1, 0, 257, 5000, 769], 4, 2, 64, 1024, 1, 0),   # both forms of dk/dv, lone columns
+    (128, [2500, 64, 4000, 700], 4, 1, 64, 256, 64, 8),                     # strided columns, groups of four heads
     (64, [1800, 255, 0, 3000], 2, 2, 64, 128, 64, 2),
     (128, [512, 200, 512, 0, 300, 512, 1000, 500], 2, 2, 0, 512, 1, 0),     # even numbers of tiles: turned and not
     (128, [5 + (37 * s) % 90 for s in range(140)], 2, 2, 4, 16, 1, 0),      # more sequences than one set of launches takes
