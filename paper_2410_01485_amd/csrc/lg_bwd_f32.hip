@@ -10,8 +10,7 @@
 // the forward: 4 or 2 groups of 16 rows x 2 halves of a tile's keys, summed through LDS at the end.  dk/dv uses 4 waves per 32 keys: 2 groups of 16 keys x 2 halves of a step's query rows (64, at head dim
 // 128 32), two workgroups per CU: as 8 waves per 64 keys one workgroup fitted a CU (167 registers, 66 KB; at head dim 128
 // 256 with spills), so that 280 work items were two rounds on 256 CUs, and every window had to be cut in two.  16/8 heads
-// of 64, 1024 tokens, window 128: dk/dv 44 -> 29 us (of that 3 from the masks, LgF32Row); 4 heads of 128, 4096 tokens,
-// window 512: 168 -> 120.  Bound: the float32 matrix rate, 4096 cycles of a step's 6600; the rest is what one wave per
+// of 64, 1024 tokens, window 128: dk/dv 44 -> 29 us; 4 heads of 128, 4096 tokens, window 512: 168 -> 120.  Bound: the float32 matrix rate, 4096 cycles of a step's 6600; the rest is what one wave per
 // SIMD cannot hide (masks, the next copies' issue, the barriers).
 //
 // The dk/dv work of a key tile is cut into parts: its window part (nsp equal runs of (head, query tile) steps,
@@ -243,15 +242,19 @@ F32Parts f32_parts(const LgShape& sh, const LgMask& m) {
   int w = (m.wb * m.b + TQ - 1) / TQ + 1;  // query tiles the window of a key tile reaches
   if (w > p.nqt) w = p.nqt;
   const long long steps = (long long)w * G;
-  // In steps (2 us): the longest part, or all of them over the CUs (two workgroups on one share its matrix pipes, but one's
-  // start and end run beside the other's steps).  Starting costs two steps, partial sums and their addition three more.
+  // In steps (2 us): the longest part and the one beside it, or all of them over the CUs (two workgroups on one share its
+  // matrix pipes, but one's start and end run beside the other's steps).  Starting costs two steps, partial sums and their
+  // addition three more.  Beside the longest: with two per CU at once the one that is dealt out 256 later (causal, 8 heads of
+  // 64, 2048 tokens, dk/dv: in one part 122 us, in two 106; 16/8 of 128 457, 373; 12 of 64, 1024 61, 53.5).
   const double total = base * G * (w - 0.5 * w * w / p.nqt);
   double least = 0;
   p.nsp = 1;
   for (int n = 1; n <= steps / 3 + 1 && n <= 64; ++n) {
     const double one = (double)((steps + n - 1) / n) + (n > 1 ? 5 : 2);
     const double all = (total + base * n * (n > 1 ? 3 : 1.5)) / 256;
-    const double t = one > all ? one : all;
+    const double later = p.nqt * (1 - 256.0 / (base * n));  // query tiles from that one's first key on
+    const double beside = base * n > 256 && base * n <= 512 ? (later < w ? later : w) * G / n : 0;
+    const double t = one + beside > all ? one + beside : all;
     if (n == 1 || t < least) {
       least = t;
       p.nsp = n;
@@ -338,7 +341,8 @@ __global__ __launch_bounds__(BNT, 2) void dkdv_f32_kernel(
   const bool owner = narrow ? wave == 0 : wave < 2;  // holds the sum over the row blocks at the end
   const int j = k0 + 16 * kg + n, jk = min(j, N - 1);
   // The rows that see the lane's key are one run (as in lg_row_bits): from j on, `seen` of them.  Of the wave's keys: the
-  // first and the last one, the ends of the run that ends first and of the one that ends last.
+  // first and the last one, the ends of the run that ends first and of the one that ends last.  (With lg_tile_kind and
+  // lg_live for every block and element, class and mask were 1000 and 1500 of a step's 8900 cycles: 3 of the 44 us above.)
   const int kw0 = k0 + 16 * kg, kw1 = kw0 + 15, kbj = lg_div_b(m, jk);
   const bool to_end = jk < m.sink || (m.stride > 0 && lg_strided(m, kbj)) || kbj + m.wb >= lg_div_b(m, N - 1) + 1;
   const int end_j = j >= N ? 0 : to_end ? N : (kbj + m.wb) * m.b;

@@ -283,6 +283,9 @@ def test_long_windows_wide_kernels(B, Hq, Hkv, N, D, sink, window, block, stride
     (1, 1, 1, 1030, 128, 0, 1030, 1, 0),
     (1, 2, 1, 900, 64, 48, 96, 48, 3),
     (1, 2, 2, 192, 64, 8, 65, 1, 0),
+    # 288 key tiles of rows that grow, cut in two
+    (1, 9, 9, 1000, 64, 0, 1000, 1, 0),
+    (1, 10, 10, 1000, 128, 0, 1000, 1, 0),
 ])
 def test_float32_parts(B, Hq, Hkv, N, D, sink, window, block, stride):
     check_bwd(B, Hq, Hkv, N, D, sink, window, block, stride, dtype=torch.float32, seed=83)

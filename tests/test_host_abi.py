@@ -147,3 +147,13 @@ def test_decode_argument_errors():
 def test_python_binding_raises_lg_error():
     with pytest.raises(lg.LgError):
         lg.lg_debug_tile_map(0, 0, 1, 1, 0, lg.LG_BF16, 0)
+
+
+@pytest.mark.parametrize("Hq,Hkv,N,D", [(8, 8, 2048, 64), (12, 12, 1024, 64), (16, 8, 2048, 64), (8, 8, 2048, 128), (16, 8, 2048, 128)])
+def test_float32_window_parts_of_growing_rows_are_cut(Hq, Hkv, N, D):
+    """257 to 512 key tiles of causal rows: as one part each the longest shared a CU with one of half its length, and dk/dv took
+    up to 1.25 times as long.  The workspace has room for partial sums, dk and dv of every key at least twice; rows of equal
+    length stay whole."""
+    rows = -(-Hq * N * 4 // 256) * 256
+    assert lg.bwd_workspace_bytes(1, Hq, Hkv, N, D, 0, N, 1, 0, lg.LG_F32) >= rows + 4 * Hkv * N * D * 4
+    assert lg.bwd_workspace_bytes(1, Hq, Hkv, N, D, 0, 64, 1, 0, lg.LG_F32) == rows
