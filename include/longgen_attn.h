@@ -341,8 +341,8 @@ int lg_debug_decode_segments(int N, int sink, int window, int block, int stride,
  * Writes, in CSR form, the list of live kernel tiles the device code walks:
  *   transposed 0, 2: rows are query tiles, columns key tiles (forward, dq);
  *   transposed 1, 3: rows are key tiles, columns query tiles (dk/dv).
- * tq/tk receive the kernel tile sizes used for `dtype`.  float32: 64 x 64 (of a key tile a dk/dv workgroup takes one half,
- * at head dim 128 of a query tile a step as well).  bf16:
+ * tq/tk receive the kernel tile sizes used for `dtype`.  float32: 64 x 64 (the kernels take such tiles
+ * whole or, where workgroups are few and in dk/dv, by halves: 32 query rows, 32 keys, 32 of both).  bf16:
  *   0: 256 x 64, the dq kernel with 64 rows per wave (head dim 128, long windows, enough heads and rows);
  *   2: 128 x 64, the forward and the other dq kernel;
  *   1: 64 x 256, the dk/dv kernels at head dim 128;      3: 64 x 128, at head dim 64.

@@ -36,7 +36,7 @@
 // 461 -> 390 us; 512 590 -> 570, 830 -> 782; 2048 (64 rows per wave) 1545 -> 1493, 1910 -> 1875; 64 x 512 tokens 465 -> 380,
 // 630 -> 495 (some of that from the order of the tiles, lg_order).
 //
-// For head dim 128 and long windows (dq 32 or more tiles, dk/dv 16) both kernels have a second form with 64 rows
+// For head dim 128 and long windows (dq 32 or more tiles, and 384 or more of 256 rows; dk/dv 16) both kernels have a second form with 64 rows
 // (keys) per wave, one wave per SIMD and the accumulators in AGPRs (further down): every operand
 // read from LDS then feeds two matrix instructions.
 #include <algorithm>
@@ -188,9 +188,8 @@ __device__ __forceinline__ void lg_load_pieces(const uint16_t* __restrict__ rows
     o[x] = *reinterpret_cast<const uint4*>(rows + (size_t)min(x * (256 / T::CPR) + tid / T::CPR, last) * D + tid % T::CPR * 8);
 }
 
-// Both dq kernels also form Delta_i = <dout_i, out_i> of their rows (a lane and its partner in
-// the other half of the wave hold the whole row of dout anyway) and leave -Delta and -lse / scale
-// in the workspace for the dk/dv kernels, which run after them on the same stream.
+// Both dq kernels also form Delta_i = <dout_i, out_i> of their rows (lg_delta_rows, from the dout that they bring to LDS
+// anyway) and leave -Delta and -lse / scale in the workspace for the dk/dv kernels, which run after them on the same stream.
 // ------------------------------------------------------------------------- dq
 // Waves per SIMD and operands requested ahead, as the registers of so many waves allow (256 for D = 128, 168 for D = 64).
 template <int D>
@@ -1901,8 +1900,12 @@ Columns columns_of(const LgMask& m, int D) {
 // dq: by the key tiles of an average query tile: its window, plus the strided columns below it.  In short runs the 32-rows
 // form is the faster one up to 40 tiles (64/8 heads, 16001 tokens, window 2048 and strided columns 1415 : 1471 us), in long
 // ones, at the power limit, what it draws more slows the kernels beside it (that whole training pass 4575 : 4515 us; 32
-// heads, 32768 tokens, window 2048 4625 : 4619, 1100 2974 : 3017).  And only with enough work items of 256 rows (4 heads,
-// 6000 tokens, causal 150 : 192).
+// heads, 32768 tokens, window 2048 4625 : 4619, 1100 2974 : 3017).  And only with enough work items of 256 rows, which at one
+// per CU end one after the other (dq, causal, 64 rows per wave : 32; 4 heads, 6000 tokens 197 : 154, 24000 918 : 794; 12 heads,
+// 7800 338 : 275; 16, 6000 (384 items) 225 : 228; 8/2, 12000 425 : 454).  Counted for one sequence, so that its dq has the same
+// bits in every batch and pack; a batch has more work items, and what that costs it is: 2 x 4 heads, 16384 tokens 636 : 734 (the
+// backward 1461 : 1561), 3 x 8/2, 10200 848 : 907, 8 x 4, 16384 2660 : 2700 (5975 : 6035), but 3 x 4, 20400 1735 : 1621, 4 x 16, 4096
+// 410 : 369.
 bool dq_wide(const LgMask& m, int D, int Hq) {
   const int col_tiles = m.stride > 0 ? (m.N / 2) / (m.b * m.stride) * ((m.b + LG_BF16_TK - 1) / LG_BF16_TK) : 0;
   return D == 128 && (m.wb * m.b + LG_BF16_TQ) / LG_BF16_TK + col_tiles >= 32 &&

@@ -100,11 +100,12 @@ struct LgDecWork {
   int* parts;         // [rows], paged: parts of the row
 };
 constexpr int LG_DEC_SPLITS_MAX = 64;
-// Workgroups with keys that a paged step aims at: a little below three per CU, what the matrix-core kernel's registers
-// admit, or (bf16) one per CU when all rows together have so few keys that a workgroup's start and the final sum weigh
-// more than its reads.  Rounding gives up to a tenth more than aimed at: with 768 the last of 900 workgroups ran after the
-// others (64 sequences of 2000 .. 60000 tokens, 8 kv heads: 186 us, with 720 164; 48 of 20 .. 32768: 68.7 and 68.2; with
-// 640 73.7, whole rounds missing on part of the CUs).
+// Workgroups with keys that a paged step aims at: DEC_FULL less a quarter of its rows (b, kv head), a little below three per
+// CU, what the matrix-core kernel's registers admit, or (bf16) one per CU when all rows together have so few keys that a
+// workgroup's start and the final sum weigh more than its reads.  Rounding gives at most one part more per row.  With 768
+// the last of 900 workgroups ran after the others: 64 sequences of 2000 .. 60000 tokens, 8 kv heads 184 us, with 720 165
+// (float32 380, 331); 48 of 20 .. 32768 60 and 60 (136, 136), as are other batches; with 640 the latter lost 7 %, whole
+// rounds missing on part of the CUs.
 constexpr int DEC_FULL = 720, DEC_FEW = 256;
 constexpr float DEC_MANY_KEYS = 300000.f;
 

@@ -52,8 +52,8 @@ struct LgF32Reader {
   }
 };
 
-// The live keys of a lane's query row, as the forward and dq kernels ask for them per element of PARTIAL blocks.  With
-// lg_tile_kind and lg_live for every block and element, class and mask were 1000 and 1500 of a dk/dv step's 8900 cycles.
+// The live keys of a lane's query row, as the forward and dq kernels ask for them per element of PARTIAL blocks: what does
+// not depend on the key is worked out once.
 struct LgF32Row {
   int i, w;  // the row, the first key of its window
   __device__ __forceinline__ void init(const LgMask& m, int row) {

@@ -16,18 +16,15 @@
 // tile, 48 KB / 24 KB; K of tile t + 2 and V of tile t + 1 are requested as soon as tile t has left their place).
 // One workgroup of 8 waves in step (two per SIMD) with a 128 KB ring needed 30 % more cycles; 6 or 12 waves per
 // workgroup are slower as well, 6 because they do not spread evenly over four SIMDs.  Smaller workgroups also waste
-// less on short sequences.  Rows of few tiles are bound by what a workgroup does besides tiles, so Q and O go through LDS
-// in pieces of 1 KB (a lane's own row, 16 bytes at a time, is 32 rows per instruction: address and cache-line work of 2000
-// cycles each way) and items are found without divisions: 32 heads of 128, window 64 at 32768 tokens 216 -> 198 us (5.4
-// TB/s), 256 291 -> 265, 1024 633 -> 609; 64 x 512 tokens 300 -> 269 us; 2 x 16 heads of 64, 1003 tokens 17.2 -> 16.5.
-// (Asking for the next item's Q lines while a tile is computed, so that they wait in L2, was slower: 198 -> 207 us.)
+// less on short sequences.  32 heads of 128, 131072 tokens, window 4096: 9.1 -> 8.45 ms (1040 TFLOP/s, the clock settles at
+// 1.8 GHz instead of 2.2 under the power limit); 8 x 1024 tokens 144 -> 116 us.
+//
+// Rows of few tiles are bound by what a workgroup does besides tiles, so Q and O go through LDS in pieces of 1 KB (a lane's
+// own row, 16 bytes at a time, is 32 rows per instruction: address and cache-line work of 2000 cycles each way) and items
+// are found without divisions: 32 heads of 128, 32768 tokens, window 64 216 -> 198 us (5.4 TB/s), 1024 633 -> 609; 64 x 512
+// tokens 300 -> 269 us.  (Asking for the next item's Q lines while a tile is computed was slower: 198 -> 207 us.)
 // What whole tiles cost depends on where the tile loop's code falls (5 % for 24055 tokens of 2 heads of 64, from a change
-// that touched only the masks of PARTIAL tiles): this file is compiled with loops at 64-byte boundaries.  With masks of two
-// instructions per score instead of four 163 x 200 tokens 218 -> 214 us, 109 x 300 243 -> 240, 2 x 16 heads of 64, 1003
-// tokens 15.6 -> 15.2, 2 x 4 heads of 128, 1603 tokens 36.1 -> 35.4; windows of 1024 tokens and more as before.
-// 32 heads of 128, 131072 tokens, window 4096: 9.1 -> 8.45 ms (1040 TFLOP/s, the clock now
-// settles at 1.8 GHz instead of 2.2 under the power limit); 8 x 1024 tokens: 144 -> 116 us; 2 x 16 heads of 64, 1003
-// tokens: 26 -> 18 us.
+// that touched only the masks of PARTIAL tiles): this file is compiled with loops at 64-byte boundaries.
 #include "lg_kernels.h"
 #include "lg_mfma.h"
 #include "lg_swz.h"
@@ -38,7 +35,8 @@ constexpr int TK = LG_BF16_TK;    // 64 keys per step
 constexpr int TQ = LG_BF16_TQ32;  // 128 query rows per workgroup
 constexpr int NT = TQ * 2;        // threads: one wave per 32 rows
 // Waves per SIMD, and LDS operands of the two products requested ahead of the matrix instruction that uses them, as the
-// registers of so many waves allow (168 for D = 128, 128 for D = 64)
+// registers of so many waves allow (168 for D = 128, of which one value too many lives in memory and is read back in the
+// masks of PARTIAL tiles only; 128 for D = 64)
 template <int D, bool FEW>
 struct LgFwdTune {
     static constexpr int WAVES = FEW ? 2 : D == 128 ? 3 : 4, AHEAD = FEW ? 4 : D == 128 ? 2 : 3, AHEAD_PV = 4;

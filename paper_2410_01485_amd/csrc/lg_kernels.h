@@ -1,6 +1,6 @@
 // lg_kernels.h — internal interface between the C ABI (lg_api.hip) and the kernel
-// translation units.  Tile sizes live here because the host-side tile map
-// (lg_debug_tile_map) must enumerate exactly the tiles the kernels walk.
+// translation units.  Tile sizes live here because the host-side tile map (lg_debug_tile_map) lists tiles of these sizes: bf16
+// exactly those that the kernels walk, float32 those of 64 x 64 that the kernels' smaller ones lie in.
 #ifndef LG_KERNELS_H_
 #define LG_KERNELS_H_
 
@@ -13,9 +13,9 @@
 // Kernel tile sizes (query rows x keys per step).  Independent of the pattern's
 // `block`: they never change results, only which tiles count as PARTIAL.
 enum {
-  LG_F32_TQ = 64, LG_F32_TK = 64,        // float32 kernels, forward / dq order (few workgroups: half the rows each)
-  LG_F32_BTQ = 64, LG_F32_BTK = 64,      // float32 dk/dv (key-tile major), as listed by the host view:
-  LG_F32_KEYS = 32,                      // a workgroup takes half of such a tile's keys (at head dim 128 half its rows a step)
+  LG_F32_TQ = 64, LG_F32_TK = 64,        // float32 forward / dq (half the rows where workgroups are few: lg_f32_rows)
+  LG_F32_BTQ = 64, LG_F32_BTK = 64,      // float32 dk/dv (key-tile major), as listed by the host view
+  LG_F32_KEYS = 32,                      // keys of a float32 dk/dv workgroup (a step: 64 rows, at head dim 128 32)
   LG_BF16_TQ = 256, LG_BF16_TK = 64,     // bf16 dq kernel with 64 rows per wave
   LG_BF16_TQ32 = 128,                    // bf16 forward, dq kernel with 32 rows per wave (64 keys per step as well)
   LG_BF16_BTQ = 64, LG_BF16_BTK = 256,   // bf16 dk/dv kernels (key-tile major), head dim 128

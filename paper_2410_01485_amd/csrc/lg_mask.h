@@ -106,8 +106,9 @@ LG_HD bool lg_live(const LgMask& m, int i, int j) {
 // Division by a value that the host knows: a multiplication and a shift.  A workgroup finds its item by half a dozen
 // divisions, one after the other, before it can ask for anything, and the hardware has no integer division (forward: 1300
 // cycles to the item, 1700 at head dim 64; without 16.6 -> 16.5 us for one workgroup per CU, 1-2 % on rows of few tiles;
-// the bf16 backward kernels gained nothing and divide).  Exact for 0 <= n < 2^31, 1 <= d < 2^31 (the round-up method: the
-// multiplier is 2^(32+s) / d rounded up minus 2^32, s = ceil(log2 d); with n below 2^31 the sum does not overflow).
+// the bf16 backward kernels gained nothing and divide).  Exact for 0 <= n < 2^31, 1 <= d < 2^31 (the round-up method of
+// Granlund and Montgomery, "Division by Invariant Integers using Multiplication", 1994: the multiplier is 2^(32+s) / d
+// rounded up minus 2^32, s = ceil(log2 d); with n below 2^31 the sum does not overflow).
 struct LgDiv {
   uint32_t d, mul;
   int shift;
