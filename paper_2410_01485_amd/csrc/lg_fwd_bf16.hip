@@ -35,8 +35,7 @@ constexpr int TK = LG_BF16_TK;    // 64 keys per step
 constexpr int TQ = LG_BF16_TQ32;  // 128 query rows per workgroup
 constexpr int NT = TQ * 2;        // threads: one wave per 32 rows
 // Waves per SIMD, and LDS operands of the two products requested ahead of the matrix instruction that uses them, as the
-// registers of so many waves allow (168 for D = 128, of which one value too many lives in memory and is read back in the
-// masks of PARTIAL tiles only; 128 for D = 64)
+// registers of so many waves allow (168 for D = 128, 128 for D = 64)
 template <int D, bool FEW>
 struct LgFwdTune {
     static constexpr int WAVES = FEW ? 2 : D == 128 ? 3 : 4, AHEAD = FEW ? 4 : D == 128 ? 2 : 3, AHEAD_PV = 4;
@@ -101,7 +100,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D,
   const size_t qbase = ((size_t)(b * Hq + hq) * m.ld + seq_row0) * D;
   const uint16_t* kh = k + ((size_t)(b * Hkv + hk) * m.ld + seq_row0) * D;
   const uint16_t* vh = v + ((size_t)(b * Hkv + hk) * m.ld + seq_row0) * D;
-  const int i = q0 + wave * 32 + n;  // this lane's query row
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   const int qw0 = min(q0 + wave_s * 32, N - 1), qw1 = min(q0 + wave_s * 32 + 31, N - 1);  // this wave's rows
 
@@ -220,7 +218,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D,
     // ---- online softmax (log2 domain) ----
     if (!full) {
       asm volatile("; masked" ::: "memory");  // (a real branch: nothing of it in whole tiles)
-      const uint32_t bits = lg_key_bits(m, min(i, N - 1), k0, g);  // a few runs of registers, in closed form
+      int ln;  // the lane, asked for here: kept from the start it was a register too many at D = 128
+      asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
+      const int row = min(q0 + wave_s * 32 + (ln & 31), N - 1);
+      const uint32_t bits = lg_key_bits(m, row, k0, ln >> 5);  // a few runs of registers, in closed form
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -299,6 +300,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D,
     lg_rows_put<D>(rows, lane, db, o, inv);
   }
   lg_rows_write<D>(rows, lane, out + qbase + (size_t)(q0 + wave_s * 32) * D, N - (q0 + wave_s * 32));
+  const int i = q0 + wave * 32 + n;  // this lane's query row
   if (lse != nullptr && g == 0 && i < N)
     lse[(size_t)(b * Hq + hq) * m.ld + seq_row0 + i] = (mref * scale_log2e + log2f(l)) * 0.69314718055994530942f;
 }

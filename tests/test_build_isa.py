@@ -187,3 +187,17 @@ def test_matrix_results_are_not_touched_too_early(wide_kernels):
                     w = written.pop(r)
                     assert n_mfma - w[0] >= MFMA_GAP or n_nop - w[1] >= NOP_STATES, \
                         f"{name}: {line} touches {r} {n_mfma - w[0]} matrix instructions after it was written"
+
+
+def test_forward_spills_nothing(tmp_path):
+    """The bf16 forward at head dim 128 uses every register that three workgroups per CU leave: one value too many went
+    through memory in every workgroup (34 MB of writes at 32 heads, 131072 tokens)."""
+    hipcc = _hipcc()
+    if hipcc is None:
+        pytest.skip("hipcc not available")
+    out = tmp_path / "lg_fwd_bf16.s"
+    cmd = [hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           "-falign-loops=64", "-S", "--cuda-device-only", "-o", str(out), os.path.join(os.path.dirname(SRC), "lg_fwd_bf16.hip")]
+    subprocess.run(cmd, check=True, capture_output=True, timeout=600)
+    spills = re.findall(r"\.vgpr_spill_count:\s+(\d+)", out.read_text())
+    assert len(spills) == 8 and set(spills) == {"0"}, spills
