@@ -1,7 +1,7 @@
 """Run one entry point on one benchmark workload a few times, for rocprofv3.
 
     rocprofv3 --kernel-trace --stats --output-format csv -d OUT -o NAME -- \
-        python3 paper_2410_01485_amd/prof_run.py {fwd|bwd|bwd_strided|decode|fwd_strided|fwd_gqa|copy|product} [reps]
+        python3 paper_2410_01485_amd/prof_run.py {fwd|bwd|bwd_strided|decode|fwd_strided|fwd_gqa|copy|product|NAME} [reps]
 
 fwd / bwd   : B1 H32 D128 N131072 bf16, sink 64 + window 4096 (the training-step workload)
 bwd_strided : B1 H32 D128 N131072 bf16, 64-token blocks: sink block, window 2048, every 64th block
@@ -12,6 +12,7 @@ copy        : a plain elementwise pass over 1 GiB (reads 2^30 bytes, writes 2^30
               that FETCH_SIZE / WRITE_SIZE counter readings are scaled by
 product     : torch's product of two 8192 x 8192 matrices, bf16 and float32: the rates that a large library
               product reaches on the card
+NAME        : the case of that name in perf/cases.py, two sets of inputs in turn
 Inputs are filled on the device (values do not matter to a profile).
 """
 import os
@@ -80,7 +81,13 @@ def main():
             kc, vc = sets[i % 3]
             lg.lg_sparse_attn_decode(q, kc, vc, out, lse, ws, N, sink, window)
     else:
-        sys.exit("unknown workload " + what)
+        from perf import cases
+        case = [c for c in cases.listed() if c["name"] == what]
+        if not case:
+            sys.exit("unknown workload " + what)
+        sets = [cases.prepare(case[0], seed) for seed in (1, 2)]
+        for i in range(2 * reps):
+            cases.run(sets[i % 2])
     torch.cuda.synchronize()
 
 
