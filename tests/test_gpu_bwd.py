@@ -72,11 +72,13 @@ def test_heads_that_take_their_tiles_in_the_other_order(Hq, N, D, window):
 
 
 @pytest.mark.parametrize("B,Hq,N,D,window", [
-    (33, 32, 500, 128, 500), (34, 32, 500, 128, 200), (17, 32, 500, 64, 500), (18, 32, 385, 64, 100), (33, 32, 600, 128, 600), (17, 64, 300, 128, 80)])
+    (33, 32, 500, 128, 500), (34, 32, 500, 128, 200), (17, 32, 500, 64, 500), (18, 32, 385, 64, 100), (33, 32, 600, 128, 600), (17, 64, 300, 128, 80),
+    (52, 32, 500, 128, 300), (33, 32, 500, 64, 500)])
 def test_heads_four_by_four(B, Hq, N, D, window):
-    """More than 2048 (key tile, kv head) pairs of 32 or 64 heads each: dk/dv, dq and the forward take heads four by four, every
-    other four the other way round where the heads are a multiple of 64; odd and even numbers of tiles.  Without a sink and
-    groups of query heads the same bits as each sequence by itself, which takes other orders and is close to the oracle."""
+    """More than 2048 (key tile, kv head) pairs of 32 or 64 heads each.  dk/dv takes heads four by four, every other four the
+    other way round where the heads are a multiple of 64; in the last two cases, with more items than four rounds, two heads
+    in four the other way round (33 x 32 heads of three tiles: head by head).  Without a sink and groups the same bits as
+    each sequence by itself, which takes other orders and is close to the oracle."""
     gen = torch.Generator(device=DEV).manual_seed(61)
     q, k, v, g = (torch.randn(B, Hq, N, D, generator=gen, device=DEV, dtype=torch.bfloat16) for _ in range(4))
     assert Hq * B % 32 == 0 and Hq * B * -(-N // (256 if D == 128 else 128)) > 2048
