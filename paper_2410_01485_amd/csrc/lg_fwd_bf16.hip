@@ -218,8 +218,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(LgFwdTune<D,
     // ---- online softmax (log2 domain) ----
     if (!full) {
       asm volatile("; masked" ::: "memory");  // (a real branch: nothing of it in whole tiles)
-      int ln;  // the lane, asked for here: kept from the start it was a register too many at D = 128
-      asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
+      int ln = lane;  // D = 128: asked for again here, kept from the start it was a register too many
+      if (D == 128) asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
       const int row = min(q0 + wave_s * 32 + (ln & 31), N - 1);
       const uint32_t bits = lg_key_bits(m, row, k0, ln >> 5);  // a few runs of registers, in closed form
 #pragma unroll
