@@ -163,6 +163,8 @@ LG_HD long long lg_run_grid(int total, int run) { return ((long long)total + 8LL
 // 80000 tokens 3003 -> 2553 us, 2 of 128, 48000 tokens 1370 -> 1245, 12/4 of 128, 16000 tokens 1178 -> 770; dq with 32 rows
 // per wave: 8/2 heads of 128, 12000 tokens 652 -> 440 us, 12/4 of 128, 1500 tokens 81 -> 71.  A run is up to 16 tiles of a
 // head, fewer where the XCDs would get less than four runs each, in equal parts so that few workgroups stay without an item.
+// Not where every workgroup has a CU to itself: nothing is left to even out, and neighbours in one L2 are worth 1-3 % (dq,
+// 20/4 heads of 64, 900 tokens 24.2, 23.4 us).
 struct LgRuns {
   int run;    // items of a run
   int heads;  // of the launch, where they take turns; 0: listed head by head
@@ -170,7 +172,7 @@ struct LgRuns {
 };
 inline LgRuns lg_runs(const LgMask& m, int heads, int tiles, int G, bool varied) {
   const int each = tiles * G;
-  if (lg_even_runs(m, heads, varied)) return LgRuns{(int)(((long long)heads * each + 7) / 8), 0, each};
+  if (lg_even_runs(m, heads, varied) || (long long)heads * each <= 256) return LgRuns{(int)(((long long)heads * each + 7) / 8), 0, each};
   const long long most = ((long long)tiles * heads + 31) / 32;
   const int parts = most < 16 ? (int)((tiles + most - 1) / most) : (tiles + 15) / 16;
   return LgRuns{(tiles + parts - 1) / parts * G, heads, each};

@@ -81,10 +81,11 @@ int main() {
         if (x != 1) return 2;
       // workgroups without an item: less than an eighth, beyond the padding to whole rounds of runs
       if (grid > total + total / 8 + 8LL * w.run) { std::printf("grid %lld for %d items\n", grid, total); return 3; }
-      // no XCD has much more than its share (a launch that each XCD gets a few rows of: not more than those)
+      // no XCD has much more than its share (a launch that each XCD gets a few rows of: not more than those; one with a CU for
+      // every workgroup: no matter)
       double most = 0;
       for (double x : work) most = x > most ? x : most;
-      if (!varied && most > 1.3 * all / 8 && most > 8 * longest) {
+      if (!varied && total > 256 && most > 1.3 * all / 8 && most > 8 * longest) {
         std::printf("B %d Hq %d Hkv %d N %d: an XCD has %.0f of %.0f tiles\n", B, Hq, Hkv, N, most, all / 8);
         return 4;
       }
