@@ -201,7 +201,7 @@ def test_rows_without_a_finite_score(dtype):
                                                           (140, 300, 0, 300, 1, 0)])
 def test_scores_far_above_the_first_ones(B, N, sink, window, block, stride, D):
     """bf16: keys 130 and 131 outscore the ones before them by more than any exponent holds, keys 200 and 201 these: rows that
-    see them overflow relative to the scores they met first, their neighbours do not.  Packed, the same bits."""
+    see them would overflow relative to the scores they met first, their neighbours would not.  Packed, the same bits."""
     q, k, v = lg_synth.prefill_inputs(1, 2, 1, N, D, 32, torch.bfloat16)
     q[:] = q.abs() + 0.5
     for j, x in ((130, 24.0), (200, 64.0)):
@@ -217,6 +217,85 @@ def test_scores_far_above_the_first_ones(B, N, sink, window, block, stride, D):
     op, lp = torch.empty_like(qp), torch.empty(2, 2 * N, dtype=torch.float32, device=DEV)
     lg.lg_sparse_attn_fwd_varlen(qp, kp, vp, op, lp, [0, N, 2 * N], sink, window, block, stride)
     assert torch.equal(op, out[0].repeat(1, 2, 1)) and torch.equal(lp, lse[0].repeat(1, 2))
+
+
+def growing_inputs(B, Hq, Hkv, N, D, grow, seed, dout=False):
+    """Normal inputs, but two keys of every sequence and kv head outscore the ones before them, the second the first: by
+    `grow` natural units or up to half as much again, another value for every row."""
+    x = lg_synth.prefill_inputs(B, Hq, Hkv, N, D, seed, torch.bfloat16, with_dout=dout)
+    q, k = x[:2]
+    q[..., 0] = 4 + 2 * torch.rand(B, Hq, N, generator=torch.Generator().manual_seed(seed))
+    k[..., 0] = 0
+    for b in range(B):
+        for h in range(Hkv):
+            for y, j in enumerate((N // 5 + 7 * h, N // 2 + 5 * h + b)):
+                k[b, h, j, 0] = (y + 1) * grow * D ** 0.5 / 4
+    return x
+
+
+def check_lse_of_growing_scores(q, k, lse, sink, window, block, stride):
+    """lse [B, Hq, N] against 64 bits.  P is rounded to bf16, by 2^-8 of the value at most, and the row sum is of the rounded
+    ones: 2^-8 for any row.  Where the largest score is more than 2^8 above all others' the reference has moved to it and its
+    P is 1, so that only the others' share is rounded.  Beside these a score of float32 products, 16 roundings of it."""
+    B, Hq, N, D = q.shape
+    live = torch.as_tensor(O.mask(N, sink, window, block, stride)).to(DEV).bool()
+    strict = 0
+    for b in range(B):
+        for h in range(Hq):
+            s = q[b, h].to(DEV).double() @ k[b, h * k.shape[1] // Hq].to(DEV).double().T / D ** 0.5
+            s = s.masked_fill(~live, -float("inf"))
+            want = torch.logsumexp(s, -1)
+            top = s.topk(min(2, N), dim=-1).values
+            moved = top[:, 0] - top[:, -1] > 6  # (2^8 is 5.55)
+            share = torch.where(moved, 1 - torch.exp(top[:, 0] - want), 1.0)
+            err = (lse[b, h].double() - want).abs()
+            bound = 2.0 ** -8 * share + 16 * 2.0 ** -24 * want.abs().clamp(min=1)
+            assert (err <= bound).all(), (b, h, int((err / bound).argmax()), float((err / bound).max()), float(err.max()))
+            strict += int(moved.sum())
+    return strict
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("grow", [3.0, 5.5, 8.0, 40.0, 80.0, 87.0, 88.5, 300.0])
+@pytest.mark.parametrize("B,Hq,Hkv,N,sink,window,block,stride", [
+    (1, 4, 2, 500, 0, 500, 1, 0), (1, 2, 2, 400, 64, 128, 64, 3),        # up to 256 work items
+    (5, 32, 4, 257, 16, 200, 1, 0), (2, 32, 16, 700, 64, 128, 64, 3)])  # more
+def test_scores_that_grow(B, Hq, Hkv, N, sink, window, block, stride, grow, D):
+    """bf16: rows whose scores outgrow the first ones, by less and by more than the 2^8 that moves the reference.  A key that
+    carries a row has the probability 1, not a rounded one, and the log-sum-exp is as exact as that."""
+    q, k, v = growing_inputs(B, Hq, Hkv, N, D, grow, 51)
+    out, lse = run_fwd(q, k, v, sink, window, block, stride)
+    strict = check_lse_of_growing_scores(q, k, lse, sink, window, block, stride)
+    assert grow < 8 or strict > B * Hq * N // 4
+    for b, h in ((0, 0), (B - 1, Hq - 1)):
+        hk = h * Hkv // Hq
+        wo, _ = O.fwd(*(f32np(x) for x in (q[b:b + 1, h:h + 1], k[b:b + 1, hk:hk + 1], v[b:b + 1, hk:hk + 1])), sink, window, block, stride)
+        assert_close(f32np(out[b:b + 1, h:h + 1]), wo, TOL_OUT[torch.bfloat16], TOL_REL[torch.bfloat16], "out %d %d" % (b, h))
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_scores_that_grow_packed(D):
+    """More than 256 work items of sequences that differ: the bits of each by itself."""
+    Hq, Hkv, lens = 32, 4, [300, 37, 129, 400, 64, 255, 513]
+    seqs = [growing_inputs(1, Hq, Hkv, n, D, 12.0 * (x + 1), 52 + x) for x, n in enumerate(lens)]
+    cu = np.concatenate([[0], np.cumsum(lens)]).tolist()
+    q, k, v = (torch.cat([s[x][0] for s in seqs], dim=1).contiguous().to(DEV) for x in range(3))
+    out, lse = torch.empty_like(q), torch.empty(Hq, cu[-1], device=DEV)
+    lg.lg_sparse_attn_fwd_varlen(q, k, v, out, lse, cu, 16, 200, 1, 0)
+    for x, s in enumerate(seqs):
+        o, l = run_fwd(*s, 16, 200)
+        assert torch.equal(out[:, cu[x]:cu[x + 1]], o[0]) and torch.equal(lse[:, cu[x]:cu[x + 1]], l[0]), x
+        check_lse_of_growing_scores(s[0], s[1], l, 16, 200, 1, 0)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_large_values_under_scores_that_grow(D):
+    """Values of 2^100: their sum weighted relative to the first scores would overflow, relative to the largest it does not."""
+    q, k, v = growing_inputs(1, 4, 2, 500, D, 60.0, 53)
+    wo, _ = O.fwd(f32np(q), f32np(k), f32np(v), 0, 500)
+    out, lse = run_fwd(q, k, v * 2.0 ** 100, 0, 500)
+    assert_close(f32np(out).astype(np.float64) * 2.0 ** -100, wo, TOL_OUT[torch.bfloat16], TOL_REL[torch.bfloat16], "out")
+    check_lse_of_growing_scores(q, k, lse, 0, 500, 1, 0)
 
 
 @pytest.mark.parametrize("D,scale", [(64, 0.0), (128, 0.0), (64, 40.0)])
