@@ -126,6 +126,20 @@ def assert_same_sums(x, y, what):
     assert bool(((x - y).abs() <= bound).all()), what + ": differs by more than the order of its sums"
 
 
+def growing_inputs(B, Hq, Hkv, N, D, grow, seed, dout=False):
+    """Normal inputs, but two keys of every sequence and kv head outscore the ones before them, the second the first: by
+    `grow` natural units or up to half as much again, another value for every row."""
+    x = lg_synth.prefill_inputs(B, Hq, Hkv, N, D, seed, torch.bfloat16, with_dout=dout)
+    q, k = x[:2]
+    q[..., 0] = 4 + 2 * torch.rand(B, Hq, N, generator=torch.Generator().manual_seed(seed))
+    k[..., 0] = 0
+    for b in range(B):
+        for h in range(Hkv):
+            for y, j in enumerate((N // 5 + 7 * h, N // 2 + 5 * h + b)):
+                k[b, h, j, 0] = (y + 1) * grow * D ** 0.5 / 4
+    return x
+
+
 def check_fwd(B, Hq, Hkv, N, D, sink, window, block=1, stride=0, dtype=torch.bfloat16, seed=1, q_mul=1.0,
               scale=0.0):
     q, k, v = lg_synth.prefill_inputs(B, Hq, Hkv, N, D, seed, dtype, q_mul=q_mul)

@@ -8,7 +8,7 @@ import torch
 
 import lg_synth
 import paper_2410_01485_amd as lg
-from gpu_util import DEV, TOL_LSE, TOL_OUT, TOL_REL, assert_close, check_fwd, dq_delta_allowance, f32np
+from gpu_util import DEV, TOL_LSE, TOL_OUT, TOL_REL, assert_close, check_fwd, dq_delta_allowance, f32np, growing_inputs
 from oracle import lg_oracle as O
 
 pytestmark = pytest.mark.gpu
@@ -180,6 +180,26 @@ def test_float32_rows_do_not_depend_on_the_batch(Hq, Hkv, N, sink, window, block
 def test_peaked_scores_and_custom_scale(dtype):
     check_bwd(1, 2, 2, 600, 128, 16, 100, dtype=dtype, seed=4, q_mul=4.0, by_tensor_max=True)
     check_bwd(1, 4, 1, 300, 64, 16, 100, dtype=dtype, seed=5, scale=0.3, by_tensor_max=True)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("grow", [7.0, 8.0, 9.3, 11.0, 40.0, 80.0])
+@pytest.mark.parametrize("N,sink,window", [(700, 0, 700), (900, 64, 200)])
+def test_dv_of_scores_that_grow(N, sink, window, grow, D):
+    """All queries of a head alike, two keys that outscore all before them, one after the other: their dv is the sum of the dO
+    of the rows that they carry, and all of those rows have the same log-sum-exp, whose error would be dv's.  The other rows'
+    share is below 2 N exp(-grow) of a row, each a rounded P; dv's D roundings to bf16 have a mean of 2^-9 / sqrt(D) or less."""
+    Hq = Hkv = 4
+    q, k, v, g = growing_inputs(1, Hq, Hkv, N, D, grow, 54, dout=True)
+    q[:] = q[:, :, :1]
+    dv = run_fwd_bwd(q, k, v, g, sink, window)[2]
+    w = O.bwd(f32np(q), f32np(k), f32np(v), f32np(g), sink, window)
+    assert_close(f32np(dv), w["dv"], TOL_OUT[torch.bfloat16], TOL_REL[torch.bfloat16], "dv", True)
+    for h in range(Hkv):
+        for j in (N // 5 + 7 * h, N // 2 + 5 * h):
+            want = w["dv"][0, h, j]
+            off = float((f32np(dv[0, h, j]).astype(np.float64) * want).sum() / (want * want).sum()) - 1
+            assert abs(off) <= 6 * 2.0 ** -9 / D ** 0.5 + 2.0 ** -8 * min(1.0, 2 * N * np.exp(-grow)), (h, j, off)
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])

@@ -5,7 +5,7 @@ import torch
 
 import lg_synth
 import paper_2410_01485_amd as lg
-from gpu_util import DEV, TOL_LSE, TOL_OUT, TOL_REL, assert_close, check_fwd, f32np, run_fwd
+from gpu_util import DEV, TOL_LSE, TOL_OUT, TOL_REL, assert_close, check_fwd, f32np, growing_inputs, run_fwd
 from oracle import lg_oracle as O
 
 pytestmark = pytest.mark.gpu
@@ -217,20 +217,6 @@ def test_scores_far_above_the_first_ones(B, N, sink, window, block, stride, D):
     op, lp = torch.empty_like(qp), torch.empty(2, 2 * N, dtype=torch.float32, device=DEV)
     lg.lg_sparse_attn_fwd_varlen(qp, kp, vp, op, lp, [0, N, 2 * N], sink, window, block, stride)
     assert torch.equal(op, out[0].repeat(1, 2, 1)) and torch.equal(lp, lse[0].repeat(1, 2))
-
-
-def growing_inputs(B, Hq, Hkv, N, D, grow, seed, dout=False):
-    """Normal inputs, but two keys of every sequence and kv head outscore the ones before them, the second the first: by
-    `grow` natural units or up to half as much again, another value for every row."""
-    x = lg_synth.prefill_inputs(B, Hq, Hkv, N, D, seed, torch.bfloat16, with_dout=dout)
-    q, k = x[:2]
-    q[..., 0] = 4 + 2 * torch.rand(B, Hq, N, generator=torch.Generator().manual_seed(seed))
-    k[..., 0] = 0
-    for b in range(B):
-        for h in range(Hkv):
-            for y, j in enumerate((N // 5 + 7 * h, N // 2 + 5 * h + b)):
-                k[b, h, j, 0] = (y + 1) * grow * D ** 0.5 / 4
-    return x
 
 
 def check_lse_of_growing_scores(q, k, lse, sink, window, block, stride):
