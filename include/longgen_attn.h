@@ -104,6 +104,8 @@ const char* lg_status_str(int status);
  *   out[b,hq,i,:] = sum_j P_ij v[b,hk,j,:],  P_ij = exp(scale*<q_i,k_j> - lse_i)
  *   over the keys j with live(i,j);  lse_i = ln sum_j exp(scale*<q_i,k_j>).
  * out has the dtype of q (float32 results rounded to nearest-even for bf16).
+ * bf16: the probabilities are rounded to bf16 before both sums, which leaves lse off by up to 2^-8 (beside the float32
+ * rounding of a score), by less the more one key outweighs the others or the more keys there are.
  */
 int lg_sparse_attn_fwd(const void* q, const void* k, const void* v, void* out, float* lse,
                        int B, int Hq, int Hkv, int N, int D,
