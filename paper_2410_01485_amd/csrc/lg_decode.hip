@@ -737,6 +737,8 @@ struct DecPlan {
   bool wide;          // a workgroup of WIDE waves for a row
   size_t part_bytes;  // workspace per part: most * rows * part_bytes serves every context up to the one given
 };
+// Rounds of keys up to which a workgroup of WIDE waves takes a whole row; 0: none does.
+constexpr int wide_rounds(int dtype, int D) { return dtype == LG_F32 ? (D == 64 ? 3 : 0) : D == 64 ? 5 : 3; }
 DecPlan dec_plan(int B, int Hq, int Hkv, int D, int valid, int dtype, bool paged) {
   const int G = Hq / Hkv;
   DecPlan p;
@@ -783,8 +785,11 @@ DecPlan dec_plan(int B, int Hq, int Hkv, int D, int valid, int dtype, bool paged
   // the other and replayed from a graph; parts, wide; 8 kv heads): bf16 of 128, 384 keys 10.9, 8.8 and 8.9, 8.6, 500 keys 10.1,
   // 10.0 and 9.0, 9.8; of 64, 384 keys 11.2, 7.5 and 8.1, 6.6, 576 11.9, 8.1 and 8.1, 7.8, 768 10.9, 9.0 and 8.0, 8.7; float32
   // of 64, 192 keys 11.0, 8.2 and 8.4, 7.0, 384 11.0, 9.4 and 8.7, 9.1; of 128, 192 keys 10.7, 10.4 and 9.4, 10.2.
-  const int wide = dtype == LG_F32 ? (D == 64 ? 3 : 0) : D == 64 ? 5 : 3;  // rounds
-  p.wide = p.splits > 1 && rounds <= wide && p.rows <= 256;
+  // Up to 256 rows, each with a CU to itself (paged, without the append, 256 and 320 rows; parts, wide): bf16 of 128, 160 keys 8.7,
+  // 6.9 and 10.1, 12.2, 384 12.8, 10.8 and 17.2, 18.7; of 64, 256 keys 7.8, 6.0 and 8.9, 9.7, 640 11.8, 8.8 and 14.1, 15.1; float32
+  // of 64, 192 keys 11.1, 7.0 and 12.7, 11.7.  (Contiguous caches: rows are cut only where that leaves a workgroup per CU, at 320
+  // rows no more.)
+  p.wide = p.splits > 1 && rounds <= wide_rounds(dtype, D) && p.rows <= 256;
   if (p.wide) {
     p.splits = 1;
     p.chunk = valid;
@@ -826,11 +831,15 @@ hipError_t launch_typed(const void* q, const void* kc, const void* vc, void* out
   decode_mfma_kernel<T, D, MODE, W><<<grid, (W) * 64, 0, s>>>((const E*)q, (const E*)kc, (const E*)vc, (T*)out, lse, wk, \
                                                               Hq, Hkv, C, valid, qmul, rest, ldexpf(1.f, ilogbf(rest)), \
                                                               LgDecExtra<MODE>{__VA_ARGS__})
-  if (plan.wide) {
-    if (paged) LG_DECODE_LAUNCH(WIDE, LG_DEC_PAGED, pg);
-    else if (plain) LG_DECODE_LAUNCH(WIDE, LG_DEC_PLAIN);
-    else LG_DECODE_LAUNCH(WIDE, LG_DEC_SEGS, segs);
-  } else if (paged) LG_DECODE_LAUNCH(WAVES, LG_DEC_PAGED, pg);
+  if constexpr (wide_rounds(dtype, D) > 0) {
+    if (plan.wide) {
+      if (paged) LG_DECODE_LAUNCH(WIDE, LG_DEC_PAGED, pg);
+      else if (plain) LG_DECODE_LAUNCH(WIDE, LG_DEC_PLAIN);
+      else LG_DECODE_LAUNCH(WIDE, LG_DEC_SEGS, segs);
+      return hipGetLastError();
+    }
+  }
+  if (paged) LG_DECODE_LAUNCH(WAVES, LG_DEC_PAGED, pg);
   else if (plain) LG_DECODE_LAUNCH(WAVES, LG_DEC_PLAIN);
   else LG_DECODE_LAUNCH(WAVES, LG_DEC_SEGS, segs);
 #undef LG_DECODE_LAUNCH
