@@ -257,6 +257,62 @@ def test_paged_parts(lens, Hq, Hkv, D, sink, window, page_size):
         assert_close(f32np(lse[b]), wl[0, :, n - 1], TOL_LSE[dt], None, "paged seq %d of %d lse" % (b, n))
 
 
+@pytest.mark.parametrize("B,Hkv,whole", [(3, 2, True), (64, 4, True), (86, 3, False)])
+@pytest.mark.parametrize("dtype,D,n_max", [(torch.bfloat16, 128, 256), (torch.bfloat16, 128, 384), (torch.bfloat16, 64, 640), (torch.float32, 64, 192)])
+def test_paged_rows_of_few_keys(dtype, D, n_max, B, Hkv, whole):
+    """Two to five rounds of keys: up to 256 rows a workgroup of twelve waves takes a whole row and leaves the workspace alone,
+    of more rows they are cut into parts."""
+    Hq, sink, page = 3 * Hkv, 8, 32
+    code = lg.LG_BF16 if dtype == torch.bfloat16 else lg.LG_F32
+    gen = torch.Generator(device=DEV).manual_seed(61)
+    lens = [n_max] + [1 + (977 * x) % n_max for x in range(1, B)]
+    table = torch.randperm(B * n_max // page, generator=gen, device=DEV).to(torch.int32).reshape(B, -1).contiguous()
+    kp, vp = (torch.randn(B * n_max // page, Hkv, page, D, generator=gen, device=DEV, dtype=dtype) for _ in range(2))
+    q = torch.randn(B, Hq, D, generator=gen, device=DEV, dtype=dtype)
+    out, lse = torch.full_like(q, float("nan")), torch.full((B, Hq), float("nan"), device=DEV)
+    need = lg.decode_paged_workspace_bytes(B, Hq, Hkv, n_max, D, sink, n_max - sink, 1, 0, code)
+    assert need > 0
+    ws = torch.full((need,), 0x5a, dtype=torch.uint8, device=DEV)
+    sl = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    lg.lg_sparse_attn_decode_paged(q, kp, vp, table, sl, out, lse, ws, n_max, sink, n_max - sink, 1, 0)
+    assert bool((ws == 0x5a).all()) == whole
+    kc, vc = (x[table.long()].permute(0, 2, 1, 3, 4).reshape(B, Hkv, n_max, D) for x in (kp, vp))
+    for b in range(0, B, 1 if B < 10 else 7):
+        wo, wl = O.decode(f32np(q[b:b + 1]), f32np(kc[b:b + 1]), f32np(vc[b:b + 1]), lens[b], sink, n_max - sink)
+        assert_close(f32np(out[b:b + 1]), wo, TOL_OUT[dtype], TOL_REL[dtype], "seq %d of %d out" % (b, lens[b]))
+        assert_close(f32np(lse[b:b + 1]), wl, TOL_LSE[dtype], None, "seq %d of %d lse" % (b, lens[b]))
+
+
+@pytest.mark.parametrize("dtype,D,N,sink,window,block,stride", [
+    (torch.bfloat16, 128, 700, 32, 96, 32, 4), (torch.bfloat16, 128, 500, 64, 128, 64, 3), (torch.bfloat16, 64, 1500, 32, 64, 32, 4),
+    (torch.bfloat16, 64, 1111, 48, 96, 48, 3), (torch.float32, 64, 400, 16, 32, 16, 3), (torch.float32, 64, 300, 16, 64, 16, 4)])
+def test_rows_of_few_keys_in_several_runs(dtype, D, N, sink, window, block, stride):
+    """Strided patterns, whose slots in use are several runs, contiguous and paged: a whole row by a workgroup of twelve waves."""
+    B, Hq, Hkv, page = 2, 6, 2, 32
+    code = lg.LG_BF16 if dtype == torch.bfloat16 else lg.LG_F32
+    q, k, v = lg_synth.prefill_inputs(B, Hq, Hkv, N, D, 62, dtype)
+    wo, wl = O.fwd(f32np(q), f32np(k), f32np(v), sink, window, block, stride, rows=(N - 1, N))
+    ql = q[:, :, N - 1].contiguous().to(DEV)
+    slots = lg.lg_kv_cache_slots(N, sink, window, block, stride)
+    n_max, table, kp, vp, _ = paged_setup([N - 8] * B, Hq, Hkv, D, sink, window, block, stride, page, dtype, 5)
+    lg.lg_kv_paged_append(k.to(DEV), v.to(DEV), kp, vp, table, torch.zeros(B, dtype=torch.int32, device=DEV), n_max, sink, window,
+                          block, stride)
+    lens = torch.full((B,), N, dtype=torch.int32, device=DEV)
+    kc, vc = gpu_append_all(k, v, sink, window, block, stride, [N], slots, 1.0e4)
+    for paged, need in ((False, lg.decode_cache_workspace_bytes(B, Hq, Hkv, N, D, sink, window, block, stride, code)),
+                        (True, lg.decode_paged_workspace_bytes(B, Hq, Hkv, n_max, D, sink, window, block, stride, code))):
+        assert need > 0
+        ws = torch.full((need,), 0x5a, dtype=torch.uint8, device=DEV)
+        out, lse = torch.full_like(ql, float("nan")), torch.full((B, Hq), float("nan"), device=DEV)
+        if paged:
+            lg.lg_sparse_attn_decode_paged(ql, kp, vp, table, lens, out, lse, ws, n_max, sink, window, block, stride)
+        else:
+            lg.lg_sparse_attn_decode_cache(ql, kc, vc, out, lse, ws, N, sink, window, block, stride)
+        assert (ws == 0x5a).all(), paged  # (one part)
+        assert_close(f32np(out), wo[:, :, N - 1], TOL_OUT[dtype], TOL_REL[dtype], "out %d" % paged)
+        assert_close(f32np(lse), wl[:, :, N - 1], TOL_LSE[dtype], None, "lse %d" % paged)
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("Hq,Hkv,D,dead", [(2, 2, 128, 1100), (8, 1, 64, 1100), (2, 1, 128, 256), (2, 1, 64, 2000)])
 def test_parts_whose_scores_are_all_minus_infinity(dtype, Hq, Hkv, D, dead):

@@ -80,14 +80,14 @@ def test_decode_float32_units(B, Hq, Hkv, D, window, N):
     (torch.bfloat16, 128, [129, 256, 257, 383, 384, 385]),
     (torch.bfloat16, 64, [257, 384, 385, 400, 639, 640, 641]),
     (torch.float32, 64, [65, 128, 129, 191, 192, 193]),
-    (torch.float32, 128, [65, 192]),
+    (torch.float32, 128, [65, 192]),  # (always parts)
 ])
 @pytest.mark.parametrize("Hq,Hkv", [(1, 1), (48, 3)])
 def test_decode_rows_of_few_keys(dtype, D, keys, Hq, Hkv):
     """Up to so many keys a workgroup of twelve waves takes a whole row, beyond it rows are cut into parts."""
     for N in keys:
         check_decode(1, Hq, Hkv, D, 8, 2000, N, dtype, seed=17)
-    check_decode(86, 3 * Hq // Hkv, 3, D, 8, 2000, keys[-2], dtype, seed=18)  # (more than 256 rows: four waves each)
+    check_decode(86, 3 * Hq // Hkv, 3, D, 8, 2000, keys[-2], dtype, seed=18)  # (so many rows are not cut: four waves each)
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
