@@ -58,7 +58,6 @@ __global__ __launch_bounds__(8 * TQ, (D == 64 ? 4 : 2) * TQ / 64) void dq_f32_ke
   const int n = lane & 15, h = lane >> 4;
   const int rg = wave % RG, kh = wave / RG;
   const int q0 = qt * TQ, q1 = min(q0 + TQ - 1, N - 1);
-  const int qw0 = min(q0 + 16 * rg, N - 1), qw1 = min(q0 + 16 * rg + 15, N - 1);
   const int i = q0 + 16 * rg + n, iq = min(i, N - 1);
   const size_t qbase = (size_t)(b * Hq + hq) * m.ld * D;
   const size_t kbase = (size_t)(b * Hkv + hk) * m.ld * D;
@@ -101,7 +100,6 @@ __global__ __launch_bounds__(8 * TQ, (D == 64 ? 4 : 2) * TQ / 64) void dq_f32_ke
     dma.issue(v + kbase + (size_t)t * TK * D, N - t * TK, lds0 + stage * STAGE + T::BYTES);
   };
   const LgQSched qs = lg_qsched_init(m, q0, q1);
-  const LgRows rows = lg_rows(m, qw0, qw1);
   LgF32Row row;
   row.init(m, i);
   int t = lg_qsched_next(m, qs, -1);
@@ -114,12 +112,10 @@ __global__ __launch_bounds__(8 * TQ, (D == 64 ? 4 : 2) * TQ / 64) void dq_f32_ke
     __syncthreads();
     const int sk = stage * STAGE, sv = sk + T::BYTES;
     const int rb0 = 2 * kh, kk = t * TK + 32 * kh;
-    int kind0 = LG_TILE_FULL, kind1 = LG_TILE_FULL;  // of the wave's two 16-key blocks
-    if (!lg_qsched_full(m, qs, t)) {
-      kind0 = lg_rows_kind(m, rows, kk, kk + 15);
-      kind1 = lg_rows_kind(m, rows, kk + 16, kk + 31);
-    }
-    const bool masked = kind0 == LG_TILE_PARTIAL || kind1 == LG_TILE_PARTIAL;
+    // live keys of the lane's row in the wave's two 16-key blocks
+    const uint32_t bits = lg_qsched_full(m, qs, t) ? 0xffu : row.bits(m, kk, h);
+    const bool on0 = __builtin_amdgcn_ballot_w64((bits & 0x0fu) != 0) != 0, on1 = __builtin_amdgcn_ballot_w64((bits & 0xf0u) != 0) != 0;
+    const bool masked = __builtin_amdgcn_ballot_w64(bits != 0xffu) != 0;
     // as in the forward: units of matrix instructions, their LDS operands requested one unit ahead
     auto run = [&](auto B0_, auto NB_) {
       constexpr int B0 = decltype(B0_)::value, NB = decltype(NB_)::value;
@@ -176,7 +172,7 @@ __global__ __launch_bounds__(8 * TQ, (D == 64 ? 4 : 2) * TQ / 64) void dq_f32_ke
         for (int x = 0; x < NB; ++x)
 #pragma unroll
           for (int r = 0; r < 4; ++r)
-            if (!row.live(m, kk + 16 * (B0 + x) + 4 * h + r)) s[x][r] = 0.f;
+            s[x][r] = lg_keep_or(s[x][r], bits, 4 * (B0 + x) + r, 0.f);
       }
 #pragma unroll
       for (int x = 0; x < NB; ++x)
@@ -190,9 +186,9 @@ __global__ __launch_bounds__(8 * TQ, (D == 64 ? 4 : 2) * TQ / 64) void dq_f32_ke
         for (int db = 0; db < DC; ++db) acc[db] = lg_mfma16(kc[u & 1][db], s[u >> 2][u & 3], acc[db]);
       }
     };
-    if (kind0 != LG_TILE_DEAD && kind1 != LG_TILE_DEAD) run(I0{}, I2{});
-    else if (kind0 != LG_TILE_DEAD) run(I0{}, I1{});
-    else if (kind1 != LG_TILE_DEAD) run(I1{}, I1{});
+    if (on0 && on1) run(I0{}, I2{});
+    else if (on0) run(I0{}, I1{});
+    else if (on1) run(I1{}, I1{});
     __syncthreads();  // everyone is done with this stage
     const int t2 = tn >= 0 ? lg_qsched_next(m, qs, tn) : -1;
     if (t2 >= 0) issue(t2, stage);

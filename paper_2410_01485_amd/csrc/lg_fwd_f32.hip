@@ -44,7 +44,6 @@ __global__ __launch_bounds__(8 * TQ, (D == 64 ? 4 : 2) * TQ / 64) void fwd_f32_k
   const int n = lane & 15, h = lane >> 4;
   const int rg = wave % RG, kh = wave / RG;
   const int q0 = qt * TQ, q1 = min(q0 + TQ - 1, N - 1);
-  const int qw0 = min(q0 + 16 * rg, N - 1), qw1 = min(q0 + 16 * rg + 15, N - 1);  // this wave's rows
   const int i = q0 + 16 * rg + n, iq = min(i, N - 1);
   const size_t qbase = (size_t)(b * Hq + hq) * m.ld * D;
   const size_t kbase = (size_t)(b * Hkv + hk) * m.ld * D;
@@ -73,7 +72,6 @@ __global__ __launch_bounds__(8 * TQ, (D == 64 ? 4 : 2) * TQ / 64) void fwd_f32_k
     dma.issue(v + kbase + (size_t)t * TK * D, N - t * TK, lds0 + stage * STAGE + T::BYTES);
   };
   const LgQSched qs = lg_qsched_init(m, q0, q1);
-  const LgRows rows = lg_rows(m, qw0, qw1);
   LgF32Row row;
   row.init(m, i);
   int t = lg_qsched_next(m, qs, -1);
@@ -86,12 +84,10 @@ __global__ __launch_bounds__(8 * TQ, (D == 64 ? 4 : 2) * TQ / 64) void fwd_f32_k
     __syncthreads();
     const int sk = stage * STAGE, sv = sk + T::BYTES;
     const int rb0 = 2 * kh, kk = t * TK + 32 * kh;
-    int kind0 = LG_TILE_FULL, kind1 = LG_TILE_FULL;  // of the wave's two 16-key blocks
-    if (!lg_qsched_full(m, qs, t)) {
-      kind0 = lg_rows_kind(m, rows, kk, kk + 15);
-      kind1 = lg_rows_kind(m, rows, kk + 16, kk + 31);
-    }
-    const bool masked = kind0 == LG_TILE_PARTIAL || kind1 == LG_TILE_PARTIAL;
+    // live keys of the lane's row in the wave's two 16-key blocks
+    const uint32_t bits = lg_qsched_full(m, qs, t) ? 0xffu : row.bits(m, kk, h);
+    const bool on0 = __builtin_amdgcn_ballot_w64((bits & 0x0fu) != 0) != 0, on1 = __builtin_amdgcn_ballot_w64((bits & 0xf0u) != 0) != 0;
+    const bool masked = __builtin_amdgcn_ballot_w64(bits != 0xffu) != 0;
     // Blocks B0 .. B0 + NB - 1 of the half tile, as a straight sequence of units whose LDS operands are requested one
     // unit ahead: DC units of the first product, then 4 NB of the second.
     auto run = [&](auto B0_, auto NB_) {
@@ -124,12 +120,13 @@ __global__ __launch_bounds__(8 * TQ, (D == 64 ? 4 : 2) * TQ / 64) void fwd_f32_k
 #pragma unroll
         for (int x = 0; x < NB; ++x) s[x] = lg_mfma16(ka[c & 1][x].w, qf[c].w, s[x]);
       }
-      if (masked)
+      if (masked) {
+        asm volatile("; masked" ::: "memory");  // (a real branch: nothing of it in whole tiles)
 #pragma unroll
         for (int x = 0; x < NB; ++x)
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (!row.live(m, kk + 16 * (B0 + x) + 4 * h + r)) s[x][r] = -INFINITY;
+          for (int r = 0; r < 4; ++r) s[x][r] = lg_keep_or(s[x][r], bits, 4 * (B0 + x) + r, -INFINITY);
+      }
       float mx = -INFINITY;
 #pragma unroll
       for (int x = 0; x < NB; ++x) mx = fmaxf(mx, fmaxf(fmaxf(s[x][0], s[x][1]), fmaxf(s[x][2], s[x][3])));
@@ -164,9 +161,9 @@ __global__ __launch_bounds__(8 * TQ, (D == 64 ? 4 : 2) * TQ / 64) void fwd_f32_k
     using I0 = std::integral_constant<int, 0>;
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
-    if (kind0 != LG_TILE_DEAD && kind1 != LG_TILE_DEAD) run(I0{}, I2{});
-    else if (kind0 != LG_TILE_DEAD) run(I0{}, I1{});
-    else if (kind1 != LG_TILE_DEAD) run(I1{}, I1{});
+    if (on0 && on1) run(I0{}, I2{});
+    else if (on0) run(I0{}, I1{});
+    else if (on1) run(I1{}, I1{});
     __syncthreads();  // everyone is done with this stage
     const int t2 = tn >= 0 ? lg_qsched_next(m, qs, tn) : -1;
     if (t2 >= 0) issue(t2, stage);

@@ -472,6 +472,23 @@ LG_HD uint32_t lg_key_bits(const LgMask& m, int i, int k0, int g) {
   return w;
 }
 
+// float32 forward / dq: bit j of the result says whether row i sees key k0 + j (j = 0..31; w: the first key of the row's
+// window).  Also a few runs of bits; the strided blocks' are the same for all rows.
+LG_HD uint32_t lg_bits_below(int x) { return x <= 0 ? 0u : x >= 32 ? ~0u : (1u << x) - 1u; }
+LG_HD uint32_t lg_strided_bits(const LgMask& m, int k0) {
+  if (m.stride == 1) return ~0u;
+  uint32_t w = 0;
+  const int kb1 = lg_div_b(m, k0 + 31);
+  for (int kb = lg_next_strided_block(m, lg_div_b(m, k0)); kb <= kb1; kb += m.stride) {
+    const int s = kb * m.b - k0;
+    w |= lg_bits_below(s + m.b) & ~lg_bits_below(s);
+  }
+  return w;
+}
+LG_HD uint32_t lg_row_key_bits(const LgMask& m, int i, int w, int k0, uint32_t strided) {
+  return lg_bits_below(i - k0 + 1) & (~lg_bits_below(w - k0) | lg_bits_below(m.sink - k0) | strided);
+}
+
 // dk/dv layout: the lane owns key j, register r is query row q0 + 4 g + c(r) of the 64-row tile at q0.
 // Bit r: that row exists (below N) and live(row, j).  The rows that see a key are ONE run: from j to the
 // last row of block kb + wb - 1, or to the end of the sequence for a sink or strided-column key.

@@ -2,6 +2,9 @@
 
 lg_debug_tile_map runs on the host the same source the kernels compile; the brute-force side
 builds the dense mask with the oracle and reduces it per tile.  No GPU needed."""
+import os
+import subprocess
+
 import numpy as np
 import pytest
 
@@ -181,6 +184,38 @@ def test_partial_tile_register_masks_match_the_predicate(N, sink, window, block,
                         if x < N and (mask[x, f] if transposed else mask[f, x]):
                             want |= 1 << r
                     assert got == want, (transposed, f, t0, half, bin(got), bin(want))
+
+
+def test_key_bits_of_the_float32_kernels_equal_the_predicate(tmp_path):
+    """Bit j of lg_row_key_bits: does the row see key k0 + j, for all 32-key half tiles and rows of patterns of every form (token
+    and block granularity, strided columns of powers of two and others, sinks that end inside a half tile)."""
+    src = tmp_path / "bits.cpp"
+    src.write_text(r"""
+#include <stdio.h>
+#include "lg_mask.h"
+int main() {
+  const int P[][5] = {{200, 0, 9, 1, 0}, {200, 16, 40, 1, 0}, {131, 17, 131, 1, 0}, {200, 4, 33, 1, 5}, {200, 0, 16, 1, 1}, {150, 3, 8, 1, 4},
+                      {300, 16, 32, 16, 0}, {300, 16, 48, 16, 3}, {300, 48, 96, 48, 2}, {400, 64, 128, 64, 4}, {270, 6, 18, 6, 7}, {1, 0, 1, 1, 0}};
+  long n = 0;
+  for (auto& p : P) {
+    const LgMask m = lg_make_mask(p[0], p[1], p[2], p[3], p[4]);
+    for (int i = 0; i < m.N; ++i)
+      for (int k0 = 0; k0 < m.N; k0 += 32, ++n) {
+        const int w = (lg_div_b(m, i) - m.wb + 1) * m.b;
+        const uint32_t got = lg_row_key_bits(m, i, w, k0, m.stride > 0 ? lg_strided_bits(m, k0) : 0u);
+        for (int j = 0; j < 32; ++j)
+          if (((got >> j) & 1) != (lg_live(m, i, k0 + j) ? 1u : 0u)) { printf("N %d row %d key %d\n", m.N, i, k0 + j); return 1; }
+      }
+  }
+  printf("%ld half tiles\n", n);
+  return 0;
+}
+""")
+    exe = tmp_path / "bits"
+    csrc = os.path.join(os.path.dirname(os.path.abspath(lg.__file__)), "csrc")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-I", csrc, str(src), "-o", str(exe)], check=True, timeout=120)
+    got = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert got.returncode == 0, got.stdout
 
 
 def test_partial_tile_bits_argument_errors():
