@@ -53,7 +53,7 @@ struct LgF32Reader {
 };
 
 // The live keys of a lane's query row: bit 4 x + r is key k0 + 16 x + 4 h + r, as the accumulators of two 16-key blocks
-// hold them.  (Element by element, with the pattern's divisions and a branch each, and a class of the blocks worked out before:
+// hold them.  (Element by element, with the pattern's divisions and a branch each:
 // 1 head of 64, 128 tokens, forward 6.7 us, so 6.2; 2 x 8 heads, 1024 tokens, window 128 14.6, 14.0, backward 45.2, 44.5.)
 struct LgF32Row {
   int i, w;  // the row, the first key of its window

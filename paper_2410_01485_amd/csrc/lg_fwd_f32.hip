@@ -72,6 +72,7 @@ __global__ __launch_bounds__(8 * TQ, (D == 64 ? 4 : 2) * TQ / 64) void fwd_f32_k
     dma.issue(v + kbase + (size_t)t * TK * D, N - t * TK, lds0 + stage * STAGE + T::BYTES);
   };
   const LgQSched qs = lg_qsched_init(m, q0, q1);
+  const LgRows rows = lg_rows(m, min(q0 + 16 * rg, N - 1), min(q0 + 16 * rg + 15, N - 1));
   LgF32Row row;
   row.init(m, i);
   int t = lg_qsched_next(m, qs, -1);
@@ -85,9 +86,12 @@ __global__ __launch_bounds__(8 * TQ, (D == 64 ? 4 : 2) * TQ / 64) void fwd_f32_k
     const int sk = stage * STAGE, sv = sk + T::BYTES;
     const int rb0 = 2 * kh, kk = t * TK + 32 * kh;
     // live keys of the lane's row in the wave's two 16-key blocks
-    const uint32_t bits = lg_qsched_full(m, qs, t) ? 0xffu : row.bits(m, kk, h);
-    const bool on0 = __builtin_amdgcn_ballot_w64((bits & 0x0fu) != 0) != 0, on1 = __builtin_amdgcn_ballot_w64((bits & 0xf0u) != 0) != 0;
-    const bool masked = __builtin_amdgcn_ballot_w64(bits != 0xffu) != 0;
+    int kind0 = LG_TILE_FULL, kind1 = LG_TILE_FULL;
+    if (!lg_qsched_full(m, qs, t)) {
+      kind0 = lg_rows_kind(m, rows, kk, kk + 15);
+      kind1 = lg_rows_kind(m, rows, kk + 16, kk + 31);
+    }
+    const bool on0 = kind0 != LG_TILE_DEAD, on1 = kind1 != LG_TILE_DEAD, masked = kind0 == LG_TILE_PARTIAL || kind1 == LG_TILE_PARTIAL;
     // Blocks B0 .. B0 + NB - 1 of the half tile, as a straight sequence of units whose LDS operands are requested one
     // unit ahead: DC units of the first product, then 4 NB of the second.
     auto run = [&](auto B0_, auto NB_) {
@@ -122,6 +126,7 @@ __global__ __launch_bounds__(8 * TQ, (D == 64 ? 4 : 2) * TQ / 64) void fwd_f32_k
       }
       if (masked) {
         asm volatile("; masked" ::: "memory");  // (a real branch: nothing of it in whole tiles)
+        const uint32_t bits = row.bits(m, kk, h);
 #pragma unroll
         for (int x = 0; x < NB; ++x)
 #pragma unroll

@@ -475,7 +475,8 @@ LG_HD uint32_t lg_key_bits(const LgMask& m, int i, int k0, int g) {
 // float32 forward / dq: bit j of the result says whether row i sees key k0 + j (j = 0..31; w: the first key of the row's
 // window).  Also a few runs of bits; the strided blocks' are the same for all rows.
 LG_HD uint32_t lg_bits_below(int x) { return x <= 0 ? 0u : x >= 32 ? ~0u : (1u << x) - 1u; }
-LG_HD uint32_t lg_strided_bits(const LgMask& m, int k0) {
+LG_HD uint32_t lg_strided_bits(const LgMask& m, int k0) {  // k0: a multiple of 32
+  if (m.bshift >= 5) return lg_strided(m, k0 >> m.bshift) ? ~0u : 0u;  // (in one block)
   if (m.stride == 1) return ~0u;
   uint32_t w = 0;
   const int kb1 = lg_div_b(m, k0 + 31);
