@@ -3,7 +3,8 @@
 //
 //   Delta_i = <dout_i, out_i>
 //   P_ij = exp(scale <q_i,k_j> - lse_i),  dP_ij = <dout_i, v_j>,  dS_ij = P_ij (dP_ij - Delta_i)
-//   dq_i = scale sum_j dS_ij k_j        (query-tile major, same tile walk as the forward; forms Delta too)
+//   dq_i = scale sum_j dS_ij k_j        (query-tile major, same tile walk as the forward; forms Delta too, or, where it shares a
+//          launch with dk/dv because neither fills the GPU, a small kernel before both)
 //   dk_j = scale sum_i dS_ij q_i,  dv_j = sum_i P_ij dout_i   (key-tile major, summed over the query heads of
 //          the group)
 // Precision path for float32 data: every product on the float32 matrix instruction (lg_f32.h).  dq uses 8 or 4 waves, as
@@ -33,23 +34,42 @@ static_assert(LG_F32_TK == 64, "two key halves of 32");
 static_assert(LG_F32_KEYS == 32, "two groups of 16 keys");
 
 // ------------------------------------------------------------------------- dq
-// Also forms Delta for the dk/dv kernel and clears its arrival counters.
-template <int D, int TQ>
-__global__ __launch_bounds__(8 * TQ, (D == 64 ? 4 : 2) * TQ / 64) void dq_f32_kernel(
-    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
+// Delta of the 16 rows whose row n the lanes n, n + 16, .. hold a float4 each of every 16 dims of: the diagonal of out dO^T, in
+// the order in which dP is summed: where out_i is v_j (a row with one live key) dP - Delta is then exactly zero, as it should be.
+template <int D>
+__device__ __forceinline__ float lg_delta_f32(const float* __restrict__ out, const float4 (&gf)[D / 16], int n, int h) {
+  f32x4_t dl = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < D / 16; ++c) {
+    const float4 ov = *reinterpret_cast<const float4*>(out + 16 * c + 4 * h);
+    dl = lg_mfma16(ov.x, gf[c].x, dl);
+    dl = lg_mfma16(ov.y, gf[c].y, dl);
+    dl = lg_mfma16(ov.z, gf[c].z, dl);
+    dl = lg_mfma16(ov.w, gf[c].w, dl);
+  }
+  // row n of column n is register n % 4 of lane (n, h = n / 4)
+  return __shfl((n & 2) ? ((n & 1) ? dl[3] : dl[2]) : ((n & 1) ? dl[1] : dl[0]), 16 * (n >> 2) + n);
+}
+
+// FORM: also forms Delta for the dk/dv kernel (otherwise it is there) and clears its arrival counters.
+template <int D>
+constexpr int DQ_LDS = 4 * LgF32Tile<D>::BYTES;
+template <int D, int TQ, bool FORM>
+__device__ __forceinline__ void dq_f32_item(
+    unsigned char* smem, int id, int ids, const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
     const float* __restrict__ out, const float* __restrict__ dout, const float* __restrict__ lse,
-    float* __restrict__ delta, float* __restrict__ dq, int Hq, int Hkv, float scale, LgMask m, LgItems items,
+    float* __restrict__ delta, float* __restrict__ dq, int Hq, int Hkv, float scale, const LgMask& m, const LgItems& items,
     unsigned* __restrict__ arrived, int ncounters) {
   using T = LgF32Tile<D>;
   constexpr int RG = TQ / 16, NT = 128 * RG;  // as in the forward
   using Dma = LgTileDma<T, NT>;
   constexpr int TK = LG_F32_TK, DC = D / 16;
   constexpr int STAGE = 2 * T::BYTES, LPT = 2 * Dma::CH;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * STAGE];
 
   const int tid = threadIdx.x;
-  for (long long x = (long long)blockIdx.x * NT + tid; x < ncounters; x += (long long)gridDim.x * NT) arrived[x] = 0u;
-  const int L = lg_item_of(blockIdx.x, items.run);
+  if (FORM)
+    for (long long x = (long long)id * NT + tid; x < ncounters; x += (long long)ids * NT) arrived[x] = 0u;
+  const int L = lg_item_of(id, items.run);
   if (L >= items.total) return;
   const LgItem it = lg_item(items, L);
   const int b = it.b, hk = it.hk, hq = it.hq, qt = (int)items.nqt.d - 1 - it.x;
@@ -64,27 +84,23 @@ __global__ __launch_bounds__(8 * TQ, (D == 64 ? 4 : 2) * TQ / 64) void dq_f32_ke
   const float c2 = scale * LOG2E;
 
   float4 qf[DC], gf[DC];
-  // Delta as the diagonal of out dO^T, in the order in which dP is summed: where out_i is v_j (a row with one live
-  // key) dP - Delta is then exactly zero, as it should be
-  f32x4_t dl = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int c = 0; c < DC; ++c) {
     const size_t at = qbase + (size_t)iq * D + 16 * c + 4 * h;
     qf[c] = *reinterpret_cast<const float4*>(q + at);
     gf[c] = *reinterpret_cast<const float4*>(dout + at);
-    const float4 ov = *reinterpret_cast<const float4*>(out + at);
-    dl = lg_mfma16(ov.x, gf[c].x, dl);
-    dl = lg_mfma16(ov.y, gf[c].y, dl);
-    dl = lg_mfma16(ov.z, gf[c].z, dl);
-    dl = lg_mfma16(ov.w, gf[c].w, dl);
   }
-  // row n of column n is register n % 4 of lane (n, h = n / 4)
-  float di = __shfl((n & 2) ? ((n & 1) ? dl[3] : dl[2]) : ((n & 1) ? dl[1] : dl[0]), 16 * (n >> 2) + n);
-  float lse2 = lse[(size_t)(b * Hq + hq) * m.ld + iq] * LOG2E;
-  if (kh == 0 && h == 0 && i < N) delta[(size_t)(b * Hq + hq) * N + i] = di;
+  float* const my_delta = delta + (size_t)(b * Hq + hq) * N + iq;
+  float lse2 = lse[(size_t)(b * Hq + hq) * m.ld + iq] * LOG2E, di;
+  if constexpr (FORM) {
+    di = lg_delta_f32<D>(out + qbase + (size_t)iq * D, gf, n, h);
+    if (kh == 0 && h == 0 && i < N) *my_delta = di;
+  } else {
+    di = *my_delta;
+  }
   asm volatile("" : "+v"(lse2), "+v"(di));  // everything loaded so far is waited for here, not in the tile loop
 #pragma unroll
-  for (int c = 0; c < DC; ++c) asm volatile("" ::"v"(qf[c].x));
+  for (int c = 0; c < DC; ++c) asm volatile("" ::"v"(qf[c].x), "v"(gf[c].x));
 
   f32x4_t acc[DC];
 #pragma unroll
@@ -113,9 +129,14 @@ __global__ __launch_bounds__(8 * TQ, (D == 64 ? 4 : 2) * TQ / 64) void dq_f32_ke
     const int sk = stage * STAGE, sv = sk + T::BYTES;
     const int rb0 = 2 * kh, kk = t * TK + 32 * kh;
     // live keys of the lane's row in the wave's two 16-key blocks
-    const uint32_t bits = lg_qsched_full(m, qs, t) ? 0xffu : row.bits(m, kk, h);
-    const bool on0 = __builtin_amdgcn_ballot_w64((bits & 0x0fu) != 0) != 0, on1 = __builtin_amdgcn_ballot_w64((bits & 0xf0u) != 0) != 0;
-    const bool masked = __builtin_amdgcn_ballot_w64(bits != 0xffu) != 0;
+    uint32_t bits = 0xffu;
+    bool on0 = true, on1 = true, masked = false;
+    if (!lg_qsched_full(m, qs, t)) {
+      bits = row.bits(m, kk, h);
+      on0 = __builtin_amdgcn_ballot_w64((bits & 0x0fu) != 0) != 0;
+      on1 = __builtin_amdgcn_ballot_w64((bits & 0xf0u) != 0) != 0;
+      masked = __builtin_amdgcn_ballot_w64(bits != 0xffu) != 0;
+    }
     // as in the forward: units of matrix instructions, their LDS operands requested one unit ahead
     auto run = [&](auto B0_, auto NB_) {
       constexpr int B0 = decltype(B0_)::value, NB = decltype(NB_)::value;
@@ -212,6 +233,16 @@ __global__ __launch_bounds__(8 * TQ, (D == 64 ? 4 : 2) * TQ / 64) void dq_f32_ke
     }
 }
 
+template <int D, int TQ>
+__global__ __launch_bounds__(8 * TQ, (D == 64 ? 4 : 2) * TQ / 64) void dq_f32_kernel(
+    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
+    const float* __restrict__ out, const float* __restrict__ dout, const float* __restrict__ lse,
+    float* __restrict__ delta, float* __restrict__ dq, int Hq, int Hkv, float scale, LgMask m, LgItems items,
+    unsigned* __restrict__ arrived, int ncounters) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[DQ_LDS<D>];
+  dq_f32_item<D, TQ, true>(smem, blockIdx.x, gridDim.x, q, k, v, out, dout, lse, delta, dq, Hq, Hkv, scale, m, items, arrived, ncounters);
+}
+
 // ---------------------------------------------------------------------- dk, dv
 // How the dk/dv work is cut (a function of the shape and the pattern alone, so that a sequence's results do not
 // depend on what else runs).
@@ -220,6 +251,7 @@ struct F32Parts {
   int nsp;    // window parts per key tile
   int ncand;  // leading key tiles that may hold column keys
   int ncc;    // column parts per such tile
+  int longest;  // steps of the longest part
   LgDiv heads, Hkv, dsp, dcc;  // divisions by the kv heads of the batch, of a sequence, by nsp and ncc
   size_t counters_off, part_off, end;  // workspace: Delta | arrival counters | partial dk, dv
 };
@@ -271,6 +303,8 @@ F32Parts f32_parts(const LgShape& sh, const LgMask& m) {
   long long ncc = (csteps + len - 1) / len;
   const int most = m.stride > 0 ? 8 : 64;
   p.ncc = p.ncand == 0 ? 0 : (int)(ncc < 1 ? 1 : ncc > most ? most : ncc);
+  p.longest = (int)((steps + p.nsp - 1) / p.nsp);
+  if (p.ncc > 0 && (csteps + p.ncc - 1) / p.ncc > p.longest) p.longest = (int)((csteps + p.ncc - 1) / p.ncc);
   const size_t rows = (((size_t)sh.B * sh.Hq * sh.N * sizeof(float)) + 255) & ~(size_t)255;
   const bool split = p.nsp > 1 || p.ncand > 0;
   const size_t heads = (size_t)sh.B * sh.Hkv;
@@ -286,25 +320,27 @@ F32Parts f32_parts(const LgShape& sh, const LgMask& m) {
 
 constexpr int BNT = 256;
 template <int D>
-__global__ __launch_bounds__(BNT, 2) void dkdv_f32_kernel(
-    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
+constexpr int DKDV_LDS = 2 * (2 * LgF32Tile<D, btq_of(D)>::BYTES + 1024);
+template <int D>
+__device__ __forceinline__ void dkdv_f32_item(
+    unsigned char* smem, int id, const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
     const float* __restrict__ dout, const float* __restrict__ lse, const float* __restrict__ delta,
-    float* __restrict__ dk, float* __restrict__ dv, int Hq, int Hkv, float scale, LgMask m, F32Parts pt, int heads,
+    float* __restrict__ dk, float* __restrict__ dv, int Hq, int Hkv, float scale, const LgMask& m, const F32Parts& pt, int heads,
     unsigned* __restrict__ arrived, float* __restrict__ part) {
   constexpr int TQ = btq_of(D), TK = LG_F32_KEYS, DC = D / 16, NB2 = TQ / 32;  // NB2: 16-row blocks of a wave
   using T = LgF32Tile<D, TQ>;
   using Dma = LgTileDma<T, BNT>;
   constexpr int OFF_G = T::BYTES, OFF_L = 2 * T::BYTES, STAGE = 2 * T::BYTES + 1024, LPT = 2 * Dma::CH;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * STAGE];
+  static_assert(DKDV_LDS<D> == 2 * STAGE, "two stages");
   __shared__ unsigned s_before;
 
   // work item: the column parts first (they are there for few tiles and as long as any), then the window parts
   const int G = Hq / Hkv, N = m.N;
   const int ncol = heads * pt.ncand * pt.ncc;
-  const bool column = (int)blockIdx.x < ncol;
+  const bool column = id < ncol;
   // heads innermost, first key tiles (the longest, where the window is) first
   int bh, pi, hk;
-  const int x = lg_divmod(pt.heads, column ? blockIdx.x : blockIdx.x - ncol, &bh);
+  const int x = lg_divmod(pt.heads, column ? id : id - ncol, &bh);
   const LgDiv np = column ? pt.dcc : pt.dsp;
   const int kt = lg_divmod(np, x, &pi), b = lg_divmod(pt.Hkv, bh, &hk);
   const int k0 = kt * TK, k1 = min(k0 + TK - 1, N - 1);
@@ -593,6 +629,56 @@ __global__ __launch_bounds__(BNT, 2) void dkdv_f32_kernel(
 }
 
 template <int D>
+__global__ __launch_bounds__(BNT, 2) void dkdv_f32_kernel(
+    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
+    const float* __restrict__ dout, const float* __restrict__ lse, const float* __restrict__ delta,
+    float* __restrict__ dk, float* __restrict__ dv, int Hq, int Hkv, float scale, LgMask m, F32Parts pt, int heads,
+    unsigned* __restrict__ arrived, float* __restrict__ part) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[DKDV_LDS<D>];
+  dkdv_f32_item<D>(smem, blockIdx.x, q, k, v, dout, lse, delta, dk, dv, Hq, Hkv, scale, m, pt, heads, arrived, part);
+}
+
+// Both in one launch (f32_both), the same bits.  Delta and the cleared arrival counters, which dk/dv needs from the start, come from
+// bwd_prep_f32_kernel, a wave for every 16 rows.
+template <int D>
+__global__ __launch_bounds__(256) void bwd_prep_f32_kernel(const float* __restrict__ out, const float* __restrict__ dout,
+                                                           float* __restrict__ delta, int N, int ld, int tiles,
+                                                           unsigned* __restrict__ arrived, int ncounters) {
+  for (long long x = (long long)blockIdx.x * 256 + threadIdx.x; x < ncounters; x += (long long)gridDim.x * 256) arrived[x] = 0u;
+  const int lane = threadIdx.x & 63, n = lane & 15, h = lane >> 4;
+  const int head = blockIdx.x / tiles, i = (blockIdx.x - head * tiles) * 64 + 16 * (threadIdx.x >> 6) + n;
+  const size_t row = ((size_t)head * ld + min(i, N - 1)) * D;
+  float4 gf[D / 16];
+#pragma unroll
+  for (int c = 0; c < D / 16; ++c) gf[c] = *reinterpret_cast<const float4*>(dout + row + 16 * c + 4 * h);
+  const float di = lg_delta_f32<D>(out + row, gf, n, h);
+  if (h == 0 && i < N) delta[(size_t)head * N + i] = di;
+}
+template <int D>
+__global__ __launch_bounds__(BNT, 2) void bwd_both_f32_kernel(
+    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v, const float* __restrict__ dout,
+    const float* __restrict__ lse, float* __restrict__ delta, float* __restrict__ dq, float* __restrict__ dk,
+    float* __restrict__ dv, int Hq, int Hkv, float scale, LgMask m, F32Parts pt, int heads, unsigned* __restrict__ arrived,
+    float* __restrict__ part, LgItems items, int nkv, int ndq, bool dq_first) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[DQ_LDS<D> > DKDV_LDS<D> ? DQ_LDS<D> : DKDV_LDS<D>];
+  // (ndq is a multiple of 8, so that dq's workgroups keep their XCDs)
+  const int id = dq_first ? (int)blockIdx.x : (int)blockIdx.x - ((nkv + 7) & ~7);
+  if (id >= 0 && id < ndq)
+    dq_f32_item<D, 32, false>(smem, id, 0, q, k, v, nullptr, dout, lse, delta, dq, Hq, Hkv, scale, m, items, nullptr, 0);
+  const int kv = dq_first ? (int)blockIdx.x - ndq : (int)blockIdx.x;
+  if (kv >= 0 && kv < nkv) dkdv_f32_item<D>(smem, kv, q, k, v, dout, lse, delta, dk, dv, Hq, Hkv, scale, m, pt, heads, arrived, part);
+}
+
+// Up to how many workgroups dq (32 rows each) and dk/dv share a launch.  One after the other they end twice with CUs idle, and a
+// sequence of a few hundred tokens has work for a fraction of them either way.  Backward in us, two launches : this, of 64: 2
+// heads, 510 tokens, causal 35 : 23, 4 x 4, 1036 101 : 56, 2, 3000 165 : 121, 2 x 8/4, 1024, window 128 45 : 41, 8, 2048 210 : 152,
+// 8/1, 3216, window 231 175 : 139, 4, 8000, window 300 129 : 126, 2 x 2/1, 5033, every 4th block 209 : 171; of 128: 1 head, 715
+// tokens, window 217 51 : 31, 8/1, 297 59 : 39, 2, 695, causal 76 : 50, 4, 1384, window 143 42 : 42.  One workgroup of head dim
+// 128 fills a CU's LDS (dk/dv alone: two): 4 x 4 heads, 502 tokens, 768 workgroups 77 : 83, 2 x 16/4, 578, 1408 94 : 100.  Which of
+// the two comes first: the one whose longest item takes longer, that is 3 : 2 in dq's tiles (2 heads of 64, 3000 tokens 176 with
+// dk/dv first; 8/2, 4096, window 512 169, dq first 214).
+constexpr long long f32_both(int D) { return D == 64 ? 4096 : 512; }
+template <int D>
 hipError_t launch_bwd(const float* q, const float* k, const float* v, const float* out, const float* lse,
                       const float* dout, float* dq, float* dk, float* dv, void* ws, const LgShape& sh,
                       const LgMask& m, hipStream_t s, hipEvent_t* ev) {
@@ -606,10 +692,31 @@ hipError_t launch_bwd(const float* q, const float* k, const float* v, const floa
   const long long tl = (long long)nqt * sh.Hq * sh.B;
   const long long items = (long long)heads * ((long long)pt.nkt * pt.nsp + (long long)pt.ncand * pt.ncc);
   if (tl > 0x7fffffffLL - 8 || items > 0x7fffffffLL || ncnt > 0x7fffffffLL) return hipErrorInvalidValue;
-  if (ev) {  // (nothing to set up on this path)
-    (void)hipEventRecord(ev[0], s);
-    (void)hipEventRecord(ev[1], s);
+  if (ev) (void)hipEventRecord(ev[0], s);
+  const int nqt32 = ceil_div(sh.N, 32);
+  const long long total32 = (long long)nqt32 * sh.Hq * sh.B;
+  if (total32 + items <= f32_both(D)) {
+    const int tiles = ceil_div(sh.N, 64);
+    bwd_prep_f32_kernel<D><<<dim3((unsigned)(tiles * sh.Hq * sh.B)), 256, 0, s>>>(out, dout, delta, sh.N, m.ld, tiles, arrived, (int)ncnt);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (ev) {
+      (void)hipEventRecord(ev[1], s);
+      (void)hipEventRecord(ev[2], s);  // (dq and dk/dv: one figure)
+    }
+    const int total = (int)total32, run = lg_run_length(m, total, sh.B * sh.Hkv, 8 * (sh.Hq / sh.Hkv), false);
+    const int nkv = (int)items, ndq = (int)lg_run_grid(total, run);
+    const long long reach = (long long)m.wb * m.b + m.sink + (m.stride > 0 ? sh.N / m.stride : 0);
+    const int tiles_dq = (int)((reach < sh.N ? reach : sh.N) / 64) + 1;
+    const bool dq_first = 2 * tiles_dq > 3 * pt.longest;
+    bwd_both_f32_kernel<D><<<dim3((unsigned)(((nkv + 7) & ~7) + ndq)), BNT, 0, s>>>(
+        q, k, v, dout, lse, delta, dq, dk, dv, sh.Hq, sh.Hkv, sh.scale, m, pt, heads, arrived, part,
+        lg_make_items(total, run, nqt32, sh.Hq, sh.Hkv, sh.D), nkv, ndq, dq_first);
+    e = hipGetLastError();
+    if (ev) (void)hipEventRecord(ev[3], s);
+    return e;
   }
+  if (ev) (void)hipEventRecord(ev[1], s);  // (nothing to set up)
   const int total = (int)tl, run = lg_run_length(m, total, sh.B * sh.Hkv, 256 / TQ * (sh.Hq / sh.Hkv), false);
   const auto kernel = TQ == 64 ? dq_f32_kernel<D, 64> : dq_f32_kernel<D, 32>;
   kernel<<<dim3((unsigned)lg_run_grid(total, run)), 8 * TQ, 0, s>>>(q, k, v, out, dout, lse, delta, dq, sh.Hq, sh.Hkv, sh.scale, m,

@@ -176,6 +176,32 @@ def test_float32_rows_do_not_depend_on_the_batch(Hq, Hkv, N, sink, window, block
             assert torch.equal(x[b:b + 1], y), (name, b)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,N,D,sink,window,block,stride", [
+    (17, 8, 4, 1030, 64, 4, 90, 1, 0), (9, 12, 12, 650, 64, 0, 650, 1, 0), (5, 4, 2, 700, 128, 16, 48, 16, 3)])
+def test_float32_backward_in_one_launch_and_in_two(B, Hq, Hkv, N, D, sink, window, block, stride):
+    """Up to 4096 (head dim 128: 512) workgroups dq and dk/dv share a launch, in either order: a batch on one side of the limit and
+    one of its sequences on the other give the same bits of dq, and dk and dv differ by float32 rounding at most (their parts are cut
+    by the batch: 2^-22 of the sum of magnitudes, taken as the tensor's largest value times 16)."""
+    gen = torch.Generator(device=DEV).manual_seed(15)
+    q, k, v, g = (torch.randn(B, h, N, D, generator=gen, device=DEV) for h in (Hq, Hkv, Hkv, Hq))
+
+    def run(*x):
+        n = x[0].shape[0]
+        out, lse, dq, dk, dv = torch.empty_like(x[0]), torch.empty(n, Hq, N, device=DEV), *(torch.full_like(y, float("nan")) for y in x[:3])
+        lg.lg_sparse_attn_fwd(*x[:3], out, lse, sink, window, block, stride)
+        need = lg.bwd_workspace_bytes(n, Hq, Hkv, N, D, sink, window, block, stride, lg.LG_F32)
+        ws = torch.full((need,), 255, dtype=torch.uint8, device=DEV)
+        lg.lg_sparse_attn_bwd(*x[:3], out, lse, x[3], dq, dk, dv, ws, sink, window, block, stride)
+        return dq, dk, dv
+
+    got = run(q, k, v, g)
+    for b in (0, B - 1):
+        one = run(*(t[b:b + 1].contiguous() for t in (q, k, v, g)))
+        assert torch.equal(got[0][b:b + 1], one[0])
+        for x, y in zip(got[1:], one[1:]):
+            assert float((x[b:b + 1] - y).abs().max()) <= 2.0 ** -18 * float(y.abs().max())
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_peaked_scores_and_custom_scale(dtype):
     check_bwd(1, 2, 2, 600, 128, 16, 100, dtype=dtype, seed=4, q_mul=4.0, by_tensor_max=True)
