@@ -616,6 +616,46 @@ LG_HD LgDecSegs lg_decode_segments(const LgMask& m) {
   return g;
 }
 
+// The same runs in places of their own (sink, ring, ring, retained blocks; those without keys in between are empty), so that a
+// kernel's copy stays in registers: start[] and pre[] as in LgDecSegs.  Returns the number of keys.
+LG_HD int lg_decode_runs(const LgMask& m, LgDecSegs& g) {
+  const int t = m.N - 1, qb = lg_div_b(m, t);
+  const int sinks = m.N < m.sink ? m.N : m.sink;
+  int s1 = m.sink, n1 = 0, s2 = m.sink, n2 = 0, s3 = 0, n3 = 0;
+  if (m.N > m.sink) {
+    const long long w0 = ((long long)qb - m.wb + 1) * m.b;  // first token of the oldest live window block
+    const int pl = w0 > m.sink ? (int)w0 : m.sink;          // first token read from the ring
+    const int len = t - pl + 1;
+    const int r0 = len >= m.window ? 0 : (pl - m.sink) % m.window;
+    n1 = len >= m.window ? m.window : len;
+    if (r0 + n1 > m.window) {  // the ring wraps
+      n2 = m.window - r0;
+      n1 -= n2;
+      s2 = m.sink + r0;
+    } else {
+      s1 = m.sink + r0;
+    }
+  }
+  if (m.stride > 0) {
+    const int x_lo = m.sb / m.stride;  // first retained block that is not a sink block
+    const int hi_kb = qb - m.wb;       // newest block older than the window
+    const int x_hi = hi_kb >= m.stride - 1 ? (hi_kb - (m.stride - 1)) / m.stride : -1;
+    s3 = m.sink + m.window + x_lo * m.b;
+    n3 = x_hi >= x_lo ? (x_hi - x_lo + 1) * m.b : 0;
+  }
+  g.n = 4;
+  g.start[0] = 0;
+  g.start[1] = s1;
+  g.start[2] = s2;
+  g.start[3] = s3;
+  g.pre[0] = 0;
+  g.pre[1] = sinks;
+  g.pre[2] = sinks + n1;
+  g.pre[3] = sinks + n1 + n2;
+  g.pre[4] = sinks + n1 + n2 + n3;
+  return g.pre[4];
+}
+
 // Slots a cache row needs for contexts of up to n_max tokens.
 LG_HD long long lg_cache_slots(int n_max, const LgMask& m) {
   const long long nb = ((long long)n_max + m.b - 1) / m.b;

@@ -2,6 +2,9 @@
 decode launch uses, exported as lg_debug_decode_segments) must name every live key of row N-1
 exactly once.  The cache contents come from the oracle's append, the live set from the oracle's
 predicate.  No GPU needed."""
+import os
+import subprocess
+
 import numpy as np
 import pytest
 
@@ -77,3 +80,39 @@ def test_paged_argument_checks():
                                 None) == INVALID   # T < 1
     assert L.lg_kv_paged_append(p, p, p, p, None, p, 2, 2, 128, 1, 400, 64, 192, 64, 8, 64, 8, 100, lg.LG_BF16,
                                 None) == NULL
+
+
+def test_runs_in_places_of_their_own_name_the_same_slots(tmp_path):
+    """lg_decode_runs (the paged kernel's) walks the slots of lg_decode_segments, in the same order, for every context length of
+    patterns of every form: sinks that are not full yet, rings that wrap, block mode, retained blocks in and beyond the window."""
+    src = tmp_path / "runs.cpp"
+    src.write_text(r"""
+#include <stdio.h>
+#include "lg_mask.h"
+int main() {
+  const int P[][4] = {{0, 9, 1, 0}, {16, 40, 1, 0}, {4, 33, 1, 5}, {0, 16, 1, 1}, {3, 8, 1, 4}, {16, 32, 16, 0}, {16, 48, 16, 3}, {48, 96, 48, 2},
+                      {64, 128, 64, 4}, {0, 64, 64, 2}, {6, 18, 6, 7}, {128, 64, 64, 1}, {0, 1, 1, 0}, {128, 64, 64, 2}};
+  for (auto& p : P)
+    for (int N = 1; N <= 900; ++N) {
+      const LgMask m = lg_make_cache_mask(N, p[0], p[1], p[2], p[3]);
+      const LgDecSegs a = lg_decode_segments(m);
+      LgDecSegs b;
+      const int keys = lg_decode_runs(m, b);
+      auto slot = [](const LgDecSegs& g, int x) {  // as the kernels do
+        int shift = g.start[0];
+        for (int r = 1; r < 4; ++r)
+          if (x >= g.pre[r]) shift = g.start[r] - g.pre[r];
+        return x + shift;
+      };
+      bool same = keys == a.pre[a.n];
+      for (int x = 0; same && x < keys; ++x) same = slot(a, x) == slot(b, x);
+      if (!same) { printf("sink %d window %d block %d stride %d N %d\n", p[0], p[1], p[2], p[3], N); return 1; }
+    }
+  return 0;
+}
+""")
+    exe = tmp_path / "runs"
+    csrc = os.path.join(os.path.dirname(os.path.abspath(lg.__file__)), "csrc")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-I", csrc, str(src), "-o", str(exe)], check=True, timeout=120)
+    got = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert got.returncode == 0, got.stdout
