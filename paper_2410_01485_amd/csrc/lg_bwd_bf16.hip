@@ -196,38 +196,25 @@ template <int D>
 struct LgDqTune {
   static constexpr int WAVES = D == 128 ? 2 : 3, AHEAD = D == 128 ? 3 : 2;
 };
+// A work item, 128 rows.  FORM: forms Delta; otherwise the set-up kernel has (launches that dq shares with dk/dv).  PAIR: of the
+// eight waves four have half 0 of a 256-row tile and four half 1, with LDS of their own and the same barriers.
 template <int D>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LgDqTune<D>::WAVES, LgDqTune<D>::WAVES))) void
-dq_bf16_kernel(
-    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-    const uint16_t* __restrict__ out, const uint16_t* __restrict__ dout, const float* __restrict__ lse,
-    float* __restrict__ ndelta, float* __restrict__ nlse, uint16_t* __restrict__ dq, int Hq, int Hkv, float scale,
-    LgMask m_in, int nqt, int total, LgRuns runs, LgBwdWork wk) {
-  LgMask m = m_in;
+constexpr int DQ_LDS = 4 * LgSwzTile<D>::BYTES;
+template <int D, bool FORM, bool PAIR>
+__device__ __forceinline__ void dq_bf16_item(
+    unsigned char* smem, float (*s_rows)[LG_BF16_TQ32], const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+    const uint16_t* __restrict__ v, const uint16_t* __restrict__ out, const uint16_t* __restrict__ dout,
+    const float* __restrict__ lse, float* __restrict__ ndelta, float* __restrict__ nlse, uint16_t* __restrict__ dq, int Hq, int Hkv,
+    float scale, LgMask m, const LgBwdWork& wk, int b, int hk, int hq, int qt, int half, int x) {
   using T = LgSwzTile<D>;
   constexpr int NT = 256;
   using Dma = LgDma<D, NT>;
   constexpr int TQ = LG_BF16_TQ32, TK = LG_BF16_TK;
   static_assert(LG_BF16_TQ == 2 * TQ && TK == 64, "4 waves x 32 query rows, 64-key tiles");
+  static_assert(!(FORM && PAIR), "a pair finds Delta formed");
   constexpr int DC = D / 16, DB = D / 32;
   constexpr int STAGE = 2 * T::BYTES;  // K tile + V tile
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * STAGE];
-  __shared__ float s_rows[2][TQ];  // Delta, log-sum-exp
-
-  const int L = lg_item_of(blockIdx.x, runs);
-  if (L < 0 || L >= total) return;
-  // logical order: (b, kv head) slowest, then query tile (longest rows first), then the query
-  // heads of the GQA group: the G workgroups that walk the same K/V tiles run side by side
-  const int G = Hq / Hkv;
-  const int gq = L % G, rest = L / G;
-  // (nqt, qtile0: in LG_BF16_TQ rows, two workgroups each)
-  const int at = lg_order_at(wk.order, rest);
-  int bhk = (at >> 1) / nqt, y = at - bhk * 2 * nqt;
-  lg_in_order(wk.order, rest, 2 * nqt, &bhk, &y);
-  const int half = 1 - (y & 1), x = y >> 1;
-  int qt = nqt - 1 - x;
-  const int b = bhk / Hkv, hk = bhk % Hkv;
-  const int hq = hk * G + gq;
+  static_assert(DQ_LDS<D> == 2 * STAGE, "two stages");
   int srow = 0, swrow = 0;  // packed: first row of the sequence inside its head, in the workspace
   if (wk.seqs) {
     const int t = wk.qt_first + x;
@@ -238,10 +225,11 @@ dq_bf16_kernel(
     m = lg_mask_for_length(m, lg_uniform(wk.seqs->len[sq]));
   }
   const int N = m.N;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = PAIR ? threadIdx.x & 255 : threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n = lane & 31, g = lane >> 5;
   const int q0 = (2 * qt + half) * TQ, q1 = min(q0 + TQ - 1, N - 1);
-  if (q0 >= N) return;
+  if (!PAIR && q0 >= N) return;
+  const int base = PAIR ? half * DQ_LDS<D> : 0;  // of this item's LDS
   const size_t row0 = (size_t)(b * Hq + hq) * m.ld + srow;       // the sequence's first row in this query head
   const size_t wrow0 = (size_t)(b * Hq + hq) * wk.wld + swrow;   // the same in the workspace
   const size_t qbase = row0 * D;
@@ -263,7 +251,7 @@ dq_bf16_kernel(
   dma.init(tid);
   LgSwzReader<D> rd;
   rd.init(n, g);
-  const uint32_t lds0 = (uint32_t)(uintptr_t)LG_LDS_PTR(unsigned char, smem);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)LG_LDS_PTR(unsigned char, smem) + base;
   const LgQSched qs = lg_qsched_init(m, q0, q1);
   const LgRows wrows = lg_rows(m, qw0, qw1);
   auto issue = [&](int t, int stage) {
@@ -274,10 +262,15 @@ dq_bf16_kernel(
 
   // patterns without strided columns walk the window run rotated (L2 sharing between neighbours)
   const LgQWalk qw = lg_qwalk_init(qs);
-  auto next_tile = [&](int prev) -> int {
+  auto walk = [&](const LgQSched& qs, const LgQWalk& qw, int prev) -> int {
     if (m.stride == 0) return prev < 0 ? lg_qwalk_first(qw) : lg_qwalk_next(qw, prev);
     return lg_qsched_next(m, qs, prev);
   };
+  auto next_tile = [&](int prev) -> int { return walk(qs, qw, prev); };
+  // the other half's walk: barriers as long as either has tiles
+  const int o0 = (2 * qt + 1 - half) * TQ;
+  const LgQSched qs_o = PAIR ? lg_qsched_init(m, min(o0, N - 1), min(o0 + TQ - 1, N - 1)) : qs;
+  const LgQWalk qw_o = PAIR ? lg_qwalk_init(qs_o) : qw;
   // Q and dO rows through the two stages' places into registers, out and the log-sum-exp once per row
 #pragma unroll
   for (int y = 0; y < 2; ++y)
@@ -287,8 +280,14 @@ dq_bf16_kernel(
       dma.issue((y ? q : dout) + qbase + (size_t)rc * D, N - rc, lds0 + y * STAGE + x * T::BYTES);
     }
   const int my_row = min(q0 + (tid & (TQ - 1)), N - 1);
-  const float my_lse = lse[row0 + my_row];
-  {
+  const float my_lse = lse[row0 + (FORM ? my_row : iq)];
+  float di = 0.f, lse2 = 0.f;
+  if constexpr (!FORM) {
+    di = -ndelta[wrow0 + iq];
+    lse2 = my_lse * LOG2E;
+    LG_WAIT_VMCNT(0);
+    __syncthreads();
+  } else {
     uint4 o[TQ * D / 2048];
     lg_load_pieces<D, TQ>(out + qbase + (size_t)q0 * D, N - 1 - q0, o);
     LG_WAIT_VMCNT(0);
@@ -299,28 +298,35 @@ dq_bf16_kernel(
   bf16x8_t qf[DC], gf[DC];
 #pragma unroll
   for (int dc = 0; dc < DC; ++dc) {
-    gf[dc] = rd.read_rows(smem, (wave_s >> 1) * T::BYTES, wave_s & 1, dc);
-    qf[dc] = rd.read_rows(smem, STAGE + (wave_s >> 1) * T::BYTES, wave_s & 1, dc);
+    gf[dc] = rd.read_rows(smem, base + (wave_s >> 1) * T::BYTES, wave_s & 1, dc);
+    qf[dc] = rd.read_rows(smem, base + STAGE + (wave_s >> 1) * T::BYTES, wave_s & 1, dc);
   }
   // Touch everything loaded so far, so that the compiler's waits for these loads sit here and
   // not inside the tile loop (where they would drain the direct loads kept in flight).
 #pragma unroll
   for (int dc = 0; dc < DC; ++dc) asm volatile("" ::"v"(qf[dc]), "v"(gf[dc]));
   __syncthreads();
-  int t = next_tile(-1);
-  issue(t, 0);
+  int t = !PAIR || q0 < N ? next_tile(-1) : -1, t_o = PAIR && o0 < N ? walk(qs_o, qw_o, -1) : -1;
+  if (!PAIR || t >= 0) issue(t, 0);
   const float sl2 = scale * LOG2E;
-  float di = s_rows[0][wave * 32 + n], lse2 = s_rows[1][wave * 32 + n] * LOG2E;
-  if (tid < TQ && q0 + tid < N) {
-    ndelta[wrow0 + q0 + tid] = -s_rows[0][tid];
-    nlse[wrow0 + q0 + tid] = -my_lse / scale;
+  if constexpr (FORM) {
+    di = s_rows[0][wave * 32 + n];
+    lse2 = s_rows[1][wave * 32 + n] * LOG2E;
+    if (tid < TQ && q0 + tid < N) {
+      ndelta[wrow0 + q0 + tid] = -s_rows[0][tid];
+      nlse[wrow0 + q0 + tid] = -my_lse / scale;
+    }
   }
   asm volatile("" : "+v"(lse2), "+v"(di));
 
   int stage = 0;
-  while (t >= 0) {
+  while (t >= 0 || (PAIR && t_o >= 0)) {
     LG_WAIT_VMCNT(0);
     __syncthreads();  // tile t landed for everyone; everyone is done with the one before
+    if (PAIR) {
+      if (t_o >= 0) t_o = walk(qs_o, qw_o, t_o);
+      if (t < 0) continue;
+    }
     const int t_next = next_tile(t);
     const int k0 = t * TK;
     // A tile that is not live throughout for the workgroup's 128 rows is classified again for
@@ -334,7 +340,7 @@ dq_bf16_kernel(
     // 470, 285 -> 279, 100.7 -> 96.8).
     const bool between = full && t_next >= 0 && N - t_next * TK >= TK;
     if (t_next >= 0 && !between) issue(t_next, stage ^ 1);
-    const int sk = stage * STAGE, sv = sk + T::BYTES;
+    const int sk = base + stage * STAGE, sv = sk + T::BYTES;
     const uint32_t bits = full ? ~0u : lg_key_bits(m, iq, k0, g);  // bit 16 kb + r: the key of register r of block kb is live
 
     if (kind != LG_TILE_DEAD)
@@ -387,7 +393,7 @@ dq_bf16_kernel(
   }
 
   // (everyone is done with the stage before the last tile's)
-  unsigned char* rows = smem + stage * STAGE + wave_s * (32 * T::ROW_BYTES);
+  unsigned char* rows = smem + base + stage * STAGE + wave_s * (32 * T::ROW_BYTES);
 #pragma unroll
   for (int db = 0; db < DB; ++db) {
     float a[16];
@@ -396,6 +402,31 @@ dq_bf16_kernel(
     lg_rows_put<D>(rows, lane, db, a, scale);
   }
   lg_rows_write<D>(rows, lane, dq + qbase + (size_t)(q0 + wave_s * 32) * D, N - (q0 + wave_s * 32));
+}
+template <int D>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(LgDqTune<D>::WAVES, LgDqTune<D>::WAVES))) void
+dq_bf16_kernel(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+    const uint16_t* __restrict__ out, const uint16_t* __restrict__ dout, const float* __restrict__ lse,
+    float* __restrict__ ndelta, float* __restrict__ nlse, uint16_t* __restrict__ dq, int Hq, int Hkv, float scale,
+    LgMask m, int nqt, int total, LgRuns runs, LgBwdWork wk) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[DQ_LDS<D>];
+  __shared__ float s_rows[2][LG_BF16_TQ32];  // Delta, log-sum-exp
+
+  const int L = lg_item_of(blockIdx.x, runs);
+  if (L < 0 || L >= total) return;
+  // logical order: (b, kv head) slowest, then query tile (longest rows first), then the query
+  // heads of the GQA group: the G workgroups that walk the same K/V tiles run side by side
+  const int G = Hq / Hkv;
+  const int gq = L % G, rest = L / G;
+  // (nqt, qtile0: in LG_BF16_TQ rows, two workgroups each)
+  const int at = lg_order_at(wk.order, rest);
+  int bhk = (at >> 1) / nqt, y = at - bhk * 2 * nqt;
+  lg_in_order(wk.order, rest, 2 * nqt, &bhk, &y);
+  const int half = 1 - (y & 1), x = y >> 1;
+  const int b = bhk / Hkv, hk = bhk % Hkv;
+  dq_bf16_item<D, true, false>(smem, s_rows, q, k, v, out, dout, lse, ndelta, nlse, dq, Hq, Hkv, scale, m, wk, b, hk, hk * G + gq,
+                               nqt - 1 - x, half, x);
 }
 
 // ---------------------------------------------------------------------- dk, dv
@@ -445,16 +476,73 @@ __device__ void column_table(int* __restrict__ col_of_group, int* __restrict__ c
   }
 }
 
+// What dq leaves for dk/dv, -Delta and -lse / scale, formed by workgroups of the set-up kernel where both share a launch: a
+// workgroup per 64 rows of a sequence and query head, a row by 8 or 16 lanes as in lg_delta_rows, the same bits.
+struct LgBwdDelta {
+  int first, chunks;  // first workgroup (none: past the grid); 64-row chunks of all sequences
+  int D, ld, wld;
+  const uint16_t *out, *dout;
+  const float* lse;
+  float *ndelta, *nlse;
+  float scale;
+};
+template <int D>
+__device__ __forceinline__ void delta_rows(const LgBwdDelta& d, const LgBwdSetup& a, int N, int id) {
+  constexpr int CPR = D / 8, RPP = SETUP_NT / CPR;
+  const int tid = threadIdx.x, lane = tid & 63, head = id / d.chunks;
+  int chunk = id - head * d.chunks, row0 = 0, wrow0 = 0;
+  if (a.n > 0) {  // the sequence that has the chunk, by sums over the lanes
+    int chunks = 0, rows = 0, found = -1;
+    for (int x0 = 0; x0 < a.n && found < 0; x0 += 64) {
+      const int len = x0 + lane < a.n ? a.len[x0 + lane] : 0;
+      int c = (len + 63) / 64, r = len;
+      for (int y = 1; y < 64; y <<= 1) {
+        const int cu = __shfl_up(c, y), ru = __shfl_up(r, y);
+        c += lane >= y ? cu : 0;
+        r += lane >= y ? ru : 0;
+      }
+      const unsigned long long past = __builtin_amdgcn_ballot_w64(chunks + c > chunk);
+      if (past != 0) {
+        const int at = __builtin_ctzll(past);
+        found = x0 + at;
+        N = a.len[found];
+        row0 = a.row0[found];
+        wrow0 = rows + lg_uniform(__shfl(r, at)) - N;
+        chunk -= chunks + lg_uniform(__shfl(c, at)) - (N + 63) / 64;
+      }
+      chunks += lg_uniform(__shfl(c, 63));
+      rows += lg_uniform(__shfl(r, 63));
+    }
+  }
+#pragma unroll
+  for (int x = 0; x < 64 / RPP; ++x) {
+    const int i = chunk * 64 + x * RPP + tid / CPR;
+    const size_t row = (size_t)head * d.ld + row0 + min(i, N - 1);
+    const size_t at = row * D + tid % CPR * 8;
+    const uint4 g = *reinterpret_cast<const uint4*>(d.dout + at), o = *reinterpret_cast<const uint4*>(d.out + at);
+    const float s = lg_group_sum<CPR>(lg_dot8(g, o, 0.f));
+    if (tid % CPR == 0 && i < N) {
+      d.ndelta[(size_t)head * d.wld + wrow0 + i] = -s;
+      d.nlse[(size_t)head * d.wld + wrow0 + i] = -d.lse[row] / d.scale;
+    }
+  }
+}
+
 // Grid: one workgroup for the counters, the descriptor and the items, one per sequence (batch: one) for its column
-// table, the others clear the partial sums.
+// table, others clear the partial sums, the last ones form Delta (where dq does not).
 __global__ __launch_bounds__(SETUP_NT) void bwd_setup_kernel(LgBwdSetup a, LgMask m, int* __restrict__ queue,
                                                              LgBwdSeqs* __restrict__ seqs, int* __restrict__ items,
                                                              int* __restrict__ col_of_group, int* __restrict__ col_list,
                                                              int ncol, unsigned* __restrict__ arrived, int narrived,
-                                                             float* __restrict__ part, size_t part_floats) {
+                                                             float* __restrict__ part, size_t part_floats, LgBwdDelta delta) {
   const int tid = threadIdx.x, nt = a.n > 0 ? a.n : 1;
+  if ((int)blockIdx.x >= delta.first) {
+    if (delta.D == 64) delta_rows<64>(delta, a, m.N, blockIdx.x - delta.first);
+    else delta_rows<128>(delta, a, m.N, blockIdx.x - delta.first);
+    return;
+  }
   if ((int)blockIdx.x > nt) {  // (device-scope stores: atomics of every XCD add to these values)
-    const size_t step = (size_t)(gridDim.x - 1 - nt) * SETUP_NT;
+    const size_t step = (size_t)(delta.first - 1 - nt) * SETUP_NT;
     for (size_t x = (size_t)(blockIdx.x - 1 - nt) * SETUP_NT + tid; x < part_floats / 2; x += step)
       lg_store_shared2(part + 2 * x, 0.f, 0.f);
     return;
@@ -672,13 +760,15 @@ __device__ __forceinline__ void lg_dkdv_block(const unsigned char* smem, const L
   }
 }
 
+template <int D>
+constexpr int DKDV_LDS = btk_of(D) / 64 * LgSwzTile<D>::BYTES + 2 * (2 * LgSwzTile<D>::BYTES + 1024);
 template <int D, bool COLUMN>
-__global__ __launch_bounds__(btk_of(D) * 2) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 3, D == 128 ? 2 : 3))) void
-dkdv_bf16_kernel(
+__device__ __forceinline__ void dkdv_bf16_item(
+    unsigned char* smem, int bid,
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const uint16_t* __restrict__ dout, const float* __restrict__ nlse, const float* __restrict__ ndelta,
     uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int Hq, int Hkv, float scale, LgMask m_in,
-    int nkt, int total, int run, LgBwdWork wk) {
+    int nkt, int total, int run, const LgBwdWork& wk) {
   LgMask m = m_in;
   using T = LgSwzTile<D>;
   constexpr int TQ = LG_BF16_BTQ, TK = btk_of(D), NT = 2 * TK, NG = TK / 64;
@@ -689,7 +779,7 @@ dkdv_bf16_kernel(
   constexpr int VRES = NG * T::BYTES;                // the workgroup's V rows
   constexpr int OFF_G = T::BYTES, OFF_L = 2 * T::BYTES;
   constexpr int STAGE = 2 * T::BYTES + 1024;         // Q tile, dO tile, -lse / scale | -Delta (2 x 64 floats)
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[VRES + 2 * STAGE];
+  static_assert(DKDV_LDS<D> == VRES + 2 * STAGE, "V rows and two stages");
 
   const int G = Hq / Hkv;
   const float sl2 = scale * LOG2E;
@@ -707,7 +797,7 @@ dkdv_bf16_kernel(
   LgBwdMain w = {0, 0, 0};
   if (COLUMN) {
     const int nh = wk.B * Hq;
-    int x = blockIdx.x;
+    int x = bid;
     const int hd = x % nh;
     x /= nh;
     if (wk.seqs) {
@@ -720,7 +810,7 @@ dkdv_bf16_kernel(
     chunk = x / nvt;
     gq = hd % G;
     w.bh = hd / G;
-  } else if (!lg_bwd_main(wk, blockIdx.x, nkt, total, run, m, it, w)) {
+  } else if (!lg_bwd_main(wk, bid, nkt, total, run, m, it, w)) {
     return;
   }
   const int bh = w.bh, kt = w.kt;
@@ -928,6 +1018,41 @@ dkdv_bf16_kernel(
     }
     lg_rows_write<D>(rows, lane, (which ? dv : dk) + kbase + (size_t)kw0 * D, N - kw0);
   }
+}
+template <int D, bool COLUMN>
+__global__ __launch_bounds__(btk_of(D) * 2) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 3, D == 128 ? 2 : 3))) void
+dkdv_bf16_kernel(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+    const uint16_t* __restrict__ dout, const float* __restrict__ nlse, const float* __restrict__ ndelta,
+    uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int Hq, int Hkv, float scale, LgMask m_in,
+    int nkt, int total, int run, LgBwdWork wk) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[DKDV_LDS<D>];
+  dkdv_bf16_item<D, COLUMN>(smem, blockIdx.x, q, k, v, dout, nlse, ndelta, dk, dv, Hq, Hkv, scale, m_in, nkt, total, run, wk);
+}
+
+// dq and dk/dv in one launch, where neither fills the GPU (rule: bwd_both): the set-up kernel has formed Delta, and every work item does
+// what it does in a launch of its own, with the same bits.  Head dim 128: dq's items two by two, for as many waves as dk/dv has.
+template <int D>
+__global__ __launch_bounds__(btk_of(D) * 2) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 3, D == 128 ? 2 : 3))) void
+bwd_both_bf16_kernel(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+    const uint16_t* __restrict__ dout, const float* __restrict__ lse, float* __restrict__ nlse, float* __restrict__ ndelta,
+    uint16_t* __restrict__ dq, uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int Hq, int Hkv, float scale, LgMask m,
+    int nkt, int total, int run, LgBwdWork wk, int nqt, int nkv, int ndq, bool dq_first) {
+  constexpr bool PAIR = D == 128;
+  constexpr int DQ = (PAIR ? 2 : 1) * DQ_LDS<D>;
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[DQ > DKDV_LDS<D> ? DQ : DKDV_LDS<D>];
+  const int id = dq_first ? (int)blockIdx.x : (int)blockIdx.x - nkv;
+  if (id >= 0 && id < ndq) {  // heads innermost, longest rows first
+    const int nh = wk.B * Hq, hd = id % nh, y = id / nh, x = PAIR ? y : y >> 1;
+    const int half = PAIR ? lg_uniform(threadIdx.x >> 8) : 1 - (y & 1);
+    const int b = hd / Hq, hq = hd - b * Hq;
+    dq_bf16_item<D, false, PAIR>(smem, nullptr, q, k, v, nullptr, dout, lse, ndelta, nlse, dq, Hq, Hkv, scale, m, wk, b, hq / (Hq / Hkv), hq,
+                                 nqt - 1 - x, half, x);
+    return;
+  }
+  const int kv = dq_first ? (int)blockIdx.x - ndq : (int)blockIdx.x;
+  dkdv_bf16_item<D, false>(smem, kv, q, k, v, dout, nlse, ndelta, dk, dv, Hq, Hkv, scale, m, nkt, total, run, wk);
 }
 
 // --------------------------------------------------------- dk, dv: the column part of a lone group
@@ -2016,9 +2141,38 @@ struct BwdLaunch {
   int chunk, citems;      // column work items of a query head where there are several groups, and their query tiles
 };
 
+// dq and dk/dv share a launch (bwd_both_bf16_kernel) up to so many workgroups, where no sequence takes the 64-rows form of dq; dk/dv
+// then takes its 32-keys form, which gives the same bits as the other.  One after the other both end with CUs idle, and a few
+// heads of a few thousand tokens have workgroups for a part of the CUs either way.  Backward in us, launches of their own :
+// this, of 64: 16 heads, 1117 tokens, causal 52 : 31, 8/4, 8 packed of up to 2186 89 : 62, 4 x 16, 997 58 : 46, 16/8, 1111, window
+// 128 50 : 44, 2 x 64/16, 7479, window 200 (9568 workgroups) 437 : 434; of 128: 8, 3249, causal 224 : 150, 4 x 8, 1111 97 : 63, 16/8,
+// 30 packed of up to 775 194 : 87, 1, 1098, causal 91 : 57, 16, 3707, window 186 93 : 90, 2 x 16/8, 8639, window 124 (1632) 254 : 241;
+// 8, 30 packed of up to 3991, window 704 (1952) 317 : 323, 32/16, 30 of up to 3428, window 448 (5952) 992 : 1065.
+int both_dq_items(const BwdLaunch& a) { return (a.D == 128 ? 1 : 2) * a.qt_rest * a.Hq * a.B; }
+bool bwd_both(const BwdLaunch& a) {
+  const long long kv = (long long)(a.kt_wide + a.kt_rest) * a.Hkv * a.B * a.cut.heads * a.cut.rows;
+  return a.qt_wide == 0 && both_dq_items(a) + kv <= (a.D == 64 ? 8192 : 1536);
+}
+// Whether dq's items come first: those that take longer, by the products of a wave in a tile (3) and a step (4).  8/4 heads of 64, 8
+// packed of up to 2186 tokens, causal, dq first 62, dk/dv first 68; 32/16, 8 of up to 1285, window 813 119, 94.
+bool both_dq_first(const BwdLaunch& a) {
+  const LgMask& m = a.m;
+  const int N = a.setup.n > 0 ? a.setup.len[0] : m.N;  // (the longest)
+  const long long reach = (long long)m.wb * m.b, cols = m.sink + (m.stride > 0 ? N / m.stride : 0);
+  const int tiles = (int)(std::min<long long>(N, reach + cols) / 64) + 1;
+  const int steps = (int)(std::min<long long>(N, reach + btk_of(a.D)) / 64) + 1;
+  return 3 * tiles > 4 * ((steps + a.cut.rows - 1) / a.cut.rows) * (a.Hq / a.Hkv / a.cut.heads);
+}
+
 hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv, const uint16_t* uo, const float* lse,
-                      const uint16_t* ug, uint16_t* dq, uint16_t* dk, uint16_t* dv, void* ws, const BwdLaunch& a,
+                      const uint16_t* ug, uint16_t* dq, uint16_t* dk, uint16_t* dv, void* ws, const BwdLaunch& in,
                       hipStream_t s, hipEvent_t* ev) {
+  BwdLaunch a = in;
+  const bool both = bwd_both(a);
+  if (both) {
+    a.kt_rest += a.kt_wide;
+    a.kt_wide = a.setup.nwide = 0;
+  }
   const LgMask& m = a.m;
   const int Hq = a.Hq, Hkv = a.Hkv, nbh = Hkv * a.B, ncol = (int)a.size.ncol, nlone = (int)a.size.lone;
   const float scale = a.scale;
@@ -2052,9 +2206,12 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
   // sums that atomics add to: all but those of lone groups with Hq == Hkv
   const size_t part_floats = a.citems > 0 || Hq != Hkv ? (l.lonepart - l.colpart) / sizeof(float) : 0;
   const size_t fill_wgs = (part_floats / 2 + 4 * SETUP_NT - 1) / (4 * SETUP_NT);
-  bwd_setup_kernel<<<dim3((unsigned)(1 + (packed ? a.setup.n : 1) + (fill_wgs < 1024 ? fill_wgs : 1024))), SETUP_NT, 0,
+  LgBwdDelta delta = {(int)(1 + (packed ? a.setup.n : 1) + (fill_wgs < 1024 ? fill_wgs : 1024)), 0, a.D, m.ld, (int)(packed ? a.size.rows : m.N),
+                      uo, ug, lse, ndelta, nlse, scale};
+  for (int x = 0; x < (packed ? a.setup.n : 1); ++x) delta.chunks += ((packed ? a.setup.len[x] : m.N) + 63) / 64;
+  bwd_setup_kernel<<<dim3((unsigned)(delta.first + (both ? delta.chunks * Hq * a.B : 0))), SETUP_NT, 0,
                      s>>>(a.setup, m, queue, seqs, items, col_of_group, col_list, ncol, arrived,
-                          nlone > 0 ? nbh * (int)a.size.seqs : 0, colpart, part_floats);
+                          nlone > 0 ? nbh * (int)a.size.seqs : 0, colpart, part_floats, delta);
   if (ev) (void)hipEventRecord(ev[1], s);
 
   LgBwdWork wk;
@@ -2090,7 +2247,7 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
       dq_wide_bf16_kernel<false><<<grid, 256, 0, s>>>(uq, uk, uv, uo, ug, lse, ndelta, nlse, dq, Hq, Hkv, scale, m,
                                                       a.qt_wide, total, run, wk, queue, nitems);
   }
-  if (a.qt_rest > 0) {
+  if (a.qt_rest > 0 && !both) {
     const int total = 2 * a.qt_rest * Hq * a.B;
     const LgRuns runs = lg_runs(m, nbh, 2 * a.qt_rest, Hq / Hkv, packed);
     const dim3 grid((unsigned)lg_run_grid(runs, total));
@@ -2142,7 +2299,15 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
     const dim3 grid((unsigned)(wk.by_tile ? total * nparts : (int)lg_run_grid(total, run)));
     wk.items = items + a.kt_wide;
     wk.order = lg_order(nbh, nkt, 1, a.D);
-    if (a.D == 64) LG_DKDV_LAUNCH(64, false, grid);
+    if (both) {
+      const int ndq = both_dq_items(a), nkv = (int)grid.x;
+#define LG_BOTH_LAUNCH(DD)                                                                                                  \
+  bwd_both_bf16_kernel<DD><<<dim3((unsigned)(nkv + ndq)), 2 * btk_of(DD), 0, s>>>(uq, uk, uv, ug, lse, nlse, ndelta, dq, dk, dv, Hq, Hkv, \
+                                                                                  scale, m, nkt, total, run, wk, a.qt_rest, nkv, ndq, both_dq_first(a))
+      if (a.D == 64) LG_BOTH_LAUNCH(64);
+      else LG_BOTH_LAUNCH(128);
+#undef LG_BOTH_LAUNCH
+    } else if (a.D == 64) LG_DKDV_LAUNCH(64, false, grid);
     else LG_DKDV_LAUNCH(128, false, grid);
   }
 #undef LG_DKDV_LAUNCH
