@@ -202,6 +202,47 @@ def test_float32_backward_in_one_launch_and_in_two(B, Hq, Hkv, N, D, sink, windo
             assert float((x[b:b + 1] - y).abs().max()) <= 2.0 ** -18 * float(y.abs().max())
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,N,D,sink,window,block,stride", [
+    (60, 8, 8, 1030, 64, 4, 90, 1, 0), (22, 8, 8, 1030, 128, 0, 300, 1, 0), (22, 8, 2, 1030, 128, 64, 300, 1, 0), (60, 8, 4, 1150, 64, 64, 192, 64, 4),
+    (50, 16, 16, 129, 128, 0, 129, 1, 0)])
+def test_bf16_backward_in_one_launch_and_in_two(B, Hq, Hkv, N, D, sink, window, block, stride):
+    """Up to 8192 (head dim 128: 1536) workgroups dq and dk/dv share a launch: a batch beyond that and one of its sequences alone and
+    packed give the same bits of dq, without groups of query heads and columns of dk and dv as well; otherwise these are sums in
+    another order, and a bf16 rounding apart at most (2^-7 of a value; 2^-16 of the tensor's largest where terms cancel)."""
+    gen = torch.Generator(device=DEV).manual_seed(16)
+    q, k, v, g = (torch.randn(B, h, N, D, generator=gen, device=DEV, dtype=torch.bfloat16) for h in (Hq, Hkv, Hkv, Hq))
+    pat = (sink, window, block, stride)
+
+    def run(*x):
+        n = x[0].shape[0]
+        out, lse, dq, dk, dv = torch.empty_like(x[0]), torch.empty(n, Hq, N, device=DEV), *(torch.full_like(y, float("nan")) for y in x[:3])
+        lg.lg_sparse_attn_fwd(*x[:3], out, lse, *pat)
+        ws = torch.full((lg.bwd_workspace_bytes(n, Hq, Hkv, N, D, *pat, lg.LG_BF16),), 255, dtype=torch.uint8, device=DEV)
+        lg.lg_sparse_attn_bwd(*x[:3], out, lse, x[3], dq, dk, dv, ws, *pat)
+        return dq, dk, dv
+
+    def run_packed(*x):  # the sequence and its first 70 rows
+        x = [torch.cat([y[0], y[0, :, :70]], dim=1).contiguous() for y in x]
+        cu = [0, N, N + 70]
+        out, lse, dq, dk, dv = torch.empty_like(x[0]), torch.empty(Hq, N + 70, device=DEV), *(torch.full_like(y, float("nan")) for y in x[:3])
+        lg.lg_sparse_attn_fwd_varlen(*x[:3], out, lse, cu, *pat)
+        ws = torch.full((lg.bwd_varlen_workspace_bytes(cu, Hq, Hkv, D, *pat, lg.LG_BF16),), 255, dtype=torch.uint8, device=DEV)
+        lg.lg_sparse_attn_bwd_varlen(*x[:3], out, lse, x[3], dq, dk, dv, ws, cu, *pat)
+        return tuple(y[None, :, :N] for y in (dq, dk, dv))
+
+    got = run(q, k, v, g)
+    for b in (0, B - 1):
+        for f in (run, run_packed):
+            one = f(*(t[b:b + 1].contiguous() for t in (q, k, v, g)))
+            assert torch.equal(got[0][b:b + 1], one[0]), (b, f)
+            for x, y in zip(got[1:], one[1:]):
+                x, y = x[b:b + 1].float(), y.float()
+                if Hq == Hkv and stride == 0:
+                    assert torch.equal(x, y), (b, f)
+                else:
+                    assert bool(((x - y).abs() <= 2.0 ** -7 * y.abs() + 2.0 ** -16 * y.abs().max()).all()), (b, f)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_peaked_scores_and_custom_scale(dtype):
     check_bwd(1, 2, 2, 600, 128, 16, 100, dtype=dtype, seed=4, q_mul=4.0, by_tensor_max=True)
