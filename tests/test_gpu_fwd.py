@@ -47,6 +47,22 @@ def test_few_work_items_give_the_same_bits(Hq, Hkv, N, sink, window, block, stri
 
 
 @pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("N,sink,window,block,stride", [
+    (4500, 0, 4500, 1, 0), (4700, 320, 4200, 1, 0), (4230, 64, 4096, 64, 0), (9000, 0, 128, 64, 2), (8300, 64, 192, 64, 40), (450, 0, 450, 1, 0)])
+def test_walks_of_few_work_items(N, sink, window, block, stride, D):
+    """The instance for few work items lists its key tiles 64 at a time: rows of 3, 4 and more than 64 tiles, lists that begin in
+    the middle of a rotated run, groups of 64 tiles of which most are dead: the bits of the instance that walks without a list."""
+    q, k, v = (x.to(DEV) for x in lg_synth.prefill_inputs(1, 1, 1, N, D, 16, torch.bfloat16))
+    out, lse = torch.empty_like(q), torch.empty(1, 1, N, dtype=torch.float32, device=DEV)
+    lg.lg_sparse_attn_fwd(q, k, v, out, lse, sink, window, block, stride)
+    many = 256 // ((N + 127) // 128) + 1
+    qm, km, vm = (x.repeat(many, 1, 1, 1) for x in (q, k, v))
+    om, lm = torch.empty_like(qm), torch.empty(many, 1, N, dtype=torch.float32, device=DEV)
+    lg.lg_sparse_attn_fwd(qm, km, vm, om, lm, sink, window, block, stride)
+    assert torch.equal(om, out.expand_as(om)) and torch.equal(lm, lse.expand_as(lm))
+
+
+@pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_sink_window_ragged_gqa(D, dtype):
     check_fwd(2, 4, 2, 700, D, 64, 200, dtype=dtype, seed=2)
