@@ -1030,31 +1030,6 @@ dkdv_bf16_kernel(
   dkdv_bf16_item<D, COLUMN>(smem, blockIdx.x, q, k, v, dout, nlse, ndelta, dk, dv, Hq, Hkv, scale, m_in, nkt, total, run, wk);
 }
 
-// dq and dk/dv in one launch, where neither fills the GPU (rule: bwd_both): the set-up kernel has formed Delta, and every work item does
-// what it does in a launch of its own, with the same bits.  Head dim 128: dq's items two by two, for as many waves as dk/dv has.
-template <int D>
-__global__ __launch_bounds__(btk_of(D) * 2) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 3, D == 128 ? 2 : 3))) void
-bwd_both_bf16_kernel(
-    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-    const uint16_t* __restrict__ dout, const float* __restrict__ lse, float* __restrict__ nlse, float* __restrict__ ndelta,
-    uint16_t* __restrict__ dq, uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int Hq, int Hkv, float scale, LgMask m,
-    int nkt, int total, int run, LgBwdWork wk, int nqt, int nkv, int ndq, bool dq_first) {
-  constexpr bool PAIR = D == 128;
-  constexpr int DQ = (PAIR ? 2 : 1) * DQ_LDS<D>;
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[DQ > DKDV_LDS<D> ? DQ : DKDV_LDS<D>];
-  const int id = dq_first ? (int)blockIdx.x : (int)blockIdx.x - nkv;
-  if (id >= 0 && id < ndq) {  // heads innermost, longest rows first
-    const int nh = wk.B * Hq, hd = id % nh, y = id / nh, x = PAIR ? y : y >> 1;
-    const int half = PAIR ? lg_uniform(threadIdx.x >> 8) : 1 - (y & 1);
-    const int b = hd / Hq, hq = hd - b * Hq;
-    dq_bf16_item<D, false, PAIR>(smem, nullptr, q, k, v, nullptr, dout, lse, ndelta, nlse, dq, Hq, Hkv, scale, m, wk, b, hq / (Hq / Hkv), hq,
-                                 nqt - 1 - x, half, x);
-    return;
-  }
-  const int kv = dq_first ? (int)blockIdx.x - ndq : (int)blockIdx.x;
-  dkdv_bf16_item<D, false>(smem, kv, q, k, v, dout, nlse, ndelta, dk, dv, Hq, Hkv, scale, m, nkt, total, run, wk);
-}
-
 // --------------------------------------------------------- dk, dv: the column part of a lone group
 // A head's only column group (the sink keys) is seen by every later query: up to N / 64 query tiles for 64 keys.  Left
 // to its key tile, one workgroup of the whole launch walks them with one wave in four (or two in eight) at work: with 2
@@ -1062,23 +1037,26 @@ bwd_both_bf16_kernel(
 // of 32 keys x the 4 blocks of 32 rows of two query tiles, double-buffered, and the range is cut into chunks.  Hq == Hkv:
 // every chunk leaves its sums in the workspace, and the one that finishes last adds them in order (bit-reproducible; the
 // cut depends on the sequence alone).  Groups of query heads: float32 atomics.
-template <int D>
-__global__ __launch_bounds__(512) void dkdv_lone_bf16_kernel(
-    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+// A work item.  WAVES: 8, or 4 for a tile at a time (GROUPS only: other sums than those of 8).  GROUPS: Hq != Hkv.
+template <int D, int WAVES>
+constexpr int LONE_LDS = LgSwzTile<D>::BYTES + WAVES / 2 * (2 * LgSwzTile<D>::BYTES + 1024);  // V rows, two steps' tiles
+template <int D, int WAVES, bool GROUPS>
+__device__ __forceinline__ void dkdv_lone_item(
+    unsigned char* smem, int id, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const uint16_t* __restrict__ dout, const float* __restrict__ nlse, const float* __restrict__ ndelta, int Hq, int Hkv,
-    float scale, LgMask m, LgBwdWork wk) {
+    float scale, LgMask m, const LgBwdWork& wk) {
   using T = LgSwzTile<D>;
   using Slot = LgSlot<D>;
-  constexpr int NT = 512;
+  static_assert(WAVES == 8 || (WAVES == 4 && GROUPS), "the order of sums");
+  constexpr int NT = 64 * WAVES, TILES = WAVES / 4;  // query tiles a step
   using Dma = LgDma<D, NT>;
   constexpr int TQ = LG_BF16_BTQ, TK = btk_of(D), DC = D / 16, DB = D / 32;
   constexpr int HALF = 32 * T::ROW_BYTES;
   constexpr int OFF_G = T::BYTES, OFF_L = 2 * T::BYTES, STAGE = 2 * T::BYTES + 1024;  // as in the kernel above
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[T::BYTES + 4 * STAGE];  // V rows, two pairs of tiles
-  __shared__ int s_last;
+  static_assert(LONE_LDS<D, WAVES> == T::BYTES + 2 * TILES * STAGE, "V rows, two steps' tiles");
 
-  const int nh = wk.B * Hq, hd = blockIdx.x % nh;
-  int chunk = blockIdx.x / nh, nchunk = wk.nlone, lone0 = 0, sq = 0, nseq = 1;
+  const int nh = wk.B * Hq, hd = id % nh;
+  int chunk = id / nh, nchunk = wk.nlone, lone0 = 0, sq = 0, nseq = 1;
   LgBwdItem it = {0, 0, 0, 0, 0, wk.ncol};
   if (wk.seqs) {
     nseq = lg_uniform(wk.seqs->n);
@@ -1092,7 +1070,8 @@ __global__ __launch_bounds__(512) void dkdv_lone_bf16_kernel(
   const int N = m.N, grp = lg_uniform(wk.col_list[it.col0]);
   const int first = lg_qtile_window_hi(m, min((64 * grp / TK) * TK + TK - 1, N - 1), TQ) + 1, last = (N - 1) / TQ;
   const int pairs = (last - first + 2) / 2;
-  const int p0 = pairs * chunk / nchunk, p1 = pairs * (chunk + 1) / nchunk;  // (never empty: nchunk <= pairs)
+  // steps [p0, p1) (never none: nchunk <= pairs)
+  const int p0 = pairs * chunk / nchunk * (2 / TILES), p1 = min(pairs * (chunk + 1) / nchunk * (2 / TILES), TILES == 2 ? pairs : last - first + 1);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = lg_uniform(tid >> 6);
   const int n = lane & 31, g = lane >> 5;
@@ -1122,9 +1101,9 @@ __global__ __launch_bounds__(512) void dkdv_lone_bf16_kernel(
   dma.issue(v + kbase + (size_t)64 * grp * D, N - 64 * grp, lds0);
   auto issue = [&](int pr, int buf) {
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
-      const int q0 = min(first + 2 * pr + x, last) * TQ;  // (an odd range repeats its last tile; nobody uses it)
-      const uint32_t st = lds0 + T::BYTES + (2 * buf + x) * STAGE;
+    for (int x = 0; x < TILES; ++x) {
+      const int q0 = min(first + TILES * pr + x, last) * TQ;  // (an odd range repeats its last tile; nobody uses it)
+      const uint32_t st = lds0 + T::BYTES + (TILES * buf + x) * STAGE;
       if ((wave >> 1) == x)  // -lse / scale rows and -Delta rows (64 floats each)
         lg_dma_f32x64(((wave & 1) ? ndelta : nlse) + wrow0 + min(q0 + lane, N - 1), st + OFF_L + (wave & 1) * 256);
       dma.issue(q + (row0 + q0) * D, N - q0, st);
@@ -1135,23 +1114,23 @@ __global__ __launch_bounds__(512) void dkdv_lone_bf16_kernel(
   for (int pr = p0; pr < p1; ++pr) {
     const int buf = (pr - p0) & 1;
     LG_WAIT_VMCNT(0);
-    __syncthreads();  // this pair landed for everyone; everyone is done with the one before
+    __syncthreads();  // this step's tiles landed for everyone; everyone is done with the one before
     if (pr + 1 < p1) issue(pr + 1, buf ^ 1);
-    const int u = first + 2 * pr + tile, q0 = u * TQ + 32 * qb;
+    const int u = first + TILES * pr + tile, q0 = u * TQ + 32 * qb;
     if (u > last || q0 >= N) continue;
     const int kind = lg_tile_kind(m, q0, min(q0 + 31, N - 1), kw0, kw0 + 31);
     if (kind == LG_TILE_DEAD) continue;
     const bool full = kind == LG_TILE_FULL && q0 + 32 <= N;
     const uint32_t bits = full ? ~0u : lg_row_bits(m, j, q0, g);
-    const int st = T::BYTES + (2 * buf + tile) * STAGE;
+    const int st = T::BYTES + (TILES * buf + tile) * STAGE;
     lg_dkdv_block<D>(smem, rd, st + qb * HALF, st + OFF_G + qb * HALF, kb * HALF,
                      reinterpret_cast<const float*>(smem + st + OFF_L) + 32 * qb, kf, ak, av, sl2, g, full,
                      [&](int r) { return !((bits >> r) & 1); });
   }
 
-  // the four row blocks' sums meet in waves 0 and 1, dk and then dv through the LDS of the tiles
+  // the row blocks' sums meet in waves 0 and 1, dk and then dv through the LDS of the tiles
   float* red = reinterpret_cast<float*>(smem + T::BYTES);
-  static_assert(6 * DB * 4096 <= 4 * STAGE, "six waves' blocks fit");
+  static_assert((WAVES - 2) * DB * 4096 <= 2 * TILES * STAGE, "the other waves' blocks fit");
 #pragma unroll
   for (int which = 0; which < 2; ++which) {
     f32x16_t(&acc)[DB] = which ? av : ak;
@@ -1164,7 +1143,7 @@ __global__ __launch_bounds__(512) void dkdv_lone_bf16_kernel(
     __syncthreads();
     if (wave < 2)
 #pragma unroll
-      for (int x = 0; x < 3; ++x)
+      for (int x = 0; x < WAVES / 2 - 1; ++x)
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -1172,7 +1151,7 @@ __global__ __launch_bounds__(512) void dkdv_lone_bf16_kernel(
   }
 
   float* sum = wk.colpart + ((size_t)bh * wk.ncol + it.col0) * Slot::FLOATS;
-  if (!wk.lonepart) {
+  if constexpr (GROUPS) {
     if (wave < 2)
 #pragma unroll
       for (int db = 0; db < DB; ++db)
@@ -1181,8 +1160,7 @@ __global__ __launch_bounds__(512) void dkdv_lone_bf16_kernel(
           unsafeAtomicAdd(sum + Slot::at(kb, 0, db) + 64 * r + lane, ak[db][r]);  // hardware float adds
           unsafeAtomicAdd(sum + Slot::at(kb, 1, db) + 64 * r + lane, av[db][r]);
         }
-    return;
-  }
+  } else {
   float* mine = wk.lonepart + ((size_t)bh * wk.nlone_all + lone0) * Slot::FLOATS;  // the sequence's first chunk
   if (wave < 2)
 #pragma unroll
@@ -1193,6 +1171,7 @@ __global__ __launch_bounds__(512) void dkdv_lone_bf16_kernel(
         lg_store_shared1(dst, ak[db][r]);
         lg_store_shared1(dst + Slot::at(0, 1, 0), av[db][r]);
       }
+  __shared__ int s_last;
   lg_shared_stores_done();
   __syncthreads();
   if (tid == 0)
@@ -1209,6 +1188,45 @@ __global__ __launch_bounds__(512) void dkdv_lone_bf16_kernel(
     for (int x = 0; x < EACH; ++x) a[x] += lg_load_shared1(mine + (size_t)c * Slot::FLOATS + x * NT + tid);
 #pragma unroll
   for (int x = 0; x < EACH; ++x) sum[x * NT + tid] = a[x];
+  }
+}
+template <int D, bool GROUPS>
+__global__ __launch_bounds__(512) void dkdv_lone_bf16_kernel(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+    const uint16_t* __restrict__ dout, const float* __restrict__ nlse, const float* __restrict__ ndelta, int Hq, int Hkv,
+    float scale, LgMask m, LgBwdWork wk) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[LONE_LDS<D, 8>];
+  dkdv_lone_item<D, 8, GROUPS>(smem, blockIdx.x, q, k, v, dout, nlse, ndelta, Hq, Hkv, scale, m, wk);
+}
+
+// dq and dk/dv in one launch, where neither fills the GPU (rule: bwd_both): the set-up kernel has formed Delta, and every work item does
+// what it does in a launch of its own, with the same bits.  Head dim 128: dq's items two by two, for as many waves as dk/dv has.  LONE: and
+// the column parts of lone groups (in one instance for all, calls without them lost up to 4 %).
+template <int D, bool LONE>
+__global__ __launch_bounds__(btk_of(D) * 2) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 3, D == 128 ? 2 : 3))) void
+bwd_both_bf16_kernel(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+    const uint16_t* __restrict__ dout, const float* __restrict__ lse, float* __restrict__ nlse, float* __restrict__ ndelta,
+    uint16_t* __restrict__ dq, uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int Hq, int Hkv, float scale, LgMask m,
+    int nkt, int total, int run, LgBwdWork wk, int nqt, int nkv, int ndq, bool dq_first) {
+  constexpr bool PAIR = D == 128;
+  constexpr int LDS = std::max({(PAIR ? 2 : 1) * DQ_LDS<D>, DKDV_LDS<D>, LONE ? LONE_LDS<D, D / 16> : 0});
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[LDS];
+  if (LONE && (int)blockIdx.x >= ndq + nkv) {
+    if constexpr (LONE) dkdv_lone_item<D, D / 16, true>(smem, blockIdx.x - (ndq + nkv), q, k, v, dout, nlse, ndelta, Hq, Hkv, scale, m, wk);
+    return;
+  }
+  const int id = dq_first ? (int)blockIdx.x : (int)blockIdx.x - nkv;
+  if (id >= 0 && id < ndq) {  // heads innermost, longest rows first
+    const int nh = wk.B * Hq, hd = id % nh, y = id / nh, x = PAIR ? y : y >> 1;
+    const int half = PAIR ? lg_uniform(threadIdx.x >> 8) : 1 - (y & 1);
+    const int b = hd / Hq, hq = hd - b * Hq;
+    dq_bf16_item<D, false, PAIR>(smem, nullptr, q, k, v, nullptr, dout, lse, ndelta, nlse, dq, Hq, Hkv, scale, m, wk, b, hq / (Hq / Hkv), hq,
+                                 nqt - 1 - x, half, x);
+    return;
+  }
+  const int kv = dq_first ? (int)blockIdx.x - ndq : (int)blockIdx.x;
+  dkdv_bf16_item<D, false>(smem, kv, q, k, v, dout, nlse, ndelta, dk, dv, Hq, Hkv, scale, m, nkt, total, run, wk);
 }
 
 // Adds the parts of a key tile's window part, in order, and its column sums, and rounds: a wave for each 32 keys x 32 dims
@@ -2018,6 +2036,11 @@ struct Columns {
     const int pairs = (last - first + 2) / 2;
     return ncol != 1 ? 0 : pairs < 16 ? 1 : pairs < 64 ? pairs / 8 : 8;
   }
+  // ... with groups of G query heads and `heads` of them in all: more where that leaves CUs idle, not below a pair, up to 64 adders
+  int lone_of_groups(int G, long long heads) const {
+    const int pairs = (last - first + 2) / 2;
+    return ncol != 1 ? 0 : std::max(lone(), (int)std::min<long long>({pairs, 64 / G, (256 + heads - 1) / heads}));
+  }
   // several: work items (virtual tile x chunk) of a query head; chunks are cut at multiples of `chunk` tiles
   int items(int D, int chunk) const {
     const int ng = btk_of(D) / 64;
@@ -2159,6 +2182,7 @@ struct BwdLaunch {
   Cut cut;
   int qt_wide, qt_rest;   // query tiles of a head in each form of the dq kernel
   int kt_wide, kt_rest;   // key tiles of a head in each form of the dk/dv kernel
+  int lone;               // chunks of lone groups
   int chunk, citems;      // column work items of a query head where there are several groups, and their query tiles
 };
 
@@ -2220,7 +2244,7 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
   const long long most = 0x7fffffffLL - 8 * 16 * 64;  // (room for the padding of the last runs)
   if ((long long)(a.qt_wide + 2 * a.qt_rest) * Hq * a.B > most ||
       (long long)(a.kt_wide + a.kt_rest) * nbh * nparts * 8 > most || (long long)a.citems * Hq * a.B > most ||
-      (long long)nlone * Hq * a.B > most)
+      (long long)a.lone * Hq * a.B > most)
     return hipErrorInvalidValue;
 
   if (ev) (void)hipEventRecord(ev[0], s);
@@ -2244,7 +2268,7 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
   wk.col_of_group = col_of_group;
   wk.col_list = col_list;
   wk.ncol = ncol;
-  wk.nlone = nlone;
+  wk.nlone = a.lone;
   wk.chunk = a.chunk;
   wk.colpart = colpart;
   wk.lonepart = Hq == Hkv ? (float*)(w + l.lonepart) : nullptr;
@@ -2288,10 +2312,20 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
 #define LG_DKDV_ARGS uq, uk, uv, ug, nlse, ndelta, dk, dv, Hq, Hkv, scale, m
 #define LG_DKDV_LAUNCH(DD, CC, GRID) \
   dkdv_bf16_kernel<DD, CC><<<GRID, 2 * btk_of(DD), 0, s>>>(LG_DKDV_ARGS, nkt, total, run, wk)
-  if (nlone > 0) {
-    const dim3 grid((unsigned)(nlone * Hq * a.B));
-    if (a.D == 64) dkdv_lone_bf16_kernel<64><<<grid, 512, 0, s>>>(uq, uk, uv, ug, nlse, ndelta, Hq, Hkv, scale, m, wk);
-    else dkdv_lone_bf16_kernel<128><<<grid, 512, 0, s>>>(uq, uk, uv, ug, nlse, ndelta, Hq, Hkv, scale, m, wk);
+  // Where there are parts a lone group's sums are for the fold, and its items go with dq's and dk/dv's.  Backward in us, a launch of
+  // their own of one to three chunks : this, 2/1 heads of 128, 2659 tokens, window 188 61.9 : 32.1, 16/2, 911, window 128 50.2 : 31.3,
+  // 4 x 8/2, 1188, 64-token blocks, window 576 84.3 : 71.0; 8/2 of 64, 1162 tokens, window 205 40.0 : 23.0, 8/1, 3129, window 2201
+  // 79.2 : 65.3, 4/2, 8 packed of up to 2456, window 194 63.0 : 53.5.
+  const bool lone_too = both && nparts > 1 && Hq != Hkv;
+  if (a.lone > 0 && !lone_too) {
+    const dim3 grid((unsigned)(a.lone * Hq * a.B));
+#define LG_LONE_LAUNCH(DD, GROUPS) \
+  dkdv_lone_bf16_kernel<DD, GROUPS><<<grid, 512, 0, s>>>(uq, uk, uv, ug, nlse, ndelta, Hq, Hkv, scale, m, wk)
+    if (a.D == 64 && Hq == Hkv) LG_LONE_LAUNCH(64, false);
+    else if (a.D == 64) LG_LONE_LAUNCH(64, true);
+    else if (Hq == Hkv) LG_LONE_LAUNCH(128, false);
+    else LG_LONE_LAUNCH(128, true);
+#undef LG_LONE_LAUNCH
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -2321,12 +2355,14 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
     wk.items = items + a.kt_wide;
     wk.order = lg_order(nbh, nkt, 1, a.D);
     if (both) {
-      const int ndq = both_dq_items(a), nkv = (int)grid.x;
-#define LG_BOTH_LAUNCH(DD)                                                                                                  \
-  bwd_both_bf16_kernel<DD><<<dim3((unsigned)(nkv + ndq)), 2 * btk_of(DD), 0, s>>>(uq, uk, uv, ug, lse, nlse, ndelta, dq, dk, dv, Hq, Hkv, \
+      const int ndq = both_dq_items(a), nkv = (int)grid.x, nlo = lone_too ? a.lone * Hq * a.B : 0;
+#define LG_BOTH_LAUNCH(DD, LL)                                                                                                \
+  bwd_both_bf16_kernel<DD, LL><<<dim3((unsigned)(nkv + ndq + nlo)), 2 * btk_of(DD), 0, s>>>(uq, uk, uv, ug, lse, nlse, ndelta, dq, dk, dv, Hq, Hkv, \
                                                                                   scale, m, nkt, total, run, wk, a.qt_rest, nkv, ndq, both_dq_first(a))
-      if (a.D == 64) LG_BOTH_LAUNCH(64);
-      else LG_BOTH_LAUNCH(128);
+      if (a.D == 64 && nlo > 0) LG_BOTH_LAUNCH(64, true);
+      else if (a.D == 64) LG_BOTH_LAUNCH(64, false);
+      else if (nlo > 0) LG_BOTH_LAUNCH(128, true);
+      else LG_BOTH_LAUNCH(128, false);
 #undef LG_BOTH_LAUNCH
     } else if (a.D == 64) LG_DKDV_LAUNCH(64, false, grid);
     else LG_DKDV_LAUNCH(128, false, grid);
@@ -2369,6 +2405,7 @@ BwdLaunch batch_launch(const LgShape& sh, const LgMask& m) {
   a.chunk = choose_chunk([&](int chunk) { return (long long)c.items(sh.D, chunk) * sh.Hq * sh.B; },
                          c.last - c.first, sh.Hq / sh.Hkv);
   a.citems = c.items(sh.D, a.chunk);
+  a.lone = sh.Hq == sh.Hkv ? c.lone() : c.lone_of_groups(sh.Hq / sh.Hkv, (long long)sh.Hq * sh.B);
   (dq_wide(m, sh.D, sh.Hq) ? a.qt_wide : a.qt_rest) = (sh.N + LG_BF16_TQ - 1) / LG_BF16_TQ;
   (dkdv_wide(m, sh.D) ? a.kt_wide : a.kt_rest) = (int)a.size.ktiles;
   a.cut = {1, 1};
@@ -2434,7 +2471,8 @@ int pack_launch(const LgShape& sh, const LgMask& tmpl, const int* cu_seqlens, in
     a.setup.len[y] = seq[y].len;
     a.setup.ncol[y] = seq[y].c.ncol;
     a.setup.citems[y] = seq[y].c.items(sh.D, a.chunk);
-    a.setup.nlone[y] = seq[y].c.lone();
+    a.setup.nlone[y] = sh.Hq == sh.Hkv ? seq[y].c.lone() : seq[y].c.lone_of_groups(sh.Hq / sh.Hkv, (long long)sh.Hq * n);
+    a.lone += a.setup.nlone[y];
     a.citems += a.setup.citems[y];
     // (both rules are monotone in the length: the wide ones come first)
     (dq_wide(m, sh.D, sh.Hq) ? a.qt_wide : a.qt_rest) += (seq[y].len + LG_BF16_TQ - 1) / LG_BF16_TQ;
