@@ -99,6 +99,7 @@ struct LgBwdWork {
   float* lonepart;        // Hq == Hkv: [b x kv head][lone chunks of all sequences] group slots
   int nlone_all;          // lone chunks of all sequences
   unsigned* arrived;      // Hq == Hkv: [b x kv head][sequence] chunks of a lone group that are done
+  bool lone_joint;        // Hq == Hkv: beside dq and dk/dv: its key tile's window part counts as a chunk and waits in colpart
   int order;              // lg_order
   bool by_tile;           // dk/dv items: heads innermost (always for packed sequences and cut window parts)
   // window parts cut into `heads_cut` sets of query heads times `rows_cut` runs of query tiles
@@ -689,6 +690,75 @@ __device__ __forceinline__ unsigned lg_rows_seeing(const LgMask& m, int j) {
   return (unsigned)((column ? m.N : lg_window_end(m, j)) - j);
 }
 
+// a[r] = the sum, in order, of n parts' values at src + 64 r, a part `step` floats after the one before, four of them asked for at a time.
+template <typename Load>
+__device__ __forceinline__ void lg_add_parts(const float* src, int n, size_t step, float (&a)[16], Load load) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) a[r] = 0.f;
+  int p = 0;
+  const auto add = [&](auto count) {
+    constexpr int P = decltype(count)::value;
+    float x[P][16];
+#pragma unroll
+    for (int i = 0; i < P; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) x[i][r] = load(src + (p + i) * step + 64 * r);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < P; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) a[r] += x[i][r];
+    p += P;
+  };
+  while (p + 4 <= n) add(std::integral_constant<int, 4>{});
+  if (p + 2 <= n) add(std::integral_constant<int, 2>{});
+  if (p < n) add(std::integral_constant<int, 1>{});
+}
+// The sums of 32 keys and 32 dims (times f) to a lane's key row: dst its first dim of the block.
+__device__ __forceinline__ void lg_put_keys(uint16_t* __restrict__ dst, const float (&a)[16], float f) {
+#pragma unroll
+  for (int r4 = 0; r4 < 4; ++r4) {
+    uint2 w;
+    w.x = lg_pack_bf16(a[4 * r4 + 0] * f, a[4 * r4 + 1] * f);
+    w.y = lg_pack_bf16(a[4 * r4 + 2] * f, a[4 * r4 + 3] * f);
+    *reinterpret_cast<uint2*>(dst + 8 * r4) = w;
+  }
+}
+
+// After a workgroup has stored a chunk of a lone group (Hq == Hkv), or its key tile's window part where that counts as one: the
+// last of them adds the chunks in order.  dk, dv: the sequence's first row.
+template <int D>
+__device__ __forceinline__ void lg_lone_done(const LgBwdWork& wk, int bh, int sq, int nseq, int nchunk, int lone0, int col0,
+                                             uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int grp, int N, float scale) {
+  using Slot = LgSlot<D>;
+  constexpr int DB = D / 32;
+  __shared__ int last;
+  lg_shared_stores_done();
+  __syncthreads();
+  if (threadIdx.x == 0)
+    last = __hip_atomic_fetch_add(wk.arrived + (size_t)bh * nseq + sq, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+           (unsigned)(nchunk - 1 + (wk.lone_joint ? 1 : 0));
+  __syncthreads();
+  if (!last) return;
+  float* sum = wk.colpart + ((size_t)bh * wk.ncol + col0) * Slot::FLOATS;
+  const float* chunks = wk.lonepart + ((size_t)bh * wk.nlone_all + lone0) * Slot::FLOATS;
+  const int lane = threadIdx.x & 63, n = lane & 31, g = lane >> 5;
+  for (int y = lg_uniform(threadIdx.x >> 6); y < 4 * DB; y += blockDim.x / 64) {  // blocks of 32 keys and 32 dims, dk's and dv's
+    const int at = 1024 * y + lane, which = y / DB & 1;
+    float a[16];
+    lg_add_parts(chunks + at, nchunk, Slot::FLOATS, a, lg_load_shared1);
+    if (!wk.lone_joint) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sum[at + 64 * r] = a[r];
+      continue;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) a[r] += lg_load_shared1(sum + at + 64 * r);
+    const int j = 64 * grp + 32 * (y / (2 * DB)) + n;
+    if (j < N) lg_put_keys((which ? dv : dk) + (size_t)j * D + y % DB * 32 + 4 * g, a, which ? 1.f : scale);
+  }
+}
+
 // 32 query rows against the wave's 32 keys, in an order that keeps few values alive at a time:
 // S -> P -> (dV += dO^T P) -> dP -> dS -> (dK += Q^T dS).  sq, sg: the rows of Q and dO in LDS; sL: their -lse / scale,
 // 64 floats further on their -Delta; voff: the V rows of the wave's keys.
@@ -762,7 +832,7 @@ __device__ __forceinline__ void lg_dkdv_block(const unsigned char* smem, const L
 
 template <int D>
 constexpr int DKDV_LDS = btk_of(D) / 64 * LgSwzTile<D>::BYTES + 2 * (2 * LgSwzTile<D>::BYTES + 1024);
-template <int D, bool COLUMN>
+template <int D, bool COLUMN, bool JOINT>
 __device__ __forceinline__ void dkdv_bf16_item(
     unsigned char* smem, int bid,
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
@@ -994,6 +1064,17 @@ __device__ __forceinline__ void dkdv_bf16_item(
     return;
   }
   const int cid = (ncol > 0 && kw0 < N) ? wk.col_of_group[it.grp0 + (kw0 >> 6)] : -1;
+  const bool joint = JOINT && wk.lone_joint && it.ncol == 1;
+  if (joint && cid >= 0) {  // (its window part counts as one of the lone group's chunks: below)
+    float* sum = wk.colpart + ((size_t)bh * wk.ncol + it.col0) * Slot::FLOATS + lane;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        lg_store_shared1(sum + Slot::at(wave_s & 1, 0, db) + 64 * r, ak[db][r]);
+        lg_store_shared1(sum + Slot::at(wave_s & 1, 1, db) + 64 * r, av[db][r]);
+      }
+  } else {
   if (cid >= 0) {
     const float* src = wk.colpart + ((size_t)bh * wk.ncol + it.col0 + cid) * Slot::FLOATS + lane;
 #pragma unroll
@@ -1018,6 +1099,19 @@ __device__ __forceinline__ void dkdv_bf16_item(
     }
     lg_rows_write<D>(rows, lane, (which ? dv : dk) + kbase + (size_t)kw0 * D, N - kw0);
   }
+  }
+  if (joint) {
+    const int grp = lg_uniform(wk.col_list[it.col0]);
+    if (64 * grp / TK != w.kt) return;
+    int sq = 0, nseq = 1, nchunk = wk.nlone, lone0 = 0;
+    if (wk.seqs) {
+      nseq = lg_uniform(wk.seqs->n);
+      sq = lg_seq_of(wk.seqs->ktile0, nseq, it.ktile0);
+      nchunk = lg_uniform(wk.seqs->nlone[sq]);
+      lone0 = lg_uniform(wk.seqs->litem0[sq]);
+    }
+    lg_lone_done<D>(wk, bh, sq, nseq, nchunk, lone0, it.col0, dk + kbase, dv + kbase, grp, N, scale);
+  }
 }
 template <int D, bool COLUMN>
 __global__ __launch_bounds__(btk_of(D) * 2) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 3, D == 128 ? 2 : 3))) void
@@ -1027,27 +1121,27 @@ dkdv_bf16_kernel(
     uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int Hq, int Hkv, float scale, LgMask m_in,
     int nkt, int total, int run, LgBwdWork wk) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[DKDV_LDS<D>];
-  dkdv_bf16_item<D, COLUMN>(smem, blockIdx.x, q, k, v, dout, nlse, ndelta, dk, dv, Hq, Hkv, scale, m_in, nkt, total, run, wk);
+  dkdv_bf16_item<D, COLUMN, false>(smem, blockIdx.x, q, k, v, dout, nlse, ndelta, dk, dv, Hq, Hkv, scale, m_in, nkt, total, run, wk);
 }
 
 // --------------------------------------------------------- dk, dv: the column part of a lone group
 // A head's only column group (the sink keys) is seen by every later query: up to N / 64 query tiles for 64 keys.  Left
 // to its key tile, one workgroup of the whole launch walks them with one wave in four (or two in eight) at work: with 2
 // heads and 24000 tokens 1.0 ms beside 0.16 ms for all the rest.  Here the eight waves of a workgroup are the 2 blocks
-// of 32 keys x the 4 blocks of 32 rows of two query tiles, double-buffered, and the range is cut into chunks.  Hq == Hkv:
-// every chunk leaves its sums in the workspace, and the one that finishes last adds them in order (bit-reproducible; the
-// cut depends on the sequence alone).  Groups of query heads: float32 atomics.
-// A work item.  WAVES: 8, or 4 for a tile at a time (GROUPS only: other sums than those of 8).  GROUPS: Hq != Hkv.
+// of 32 keys x the 4 blocks of 32 rows of two query tiles (head dim 64: four waves, a query tile, as many as share a launch with
+// dq), double-buffered, and the range is cut into chunks.  Hq == Hkv: every chunk leaves its sums in the workspace, and the one that
+// finishes last adds them in order (bit-reproducible; the cut depends on the sequence and its heads alone).  Groups of query
+// heads: float32 atomics.
+// A work item.  WAVES: 8, two query tiles at a time, or 4, one.  GROUPS: Hq != Hkv.  dk, dv: for wk.lone_joint.
 template <int D, int WAVES>
 constexpr int LONE_LDS = LgSwzTile<D>::BYTES + WAVES / 2 * (2 * LgSwzTile<D>::BYTES + 1024);  // V rows, two steps' tiles
 template <int D, int WAVES, bool GROUPS>
 __device__ __forceinline__ void dkdv_lone_item(
     unsigned char* smem, int id, const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-    const uint16_t* __restrict__ dout, const float* __restrict__ nlse, const float* __restrict__ ndelta, int Hq, int Hkv,
-    float scale, LgMask m, const LgBwdWork& wk) {
+    const uint16_t* __restrict__ dout, const float* __restrict__ nlse, const float* __restrict__ ndelta,
+    uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int Hq, int Hkv, float scale, LgMask m, const LgBwdWork& wk) {
   using T = LgSwzTile<D>;
   using Slot = LgSlot<D>;
-  static_assert(WAVES == 8 || (WAVES == 4 && GROUPS), "the order of sums");
   constexpr int NT = 64 * WAVES, TILES = WAVES / 4;  // query tiles a step
   using Dma = LgDma<D, NT>;
   constexpr int TQ = LG_BF16_BTQ, TK = btk_of(D), DC = D / 16, DB = D / 32;
@@ -1161,48 +1255,33 @@ __device__ __forceinline__ void dkdv_lone_item(
           unsafeAtomicAdd(sum + Slot::at(kb, 1, db) + 64 * r + lane, av[db][r]);
         }
   } else {
-  float* mine = wk.lonepart + ((size_t)bh * wk.nlone_all + lone0) * Slot::FLOATS;  // the sequence's first chunk
-  if (wave < 2)
+    float* mine = wk.lonepart + ((size_t)bh * wk.nlone_all + lone0) * Slot::FLOATS;  // the sequence's first chunk
+    if (wave < 2)
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+      for (int db = 0; db < DB; ++db)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        float* dst = mine + (size_t)chunk * Slot::FLOATS + Slot::at(kb, 0, db) + 64 * r + lane;
-        lg_store_shared1(dst, ak[db][r]);
-        lg_store_shared1(dst + Slot::at(0, 1, 0), av[db][r]);
-      }
-  __shared__ int s_last;
-  lg_shared_stores_done();
-  __syncthreads();
-  if (tid == 0)
-    s_last = __hip_atomic_fetch_add(wk.arrived + (size_t)bh * nseq + sq, 1u, __ATOMIC_RELAXED,
-                                    __HIP_MEMORY_SCOPE_AGENT) == (unsigned)(nchunk - 1);
-  __syncthreads();
-  if (!s_last) return;
-  constexpr int EACH = Slot::FLOATS / NT;
-  float a[EACH];
-#pragma unroll
-  for (int x = 0; x < EACH; ++x) a[x] = 0.f;
-  for (int c = 0; c < nchunk; ++c)
-#pragma unroll
-    for (int x = 0; x < EACH; ++x) a[x] += lg_load_shared1(mine + (size_t)c * Slot::FLOATS + x * NT + tid);
-#pragma unroll
-  for (int x = 0; x < EACH; ++x) sum[x * NT + tid] = a[x];
+        for (int r = 0; r < 16; ++r) {
+          float* dst = mine + (size_t)chunk * Slot::FLOATS + Slot::at(kb, 0, db) + 64 * r + lane;
+          lg_store_shared1(dst, ak[db][r]);
+          lg_store_shared1(dst + Slot::at(0, 1, 0), av[db][r]);
+        }
+    lg_lone_done<D>(wk, bh, sq, nseq, nchunk, lone0, it.col0, dk + kbase, dv + kbase, grp, N, scale);
   }
 }
 template <int D, bool GROUPS>
-__global__ __launch_bounds__(512) void dkdv_lone_bf16_kernel(
+__global__ __launch_bounds__(4 * D) void dkdv_lone_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const uint16_t* __restrict__ dout, const float* __restrict__ nlse, const float* __restrict__ ndelta, int Hq, int Hkv,
     float scale, LgMask m, LgBwdWork wk) {
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[LONE_LDS<D, 8>];
-  dkdv_lone_item<D, 8, GROUPS>(smem, blockIdx.x, q, k, v, dout, nlse, ndelta, Hq, Hkv, scale, m, wk);
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[LONE_LDS<D, D / 16>];
+  dkdv_lone_item<D, D / 16, GROUPS>(smem, blockIdx.x, q, k, v, dout, nlse, ndelta, nullptr, nullptr, Hq, Hkv, scale, m, wk);
 }
 
 // dq and dk/dv in one launch, where neither fills the GPU (rule: bwd_both): the set-up kernel has formed Delta, and every work item does
 // what it does in a launch of its own, with the same bits.  Head dim 128: dq's items two by two, for as many waves as dk/dv has.  LONE: and
 // the column parts of lone groups (in one instance for all, calls without them lost up to 4 %).
-template <int D, bool LONE>
+enum { LONE_NONE, LONE_GROUPS, LONE_HEADS };
+template <int D, int LONE>
 __global__ __launch_bounds__(btk_of(D) * 2) __attribute__((amdgpu_waves_per_eu(D == 128 ? 2 : 3, D == 128 ? 2 : 3))) void
 bwd_both_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
@@ -1210,10 +1289,11 @@ bwd_both_bf16_kernel(
     uint16_t* __restrict__ dq, uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int Hq, int Hkv, float scale, LgMask m,
     int nkt, int total, int run, LgBwdWork wk, int nqt, int nkv, int ndq, bool dq_first) {
   constexpr bool PAIR = D == 128;
-  constexpr int LDS = std::max({(PAIR ? 2 : 1) * DQ_LDS<D>, DKDV_LDS<D>, LONE ? LONE_LDS<D, D / 16> : 0});
+  constexpr int LDS = std::max({(PAIR ? 2 : 1) * DQ_LDS<D>, DKDV_LDS<D>, LONE != LONE_NONE ? LONE_LDS<D, D / 16> : 0});
   __shared__ __attribute__((aligned(1024))) unsigned char smem[LDS];
-  if (LONE && (int)blockIdx.x >= ndq + nkv) {
-    if constexpr (LONE) dkdv_lone_item<D, D / 16, true>(smem, blockIdx.x - (ndq + nkv), q, k, v, dout, nlse, ndelta, Hq, Hkv, scale, m, wk);
+  if (LONE != LONE_NONE && (int)blockIdx.x >= ndq + nkv) {
+    if constexpr (LONE != LONE_NONE)
+      dkdv_lone_item<D, D / 16, LONE == LONE_GROUPS>(smem, blockIdx.x - (ndq + nkv), q, k, v, dout, nlse, ndelta, dk, dv, Hq, Hkv, scale, m, wk);
     return;
   }
   const int id = dq_first ? (int)blockIdx.x : (int)blockIdx.x - nkv;
@@ -1226,7 +1306,7 @@ bwd_both_bf16_kernel(
     return;
   }
   const int kv = dq_first ? (int)blockIdx.x - ndq : (int)blockIdx.x;
-  dkdv_bf16_item<D, false>(smem, kv, q, k, v, dout, nlse, ndelta, dk, dv, Hq, Hkv, scale, m, nkt, total, run, wk);
+  dkdv_bf16_item<D, false, LONE == LONE_HEADS>(smem, kv, q, k, v, dout, nlse, ndelta, dk, dv, Hq, Hkv, scale, m, nkt, total, run, wk);
 }
 
 // Adds the parts of a key tile's window part, in order, and its column sums, and rounds: a wave for each 32 keys x 32 dims
@@ -1254,42 +1334,12 @@ __global__ __launch_bounds__(256) void bwd_fold_kernel(uint16_t* __restrict__ dk
   const int y = blockIdx.x % WG * 4 + wave, which = y / DB, db = y % DB, at = Slot::at(kb32 & 1, which, db);
   float a[16], c[16];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    a[r] = 0.f;
-    c[r] = cid >= 0 ? lg_load_shared1(csum + at + 64 * r) : 0.f;
-  }
-  int p = 0;
-  const auto add = [&](auto count) {
-    constexpr int P = decltype(count)::value;
-    float x[P][16];
-#pragma unroll
-    for (int i = 0; i < P; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) x[i][r] = src[(size_t)(p + i) * (KB / 2 * Slot::FLOATS) + at + 64 * r];
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < P; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) a[r] += x[i][r];
-    p += P;
-  };
-  while (p + 4 <= nparts) add(std::integral_constant<int, 4>{});
-  if (p + 2 <= nparts) add(std::integral_constant<int, 2>{});
-  if (p < nparts) add(std::integral_constant<int, 1>{});
+  for (int r = 0; r < 16; ++r) c[r] = cid >= 0 ? lg_load_shared1(csum + at + 64 * r) : 0.f;
+  lg_add_parts(src + at, nparts, KB / 2 * Slot::FLOATS, a, [](const float* p) { return *p; });
   if (cid >= 0)
 #pragma unroll
     for (int r = 0; r < 16; ++r) a[r] += c[r];
-  if (j < m.N) {
-    const float f = which ? 1.f : scale;
-    uint16_t* dst = (which ? dv : dk) + ((size_t)bh * m.ld + it.row0 + j) * D + db * 32 + 4 * g;
-#pragma unroll
-    for (int r4 = 0; r4 < 4; ++r4) {
-      uint2 w;
-      w.x = lg_pack_bf16(a[4 * r4 + 0] * f, a[4 * r4 + 1] * f);
-      w.y = lg_pack_bf16(a[4 * r4 + 2] * f, a[4 * r4 + 3] * f);
-      *reinterpret_cast<uint2*>(dst + 8 * r4) = w;
-    }
-  }
+  if (j < m.N) lg_put_keys((which ? dv : dk) + ((size_t)bh * m.ld + it.row0 + j) * D + db * 32 + 4 * g, a, which ? 1.f : scale);
 }
 
 // Work queue of the kernels that keep one workgroup per CU: queue[x] counts the items handed out
@@ -2031,15 +2081,18 @@ namespace {
 struct Columns {
   int ncol;         // column groups
   int first, last;  // query tiles of the first group's column part, the longest
-  // a lone group: its chunks, up to 8 and not below 8 pairs of tiles each, by the sequence alone
-  int lone() const {
-    const int pairs = (last - first + 2) / 2;
-    return ncol != 1 ? 0 : pairs < 16 ? 1 : pairs < 64 ? pairs / 8 : 8;
+  // A lone group: its chunks, up to 8 and not below 8 pairs of tiles each; up to 16 heads, and with head dim 64, whose items take a
+  // tile at a time, up to 16 (up to 16 heads of 64: 4 pairs).  By the sequence and its heads alone.  Backward in us, 8 : this, 8
+  // heads of 64, 37511 tokens, window 600 268 : 241, 4 of 128 198 : 170; 32 of 64, window 128 503 : 493, but 2 x 32, window 300 1286 :
+  // 1308.  Down to a pair each, 16 x 8 of 128, 3500 tokens 412 : 476.
+  int lone(int D, int Hq) const {
+    const int pairs = (last - first + 2) / 2, each = Hq <= 16 && D == 64 ? 4 : 8;
+    return ncol != 1 ? 0 : std::min(std::max(pairs / each, 1), Hq <= 16 || D == 64 ? 16 : 8);
   }
   // ... with groups of G query heads and `heads` of them in all: more where that leaves CUs idle, not below a pair, up to 64 adders
   int lone_of_groups(int G, long long heads) const {
     const int pairs = (last - first + 2) / 2;
-    return ncol != 1 ? 0 : std::max(lone(), (int)std::min<long long>({pairs, 64 / G, (256 + heads - 1) / heads}));
+    return ncol != 1 ? 0 : std::max(lone(128, 64), (int)std::min<long long>({pairs, 64 / G, (256 + heads - 1) / heads}));
   }
   // several: work items (virtual tile x chunk) of a query head; chunks are cut at multiples of `chunk` tiles
   int items(int D, int chunk) const {
@@ -2142,13 +2195,13 @@ struct BwdSize {
   size_t groups = 0;  // 64-key groups of a head
   size_t ncol = 0;    // split-off column groups of a head
   size_t lone = 0;    // chunks of lone groups
-  void add(int n, int D, const Columns& c) {
+  void add(int n, int D, int Hq, const Columns& c) {
     ++seqs;
     rows += n;
     ktiles += (n + btk_of(D) - 1) / btk_of(D);
     groups += (n + 63) / 64;
     ncol += c.ncol;
-    lone += c.lone();
+    lone += c.lone(D, Hq);
   }
 };
 struct BwdLayout {  // offsets; -Delta is first
@@ -2312,15 +2365,19 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
 #define LG_DKDV_ARGS uq, uk, uv, ug, nlse, ndelta, dk, dv, Hq, Hkv, scale, m
 #define LG_DKDV_LAUNCH(DD, CC, GRID) \
   dkdv_bf16_kernel<DD, CC><<<GRID, 2 * btk_of(DD), 0, s>>>(LG_DKDV_ARGS, nkt, total, run, wk)
-  // Where there are parts a lone group's sums are for the fold, and its items go with dq's and dk/dv's.  Backward in us, a launch of
-  // their own of one to three chunks : this, 2/1 heads of 128, 2659 tokens, window 188 61.9 : 32.1, 16/2, 911, window 128 50.2 : 31.3,
+  // A lone group's items go with dq's and dk/dv's: where there are parts its sums are for the fold, with Hq == Hkv whoever comes last
+  // adds them to the key tile's.  (Groups without parts: dk/dv adds what atomics have left, so they come before it.)  Backward in
+  // us, a launch of their own : this, 4 heads of 128, 3500 tokens, window 128 58.3 : 36.9, 8, 3500, window 600 85.7 : 58.8, 16 x 4,
+  // 900, window 128 73.6 : 62.7, 1, 37511, window 600 160.9 : 101.7; of 64, 2, 1700, window 128 36.1 : 18.7, 4 x 8, 1700 50.2 : 34.9,
+  // 32, 900 32.8 : 26.4; with groups (and more chunks) 2/1 heads of 128, 2659 tokens, window 188 61.9 : 32.1, 16/2, 911, window 128 50.2 : 31.3,
   // 4 x 8/2, 1188, 64-token blocks, window 576 84.3 : 71.0; 8/2 of 64, 1162 tokens, window 205 40.0 : 23.0, 8/1, 3129, window 2201
   // 79.2 : 65.3, 4/2, 8 packed of up to 2456, window 194 63.0 : 53.5.
-  const bool lone_too = both && nparts > 1 && Hq != Hkv;
+  const bool lone_too = both && (nparts > 1 || Hq == Hkv);
+  wk.lone_joint = lone_too && nparts == 1;
   if (a.lone > 0 && !lone_too) {
     const dim3 grid((unsigned)(a.lone * Hq * a.B));
 #define LG_LONE_LAUNCH(DD, GROUPS) \
-  dkdv_lone_bf16_kernel<DD, GROUPS><<<grid, 512, 0, s>>>(uq, uk, uv, ug, nlse, ndelta, Hq, Hkv, scale, m, wk)
+  dkdv_lone_bf16_kernel<DD, GROUPS><<<grid, 4 * DD, 0, s>>>(uq, uk, uv, ug, nlse, ndelta, Hq, Hkv, scale, m, wk)
     if (a.D == 64 && Hq == Hkv) LG_LONE_LAUNCH(64, false);
     else if (a.D == 64) LG_LONE_LAUNCH(64, true);
     else if (Hq == Hkv) LG_LONE_LAUNCH(128, false);
@@ -2359,10 +2416,13 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
 #define LG_BOTH_LAUNCH(DD, LL)                                                                                                \
   bwd_both_bf16_kernel<DD, LL><<<dim3((unsigned)(nkv + ndq + nlo)), 2 * btk_of(DD), 0, s>>>(uq, uk, uv, ug, lse, nlse, ndelta, dq, dk, dv, Hq, Hkv, \
                                                                                   scale, m, nkt, total, run, wk, a.qt_rest, nkv, ndq, both_dq_first(a))
-      if (a.D == 64 && nlo > 0) LG_BOTH_LAUNCH(64, true);
-      else if (a.D == 64) LG_BOTH_LAUNCH(64, false);
-      else if (nlo > 0) LG_BOTH_LAUNCH(128, true);
-      else LG_BOTH_LAUNCH(128, false);
+      const int lone = nlo == 0 ? LONE_NONE : Hq != Hkv ? LONE_GROUPS : LONE_HEADS;
+      if (a.D == 64 && lone == LONE_NONE) LG_BOTH_LAUNCH(64, LONE_NONE);
+      else if (a.D == 64 && lone == LONE_GROUPS) LG_BOTH_LAUNCH(64, LONE_GROUPS);
+      else if (a.D == 64) LG_BOTH_LAUNCH(64, LONE_HEADS);
+      else if (lone == LONE_NONE) LG_BOTH_LAUNCH(128, LONE_NONE);
+      else if (lone == LONE_GROUPS) LG_BOTH_LAUNCH(128, LONE_GROUPS);
+      else LG_BOTH_LAUNCH(128, LONE_HEADS);
 #undef LG_BOTH_LAUNCH
     } else if (a.D == 64) LG_DKDV_LAUNCH(64, false, grid);
     else LG_DKDV_LAUNCH(128, false, grid);
@@ -2401,11 +2461,11 @@ BwdLaunch batch_launch(const LgShape& sh, const LgMask& m) {
   a.scale = sh.scale;
   const Columns c = columns_of(m, sh.D);
   a.setup.btk = btk_of(sh.D);
-  a.size.add(sh.N, sh.D, c);
+  a.size.add(sh.N, sh.D, sh.Hq, c);
   a.chunk = choose_chunk([&](int chunk) { return (long long)c.items(sh.D, chunk) * sh.Hq * sh.B; },
                          c.last - c.first, sh.Hq / sh.Hkv);
   a.citems = c.items(sh.D, a.chunk);
-  a.lone = sh.Hq == sh.Hkv ? c.lone() : c.lone_of_groups(sh.Hq / sh.Hkv, (long long)sh.Hq * sh.B);
+  a.lone = sh.Hq == sh.Hkv ? c.lone(sh.D, sh.Hq) : c.lone_of_groups(sh.Hq / sh.Hkv, (long long)sh.Hq * sh.B);
   (dq_wide(m, sh.D, sh.Hq) ? a.qt_wide : a.qt_rest) = (sh.N + LG_BF16_TQ - 1) / LG_BF16_TQ;
   (dkdv_wide(m, sh.D) ? a.kt_wide : a.kt_rest) = (int)a.size.ktiles;
   a.cut = {1, 1};
@@ -2444,7 +2504,7 @@ int pack_launch(const LgShape& sh, const LgMask& tmpl, const int* cu_seqlens, in
     if (len == 0) continue;
     const Seq one = {cu_seqlens[x], len, columns_of(lg_mask_for_length(tmpl, len), sh.D)};
     BwdSize z = a.size;
-    z.add(len, sh.D, one.c);
+    z.add(len, sh.D, sh.Hq, one.c);
     if (n > 0 && (end(z) > budget || z.ktiles > 0xffffff || (double)z.rows * sh.Hq > 1e9)) break;
     a.size = z;
     int y = n++;
@@ -2471,7 +2531,7 @@ int pack_launch(const LgShape& sh, const LgMask& tmpl, const int* cu_seqlens, in
     a.setup.len[y] = seq[y].len;
     a.setup.ncol[y] = seq[y].c.ncol;
     a.setup.citems[y] = seq[y].c.items(sh.D, a.chunk);
-    a.setup.nlone[y] = sh.Hq == sh.Hkv ? seq[y].c.lone() : seq[y].c.lone_of_groups(sh.Hq / sh.Hkv, (long long)sh.Hq * n);
+    a.setup.nlone[y] = sh.Hq == sh.Hkv ? seq[y].c.lone(sh.D, sh.Hq) : seq[y].c.lone_of_groups(sh.Hq / sh.Hkv, (long long)sh.Hq * n);
     a.lone += a.setup.nlone[y];
     a.citems += a.setup.citems[y];
     // (both rules are monotone in the length: the wide ones come first)

@@ -204,7 +204,8 @@ def test_float32_backward_in_one_launch_and_in_two(B, Hq, Hkv, N, D, sink, windo
 
 @pytest.mark.parametrize("B,Hq,Hkv,N,D,sink,window,block,stride", [
     (60, 8, 8, 1030, 64, 4, 90, 1, 0), (22, 8, 8, 1030, 128, 0, 300, 1, 0), (22, 8, 2, 1030, 128, 64, 300, 1, 0), (60, 8, 4, 1150, 64, 64, 192, 64, 4),
-    (60, 8, 4, 1030, 64, 16, 100, 1, 0), (50, 16, 16, 129, 128, 0, 129, 1, 0)])
+    (60, 8, 4, 1030, 64, 16, 100, 1, 0), (22, 8, 8, 1030, 128, 16, 100, 1, 0),
+    (50, 16, 16, 129, 128, 0, 129, 1, 0)])
 def test_bf16_backward_in_one_launch_and_in_two(B, Hq, Hkv, N, D, sink, window, block, stride):
     """Up to 8192 (head dim 128: 1536) workgroups dq and dk/dv share a launch: a batch beyond that and one of its sequences alone and
     packed give the same bits of dq, without groups of query heads and columns of dk and dv as well; otherwise these are sums in
