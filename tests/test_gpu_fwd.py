@@ -63,6 +63,28 @@ def test_walks_of_few_work_items(N, sink, window, block, stride, D):
 
 
 @pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv,N,sink,window,block,stride", [
+    (4, 2, 700, 64, 200, 1, 0), (2, 1, 1000, 64, 128, 64, 4), (1, 1, 4700, 320, 4200, 1, 0), (1, 1, 4230, 64, 4096, 64, 0),
+    (1, 1, 8300, 64, 192, 64, 40), (1, 1, 450, 0, 450, 1, 0), (2, 1, 129, 4, 60, 1, 0)])
+def test_384_work_items_and_more_give_the_same_bits(Hq, Hkv, N, sink, window, block, stride, D):
+    """The instance for few work items takes up to 384: one sequence, the most copies of it within that and one more, as a batch
+    and packed (up to 128 sequences)."""
+    q, k, v = (x.to(DEV) for x in lg_synth.prefill_inputs(1, Hq, Hkv, N, D, 17, torch.bfloat16))
+    out, lse = torch.empty_like(q), torch.empty(1, Hq, N, dtype=torch.float32, device=DEV)
+    lg.lg_sparse_attn_fwd(q, k, v, out, lse, sink, window, block, stride)
+    most = 384 // (Hq * ((N + 127) // 128))
+    for many in (most, most + 1):
+        qm, km, vm = (x.repeat(many, 1, 1, 1) for x in (q, k, v))
+        om, lm = torch.empty_like(qm), torch.empty(many, Hq, N, dtype=torch.float32, device=DEV)
+        lg.lg_sparse_attn_fwd(qm, km, vm, om, lm, sink, window, block, stride)
+        assert torch.equal(om, out.expand_as(om)) and torch.equal(lm, lse.expand_as(lm))
+        qp, kp, vp = (x[0].repeat(1, many, 1) for x in (q, k, v))
+        op, lp = torch.empty_like(qp), torch.empty(Hq, many * N, dtype=torch.float32, device=DEV)
+        lg.lg_sparse_attn_fwd_varlen(qp, kp, vp, op, lp, [N * x for x in range(many + 1)], sink, window, block, stride)
+        assert torch.equal(op, out[0].repeat(1, many, 1)) and torch.equal(lp, lse[0].repeat(1, many))
+
+
+@pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_sink_window_ragged_gqa(D, dtype):
     check_fwd(2, 4, 2, 700, D, 64, 200, dtype=dtype, seed=2)
