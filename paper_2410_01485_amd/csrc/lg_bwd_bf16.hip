@@ -760,55 +760,36 @@ __device__ __forceinline__ void lg_lone_done(const LgBwdWork& wk, int bh, int sq
 }
 
 // 32 query rows against the wave's 32 keys, in an order that keeps few values alive at a time:
-// S -> P -> (dV += dO^T P) -> dP -> dS -> (dK += Q^T dS).  sq, sg: the rows of Q and dO in LDS; sL: their -lse / scale,
-// 64 floats further on their -Delta; voff: the V rows of the wave's keys.
+// S -> P -> (dV += dO^T P) -> dP -> dS -> (dK += Q^T dS), head dim 128: S -> dP and P -> (dV += dO^T P) -> dS -> (dK += Q^T dS), two
+// exponentials behind each matrix instruction of dP.  sq, sg: the rows of Q and dO in LDS; sL: their -lse / scale, 64 floats further
+// on their -Delta; voff: the V rows of the wave's keys.
+// Exponentials by themselves, and behind dP's (backward, us): 8 heads of 128, 3500 tokens, window 600 55.9 -> 55.3; 4 x 8, 1111,
+// causal 63.2 -> 61.8; 1, 1098 55.9 -> 54.2; 32, 16384, window 640 817 -> 808; 2 x 16/4, 1500 104.0 -> 102.5.  Head dim 64 has four
+// of them for each of half as many matrix instructions and lost: 16, 1117 31.2 -> 32.5; 32, 16384, window 2048 947 -> 974.
 template <int D, typename Dead>
 __device__ __forceinline__ void lg_dkdv_block(const unsigned char* smem, const LgSwzReader<D>& rd, int sq, int sg, int voff,
                                               const float* sL, const bf16x8_t (&kf)[D / 16], f32x16_t (&ak)[D / 32],
                                               f32x16_t (&av)[D / 32], float sl2, int g, bool full, Dead dead) {
   constexpr int DC = D / 16, DB = D / 32, AHEAD = D == 128 ? 2 : 3;
+  constexpr bool BEHIND = D == 128;  // P's exponentials behind dP's matrix instructions
   float p[16];
+  f32x16_t sc, dp;  // start from -lse / scale and -Delta of their rows (register r <-> row 8 (r / 4) + 4g + r % 4)
+  LgRing<DC, AHEAD> rows, vrows;
   LgRing<2 * DB, AHEAD> cols;
+  auto q_rows = [&](int u) { return rd.read_rows(smem, sq, 0, u); };
+  auto g_rows = [&](int u) { return rd.read_rows(smem, sg, 0, u); };
+  auto v_rows = [&](int u) { return rd.read_rows(smem, voff, 0, u); };
   auto g_cols = [&](int u) { return rd.read_cols(smem, sg, u % DB, u / DB); };
   auto q_cols = [&](int u) { return rd.read_cols(smem, sq, u % DB, u / DB); };
-  __builtin_amdgcn_sched_barrier(0);  // phases stay apart: bounds the operands held at once
-  {
-    // the accumulator starts from -lse / scale of its rows (register r <-> row 8 (r / 4) + 4g + r % 4)
-    f32x16_t sc;
+  auto start = [&](f32x16_t& x, const float* from) {
 #pragma unroll
     for (int r4 = 0; r4 < 4; ++r4) {
-      const float4 l4 = *reinterpret_cast<const float4*>(sL + 8 * r4 + 4 * g);
-      sc[4 * r4 + 0] = l4.x; sc[4 * r4 + 1] = l4.y; sc[4 * r4 + 2] = l4.z; sc[4 * r4 + 3] = l4.w;
+      const float4 f = *reinterpret_cast<const float4*>(from + 8 * r4 + 4 * g);
+      x[4 * r4 + 0] = f.x; x[4 * r4 + 1] = f.y; x[4 * r4 + 2] = f.z; x[4 * r4 + 3] = f.w;
     }
-    LgRing<DC, AHEAD> rows;
-    auto q_rows = [&](int u) { return rd.read_rows(smem, sq, 0, u); };
-    rows.begin(q_rows);
-    rows.run(q_rows, [&](int u, bf16x8_t a) { sc = lg_mfma32(a, kf[u], sc); });
-    cols.begin(g_cols);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) p[r] = __builtin_amdgcn_exp2f(sc[r] * sl2);
-    if (!full) {
-      asm volatile("; masked" ::: "memory");  // (a real branch: as selects the masks cost whole tiles 5 % at head dim 64)
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (dead(r)) p[r] = 0.f;
-    }
-  }
-  {
-    const bf16x8_t pb[2] = {lg_pack8(p), lg_pack8(p + 8)};
-    cols.run(g_cols, [&](int u, bf16x8_t a) { av[u % DB] = lg_mfma32(a, pb[u / DB], av[u % DB]); });
-  }
-  __builtin_amdgcn_sched_barrier(0);
-  {
-    f32x16_t dp;  // starts from -Delta of its rows
-#pragma unroll
-    for (int r4 = 0; r4 < 4; ++r4) {
-      const float4 d4 = *reinterpret_cast<const float4*>(sL + 64 + 8 * r4 + 4 * g);
-      dp[4 * r4 + 0] = d4.x; dp[4 * r4 + 1] = d4.y; dp[4 * r4 + 2] = d4.z; dp[4 * r4 + 3] = d4.w;
-    }
-    LgRing<DC, AHEAD> rows, vrows;
-    auto g_rows = [&](int u) { return rd.read_rows(smem, sg, 0, u); };
-    auto v_rows = [&](int u) { return rd.read_rows(smem, voff, 0, u); };
+  };
+  auto product_dp = [&](auto behind) {  // behind(u) goes behind matrix instruction u
+    start(dp, sL + 64);
     rows.begin(g_rows);
     vrows.begin(v_rows);
     lg_static_for<DC>([&](auto U) {
@@ -819,11 +800,40 @@ __device__ __forceinline__ void lg_dkdv_block(const unsigned char* smem, const L
         vrows.op[x] = v_rows(w);
       }
       dp = lg_mfma32(rows.op[y], vrows.op[y], dp);
+      behind(u);
     });
-    cols.begin(q_cols);
+  };
+  __builtin_amdgcn_sched_barrier(0);  // phases stay apart: bounds the operands held at once
+  start(sc, sL);
+  rows.begin(q_rows);
+  rows.run(q_rows, [&](int u, bf16x8_t a) { sc = lg_mfma32(a, kf[u], sc); });
+  if constexpr (BEHIND) {
+    product_dp([&](int u) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) p[r] *= dp[r];  // p becomes dS
+      for (int x = 0; x < 16 / DC; ++x) p[16 / DC * u + x] = __builtin_amdgcn_exp2f(sc[16 / DC * u + x] * sl2);
+    });
+    __builtin_amdgcn_sched_barrier(0);
+    cols.begin(g_cols);
+  } else {
+    cols.begin(g_cols);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) p[r] = __builtin_amdgcn_exp2f(sc[r] * sl2);
   }
+  if (!full) {
+    asm volatile("; masked" ::: "memory");  // (a real branch: as selects the masks cost whole tiles 5 % at head dim 64)
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if (dead(r)) p[r] = 0.f;
+  }
+  {
+    const bf16x8_t pb[2] = {lg_pack8(p), lg_pack8(p + 8)};
+    cols.run(g_cols, [&](int u, bf16x8_t a) { av[u % DB] = lg_mfma32(a, pb[u / DB], av[u % DB]); });
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (!BEHIND) product_dp([](int) {});
+  cols.begin(q_cols);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) p[r] *= dp[r];  // p becomes dS
   {
     const bf16x8_t db_[2] = {lg_pack8(p), lg_pack8(p + 8)};
     cols.run(q_cols, [&](int u, bf16x8_t a) { ak[u % DB] = lg_mfma32(a, db_[u / DB], ak[u % DB]); });
