@@ -2160,10 +2160,18 @@ struct Cut {
 // pass that adds the parts 4 TB/s.  Only with groups of query heads or strided columns: elsewhere dk and dv do not
 // depend on what else a launch holds.
 //   nbh: b x kv heads; tiles: key tiles of a head; steps, longest: query tiles of all of a head's key tiles, and the most
-//   of one; most: parts of a key tile that the workspace has room for
-Cut choose_cut(int D, int G, int nbh, size_t tiles, double steps, int longest, size_t most) {
-  const double each1 = D == 128 ? 3.0 : 1.5, each = D == 128 ? 3.0 : 1.0, start = D == 128 ? 8 : 3;
+//   of one; most: parts of a key tile that the workspace has room for; ndq: dq's work items, -1: not in a launch with dk/dv
+// Where dq shares the launch, its items take as many rounds as dk/dv's, and more parts gain less than their sum takes: head dim 128
+// then counts 2 us for a query tile, dq's as well, 3 TB/s for the sum, and does not ask for a tenth, up to three work items per CU
+// before the cut (beyond that the launch may be cut in two: 4 x 16/2 heads, 4910 tokens, causal, 1440 items 1240 -> 1420).  23 shapes
+// with groups, all cuts timed: the former rule's were 5.8 % from the best one (geometric mean), these 2.4.  Backward in us: 32/8
+// heads, 1807 tokens, window 252 89.0 -> 79.9, 2 x 32/8, 370 43.1 -> 36.8, 4 x 16/2, 1786, causal 222 -> 209, 2 packed of up to 483,
+// 64/8 64.4 -> 59.4; the least: 2/1, 1240, every 8th block 54.0 -> 55.6.  (Head dim 64: 5.2 % with the former rule, 6.0 with the best
+// of this form.)
+Cut choose_cut(int D, int G, int nbh, size_t tiles, double steps, int longest, size_t most, long long ndq) {
   const double items = (double)tiles * nbh;
+  const bool shared = D == 128 && ndq >= 0 && ndq + items <= 3 * CUS;
+  const double each1 = shared ? 2.0 : D == 128 ? 3.0 : 1.5, each = shared ? 4.0 : D == 128 ? 3.0 : 1.0, start = D == 128 ? 8 : 3;
   Cut best = {1, 1};
   double least = 0;
   for (int heads = 1; heads <= G; ++heads) {
@@ -2171,11 +2179,12 @@ Cut choose_cut(int D, int G, int nbh, size_t tiles, double steps, int longest, s
     for (int rows = 1; rows <= 8 && rows <= longest; ++rows) {
       const double parts = heads * rows;
       if (parts > 1 && (items * parts > (D == 128 ? 4 : 8) * CUS || parts > most)) break;
-      const double one = (double)(G / heads) * ((longest + rows - 1) / rows) * each1 + 8;
+      const double one = (double)(G / heads) * ((longest + rows - 1) / rows) * each1 + (shared ? 4 : 8);
       const double all = (steps * G * nbh * each + items * parts * start) / CUS;
-      const double fold = parts > 1 ? 5 + items * parts * (btk_of(D) * D * 8.0) / 4e6 : 0;
+      const double fold = parts > 1 ? 5 + items * parts * (btk_of(D) * D * 8.0) / (shared ? 3e6 : 4e6) : 0;
       const double t = (one > all ? one : all) + fold;
-      if (parts == 1 || t < 0.9 * least) {
+      const bool level = shared && t == least && parts <= best.heads * best.rows;  // (of two alike the one of more heads)
+      if (parts == 1 || t < (shared ? 1.0 : 0.9) * least || level) {
         least = t;
         best = {heads, rows};
       }
@@ -2483,7 +2492,7 @@ BwdLaunch batch_launch(const LgShape& sh, const LgMask& m) {
     double steps = 0;
     int longest = 0;
     window_steps(m, a.setup.btk, &steps, &longest);
-    a.cut = choose_cut(sh.D, sh.Hq / sh.Hkv, sh.B * sh.Hkv, a.size.ktiles, steps, longest, MOST_PARTS);
+    a.cut = choose_cut(sh.D, sh.Hq / sh.Hkv, sh.B * sh.Hkv, a.size.ktiles, steps, longest, MOST_PARTS, a.qt_wide > 0 ? -1 : both_dq_items(a));
   }
   return a;
 }
@@ -2554,7 +2563,7 @@ int pack_launch(const LgShape& sh, const LgMask& tmpl, const int* cu_seqlens, in
     for (int y = 0; y < n; ++y) window_steps(lg_mask_for_length(tmpl, seq[y].len), a.setup.btk, &steps, &longest);
     const size_t tile = (size_t)sh.Hkv * a.size.ktiles * (a.setup.btk * 2 * sizeof(float)) * sh.D, used = end(a.size);
     a.cut = choose_cut(sh.D, sh.Hq / sh.Hkv, sh.Hkv, a.size.ktiles, steps, longest,
-                       n == 1 ? MOST_PARTS : used < budget ? (budget - used) / tile : 0);
+                       n == 1 ? MOST_PARTS : used < budget ? (budget - used) / tile : 0, a.qt_wide > 0 ? -1 : both_dq_items(a));
   }
   *bytes = end(a.size);
   return x;
