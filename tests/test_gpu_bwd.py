@@ -400,6 +400,16 @@ def test_window_parts_and_lone_columns(B, Hq, Hkv, N, D, sink, window, block, st
     check_bwd(B, Hq, Hkv, N, D, sink, window, block, stride, seed=84)
 
 
+@pytest.mark.parametrize("Hq,Hkv,N,sink,window,block,stride", [
+    (2, 1, 65, 0, 65, 1, 0),            # one key tile, two steps
+    (8, 1, 300, 16, 128, 1, 0), (16, 4, 473, 0, 473, 1, 0), (4, 2, 1131, 64, 128, 64, 8), (3, 3, 1200, 64, 256, 64, 4),
+    (64, 32, 2048, 64, 192, 64, 0),     # 768 work items of dq and dk/dv before the cut, and more
+    (64, 32, 2049, 64, 192, 64, 0)])
+def test_window_parts_beside_dq(Hq, Hkv, N, sink, window, block, stride):
+    """bf16, head dim 128: up to 768 work items the window parts are cut in view of dq's, which share the launch."""
+    check_bwd(1, Hq, Hkv, N, 128, sink, window, block, stride, seed=33)
+
+
 def test_bwd_deterministic_long_window():
     q, k, v, g = lg_synth.prefill_inputs(1, 2, 2, 2000, 128, 10, torch.bfloat16, with_dout=True)
     a = run_fwd_bwd(q, k, v, g, 64, 1024)
