@@ -144,8 +144,8 @@ int lg_sparse_attn_bwd(const void* q, const void* k, const void* v, const void* 
  * bracketed by HIP events on hip_stream.  Synchronises the stream and writes the kernel
  * durations in milliseconds to the HOST array kernel_ms[3] = {set-up, dq, dk/dv}:
  *   set-up  bf16 path: the kernel that clears the work-queue counters and the partial sums and writes the
- *           column tables (a few microseconds; Delta is formed inside the dq kernel); float32 path: nothing, or, where
- *           dq and dk/dv share a launch, the kernel that forms Delta
+ *           column tables (a few microseconds; Delta is formed inside the dq kernel, or here where dq and dk/dv share a
+ *           launch); float32 path: nothing, or, where they do, the kernel that forms Delta
  *   dq      the dq kernel (nothing where it shares a launch with dk/dv, which then stands for both)
  *   dk/dv   the dk/dv kernel with the kernels of the split-off column parts before it and, where window parts are
  *           cut, the one that adds the parts after it

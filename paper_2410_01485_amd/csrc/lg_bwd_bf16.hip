@@ -1278,13 +1278,13 @@ __device__ __forceinline__ void dkdv_lone_item(
     lg_lone_done<D>(wk, bh, sq, nseq, nchunk, lone0, it.col0, dk + kbase, dv + kbase, grp, N, scale);
   }
 }
-template <int D, bool GROUPS>
-__global__ __launch_bounds__(4 * D) void dkdv_lone_bf16_kernel(
+template <int D, int WAVES, bool GROUPS>
+__global__ __launch_bounds__(64 * WAVES) void dkdv_lone_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const uint16_t* __restrict__ dout, const float* __restrict__ nlse, const float* __restrict__ ndelta, int Hq, int Hkv,
     float scale, LgMask m, LgBwdWork wk) {
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[LONE_LDS<D, D / 16>];
-  dkdv_lone_item<D, D / 16, GROUPS>(smem, blockIdx.x, q, k, v, dout, nlse, ndelta, nullptr, nullptr, Hq, Hkv, scale, m, wk);
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[LONE_LDS<D, WAVES>];
+  dkdv_lone_item<D, WAVES, GROUPS>(smem, blockIdx.x, q, k, v, dout, nlse, ndelta, nullptr, nullptr, Hq, Hkv, scale, m, wk);
 }
 
 // dq and dk/dv in one launch, where neither fills the GPU (rule: bwd_both): the set-up kernel has formed Delta, and every work item does
@@ -2264,9 +2264,14 @@ struct BwdLaunch {
 // this, of 64: 16 heads, 1117 tokens, causal 52 : 31, 8/4, 8 packed of up to 2186 89 : 62, 4 x 16, 997 58 : 46, 16/8, 1111, window
 // 128 50 : 44, 2 x 64/16, 7479, window 200 (9568 workgroups) 437 : 434; of 128: 8, 3249, causal 224 : 150, 4 x 8, 1111 97 : 63, 16/8,
 // 30 packed of up to 775 194 : 87, 1, 1098, causal 91 : 57, 16, 3707, window 186 93 : 90, 2 x 16/8, 8639, window 124 (1632) 254 : 241;
-// 8, 30 packed of up to 3991, window 704 (1952) 317 : 323, 32/16, 30 of up to 3428, window 448 (5952) 992 : 1065.
+// 8, 30 packed of up to 3991, window 704 (1952) 317 : 323, 32/16, 30 of up to 3428, window 448 (5952) 992 : 1065.  Delta is a pass of
+// its own then, over all of out and dO, which is got back up to 100 MB, of 64 up to 140: of 128, 129 (23 us), 2 x 32/16 heads, 3934
+// tokens, window 182 221 : 236; 85, 2 x 8, 10341, window 128 159 : 159; 72, 32/8, 4408, window 320, every 8th block 301 : 248; of 64,
+// 151, 32/16, 18467, window 192 214 : 223; 154, 4 x 64/8, 2349, causal 674 : 682; 107, 32/8, 13032, window 2930 986 : 954.
 int both_dq_items(const BwdLaunch& a) { return (a.D == 128 ? 1 : 2) * a.qt_rest * a.Hq * a.B; }
 bool bwd_both(const BwdLaunch& a) {
+  const double delta = 4.0 * a.size.rows * a.B * a.Hq * a.D;  // bytes of out and dO
+  if (delta > (a.D == 128 ? 101e6 : 140e6)) return false;
   const long long kv = (long long)(a.kt_wide + a.kt_rest) * a.Hkv * a.B * a.cut.heads * a.cut.rows;
   return a.qt_wide == 0 && both_dq_items(a) + kv <= (a.D == 64 ? 8192 : 1536);
 }
@@ -2395,12 +2400,14 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
   wk.lone_joint = lone_too && nparts == 1;
   if (a.lone > 0 && !lone_too) {
     const dim3 grid((unsigned)(a.lone * Hq * a.B));
-#define LG_LONE_LAUNCH(DD, GROUPS) \
-  dkdv_lone_bf16_kernel<DD, GROUPS><<<grid, 4 * DD, 0, s>>>(uq, uk, uv, ug, nlse, ndelta, Hq, Hkv, scale, m, wk)
-    if (a.D == 64 && Hq == Hkv) LG_LONE_LAUNCH(64, false);
-    else if (a.D == 64) LG_LONE_LAUNCH(64, true);
-    else if (Hq == Hkv) LG_LONE_LAUNCH(128, false);
-    else LG_LONE_LAUNCH(128, true);
+    // (groups have a chunk per CU: eight waves of head dim 64 as well.  32/16 heads, 8148 tokens 33 us with four, 26 with eight; 32/8,
+    // 11624 47, 36)
+#define LG_LONE_LAUNCH(DD, WAVES, GROUPS) \
+  dkdv_lone_bf16_kernel<DD, WAVES, GROUPS><<<grid, 64 * WAVES, 0, s>>>(uq, uk, uv, ug, nlse, ndelta, Hq, Hkv, scale, m, wk)
+    if (a.D == 64 && Hq == Hkv) LG_LONE_LAUNCH(64, 4, false);
+    else if (a.D == 64) LG_LONE_LAUNCH(64, 8, true);
+    else if (Hq == Hkv) LG_LONE_LAUNCH(128, 8, false);
+    else LG_LONE_LAUNCH(128, 8, true);
 #undef LG_LONE_LAUNCH
     e = hipGetLastError();
     if (e != hipSuccess) return e;
