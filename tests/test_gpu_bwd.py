@@ -410,6 +410,13 @@ def test_window_parts_beside_dq(Hq, Hkv, N, sink, window, block, stride):
     check_bwd(1, Hq, Hkv, N, 128, sink, window, block, stride, seed=33)
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,N,D,sink,window", [(4, 32, 16, 2177, 64, 16, 128), (3, 32, 16, 2753, 128, 5, 128)])
+def test_lone_groups_before_the_shared_launch(B, Hq, Hkv, N, D, sink, window):
+    """bf16, groups of query heads, too many key tiles for a cut: the sink's column parts come before the launch of dq and dk/dv (head
+    dim 64), and beyond 100 MB of out and dO (head dim 128) dq and dk/dv have one each."""
+    check_bwd(B, Hq, Hkv, N, D, sink, window, seed=34)
+
+
 def test_bwd_deterministic_long_window():
     q, k, v, g = lg_synth.prefill_inputs(1, 2, 2, 2000, 128, 10, torch.bfloat16, with_dout=True)
     a = run_fwd_bwd(q, k, v, g, 64, 1024)
