@@ -25,7 +25,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 
 # flags of one file: the forward's tile loop runs up to 5 % slower where its code happens to start off a 64-byte boundary
 # (the backward kernels' unrolled steps do not: within 0.3 %)
-FILE_FLAGS = {"lg_fwd_bf16.hip": ["-falign-loops=64"]}
+FILE_FLAGS = {"lg_fwd_bf16.hip": ["-falign-loops=64"], "lg_fwd_list_bf16.hip": ["-falign-loops=64"]}
 
 
 def sources():

@@ -378,6 +378,18 @@ LG_HD bool lg_qsched_full(const LgMask& m, const LgQSched& s, int t) {
   return kb == lg_div_b(m, hi) && lg_strided(m, kb);
 }
 
+// bf16 forward, the instance for few work items: whether its waves list their key tiles 64 at a time.  What a list costs before the
+// first tile is worth it from LG_FWD_LIST tiles of the longest rows on, and with strided columns, where the live ones of 64 tiles
+// are a list, while every 16th or more of the tiles between sink and window is live.
+constexpr int LG_FWD_LIST = 10;
+inline bool lg_fwd_lists(const LgMask& m, int rows) {  // m: of the longest sequence; rows: of a query tile
+  if (m.stride > 0 && (long long)m.stride * (m.b < 64 ? m.b : 64) > 1024) return false;
+  const LgQSched s = lg_qsched_init(m, m.N > rows ? m.N - rows : 0, m.N - 1);
+  int n = 0;
+  for (int t = lg_qsched_next(m, s, -1); t >= 0 && n < LG_FWD_LIST; t = lg_qsched_next(m, s, t)) ++n;
+  return n == LG_FWD_LIST;
+}
+
 // Walk order for patterns without strided columns (the live key tiles of a query tile are then
 // the sink tiles plus ONE contiguous run [tws, tmax]).  The online softmax takes tiles in any
 // order, so the run is walked rotated: at step x every query tile is at the key tile of its run

@@ -200,3 +200,24 @@ def test_engines_and_cus_get_even_shares(tmp_path):
 @pytest.mark.parametrize("opt", ["-O0", "-O2"])
 def test_division_by_multiplication_and_items(tmp_path, opt):
     run(tmp_path, PROGRAM, opt)
+
+
+LISTS = r"""
+#include <cstdio>
+#include "lg_mask.h"
+// N, sink, window, block, stride, and whether tiles are listed: causal rows of 9 and 10 tiles, windows, columns near and far
+int main() {
+  const int shapes[][6] = {{1, 0, 1, 1, 0, 0}, {576, 0, 576, 1, 0, 0}, {577, 0, 577, 1, 0, 1}, {9000, 0, 9000, 1, 0, 1}, {9000, 64, 384, 64, 0, 0},
+                           {9088, 64, 448, 64, 0, 0}, {9088, 64, 512, 64, 0, 1}, {9088, 64, 64, 64, 0, 0}, {24000, 64, 64, 64, 16, 1}, {24000, 64, 64, 64, 17, 0}, {24000, 64, 64, 64, 64, 0},
+                           {24000, 64, 640, 64, 64, 0}, {24000, 128, 128, 128, 16, 1}, {24000, 16, 64, 16, 64, 1}, {24000, 16, 64, 16, 65, 0},
+                           {24000, 0, 64, 1, 1024, 1}, {24000, 0, 64, 1, 1025, 0}, {600, 64, 64, 64, 8, 0}, {130, 0, 130, 1, 0, 0}};
+  for (auto& s : shapes)
+    if (lg_fwd_lists(lg_make_mask(s[0], s[1], s[2], s[3], s[4]), 128) != (s[5] != 0)) { std::printf("%d %d %d %d %d\n", s[0], s[1], s[2], s[3], s[4]); return 1; }
+  return 0;
+}
+"""
+
+
+def test_which_small_forwards_list_their_tiles(tmp_path):
+    """Rows of a few tiles, and tiles that are live few and far between, are walked without a list."""
+    run(tmp_path, LISTS, "-O1")
