@@ -85,6 +85,38 @@ def test_384_work_items_and_more_give_the_same_bits(Hq, Hkv, N, sink, window, bl
 
 
 @pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv,N,sink,window,block,stride", [
+    # rows of a few tiles (walked), of 9 and 10 (walked, listed), of more than 64 and more than 128 (lists follow one another)
+    (2, 1, 1, 0, 1, 1, 0), (2, 2, 64, 0, 64, 1, 0), (2, 1, 129, 4, 60, 1, 0), (4, 2, 700, 64, 200, 1, 0), (2, 2, 576, 0, 576, 1, 0),
+    (2, 2, 577, 0, 577, 1, 0), (2, 2, 640, 0, 640, 1, 0), (2, 2, 1090, 16, 100, 1, 0), (1, 1, 4500, 0, 4500, 1, 0), (1, 1, 4700, 320, 4200, 1, 0),
+    (1, 1, 4230, 64, 4096, 64, 0), (1, 1, 9000, 0, 9000, 1, 0),
+    # strided columns: near (listed) and far apart (walked), most of a group of 64 tiles live, few of them, one
+    (2, 1, 1000, 64, 128, 64, 4), (1, 1, 9000, 0, 128, 64, 2), (1, 1, 9000, 64, 64, 64, 16), (1, 1, 9000, 64, 64, 64, 17),
+    (1, 1, 8300, 64, 192, 64, 40), (1, 1, 3000, 16, 64, 16, 64), (1, 1, 3000, 0, 64, 1, 7)])
+def test_few_work_items_and_more_than_384(Hq, Hkv, N, sink, window, block, stride, D):
+    """Both instances for up to 384 work items, as a batch and packed: the bits of a batch of more than 384, which takes the instance
+    without a list, and whose rows are close to the oracle."""
+    items = Hq * ((N + 127) // 128)
+    many = 384 // items + 1
+    assert items <= 384 < many * items
+    q, k, v = (x.to(DEV) for x in lg_synth.prefill_inputs(1, Hq, Hkv, N, D, 18, torch.bfloat16))
+    qm, km, vm = (x.repeat(many, 1, 1, 1) for x in (q, k, v))
+    om, lm = torch.empty_like(qm), torch.empty(many, Hq, N, dtype=torch.float32, device=DEV)
+    lg.lg_sparse_attn_fwd(qm, km, vm, om, lm, sink, window, block, stride)
+    for packed in (False, True):
+        out, lse = torch.full_like(q, float("nan")), torch.full((1, Hq, N), float("nan"), dtype=torch.float32, device=DEV)
+        if packed:
+            lg.lg_sparse_attn_fwd_varlen(q[0], k[0], v[0], out[0], lse[0], [0, N], sink, window, block, stride)
+        else:
+            lg.lg_sparse_attn_fwd(q, k, v, out, lse, sink, window, block, stride)
+        assert torch.equal(om, out.expand_as(om)) and torch.equal(lm, lse.expand_as(lm)), packed
+    rows = (max(0, N - 300), N)
+    wo, wl = O.fwd(f32np(q), f32np(k), f32np(v), sink, window, block, stride, rows=rows)
+    assert_close(f32np(om[many - 1:, :, rows[0]:]), wo[:, :, rows[0]:], TOL_OUT[torch.bfloat16], TOL_REL[torch.bfloat16], "out")
+    assert_close(f32np(lm[many - 1:, :, rows[0]:]), wl[:, :, rows[0]:], TOL_LSE[torch.bfloat16], None, "lse")
+
+
+@pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_sink_window_ragged_gqa(D, dtype):
     check_fwd(2, 4, 2, 700, D, 64, 200, dtype=dtype, seed=2)
