@@ -159,6 +159,17 @@ int lg_debug_bwd_kernel_ms(const void* q, const void* k, const void* v, const vo
                            int dtype, float scale, void* hip_stream, float* kernel_ms);
 
 /*
+ * Host-only: which kernels the backward of a shape takes.  cu_seqlens NULL: lg_sparse_attn_bwd; otherwise the first set of launches
+ * of lg_sparse_attn_bwd_varlen with the workspace that lg_sparse_attn_bwd_varlen_workspace_bytes asks for (B and N unused).  plan:
+ * HOST array of 8 entries = {1 if dq and dk/dv share a launch, dq's 256-row tiles of a head in the form with 64 rows per wave, those
+ * in the form with 32, dk/dv's key tiles of a head in the form with 64 keys per wave, those in the form with 32, sets of query heads
+ * and runs of query tiles that a key tile's window part is cut into, chunks of the column parts of lone column groups}.  float32:
+ * the first entry, the others 0.
+ */
+int lg_debug_bwd_plan(const int* cu_seqlens, int num_seqs, int B, int Hq, int Hkv, int N, int D,
+                      int sink, int window, int block, int stride, int dtype, int32_t* plan);
+
+/*
  * Prefill over a batch of sequences of DIFFERENT lengths, packed without padding (Section 4.3 measures
  * prefilling in a serving setting, where the requests of a batch differ in length; Section 3.2's
  * kernel applied per sequence).  Layout: the sequences lie one after the other along the token axis

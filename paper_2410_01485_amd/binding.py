@@ -83,6 +83,8 @@ def lib():
         L.lg_debug_decode_segments.restype = _i
         L.lg_debug_tile_walk.argtypes = [_i] * 7 + [_vp, _sz, ctypes.POINTER(_sz)]
         L.lg_debug_tile_walk.restype = _i
+        L.lg_debug_bwd_plan.argtypes = [ctypes.POINTER(_i)] + [_i] * 11 + [ctypes.POINTER(ctypes.c_int32)]
+        L.lg_debug_bwd_plan.restype = _i
         L.lg_debug_partial_tile_bits.argtypes = [_i] * 9 + [ctypes.POINTER(ctypes.c_uint32)]
         L.lg_debug_partial_tile_bits.restype = _i
         L.lg_debug_pattern_fields.argtypes = [_i] * 6 + [ctypes.POINTER(ctypes.c_int32)]
@@ -384,6 +386,16 @@ def lg_debug_tile_walk(N, sink, window, block, stride, transposed, row):
     if st != 0:
         raise LgError(st, "lg_debug_tile_walk")
     return order[:cnt.value]
+
+
+def lg_debug_bwd_plan(B, Hq, Hkv, N, D, sink, window, block=1, stride=0, dtype=1, cu_seqlens=None):
+    """Host-only: which kernels the backward of a shape takes, or of a pack's first set of launches (B and N then unused)."""
+    cu, n = (None, 0) if cu_seqlens is None else _cu_array(cu_seqlens)
+    plan = (ctypes.c_int32 * 8)()
+    st = lib().lg_debug_bwd_plan(cu, n, B, Hq, Hkv, N, D, sink, window, block, stride, dtype, plan)
+    if st != 0:
+        raise LgError(st, "lg_debug_bwd_plan")
+    return dict(zip(("shared", "dq_wide", "dq", "dkdv_wide", "dkdv", "heads_cut", "rows_cut", "lone"), plan))
 
 
 def lg_debug_decode_split_headdim(q, k_cache, v_cache, out, lse, N, sink, window, scale=0.0):

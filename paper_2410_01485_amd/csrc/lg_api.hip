@@ -300,6 +300,23 @@ int lg_sparse_attn_bwd_varlen(const void* q, const void* k, const void* v, const
   return LG_OK;
 }
 
+int lg_debug_bwd_plan(const int* cu_seqlens, int num_seqs, int B, int Hq, int Hkv, int N, int D,
+                      int sink, int window, int block, int stride, int dtype, int32_t* plan) {
+  if (!plan) return LG_ERR_NULL;
+  int total = 0, longest = N;
+  const int st = cu_seqlens ? check_varlen(cu_seqlens, num_seqs, Hq, Hkv, D, sink, window, block, stride, dtype, &total, &longest)
+                            : check_common(B, Hq, Hkv, N, D, sink, window, block, stride, dtype);
+  if (st != LG_OK) return st;
+  for (int x = 0; x < 8; ++x) plan[x] = 0;
+  if (longest == 0) return LG_OK;  // (only empty sequences)
+  const LgShape sh = make_shape(cu_seqlens ? 1 : B, Hq, Hkv, longest, D, 0.0f);
+  const LgMask m = cu_seqlens && dtype == LG_BF16 ? pack_pattern(total, sink, window, block, stride) : lg_make_mask(longest, sink, window, block, stride);
+  const size_t ws = cu_seqlens ? lg_sparse_attn_bwd_varlen_workspace_bytes(cu_seqlens, num_seqs, Hq, Hkv, D, sink, window, block, stride, dtype) : 0;
+  if (dtype == LG_F32) plan[0] = lg_bwd_f32_shares(sh, m);
+  else lg_bwd_bf16_plan(sh, m, cu_seqlens, num_seqs, ws, plan);
+  return LG_OK;
+}
+
 static int check_decode(int B, int Hq, int Hkv, int N, int D, int sink, int window, int block,
                         int stride, int dtype) {
   int st = check_common(B, Hq, Hkv, N, D, sink, window, block, stride, dtype);

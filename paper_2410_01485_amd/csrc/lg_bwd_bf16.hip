@@ -2600,6 +2600,16 @@ size_t lg_bwd_bf16_pack_workspace_bytes(const LgShape& sh, const LgMask& tmpl, c
   return need;
 }
 
+void lg_bwd_bf16_plan(const LgShape& sh, const LgMask& m, const int* cu_seqlens, int num_seqs, size_t ws_bytes, int32_t* plan) {
+  BwdLaunch a = {};
+  size_t bytes = 0;
+  if (!cu_seqlens) a = batch_launch(sh, m);
+  else (void)pack_launch(sh, m, cu_seqlens, num_seqs, 0, std::max(ws_bytes, BWD_PACK_BYTES), &a, &bytes);
+  const bool both = bwd_both(a);
+  const int p[8] = {both, a.qt_wide, a.qt_rest, both ? 0 : a.kt_wide, both ? a.kt_wide + a.kt_rest : a.kt_rest, a.cut.heads, a.cut.rows, a.lone};
+  std::copy(p, p + 8, plan);
+}
+
 hipError_t lg_launch_bwd_bf16(const void* q, const void* k, const void* v, const void* out, const float* lse,
                               const void* dout, void* dq, void* dk, void* dv, void* ws, const LgShape& sh,
                               const LgMask& m, hipStream_t s, hipEvent_t* ev) {

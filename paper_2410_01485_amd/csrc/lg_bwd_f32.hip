@@ -677,7 +677,10 @@ __global__ __launch_bounds__(BNT, 2) void bwd_both_f32_kernel(
 // 128 fills a CU's LDS (dk/dv alone: two): 4 x 4 heads, 502 tokens, 768 workgroups 77 : 83, 2 x 16/4, 578, 1408 94 : 100.  Which of
 // the two comes first: the one whose longest item takes longer, that is 3 : 2 in dq's tiles (2 heads of 64, 3000 tokens 176 with
 // dk/dv first; 8/2, 4096, window 512 169, dq first 214).
-constexpr long long f32_both(int D) { return D == 64 ? 4096 : 512; }
+bool f32_both(const LgShape& sh, const F32Parts& pt) {
+  const long long items = (long long)sh.B * sh.Hkv * ((long long)pt.nkt * pt.nsp + (long long)pt.ncand * pt.ncc);
+  return (long long)ceil_div(sh.N, 32) * sh.Hq * sh.B + items <= (sh.D == 64 ? 4096 : 512);
+}
 template <int D>
 hipError_t launch_bwd(const float* q, const float* k, const float* v, const float* out, const float* lse,
                       const float* dout, float* dq, float* dk, float* dv, void* ws, const LgShape& sh,
@@ -694,8 +697,7 @@ hipError_t launch_bwd(const float* q, const float* k, const float* v, const floa
   if (tl > 0x7fffffffLL - 8 || items > 0x7fffffffLL || ncnt > 0x7fffffffLL) return hipErrorInvalidValue;
   if (ev) (void)hipEventRecord(ev[0], s);
   const int nqt32 = ceil_div(sh.N, 32);
-  const long long total32 = (long long)nqt32 * sh.Hq * sh.B;
-  if (total32 + items <= f32_both(D)) {
+  if (f32_both(sh, pt)) {
     const int tiles = ceil_div(sh.N, 64);
     bwd_prep_f32_kernel<D><<<dim3((unsigned)(tiles * sh.Hq * sh.B)), 256, 0, s>>>(out, dout, delta, sh.N, m.ld, tiles, arrived, (int)ncnt);
     hipError_t e = hipGetLastError();
@@ -704,7 +706,7 @@ hipError_t launch_bwd(const float* q, const float* k, const float* v, const floa
       (void)hipEventRecord(ev[1], s);
       (void)hipEventRecord(ev[2], s);  // (dq and dk/dv: one figure)
     }
-    const int total = (int)total32, run = lg_run_length(m, total, sh.B * sh.Hkv, 8 * (sh.Hq / sh.Hkv), false);
+    const int total = nqt32 * sh.Hq * sh.B, run = lg_run_length(m, total, sh.B * sh.Hkv, 8 * (sh.Hq / sh.Hkv), false);
     const int nkv = (int)items, ndq = (int)lg_run_grid(total, run);
     const long long reach = (long long)m.wb * m.b + m.sink + (m.stride > 0 ? sh.N / m.stride : 0);
     const int tiles_dq = (int)((reach < sh.N ? reach : sh.N) / 64) + 1;
@@ -737,6 +739,8 @@ size_t lg_bwd_workspace_bytes(const LgShape& sh, const LgMask& m, int dtype) {
   if (dtype == LG_F32) return f32_parts(sh, m).end;
   return lg_bwd_bf16_workspace_bytes(sh, m);
 }
+
+bool lg_bwd_f32_shares(const LgShape& sh, const LgMask& m) { return f32_both(sh, f32_parts(sh, m)); }
 
 hipError_t lg_launch_bwd_f32(const float* q, const float* k, const float* v, const float* out,
                              const float* lse, const float* dout, float* dq, float* dk, float* dv,

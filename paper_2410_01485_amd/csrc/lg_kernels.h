@@ -84,6 +84,9 @@ bool lg_bwd_bf16_splits_columns(const LgMask& m, int D);
 // For the packed launch below; least: the most that any of its sequences needs by itself, with which it runs as well.
 size_t lg_bwd_bf16_pack_workspace_bytes(const LgShape& sh, const LgMask& tmpl, const int* cu_seqlens, int num_seqs,
                                         size_t least);
+// The kernels of a shape, or of the first set of launches of a pack (cu_seqlens), as lg_debug_bwd_plan tells them.
+void lg_bwd_bf16_plan(const LgShape& sh, const LgMask& m, const int* cu_seqlens, int num_seqs, size_t ws_bytes, int32_t* plan);
+bool lg_bwd_f32_shares(const LgShape& sh, const LgMask& m);
 // ev: NULL, or 4 events recorded before the set-up, before the dq kernel, before the dk/dv kernels and after the
 // last one (measurement aid).
 hipError_t lg_launch_bwd_f32(const float* q, const float* k, const float* v, const float* out,

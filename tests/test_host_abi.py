@@ -157,3 +157,22 @@ def test_float32_window_parts_of_growing_rows_are_cut(Hq, Hkv, N, D):
     rows = -(-Hq * N * 4 // 256) * 256
     assert lg.bwd_workspace_bytes(1, Hq, Hkv, N, D, 0, N, 1, 0, lg.LG_F32) >= rows + 4 * Hkv * N * D * 4
     assert lg.bwd_workspace_bytes(1, Hq, Hkv, N, D, 0, 64, 1, 0, lg.LG_F32) == rows
+
+
+def test_bwd_plan():
+    """Which kernels a backward takes, as the host decides it: a launch for both up to 1536 workgroups (float32: 512), else the
+    64-keys form for windows of 16 tiles; a pack's first set of launches; errors."""
+    pat = (64, 1024, 1, 0)
+    one, many = (lg.lg_debug_bwd_plan(B, 2, 2, 3001, 128, *pat) for B in (1, 40))
+    assert one == dict(shared=1, dq_wide=0, dq=12, dkdv_wide=0, dkdv=12, heads_cut=1, rows_cut=1, lone=one["lone"]) and one["lone"] > 0
+    assert many == dict(one, shared=0, dkdv_wide=12, dkdv=0)
+    assert lg.lg_debug_bwd_plan(1, 1, 1, 300, 64, *pat, dtype=lg.LG_F32)["shared"] == 1
+    assert not any(lg.lg_debug_bwd_plan(8, 8, 8, 3001, 64, *pat, dtype=lg.LG_F32).values())
+    assert lg.lg_debug_bwd_plan(1, 2, 2, 0, 128, *pat, cu_seqlens=[0, 3001]) == one
+    assert lg.lg_debug_bwd_plan(1, 2, 2, 0, 128, *pat, cu_seqlens=[0, 0, 3001, 3001]) == one
+    assert not any(lg.lg_debug_bwd_plan(1, 2, 2, 0, 128, *pat, cu_seqlens=[0, 0]).values())
+    for bad in ((1, 3, 2, 300, 128, *pat), (1, 2, 2, 300, 96, *pat), (1, 2, 2, 0, 128, *pat)):
+        with pytest.raises(lg.LgError):
+            lg.lg_debug_bwd_plan(*bad)
+    with pytest.raises(lg.LgError):
+        lg.lg_debug_bwd_plan(1, 2, 2, 0, 128, *pat, cu_seqlens=[0, 5, 3])
