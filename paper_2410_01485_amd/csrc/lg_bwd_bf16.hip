@@ -2351,9 +2351,7 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
   wk.lonepart = Hq == Hkv ? (float*)(w + l.lonepart) : nullptr;
   wk.nlone_all = nlone;
   wk.arrived = arrived;
-  // heads innermost also where a CU gets few items and every XCD whole heads: head by head, CUs 0, 8, .. of an XCD
-  // would get the longest items of several heads, CUs 7, 15, .. the shortest
-  wk.by_tile = packed || nparts > 1 || (nbh % 8 == 0 && (long long)(a.kt_wide + a.kt_rest) * nbh <= 8 * CUS);
+  wk.by_tile = packed || nparts > 1 || lg_dkdv_by_tile(m, nbh, (long long)(a.kt_wide + a.kt_rest) * nbh, both);
   wk.heads_cut = a.cut.heads;
   wk.rows_cut = a.cut.rows;
   wk.parts = (float*)(w + l.parts);

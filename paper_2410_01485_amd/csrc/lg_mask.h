@@ -157,6 +157,18 @@ LG_HD int lg_run_length(const LgMask& m, int total, int heads, int few, bool var
 }
 LG_HD long long lg_run_grid(int total, int run) { return ((long long)total + 8LL * run - 1) / (8LL * run) * (8LL * run); }
 
+// bf16 dk/dv: whether a launch lists its key tiles with the heads innermost and not in runs of a head.
+//   Where a CU gets few items and every XCD whole heads: head by head, CUs 0, 8, .. of an XCD would get the longest items of several
+// heads, CUs 7, 15, .. the shortest.
+//   Where the hardware deals them (shared with dq, that is; the 64-keys form has a queue), rows grow along the sequence and XCDs do not
+// get whole heads: runs of 8 tiles give the longest of every head to one XCD where a head has about 64 tiles, or 128, .., twice its
+// share.  Backward of causal heads of 128, us, launches of their own : shared, in runs : heads innermost: 4 heads, 16384 tokens
+// 1212 : 1310 : 906, 2, 48000 3960 : 4295 : 3795, 3, 13989, window 4663 412 : 376 : 326; of 64: 3 x 3, 4096 186 : 130 : 107; 93 shapes
+// of up to 16 heads 1.030 of runs (geometric mean), 0.992 the least.
+inline bool lg_dkdv_by_tile(const LgMask& m, int heads, long long items, bool shared) {
+  return (heads % 8 == 0 && items <= 8 * 256) || (shared && !lg_even_runs(m, heads, false));
+}
+
 // Runs of the bf16 kernels that the hardware deals their items (not a queue).  Where rows grow the runs of all heads take
 // turns, longest rows first: head by head the longest rows of the last head start when the others are nearly done and end
 // the launch alone, and a dozen long runs leave some XCDs twice the work of others.  Full causal, forward: 3 heads of 64,

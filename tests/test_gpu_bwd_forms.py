@@ -75,6 +75,12 @@ def test_dkdv_in_32_key_form(Hq, Hkv, N, D, sink, window, block, stride):
     assert plan["dkdv"] == -(-N // (256 if D == 128 else 128)) and plan["dkdv_wide"] == 0
 
 
+@pytest.mark.parametrize("H,N,D,window", [(3, 4100, 128, 4100), (2, 2300, 64, 2300), (5, 1290, 128, 600), (1, 700, 64, 700)])
+def test_growing_rows_of_few_heads(H, N, D, window):
+    """dk/dv's key tiles with the heads innermost beside dq, and in runs of a head apart."""
+    check_apart_and_shared(H, H, N, D, (0, window, 1, 0))
+
+
 @pytest.mark.parametrize("lens,Hq,Hkv,window,oracle_rows", [
     ([5000, 700, 9000], 14, 14, 4096, 1000),  # the longest takes dq with 64 rows per wave as well
     ([300, 1500, 6000, 1, 0, 257, 5000, 769], 24, 12, 1024, 400)])

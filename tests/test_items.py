@@ -221,3 +221,44 @@ int main() {
 def test_which_small_forwards_list_their_tiles(tmp_path):
     """Rows of a few tiles, and tiles that are live few and far between, are walked without a list."""
     run(tmp_path, LISTS, "-O1")
+
+
+SHARED = r"""
+#include <cstdio>
+#include <vector>
+#include "lg_mask.h"
+// B x heads, N, window, tile: dk/dv's items beside dq's, as the hardware deals them
+int main() {
+  const int shapes[][4] = {{4, 16384, 16384, 256}, {2, 48000, 48000, 256}, {3, 13989, 4663, 256}, {1, 65000, 65000, 256}, {4, 24000, 24000, 256},
+                           {9, 4096, 4096, 128}, {6, 5666, 1888, 128}, {8, 6000, 6000, 256}, {12, 5218, 5218, 128}, {5, 6000, 6000, 256}};
+  for (auto& s : shapes) {
+    const int heads = s[0], N = s[1], TK = s[3], tiles = (N + TK - 1) / TK, total = tiles * heads;
+    const LgMask m = lg_make_mask(N, 0, s[2], 1, 0);
+    const bool by_tile = lg_dkdv_by_tile(m, heads, total, true);
+    const int run = lg_run_length(m, total, heads, 8, false);
+    const long long grid = by_tile ? total : lg_run_grid(total, run);
+    std::vector<int> seen(total, 0);
+    double work[8] = {}, all = 0, longest = 0;
+    for (long long id = 0; id < grid; ++id) {
+      const int L = by_tile ? (int)(id % heads * tiles + id / heads) : lg_item_of((int)id, run);
+      if (L >= total) continue;
+      ++seen[L];
+      const int k0 = L % tiles * TK, last = k0 + TK - 1 + s[2] - 1, end = last < N - 1 ? last : N - 1;
+      const double steps = 4 + end / 64 - k0 / 64;
+      work[id & 7] += steps;
+      all += steps;
+      longest = steps > longest ? steps : longest;
+    }
+    for (int x : seen)
+      if (x != 1) return 2;
+    for (double x : work)
+      if (x > 1.1 * all / 8 + longest) { std::printf("%d heads, %d tokens: an XCD has %.0f of %.0f steps\n", heads, N, x, all / 8); return 3; }
+  }
+  return 0;
+}
+"""
+
+
+def test_dkdv_beside_dq_gives_the_xcds_even_shares(tmp_path):
+    """In runs of 8 tiles one XCD had the longest tiles of all of 4 heads of 64 tiles."""
+    run(tmp_path, SHARED, "-O2")
