@@ -2268,22 +2268,37 @@ struct BwdLaunch {
 // its own then, over all of out and dO, which is got back up to 100 MB, of 64 up to 140: of 128, 129 (23 us), 2 x 32/16 heads, 3934
 // tokens, window 182 221 : 236; 85, 2 x 8, 10341, window 128 159 : 159; 72, 32/8, 4408, window 320, every 8th block 301 : 248; of 64,
 // 151, 32/16, 18467, window 192 214 : 223; 154, 4 x 64/8, 2349, causal 674 : 682; 107, 32/8, 13032, window 2930 986 : 954.
+// Nor, of 128, where dq's rows are far longer than dk/dv's (strided columns, long sinks) and its items of 128 rows would have a CU
+// each, or, with strided columns, half of them short rows beside: two by two they share one, and a tile takes about 0.4 us more; what
+// there is of dk/dv to run beside them, 1.2 us a step, and the launch saved, 5, are less than that.  Every 2nd of 64-token blocks: 1
+// head, 18047 tokens, window 128 401 : 474, 1, 58287, window 1024 1720 : 1895, 3, 15993, window 512 (189 pairs) 494 : 526; every 4th: 2,
+// 16956, window 256 292 : 307; sink 2170, 2/1, 4340, window 200 78 : 81, but sink 3443, 8/4, 6887 (216 pairs) 1.13 times as fast
+// shared.  The most that the rule costs: 4/1, every 4th block, 9776, window 256 218 : 215.
 int both_dq_items(const BwdLaunch& a) { return (a.D == 128 ? 1 : 2) * a.qt_rest * a.Hq * a.B; }
-bool bwd_both(const BwdLaunch& a) {
+struct Reach {
+  int tiles, steps;  // of dq's longest rows, of dk/dv's window parts
+};
+Reach bwd_reach(const BwdLaunch& a) {
+  const LgMask& m = a.m;
+  const int N = a.setup.n > 0 ? a.setup.len[0] : m.N;  // (the longest)
+  const long long reach = (long long)m.wb * m.b, cols = m.sink + (m.stride > 0 ? N / m.stride : 0);
+  return {(int)(std::min<long long>(N, reach + cols) / 64) + 1, (int)(std::min<long long>(N, reach + btk_of(a.D)) / 64) + 1};
+}
+bool may_share(const BwdLaunch& a) {  // (however the window parts are cut)
   const double delta = 4.0 * a.size.rows * a.B * a.Hq * a.D;  // bytes of out and dO
-  if (delta > (a.D == 128 ? 101e6 : 140e6)) return false;
+  if (a.qt_wide > 0 || delta > (a.D == 128 ? 101e6 : 140e6)) return false;
+  const Reach r = bwd_reach(a);
+  return !(a.D == 128 && both_dq_items(a) <= (a.m.stride > 0 ? 240 : 128) && r.tiles > 3 * r.steps + 13);
+}
+bool bwd_both(const BwdLaunch& a) {
   const long long kv = (long long)(a.kt_wide + a.kt_rest) * a.Hkv * a.B * a.cut.heads * a.cut.rows;
-  return a.qt_wide == 0 && both_dq_items(a) + kv <= (a.D == 64 ? 8192 : 1536);
+  return may_share(a) && both_dq_items(a) + kv <= (a.D == 64 ? 8192 : 1536);
 }
 // Whether dq's items come first: those that take longer, by the products of a wave in a tile (3) and a step (4).  8/4 heads of 64, 8
 // packed of up to 2186 tokens, causal, dq first 62, dk/dv first 68; 32/16, 8 of up to 1285, window 813 119, 94.
 bool both_dq_first(const BwdLaunch& a) {
-  const LgMask& m = a.m;
-  const int N = a.setup.n > 0 ? a.setup.len[0] : m.N;  // (the longest)
-  const long long reach = (long long)m.wb * m.b, cols = m.sink + (m.stride > 0 ? N / m.stride : 0);
-  const int tiles = (int)(std::min<long long>(N, reach + cols) / 64) + 1;
-  const int steps = (int)(std::min<long long>(N, reach + btk_of(a.D)) / 64) + 1;
-  return 3 * tiles > 4 * ((steps + a.cut.rows - 1) / a.cut.rows) * (a.Hq / a.Hkv / a.cut.heads);
+  const Reach r = bwd_reach(a);
+  return 3 * r.tiles > 4 * ((r.steps + a.cut.rows - 1) / a.cut.rows) * (a.Hq / a.Hkv / a.cut.heads);
 }
 
 hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv, const uint16_t* uo, const float* lse,
@@ -2497,7 +2512,7 @@ BwdLaunch batch_launch(const LgShape& sh, const LgMask& m) {
     double steps = 0;
     int longest = 0;
     window_steps(m, a.setup.btk, &steps, &longest);
-    a.cut = choose_cut(sh.D, sh.Hq / sh.Hkv, sh.B * sh.Hkv, a.size.ktiles, steps, longest, MOST_PARTS, a.qt_wide > 0 ? -1 : both_dq_items(a));
+    a.cut = choose_cut(sh.D, sh.Hq / sh.Hkv, sh.B * sh.Hkv, a.size.ktiles, steps, longest, MOST_PARTS, may_share(a) ? both_dq_items(a) : -1);
   }
   return a;
 }
@@ -2568,7 +2583,7 @@ int pack_launch(const LgShape& sh, const LgMask& tmpl, const int* cu_seqlens, in
     for (int y = 0; y < n; ++y) window_steps(lg_mask_for_length(tmpl, seq[y].len), a.setup.btk, &steps, &longest);
     const size_t tile = (size_t)sh.Hkv * a.size.ktiles * (a.setup.btk * 2 * sizeof(float)) * sh.D, used = end(a.size);
     a.cut = choose_cut(sh.D, sh.Hq / sh.Hkv, sh.Hkv, a.size.ktiles, steps, longest,
-                       n == 1 ? MOST_PARTS : used < budget ? (budget - used) / tile : 0, a.qt_wide > 0 ? -1 : both_dq_items(a));
+                       n == 1 ? MOST_PARTS : used < budget ? (budget - used) / tile : 0, may_share(a) ? both_dq_items(a) : -1);
   }
   *bytes = end(a.size);
   return x;
