@@ -2167,10 +2167,16 @@ struct Cut {
 // with groups, all cuts timed: the former rule's were 5.8 % from the best one (geometric mean), these 2.4.  Backward in us: 32/8
 // heads, 1807 tokens, window 252 89.0 -> 79.9, 2 x 32/8, 370 43.1 -> 36.8, 4 x 16/2, 1786, causal 222 -> 209, 2 packed of up to 483,
 // 64/8 64.4 -> 59.4; the least: 2/1, 1240, every 8th block 54.0 -> 55.6.  (Head dim 64: 5.2 % with the former rule, 6.0 with the best
-// of this form.)
+// of this form.)  Parts of more than 200 query tiles, or of more than 64 with more than two work items per CU, outlast the others
+// where they start late: half an average one is added to the rounds.  Without that and with it (and launches of their own): 16/8
+// heads, 5529 tokens, window 4096 419, 398 (398), 4/1, 24000, causal 1936, 1821 (1835), 2/1, 48450, causal 3891, 3723 (3714); for all
+// parts of more than 64 4/2, 16450, window 4096 would go from 418 to 466.  375 shapes with groups or strided columns are 1.317 times as
+// fast as with launches of their own (geometric mean; without it 1.316, with the best cuts 1.355); slower are 9/3, 6407, window 500
+// 96 : 99, 16/8, 5529, causal 426 : 437, 7450, window 1500 342 : 351, 4/2, 24200, causal 1844 : 1860.
 Cut choose_cut(int D, int G, int nbh, size_t tiles, double steps, int longest, size_t most, long long ndq) {
   const double items = (double)tiles * nbh;
   const bool shared = D == 128 && ndq >= 0 && ndq + items <= 3 * CUS;
+  const bool late = shared && (longest > 200 || (longest > 64 && ndq + items > 2 * CUS));  // items that start late end the launch alone
   const double each1 = shared ? 2.0 : D == 128 ? 3.0 : 1.5, each = shared ? 4.0 : D == 128 ? 3.0 : 1.0, start = D == 128 ? 8 : 3;
   Cut best = {1, 1};
   double least = 0;
@@ -2182,7 +2188,8 @@ Cut choose_cut(int D, int G, int nbh, size_t tiles, double steps, int longest, s
       const double one = (double)(G / heads) * ((longest + rows - 1) / rows) * each1 + (shared ? 4 : 8);
       const double all = (steps * G * nbh * each + items * parts * start) / CUS;
       const double fold = parts > 1 ? 5 + items * parts * (btk_of(D) * D * 8.0) / (shared ? 3e6 : 4e6) : 0;
-      const double t = (one > all ? one : all) + fold;
+      const double tail = late ? 0.5 * ((double)(G / heads) * steps / tiles / rows * each1 + 4) : 0;
+      const double t = (one > all + tail ? one : all + tail) + fold;
       const bool level = shared && t == least && parts <= best.heads * best.rows;  // (of two alike the one of more heads)
       if (parts == 1 || t < (shared ? 1.0 : 0.9) * least || level) {
         least = t;
@@ -2288,7 +2295,7 @@ bool may_share(const BwdLaunch& a) {  // (however the window parts are cut)
   const double delta = 4.0 * a.size.rows * a.B * a.Hq * a.D;  // bytes of out and dO
   if (a.qt_wide > 0 || delta > (a.D == 128 ? 101e6 : 140e6)) return false;
   const Reach r = bwd_reach(a);
-  return !(a.D == 128 && both_dq_items(a) <= (a.m.stride > 0 ? 240 : 128) && r.tiles > 3 * r.steps + 13);
+  return !(a.D == 128 && both_dq_items(a) <= (a.m.stride > 0 ? 255 : 128) && r.tiles > 3 * r.steps + 13);
 }
 bool bwd_both(const BwdLaunch& a) {
   const long long kv = (long long)(a.kt_wide + a.kt_rest) * a.Hkv * a.B * a.cut.heads * a.cut.rows;

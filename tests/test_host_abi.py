@@ -178,10 +178,19 @@ def test_bwd_plan():
         lg.lg_debug_bwd_plan(1, 2, 2, 0, 128, *pat, cu_seqlens=[0, 5, 3])
 
 
+@pytest.mark.parametrize("Hq,Hkv,N,window,least,most", [
+    (16, 8, 5529, 4096, 2, 4), (4, 1, 24000, 24000, 5, 8), (2, 1, 48450, 48450, 4, 6), (4, 2, 16450, 4096, 1, 2), (32, 8, 2012, 2012, 2, 4)])
+def test_long_window_parts_beside_dq_are_cut(Hq, Hkv, N, window, least, most):
+    """Head dim 128: left whole or in few parts, long window parts that start late end the launch alone (up to 6 % slower than with
+    launches of their own); not so where all start at once, and for shorter ones."""
+    plan = lg.lg_debug_bwd_plan(1, Hq, Hkv, N, 128, 0, window, 1, 0)
+    assert plan["shared"] and least <= plan["heads_cut"] * plan["rows_cut"] <= most
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,N,D,sink,window,block,stride,shared", [
     (1, 1, 1, 18047, 128, 64, 128, 64, 2, 0), (1, 3, 3, 15993, 128, 64, 512, 64, 2, 0), (1, 2, 2, 16956, 128, 64, 256, 64, 4, 0),
     (1, 2, 1, 4340, 128, 2170, 200, 1, 0, 0), (1, 1, 1, 18047, 64, 64, 128, 64, 2, 1), (1, 8, 4, 6887, 128, 3443, 200, 1, 0, 1),
-    (1, 1, 1, 1918, 128, 64, 512, 64, 2, 1), (2, 3, 3, 10565, 128, 64, 512, 64, 2, 1), (1, 1, 1, 18047, 128, 0, 18047, 1, 0, 1)])
+    (1, 1, 1, 1918, 128, 64, 512, 64, 2, 1), (2, 3, 3, 11565, 128, 64, 512, 64, 2, 1), (1, 1, 1, 18047, 128, 0, 18047, 1, 0, 1)])
 def test_dq_with_far_longer_rows_has_a_launch_of_its_own(B, Hq, Hkv, N, D, sink, window, block, stride, shared):
     """Head dim 128: rows of many strided columns or a long sink beside a short window, in few work items, were up to 15 % slower in the
     launch that dq and dk/dv share; as a pack of one the same."""
