@@ -126,9 +126,11 @@ int lg_sparse_attn_fwd(const void* q, const void* k, const void* v, void* out, f
  * PyTorch): with a strided pattern or Hq > Hkv the bf16 path adds partial dk/dv sums of sink
  * and strided-column keys into it with hardware float atomics; their order is not fixed, so
  * the last bits of those dk/dv rows can differ between runs (a sink + window call with
- * Hq == Hkv uses no atomics and is bit-reproducible; there dk and dv do not depend on B either, elsewhere
- * and on the float32 path the number of float32 partial sums of a key does).  out, lse and dq of a sequence have the same bits
- * in every batch, on both paths.
+ * Hq == Hkv uses no atomics and is bit-reproducible; there dk and dv do not depend on B either, and on the
+ * other heads of the call only in the sink's keys, whose float32 sums are cut more finely in calls of up to 16
+ * heads than in those of more: a layer whose heads are split over calls may differ there in the last bits; elsewhere
+ * and on the float32 path the number of float32 partial sums of a key depends on B, Hq and Hkv).  out, lse and dq of a
+ * sequence have the same bits in every batch, on both paths.
  */
 size_t lg_sparse_attn_bwd_workspace_bytes(int B, int Hq, int Hkv, int N, int D,
                                           int sink, int window, int block, int stride, int dtype);

@@ -111,3 +111,18 @@ def test_a_lone_strided_column(H, D, cut):
     assert plan["shared"] and plan["lone"] > 0 and (plan["heads_cut"] * plan["rows_cut"] > 1) == cut
     x = [t.to(DEV) for t in lg_synth.prefill_inputs(1, H, H, N, D, 92, torch.bfloat16, with_dout=True)]
     check_heads(x, run_fwd_bwd(*x, *pattern), 0, H, H, pattern, "lone column")
+
+
+@pytest.mark.parametrize("D,N", [(128, 12000), (64, 3000)])
+def test_heads_split_over_calls(D, N):
+    """Ungrouped heads, sink and window: in calls of 17 heads and of 16 and 1 of them dk and dv have the same bits but in the sink's
+    keys, whose sums are cut otherwise there, and the same bits there as well in calls of 8 and 8 of 16 heads."""
+    pattern = (16, 128, 1, 0)
+    x = [t.to(DEV) for t in lg_synth.prefill_inputs(1, 17, 17, N, D, 93, torch.bfloat16, with_dout=True)]
+    part = lambda a, b: run_fwd_bwd(*(t[:, a:b].contiguous() for t in x), *pattern)
+    whole, most, half, rest = part(0, 17), part(0, 16), part(0, 8), part(8, 16)
+    assert lg.lg_debug_bwd_plan(1, 17, 17, N, D, *pattern)["lone"] != lg.lg_debug_bwd_plan(1, 16, 16, N, D, *pattern)["lone"]
+    for y, z, a, b in zip(whole, most, half, rest):
+        assert torch.equal(z, torch.cat([a, b], dim=1))
+        assert torch.equal(y[:, :16, 16:], z[:, :, 16:])
+        assert_same_sums(y[:, :16, :16], z[:, :, :16], "sink keys")
