@@ -2312,7 +2312,10 @@ hipError_t launch_bwd(const uint16_t* uq, const uint16_t* uk, const uint16_t* uv
                       const uint16_t* ug, uint16_t* dq, uint16_t* dk, uint16_t* dv, void* ws, const BwdLaunch& in,
                       hipStream_t s, hipEvent_t* ev) {
   BwdLaunch a = in;
-  const bool both = bwd_both(a);
+  const size_t kv_bytes = (size_t)a.B * a.Hkv * a.m.ld * a.D * sizeof(uint16_t), lse_bytes = (size_t)a.B * a.Hq * a.m.ld * sizeof(float);
+  bool both = bwd_both(a);
+  for (const uint16_t* d : {dk, dv})
+    both = both && !lg_overlap(d, kv_bytes, uk, kv_bytes) && !lg_overlap(d, kv_bytes, uv, kv_bytes) && !lg_overlap(d, kv_bytes, lse, lse_bytes);
   if (both) {
     a.kt_rest += a.kt_wide;
     a.kt_wide = a.setup.nwide = 0;

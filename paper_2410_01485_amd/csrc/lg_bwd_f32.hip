@@ -697,7 +697,10 @@ hipError_t launch_bwd(const float* q, const float* k, const float* v, const floa
   if (tl > 0x7fffffffLL - 8 || items > 0x7fffffffLL || ncnt > 0x7fffffffLL) return hipErrorInvalidValue;
   if (ev) (void)hipEventRecord(ev[0], s);
   const int nqt32 = ceil_div(sh.N, 32);
-  if (f32_both(sh, pt)) {
+  const size_t kv_bytes = (size_t)heads * m.ld * D * sizeof(float);
+  bool both = f32_both(sh, pt);
+  for (const float* d : {dk, dv}) both = both && !lg_overlap(d, kv_bytes, k, kv_bytes) && !lg_overlap(d, kv_bytes, v, kv_bytes);
+  if (both) {
     const int tiles = ceil_div(sh.N, 64);
     bwd_prep_f32_kernel<D><<<dim3((unsigned)(tiles * sh.Hq * sh.B)), 256, 0, s>>>(out, dout, delta, sh.N, m.ld, tiles, arrived, (int)ncnt);
     hipError_t e = hipGetLastError();

@@ -84,6 +84,11 @@ bool lg_bwd_bf16_splits_columns(const LgMask& m, int D);
 // For the packed launch below; least: the most that any of its sequences needs by itself, with which it runs as well.
 size_t lg_bwd_bf16_pack_workspace_bytes(const LgShape& sh, const LgMask& tmpl, const int* cu_seqlens, int num_seqs,
                                         size_t least);
+// Do two ranges of bytes overlap?  dk and dv may be written over k and v (a key tile is read by the workgroup that writes it, and
+// before that): dq and dk/dv then keep launches of their own, one after the other.
+inline bool lg_overlap(const void* a, size_t na, const void* b, size_t nb) {
+  return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
 // The kernels of a shape, or of the first set of launches of a pack (cu_seqlens), as lg_debug_bwd_plan tells them.
 void lg_bwd_bf16_plan(const LgShape& sh, const LgMask& m, const int* cu_seqlens, int num_seqs, size_t ws_bytes, int32_t* plan);
 bool lg_bwd_f32_shares(const LgShape& sh, const LgMask& m);

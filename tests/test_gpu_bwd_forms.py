@@ -126,3 +126,29 @@ def test_heads_split_over_calls(D, N):
         assert torch.equal(z, torch.cat([a, b], dim=1))
         assert torch.equal(y[:, :16, 16:], z[:, :, 16:])
         assert_same_sums(y[:, :16, :16], z[:, :, :16], "sink keys")
+
+
+@pytest.mark.parametrize("Hq,Hkv,N,D,sink,window,block,stride,dtype", [
+    (4, 4, 1500, 128, 64, 300, 1, 0, torch.bfloat16), (3, 3, 900, 64, 0, 900, 1, 0, torch.bfloat16), (8, 2, 1300, 128, 16, 500, 1, 0, torch.bfloat16),
+    (2, 2, 2500, 64, 64, 64, 64, 4, torch.bfloat16), (2, 2, 700, 64, 16, 100, 1, 0, torch.float32), (2, 1, 500, 128, 0, 500, 1, 0, torch.float32)])
+def test_dk_dv_over_k_v(Hq, Hkv, N, D, sink, window, block, stride, dtype):
+    """Gradients written over the keys and values, either way round, of shapes whose dq, which reads all keys, shares a launch with
+    dk/dv otherwise."""
+    pattern = (sink, window, block, stride)
+    code = lg.LG_BF16 if dtype == torch.bfloat16 else lg.LG_F32
+    assert lg.lg_debug_bwd_plan(1, Hq, Hkv, N, D, *pattern, dtype=code)["shared"]
+    x = [t.to(DEV) for t in lg_synth.prefill_inputs(1, Hq, Hkv, N, D, 94, dtype, with_dout=True)]
+    want = run_fwd_bwd(*x, *pattern)
+    for crossed in (False, True):
+        q, k, v, g = (t.clone() for t in x)
+        out, lse, dq = torch.empty_like(q), torch.empty(1, Hq, N, device=DEV), torch.empty_like(q)
+        lg.lg_sparse_attn_fwd(q, k, v, out, lse, *pattern)
+        ws = torch.empty(lg.bwd_workspace_bytes(1, Hq, Hkv, N, D, *pattern, code), dtype=torch.uint8, device=DEV)
+        dk, dv = (v, k) if crossed else (k, v)
+        lg.lg_sparse_attn_bwd(q, k, v, out, lse, g, dq, dk, dv, ws, *pattern)
+        assert torch.equal(dq, want[0])
+        for y, z in ((dk, want[1]), (dv, want[2])):
+            if Hq == Hkv and stride == 0:
+                assert torch.equal(y, z), crossed
+            else:
+                assert_same_sums(y, z, "over the inputs")
