@@ -1,7 +1,8 @@
 // lg_bwd_bf16.hip — bf16 backward on the gfx950 matrix cores (paper Section 3.2: the
 // backward step skips masked key blocks just like the forward; Table 1 counts both).
 //
-// Two kernels (the first one also forms Delta).  Sink + window without GQA uses no atomics and is
+// Two kernels (the first one also forms Delta), or one for both where neither fills the GPU (bwd_both_bf16_kernel; the
+// set-up kernel then forms Delta).  Sink + window without GQA uses no atomics and is
 // bit-reproducible; strided patterns and GQA add float32 partial dk/dv sums of the column keys
 // with atomics (see the dk/dv section).  Tiles travel global -> LDS directly (row-major,
 // swizzled; lg_swz.h) and are read both with the contraction over dims (row reads) and with the
@@ -36,9 +37,9 @@
 // 461 -> 390 us; 512 590 -> 570, 830 -> 782; 2048 (64 rows per wave) 1545 -> 1493, 1910 -> 1875; 64 x 512 tokens 465 -> 380,
 // 630 -> 495 (some of that from the order of the tiles, lg_order).
 //
-// For head dim 128 and long windows (dq 32 or more tiles, and 384 or more of 256 rows; dk/dv 16) both kernels have a second form with 64 rows
-// (keys) per wave, one wave per SIMD and the accumulators in AGPRs (further down): every operand
-// read from LDS then feeds two matrix instructions.
+// For head dim 128 and long windows (dq 32 or more tiles, and 384 or more of 256 rows; dk/dv 16, in a launch of its own)
+// both kernels have a second form with 64 rows (keys) per wave, one wave per SIMD and the accumulators in AGPRs (further
+// down): every operand read from LDS then feeds two matrix instructions.
 #include <algorithm>
 
 #include "../../include/longgen_attn.h"
@@ -189,8 +190,9 @@ __device__ __forceinline__ void lg_load_pieces(const uint16_t* __restrict__ rows
     o[x] = *reinterpret_cast<const uint4*>(rows + (size_t)min(x * (256 / T::CPR) + tid / T::CPR, last) * D + tid % T::CPR * 8);
 }
 
-// Both dq kernels also form Delta_i = <dout_i, out_i> of their rows (lg_delta_rows, from the dout that they bring to LDS
-// anyway) and leave -Delta and -lse / scale in the workspace for the dk/dv kernels, which run after them on the same stream.
+// In launches of their own both dq kernels also form Delta_i = <dout_i, out_i> of their rows (lg_delta_rows, from the dout
+// that they bring to LDS anyway) and leave -Delta and -lse / scale in the workspace for the dk/dv kernels, which run after them on
+// the same stream.  Where they share a launch with dk/dv, the set-up kernel leaves both there before.
 // ------------------------------------------------------------------------- dq
 // Waves per SIMD and operands requested ahead, as the registers of so many waves allow (256 for D = 128, 168 for D = 64).
 template <int D>
@@ -1085,30 +1087,30 @@ __device__ __forceinline__ void dkdv_bf16_item(
         lg_store_shared1(sum + Slot::at(wave_s & 1, 1, db) + 64 * r, av[db][r]);
       }
   } else {
-  if (cid >= 0) {
-    const float* src = wk.colpart + ((size_t)bh * wk.ncol + it.col0 + cid) * Slot::FLOATS + lane;
+    if (cid >= 0) {
+      const float* src = wk.colpart + ((size_t)bh * wk.ncol + it.col0 + cid) * Slot::FLOATS + lane;
 #pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      __builtin_amdgcn_sched_barrier(0);  // (not all loads at once)
+      for (int db = 0; db < DB; ++db) {
+        __builtin_amdgcn_sched_barrier(0);  // (not all loads at once)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        ak[db][r] += lg_load_shared1(src + Slot::at(wave_s & 1, 0, db) + 64 * r);
-        av[db][r] += lg_load_shared1(src + Slot::at(wave_s & 1, 1, db) + 64 * r);
+        for (int r = 0; r < 16; ++r) {
+          ak[db][r] += lg_load_shared1(src + Slot::at(wave_s & 1, 0, db) + 64 * r);
+          av[db][r] += lg_load_shared1(src + Slot::at(wave_s & 1, 1, db) + 64 * r);
+        }
       }
     }
-  }
-  unsigned char* rows = smem + voff;  // (its V rows' place: no other wave reads them)
+    unsigned char* rows = smem + voff;  // (its V rows' place: no other wave reads them)
 #pragma unroll
-  for (int which = 0; which < 2; ++which) {
+    for (int which = 0; which < 2; ++which) {
 #pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      float a[16];
+      for (int db = 0; db < DB; ++db) {
+        float a[16];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) a[r] = which ? av[db][r] : ak[db][r];
-      lg_rows_put<D>(rows, lane, db, a, which ? 1.f : scale);
+        for (int r = 0; r < 16; ++r) a[r] = which ? av[db][r] : ak[db][r];
+        lg_rows_put<D>(rows, lane, db, a, which ? 1.f : scale);
+      }
+      lg_rows_write<D>(rows, lane, (which ? dv : dk) + kbase + (size_t)kw0 * D, N - kw0);
     }
-    lg_rows_write<D>(rows, lane, (which ? dv : dk) + kbase + (size_t)kw0 * D, N - kw0);
-  }
   }
   if (joint) {
     const int grp = lg_uniform(wk.col_list[it.col0]);
@@ -2271,8 +2273,9 @@ struct BwdLaunch {
 // this, of 64: 16 heads, 1117 tokens, causal 52 : 31, 8/4, 8 packed of up to 2186 89 : 62, 4 x 16, 997 58 : 46, 16/8, 1111, window
 // 128 50 : 44, 2 x 64/16, 7479, window 200 (9568 workgroups) 437 : 434; of 128: 8, 3249, causal 224 : 150, 4 x 8, 1111 97 : 63, 16/8,
 // 30 packed of up to 775 194 : 87, 1, 1098, causal 91 : 57, 16, 3707, window 186 93 : 90, 2 x 16/8, 8639, window 124 (1632) 254 : 241;
-// 8, 30 packed of up to 3991, window 704 (1952) 317 : 323, 32/16, 30 of up to 3428, window 448 (5952) 992 : 1065.  Delta is a pass of
-// its own then, over all of out and dO, which is got back up to 100 MB, of 64 up to 140: of 128, 129 (23 us), 2 x 32/16 heads, 3934
+// 8, 30 packed of up to 3991, window 704 (1952) 317 : 323, 32/16, 30 of up to 3428, window 448 (5952) 992 : 1065.  Rows may be long:
+// of 128, causal, 1, 49000 3073 : 2309, 4, 24000 1989 : 1805, 2, 48000 3904 : 3704, 1, 98000 8059 : 7855, window 4096 2, 24000 410 : 375.  Delta is a pass of
+// its own then, over all of out and dO, which is got back up to 101 MB, of 64 up to 140: of 128, 129 (23 us), 2 x 32/16 heads, 3934
 // tokens, window 182 221 : 236; 85, 2 x 8, 10341, window 128 159 : 159; 72, 32/8, 4408, window 320, every 8th block 301 : 248; of 64,
 // 151, 32/16, 18467, window 192 214 : 223; 154, 4 x 64/8, 2349, causal 674 : 682; 107, 32/8, 13032, window 2930 986 : 954.
 // Nor, of 128, where dq's rows are far longer than dk/dv's (strided columns, long sinks) and its items of 128 rows would have a CU

@@ -839,7 +839,7 @@ hipError_t launch_typed(const void* q, const void* kc, const void* vc, void* out
     pg.few = dtype == LG_F32 ? DEC_FULL : DEC_FEW;
     // a part per 1 / DEC_FULL of all keys, and one more per row for what is left over
     const long long most = std::min<long long>((long long)plan.rows * plan.splits, (long long)DEC_FULL + plan.rows);
-    grid = dim3((unsigned)(plan.splits == 1 ? plan.rows : most));
+    grid = dim3((unsigned)most);
   }
   typedef typename LgDecElem<T>::type E;
 #define LG_DECODE_LAUNCH(W, MODE, ...)                                                                               \
