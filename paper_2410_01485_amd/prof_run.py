@@ -1,7 +1,7 @@
 """Run one entry point on one benchmark workload a few times, for rocprofv3.
 
     rocprofv3 --kernel-trace --stats --output-format csv -d OUT -o NAME -- \
-        python3 paper_2410_01485_amd/prof_run.py {fwd|bwd|bwd_strided|decode|fwd_strided|fwd_gqa|copy|product|NAME} [reps]
+        python3 paper_2410_01485_amd/prof_run.py {fwd|bwd|bwd_strided|decode|fwd_strided|fwd_gqa|copy|product|SHAPE|NAME} [reps]
 
 fwd / bwd   : B1 H32 D128 N131072 bf16, sink 64 + window 4096 (the training-step workload)
 bwd_strided : B1 H32 D128 N131072 bf16, 64-token blocks: sink block, window 2048, every 64th block
@@ -12,6 +12,7 @@ copy        : a plain elementwise pass over 1 GiB (reads 2^30 bytes, writes 2^30
               that FETCH_SIZE / WRITE_SIZE counter readings are scaled by
 product     : torch's product of two 8192 x 8192 matrices, bf16 and float32: the rates that a large library
               product reaches on the card
+SHAPE       : B,Hq,Hkv,N,D,sink,window,block,stride: the bf16 backward of that shape
 NAME        : the case of that name in perf/cases.py, two sets of inputs in turn
 Inputs are filled on the device (values do not matter to a profile).
 """
@@ -45,22 +46,23 @@ def main():
             c = torch.empty_like(a)
             for _ in range(reps):
                 torch.mm(a, b, out=c)
-    elif what in ("fwd", "bwd", "bwd_strided", "fwd_strided", "fwd_gqa"):
-        Hq, Hkv, N, sink, window, block, stride = 32, 32, 131072, 64, 4096, 1, 0
+    elif what in ("fwd", "bwd", "bwd_strided", "fwd_strided", "fwd_gqa") or "," in what:
+        B, Hq, Hkv, N, D, sink, window, block, stride = 1, 32, 32, 131072, 128, 64, 4096, 1, 0
         if what == "fwd_strided":
             N, sink, window, block, stride = 32768, 64, 192, 64, 8
         if what == "fwd_gqa":
             Hq, Hkv = 64, 8
         if what == "bwd_strided":
             sink, window, block, stride = 64, 2048, 64, 64
-        D = 128
-        q, k, v = rnd(1, Hq, N, D), rnd(1, Hkv, N, D), rnd(1, Hkv, N, D)
+        if "," in what:
+            B, Hq, Hkv, N, D, sink, window, block, stride = (int(x) for x in what.split(","))
+        q, k, v = rnd(B, Hq, N, D), rnd(B, Hkv, N, D), rnd(B, Hkv, N, D)
         out = torch.empty_like(q)
-        lse = torch.empty(1, Hq, N, dtype=torch.float32, device=dev)
+        lse = torch.empty(B, Hq, N, dtype=torch.float32, device=dev)
         lg.lg_sparse_attn_fwd(q, k, v, out, lse, sink, window, block, stride)
-        if what in ("bwd", "bwd_strided"):
-            g = rnd(1, Hq, N, D)
-            ws = torch.empty(lg.bwd_workspace_bytes(1, Hq, Hkv, N, D, sink, window, block, stride, lg.LG_BF16),
+        if what in ("bwd", "bwd_strided") or "," in what:
+            g = rnd(B, Hq, N, D)
+            ws = torch.empty(lg.bwd_workspace_bytes(B, Hq, Hkv, N, D, sink, window, block, stride, lg.LG_BF16),
                              dtype=torch.uint8, device=dev)
             dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
             for _ in range(reps):
